@@ -34,9 +34,25 @@ int grow_events(tmps_stage* st, size_t n) {
     return TMPS_OK;
 }
 
+// What a worker issues in one go: a backward pass with its update, or the forward passes of `count` consecutive
+// micro-batches of one mini-batch that stand next to each other in the worker's order and read the same weights.
+// Their rows are consecutive in the stash, so they are one pass over `count` times the rows: the layers' kernels then
+// have the rows to fill the device and are launched once.  (A micro-batch of the GPT-2 configuration is 1024 rows: its
+// forward GEMMs ran at 260 TFLOP/s and were bound by launches and latency, 8192 rows reach 700; a mini-batch took 13.1 ms
+// pass by pass and takes 11.9 ms, the tiny fp32 MLP 283 and 185 us, VGG-16 1.47 and 1.26 ms, ResNet-50 8.9 and 8.3 ms.)
+// No dependency is added that could close a circle: whatever follows from one member and precedes a later one would
+// have to pass through a backward pass of this worker between the two.
+struct Node {
+    int stage, kind, b0, j0, count;
+    int32_t t, stage_version, net_version;   // of the first task
+    size_t first_task;                       // indices into the task list: first_task, and the members' own in `tasks`
+    std::vector<size_t> tasks;
+};
+
 struct RunCtx {
     bool vsync = false;              // forward passes read the weight version they are tagged with
     bool one_f1b = false;            // the comparison system: a backward pass per batch, on the weights of its forward pass
+    bool one_queue = false;          // all stages issue on one stream: its order stands for the events
     std::vector<long> base_version;  // every stage's version when the run started
     tmps_stage** stages;
     int K, N, M, mb, n_minibatches;
@@ -45,8 +61,11 @@ struct RunCtx {
     void** streams;
     float* losses_out;
     int32_t* log;
-    size_t asz, total_micro, n_fwd_ev;
+    const Task* tasks;
+    size_t total_micro, n_fwd_ev;
     std::vector<int> groups;
+    std::vector<std::vector<Node>> nodes;     // per stage, in the worker's order
+    std::vector<size_t> last_of;              // [stage * total_micro + q]: the last micro-batch of the pass that forwards q
     std::vector<std::atomic<unsigned char>> recorded;
     std::atomic<int> err{TMPS_OK};
     char err_text[512];
@@ -63,6 +82,7 @@ struct RunCtx {
 
     // Block until the producer thread has recorded event e (or a thread failed), then make stream s wait for it.
     int wait_for(size_t e, hipStream_t s) {
+        if (one_queue) return TMPS_OK;
         while (!recorded[e].load(std::memory_order_acquire)) {
             if (err.load(std::memory_order_relaxed) != TMPS_OK) return TMPS_EINVAL;
             std::this_thread::yield();
@@ -72,9 +92,25 @@ struct RunCtx {
         return TMPS_OK;
     }
     int record(size_t e, hipStream_t s) {
-        TMPS_HIP(hipEventRecord(event(e), s));
+        if (!one_queue) TMPS_HIP(hipEventRecord(event(e), s));
         recorded[e].store(1, std::memory_order_release);
         return TMPS_OK;
+    }
+    // The events that node n waits for.
+    template <class F> void for_each_dependency(const Node& n, F&& f) const {
+        if (n.kind == kFwd) {
+            if (n.stage == 0) return;
+            const size_t q0 = (size_t)n.b0 * N + n.j0;
+            for (size_t q = q0; q < q0 + n.count;) {
+                const size_t last = last_of[(size_t)(n.stage - 1) * total_micro + q];
+                f(fwd_ev(n.stage - 1, last));
+                q = last + 1;
+            }
+        } else {
+            if (n.stage < K - 1) f(bwd_ev(n.stage + 1, n.b0));
+            // the worker below must have consumed what the boundary-gradient buffer held two mini-batches ago
+            if (n.stage > 0 && n.b0 >= 2) f(bwd_ev(n.stage - 1, n.b0 - 2));
+        }
     }
     void set_error(int rc) {
         while (err_lock.test_and_set(std::memory_order_acquire)) {}
@@ -87,71 +123,105 @@ struct RunCtx {
     }
 };
 
-// Issue one task on its stage's stream.
-int issue(RunCtx& c, const Task& k, size_t ti) {
-    tmps_stage* st = c.stages[k.stage];
-    hipStream_t s = (hipStream_t)c.streams[k.stage];
-    const int b0 = k.b - 1, N = c.N, K = c.K;
+// Issue one node on its stage's stream.
+int issue(RunCtx& c, const Node& n) {
+    tmps_stage* st = c.stages[n.stage];
+    hipStream_t s = (hipStream_t)(c.one_queue ? c.streams[0] : c.streams[n.stage]);
+    const int b0 = n.b0, N = c.N, K = c.K;
     if (c.log) {
-        int32_t* o = c.log + 7 * ti;
-        o[0] = k.t; o[1] = k.stage; o[2] = k.kind; o[3] = k.b; o[4] = k.j;
-        const int32_t live = (int32_t)(st->version - c.base_version[k.stage]);
-        if (c.one_f1b) {   // version the task reads (a backward pass: the one its forward pass read), version the worker is at
-            o[5] = k.kind == kFwd ? live : k.stage_version;
-            o[6] = live;
-        } else {
-            o[5] = live;
-            o[6] = k.net_version;
+        const int32_t live = (int32_t)(st->version - c.base_version[n.stage]);
+        for (size_t ti : n.tasks) {
+            const Task& k = c.tasks[ti];
+            int32_t* o = c.log + 7 * ti;
+            o[0] = k.t; o[1] = k.stage; o[2] = k.kind; o[3] = k.b; o[4] = k.j;
+            if (c.one_f1b) {   // version the task reads (a backward pass: the one its forward pass read), version the worker is at
+                o[5] = k.kind == kFwd ? live : k.stage_version;
+                o[6] = live;
+            } else {
+                o[5] = live;
+                o[6] = k.net_version;
+            }
         }
     }
-    const int group = b0 % c.groups[k.stage];
-    int rc;
-    if (k.kind == kFwd) {
-        const int j = k.j < 0 ? 0 : k.j;   // (the comparison system has no micro-batches: N = 1)
-        const size_t q = (size_t)b0 * N + j;
-        const int slot = group * N + j;
-        const void* x;
-        if (k.stage == 0) {
-            x = (const char*)c.inputs + ((size_t)b0 * c.M + (size_t)j * c.mb) * st->in_elems * st->in_esize;
-        } else {
-            x = tmps_stage_output_ptr(c.stages[k.stage - 1], (b0 % c.groups[k.stage - 1]) * N + j);
-            if ((rc = c.wait_for(c.fwd_ev(k.stage - 1, q), s)) != TMPS_OK) return rc;
-        }
-        const int32_t* lab = st->cfg.is_last ? c.labels + ((size_t)b0 * c.M + (size_t)j * c.mb) * st->label_rps : nullptr;
-        if (c.vsync)
-            rc = tmps_forward_micro_at(st, c.base_version[k.stage] + k.net_version, slot, x, nullptr, lab, nullptr, s);
-        else
-            rc = tmps_forward_micro(st, slot, x, nullptr, lab, nullptr, s);
-        if (rc != TMPS_OK) return rc;
-        if (k.stage < K - 1 && (rc = c.record(c.fwd_ev(k.stage, q), s)) != TMPS_OK) return rc;
-        if (st->cfg.is_last && j == N - 1 && c.losses_out) {
+    int rc = TMPS_OK;
+    c.for_each_dependency(n, [&](size_t e) {
+        if (rc == TMPS_OK) rc = c.wait_for(e, s);
+    });
+    if (rc != TMPS_OK) return rc;
+    const int group = b0 % c.groups[n.stage];
+    if (n.kind == kFwd) {
+        const size_t row = (size_t)b0 * c.M + (size_t)n.j0 * c.mb;
+        const int slot = group * N + n.j0;
+        const void* x = n.stage == 0 ? (const void*)((const char*)c.inputs + row * st->in_elems * st->in_esize)
+                                     : tmps_stage_output_ptr(c.stages[n.stage - 1], (b0 % c.groups[n.stage - 1]) * N + n.j0);
+        const int32_t* lab = st->cfg.is_last ? c.labels + row * st->label_rps : nullptr;
+        const long version = c.vsync ? c.base_version[n.stage] + n.net_version : st->version;
+        if ((rc = forward_run_at(st, version, slot, n.count, x, nullptr, lab, nullptr, s)) != TMPS_OK) return rc;
+        if (n.stage < K - 1 && (rc = c.record(c.fwd_ev(n.stage, (size_t)b0 * N + n.j0 + n.count - 1), s)) != TMPS_OK) return rc;
+        if (st->cfg.is_last && n.j0 + n.count == N && c.losses_out) {
             ProfileScope scope(kcReduce, s);
             const int rows = c.M * st->label_rps;
             TMPS_HIP(reduce_scaled_sum(stage_row_loss(st, group * N), rows, 1.0f / (float)rows, c.losses_out + b0, s));
         }
     } else {
-        const void* dy = nullptr;
-        if (k.stage < K - 1) {
-            dy = stage_dxout(c.stages[k.stage + 1], b0 & 1);
-            if ((rc = c.wait_for(c.bwd_ev(k.stage + 1, b0), s)) != TMPS_OK) return rc;
-        }
-        void* dx = nullptr;
-        if (k.stage > 0) {
-            dx = stage_dxout(st, b0 & 1);
-            // the worker below must have consumed what this buffer held two mini-batches ago
-            if (b0 >= 2 && (rc = c.wait_for(c.bwd_ev(k.stage - 1, b0 - 2), s)) != TMPS_OK) return rc;
-        }
+        const void* dy = n.stage < K - 1 ? stage_dxout(c.stages[n.stage + 1], b0 & 1) : nullptr;
+        void* dx = n.stage > 0 ? stage_dxout(st, b0 & 1) : nullptr;
         int slots[64];
         for (int j = 0; j < N; ++j) slots[j] = group * N + j;
         if (c.one_f1b)   // horizontal weight stashing: differentiate at the weights the forward pass read
-            rc = tmps_backward_at(st, c.base_version[k.stage] + k.stage_version, slots, N, dy, dx, s);
+            rc = tmps_backward_at(st, c.base_version[n.stage] + n.stage_version, slots, N, dy, dx, s);
         else
             rc = tmps_backward(st, slots, N, dy, dx, s);
         if (rc != TMPS_OK) return rc;
-        if ((rc = c.record(c.bwd_ev(k.stage, b0), s)) != TMPS_OK) return rc;
+        if ((rc = c.record(c.bwd_ev(n.stage, b0), s)) != TMPS_OK) return rc;
         if ((rc = tmps_update(st, s)) != TMPS_OK) return rc;
     }
     return TMPS_OK;
+}
+
+// Nodes of every stage in the worker's order, and which node forwards which micro-batch.
+void build_nodes(RunCtx& c, const std::vector<Task>& tasks) {
+    c.nodes.assign(c.K, {});
+    c.last_of.assign((size_t)c.K * c.total_micro, 0);
+    for (size_t i = 0; i < tasks.size(); ++i) {
+        const Task& k = tasks[i];
+        std::vector<Node>& mine = c.nodes[k.stage];
+        const int j = k.j < 0 ? 0 : k.j;   // (the comparison system has no micro-batches: N = 1)
+        if (k.kind == kFwd && !mine.empty()) {
+            Node& p = mine.back();
+            if (p.kind == kFwd && p.b0 == k.b - 1 && p.j0 + p.count == j && p.count < c.stages[k.stage]->max_run &&
+                (!c.vsync || p.net_version == k.net_version)) {
+                ++p.count;
+                p.tasks.push_back(i);
+                continue;
+            }
+        }
+        mine.push_back(Node{k.stage, k.kind, k.b - 1, j, 1, k.t, k.stage_version, k.net_version, i, {i}});
+    }
+    for (int s = 0; s < c.K; ++s)
+        for (const Node& n : c.nodes[s])
+            if (n.kind == kFwd)
+                for (int j = 0; j < n.count; ++j)
+                    c.last_of[(size_t)s * c.total_micro + (size_t)n.b0 * c.N + n.j0 + j] = (size_t)n.b0 * c.N + n.j0 + n.count - 1;
+}
+
+// From one host thread: every node after the nodes it depends on, otherwise in the order of the schedule's time-points.
+int issue_all(RunCtx& c) {
+    std::vector<size_t> head(c.K, 0);
+    for (;;) {
+        const Node* best = nullptr;
+        for (int s = 0; s < c.K; ++s) {
+            if (head[s] == c.nodes[s].size()) continue;
+            const Node& n = c.nodes[s][head[s]];
+            bool ready = true;
+            c.for_each_dependency(n, [&](size_t e) { ready = ready && c.recorded[e].load(std::memory_order_relaxed); });
+            if (ready && (!best || n.first_task < best->first_task)) best = &n;
+        }
+        if (!best) return TMPS_OK;   // (all issued: a node whose predecessors are issued is always there before that)
+        const int rc = issue(c, *best);
+        if (rc != TMPS_OK) return rc;
+        ++head[best->stage];
+    }
 }
 
 }  // namespace
@@ -196,7 +266,6 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
     c.vsync = vsync;
     c.one_f1b = one_f1b;
     for (int s = 0; s < K; ++s) c.base_version.push_back(stages[s]->version);
-    c.asz = stages[0]->asz;
     c.total_micro = (size_t)n_minibatches * N;
     c.n_fwd_ev = (size_t)(K - 1) * c.total_micro;
     c.groups.resize(K);
@@ -209,12 +278,13 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
     c.recorded = std::vector<std::atomic<unsigned char>>(n_events);
     for (auto& f : c.recorded) f.store(0, std::memory_order_relaxed);
 
-    // per-stage task lists (indices into `tasks`, which is also the order of the version log)
-    std::vector<std::vector<size_t>> mine(K);
-    for (size_t i = 0; i < tasks.size(); ++i) mine[tasks[i].stage].push_back(i);
+    c.tasks = tasks.data();
+    build_nodes(c, tasks);
+    c.one_queue = true;
+    for (int s = 1; s < K; ++s) c.one_queue = c.one_queue && hip_streams[s] == hip_streams[0];
 
     const char* env = getenv("TMPS_ISSUE_THREADS");
-    const bool threaded = K > 1 && !(env && env[0] == '0');
+    const bool threaded = K > 1 && !(env && env[0] == '0') && !c.one_queue;
     const bool report = getenv("TMPS_REPORT_ISSUE_TIME") != nullptr;
     const auto t0 = std::chrono::steady_clock::now();
     if (threaded) {
@@ -228,9 +298,9 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
                     c.set_error(TMPS_EHIP);
                     return;
                 }
-                for (size_t i : mine[s]) {
+                for (const Node& n : c.nodes[s]) {
                     if (c.err.load(std::memory_order_relaxed) != TMPS_OK) return;
-                    int r = issue(c, tasks[i], i);
+                    int r = issue(c, n);
                     if (r != TMPS_OK) {
                         if (c.err.load() == TMPS_OK) c.set_error(r);
                         return;
@@ -239,13 +309,8 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
             });
         for (std::thread& t : workers) t.join();
     } else {
-        for (size_t i = 0; i < tasks.size(); ++i) {
-            int r = issue(c, tasks[i], i);
-            if (r != TMPS_OK) {
-                c.set_error(r);
-                break;
-            }
-        }
+        const int r = issue_all(c);
+        if (r != TMPS_OK) c.set_error(r);
     }
     const auto t1 = std::chrono::steady_clock::now();
     for (int s = 0; s < K; ++s) TMPS_HIP(hipStreamSynchronize((hipStream_t)hip_streams[s]));

@@ -54,6 +54,13 @@ static ConvShape conv_shape(const tmps_layer_desc& d, int B) {
     return c;
 }
 
+// The MFMA convolutions index positions with 24 bits and tensors with 31 (larger ones take an element-wise path): a
+// forward pass over several micro-batches stays within that.
+static bool conv_index_range_ok(const ConvShape& c) {
+    const int64_t pin = (int64_t)c.B * c.H * c.W, pout = (int64_t)c.B * c.Ho * c.Wo;
+    return pin < (1 << 24) && pout < (1 << 24) && pin * c.Cin < (int64_t(1) << 31) && pout * c.Cout < (int64_t(1) << 31);
+}
+
 int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, const tmps_stage_cfg* cfg) {
     if (!layers || !cfg || n_layers < 1) return fail(TMPS_EINVAL, "null layers/cfg or no layers");
     if (cfg->dtype != TMPS_F32 && cfg->dtype != TMPS_BF16_F32MASTER) return fail(TMPS_EINVAL, "unknown dtype %d", cfg->dtype);
@@ -66,6 +73,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
     st.asz = act_bytes(cfg->dtype);
     st.in_esize = st.asz;
     st.layers.clear();
+    st.max_run = cfg->n_micro;
     st.ws_fwd_bytes = 0;
     const int mb = cfg->micro_batch;
     const int M = mb * cfg->n_micro;
@@ -114,6 +122,8 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 L.ws_fwd_elems = gemm_workspace_elems(rf, d[1], d[0], 0);
                 L.ws_elems = std::max({L.ws_fwd_elems, gemm_workspace_elems(rb, d[0], d[1], 0),
                                        gemm_workspace_elems(d[1], d[0], rb, 1)});
+                for (int r = 2; r <= cfg->n_micro; ++r)   // (micro-batches forwarded together)
+                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems(r * rf, d[1], d[0], 0));
                 break;
             }
             case TMPS_CONV2D: {
@@ -122,6 +132,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 if (d[7] < 0) return fail(TMPS_EINVAL, "layer %d: negative padding", i);
                 if (L.act == 2) return fail(TMPS_EUNSUPPORTED, "layer %d: GELU on a convolution is not built", i);
                 ConvShape c = conv_shape(L.d, M);
+                while (st.max_run > 1 && !conv_index_range_ok(conv_shape(L.d, mb * st.max_run))) --st.max_run;
                 if (c.Ho < 1 || c.Wo < 1) return fail(TMPS_ESHAPE, "layer %d: empty convolution output", i);
                 L.in_elems = (int64_t)c.H * c.W * c.Cin;
                 L.out_elems = (int64_t)c.Ho * c.Wo * c.Cout;
@@ -131,6 +142,8 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 L.ws_elems = std::max({L.ws_fwd_elems,
                                        gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin, kd, 0),
                                        gemm_workspace_elems(c.Cout, kf, (int64_t)M * c.Ho * c.Wo, 1)});
+                for (int r = 2; r <= cfg->n_micro; ++r)
+                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)r * mb * c.Ho * c.Wo, c.Cout, kf, 0));
                 break;
             }
             case TMPS_MAXPOOL: {
@@ -457,33 +470,36 @@ static const void* layer_input(const tmps_stage* st, int li, const void* x0, int
 extern "C" int tmps_forward_micro(tmps_stage* st, int slot, const void* x, void* y, const int32_t* labels,
                                   float* loss_out, void* hip_stream) {
     if (!st) return fail(TMPS_EINVAL, "stage or x is null");
-    return forward_with_workspace(st, slot, x, y, labels, loss_out, hip_stream, reinterpret_cast<float*>(st->scratch + st->ws_off));
+    return forward_with_workspace(st, slot, 1, x, y, labels, loss_out, hip_stream, reinterpret_cast<float*>(st->scratch + st->ws_off));
 }
 
-int tmps::forward_with_workspace(tmps_stage* st, int slot, const void* x, void* y, const int32_t* labels, float* loss_out,
-                                 void* hip_stream, float* ws) {
+int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void* x, void* y, const int32_t* labels,
+                                 float* loss_out, void* hip_stream, float* ws) {
     if (!st || !x) return fail(TMPS_EINVAL, "stage or x is null");
     if (slot < 0 || slot >= st->cfg.max_stash) return fail(TMPS_ESLOT, "slot %d outside 0..%d", slot, st->cfg.max_stash - 1);
-    if (st->slot_used[slot]) return fail(TMPS_ESLOT, "slot %d is in use", slot);
+    if (slot % st->cfg.n_micro + count > st->cfg.n_micro) return fail(TMPS_ESLOT, "slots %d..%d are not of one mini-batch group", slot, slot + count - 1);
+    for (int j = 0; j < count; ++j)
+        if (st->slot_used[slot + j]) return fail(TMPS_ESLOT, "slot %d is in use", slot + j);
     if (st->cfg.is_last && !labels) return fail(TMPS_EINVAL, "the last stage needs labels");
     hipStream_t s = (hipStream_t)hip_stream;
-    const int mb = st->cfg.micro_batch;
+    const int mb = st->cfg.micro_batch * count;   // samples of this pass: rows of consecutive slots are consecutive
     const int dt = st->cfg.dtype;
-    const int64_t row0 = (int64_t)slot * mb;
+    const int64_t row0 = (int64_t)slot * st->cfg.micro_batch;
     const void* x0 = x;
     if (!st->cfg.borrow_input) {
         char* dst = st->stash + st->in_off + (size_t)row0 * st->in_elems * st->in_esize;
         TMPS_RUN(kcCopy, s, hipMemcpyAsync(dst, x, (size_t)mb * st->in_elems * st->in_esize, hipMemcpyDeviceToDevice, s));
         x0 = dst;
     }
-    st->slot_x[slot] = x;
+    const size_t x_step = (size_t)st->cfg.micro_batch * st->in_elems * st->in_esize;
+    for (int j = 0; j < count; ++j) st->slot_x[slot + j] = (const char*)x + j * x_step;
     if (st->use_graphs && st->cfg.is_last) {
         // a captured loss kernel reads its labels at a fixed address: the stage's own copy of this slot's labels
         int32_t* lab = reinterpret_cast<int32_t*>(st->stash + st->lab_off) + (size_t)row0 * st->label_rps;
         TMPS_RUN(kcCopy, s, hipMemcpyAsync(lab, labels, (size_t)mb * st->label_rps * 4, hipMemcpyDeviceToDevice, s));
         labels = lab;
     }
-    const tmps_stage::GraphKey key = {1, (uintptr_t)slot, (uintptr_t)x0, (uintptr_t)labels, (uintptr_t)loss_out, (uintptr_t)ws,
+    const tmps_stage::GraphKey key = {1 + 2 * (uintptr_t)count, (uintptr_t)slot, (uintptr_t)x0, (uintptr_t)labels, (uintptr_t)loss_out, (uintptr_t)ws,
                                       (uintptr_t)st->master, (uintptr_t)st->wcopy};
     const int rc = run_or_replay(st, key, s, [&]() -> int {
     for (size_t li = 0; li < st->layers.size(); ++li) {
@@ -576,7 +592,7 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, const void* x, void* 
         TMPS_RUN(kcCopy, s, hipMemcpyAsync(y, st->out_ptr(L, row0), (size_t)mb * L.out_elems * L.out_esize,
                                 hipMemcpyDeviceToDevice, s));
     }
-    st->slot_used[slot] = 1;
+    for (int j = 0; j < count; ++j) st->slot_used[slot + j] = 1;
     return TMPS_OK;
 }
 
@@ -895,10 +911,10 @@ extern "C" int tmps_backward_at(tmps_stage* st, long version, const int* slots, 
     return rc;
 }
 
-extern "C" int tmps_forward_micro_at(tmps_stage* st, long version, int slot, const void* x, void* y, const int32_t* labels,
-                                     float* loss_out, void* hip_stream) {
-    if (!st) return fail(TMPS_EINVAL, "stage is null");
-    if (version == st->version) return tmps_forward_micro(st, slot, x, y, labels, loss_out, hip_stream);
+int tmps::forward_run_at(tmps_stage* st, long version, int slot, int count, const void* x, void* y, const int32_t* labels,
+                         float* loss_out, void* hip_stream) {
+    float* const ws = reinterpret_cast<float*>(st->scratch + st->ws_off);
+    if (version == st->version) return forward_with_workspace(st, slot, count, x, y, labels, loss_out, hip_stream, ws);
     int found = -1;
     for (int k = 0; k < st->shadow_n; ++k)
         if (st->shadow_ver[k] == version) found = k;
@@ -912,8 +928,14 @@ extern "C" int tmps_forward_micro_at(tmps_stage* st, long version, int slot, con
     char* base = st->shadow + (size_t)found * st->param_bytes;
     st->master = reinterpret_cast<float*>(base);
     if (live_wcopy) st->wcopy = base + (size_t)st->P * 4;
-    const int rc = tmps_forward_micro(st, slot, x, y, labels, loss_out, hip_stream);
+    const int rc = forward_with_workspace(st, slot, count, x, y, labels, loss_out, hip_stream, ws);
     st->master = live_master;
     st->wcopy = live_wcopy;
     return rc;
+}
+
+extern "C" int tmps_forward_micro_at(tmps_stage* st, long version, int slot, const void* x, void* y, const int32_t* labels,
+                                     float* loss_out, void* hip_stream) {
+    if (!st) return fail(TMPS_EINVAL, "stage is null");
+    return forward_run_at(st, version, slot, 1, x, y, labels, loss_out, hip_stream);
 }

@@ -37,6 +37,7 @@ struct tmps_stage {
     size_t in_esize = 4;  // bytes per element of the stage input (int32 tokens in front of an embedding)
     int label_rps = 1;    // labels per sample on the last stage
     int n_gbuf = 2;       // gradient buffers in scratch
+    int max_run = 1;      // micro-batches that one forward pass can cover (tensors within the convolutions' index range)
     std::vector<int> readers;  // readers[t + 1] = number of layers that read result t (t = -1: the stage input)
     char* params = nullptr;
     char* state = nullptr;
@@ -103,7 +104,13 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
 void* stage_dxout(tmps_stage* st, int which);
 // Per-row losses of a slot on the last stage.
 float* stage_row_loss(tmps_stage* st, int slot);
-// tmps_forward_micro with the fp32 workspace of its contractions (st->ws_fwd_bytes) given by the caller.
-int forward_with_workspace(tmps_stage* st, int slot, const void* x, void* y, const int32_t* labels, float* loss_out,
-                           void* hip_stream, float* ws);
+// The forward passes of `count` micro-batches in the slots from `slot` on (of one mini-batch group, their inputs
+// consecutive in memory) as ONE pass over their rows with the current weights; `ws`: the fp32 workspace of its
+// contractions (st->ws_fwd_bytes for count = 1; the part of the scratch region is large enough for any count).  y and
+// loss_out belong to count = 1.
+int forward_with_workspace(tmps_stage* st, int slot, int count, const void* x, void* y, const int32_t* labels,
+                           float* loss_out, void* hip_stream, float* ws);
+// The same in the stage's own workspace on the weights as they were after `version` updates (tmps_forward_micro_at).
+int forward_run_at(tmps_stage* st, long version, int slot, int count, const void* x, void* y, const int32_t* labels,
+                   float* loss_out, void* hip_stream);
 }  // namespace tmps
