@@ -1,5 +1,5 @@
-// Main MFMA GEMM skeleton for gfx950 (bf16 in, fp32 accumulate), used by every contraction whose
-// operands can be fetched with aligned 16-byte loads.
+// Main MFMA GEMM skeleton for gfx950 (bf16 or fp32 in, fp32 accumulate): every contraction that does not run on the
+// persistent kernel of gemm3.hip.h.
 //
 //   C[m, n] = sum_k A(m, k) * B(n, k)
 //
@@ -12,14 +12,18 @@
 //                  k of its own row.  No operand is ever transposed in registers or in memory.
 // Dense forward (A, B k-contiguous), dense input gradient (B = W row-contiguous), dense weight
 // gradient (both row-contiguous) and the three implicit-GEMM forms of convolution are instances.
+// The descriptions say "8 consecutive" for bf16; fp32 chunks are 4 elements.  fp32 runs on v_mfma_f32_32x32x2_f32 (fp32
+// products and sums, 157 TFLOP/s): a k-tile is 32 k, the LDS layout and the data movement are the same byte for byte.
 //
-// 256 threads = 4 waves (2x2), wave tile (BM/2)x(BN/2) of 32x32x16 MFMA tiles, BK = 64.  The global
+// 256 threads = 4 waves (2x2), wave tile (BM/2)x(BN/2) of 32x32 MFMA tiles, k-tiles of 128 bytes.  The global
 // loads of the next D k-tiles are in flight in a register ring while the current tile is multiplied
 // (these contractions are short and few workgroups share a CU, so memory latency has to be hidden
 // inside the workgroup); LDS is double-buffered, one barrier per k-tile.
 // blockIdx.z selects a k-slice; with more than one slice the epilogue stores fp32 partial sums that a
 // finishing kernel reduces.
 #pragma once
+#include <type_traits>
+
 #include "gemm.hip.h"
 
 namespace tmps {
@@ -43,18 +47,43 @@ struct FastDiv {
     }
 };
 
-constexpr int kBK2 = 64;
+// A k-tile is 128 bytes of every row: 64 k in bf16, 32 in fp32; a chunk is 16 bytes: 8 or 4 elements.
+template <class T> struct ElemTile {
+    static constexpr int V = 16 / (int)sizeof(T), BK = 128 / (int)sizeof(T);
+};
 
 __device__ __forceinline__ uint4 zero16() { return make_uint4(0, 0, 0, 0); }
-__device__ __forceinline__ uint4 ld16(const bf16_t* p) { return *reinterpret_cast<const uint4*>(p); }
+template <class T> __device__ __forceinline__ uint4 ld16(const T* p) { return *reinterpret_cast<const uint4*>(p); }
 // Load that is ALWAYS issued: lanes whose chunk lies outside the operand read 16 zero bytes from a
 // dummy location instead.  With neither a branch around the load nor a select on its result, the
 // compiler counts the loads in flight exactly and a tile is waited for only when it is copied to LDS,
 // D tiles after it was requested.
 static __device__ __attribute__((aligned(16))) uint4 g_zero_chunk;  // zero-initialised, never written
-__device__ __forceinline__ uint4 ld16_if(const bf16_t* base, int64_t off, bool ok) {
-    const bf16_t* p = ok ? base + off : reinterpret_cast<const bf16_t*>(&g_zero_chunk);
+template <class T> __device__ __forceinline__ uint4 ld16_if(const T* base, int64_t off, bool ok) {
+    const T* p = ok ? base + off : reinterpret_cast<const T*>(&g_zero_chunk);
     return ld16(p);
+}
+// the same from an address that is aligned to an element only
+template <class T> __device__ __forceinline__ uint4 ld16u_if(const T* base, int64_t off, bool ok) {
+    const T* p = ok ? base + off : reinterpret_cast<const T*>(&g_zero_chunk);
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+// Drops the first `bytes` bytes of a chunk and fills up with zeros from behind.
+__device__ __forceinline__ uint4 chunk_drop(uint4 v, int bytes) {
+    uint64_t lo = v.x | ((uint64_t)v.y << 32), hi = v.z | ((uint64_t)v.w << 32);
+    if (bytes >= 8) {
+        lo = hi;
+        hi = 0;
+        bytes -= 8;
+    }
+    if (bytes >= 8) lo = 0;
+    else if (bytes > 0) {
+        lo = (lo >> (8 * bytes)) | (hi << (64 - 8 * bytes));
+        hi >>= 8 * bytes;
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
 // full-rate 24-bit multiply (both factors below 2^24, product below 2^31)
 __device__ __forceinline__ int mul24(int a, int b) { return __mul24(a, b); }
@@ -63,51 +92,110 @@ __device__ __forceinline__ int mul24(int a, int b) { return __mul24(a, b); }
 // Loaders.  A thread fetches a fixed set of 16-byte chunks of every k-tile; a loader is an iterator
 // over k-tiles, so that the k-loop needs no integer division and no 64-bit multiply:
 //   init_thread(ks, k_begin, col)  per-thread state for the first tile; col = the thread's chunk column
-//                                  (k offset col*8) for k-contiguous loaders, unused otherwise
+//                                  (k offset col*V) for k-contiguous loaders, unused otherwise
 //   init(ctx, row, col, k_begin)   per-chunk state.  k-contiguous: row = global row.  row-contiguous:
-//                                  row = first of 8 consecutive rows, col = k offset inside a tile.
+//                                  row = first of V consecutive rows, col = k offset inside a tile.
 //   load(ctx, ks, k_end)           the chunk of the current tile (zeros outside the operand); called once
 //                                  per tile and chunk, in order; may step per-chunk state
-//   next(ks)                       step the per-thread state to the next tile (k += 64)
+//   next(ks)                       step the per-thread state to the next tile (k += BK)
+//   settle(ctx, v, k, k_end)       only where kSettle: what remains to be done with a loaded chunk (whose first k is k, for
+//                                  k-contiguous loaders) before it goes to LDS
 // Element offsets are 32-bit: every tensor here has fewer than 2^31 elements.
 // ------------------------------------------------------------------------------------------
-struct DenseKC {
-    static constexpr bool kContig = true;
-    const bf16_t* p;
+template <class T_> struct DenseKC {
+    typedef T_ T;
+    static constexpr bool kContig = true, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* p;
     int rows, K;
     int64_t ld;
     struct KS { int k; };
     struct Ctx { int64_t roff; bool ok; };
-    __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int col) const { ks.k = k_begin + col * 8; }
+    __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int col) const { ks.k = k_begin + col * V; }
     __device__ __forceinline__ void init(Ctx& c, int row, int, int) const {
         c.ok = row < rows;
         c.roff = (int64_t)(c.ok ? row : 0) * ld;
     }
     __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
-        return ld16_if(p, c.roff + ks.k, c.ok && ks.k + 8 <= k_end);
+        return ld16_if(p, c.roff + ks.k, c.ok && ks.k + V <= k_end);
     }
-    __device__ __forceinline__ void next(KS& ks) const { ks.k += kBK2; }
+    __device__ __forceinline__ void next(KS& ks) const { ks.k += BK; }
 };
 
-struct DenseRC {
-    static constexpr bool kContig = false;
-    const bf16_t* p;  // element(row, k) = p[k*ld + row]
+template <class T_> struct DenseRC {
+    typedef T_ T;
+    static constexpr bool kContig = false, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* p;  // element(row, k) = p[k*ld + row]
     int rows, K;
     int64_t ld;
     struct KS { int kb; };
     struct Ctx { int64_t off; int kl; bool ok; };
     __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int) const { ks.kb = k_begin; }
     __device__ __forceinline__ void init(Ctx& c, int row0, int kl, int k_begin) const {
-        c.ok = row0 + 8 <= rows;
+        c.ok = row0 + V <= rows;
         c.kl = kl;
         c.off = (c.ok ? row0 : 0) + (int64_t)(k_begin + kl) * ld;
     }
     __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
         uint4 v = ld16_if(p, c.off, c.ok && ks.kb + c.kl < k_end);
-        c.off += kBK2 * ld;
+        c.off += BK * ld;
         return v;
     }
-    __device__ __forceinline__ void next(KS& ks) const { ks.kb += kBK2; }
+    __device__ __forceinline__ void next(KS& ks) const { ks.kb += BK; }
+};
+
+// The same two for matrices whose rows are not whole chunks or not 16-byte aligned (a 10-way or an odd-sized output
+// layer): chunks are fetched from element-aligned addresses, and the last chunk of a row is fetched so that it ENDS
+// with the row (nothing behind the matrix is read) and moved into place when it has arrived.  Rows (k-contiguous:
+// the k extent) hold at least one chunk.
+template <class T_> struct RaggedKC {
+    typedef T_ T;
+    static constexpr bool kContig = true, kSettle = true;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* p;
+    int rows, K;
+    int64_t ld;
+    struct KS { int k; };
+    struct Ctx { int64_t roff; bool ok; };
+    __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int col) const { ks.k = k_begin + col * V; }
+    __device__ __forceinline__ void init(Ctx& c, int row, int, int) const {
+        c.ok = row < rows;
+        c.roff = (int64_t)(c.ok ? row : 0) * ld;
+    }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+        return ld16u_if(p, c.roff + min(ks.k, k_end - V), c.ok && ks.k < k_end);
+    }
+    __device__ __forceinline__ void next(KS& ks) const { ks.k += BK; }
+    __device__ __forceinline__ uint4 settle(const Ctx&, uint4 v, int k, int k_end) const {
+        return k + V > k_end && k < k_end ? chunk_drop(v, (k + V - k_end) * (int)sizeof(T)) : v;
+    }
+};
+
+template <class T_> struct RaggedRC {
+    typedef T_ T;
+    static constexpr bool kContig = false, kSettle = true;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* p;
+    int rows, K;
+    int64_t ld;
+    struct KS { int kb; };
+    struct Ctx { int64_t off; int kl, drop; bool ok; };
+    __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int) const { ks.kb = k_begin; }
+    __device__ __forceinline__ void init(Ctx& c, int row0, int kl, int k_begin) const {
+        c.ok = row0 < rows;
+        c.kl = kl;
+        const int r = c.ok ? min(row0, rows - V) : 0;
+        c.drop = c.ok ? (row0 - r) * (int)sizeof(T) : 0;
+        c.off = r + (int64_t)(k_begin + kl) * ld;
+    }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+        uint4 v = ld16u_if(p, c.off, c.ok && ks.kb + c.kl < k_end);
+        c.off += BK * ld;
+        return v;
+    }
+    __device__ __forceinline__ void next(KS& ks) const { ks.kb += BK; }
+    __device__ __forceinline__ uint4 settle(const Ctx& c, uint4 v, int, int) const { return c.drop ? chunk_drop(v, c.drop) : v; }
 };
 
 struct ConvGeom2 {
@@ -116,16 +204,18 @@ struct ConvGeom2 {
 };
 
 // Forward A: row m = (n, ho, wo), k = (r, s, c) -> x[n, ho*stride + r - pad, wo*stride + s - pad, c].
-// Per thread: (r, s, c) of its chunk column, stepped by 64 channels per tile.
-struct ConvFwdA2 {
-    static constexpr bool kContig = true;
-    const bf16_t* x;
+// Per thread: (r, s, c) of its chunk column, stepped by BK channels per tile.
+template <class T_> struct ConvFwdA2 {
+    typedef T_ T;
+    static constexpr bool kContig = true, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* x;
     ConvGeom2 g;
     int rows, K;
     struct KS { int k, r, s, ch, koff; };
     struct Ctx { int base, h0, w0; bool ok; };
     __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int col) const {
-        ks.k = k_begin + col * 8;
+        ks.k = k_begin + col * V;
         uint32_t r, rem, s, ch;
         g.d_scin.divmod(ks.k, r, rem);
         g.d_cin.divmod(rem, s, ch);
@@ -143,12 +233,12 @@ struct ConvFwdA2 {
     }
     __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
         const int h = c.h0 + ks.r, w = c.w0 + ks.s;
-        const bool ok = c.ok && ks.k + 8 <= k_end && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
+        const bool ok = c.ok && ks.k + V <= k_end && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
         return ld16_if(x, c.base + ks.koff, ok);
     }
     __device__ __forceinline__ void next(KS& ks) const {
-        ks.k += kBK2;
-        ks.ch += kBK2;
+        ks.k += BK;
+        ks.ch += BK;
         while (ks.ch >= g.Cin) {
             ks.ch -= g.Cin;
             if (++ks.s == g.S) { ks.s = 0; ++ks.r; }
@@ -159,15 +249,17 @@ struct ConvFwdA2 {
 
 // Input-gradient A: row m = (n, h, w), k = (r, s, co) -> dy[n, (h+pad-r)/stride, (w+pad-s)/stride, co]
 // when both divisions are exact and in range.
-struct ConvDgradA2 {
-    static constexpr bool kContig = true;
-    const bf16_t* dy;
+template <class T_> struct ConvDgradA2 {
+    typedef T_ T;
+    static constexpr bool kContig = true, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* dy;
     ConvGeom2 g;
     int rows, K;
     struct KS { int k, r, s, co, kterm; };
     struct Ctx { int c0, hp, wp, nbase; bool ok; };
     __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int col) const {
-        ks.k = k_begin + col * 8;
+        ks.k = k_begin + col * V;
         uint32_t r, rem, s, co;
         g.d_scout.divmod(ks.k, r, rem);
         g.d_cout.divmod(rem, s, co);
@@ -185,7 +277,7 @@ struct ConvDgradA2 {
         c.c0 = c.nbase + (c.hp * g.Wo + c.wp) * g.Cout;  // stride 1: offset = c0 + kterm
     }
     __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
-        const bool in_k = c.ok && ks.k + 8 <= k_end;
+        const bool in_k = c.ok && ks.k + V <= k_end;
         const int hy = c.hp - ks.r, wy = c.wp - ks.s;
         if (g.stride == 1) {
             const bool ok = in_k && (unsigned)hy < (unsigned)g.Ho && (unsigned)wy < (unsigned)g.Wo;
@@ -198,8 +290,8 @@ struct ConvDgradA2 {
         return ld16_if(dy, c.nbase + ((int)ho * g.Wo + (int)wo) * g.Cout + ks.co, ok);
     }
     __device__ __forceinline__ void next(KS& ks) const {
-        ks.k += kBK2;
-        ks.co += kBK2;
+        ks.k += BK;
+        ks.co += BK;
         while (ks.co >= g.Cout) {
             ks.co -= g.Cout;
             if (++ks.s == g.S) { ks.s = 0; ++ks.r; }
@@ -208,12 +300,14 @@ struct ConvDgradA2 {
     }
 };
 
-// Input-gradient B: row n = ci (8 consecutive), k = (r, s, co) -> w[co, r, s, ci].
+// Input-gradient B: row n = ci (V consecutive), k = (r, s, co) -> w[co, r, s, ci].
 // Per thread: (r, s, co) of the tile's first k; a chunk adds its k offset (with carry when the tile
 // crosses a filter tap).
-struct ConvDgradB2 {
-    static constexpr bool kContig = false;
-    const bf16_t* w;
+template <class T_> struct ConvDgradB2 {
+    typedef T_ T;
+    static constexpr bool kContig = false, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* w;
     ConvGeom2 g;
     int rows, K;
     struct KS { int kb, r, s, co; };
@@ -226,7 +320,7 @@ struct ConvDgradB2 {
         ks.r = (int)r; ks.s = (int)s; ks.co = (int)co;
     }
     __device__ __forceinline__ void init(Ctx& c, int row0, int kl, int) const {
-        c.ok = row0 + 8 <= rows;
+        c.ok = row0 + V <= rows;
         c.ci0 = row0;
         c.kl = kl;
     }
@@ -241,8 +335,8 @@ struct ConvDgradB2 {
         return ld16_if(w, off, ok);
     }
     __device__ __forceinline__ void next(KS& ks) const {
-        ks.kb += kBK2;
-        ks.co += kBK2;
+        ks.kb += BK;
+        ks.co += BK;
         while (ks.co >= g.Cout) {
             ks.co -= g.Cout;
             if (++ks.s == g.S) { ks.s = 0; ++ks.r; }
@@ -250,21 +344,23 @@ struct ConvDgradB2 {
     }
 };
 
-// Weight-gradient B: row = (r, s, ci) (8 consecutive ci), k = m = (n, ho, wo)
+// Weight-gradient B: row = (r, s, ci) (V consecutive ci), k = m = (n, ho, wo)
 // -> x[n, ho*stride + r - pad, wo*stride + s - pad, ci].
-// Per chunk: (ho, wo) of its position and the element offset of that position, stepped by 64
+// Per chunk: (ho, wo) of its position and the element offset of that position, stepped by BK
 // positions per tile with precomputed carries.
-struct ConvWgradB2 {
-    static constexpr bool kContig = false;
-    const bf16_t* x;
+template <class T_> struct ConvWgradB2 {
+    typedef T_ T;
+    static constexpr bool kContig = false, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* x;
     ConvGeom2 g;
     int rows, K;
-    int step_wo, step_ho, step_n;  // 64 positions = step_n images + step_ho rows + step_wo columns
+    int step_wo, step_ho, step_n;  // BK positions = step_n images + step_ho rows + step_wo columns
     struct KS { int kb; };
     struct Ctx { int dr, ds, ci0, kl, ho, wo, n; bool ok; };
     __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int) const { ks.kb = k_begin; }
     __device__ __forceinline__ void init(Ctx& c, int row0, int kl, int k_begin) const {
-        c.ok = row0 + 8 <= rows;
+        c.ok = row0 + V <= rows;
         uint32_t r, rem, s, ci;
         g.d_scin.divmod(c.ok ? row0 : 0, r, rem);
         g.d_cin.divmod(rem, s, ci);
@@ -281,7 +377,7 @@ struct ConvWgradB2 {
         const int h = c.ho * g.stride + c.dr, w = c.wo * g.stride + c.ds;
         const bool ok = c.ok && ks.kb + c.kl < k_end && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
         uint4 v = ld16_if(x, mul24(mul24(mul24(c.n, g.H) + h, g.W) + w, g.Cin) + c.ci0, ok);
-        // advance this chunk's position by 64
+        // advance this chunk's position by BK
         c.wo += step_wo;
         c.ho += step_ho;
         c.n += step_n;
@@ -289,7 +385,7 @@ struct ConvWgradB2 {
         if (c.ho >= g.Ho) { c.ho -= g.Ho; ++c.n; }
         return v;
     }
-    __device__ __forceinline__ void next(KS& ks) const { ks.kb += kBK2; }
+    __device__ __forceinline__ void next(KS& ks) const { ks.kb += BK; }
 };
 
 // Input gradient of a convolution with stride 2, rows ordered by the PARITY of their position: row
@@ -329,9 +425,11 @@ struct ParityTaps {
     }
 };
 
-struct ConvDgradA2P {
-    static constexpr bool kContig = true;
-    const bf16_t* dy;
+template <class T_> struct ConvDgradA2P {
+    typedef T_ T;
+    static constexpr bool kContig = true, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* dy;
     ConvGeom2 g;
     int rows, K;
     ParityGeom p;
@@ -355,7 +453,7 @@ struct ConvDgradA2P {
         return (n * g.H + h) * g.W + w;
     }
     __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int col) const {
-        ks.k = k_begin + col * 8;
+        ks.k = k_begin + col * V;
         taps.locate(ks.k, g, ks.r, ks.s, ks.co);
     }
     __device__ __forceinline__ void init(Ctx& c, int m, int, int) const {
@@ -369,20 +467,22 @@ struct ConvDgradA2P {
     __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
         const int hy = c.hp - ks.r, wy = c.wp - ks.s;   // even for the taps of this class
         const int ho = hy >> 1, wo = wy >> 1;
-        const bool ok = c.ok && ks.k + 8 <= k_end && hy >= 0 && wy >= 0 && ho < g.Ho && wo < g.Wo;
+        const bool ok = c.ok && ks.k + V <= k_end && hy >= 0 && wy >= 0 && ho < g.Ho && wo < g.Wo;
         return ld16_if(dy, c.nbase + (ho * g.Wo + wo) * g.Cout + ks.co, ok);
     }
     __device__ __forceinline__ void next(KS& ks) const {
-        ks.k += kBK2;
-        ks.co += kBK2;
+        ks.k += BK;
+        ks.co += BK;
         taps.carry(ks.r, ks.s, ks.co, g);
     }
 };
 
-// The filter taps in the same order: row n = ci (8 consecutive), k = (r, s, co) of the tile's class -> w[co, r, s, ci].
-struct ConvDgradB2P {
-    static constexpr bool kContig = false;
-    const bf16_t* w;
+// The filter taps in the same order: row n = ci (V consecutive), k = (r, s, co) of the tile's class -> w[co, r, s, ci].
+template <class T_> struct ConvDgradB2P {
+    typedef T_ T;
+    static constexpr bool kContig = false, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* w;
     ConvGeom2 g;
     int rows, K;
     ParityGeom p;
@@ -395,7 +495,7 @@ struct ConvDgradB2P {
         taps.locate(k_begin, g, ks.r, ks.s, ks.co);
     }
     __device__ __forceinline__ void init(Ctx& c, int row0, int kl, int) const {
-        c.ok = row0 + 8 <= rows;
+        c.ok = row0 + V <= rows;
         c.ci0 = row0;
         c.kl = kl;
     }
@@ -407,10 +507,156 @@ struct ConvDgradB2P {
         return ld16_if(w, off, ok);
     }
     __device__ __forceinline__ void next(KS& ks) const {
-        ks.kb += kBK2;
-        ks.co += kBK2;
+        ks.kb += BK;
+        ks.co += BK;
         taps.carry(ks.r, ks.s, ks.co, g);
     }
+};
+
+// ------------------------------------------------------------------------------------------
+// Gathering loaders: chunks are put together element by element from a view that knows where (row, k) lies.  For
+// operands whose chunks are not runs of memory: convolutions over channel counts that are not whole chunks (an RGB image),
+// matrices with rows of less than a chunk.  A view has row(r) and col(k), the parts of the position that belong to one
+// index, and off(row, col), the element's offset or -1 where the operand is zero.
+// ------------------------------------------------------------------------------------------
+template <bool KC> struct MatrixView {
+    int rows, K;
+    int64_t ld;
+    typedef int Row;
+    typedef int Col;
+    __device__ __forceinline__ Row row(int r) const { return r < rows ? r : -1; }
+    __device__ __forceinline__ Col col(int k) const { return k < K ? k : -1; }
+    __device__ __forceinline__ int64_t off(Row r, Col k) const { return (r | k) < 0 ? -1 : (KC ? r * ld + k : k * ld + r); }
+};
+// output positions of a convolution against its filter taps: x[n, ho * stride + r - pad, wo * stride + s - pad, c]
+struct PatchView {
+    ConvGeom2 g;
+    int rows, K;      // positions, taps
+    struct Row { int64_t base; int h0, w0; };
+    struct Col { int r, s, add; };
+    __device__ __forceinline__ Row row(int m) const {
+        uint32_t n, rem, ho, wo;
+        g.d_howo.divmod(m < rows ? m : 0, n, rem);
+        g.d_wo.divmod(rem, ho, wo);
+        Row q;
+        q.h0 = m < rows ? (int)ho * g.stride - g.pad : -(1 << 28);
+        q.w0 = (int)wo * g.stride - g.pad;
+        q.base = (((int64_t)n * g.H + (int)ho * g.stride - g.pad) * g.W + q.w0) * g.Cin;
+        return q;
+    }
+    __device__ __forceinline__ Col col(int k) const {
+        uint32_t r, rem, s, c;
+        g.d_scin.divmod(k < K ? k : 0, r, rem);
+        g.d_cin.divmod(rem, s, c);
+        Col q;
+        q.r = k < K ? (int)r : -(1 << 28);
+        q.s = (int)s;
+        q.add = ((int)r * g.W + (int)s) * g.Cin + (int)c;
+        return q;
+    }
+    __device__ __forceinline__ int64_t off(const Row& a, const Col& b) const {
+        const int h = a.h0 + b.r, w = a.w0 + b.s;
+        return (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W ? a.base + b.add : -1;
+    }
+};
+// the same with the roles exchanged (rows are taps, k runs over positions): the weight gradient's second operand
+struct TapView {
+    PatchView v;
+    typedef PatchView::Col Row;
+    typedef PatchView::Row Col;
+    __device__ __forceinline__ Row row(int r) const { return v.col(r); }
+    __device__ __forceinline__ Col col(int k) const { return v.row(k); }
+    __device__ __forceinline__ int64_t off(const Row& a, const Col& b) const { return v.off(b, a); }
+};
+// input positions against (r, s, co): dy[n, (h + pad - r) / stride, (w + pad - s) / stride, co] where both divide
+struct BackPatchView {
+    ConvGeom2 g;
+    int rows, K;
+    struct Row { int64_t nbase; int hp, wp; };
+    struct Col { int r, s, co; };
+    __device__ __forceinline__ Row row(int m) const {
+        uint32_t n, rem, h, w;
+        g.d_hw.divmod(m < rows ? m : 0, n, rem);
+        g.d_w.divmod(rem, h, w);
+        Row q;
+        q.hp = m < rows ? (int)h + g.pad : -(1 << 28);
+        q.wp = (int)w + g.pad;
+        q.nbase = (int64_t)n * g.Ho * g.Wo * g.Cout;
+        return q;
+    }
+    __device__ __forceinline__ Col col(int k) const {
+        uint32_t r, rem, s, co;
+        g.d_scout.divmod(k < K ? k : 0, r, rem);
+        g.d_cout.divmod(rem, s, co);
+        Col q;
+        q.r = k < K ? (int)r : (1 << 28);
+        q.s = (int)s;
+        q.co = (int)co;
+        return q;
+    }
+    __device__ __forceinline__ int64_t off(const Row& a, const Col& b) const {
+        const int hy = a.hp - b.r, wy = a.wp - b.s;
+        if ((hy | wy) < 0) return -1;
+        uint32_t ho, hr, wo, wr;
+        g.d_stride.divmod(hy, ho, hr);
+        g.d_stride.divmod(wy, wo, wr);
+        return hr == 0 && wr == 0 && (int)ho < g.Ho && (int)wo < g.Wo ? a.nbase + ((int)ho * g.Wo + (int)wo) * g.Cout + b.co : -1;
+    }
+};
+// input channels against (r, s, co): w[co, r, s, ci]
+struct BackTapView {
+    ConvGeom2 g;
+    int rows, K;
+    typedef int Row;
+    typedef int Col;
+    __device__ __forceinline__ Row row(int ci) const { return ci < rows ? ci : -1; }
+    __device__ __forceinline__ Col col(int k) const {
+        uint32_t r, rem, s, co;
+        g.d_scout.divmod(k < K ? k : 0, r, rem);
+        g.d_cout.divmod(rem, s, co);
+        return k < K ? (((int)co * g.R + (int)r) * g.S + (int)s) * g.Cin : -1;
+    }
+    __device__ __forceinline__ int64_t off(Row a, Col b) const { return (a | b) < 0 ? -1 : (int64_t)b + a; }
+};
+
+template <class T_, bool KC, class View> struct Gather {
+    typedef T_ T;
+    static constexpr bool kContig = KC, kSettle = false;
+    static constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    const T* p;
+    View v;
+    struct KS { int k; };
+    struct CtxKC { typename View::Row row; };
+    struct CtxRC { int row0, kl; };
+    typedef typename std::conditional<KC, CtxKC, CtxRC>::type Ctx;
+    __device__ __forceinline__ void init_thread(KS& ks, int k_begin, int col) const { ks.k = KC ? k_begin + col * V : k_begin; }
+    __device__ __forceinline__ void init(Ctx& c, int row, int kl, int) const {
+        if constexpr (KC) c.row = v.row(row);
+        else {
+            c.row0 = row;
+            c.kl = kl;
+        }
+    }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+        union { uint4 u; T e[V]; } r;
+        if constexpr (KC) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const int64_t o = v.off(c.row, v.col(ks.k + e));
+                r.e[e] = *(o >= 0 && ks.k + e < k_end ? p + o : reinterpret_cast<const T*>(&g_zero_chunk));
+            }
+        } else {
+            const auto col = v.col(ks.k + c.kl);
+            const bool ok = ks.k + c.kl < k_end;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const int64_t o = v.off(v.row(c.row0 + e), col);
+                r.e[e] = *(o >= 0 && ok ? p + o : reinterpret_cast<const T*>(&g_zero_chunk));
+            }
+        }
+        return r.u;
+    }
+    __device__ __forceinline__ void next(KS& ks) const { ks.k += BK; }
 };
 
 // What gemm2_kernel asks of a loader beyond its chunks; loaders without these members get the defaults.
@@ -422,24 +668,34 @@ template <class Op> __device__ __forceinline__ auto op_out_row(const Op& op, int
 template <class Op> __device__ __forceinline__ int op_out_row(const Op&, int m, long) { return m; }
 
 // ------------------------------------------------------------------------------------------
-// LDS tile shapes.  k-contiguous: [rows][64 + 8] (144-byte rows: 16-byte reads of 8 consecutive rows
-// hit disjoint banks).  row-contiguous: [64][rows + 16] (row pitch = 32 bytes mod 128, so the 4 k-rows
-// a 16-lane group reads in one transpose read hit disjoint banks).
+// LDS tile shapes.  k-contiguous: [rows][128 + 16 bytes] (144-byte rows: 16-byte reads of 8 consecutive rows
+// hit disjoint banks).  row-contiguous: bf16 [64][rows + 16] (row pitch = 32 bytes mod 128, so the 4 k-rows
+// a 16-lane group reads in one transpose read hit disjoint banks), fp32 [32][rows + 8] (the half-waves of a 4-byte read
+// are 4 k-rows apart: 128 bytes mod 256).
 // ------------------------------------------------------------------------------------------
-template <int ROWS, bool KC> struct TileShape {
-    static constexpr int pitch = KC ? (kBK2 + 8) : (ROWS + 16);
-    static constexpr int elems = KC ? ROWS * pitch : kBK2 * pitch;
+template <class T, int ROWS, bool KC> struct TileShape {
+    static constexpr int BK = ElemTile<T>::BK;
+    static constexpr int pitch = KC ? (BK + ElemTile<T>::V) : (ROWS + (sizeof(T) == 2 ? 16 : 8));
+    static constexpr int elems = KC ? ROWS * pitch : BK * pitch;
 };
 
-template <int ROWS, bool KC> __device__ __forceinline__ bf16x8_t read_frag(const bf16_t* tile, int row_base, int kk, int lane) {
+// Fragment g (of 4 in a k-tile) of 32 rows: in bf16 the 16 k of one MFMA (lane: row lane % 32, 8 consecutive k), in fp32
+// the 8 k of four MFMAs (lane: row lane % 32, k = 8 g + 4 (lane / 32) + e for MFMA e).
+template <class T> struct Frag;
+template <> struct Frag<bf16_t> { typedef bf16x8_t type; };
+typedef float f32x4v_t __attribute__((ext_vector_type(4)));
+template <> struct Frag<float> { typedef f32x4v_t type; };
+
+template <class T, int ROWS, bool KC>
+__device__ __forceinline__ typename Frag<T>::type read_frag(const T* tile, int row_base, int g, int lane) {
+    constexpr int pitch = TileShape<T, ROWS, KC>::pitch, V = ElemTile<T>::V;
     if constexpr (KC) {
-        const bf16_t* p = tile + (row_base + (lane & 31)) * TileShape<ROWS, true>::pitch + kk * 16 + (lane >> 5) * 8;
-        return *reinterpret_cast<const bf16x8_t*>(p);
-    } else {
+        const T* p = tile + (row_base + (lane & 31)) * pitch + (g * 2 + (lane >> 5)) * V;
+        return *reinterpret_cast<const typename Frag<T>::type*>(p);
+    } else if constexpr (sizeof(T) == 2) {
         // Transpose read: within 16 lanes, lane j supplies the address of 4 consecutive rows at
         // k = k0 + j/4, rows c0 + 4*(j%4); lane i receives k0..k0+3 of row c0 + i.
-        constexpr int pitch = TileShape<ROWS, false>::pitch;
-        const int k = kk * 16 + (lane >> 5) * 8 + ((lane & 15) >> 2);
+        const int k = g * 16 + (lane >> 5) * 8 + ((lane & 15) >> 2);
         const int col = row_base + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
         typedef __attribute__((address_space(3))) s16x4_t* lds_ptr_t;
         const bf16_t* p0 = tile + k * pitch + col;
@@ -450,12 +706,19 @@ template <int ROWS, bool KC> __device__ __forceinline__ bf16x8_t read_frag(const
         u.h[0] = lo;
         u.h[1] = hi;
         return u.v;
+    } else {
+        const T* p = tile + (g * 8 + (lane >> 5) * 4) * pitch + row_base + (lane & 31);
+        f32x4v_t v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = p[e * pitch];
+        return v;
     }
 }
 
 // LDS bytes of one launch: two buffers of an A tile and a B tile.
 template <int BM, int BN, class AOp, class BOp> constexpr int gemm2_lds_bytes() {
-    return 2 * (TileShape<BM, AOp::kContig>::elems + TileShape<BN, BOp::kContig>::elems) * (int)sizeof(bf16_t);
+    typedef typename AOp::T T;
+    return 2 * (TileShape<T, BM, AOp::kContig>::elems + TileShape<T, BN, BOp::kContig>::elems) * (int)sizeof(T);
 }
 
 // D = number of k-tiles whose global loads are in flight per thread (register ring).
@@ -466,12 +729,14 @@ template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
 __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice,
                                                     int col_major, int wide, FastDiv d_plane, FastDiv d_minor) {
     constexpr bool AKC = AOp::kContig, BKC = BOp::kContig;
+    typedef typename AOp::T T;
+    constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
     constexpr int TM = BM / 64, TN = BN / 64;
-    constexpr int A_CH = BM * (kBK2 / 8) / 256, B_CH = BN * (kBK2 / 8) / 256;
-    constexpr int A_ELEMS = TileShape<BM, AKC>::elems, B_ELEMS = TileShape<BN, BKC>::elems;
+    constexpr int A_CH = BM * 8 / 256, B_CH = BN * 8 / 256;   // 16-byte chunks per thread and k-tile
+    constexpr int A_ELEMS = TileShape<T, BM, AKC>::elems, B_ELEMS = TileShape<T, BN, BKC>::elems;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    bf16_t* const sA = reinterpret_cast<bf16_t*>(smem_raw);  // [2][A_ELEMS]
-    bf16_t* const sB = sA + 2 * A_ELEMS;                      // [2][B_ELEMS]
+    T* const sA = reinterpret_cast<T*>(smem_raw);  // [2][A_ELEMS]
+    T* const sB = sA + 2 * A_ELEMS;                // [2][B_ELEMS]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -510,7 +775,7 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
     op_begin_tile(B, m0, 0);
     const int k_begin = z * k_per_slice;
     const int k_end = min(op_k_total(A, K, 0), k_begin + k_per_slice);
-    const int nk = max(0, (k_end - k_begin + kBK2 - 1) / kBK2);
+    const int nk = max(0, (k_end - k_begin + BK - 1) / BK);
 
     typename AOp::KS ksa;
     typename BOp::KS ksb;
@@ -525,11 +790,11 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
         if constexpr (AKC) {
             int row = c >> 3, kc = c & 7;
             A.init(ca[i], m0 + row, kc, k_begin);
-            sa_off[i] = row * TileShape<BM, true>::pitch + kc * 8;
+            sa_off[i] = row * TileShape<T, BM, true>::pitch + kc * V;
         } else {
-            int rc = c % (BM / 8), kl = c / (BM / 8);
-            A.init(ca[i], m0 + rc * 8, kl, k_begin);
-            sa_off[i] = kl * TileShape<BM, false>::pitch + rc * 8;
+            int rc = c % (BM / V), kl = c / (BM / V);
+            A.init(ca[i], m0 + rc * V, kl, k_begin);
+            sa_off[i] = kl * TileShape<T, BM, false>::pitch + rc * V;
         }
     }
 #pragma unroll
@@ -538,16 +803,16 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
         if constexpr (BKC) {
             int row = c >> 3, kc = c & 7;
             B.init(cb[i], n0 + row, kc, k_begin);
-            sb_off[i] = row * TileShape<BN, true>::pitch + kc * 8;
+            sb_off[i] = row * TileShape<T, BN, true>::pitch + kc * V;
         } else {
-            int rc = c % (BN / 8), kl = c / (BN / 8);
-            B.init(cb[i], n0 + rc * 8, kl, k_begin);
-            sb_off[i] = kl * TileShape<BN, false>::pitch + rc * 8;
+            int rc = c % (BN / V), kl = c / (BN / V);
+            B.init(cb[i], n0 + rc * V, kl, k_begin);
+            sb_off[i] = kl * TileShape<T, BN, false>::pitch + rc * V;
         }
     }
 
     // A wave with a single 32x32 output tile alternates between two accumulators (even and odd 16-k steps), so that
-    // consecutive MFMAs do not wait for each other's result; they are added at the end.
+    // consecutive MFMAs do not wait for each other's result; they are added at the end.  (fp32: even and odd k.)
     constexpr int NACC = TM * TN == 1 ? 2 : 1;
     f32x16_t acc[NACC][TM][TN];
 #pragma unroll
@@ -575,50 +840,70 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
         A.next(ksa);
         B.next(ksb);
     };
-    auto stash = [&](const uint4 (&a)[A_CH], const uint4 (&b)[B_CH], int buf) {
-        bf16_t* da = sA + buf * A_ELEMS;
-        bf16_t* db = sB + buf * B_ELEMS;
+    // (kt: the k-tile, for the loaders that have something left to do)
+    auto stash = [&](const uint4 (&a)[A_CH], const uint4 (&b)[B_CH], int kt, int buf) {
+        T* da = sA + buf * A_ELEMS;
+        T* db = sB + buf * B_ELEMS;
+        const int k = k_begin + kt * BK + (tid & 7) * V;
 #pragma unroll
-        for (int i = 0; i < A_CH; ++i) *reinterpret_cast<uint4*>(da + sa_off[i]) = a[i];
+        for (int i = 0; i < A_CH; ++i) {
+            uint4 v = a[i];
+            if constexpr (AOp::kSettle) v = A.settle(ca[i], v, k, k_end);
+            *reinterpret_cast<uint4*>(da + sa_off[i]) = v;
+        }
 #pragma unroll
-        for (int i = 0; i < B_CH; ++i) *reinterpret_cast<uint4*>(db + sb_off[i]) = b[i];
+        for (int i = 0; i < B_CH; ++i) {
+            uint4 v = b[i];
+            if constexpr (BOp::kSettle) v = B.settle(cb[i], v, k, k_end);
+            *reinterpret_cast<uint4*>(db + sb_off[i]) = v;
+        }
     };
     // Fetches beyond the slice return zeros (the loaders clamp), so the ring is always kept full and the
     // steady-state loop has no branch around a load or a store.
 #pragma unroll
     for (int d = 0; d < D; ++d) fetch(ra[d], rb[d]);
-    stash(ra[0], rb[0], 0);
+    stash(ra[0], rb[0], 0, 0);
     fetch(ra[0], rb[0]);
     __syncthreads();
 
     auto multiply = [&](int buf) {
-        const bf16_t* tA = sA + buf * A_ELEMS;
-        const bf16_t* tB = sB + buf * B_ELEMS;
+        const T* tA = sA + buf * A_ELEMS;
+        const T* tB = sB + buf * B_ELEMS;
         // every fragment of the k-tile is requested before the first MFMA: the LDS latency is paid once per k-tile,
-        // not once per 16-k step
-        constexpr int KK = kBK2 / 16;
-        bf16x8_t af[KK][TM], bfr[KK][TN];
+        // not once per fragment
+        typename Frag<T>::type af[4][TM], bfr[4][TN];
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
+        for (int g = 0; g < 4; ++g) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) af[kk][i] = read_frag<BM, AKC>(tA, wm * (BM / 2) + i * 32, kk, lane);
+            for (int i = 0; i < TM; ++i) af[g][i] = read_frag<T, BM, AKC>(tA, wm * (BM / 2) + i * 32, g, lane);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) bfr[kk][j] = read_frag<BN, BKC>(tB, wn * (BN / 2) + j * 32, kk, lane);
+            for (int j = 0; j < TN; ++j) bfr[g][j] = read_frag<T, BN, BKC>(tB, wn * (BN / 2) + j * 32, g, lane);
         }
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[kk % NACC][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk][i], bfr[kk][j], acc[kk % NACC][i][j], 0, 0, 0);
-        if (sums_rows) {
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk)
+        for (int g = 0; g < 4; ++g) {
+            if constexpr (sizeof(T) == 2) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) rsum[i] += (float)af[kk][i][e];
+                    for (int j = 0; j < TN; ++j)
+                        acc[g % NACC][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[g][i], bfr[g][j], acc[g % NACC][i][j], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+                            acc[e % NACC][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[g][i][e], bfr[g][j][e], acc[e % NACC][i][j], 0, 0, 0);
+            }
+        }
+        if (sums_rows) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) rsum[i] += (float)af[g][i][e];
         }
     };
 
@@ -630,7 +915,7 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
             const int kt = round * D + d;
             const int dn = (d + 1) % D;  // compile-time after unrolling
             // LDS buffer (kt+1)&1 was last read in iteration kt-1, which ended with a barrier
-            stash(ra[dn], rb[dn], (kt + 1) & 1);
+            stash(ra[dn], rb[dn], kt + 1, (kt + 1) & 1);
             fetch(ra[dn], rb[dn]);
             multiply(kt & 1);
             __syncthreads();
@@ -733,9 +1018,6 @@ struct EpiPartial {
     __device__ __forceinline__ int column(int) const { return 0; }
     __device__ __forceinline__ void at(int, int64_t idx, float v, int z) const {
         part[z * slice_stride + idx] = v;
-    }
-    __device__ __forceinline__ void at8(int, int64_t idx, float (&v)[8], int z) const {
-        store8(part + z * slice_stride + idx, v);
     }
     typedef NoCol8 Col8;
     typedef NoRow8 Row8;

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G
     // (the wave's index as a scalar: what derives from it — LDS addresses of its copies, its place in the tile — then
     // lives in scalar registers and is computed by the scalar unit)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN, half = lane >> 5;
+    const int wm = wave / WN, wn = wave % WN;
     const int grid = gridDim.x;
     // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin in launch order.  Renumber them so that
     // the workgroups of one XCD take CONSECUTIVE units of every round: consecutive units are tiles of one row and

@@ -1,0 +1,269 @@
+// Dispatch of the contractions, written once for bf16 and fp32 operands and instantiated in one source file per type
+// (kernels_gemm.hip, kernels_gemm_f32.hip; the gathering bf16 instances in kernels_gemm_gather.hip): tile sizes and
+// k-splits, the choice between the kernels, and the dense and convolution passes in terms of them.
+#pragma once
+#include <hip/hip_ext.h>
+
+#include "gemm3.hip.h"
+#include "gemm_small.hip.h"
+#include "kernels.h"
+#include "launch.h"
+#include "profile.h"
+
+namespace tmps {
+
+static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// What a contraction runs on: tile shape of the tiled kernel and k-slices, or (bm = 32) the small kernel.
+struct Plan2 {
+    int bm, bn, slices;
+};
+
+constexpr int kCUs = 256;   // compute units of the device the rules below are written for
+
+// ---- plans ----------------------------------------------------------------------------------------
+// fp32: the tile shape and k-slices of least estimated time.
+Plan2 plan_f32(int64_t M, int64_t N, int64_t K, bool rowsum);
+// bf16: plan_gemm's tile edge and slices; where the edge is 64 and the output tall the tiles are 128 x 64 (see there).
+Plan2 plan_bf16(int64_t M, int64_t N, int64_t K, bool rowsum);
+template <class T> static Plan2 plan_of(int64_t M, int64_t N, int64_t K, bool rowsum) {
+    if constexpr (sizeof(T) == 4) return plan_f32(M, N, K, rowsum);
+    else return plan_bf16(M, N, K, rowsum);
+}
+// Whether a dense contraction runs on the small kernel (gemm_small.hip.h) rather than on the given tiled plan.
+bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& tiled);
+
+// out[i] = sum over slices of part[slice * count + i], in slice order
+hipError_t slice_sum(const float* part, float* out, int64_t count, int slices, hipStream_t s);
+
+// slice length (whole k-tiles) and the number of slices really launched
+static void slice_geometry(int64_t K, int want, int ktile, int& per, int& nz) {
+    if (want < 1) want = 1;
+    per = cdiv(cdiv(K, want), ktile) * ktile;
+    if (per < ktile) per = ktile;
+    nz = K > 0 ? cdiv(K, per) : 1;
+}
+
+
+// ---- launches -------------------------------------------------------------------------------------
+template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t launch2_inst(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
+                               int nz, hipStream_t s) {
+    constexpr int lds = gemm2_lds_bytes<BM, BN, AOp, BOp>();
+    auto kern = gemm2_kernel<BM, BN, D, ROWSUM, AOp, BOp, Epi>;
+    if (lds > 64 * 1024) {
+        // more LDS than the default per-workgroup limit: raise it once per kernel instance
+        static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (attr != hipSuccess) return attr;
+    }
+    dim3 grid(cdiv(N, BN), cdiv(M, BM), nz);
+    // the XCDs split the operand with more rows between them and each reads the other one whole
+    const int col_major = N > M ? 1 : 0;
+    return launch_timed(kc, kern, grid, dim3(256), lds, s, A, B, epi, M, N, K, per, col_major,
+                        (N % 8 == 0 && epi.wide_ok()) ? 1 : 0, FastDiv(grid.x * grid.y), FastDiv(col_major ? grid.y : grid.x));
+}
+
+// (gathering loaders put a chunk together from eight or four loads: one small tile, a short ring)
+template <class Op> struct IsGather { static constexpr bool value = false; };
+template <class T, bool KC, class View> struct IsGather<Gather<T, KC, View>> { static constexpr bool value = true; };
+
+template <bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t launch2_tile(int kc, const Plan2& p, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
+                               int nz, hipStream_t s) {
+    if constexpr (IsGather<AOp>::value || IsGather<BOp>::value) return launch2_inst<64, 64, 1, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+    else {
+        if (p.bm == 128 && p.bn == 128) return launch2_inst<128, 128, 2, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+        if constexpr (!ROWSUM && !AOp::kSettle) {
+            if (p.bm == 128) return launch2_inst<128, 64, 2, false>(kc, A, B, epi, M, N, K, per, nz, s);
+        }
+        // (fp32: a k-tile is multiplied for 1000 cycles, and two in flight are enough; ragged operands: no registers for four)
+        constexpr int D = sizeof(typename AOp::T) == 4 || AOp::kSettle ? 2 : 4;
+        return launch2_inst<64, 64, D, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+    }
+}
+
+// Forward / input-gradient style GEMM: epilogue `epi` applied once per output element.
+// tile: 0 = the plan's choice, else the edge of the square tiles to use (the slices stay the plan's)
+template <class AOp, class BOp, class Epi>
+static hipError_t run2(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, float* ws, hipStream_t s, int tile = 0) {
+    typedef typename AOp::T T;
+    if (M <= 0 || N <= 0) return hipSuccess;
+    Plan2 p = plan_of<T>(M, N, K, false);
+    if (tile) p.bm = p.bn = tile;
+    int per, nz;
+    slice_geometry(K, ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
+    if (nz <= 1) return launch2_tile<false>(kc, p, A, B, epi, M, N, K, per, nz, s);
+    EpiPartial part{ws, N, (int64_t)M * N};
+    hipError_t e = launch2_tile<false>(kc, p, A, B, part, M, N, K, per, nz, s);
+    if (e != hipSuccess) return e;
+    int64_t total = (int64_t)M * N;
+    if (N % 8 == 0 && epi.wide_ok() && aligned16(ws))
+        return launch_timed(kcSplitFinish, splitk_finish8_kernel<Epi>, dim3(cdiv(total / 8, 256)), dim3(256), 0, s,
+                            (const float*)ws, epi, M, N, nz);
+    return launch_timed(kcSplitFinish, splitk_finish_kernel<Epi>, dim3(cdiv(total, 256)), dim3(256), 0, s,
+                        (const float*)ws, epi, M, N, nz);
+}
+
+// Weight-gradient style GEMM: fp32 result [rows x cols] followed by the row sums of A (bias gradient).
+template <class AOp, class BOp>
+static hipError_t run2_wgrad(int kc, const AOp& A, const BOp& B, float* gw, int rows, int cols, int64_t K, float* ws, hipStream_t s) {
+    typedef typename AOp::T T;
+    const Plan2 p = plan_of<T>(rows, cols, K, true);
+    int per, nz;
+    slice_geometry(K, ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
+    int64_t count = (int64_t)rows * cols + rows;
+    EpiWgrad epi{nz > 1 ? ws : gw, cols, (int64_t)rows * cols, count};
+    hipError_t e = launch2_tile<true>(kc, p, A, B, epi, rows, cols, (int)K, per, nz, s);
+    if (e != hipSuccess || nz <= 1) return e;
+    return slice_sum((const float*)ws, gw, count, nz, s);
+}
+
+// Small kernel: as many waves as the contraction has fragment pairs for, in powers of two up to 16.
+template <bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t run_small(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, hipStream_t s) {
+    constexpr int GK = 2 * ElemTile<typename AOp::T>::V;
+    const dim3 grid(cdiv(N, 32), cdiv(M, 32));
+    const int groups = cdiv(K, GK);
+    if (groups > 32) return launch_timed(kc, gemm_small_kernel<16, ROWSUM, AOp, BOp, Epi>, grid, dim3(1024), 16 * 1056 * 4, s, A, B, epi, M, N, K);
+    if (groups > 8) return launch_timed(kc, gemm_small_kernel<8, ROWSUM, AOp, BOp, Epi>, grid, dim3(512), 8 * 1056 * 4, s, A, B, epi, M, N, K);
+    return launch_timed(kc, gemm_small_kernel<4, ROWSUM, AOp, BOp, Epi>, grid, dim3(256), 4 * 1056 * 4, s, A, B, epi, M, N, K);
+}
+
+// ---- element-wise gathering instances (kernels_gemm_gather.hip, both types) ------------------------------
+template <class T, class Epi> hipError_t gather_dense_kc_kc(int kc, const T* a, const T* b, const Epi& epi, int M, int N, int K, float* ws, hipStream_t s);
+template <class T> hipError_t gather_dense_dgrad(int kc, const T* dy, const T* w, const EpiMask<T, T>& epi, int M, int N, int K, float* ws, hipStream_t s);
+template <class T> hipError_t gather_dense_wgrad(int kc, const T* dy, const T* x, float* gw, int rows, int cols, int K, float* ws, hipStream_t s);
+template <class T, class Epi> hipError_t gather_conv_forward(const T* x, const T* w, const Epi& epi, const ConvShape& c, float* ws, hipStream_t s);
+template <class T> hipError_t gather_conv_dgrad(const T* dy, const T* w, const EpiMask<T, T>& epi, const ConvShape& c, float* ws, hipStream_t s);
+template <class T> hipError_t gather_conv_wgrad(const T* dy, const T* x, float* gw, const ConvShape& c, float* ws, hipStream_t s);
+
+static inline ConvGeom2 geom2(const ConvShape& c) {
+    ConvGeom2 g;
+    g.B = c.B; g.H = c.H; g.W = c.W; g.Cin = c.Cin; g.Ho = c.Ho; g.Wo = c.Wo; g.Cout = c.Cout;
+    g.R = c.R; g.S = c.S; g.stride = c.stride; g.pad = c.pad;
+    g.d_howo = FastDiv(c.Ho * c.Wo); g.d_wo = FastDiv(c.Wo);
+    g.d_hw = FastDiv(c.H * c.W); g.d_w = FastDiv(c.W);
+    g.d_scin = FastDiv(c.S * c.Cin); g.d_cin = FastDiv(c.Cin);
+    g.d_scout = FastDiv(c.S * c.Cout); g.d_cout = FastDiv(c.Cout);
+    g.d_stride = FastDiv(c.stride);
+    return g;
+}
+
+// ---- dense passes (without the persistent kernel) -----------------------------------------------------
+// Rows in whole 16-byte chunks take the plain loaders, ragged ones of a chunk or more the ragged loaders, the rest is gathered.
+template <class T, class Epi>
+static hipError_t dense_forward_t(int kc, const T* x, const T* w, const Epi& epi, int B, int Din, int Dout, float* ws, hipStream_t s) {
+    constexpr int V = ElemTile<T>::V;
+    if (small_is_better(B, Dout, Din, sizeof(T), plan_of<T>(B, Dout, Din, false)))
+        return run_small<false>(kc, SmallOperand<T, true>{x, B, Din}, SmallOperand<T, true>{w, Dout, Din}, epi, B, Dout, Din, s);
+    if (Din % V == 0 && aligned16(x) && aligned16(w))
+        return run2(kc, DenseKC<T>{x, B, Din, Din}, DenseKC<T>{w, Dout, Din, Din}, epi, B, Dout, Din, ws, s);
+    if (Din >= V) return run2(kc, RaggedKC<T>{x, B, Din, Din}, RaggedKC<T>{w, Dout, Din, Din}, epi, B, Dout, Din, ws, s);
+    return gather_dense_kc_kc<T>(kc, x, w, epi, B, Dout, Din, ws, s);
+}
+
+// dx[m, n] = sum_k dy[m, k] * w[k, n]:  A = dy (k-contiguous), B(n, k) = w[k*Din + n] (row-contiguous)
+template <class T>
+static hipError_t dense_dgrad_t(int kc, const T* dy, const T* w, const EpiMask<T, T>& epi, int B, int Din, int Dout, float* ws, hipStream_t s) {
+    constexpr int V = ElemTile<T>::V;
+    if (small_is_better(B, Din, Dout, sizeof(T), plan_of<T>(B, Din, Dout, false)))
+        return run_small<false>(kc, SmallOperand<T, true>{dy, B, Dout}, SmallOperand<T, false>{w, Din, Din}, epi, B, Din, Dout, s);
+    if (Dout % V == 0 && Din % V == 0 && aligned16(dy) && aligned16(w))
+        return run2(kc, DenseKC<T>{dy, B, Dout, Dout}, DenseRC<T>{w, Din, Dout, Din}, epi, B, Din, Dout, ws, s);
+    if (Dout >= V && Din >= V)
+        return run2(kc, RaggedKC<T>{dy, B, Dout, Dout}, RaggedRC<T>{w, Din, Dout, Din}, epi, B, Din, Dout, ws, s);
+    return gather_dense_dgrad<T>(kc, dy, w, epi, B, Din, Dout, ws, s);
+}
+
+// gw[m, n] = sum_k dy[k, m] * x[k, n]: both operands row-contiguous, contraction over the batch
+template <class T>
+static hipError_t dense_wgrad_t(int kc, const T* dy, const T* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) {
+    constexpr int V = ElemTile<T>::V;
+    if (small_is_better(Dout, Din, B, sizeof(T), plan_of<T>(Dout, Din, B, true)))
+        return run_small<true>(kc, SmallOperand<T, false>{dy, Dout, Dout}, SmallOperand<T, false>{x, Din, Din},
+                               EpiWgrad{gw, Din, (int64_t)Dout * Din, 0}, Dout, Din, B, s);
+    if (Dout % V == 0 && Din % V == 0 && aligned16(dy) && aligned16(x))
+        return run2_wgrad(kc, DenseRC<T>{dy, Dout, B, Dout}, DenseRC<T>{x, Din, B, Din}, gw, Dout, Din, B, ws, s);
+    if (Dout >= V && Din >= V)
+        return run2_wgrad(kc, RaggedRC<T>{dy, Dout, B, Dout}, RaggedRC<T>{x, Din, B, Din}, gw, Dout, Din, B, ws, s);
+    return gather_dense_wgrad<T>(kc, dy, x, gw, Dout, Din, B, ws, s);
+}
+
+// ---- convolution passes -------------------------------------------------------------------------------
+// The chunked loaders index positions with 24-bit multiplies and tensors with 32-bit element offsets.
+static inline bool small_enough(const ConvShape& c) {
+    const int64_t pin = (int64_t)c.B * c.H * c.W, pout = (int64_t)c.B * c.Ho * c.Wo;
+    const int64_t wel = (int64_t)c.Cout * c.R * c.S * c.Cin;
+    return pin < (1 << 24) && pout < (1 << 24) && pin * c.Cin < (int64_t(1) << 31) &&
+           pout * c.Cout < (int64_t(1) << 31) && wel < (int64_t(1) << 31) && c.Cin < (1 << 20) && c.Cout < (1 << 20);
+}
+
+template <class T, class Epi>
+static hipError_t conv_forward_t(const T* x, const T* w, const Epi& epi, const ConvShape& c, float* ws, hipStream_t s) {
+    const int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
+    if (c.Cin % ElemTile<T>::V == 0 && aligned16(x) && aligned16(w) && small_enough(c))
+        return run2(kcConvFwd, ConvFwdA2<T>{x, geom2(c), M, K}, DenseKC<T>{w, c.Cout, K, K}, epi, M, c.Cout, K, ws, s);
+    return gather_conv_forward<T>(x, w, epi, c, ws, s);
+}
+
+template <class T>
+static hipError_t conv_dgrad_t(const T* dy, const T* w, const EpiMask<T, T>& epi, const ConvShape& c, float* ws, hipStream_t s) {
+    const int M = c.B * c.H * c.W, K = c.R * c.S * c.Cout;
+    constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    if (c.Cin % V != 0 || c.Cout % V != 0 || !aligned16(dy) || !aligned16(w) || !small_enough(c)) return gather_conv_dgrad<T>(dy, w, epi, c, ws, s);
+    if (c.stride == 2 && c.H % 2 == 0 && c.W % 2 == 0 && c.Cin % 8 == 0) {
+        // Rows ordered by the parity of their position, each class walking only the filter taps that reach it:
+        // k extent of the largest class; every class a whole number of tiles; the 16-byte epilogue (the one
+        // that asks the loader where a row lies in memory), also for the partial sums of a split.
+        const int Kp = ((c.R + 1) / 2) * ((c.S + 1) / 2) * c.Cout;
+        const Plan2 plan = plan_of<T>(M, c.Cin, Kp, false);
+        const int edge = plan.bn;   // (64 for the tall tiles: this order needs square ones)
+        const int Mc = M / 4;
+        int per, nz;
+        slice_geometry(Kp, ws ? plan.slices : 1, BK, per, nz);
+        const bool split_ok = nz <= 1 || (aligned16(ws) && ((int64_t)M * c.Cin) % 4 == 0);
+        // (where a class is no whole number of the plan's tiles, smaller tiles still pay for a filter with
+        // several taps; a 1x1 filter's launch is mostly epilogue either way and keeps the plain order then)
+        const int tile = (Mc % edge == 0 || c.R * c.S == 1) ? edge : 64;
+        if (Mc % tile == 0 && epi.wide_ok() && split_ok) {
+            ParityGeom pg;
+            pg.Mc = Mc;
+            pg.W2 = c.W / 2;
+            pg.d_mc = FastDiv(Mc);
+            pg.d_h2w2 = FastDiv((c.H / 2) * (c.W / 2));
+            pg.d_w2 = FastDiv(c.W / 2);
+            return run2(kcConvDgrad, ConvDgradA2P<T>{dy, geom2(c), M, Kp, pg, {}}, ConvDgradB2P<T>{w, geom2(c), c.Cin, Kp, pg, {}}, epi, M,
+                        c.Cin, Kp, ws, s, tile);
+        }
+    }
+    return run2(kcConvDgrad, ConvDgradA2<T>{dy, geom2(c), M, K}, ConvDgradB2<T>{w, geom2(c), c.Cin, K}, epi, M, c.Cin, K, ws, s);
+}
+
+template <class T> static hipError_t conv_wgrad_t(const T* dy, const T* x, float* gw, const ConvShape& c, float* ws, hipStream_t s) {
+    const int rows = c.Cout, cols = c.R * c.S * c.Cin;
+    const int64_t K = (int64_t)c.B * c.Ho * c.Wo;
+    constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
+    if (c.Cin % V != 0 || c.Cout % V != 0 || !aligned16(dy) || !aligned16(x) || !small_enough(c)) return gather_conv_wgrad<T>(dy, x, gw, c, ws, s);
+    const int rows_bk = BK / c.Wo;
+    ConvWgradB2<T> Bv{x, geom2(c), cols, (int)K, BK % c.Wo, rows_bk % c.Ho, rows_bk / c.Ho};
+    return run2_wgrad(kcConvWgrad, DenseRC<T>{dy, rows, (int)K, c.Cout}, Bv, gw, rows, cols, K, ws, s);
+}
+
+// A 1x1 convolution with unit stride and no padding on NHWC tensors IS a dense layer over the B*H*W positions
+// (weights [Cout][Cin]) and takes the dense paths.
+static inline bool pointwise(const ConvShape& c) {
+    return c.R == 1 && c.S == 1 && c.stride == 1 && c.pad == 0 && (int64_t)c.B * c.H * c.W < (int64_t(1) << 31);
+}
+
+// fp32 passes (kernels_gemm_f32.hip)
+hipError_t dense_forward_f32(int kc, const float* x, const float* w, const EpiBiasAct<float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
+hipError_t dense_dgrad_f32(int kc, const float* dy, const float* w, const EpiMask<float, float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
+hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s);
+hipError_t conv_forward_f32(const float* x, const float* w, const EpiBiasAct<float>& epi, const ConvShape& c, float* ws, hipStream_t s);
+hipError_t conv_affine_f32(const float* x, const float* w, const EpiConvAffine<float>& epi, const ConvShape& c, float* ws, hipStream_t s);
+hipError_t conv_dgrad_f32(const float* dy, const float* w, const EpiMask<float, float>& epi, const ConvShape& c, float* ws, hipStream_t s);
+hipError_t conv_wgrad_f32(const float* dy, const float* x, float* gw, const ConvShape& c, float* ws, hipStream_t s);
+
+}  // namespace tmps

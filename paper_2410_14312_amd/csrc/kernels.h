@@ -16,15 +16,16 @@ struct ConvShape {
     int B, H, W, Cin, Ho, Wo, Cout, R, S, stride, pad;
 };
 
-// Tile edge (64 or 128) and number of k-slices chosen for a [M x N x K] contraction, and the fp32
-// workspace elements its partial sums need (0 without a split).  with_rowsum: weight-gradient GEMMs
-// also keep M row sums per slice.  Every launcher below takes that workspace as `ws` (may be null:
-// then nothing is split).
+// Tile edge (64 or 128) and number of k-slices chosen for a bf16 [M x N x K] contraction.
 struct GemmPlan {
     int tile, slices;
 };
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K);
-size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t K, int with_rowsum);
+// fp32 workspace elements that the partial sums of a contraction need (0 without a split).  flags: kWsRowSums: a
+// weight-gradient GEMM, which also keeps M row sums per slice; kWsF32: fp32 operands.  Every launcher below takes that
+// workspace as `ws` (may be null: then nothing is split).
+enum { kWsRowSums = 1, kWsF32 = 2 };
+size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t K, int flags);
 
 // y[B, Dout] = act(x[B, Din] w^T + b).  w is the working copy (bf16 or fp32 per dtype), bias fp32.
 // out_f32: write fp32 regardless of dtype (logits).

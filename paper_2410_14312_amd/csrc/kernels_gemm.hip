@@ -1,20 +1,13 @@
-// Launchers of the contraction kernels: dense and convolution forward, input gradient and weight
-// gradient.  bf16 stages use the MFMA skeleton of gemm2.hip.h whenever every operand can be fetched
-// with aligned 16-byte loads (channel / feature counts that are multiples of 8), and the
-// element-wise skeleton of gemm.hip.h otherwise (3-channel input layer, 10-way logits layer);
-// fp32 stages use the fp32 skeleton.
-#include <cstdlib>
-#include <hip/hip_ext.h>
+// Launchers of the contraction kernels: dense and convolution forward, input gradient and weight gradient, for both
+// element types; the bf16 instances of the tiled, the small and the persistent kernel (the fp32 ones are in
+// kernels_gemm_f32.hip, those with gathering loaders in kernels_gemm_gather.hip).
+#include <math.h>
 
-#include "gemm3.hip.h"
-#include "kernels.h"
-#include "launch.h"
-#include "profile.h"
+#include <cstdlib>
+
+#include "gemm_dispatch.hip.h"
 
 namespace tmps {
-
-static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // ------------------------------------------------------------------------------------------
 // Tile size and k-split of a [M x N x K] contraction.  Small outputs are split along k until the grid
@@ -53,13 +46,80 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K) {
     return p;
 }
 
-static int g3_wgrad_slices(int64_t M, int64_t N, int64_t K);
-static int g3_long_k_slices(int64_t M, int64_t N, int64_t K);
+Plan2 plan_bf16(int64_t M, int64_t N, int64_t K, bool rowsum) {
+    const GemmPlan p = plan_gemm(M, N, K);
+    // Where the plan's edge is 64, the output has 512 rows or more and 128 x 64 tiles still make 192 workgroups, the tiles
+    // are 128 rows tall: a 128 x 64 tile reads a quarter less LDS per MFMA than a 64 x 64 one, and with the stages'
+    // kernels sharing the device that outweighs having half as many workgroups (measured: GPT-2 and ResNet-50 steps 1 %
+    // shorter, VGG-16 1-2 %; 128 x 128 and 64 x 128 for the same launches did worse; below 192 workgroups the launch
+    // itself gets slower and the step no faster).
+    const bool tall = p.tile == 64 && !rowsum && M >= 512 && (int64_t)cdiv(M, 128) * cdiv(N, 64) * p.slices >= 192;
+    return {tall ? 128 : p.tile, p.tile, p.slices};
+}
 
-size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t K, int with_rowsum) {
-    GemmPlan p = plan_gemm(M, N, K);
-    int slices = p.slices;
-    if (with_rowsum) {   // a weight gradient may go to the persistent path, with its own number of slices
+// Estimated cycles (2.4 GHz) of an fp32 contraction on the tiled kernel: the busiest compute unit's multiplies (1024
+// cycles for a k-tile of a 64 x 64 tile; small tiles weighed up for the LDS traffic they need more of per product), what
+// a workgroup alone on its unit cannot hide, the fixed part of a launch, and the finishing launch and partial sums of a
+// split (5 TB/s).
+static double tiled_cost_f32(int64_t M, int64_t N, int64_t K, int bm, int bn, int64_t slices) {
+    const double per_ktile = (bm / 64) * (bn / 64) * 1024.0, weight = bm * bn == 4096 ? 1.10 : bm * bn == 8192 ? 1.04 : 1.0;
+    const double nk = (double)cdiv(cdiv(K, 32), slices), rounds = (double)cdiv((int64_t)cdiv(M, bm) * cdiv(N, bn) * slices, kCUs);
+    double t = rounds * nk * per_ktile * weight + (rounds <= 1.0 ? 300.0 * nk : 0.0) + 5000.0;
+    if (slices > 1) t += 8000.0 + (double)slices * M * N * 8.0 / 2083.0;
+    return t;
+}
+
+Plan2 plan_f32(int64_t M, int64_t N, int64_t K, bool rowsum) {
+    static const int shape[3][2] = {{64, 64}, {128, 64}, {128, 128}};
+    Plan2 best{64, 64, 1};
+    double best_t = 0.0;
+    for (const auto& sh : shape) {
+        if (rowsum && sh[0] != sh[1]) continue;
+        for (int64_t sl = 1; sl <= 64; sl += sl < 8 ? 1 : sl < 16 ? 2 : 8) {
+            if (sl > 1 && (K < sl * 128 || sl * M * N > (int64_t(1) << 24))) break;   // (at most 64 MB of partial sums)
+            const double t = tiled_cost_f32(M, N, K, sh[0], sh[1], sl);
+            if (best_t == 0.0 || t < best_t) {
+                best_t = t;
+                best = {sh[0], sh[1], (int)sl};
+            }
+        }
+    }
+    return best;
+}
+
+// The small kernel against the tiled plan, both in estimated cycles.  Small: the busiest unit's multiplies (its waves
+// share the k range), or the operands' way from L2 (64 elements per k and tile, some 14 TB/s over the device), whichever
+// is longer.  Tiled in bf16: 720 cycles per k-tile of a workgroup (measured on 1024 x 768 x 768: 0.3 us), up to two
+// workgroups of a unit overlapping.
+bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& tiled) {
+    const int64_t tiles = (int64_t)cdiv(M, 32) * cdiv(N, 32);
+    if (tiles > 2 * kCUs) return false;
+    const int gk = esize == 4 ? 8 : 16;
+    const int64_t groups = cdiv(K, gk), nw = groups > 32 ? 16 : groups > 8 ? 8 : 4;
+    const double mfma = (double)cdiv(tiles, kCUs) * cdiv(groups, nw) * (nw / 4) * (esize == 4 ? 256.0 : 32.0);
+    const double bytes = (double)tiles * 64.0 * K * esize;
+    const double small = fmax(mfma, bytes / 6000.0) + 5000.0;
+    double t;
+    if (esize == 4) t = tiled_cost_f32(M, N, K, tiled.bm, tiled.bn, tiled.slices);
+    else {
+        const double load = (double)cdiv(M, tiled.bm) * cdiv(N, tiled.bn) * tiled.slices / (2.0 * kCUs);
+        t = 5300.0 + (double)cdiv(cdiv(K, 64), tiled.slices) * 720.0 * fmax(1.0, load);
+        if (tiled.slices > 1) t += 8000.0 + (double)tiled.slices * M * N * 8.0 / 2083.0;
+    }
+    return small < t;
+}
+
+int g3_wgrad_slices(int64_t M, int64_t N, int64_t K);
+int g3_long_k_slices(int64_t M, int64_t N, int64_t K);
+
+size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t K, int flags) {
+    const bool with_rowsum = (flags & kWsRowSums) != 0;
+    int slices;
+    if (flags & kWsF32) slices = plan_f32(M, N, K, with_rowsum).slices;
+    else slices = plan_gemm(M, N, K).slices;
+    if (flags & kWsF32) {
+        // (no persistent path)
+    } else if (with_rowsum) {   // a weight gradient may go to the persistent path, with its own number of slices
         const int s3 = g3_wgrad_slices(M, N, K);
         if (s3 > slices) slices = s3;
     } else {             // and so may an input gradient with a very long contraction
@@ -119,94 +179,10 @@ __global__ __launch_bounds__(256) void slice_sum4_kernel(const float* __restrict
     *reinterpret_cast<float4*>(out + i) = a;
 }
 
-static hipError_t slice_sum(const float* part, float* out, int64_t count, int slices, hipStream_t s) {
+hipError_t slice_sum(const float* part, float* out, int64_t count, int slices, hipStream_t s) {
     if (count % 4 == 0 && aligned16(part) && aligned16(out))
         return launch_timed(kcSliceSum, slice_sum4_kernel, dim3(cdiv(count / 4, 256)), dim3(256), 0, s, part, out, count, slices);
     return launch_timed(kcSliceSum, slice_sum_kernel, dim3(cdiv(count, 256)), dim3(256), 0, s, part, out, count, slices);
-}
-
-// slice length (whole k-tiles) and the number of slices really launched
-static void slice_geometry(int64_t K, int want, int ktile, int& per, int& nz) {
-    if (want < 1) want = 1;
-    per = cdiv(cdiv(K, want), ktile) * ktile;
-    if (per < ktile) per = ktile;
-    nz = K > 0 ? cdiv(K, per) : 1;
-}
-
-// ---- MFMA path --------------------------------------------------------------------------------
-template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
-static hipError_t launch2_inst(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
-                               int nz, hipStream_t s) {
-    constexpr int lds = gemm2_lds_bytes<BM, BN, AOp, BOp>();
-    auto kern = gemm2_kernel<BM, BN, D, ROWSUM, AOp, BOp, Epi>;
-    if (lds > 64 * 1024) {
-        // more LDS than the default per-workgroup limit: raise it once per kernel instance
-        static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (attr != hipSuccess) return attr;
-    }
-    dim3 grid(cdiv(N, BN), cdiv(M, BM), nz);
-    // the XCDs split the operand with more rows between them and each reads the other one whole
-    const int col_major = N > M ? 1 : 0;
-    return launch_timed(kc, kern, grid, dim3(256), lds, s, A, B, epi, M, N, K, per, col_major,
-                        (N % 8 == 0 && epi.wide_ok()) ? 1 : 0, FastDiv(grid.x * grid.y), FastDiv(col_major ? grid.y : grid.x));
-}
-
-// tile: the plan's tile edge.  Where it is 64, the output has 512 rows or more and 128 x 64 tiles still make 192
-// workgroups, the tiles are 128 rows tall unless the caller needs them square (`square`): a 128 x 64 tile reads a
-// quarter less LDS per MFMA than a 64 x 64 one, and with the stages' kernels sharing the device that outweighs
-// having half as many workgroups (measured: GPT-2 and ResNet-50 steps 1 % shorter, VGG-16 1-2 %; 128 x 128 and
-// 64 x 128 for the same launches did worse; below 192 workgroups the launch itself gets slower and the step no faster).
-template <bool ROWSUM, class AOp, class BOp, class Epi>
-static hipError_t launch2_tile(int kc, int tile, bool square, const AOp& A, const BOp& B, const Epi& epi, int M, int N,
-                               int K, int per, int nz, hipStream_t s) {
-    if (tile == 128) return launch2_inst<128, 128, 2, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
-    if constexpr (!ROWSUM) {
-        if (!square && M >= 512 && (int64_t)cdiv(M, 128) * cdiv(N, 64) * nz >= 192)
-            return launch2_inst<128, 64, 2, false>(kc, A, B, epi, M, N, K, per, nz, s);
-    }
-    return launch2_inst<64, 64, 4, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
-}
-
-// Forward / input-gradient style GEMM: epilogue `epi` applied once per output element.
-// tile: 0 = the plan's choice, else the edge of the square tiles to use (the slices stay the plan's)
-template <class AOp, class BOp, class Epi>
-static hipError_t run2(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, float* ws,
-                       hipStream_t s, int tile = 0) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    GemmPlan p = plan_gemm(M, N, K);
-    if (tile) p.tile = tile;
-    int per, nz;
-    slice_geometry(K, ws ? p.slices : 1, kBK2, per, nz);
-    if (nz <= 1) return launch2_tile<false>(kc, p.tile, tile != 0, A, B, epi, M, N, K, per, nz, s);
-    EpiPartial part{ws, N, (int64_t)M * N};
-    hipError_t e = launch2_tile<false>(kc, p.tile, tile != 0, A, B, part, M, N, K, per, nz, s);
-    if (e != hipSuccess) return e;
-    int64_t total = (int64_t)M * N;
-    if (N % 8 == 0 && epi.wide_ok() && aligned16(ws))
-        return launch_timed(kcSplitFinish, splitk_finish8_kernel<Epi>, dim3(cdiv(total / 8, 256)), dim3(256), 0, s,
-                            (const float*)ws, epi, M, N, nz);
-    return launch_timed(kcSplitFinish, splitk_finish_kernel<Epi>, dim3(cdiv(total, 256)), dim3(256), 0, s,
-                        (const float*)ws, epi, M, N, nz);
-}
-
-// Weight-gradient style GEMM: fp32 result [rows x cols] followed by the row sums of A (bias gradient).
-template <class AOp, class BOp>
-static hipError_t run2_wgrad(int kc, const AOp& A, const BOp& B, float* gw, int rows, int cols, int64_t K,
-                             float* ws, hipStream_t s) {
-    GemmPlan p = plan_gemm(rows, cols, K);
-    int per, nz;
-    slice_geometry(K, ws ? p.slices : 1, kBK2, per, nz);
-    int64_t count = (int64_t)rows * cols + rows;
-    EpiWgrad epi{nz > 1 ? ws : gw, cols, (int64_t)rows * cols, count};
-    hipError_t e = launch2_tile<true>(kc, p.tile, true, A, B, epi, rows, cols, (int)K, per, nz, s);
-    if (e != hipSuccess || nz <= 1) return e;
-    return slice_sum((const float*)ws, gw, count, nz, s);
-}
-
-static int one_slice(int64_t K, int ktile) {
-    int per = cdiv(K, ktile) * ktile;
-    return per < ktile ? ktile : per;
 }
 
 // ---- persistent MFMA path (gemm3.hip.h): large dense contractions --------------------------------------
@@ -224,7 +200,7 @@ constexpr int kG3Tile = 256;
 static int64_t g3_tiles(int64_t M, int64_t N) { return (int64_t)cdiv(M, kG3Tile) * cdiv(N, kG3Tile); }
 // k-slices of a weight-gradient contraction on the persistent path (0: leave it to the other path).  Measured:
 // the path pays once a launch has about as many (tile, slice) units as the device has compute units.
-static int g3_wgrad_slices(int64_t M, int64_t N, int64_t K) {
+int g3_wgrad_slices(int64_t M, int64_t N, int64_t K) {
     if (K % 64 != 0 || M % 8 != 0 || N % 8 != 0) return 0;
     const int64_t tiles = g3_tiles(M, N);
     int64_t s = tiles >= 192 ? 1 : 256 / tiles;
@@ -254,7 +230,7 @@ static bool g3_narrow_ok(int64_t M, int64_t N, int64_t K) {
 // 96 tiles, k = 32000) goes to the persistent kernel in k-slices: the slice count is the one whose (tile, slice) units
 // fill whole rounds of the device best, weighed against the fp32 partial sums it writes and the finishing pass reads
 // (rates measured: 1 PFLOP/s in the k-loop, 5 TB/s for the partial sums).  0: leave it to the tiled kernel.
-static int g3_long_k_slices(int64_t M, int64_t N, int64_t K) {
+int g3_long_k_slices(int64_t M, int64_t N, int64_t K) {
     if (K % 64 != 0 || N % 8 != 0 || K < 8192) return 0;
     const int64_t tiles = g3_tiles(M, N);
     if (tiles >= 192 || tiles < 32 || (int64_t)cdiv(N, 256) * 256 * 3 > N * 4) return 0;
@@ -325,70 +301,30 @@ static hipError_t launch3(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>&
     return launch3_inst<256, 256, 2, 4, 2, 1, AKC, BKC, ROWSUM>(kc, A, B, epi, M, N, K, plan, s);
 }
 
-// ---- element-wise fallbacks ------------------------------------------------------------------
-template <bool ROWSUM, class AOp, class BOp, class Epi>
-static hipError_t launch_bf16(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
-                              int nz, hipStream_t s) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    dim3 grid(cdiv(N, 64), cdiv(M, 64), nz);
-    return launch_timed(kc, gemm_bf16_kernel<64, 64, ROWSUM, AOp, BOp, Epi>, grid, dim3(256), 0, s, A, B, epi, M, N,
-                        K, per);
-}
-
-template <bool ROWSUM, class AOp, class BOp, class Epi>
-static hipError_t launch_f32(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
-                             int nz, hipStream_t s) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    dim3 grid(cdiv(N, 64), cdiv(M, 64), nz);
-    return launch_timed(kc, gemm_f32_kernel<ROWSUM, AOp, BOp, Epi>, grid, dim3(256), 0, s, A, B, epi, M, N, K, per);
-}
-
-template <typename T, class AOp, class BOp>
-static hipError_t wgrad_fallback(int kc, const AOp& A, const BOp& B, float* gw, int rows, int cols, int64_t K, float* ws,
-                                 hipStream_t s) {
-    GemmPlan p = plan_gemm(rows, cols, K);
-    constexpr int ktile = sizeof(T) == 2 ? kBK : 16;
-    int per, nz;
-    slice_geometry(K, ws ? p.slices : 1, ktile, per, nz);
-    int64_t count = (int64_t)rows * cols + rows;
-    EpiWgrad epi{nz > 1 ? ws : gw, cols, (int64_t)rows * cols, count};
-    hipError_t e;
-    if constexpr (sizeof(T) == 2)
-        e = launch_bf16<true>(kc, A, B, epi, rows, cols, (int)K, per, nz, s);
-    else
-        e = launch_f32<true>(kc, A, B, epi, rows, cols, (int)K, per, nz, s);
-    if (e != hipSuccess || nz <= 1) return e;
-    return slice_sum((const float*)ws, gw, count, nz, s);
-}
-
 // ---------------------------------------------------------------------------------------- dense
 // The dense contractions with the kernel class they are accounted under as a parameter: a 1x1 convolution with unit
 // stride and no padding is the same contraction over its positions.
+template <class Epi>
+static hipError_t dense_forward_bf16(int kc, const bf16_t* x, const bf16_t* w, const Epi& epi, bool aligned, int B, int Din, int Dout, float* ws,
+                                     hipStream_t s) {
+    if (aligned && g3_forward_ok(B, Dout, Din) && aligned16(x) && aligned16(w)) {
+        G3Operand<true> A{x, B, Din};
+        G3Operand<true> Bv{w, Dout, Din};
+        return launch3<true, true, false>(kc, A, Bv, epi, B, Dout, Din, g3_plan(B, Dout, Din, 1), s);
+    }
+    return dense_forward_t<bf16_t>(kc, x, w, epi, B, Din, Dout, ws, s);
+}
+
 static hipError_t dense_forward_as(int kc, int dtype, const void* x, const void* w, const float* bias, void* y, int B, int Din,
                                    int Dout, int relu, int out_f32, const void* res, void* zout, float* ws, hipStream_t s) {
-    if (dtype == kBF16) {
-        const bool fast = (Din % 8 == 0) && aligned16(x) && aligned16(w);
-        if (fast && g3_forward_ok(B, Dout, Din) && aligned16(y) && aligned16(bias) && aligned16(res) && aligned16(zout)) {
-            G3Operand<true> A{(const bf16_t*)x, B, Din};
-            G3Operand<true> Bv{(const bf16_t*)w, Dout, Din};
-            const G3Plan plan = g3_plan(B, Dout, Din, 1);
-            if (out_f32) return launch3<true, true, false>(kc, A, Bv, EpiBiasAct<float>{(float*)y, bias, Dout, relu}, B, Dout, Din, plan, s);
-            return launch3<true, true, false>(kc, A, Bv, EpiBiasAct<bf16_t>{(bf16_t*)y, bias, Dout, relu, (const bf16_t*)res, (bf16_t*)zout}, B, Dout, Din, plan, s);
-        }
-        if (fast) {
-            DenseKC A{(const bf16_t*)x, B, Din, Din};
-            DenseKC Bv{(const bf16_t*)w, Dout, Din, Din};
-            if (out_f32) return run2(kc, A, Bv, EpiBiasAct<float>{(float*)y, bias, Dout, relu}, B, Dout, Din, ws, s);
-            return run2(kc, A, Bv, EpiBiasAct<bf16_t>{(bf16_t*)y, bias, Dout, relu, (const bf16_t*)res, (bf16_t*)zout}, B, Dout, Din, ws, s);
-        }
-        DenseView<bf16_t, true> A{(const bf16_t*)x, B, Din, Din, 0};
-        DenseView<bf16_t, true> Bv{(const bf16_t*)w, Dout, Din, Din, 0};
-        if (out_f32) return launch_bf16<false>(kc, A, Bv, EpiBiasAct<float>{(float*)y, bias, Dout, relu}, B, Dout, Din, one_slice(Din, kBK), 1, s);
-        return launch_bf16<false>(kc, A, Bv, EpiBiasAct<bf16_t>{(bf16_t*)y, bias, Dout, relu, (const bf16_t*)res, (bf16_t*)zout}, B, Dout, Din, one_slice(Din, kBK), 1, s);
-    }
-    DenseView<float, true> A{(const float*)x, B, Din, Din, 0};
-    DenseView<float, true> Bv{(const float*)w, Dout, Din, Din, 0};
-    return launch_f32<false>(kc, A, Bv, EpiBiasAct<float>{(float*)y, bias, Dout, relu, (const float*)res, (float*)zout}, B, Dout, Din, one_slice(Din, 16), 1, s);
+    if (dtype != kBF16)
+        return dense_forward_f32(kc, (const float*)x, (const float*)w, EpiBiasAct<float>{(float*)y, bias, Dout, relu, (const float*)res, (float*)zout},
+                                 B, Din, Dout, ws, s);
+    const bool aligned = aligned16(y) && aligned16(bias) && aligned16(res) && aligned16(zout);
+    if (out_f32)
+        return dense_forward_bf16(kc, (const bf16_t*)x, (const bf16_t*)w, EpiBiasAct<float>{(float*)y, bias, Dout, relu}, aligned, B, Din, Dout, ws, s);
+    return dense_forward_bf16(kc, (const bf16_t*)x, (const bf16_t*)w, EpiBiasAct<bf16_t>{(bf16_t*)y, bias, Dout, relu, (const bf16_t*)res, (bf16_t*)zout},
+                              aligned, B, Din, Dout, ws, s);
 }
 
 hipError_t dense_forward(int dtype, const void* x, const void* w, const float* bias, void* y, int B, int Din,
@@ -424,18 +360,10 @@ static hipError_t dense_dgrad_as(int kc, int dtype, const void* dy, const void* 
             G3Operand<false> Bv{(const bf16_t*)w, Din, Din};
             return launch3_inst<256, 128, 2, 2, 2, 1, true, false, false>(kc, A, Bv, epi, B, Din, Dout, g3_plan(B, Din, Dout, 1, 256, 128), s);
         }
-        if (fast) {
-            DenseKC A{(const bf16_t*)dy, B, Dout, Dout};
-            DenseRC Bv{(const bf16_t*)w, Din, Dout, Din};
-            return run2(kc, A, Bv, epi, B, Din, Dout, ws, s);
-        }
-        DenseView<bf16_t, true> A{(const bf16_t*)dy, B, Dout, Dout, 0};
-        DenseView<bf16_t, false> Bv{(const bf16_t*)w, Din, Dout, Din, 0};
-        return launch_bf16<false>(kc, A, Bv, epi, B, Din, Dout, one_slice(Dout, kBK), 1, s);
+        return dense_dgrad_t<bf16_t>(kc, (const bf16_t*)dy, (const bf16_t*)w, epi, B, Din, Dout, ws, s);
     }
-    DenseView<float, true> A{(const float*)dy, B, Dout, Dout, 0};
-    DenseView<float, false> Bv{(const float*)w, Din, Dout, Din, 0};
-    return launch_f32<false>(kc, A, Bv, EpiMask<float, float>{(float*)dx, (const float*)mask, Din, mask_mode, (const float*)add}, B, Din, Dout, one_slice(Dout, 16), 1, s);
+    return dense_dgrad_f32(kc, (const float*)dy, (const float*)w,
+                           EpiMask<float, float>{(float*)dx, (const float*)mask, Din, mask_mode, (const float*)add}, B, Din, Dout, ws, s);
 }
 
 hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, int mask_mode,
@@ -459,18 +387,9 @@ static hipError_t dense_wgrad_as(int kc, int dtype, const void* dy, const void* 
             if (e != hipSuccess || plan.slices <= 1) return e;
             return slice_sum((const float*)ws, gw, count, plan.slices, s);
         }
-        if (fast) {
-            DenseRC A{(const bf16_t*)dy, Dout, B, Dout};
-            DenseRC Bv{(const bf16_t*)x, Din, B, Din};
-            return run2_wgrad(kc, A, Bv, gw, Dout, Din, B, ws, s);
-        }
-        DenseView<bf16_t, false> A{(const bf16_t*)dy, Dout, B, Dout, 0};
-        DenseView<bf16_t, false> Bv{(const bf16_t*)x, Din, B, Din, 0};
-        return wgrad_fallback<bf16_t>(kc, A, Bv, gw, Dout, Din, B, ws, s);
+        return dense_wgrad_t<bf16_t>(kc, (const bf16_t*)dy, (const bf16_t*)x, gw, B, Din, Dout, ws, s);
     }
-    DenseView<float, false> A{(const float*)dy, Dout, B, Dout, 0};
-    DenseView<float, false> Bv{(const float*)x, Din, B, Din, 0};
-    return wgrad_fallback<float>(kc, A, Bv, gw, Dout, Din, B, ws, s);
+    return dense_wgrad_f32(kc, (const float*)dy, (const float*)x, gw, B, Din, Dout, ws, s);
 }
 
 hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout, float* ws,
@@ -479,155 +398,49 @@ hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int 
 }
 
 // ---------------------------------------------------------------------------------- convolution
-static ConvGeom geom(const ConvShape& c) {
-    return ConvGeom{c.B, c.H, c.W, c.Cin, c.Ho, c.Wo, c.Cout, c.R, c.S, c.stride, c.pad};
-}
-
-// The MFMA loaders index positions with 24-bit multiplies and tensors with 32-bit element offsets.
-static bool small_enough(const ConvShape& c) {
-    const int64_t pin = (int64_t)c.B * c.H * c.W, pout = (int64_t)c.B * c.Ho * c.Wo;
-    const int64_t wel = (int64_t)c.Cout * c.R * c.S * c.Cin;
-    return pin < (1 << 24) && pout < (1 << 24) && pin * c.Cin < (int64_t(1) << 31) &&
-           pout * c.Cout < (int64_t(1) << 31) && wel < (int64_t(1) << 31) && c.Cin < (1 << 20) && c.Cout < (1 << 20);
-}
-
-static ConvGeom2 geom2(const ConvShape& c) {
-    ConvGeom2 g;
-    g.B = c.B; g.H = c.H; g.W = c.W; g.Cin = c.Cin; g.Ho = c.Ho; g.Wo = c.Wo; g.Cout = c.Cout;
-    g.R = c.R; g.S = c.S; g.stride = c.stride; g.pad = c.pad;
-    g.d_howo = FastDiv(c.Ho * c.Wo); g.d_wo = FastDiv(c.Wo);
-    g.d_hw = FastDiv(c.H * c.W); g.d_w = FastDiv(c.W);
-    g.d_scin = FastDiv(c.S * c.Cin); g.d_cin = FastDiv(c.Cin);
-    g.d_scout = FastDiv(c.S * c.Cout); g.d_cout = FastDiv(c.Cout);
-    g.d_stride = FastDiv(c.stride);
-    return g;
-}
-
-// A 1x1 convolution with unit stride and no padding on NHWC tensors IS a dense layer over the B*H*W positions
-// (weights [Cout][Cin]); bf16 ones take the dense paths, which have plain loaders and the persistent kernel.
-static bool pointwise(int dtype, const ConvShape& c) {
-    return dtype == kBF16 && c.R == 1 && c.S == 1 && c.stride == 1 && c.pad == 0 &&
-           (int64_t)c.B * c.H * c.W < (int64_t(1) << 31);
-}
-
 hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y, const ConvShape& c,
                         int relu, float* ws, hipStream_t s) {
-    int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
-    if (pointwise(dtype, c))
-        return dense_forward_as(kcConvFwd, dtype, x, w, bias, y, M, c.Cin, c.Cout, relu ? kActRelu : kActNone, 0, nullptr, nullptr,
-                                ws, s);
-    if (dtype == kBF16) {
-        EpiBiasAct<bf16_t> epi{(bf16_t*)y, bias, c.Cout, relu};
-        if (c.Cin % 8 == 0 && aligned16(x) && aligned16(w) && small_enough(c)) {
-            ConvFwdA2 A{(const bf16_t*)x, geom2(c), M, K};
-            DenseKC Bv{(const bf16_t*)w, c.Cout, K, K};
-            return run2(kcConvFwd, A, Bv, epi, M, c.Cout, K, ws, s);
-        }
-        ConvFwdA<bf16_t> A{(const bf16_t*)x, geom(c), M, K, 0};
-        DenseView<bf16_t, true> Bv{(const bf16_t*)w, c.Cout, K, K, 0};
-        return launch_bf16<false>(kcConvFwd, A, Bv, epi, M, c.Cout, K, one_slice(K, kBK), 1, s);
-    }
-    ConvFwdA<float> A{(const float*)x, geom(c), M, K, 0};
-    DenseView<float, true> Bv{(const float*)w, c.Cout, K, K, 0};
-    return launch_f32<false>(kcConvFwd, A, Bv, EpiBiasAct<float>{(float*)y, bias, c.Cout, relu}, M, c.Cout, K, one_slice(K, 16), 1, s);
+    if (dtype != kBF16)
+        return conv_forward_f32((const float*)x, (const float*)w, EpiBiasAct<float>{(float*)y, bias, c.Cout, relu ? kActRelu : kActNone}, c, ws, s);
+    if (pointwise(c))
+        return dense_forward_as(kcConvFwd, dtype, x, w, bias, y, c.B * c.Ho * c.Wo, c.Cin, c.Cout, relu ? kActRelu : kActNone, 0, nullptr,
+                                nullptr, ws, s);
+    return conv_forward_t<bf16_t>((const bf16_t*)x, (const bf16_t*)w, EpiBiasAct<bf16_t>{(bf16_t*)y, bias, c.Cout, relu}, c, ws, s);
 }
 
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain,
                                const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c,
                                float* ws, hipStream_t s) {
-    int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
-    if (dtype == kBF16) {
-        EpiConvAffine<bf16_t> epi{(bf16_t*)z, bias, c.Cout, gain, shift, (bf16_t*)aout, (const bf16_t*)res, (bf16_t*)yout, relu};
-        if (pointwise(dtype, c) && c.Cin % 8 == 0 && aligned16(x) && aligned16(w)) {
-            if (g3_forward_ok(M, c.Cout, K) && aligned16(z) && aligned16(bias) && aligned16(gain) && aligned16(shift) &&
-                aligned16(aout) && aligned16(res) && aligned16(yout)) {
-                G3Operand<true> A{(const bf16_t*)x, M, K};
-                G3Operand<true> Bv{(const bf16_t*)w, c.Cout, K};
-                return launch3<true, true, false>(kcConvFwd, A, Bv, epi, M, c.Cout, K, g3_plan(M, c.Cout, K, 1), s);
-            }
-            DenseKC A{(const bf16_t*)x, M, K, K};
-            DenseKC Bv{(const bf16_t*)w, c.Cout, K, K};
-            return run2(kcConvFwd, A, Bv, epi, M, c.Cout, K, ws, s);
-        }
-        if (c.Cin % 8 == 0 && aligned16(x) && aligned16(w) && small_enough(c)) {
-            ConvFwdA2 A{(const bf16_t*)x, geom2(c), M, K};
-            DenseKC Bv{(const bf16_t*)w, c.Cout, K, K};
-            return run2(kcConvFwd, A, Bv, epi, M, c.Cout, K, ws, s);
-        }
-        ConvFwdA<bf16_t> A{(const bf16_t*)x, geom(c), M, K, 0};
-        DenseView<bf16_t, true> Bv{(const bf16_t*)w, c.Cout, K, K, 0};
-        return launch_bf16<false>(kcConvFwd, A, Bv, epi, M, c.Cout, K, one_slice(K, kBK), 1, s);
+    if (dtype != kBF16)
+        return conv_affine_f32((const float*)x, (const float*)w,
+                               EpiConvAffine<float>{(float*)z, bias, c.Cout, gain, shift, (float*)aout, (const float*)res, (float*)yout, relu}, c, ws, s);
+    const int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
+    const bf16_t *xb = (const bf16_t*)x, *wb = (const bf16_t*)w;
+    const EpiConvAffine<bf16_t> epi{(bf16_t*)z, bias, c.Cout, gain, shift, (bf16_t*)aout, (const bf16_t*)res, (bf16_t*)yout, relu};
+    if (pointwise(c) && c.Cin % 8 == 0 && aligned16(x) && aligned16(w)) {
+        if (g3_forward_ok(M, c.Cout, K) && aligned16(z) && aligned16(bias) && aligned16(gain) && aligned16(shift) &&
+            aligned16(aout) && aligned16(res) && aligned16(yout))
+            return launch3<true, true, false>(kcConvFwd, G3Operand<true>{xb, M, K}, G3Operand<true>{wb, c.Cout, K}, epi, M, c.Cout, K,
+                                              g3_plan(M, c.Cout, K, 1), s);
+        return run2(kcConvFwd, DenseKC<bf16_t>{xb, M, K, K}, DenseKC<bf16_t>{wb, c.Cout, K, K}, epi, M, c.Cout, K, ws, s);
     }
-    ConvFwdA<float> A{(const float*)x, geom(c), M, K, 0};
-    DenseView<float, true> Bv{(const float*)w, c.Cout, K, K, 0};
-    EpiConvAffine<float> epi{(float*)z, bias, c.Cout, gain, shift, (float*)aout, (const float*)res, (float*)yout, relu};
-    return launch_f32<false>(kcConvFwd, A, Bv, epi, M, c.Cout, K, one_slice(K, 16), 1, s);
+    return conv_forward_t<bf16_t>(xb, wb, epi, c, ws, s);
 }
 
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add,
                       const ConvShape& c, float* ws, hipStream_t s) {
-    int M = c.B * c.H * c.W, K = c.R * c.S * c.Cout;
-    if (pointwise(dtype, c)) return dense_dgrad_as(kcConvDgrad, dtype, dy, w, dx, mask, kActRelu, add, M, c.Cin, c.Cout, ws, s);
-    if (dtype == kBF16) {
-        EpiMask<bf16_t, bf16_t> epi{(bf16_t*)dx, (const bf16_t*)mask, c.Cin, kActRelu, (const bf16_t*)add};
-        if (c.Cin % 8 == 0 && c.Cout % 8 == 0 && aligned16(dy) && aligned16(w) && small_enough(c)) {
-            if (c.stride == 2 && c.H % 2 == 0 && c.W % 2 == 0) {
-                // Rows ordered by the parity of their position, each class walking only the filter taps that reach it:
-                // k extent of the largest class; every class a whole number of tiles; the 16-byte epilogue (the one
-                // that asks the loader where a row lies in memory), also for the partial sums of a split.
-                const int Kp = ((c.R + 1) / 2) * ((c.S + 1) / 2) * c.Cout;
-                const GemmPlan plan = plan_gemm(M, c.Cin, Kp);
-                const int Mc = M / 4;
-                int per, nz;
-                slice_geometry(Kp, ws ? plan.slices : 1, kBK2, per, nz);
-                const bool split_ok = nz <= 1 || (aligned16(ws) && ((int64_t)M * c.Cin) % 4 == 0);
-                // (where a class is no whole number of the plan's tiles, smaller tiles still pay for a filter with
-                // several taps; a 1x1 filter's launch is mostly epilogue either way and keeps the plain order then)
-                const int tile = (Mc % plan.tile == 0 || c.R * c.S == 1) ? plan.tile : 64;
-                if (Mc % tile == 0 && epi.wide_ok() && split_ok) {
-                    ParityGeom pg;
-                    pg.Mc = Mc;
-                    pg.W2 = c.W / 2;
-                    pg.d_mc = FastDiv(Mc);
-                    pg.d_h2w2 = FastDiv((c.H / 2) * (c.W / 2));
-                    pg.d_w2 = FastDiv(c.W / 2);
-                    ConvDgradA2P A{(const bf16_t*)dy, geom2(c), M, Kp, pg, {}};
-                    ConvDgradB2P Bv{(const bf16_t*)w, geom2(c), c.Cin, Kp, pg, {}};
-                    return run2(kcConvDgrad, A, Bv, epi, M, c.Cin, Kp, ws, s, tile);
-                }
-            }
-            ConvDgradA2 A{(const bf16_t*)dy, geom2(c), M, K};
-            ConvDgradB2 Bv{(const bf16_t*)w, geom2(c), c.Cin, K};
-            return run2(kcConvDgrad, A, Bv, epi, M, c.Cin, K, ws, s);
-        }
-        ConvDgradA<bf16_t> A{(const bf16_t*)dy, geom(c), M, K, 0};
-        ConvDgradB<bf16_t> Bv{(const bf16_t*)w, geom(c), c.Cin, K};
-        return launch_bf16<false>(kcConvDgrad, A, Bv, epi, M, c.Cin, K, one_slice(K, kBK), 1, s);
-    }
-    ConvDgradA<float> A{(const float*)dy, geom(c), M, K, 0};
-    ConvDgradB<float> Bv{(const float*)w, geom(c), c.Cin, K};
-    return launch_f32<false>(kcConvDgrad, A, Bv, EpiMask<float, float>{(float*)dx, (const float*)mask, c.Cin, kActRelu, (const float*)add}, M, c.Cin, K, one_slice(K, 16), 1, s);
+    if (dtype != kBF16)
+        return conv_dgrad_f32((const float*)dy, (const float*)w, EpiMask<float, float>{(float*)dx, (const float*)mask, c.Cin, kActRelu, (const float*)add},
+                              c, ws, s);
+    if (pointwise(c)) return dense_dgrad_as(kcConvDgrad, dtype, dy, w, dx, mask, kActRelu, add, c.B * c.H * c.W, c.Cin, c.Cout, ws, s);
+    return conv_dgrad_t<bf16_t>((const bf16_t*)dy, (const bf16_t*)w,
+                                EpiMask<bf16_t, bf16_t>{(bf16_t*)dx, (const bf16_t*)mask, c.Cin, kActRelu, (const bf16_t*)add}, c, ws, s);
 }
 
-hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, float* ws,
-                      hipStream_t s) {
-    int rows = c.Cout, cols = c.R * c.S * c.Cin;
-    int64_t K = (int64_t)c.B * c.Ho * c.Wo;
-    if (pointwise(dtype, c)) return dense_wgrad_as(kcConvWgrad, dtype, dy, x, gw, (int)K, c.Cin, c.Cout, ws, s);
-    if (dtype == kBF16) {
-        if (c.Cin % 8 == 0 && c.Cout % 8 == 0 && aligned16(dy) && aligned16(x) && small_enough(c)) {
-            DenseRC A{(const bf16_t*)dy, rows, (int)K, c.Cout};
-            const int rows64 = kBK2 / c.Wo;
-            ConvWgradB2 Bv{(const bf16_t*)x, geom2(c), cols, (int)K, kBK2 % c.Wo, rows64 % c.Ho, rows64 / c.Ho};
-            return run2_wgrad(kcConvWgrad, A, Bv, gw, rows, cols, K, ws, s);
-        }
-        DenseView<bf16_t, false> A{(const bf16_t*)dy, rows, (int)K, c.Cout, 0};
-        ConvWgradB<bf16_t> Bv{(const bf16_t*)x, geom(c), cols, (int)K};
-        return wgrad_fallback<bf16_t>(kcConvWgrad, A, Bv, gw, rows, cols, K, ws, s);
-    }
-    DenseView<float, false> A{(const float*)dy, rows, (int)K, c.Cout, 0};
-    ConvWgradB<float> Bv{(const float*)x, geom(c), cols, (int)K};
-    return wgrad_fallback<float>(kcConvWgrad, A, Bv, gw, rows, cols, K, ws, s);
+hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, float* ws, hipStream_t s) {
+    if (dtype != kBF16) return conv_wgrad_f32((const float*)dy, (const float*)x, gw, c, ws, s);
+    if (pointwise(c)) return dense_wgrad_as(kcConvWgrad, dtype, dy, x, gw, c.B * c.Ho * c.Wo, c.Cin, c.Cout, ws, s);
+    return conv_wgrad_t<bf16_t>((const bf16_t*)dy, (const bf16_t*)x, gw, c, ws, s);
 }
 
 }  // namespace tmps

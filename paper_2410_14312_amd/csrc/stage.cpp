@@ -77,6 +77,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
     st.ws_fwd_bytes = 0;
     const int mb = cfg->micro_batch;
     const int M = mb * cfg->n_micro;
+    const int f32 = cfg->dtype == TMPS_F32 ? kWsF32 : 0;
     const int64_t rows_all = (int64_t)cfg->max_stash * mb;
     int64_t poff = 0, gmax = 0;
     size_t soff = 0, ws = 0;
@@ -119,11 +120,11 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                     any_skip = true;
                 }
                 const int64_t rf = (int64_t)mb * L.rps, rb = (int64_t)M * L.rps;
-                L.ws_fwd_elems = gemm_workspace_elems(rf, d[1], d[0], 0);
-                L.ws_elems = std::max({L.ws_fwd_elems, gemm_workspace_elems(rb, d[0], d[1], 0),
-                                       gemm_workspace_elems(d[1], d[0], rb, 1)});
+                L.ws_fwd_elems = gemm_workspace_elems(rf, d[1], d[0], f32);
+                L.ws_elems = std::max({L.ws_fwd_elems, gemm_workspace_elems(rb, d[0], d[1], f32),
+                                       gemm_workspace_elems(d[1], d[0], rb, kWsRowSums | f32)});
                 for (int r = 2; r <= cfg->n_micro; ++r)   // (micro-batches forwarded together)
-                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems(r * rf, d[1], d[0], 0));
+                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems(r * rf, d[1], d[0], f32));
                 break;
             }
             case TMPS_CONV2D: {
@@ -138,12 +139,15 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 L.out_elems = (int64_t)c.Ho * c.Wo * c.Cout;
                 L.w_count = (int64_t)c.Cout * c.R * c.S * c.Cin; L.b_count = c.Cout;
                 const int64_t kf = (int64_t)c.R * c.S * c.Cin, kd = (int64_t)c.R * c.S * c.Cout;
-                L.ws_fwd_elems = gemm_workspace_elems((int64_t)mb * c.Ho * c.Wo, c.Cout, kf, 0);
+                L.ws_fwd_elems = gemm_workspace_elems((int64_t)mb * c.Ho * c.Wo, c.Cout, kf, f32);
                 L.ws_elems = std::max({L.ws_fwd_elems,
-                                       gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin, kd, 0),
-                                       gemm_workspace_elems(c.Cout, kf, (int64_t)M * c.Ho * c.Wo, 1)});
+                                       gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin, kd, f32),
+                                       gemm_workspace_elems(c.Cout, kf, (int64_t)M * c.Ho * c.Wo, kWsRowSums | f32)});
+                if (c.stride == 2)   // (the input gradient may walk each position's own taps only)
+                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin,
+                                                                           (int64_t)((c.R + 1) / 2) * ((c.S + 1) / 2) * c.Cout, f32));
                 for (int r = 2; r <= cfg->n_micro; ++r)
-                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)r * mb * c.Ho * c.Wo, c.Cout, kf, 0));
+                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)r * mb * c.Ho * c.Wo, c.Cout, kf, f32));
                 break;
             }
             case TMPS_MAXPOOL: {

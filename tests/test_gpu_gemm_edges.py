@@ -1,0 +1,47 @@
+"""Contractions at the edges of their kernels' ranges: the small kernel (32 x 32 tiles, the k range shared by the waves)
+at its tile, fragment and wave-count borders, matrices whose rows are not whole 16-byte chunks (ragged loaders) or less
+than one (gathering loaders), convolutions over channel counts that are not whole chunks, and the tiled fp32 kernel
+with and without k-slices.  Against the oracle, all three passes, in both types."""
+import pytest
+
+from tests.test_gpu_stage import run_stage_case
+from workloads.configs import conv, linear
+
+pytestmark = pytest.mark.gpu
+
+DENSE = [
+    # (din, dout, micro, N)
+    (3, 5, 2, 2),          # rows of less than a chunk: gathered
+    (8, 4, 1, 1),          # one row
+    (16, 33, 33, 1),       # one fragment pair of k (bf16) / two (fp32), a tile and a column over
+    (17, 31, 16, 2),       # a tail of one k
+    (127, 129, 31, 2),     # 4 and 8 waves, tails in every pass
+    (513, 65, 47, 1),      # 16 waves and a tail
+    (1000, 10, 235, 1),    # a narrow output layer
+    (72, 2601, 40, 2),     # odd output: ragged rows of dY in both gradients
+    (1001, 1003, 300, 1),  # ragged everywhere, tiled
+    (264, 520, 700, 1),    # fp32 tiles of several sizes, ragged last tiles
+    (2048, 96, 512, 1),    # few tiles, long k: k-slices
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("din,dout,micro,N", DENSE)
+def test_dense_edges(dtype, din, dout, micro, N):
+    run_stage_case([linear(din, dout, False)], dtype, micro, N, seed=din + 3 * dout)
+
+
+CONV = [
+    # (h, w, cin, cout, r, stride, pad, micro, N)
+    (9, 7, 3, 5, 3, 1, 1, 2, 2),     # neither channel count a chunk
+    (8, 8, 6, 16, 3, 2, 1, 2, 2),    # stride 2, input channels no chunk (of 8)
+    (8, 8, 16, 10, 1, 1, 0, 2, 2),   # 1x1: a dense layer with ragged output rows
+    (12, 12, 4, 12, 3, 2, 1, 3, 1),  # whole chunks in fp32 only
+    (16, 16, 8, 8, 5, 2, 2, 2, 1),   # 5x5 over parity classes
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("h,w,cin,cout,r,stride,pad,micro,N", CONV)
+def test_conv_edges(dtype, h, w, cin, cout, r, stride, pad, micro, N):
+    run_stage_case([conv(h, w, cin, cout, r, stride, pad, False)], dtype, micro, N, seed=h + cin * cout)
