@@ -87,24 +87,20 @@ Plan2 plan_f32(int64_t M, int64_t N, int64_t K, bool rowsum) {
     return best;
 }
 
-// The small kernel against the tiled plan, both in estimated cycles.  Small: the busiest unit's multiplies (its waves
-// share the k range), or the operands' way from L2 (64 elements per k and tile, some 14 TB/s over the device), whichever
-// is longer.  Tiled in bf16: 720 cycles per k-tile of a workgroup (measured on 1024 x 768 x 768: 0.3 us), up to two
-// workgroups of a unit overlapping.
+// The small kernel against the tiled plan, both in estimated cycles.  Small: its fragment loads touch 32 rows each, so a
+// compute unit's L1 sets the pace: 9.5 cycles per k of a tile in bf16, 18.5 in fp32 (measured from K = 512 to 4096 on 64 to
+// 512 tiles), and a fixed part.  Tiled in bf16: 720 cycles per k-tile of a workgroup (1024 x 768 x 768: 0.3 us), up to two
+// workgroups of a unit overlapping; 9000 cycles for the finishing launch of a split.
 bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& tiled) {
     const int64_t tiles = (int64_t)cdiv(M, 32) * cdiv(N, 32);
     if (tiles > 2 * kCUs) return false;
-    const int gk = esize == 4 ? 8 : 16;
-    const int64_t groups = cdiv(K, gk), nw = groups > 32 ? 16 : groups > 8 ? 8 : 4;
-    const double mfma = (double)cdiv(tiles, kCUs) * cdiv(groups, nw) * (nw / 4) * (esize == 4 ? 256.0 : 32.0);
-    const double bytes = (double)tiles * 64.0 * K * esize;
-    const double small = fmax(mfma, bytes / 6000.0) + 5000.0;
+    const double small = 2500.0 + (double)cdiv(tiles, kCUs) * K * (esize == 4 ? 18.5 : 9.5);
     double t;
     if (esize == 4) t = tiled_cost_f32(M, N, K, tiled.bm, tiled.bn, tiled.slices);
     else {
         const double load = (double)cdiv(M, tiled.bm) * cdiv(N, tiled.bn) * tiled.slices / (2.0 * kCUs);
         t = 5300.0 + (double)cdiv(cdiv(K, 64), tiled.slices) * 720.0 * fmax(1.0, load);
-        if (tiled.slices > 1) t += 8000.0 + (double)tiled.slices * M * N * 8.0 / 2083.0;
+        if (tiled.slices > 1) t += 9000.0 + (double)tiled.slices * M * N * 8.0 / 2083.0;
     }
     return small < t;
 }
