@@ -205,6 +205,42 @@ void build_nodes(RunCtx& c, const std::vector<Task>& tasks) {
                     c.last_of[(size_t)s * c.total_micro + (size_t)n.b0 * c.N + n.j0 + j] = (size_t)n.b0 * c.N + n.j0 + n.count - 1;
 }
 
+// Device time of a pass over `rows` samples, roughly: 5 us for every launch it is expected to make (a contraction one
+// forward and a split now and then, two to three backward; other layers one and two), its operations at the rates that
+// mid-sized contractions reach, and the update at 4 TB/s.
+double pass_us(const tmps_stage& st, int rows, bool backward) {
+    double us = 0.0;
+    for (const LayerRT& L : st.layers) {
+        const int32_t* d = L.d.dims;
+        double flops = 0.0;
+        bool contraction = true;
+        if (L.d.kind == TMPS_LINEAR) flops = 2.0 * L.rps * d[0] * d[1];
+        else if (L.d.kind == TMPS_CONV2D) flops = 2.0 * L.out_elems * d[4] * d[5] * d[2];
+        else contraction = false;
+        us += (contraction ? (backward ? 12.5 : 6.5) : (backward ? 7.5 : 5.0)) + flops * rows * (backward ? 2.0 : 1.0) / (st.asz == 2 ? 250e6 : 60e6);
+    }
+    return backward ? us + 5.0 + (double)st.P * 22.0 / 4e6 : us;
+}
+
+// Whether the whole run is quicker on ONE stream, issued from one host thread.  On K streams it pays for issue threads
+// (about 100 us a run) and for every hand-over from stream to stream (about 25 us in a chain of short passes) and gains
+// what the workers' passes overlap: nothing within a single mini-batch, some 5 % of the work where a mini-batch's
+// micro-batches are forwarded together, some 20 % where mini-batches are short against the pipeline (N <= 2) and in 1F1B
+// order (measured over the four kinds of networks, K = 2 to 4: the tiny fp32 MLP 254 us per two mini-batches on two streams
+// and 113 on one, the bf16 MLP 830 and 600 for four; GPT-2 2 % and its 1F1B run 25 % quicker on four).
+bool serial_is_quicker(const RunCtx& c) {
+    double total = 0.0;
+    size_t nodes = 0;
+    for (int s = 0; s < c.K; ++s)
+        for (const Node& n : c.nodes[s]) {
+            total += pass_us(*c.stages[s], n.kind == kFwd ? n.count * c.mb : c.M, n.kind != kFwd);
+            ++nodes;
+        }
+    const double overlapped = c.n_minibatches == 1 ? 1.0 : (c.one_f1b || c.N <= 2) ? 0.78 : 0.95;
+    const double chain = (double)nodes / c.K * (total / nodes + 25.0);
+    return total <= 100.0 + (overlapped * total > chain ? overlapped * total : chain);
+}
+
 // From one host thread: every node after the nodes it depends on, otherwise in the order of the schedule's time-points.
 int issue_all(RunCtx& c) {
     std::vector<size_t> head(c.K, 0);
@@ -282,6 +318,16 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
     build_nodes(c, tasks);
     c.one_queue = true;
     for (int s = 1; s < K; ++s) c.one_queue = c.one_queue && hip_streams[s] == hip_streams[0];
+    if (!c.one_queue && serial_is_quicker(c)) {
+        // (what the caller has pending on the other streams comes first)
+        for (int s = 1; s < K; ++s) {
+            if (hip_streams[s] == hip_streams[0] || hipStreamQuery((hipStream_t)hip_streams[s]) == hipSuccess) continue;
+            (void)hipGetLastError();   // ("not ready" is an answer, not an error)
+            TMPS_HIP(hipEventRecord(stages[s]->events[0], (hipStream_t)hip_streams[s]));
+            TMPS_HIP(hipStreamWaitEvent((hipStream_t)hip_streams[0], stages[s]->events[0], 0));
+        }
+        c.one_queue = true;
+    }
 
     const char* env = getenv("TMPS_ISSUE_THREADS");
     const bool threaded = K > 1 && !(env && env[0] == '0') && !c.one_queue;
@@ -313,7 +359,7 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
         if (r != TMPS_OK) c.set_error(r);
     }
     const auto t1 = std::chrono::steady_clock::now();
-    for (int s = 0; s < K; ++s) TMPS_HIP(hipStreamSynchronize((hipStream_t)hip_streams[s]));
+    for (int s = 0; s < (c.one_queue ? 1 : K); ++s) TMPS_HIP(hipStreamSynchronize((hipStream_t)hip_streams[s]));
     if (c.err.load() != TMPS_OK) {
         // the mini-batches in flight are lost: free their stash slots, so that the stages can run again
         for (int s = 0; s < K; ++s) {
