@@ -1,0 +1,764 @@
+// Causal multi-head self-attention for gfx950: forward and the query and key/value gradients.
+//
+// The MFMA path (32 or 64 features per head, bf16 or fp32) is a flash-style kernel: a wave owns 32 query rows (or 32 key
+// rows in the key/value-gradient kernel), streams blocks of keys (queries) through LDS and keeps running softmax
+// statistics, so the S x S score matrix never exists in memory.  Products are arranged so that the softmax reduction runs
+// over a lane's own registers: scores are computed TRANSPOSED (keys along the accumulator registers, queries along the
+// lanes), and the probabilities leave the accumulators straight into the B operand of the next MFMA with no shuffle.
+// Operands that the next product needs transposed (V^T, K^T, Q^T, dO^T) are read from their row-major LDS tile: in bf16
+// with the transpose read of gfx950, in fp32 value by value (an fp32 MFMA takes one value per lane).
+// The generic path (any head size) is a plain one-row-per-wave kernel.  The fp32 configurations ran on it before they had
+// an MFMA path: 98 positions, 90 (batch, head) pairs of 64 features, 70 us forward and 260 us backward.
+#include <math.h>
+
+#include <cstdlib>
+#include <type_traits>
+
+#include "gemm2.hip.h"
+#include "kernels.h"
+#include "launch.h"
+
+namespace tmps {
+
+static inline int cdiv_at(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+__device__ __forceinline__ float wsum(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+__device__ __forceinline__ float wmax(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
+// ------------------------------------------------------------------------- generic path
+// qkv rows are [q | k | v] of D features each; head h owns features h*dh .. h*dh+dh-1 of each part.
+// One wave per (batch, head, query row).  Dynamic LDS: S floats (probabilities).
+template <typename T>
+__global__ __launch_bounds__(64) void attn_fwd_row_kernel(const T* __restrict__ qkv, T* __restrict__ o,
+                                                          float* __restrict__ lse, int S, int D, int H, float scale) {
+    extern __shared__ float sp[];
+    const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
+    const int dh = D / H;
+    const int64_t ld = 3 * (int64_t)D;
+    const T* base = qkv + (int64_t)b * S * ld + h * dh;
+    const T* qi = base + i * ld;
+    float mx = -INFINITY;
+    for (int j = lane; j <= i; j += 64) {
+        const T* kj = base + j * ld + D;
+        float a = 0.0f;
+        for (int d = 0; d < dh; ++d) a += to_f32(qi[d]) * to_f32(kj[d]);
+        a *= scale;
+        sp[j] = a;
+        mx = fmaxf(mx, a);
+    }
+    mx = wmax(mx);
+    float sum = 0.0f;
+    for (int j = lane; j <= i; j += 64) {
+        const float e = expf(sp[j] - mx);
+        sp[j] = e;
+        sum += e;
+    }
+    sum = wsum(sum);
+    __syncthreads();
+    const float inv = 1.0f / sum;
+    for (int d = lane; d < dh; d += 64) {
+        float a = 0.0f;
+        for (int j = 0; j <= i; ++j) a += sp[j] * to_f32(base[j * ld + 2 * D + d]);
+        o[((int64_t)b * S + i) * D + h * dh + d] = from_f32<T>(a * inv);
+    }
+    if (lane == 0) lse[((int64_t)b * H + h) * S + i] = mx + logf(sum);
+}
+
+// delta[b, h, i] = sum_d dO[i, d] * O[i, d]
+template <typename T>
+__global__ __launch_bounds__(256) void attn_delta_kernel(const T* __restrict__ o, const T* __restrict__ dout,
+                                                         float* __restrict__ delta, int64_t BS, int S, int D, int H) {
+    const int lane = threadIdx.x & 63;
+    const int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // (b*S + i)*H + h
+    if (idx >= BS * H) return;
+    const int h = (int)(idx % H);
+    const int64_t bi = idx / H;
+    const int dh = D / H;
+    float a = 0.0f;
+    for (int d = lane; d < dh; d += 64) a += to_f32(o[bi * D + h * dh + d]) * to_f32(dout[bi * D + h * dh + d]);
+    a = wsum(a);
+    if (lane == 0) delta[((bi / S) * H + h) * S + (bi % S)] = a;
+}
+
+// Query gradient, one wave per (b, h, i).  Dynamic LDS: S floats (dS row).
+template <typename T>
+__global__ __launch_bounds__(64) void attn_bwd_q_row_kernel(const T* __restrict__ qkv, const T* __restrict__ dout,
+                                                            const float* __restrict__ lse, const float* __restrict__ delta,
+                                                            T* __restrict__ dqkv, int S, int D, int H, float scale) {
+    extern __shared__ float sp[];
+    const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
+    const int dh = D / H;
+    const int64_t ld = 3 * (int64_t)D;
+    const T* base = qkv + (int64_t)b * S * ld + h * dh;
+    const T* qi = base + i * ld;
+    const T* doi = dout + ((int64_t)b * S + i) * D + h * dh;
+    const float L = lse[((int64_t)b * H + h) * S + i], dl = delta[((int64_t)b * H + h) * S + i];
+    for (int j = lane; j <= i; j += 64) {
+        const T* kj = base + j * ld + D;
+        const T* vj = base + j * ld + 2 * D;
+        float a = 0.0f, dp = 0.0f;
+        for (int d = 0; d < dh; ++d) {
+            a += to_f32(qi[d]) * to_f32(kj[d]);
+            dp += to_f32(doi[d]) * to_f32(vj[d]);
+        }
+        sp[j] = expf(a * scale - L) * (dp - dl);
+    }
+    __syncthreads();
+    for (int d = lane; d < dh; d += 64) {
+        float a = 0.0f;
+        for (int j = 0; j <= i; ++j) a += sp[j] * to_f32(base[j * ld + D + d]);
+        dqkv[((int64_t)b * S + i) * ld + h * dh + d] = from_f32<T>(a * scale);
+    }
+}
+
+// Key / value gradients, one wave per (b, h, j).  Dynamic LDS: 2*S floats (P and dS columns).
+template <typename T>
+__global__ __launch_bounds__(64) void attn_bwd_kv_row_kernel(const T* __restrict__ qkv, const T* __restrict__ dout,
+                                                             const float* __restrict__ lse, const float* __restrict__ delta,
+                                                             T* __restrict__ dqkv, int S, int D, int H, float scale) {
+    extern __shared__ float sp[];
+    float* sds = sp + S;
+    const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
+    const int dh = D / H;
+    const int64_t ld = 3 * (int64_t)D;
+    const T* base = qkv + (int64_t)b * S * ld + h * dh;
+    const T* kj = base + j * ld + D;
+    const T* vj = base + j * ld + 2 * D;
+    for (int i = j + lane; i < S; i += 64) {
+        const T* qi = base + i * ld;
+        const T* doi = dout + ((int64_t)b * S + i) * D + h * dh;
+        float a = 0.0f, dp = 0.0f;
+        for (int d = 0; d < dh; ++d) {
+            a += to_f32(qi[d]) * to_f32(kj[d]);
+            dp += to_f32(doi[d]) * to_f32(vj[d]);
+        }
+        const float p = expf(a * scale - lse[((int64_t)b * H + h) * S + i]);
+        sp[i] = p;
+        sds[i] = p * (dp - delta[((int64_t)b * H + h) * S + i]);
+    }
+    __syncthreads();
+    for (int d = lane; d < dh; d += 64) {
+        float dk = 0.0f, dv = 0.0f;
+        for (int i = j; i < S; ++i) {
+            dk += sds[i] * to_f32(base[i * ld + d]);
+            dv += sp[i] * to_f32(dout[((int64_t)b * S + i) * D + h * dh + d]);
+        }
+        dqkv[((int64_t)b * S + j) * ld + D + h * dh + d] = from_f32<T>(dk * scale);
+        dqkv[((int64_t)b * S + j) * ld + 2 * D + h * dh + d] = from_f32<T>(dv);
+    }
+}
+
+// ---------------------------------------------------------------------------- MFMA path
+// Exponentials use the hardware exp2 (one ulp; the library expf costs some 25 instructions and made the softmax, not the
+// MFMAs, the bulk of the bf16 kernels).  Scores are kept in units of log 2 (scale * log2(e) folded into one factor), so
+// that a probability costs one fused multiply-add and one exp2.
+__device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+// 16 bytes in flight between global memory and LDS (a native vector: arrays of it stay in registers)
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// What depends on the element type and the features per head.
+template <class T, int DH> struct Attn {
+    static constexpr bool BF = sizeof(T) == 2;
+    static constexpr int V = 16 / (int)sizeof(T);     // elements of a 16-byte chunk
+    static constexpr int FT = DH / 32;                // 32-feature tiles
+    static constexpr int NF = DH / (2 * V);           // fragments of a row: 16 features each in bf16, 8 in fp32
+    static constexpr int P = DH + V;                  // LDS row pitch (16 bytes over: rows of a fragment on other banks)
+    static constexpr int R = BF ? 64 : 32;            // rows of an LDS tile
+    typedef typename Frag<T>::type frag_t;
+
+    // Fragment t of 32 rows (lane: row lane % 32, V features from 2 V t + V (lane / 32)): from global memory (rows
+    // clamped to the last valid one) or from an LDS tile.
+    static __device__ __forceinline__ frag_t gfrag(const T* base, int64_t ld, int row, int max_row, int t, int lane) {
+        int r = row + (lane & 31);
+        r = r < max_row ? r : max_row - 1;
+        return *reinterpret_cast<const frag_t*>(base + r * ld + t * 2 * V + (lane >> 5) * V);
+    }
+    static __device__ __forceinline__ frag_t lfrag(const T* tile, int row0, int t, int lane) {
+        return *reinterpret_cast<const frag_t*>(tile + (row0 + (lane & 31)) * P + t * 2 * V + (lane >> 5) * V);
+    }
+    // acc += rows of a times rows of b over one fragment's features
+    static __device__ __forceinline__ f32x16_t mul(frag_t a, frag_t b, f32x16_t acc) {
+        if constexpr (BF) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+        else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
+            return acc;
+        }
+    }
+    // out[i] += transposed tile rows r0 .. r0+31 (features 32 i ..) times p, whose accumulator registers run over those
+    // rows: register r of a lane in half h belongs to row r0 + 8 (r / 4) + 4 h + r % 4.
+    static __device__ __forceinline__ void mul_t(const T* tile, int r0, const f32x16_t& p, f32x16_t (&out)[FT], int lane) {
+        if constexpr (BF) {
+            typedef __attribute__((address_space(3))) s16x4_t* lds_ptr_t;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                bf16x8_t pf;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) pf[e] = (bf16_t)p[8 * t + e];
+#pragma unroll
+                for (int i = 0; i < FT; ++i) {
+                    // two transpose reads of 4 rows each: slot (half, e) is row r0 + 16 t + 8 (e / 4) + 4 half + e % 4
+                    const int row = r0 + 16 * t + 4 * (lane >> 5) + ((lane & 15) >> 2);
+                    const int col = 32 * i + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+                    const T* p0 = tile + row * P + col;
+                    union { s16x4_t h[2]; bf16x8_t v; } u;
+                    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p0));
+                    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p0 + 8 * P));
+                    out[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u.v, pf, out[i], 0, 0, 0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int i = 0; i < FT; ++i) {
+                    const T a = tile[(r0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * P + 32 * i + (lane & 31)];
+                    out[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, p[r], out[i], 0, 0, 0);
+                }
+        }
+    }
+    // four consecutive features of a row
+    static __device__ __forceinline__ void store4(T* p, float a, float b, float c, float d) {
+        if constexpr (BF) {
+            union { bf16_t hv[4]; uint2 u; } pk;
+            pk.hv[0] = (bf16_t)a; pk.hv[1] = (bf16_t)b; pk.hv[2] = (bf16_t)c; pk.hv[3] = (bf16_t)d;
+            *reinterpret_cast<uint2*>(p) = pk.u;
+        } else *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
+    }
+    // a result with features along the registers, times f, to one row
+    static __device__ __forceinline__ void store_row(T* row, const f32x16_t (&v)[FT], float f, int half) {
+#pragma unroll
+        for (int i = 0; i < FT; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                store4(row + 32 * i + 8 * g + 4 * half, v[i][4 * g] * f, v[i][4 * g + 1] * f, v[i][4 * g + 2] * f, v[i][4 * g + 3] * f);
+    }
+    // Cooperative copy of R rows into an LDS tile in two halves, so that the global loads of the next tile are in flight
+    // while the current one is multiplied: fetch() issues the loads, put() writes them to LDS.  Rows >= max_row are clamped.
+    template <int NT> struct Fetch {
+        static constexpr int C = DH / V, N = (R * C + NT - 1) / NT;   // chunks of a row, chunks of a thread
+        u32x4_t r[N];
+        __device__ __forceinline__ void fetch(const T* base, int64_t ld, int row0, int max_row, int tid) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = tid + i * NT;
+                int row = row0 + c / C;
+                row = row < max_row ? row : max_row - 1;
+                r[i] = *reinterpret_cast<const u32x4_t*>(base + row * ld + (c % C) * V);
+            }
+        }
+        __device__ __forceinline__ void put(T* tile, int tid) const {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = tid + i * NT;
+                if (R * C % NT == 0 || c < R * C) *reinterpret_cast<u32x4_t*>(tile + (c / C) * P + (c % C) * V) = r[i];
+            }
+        }
+    };
+};
+
+template <int FT> __device__ __forceinline__ void clear(f32x16_t (&v)[FT]) {
+#pragma unroll
+    for (int i = 0; i < FT; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[i][r] = 0.0f;
+}
+
+// One 32-key block of the running softmax of 32 queries (one per lane pair; keys along the registers).  st holds the
+// raw scores q.k and leaves as unnormalised probabilities; m_run (in units of log 2) and l_run are the running
+// maximum and sum, ot the running output, rescaled here.  MASK: the block straddles the diagonal (or the end of
+// the sequence): keys after the query are excluded.  Blocks below the diagonal skip the three mask instructions
+// per element.
+template <bool MASK, int FT>
+__device__ __forceinline__ void softmax_block(f32x16_t& st, int kb, int q, int half, float scale2, float& m_run, float& l_run,
+                                              f32x16_t (&ot)[FT]) {
+    float mt = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        if constexpr (MASK) {
+            const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
+            st[r] = key <= q ? st[r] : -INFINITY;
+        }
+        mt = fmaxf(mt, st[r]);
+    }
+    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    const float m_new = fmaxf(m_run, mt * scale2);       // scale2 > 0: the maximum commutes with the scaling
+    const float m_use = m_new == -INFINITY ? 0.0f : m_new;   // a query with no key yet keeps zeros
+    const float alpha = exp2_hw(m_run - m_use);
+    float ls = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        st[r] = exp2_hw(fmaf(st[r], scale2, -m_use));
+        ls += st[r];
+    }
+    l_run = l_run * alpha + ls;
+    m_run = m_new;
+#pragma unroll
+    for (int i = 0; i < FT; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ot[i][r] *= alpha;
+}
+
+// Workgroups go to the 8 XCDs (each with its own L2) round-robin in launch order (x fastest, then y, then z).  Hand
+// every XCD a contiguous run of that order instead: the query (or key) blocks of one (batch, head) then sit on one XCD,
+// and the keys and values (queries and output gradients) they all read come in from memory once, not once per XCD.
+__device__ __forceinline__ void xcd_local_block(int& x, int& y, int& z) {
+    const int gx = gridDim.x, gy = gridDim.y, plane = gx * gy, total = plane * gridDim.z;
+    x = blockIdx.x; y = blockIdx.y; z = blockIdx.z;
+    if (total < 16) return;
+    const int lin = (z * gy + y) * gx + x;
+    const int xcd = lin & 7, idx = lin >> 3, q = total >> 3, r = total & 7;
+    int moved = xcd * q + min(xcd, r) + idx;
+    z = moved / plane;
+    moved -= z * plane;
+    y = moved / gx;
+    x = moved - y * gx;
+}
+
+// Forward.  Block = NW waves = 32*NW query rows of one (batch, head).
+template <class T, int DH, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int S,
+                                                                int D, int H, float scale) {
+    typedef Attn<T, DH> X;
+    __shared__ __attribute__((aligned(16))) T sKb[2][X::R * X::P];
+    __shared__ __attribute__((aligned(16))) T sVb[2][X::R * X::P];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+    int bx, h, b;
+    xcd_local_block(bx, h, b);
+    const int qb = gridDim.x - 1 - bx;
+    const int64_t ld = 3 * (int64_t)D;
+    const T* base = qkv + (int64_t)b * S * ld + h * DH;
+    const int q0 = (qb * NW + wave) * 32;
+    const int q = q0 + (lane & 31);
+    typename X::template Fetch<64 * NW> fk, fv;
+    fk.fetch(base + D, ld, 0, S, tid);
+    fv.fetch(base + 2 * D, ld, 0, S, tid);
+    typename X::frag_t qf[X::NF];
+#pragma unroll
+    for (int t = 0; t < X::NF; ++t) qf[t] = X::gfrag(base, ld, q0, S, t, lane);
+    f32x16_t ot[X::FT];
+    clear(ot);
+    float m_run = -INFINITY, l_run = 0.0f;
+    const float scale2 = scale * kLog2e;
+    const int kv_end = min(S, (qb + 1) * NW * 32);
+    fk.put(sKb[0], tid);
+    fv.put(sVb[0], tid);
+    __syncthreads();
+    for (int kv0 = 0, it = 0; kv0 < kv_end; kv0 += X::R, ++it) {
+        const T* sK = sKb[it & 1];
+        const T* sV = sVb[it & 1];
+        // the next tile's loads fly while this one is multiplied (past the last tile they re-read clamped, valid rows
+        // and the copy lands in the buffer that nobody reads again)
+        fk.fetch(base + D, ld, kv0 + X::R, S, tid);
+        fv.fetch(base + 2 * D, ld, kv0 + X::R, S, tid);
+#pragma unroll
+        for (int sub = 0; sub < X::R / 32; ++sub) {
+            const int kb = kv0 + 32 * sub;
+            if (kb > q0 + 31) continue;   // every key of the tile lies after every query of this wave
+            f32x16_t st;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st[r] = 0.0f;
+#pragma unroll
+            for (int t = 0; t < X::NF; ++t) st = X::mul(X::lfrag(sK, 32 * sub, t, lane), qf[t], st);
+            if (kb + 31 <= q0) softmax_block<false>(st, kb, q, half, scale2, m_run, l_run, ot);
+            else softmax_block<true>(st, kb, q, half, scale2, m_run, l_run, ot);
+            X::mul_t(sV, 32 * sub, st, ot, lane);
+        }
+        fk.put(sKb[(it + 1) & 1], tid);   // the other buffer was last read before the previous barrier
+        fv.put(sVb[(it + 1) & 1], tid);
+        __syncthreads();
+    }
+    const float l = l_run + __shfl_xor(l_run, 32, 64);
+    if (q < S) {
+        X::store_row(o + ((int64_t)b * S + q) * D + h * DH, ot, 1.0f / l, half);
+        if (half == 0) lse[((int64_t)b * H + h) * S + q] = m_run * kLn2 + logf(l);
+    }
+}
+
+// Forward for launches with few (batch, head) pairs, where the kernel above leaves most of the chip idle and its
+// longest workgroup walks the whole key range alone.  A workgroup owns 32 query rows; its NW waves take the 32-key
+// blocks up to the diagonal in turn (wave w: blocks w, w + NW, ...) with their own running statistics, and the
+// partial results are merged at the end: O = sum_w e^{m_w - m} O_w, l = sum_w e^{m_w - m} l_w, m = max_w m_w.
+// Nothing is shared between the waves inside the loop, so there is no workgroup barrier in it: K fragments come
+// straight from global memory, V passes through a wave-private LDS tile.
+template <class T, int DH, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_fwd_split_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int S,
+                                                                 int D, int H, float scale) {
+    typedef Attn<T, DH> X;
+    constexpr int FT = X::FT, C = DH / X::V, NV = 32 * C / 64;   // 16-byte chunks of a row, chunks per lane of 32 rows
+    __shared__ __attribute__((aligned(16))) T sVw[NW][32 * X::P];
+    __shared__ float sOw[NW - 1][16 * FT][64];
+    __shared__ float sMw[NW - 1][32], sLw[NW - 1][32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+    int bx, h, b;
+    xcd_local_block(bx, h, b);
+    const int qb = gridDim.x - 1 - bx;
+    const int64_t ld = 3 * (int64_t)D;
+    const T* base = qkv + (int64_t)b * S * ld + h * DH;
+    const int q0 = qb * 32;
+    const int q = q0 + (lane & 31);
+    T* const sV = sVw[wave];
+    typename X::frag_t qf[X::NF], kn[X::NF];
+    u32x4_t vn[NV];
+    auto fetch = [&](int j) {   // rows are clamped: a fetch past the diagonal re-reads valid rows and is never used
+#pragma unroll
+        for (int t = 0; t < X::NF; ++t) kn[t] = X::gfrag(base + D, ld, 32 * j, S, t, lane);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int c = lane + 64 * i;
+            int row = 32 * j + c / C;
+            row = row < S ? row : S - 1;
+            vn[i] = *reinterpret_cast<const u32x4_t*>(base + 2 * D + row * ld + (c % C) * X::V);
+        }
+    };
+    fetch(wave);
+#pragma unroll
+    for (int t = 0; t < X::NF; ++t) qf[t] = X::gfrag(base, ld, q0, S, t, lane);
+    f32x16_t ot[FT];
+    clear(ot);
+    float m_run = -INFINITY, l_run = 0.0f;
+    const float scale2 = scale * kLog2e;
+    for (int j = wave; j <= qb; j += NW) {
+        typename X::frag_t kf[X::NF];
+#pragma unroll
+        for (int t = 0; t < X::NF; ++t) kf[t] = kn[t];
+        // LDS serves a wave's accesses in order: the reads of the previous block are done before these writes
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int c = lane + 64 * i;
+            *reinterpret_cast<u32x4_t*>(sV + (c / C) * X::P + (c % C) * X::V) = vn[i];
+        }
+        __builtin_amdgcn_wave_barrier();
+        fetch(j + NW);
+        const int kb = 32 * j;
+        f32x16_t st;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[r] = 0.0f;
+#pragma unroll
+        for (int t = 0; t < X::NF; ++t) st = X::mul(kf[t], qf[t], st);
+        if (kb + 31 <= q0) softmax_block<false>(st, kb, q, half, scale2, m_run, l_run, ot);
+        else softmax_block<true>(st, kb, q, half, scale2, m_run, l_run, ot);
+        X::mul_t(sV, 0, st, ot, lane);
+    }
+    float l = l_run + __shfl_xor(l_run, 32, 64);
+    if (wave > 0) {
+#pragma unroll
+        for (int i = 0; i < FT; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sOw[wave - 1][16 * i + r][lane] = ot[i][r];
+        if (half == 0) {
+            sMw[wave - 1][lane] = m_run;
+            sLw[wave - 1][lane] = l;
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    // wave 0 always owns key block 0, which every query sees: its maximum is finite
+    float m = m_run;
+#pragma unroll
+    for (int w = 0; w < NW - 1; ++w) m = fmaxf(m, sMw[w][lane & 31]);
+    const float f0 = exp2_hw(m_run - m);
+    l *= f0;
+#pragma unroll
+    for (int i = 0; i < FT; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ot[i][r] *= f0;
+#pragma unroll
+    for (int w = 0; w < NW - 1; ++w) {
+        const float fw = exp2_hw(sMw[w][lane & 31] - m);   // a wave that had no block holds -inf: factor 0
+        l += fw * sLw[w][lane & 31];
+#pragma unroll
+        for (int i = 0; i < FT; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) ot[i][r] += fw * sOw[w][16 * i + r][lane];
+    }
+    if (q < S) {
+        X::store_row(o + ((int64_t)b * S + q) * D + h * DH, ot, 1.0f / l, half);
+        if (half == 0) lse[((int64_t)b * H + h) * S + q] = m * kLn2 + logf(l);
+    }
+}
+
+// Query gradient.  Same arrangement as the forward pass: P^T and dS^T have keys along the registers.  The workgroup also
+// forms delta[q] = dO[q] . O[q] of its queries, from the dO fragments it holds anyway, for itself and for the
+// key/value-gradient kernel that follows (as a kernel of its own it took 6 us per layer of the GPT-2 configuration).
+template <class T, int DH, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_q_mfma_kernel(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dout,
+                                                                  const float* __restrict__ lse, float* __restrict__ delta,
+                                                                  T* __restrict__ dqkv, int S, int D, int H, float scale) {
+    typedef Attn<T, DH> X;
+    __shared__ __attribute__((aligned(16))) T sKb[2][X::R * X::P];
+    __shared__ __attribute__((aligned(16))) T sVb[2][X::R * X::P];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+    int bx, h, b;
+    xcd_local_block(bx, h, b);
+    const int qb = gridDim.x - 1 - bx;
+    const int64_t ld = 3 * (int64_t)D;
+    const T* base = qkv + (int64_t)b * S * ld + h * DH;
+    const T* dob = dout + (int64_t)b * S * D + h * DH;
+    const T* ob = o + (int64_t)b * S * D + h * DH;
+    typename X::template Fetch<64 * NW> fk, fv;
+    fk.fetch(base + D, ld, 0, S, tid);
+    fv.fetch(base + 2 * D, ld, 0, S, tid);
+    const int q0 = (qb * NW + wave) * 32;
+    const int q = q0 + (lane & 31);
+    const int qc = q < S ? q : S - 1;
+    typename X::frag_t qf[X::NF], dof[X::NF], of[X::NF];
+#pragma unroll
+    for (int t = 0; t < X::NF; ++t) {
+        qf[t] = X::gfrag(base, ld, q0, S, t, lane);
+        dof[t] = X::gfrag(dob, D, q0, S, t, lane);
+        of[t] = X::gfrag(ob, D, q0, S, t, lane);
+    }
+    const float L2 = lse[((int64_t)b * H + h) * S + qc] * kLog2e;
+    float dl = 0.0f;
+#pragma unroll
+    for (int t = 0; t < X::NF; ++t)
+#pragma unroll
+        for (int e = 0; e < X::V; ++e) dl += (float)of[t][e] * (float)dof[t][e];
+    dl += __shfl_xor(dl, 32, 64);
+    if (half == 0 && q < S) delta[((int64_t)b * H + h) * S + q] = dl;
+    const float scale2 = scale * kLog2e;
+    f32x16_t dq[X::FT];
+    clear(dq);
+    const int kv_end = min(S, (qb + 1) * NW * 32);
+    fk.put(sKb[0], tid);
+    fv.put(sVb[0], tid);
+    __syncthreads();
+    for (int kv0 = 0, it = 0; kv0 < kv_end; kv0 += X::R, ++it) {
+        const T* sK = sKb[it & 1];
+        const T* sV = sVb[it & 1];
+        fk.fetch(base + D, ld, kv0 + X::R, S, tid);
+        fv.fetch(base + 2 * D, ld, kv0 + X::R, S, tid);
+#pragma unroll
+        for (int sub = 0; sub < X::R / 32; ++sub) {
+            const int kb = kv0 + 32 * sub;
+            if (kb > q0 + 31) continue;
+            f32x16_t st, dp;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st[r] = dp[r] = 0.0f;
+#pragma unroll
+            for (int t = 0; t < X::NF; ++t) {
+                st = X::mul(X::lfrag(sK, 32 * sub, t, lane), qf[t], st);
+                dp = X::mul(X::lfrag(sV, 32 * sub, t, lane), dof[t], dp);
+            }
+            if (kb + 31 <= q0) {   // below the diagonal: no key is excluded
+#pragma unroll
+                for (int r = 0; r < 16; ++r) st[r] = exp2_hw(fmaf(st[r], scale2, -L2)) * (dp[r] - dl);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
+                    const float p = key <= q ? exp2_hw(fmaf(st[r], scale2, -L2)) : 0.0f;
+                    st[r] = p * (dp[r] - dl);
+                }
+            }
+            X::mul_t(sK, 32 * sub, st, dq, lane);
+        }
+        fk.put(sKb[(it + 1) & 1], tid);
+        fv.put(sVb[(it + 1) & 1], tid);
+        __syncthreads();
+    }
+    if (q < S) X::store_row(dqkv + ((int64_t)b * S + q) * ld + h * DH, dq, scale, half);
+}
+
+// Key and value gradients.  A wave owns 32 keys (lanes); queries run along the accumulator registers, so the
+// per-query statistics (log-sum-exp, delta) are read per register from LDS.
+template <class T, int DH, int NW>
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 1 : 2) void attn_bwd_kv_mfma_kernel(const T* __restrict__ qkv, const T* __restrict__ dout,
+                                                                   const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                   T* __restrict__ dqkv, int S, int D, int H, float scale) {
+    typedef Attn<T, DH> X;
+    __shared__ __attribute__((aligned(16))) T sQb[2][X::R * X::P];
+    __shared__ __attribute__((aligned(16))) T sOb[2][X::R * X::P];
+    __shared__ __attribute__((aligned(16))) float sLb[2][X::R], sDlb[2][X::R];   // log-sum-exp (in units of log 2) and delta
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+    int kblk, h, b;
+    xcd_local_block(kblk, h, b);
+    const int64_t ld = 3 * (int64_t)D;
+    const T* base = qkv + (int64_t)b * S * ld + h * DH;
+    const T* dob = dout + (int64_t)b * S * D + h * DH;
+    const int k0 = (kblk * NW + wave) * 32;
+    const int key = k0 + (lane & 31);
+    const float scale2 = scale * kLog2e;
+    typename X::frag_t kf[X::NF], vf[X::NF];
+#pragma unroll
+    for (int t = 0; t < X::NF; ++t) {
+        kf[t] = X::gfrag(base + D, ld, k0, S, t, lane);
+        vf[t] = X::gfrag(base + 2 * D, ld, k0, S, t, lane);
+    }
+    f32x16_t dk[X::FT], dv[X::FT];
+    clear(dk);
+    clear(dv);
+    const int qstart = (kblk * NW * 32) / X::R * X::R;   // first query block that can see a key of this workgroup
+    typename X::template Fetch<64 * NW> fq, fo;
+    float pl = 0.0f, pd = 0.0f;   // statistics of query qb0 + tid (threads 0 .. R-1)
+    auto fetch_stats = [&](int qb0) {
+        if (tid < X::R) {
+            const int qq = qb0 + tid < S ? qb0 + tid : S - 1;
+            pl = lse[((int64_t)b * H + h) * S + qq];
+            pd = delta[((int64_t)b * H + h) * S + qq];
+        }
+    };
+    auto put_stats = [&](int buf) {
+        if (tid < X::R) {
+            sLb[buf][tid] = pl * kLog2e;
+            sDlb[buf][tid] = pd;
+        }
+    };
+    fq.fetch(base, ld, qstart, S, tid);
+    fo.fetch(dob, D, qstart, S, tid);
+    fetch_stats(qstart);
+    fq.put(sQb[0], tid);
+    fo.put(sOb[0], tid);
+    put_stats(0);
+    __syncthreads();
+    for (int qb0 = qstart, it = 0; qb0 < S; qb0 += X::R, ++it) {
+        const T* sQ = sQb[it & 1];
+        const T* sO = sOb[it & 1];
+        const float* sL = sLb[it & 1];
+        const float* sDl = sDlb[it & 1];
+        fq.fetch(base, ld, qb0 + X::R, S, tid);
+        fo.fetch(dob, D, qb0 + X::R, S, tid);
+        fetch_stats(qb0 + X::R);
+#pragma unroll
+        for (int sub = 0; sub < X::R / 32; ++sub) {
+            const int qs = qb0 + 32 * sub;
+            if (qs + 31 < k0) continue;   // every query of the tile lies before every key of this wave
+            f32x16_t st, dp;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st[r] = dp[r] = 0.0f;
+#pragma unroll
+            for (int t = 0; t < X::NF; ++t) {
+                st = X::mul(X::lfrag(sQ, 32 * sub, t, lane), kf[t], st);
+                dp = X::mul(X::lfrag(sO, 32 * sub, t, lane), vf[t], dp);
+            }
+            // statistics of the 4 consecutive queries of a register group in one LDS read each
+            float4 l4[4], d4[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                l4[g] = *reinterpret_cast<const float4*>(sL + 32 * sub + 8 * g + 4 * half);
+                d4[g] = *reinterpret_cast<const float4*>(sDl + 32 * sub + 8 * g + 4 * half);
+            }
+            const bool inner = k0 + 31 <= qs && qs + 32 <= S;   // every query of the block sees every key of this wave
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float Lq = (r & 3) == 0 ? l4[r >> 2].x : (r & 3) == 1 ? l4[r >> 2].y : (r & 3) == 2 ? l4[r >> 2].z : l4[r >> 2].w;
+                const float Dq = (r & 3) == 0 ? d4[r >> 2].x : (r & 3) == 1 ? d4[r >> 2].y : (r & 3) == 2 ? d4[r >> 2].z : d4[r >> 2].w;
+                float p = exp2_hw(fmaf(st[r], scale2, -Lq));
+                if (!inner) {
+                    const int qq = qs + 8 * (r >> 2) + 4 * half + (r & 3);
+                    p = (key <= qq && qq < S) ? p : 0.0f;
+                }
+                st[r] = p;
+                dp[r] = p * (dp[r] - Dq);
+            }
+            X::mul_t(sO, 32 * sub, st, dv, lane);
+            X::mul_t(sQ, 32 * sub, dp, dk, lane);
+        }
+        fq.put(sQb[(it + 1) & 1], tid);
+        fo.put(sOb[(it + 1) & 1], tid);
+        put_stats((it + 1) & 1);
+        __syncthreads();
+    }
+    if (key < S) {
+        T* drow = dqkv + ((int64_t)b * S + key) * ld + h * DH;
+        X::store_row(drow + D, dk, scale, half);
+        X::store_row(drow + 2 * D, dv, 1.0f, half);
+    }
+}
+
+// Waves per workgroup of the tiled kernels.  bf16: every workgroup streams the whole key (query) range of its
+// (batch, head) pair through LDS, so the traffic from L2 falls with the number of rows that share a tile: the widest
+// workgroup that still leaves about one per compute unit.  fp32: the MFMAs take sixteen times as long and the traffic is
+// no matter, so workgroups stay small, for balance along the diagonal.
+template <class T> static int attn_waves(int B, int S, int H) {
+    const int64_t bh = (int64_t)B * H;
+    if (sizeof(T) == 4) return cdiv_at(S, 128) * bh >= 1024 ? 4 : 2;
+    if (cdiv_at(S, 256) * bh >= 192) return 8;
+    if (cdiv_at(S, 128) * bh >= 192) return 4;
+    return 2;
+}
+
+size_t attention_workspace_elems(int B, int S, int H) { return (size_t)B * S * H; }
+
+template <class T, int DH>
+static hipError_t forward_mfma(const T* qkv, T* o, float* lse, int B, int S, int D, int H, float scale, hipStream_t s) {
+    if ((int64_t)cdiv_at(S, 64) * H * B < 512)   // too few workgroups of the tiled kernel to fill the chip
+        return launch_timed(kcAttnFwd, attn_fwd_split_kernel<T, DH, 4>, dim3(cdiv_at(S, 32), H, B), dim3(256), 0, s, qkv, o, lse, S, D, H, scale);
+    auto go = [&](auto nwc) {
+        constexpr int NW = decltype(nwc)::value;
+        return launch_timed(kcAttnFwd, attn_fwd_mfma_kernel<T, DH, NW>, dim3(cdiv_at(S, 32 * NW), H, B), dim3(64 * NW), 0, s, qkv, o, lse, S, D, H, scale);
+    };
+    switch (attn_waves<T>(B, S, H)) {
+        case 8: return go(std::integral_constant<int, sizeof(T) == 2 ? 8 : 4>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        default: return go(std::integral_constant<int, 2>{});
+    }
+}
+
+template <class T, int DH>
+static hipError_t backward_mfma(const T* qkv, const T* o, const T* dout, const float* lse, float* delta, T* dqkv, int B, int S, int D, int H,
+                                float scale, hipStream_t s) {
+    auto go = [&](auto nwc) {
+        constexpr int NW = decltype(nwc)::value;
+        const dim3 grid(cdiv_at(S, 32 * NW), H, B);
+        hipError_t e = launch_timed(kcAttnBwd, attn_bwd_q_mfma_kernel<T, DH, NW>, grid, dim3(64 * NW), 0, s, qkv, o, dout, lse, delta, dqkv, S, D, H, scale);
+        if (e != hipSuccess) return e;
+        return launch_timed(kcAttnBwd, attn_bwd_kv_mfma_kernel<T, DH, NW>, grid, dim3(64 * NW), 0, s, qkv, dout, lse, (const float*)delta, dqkv, S, D, H, scale);
+    };
+    switch (attn_waves<T>(B, S, H)) {
+        case 8: return go(std::integral_constant<int, sizeof(T) == 2 ? 8 : 4>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        default: return go(std::integral_constant<int, 2>{});
+    }
+}
+
+template <class T> static hipError_t forward_t(const T* qkv, T* o, float* lse, int B, int S, int D, int H, hipStream_t s) {
+    const float scale = 1.0f / sqrtf((float)(D / H));
+    const bool aligned = ((reinterpret_cast<uintptr_t>(qkv) | reinterpret_cast<uintptr_t>(o)) & 15) == 0;
+    if (aligned && D == 64 * H) return forward_mfma<T, 64>(qkv, o, lse, B, S, D, H, scale, s);
+    if (aligned && D == 32 * H) return forward_mfma<T, 32>(qkv, o, lse, B, S, D, H, scale, s);
+    return launch_timed(kcAttnFwd, attn_fwd_row_kernel<T>, dim3(S, H, B), dim3(64), (unsigned)S * 4, s, qkv, o, lse, S, D, H, scale);
+}
+
+template <class T>
+static hipError_t backward_t(const T* qkv, const T* o, const T* dout, const float* lse, float* delta, T* dqkv, int B, int S, int D, int H, hipStream_t s) {
+    const float scale = 1.0f / sqrtf((float)(D / H));
+    const bool aligned = ((reinterpret_cast<uintptr_t>(qkv) | reinterpret_cast<uintptr_t>(o) | reinterpret_cast<uintptr_t>(dout) |
+                           reinterpret_cast<uintptr_t>(dqkv)) & 15) == 0;
+    if (aligned && D == 64 * H) return backward_mfma<T, 64>(qkv, o, dout, lse, delta, dqkv, B, S, D, H, scale, s);
+    if (aligned && D == 32 * H) return backward_mfma<T, 32>(qkv, o, dout, lse, delta, dqkv, B, S, D, H, scale, s);
+    const int64_t BS = (int64_t)B * S;
+    hipError_t e = launch_timed(kcAttnBwd, attn_delta_kernel<T>, dim3(cdiv_at(BS * H, 4)), dim3(256), 0, s, o, dout, delta, BS, S, D, H);
+    if (e != hipSuccess) return e;
+    const dim3 grid(S, H, B);
+    e = launch_timed(kcAttnBwd, attn_bwd_q_row_kernel<T>, grid, dim3(64), (unsigned)S * 4, s, qkv, dout, lse, (const float*)delta, dqkv, S, D, H, scale);
+    if (e != hipSuccess) return e;
+    return launch_timed(kcAttnBwd, attn_bwd_kv_row_kernel<T>, grid, dim3(64), (unsigned)S * 8, s, qkv, dout, lse, (const float*)delta, dqkv, S, D, H, scale);
+}
+
+hipError_t attention_forward(int dtype, const void* qkv, void* o, float* lse, int B, int S, int D, int H, hipStream_t s) {
+    if (B <= 0) return hipSuccess;
+    if (dtype == kBF16) return forward_t<bf16_t>((const bf16_t*)qkv, (bf16_t*)o, lse, B, S, D, H, s);
+    return forward_t<float>((const float*)qkv, (float*)o, lse, B, S, D, H, s);
+}
+
+hipError_t attention_backward(int dtype, const void* qkv, const void* o, const void* dout, const float* lse, float* delta,
+                              void* dqkv, int B, int S, int D, int H, hipStream_t s) {
+    if (B <= 0) return hipSuccess;
+    if (dtype == kBF16)
+        return backward_t<bf16_t>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, B, S, D, H, s);
+    return backward_t<float>((const float*)qkv, (const float*)o, (const float*)dout, lse, delta, (float*)dqkv, B, S, D, H, s);
+}
+
+}  // namespace tmps

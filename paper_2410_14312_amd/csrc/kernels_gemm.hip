@@ -308,6 +308,10 @@ static hipError_t dense_forward_bf16(int kc, const bf16_t* x, const bf16_t* w, c
         G3Operand<true> Bv{w, Dout, Din};
         return launch3<true, true, false>(kc, A, Bv, epi, B, Dout, Din, g3_plan(B, Dout, Din, 1), s);
     }
+    // (from 1024 on: below that the 128 x 128 tiles of the tiled kernel are as quick; 8192 x 768 x 3072 62 -> 57 us)
+    if (aligned && Din >= 1024 && g3_narrow_ok(B, Dout, Din) && aligned16(x) && aligned16(w))
+        return launch3_inst<256, 128, 2, 2, 2, 1, true, true, false>(kc, G3Operand<true>{x, B, Din}, G3Operand<true>{w, Dout, Din}, epi, B, Dout, Din,
+                                                                     g3_plan(B, Dout, Din, 1, 256, 128), s);
     return dense_forward_t<bf16_t>(kc, x, w, epi, B, Din, Dout, ws, s);
 }
 
