@@ -59,15 +59,13 @@ template <class T> __device__ __forceinline__ uint4 ld16(const T* p) { return *r
 // compiler counts the loads in flight exactly and a tile is waited for only when it is copied to LDS,
 // D tiles after it was requested.
 static __device__ __attribute__((aligned(16))) uint4 g_zero_chunk;  // zero-initialised, never written
-template <class T> __device__ __forceinline__ uint4 ld16_if(const T* base, int64_t off, bool ok) {
-    const T* p = ok ? base + off : reinterpret_cast<const T*>(&g_zero_chunk);
-    return ld16(p);
+template <class T> __device__ __forceinline__ const T* at_if(const T* base, int64_t off, bool ok) {
+    return ok ? base + off : reinterpret_cast<const T*>(&g_zero_chunk);
 }
 // the same from an address that is aligned to an element only
 template <class T> __device__ __forceinline__ uint4 ld16u_if(const T* base, int64_t off, bool ok) {
-    const T* p = ok ? base + off : reinterpret_cast<const T*>(&g_zero_chunk);
     uint4 v;
-    __builtin_memcpy(&v, p, 16);
+    __builtin_memcpy(&v, at_if(base, off, ok), 16);
     return v;
 }
 // Drops the first `bytes` bytes of a chunk and fills up with zeros from behind.
@@ -97,6 +95,8 @@ __device__ __forceinline__ int mul24(int a, int b) { return __mul24(a, b); }
 //                                  row = first of V consecutive rows, col = k offset inside a tile.
 //   load(ctx, ks, k_end)           the chunk of the current tile (zeros outside the operand); called once
 //                                  per tile and chunk, in order; may step per-chunk state
+//   addr(ctx, ks, k_end)           the same, the address of the chunk (of sixteen zero bytes outside the operand); not for
+//                                  ragged and gathering loaders
 //   next(ks)                       step the per-thread state to the next tile (k += BK)
 //   settle(ctx, v, k, k_end)       only where kSettle: what remains to be done with a loaded chunk (whose first k is k, for
 //                                  k-contiguous loaders) before it goes to LDS
@@ -116,9 +116,10 @@ template <class T_> struct DenseKC {
         c.ok = row < rows;
         c.roff = (int64_t)(c.ok ? row : 0) * ld;
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
-        return ld16_if(p, c.roff + ks.k, c.ok && ks.k + V <= k_end);
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
+        return at_if(p, c.roff + ks.k, c.ok && ks.k + V <= k_end);
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const { ks.k += BK; }
 };
 
@@ -137,11 +138,12 @@ template <class T_> struct DenseRC {
         c.kl = kl;
         c.off = (c.ok ? row0 : 0) + (int64_t)(k_begin + kl) * ld;
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
-        uint4 v = ld16_if(p, c.off, c.ok && ks.kb + c.kl < k_end);
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
+        const T* q = at_if(p, c.off, c.ok && ks.kb + c.kl < k_end);
         c.off += BK * ld;
-        return v;
+        return q;
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const { ks.kb += BK; }
 };
 
@@ -231,11 +233,12 @@ template <class T_> struct ConvFwdA2 {
         c.w0 = (int)wo * g.stride - g.pad;
         c.base = (((int)n * g.H + c.h0) * g.W + c.w0) * g.Cin;
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
         const int h = c.h0 + ks.r, w = c.w0 + ks.s;
         const bool ok = c.ok && ks.k + V <= k_end && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
-        return ld16_if(x, c.base + ks.koff, ok);
+        return at_if(x, c.base + ks.koff, ok);
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const {
         ks.k += BK;
         ks.ch += BK;
@@ -276,19 +279,20 @@ template <class T_> struct ConvDgradA2 {
         c.nbase = (int)n * g.Ho * g.Wo * g.Cout;
         c.c0 = c.nbase + (c.hp * g.Wo + c.wp) * g.Cout;  // stride 1: offset = c0 + kterm
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
         const bool in_k = c.ok && ks.k + V <= k_end;
         const int hy = c.hp - ks.r, wy = c.wp - ks.s;
         if (g.stride == 1) {
             const bool ok = in_k && (unsigned)hy < (unsigned)g.Ho && (unsigned)wy < (unsigned)g.Wo;
-            return ld16_if(dy, c.c0 + ks.kterm, ok);
+            return at_if(dy, c.c0 + ks.kterm, ok);
         }
         uint32_t ho, hr, wo, wr;
         g.d_stride.divmod(hy < 0 ? 0 : hy, ho, hr);
         g.d_stride.divmod(wy < 0 ? 0 : wy, wo, wr);
         const bool ok = in_k && hy >= 0 && wy >= 0 && hr == 0 && wr == 0 && (int)ho < g.Ho && (int)wo < g.Wo;
-        return ld16_if(dy, c.nbase + ((int)ho * g.Wo + (int)wo) * g.Cout + ks.co, ok);
+        return at_if(dy, c.nbase + ((int)ho * g.Wo + (int)wo) * g.Cout + ks.co, ok);
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const {
         ks.k += BK;
         ks.co += BK;
@@ -324,7 +328,7 @@ template <class T_> struct ConvDgradB2 {
         c.ci0 = row0;
         c.kl = kl;
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
         const bool ok = c.ok && ks.kb + c.kl < k_end;
         int co = ks.co + c.kl, s = ks.s, r = ks.r;
         while (co >= g.Cout) {
@@ -332,8 +336,9 @@ template <class T_> struct ConvDgradB2 {
             if (++s == g.S) { s = 0; ++r; }
         }
         const int off = mul24(mul24(mul24(co, g.R) + r, g.S) + s, g.Cin) + c.ci0;
-        return ld16_if(w, off, ok);
+        return at_if(w, off, ok);
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const {
         ks.kb += BK;
         ks.co += BK;
@@ -373,10 +378,10 @@ template <class T_> struct ConvWgradB2 {
         g.d_wo.divmod(rem2, ho, wo);
         c.n = (int)n; c.ho = (int)ho; c.wo = (int)wo;
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
         const int h = c.ho * g.stride + c.dr, w = c.wo * g.stride + c.ds;
         const bool ok = c.ok && ks.kb + c.kl < k_end && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
-        uint4 v = ld16_if(x, mul24(mul24(mul24(c.n, g.H) + h, g.W) + w, g.Cin) + c.ci0, ok);
+        const T* v = at_if(x, mul24(mul24(mul24(c.n, g.H) + h, g.W) + w, g.Cin) + c.ci0, ok);
         // advance this chunk's position by BK
         c.wo += step_wo;
         c.ho += step_ho;
@@ -385,6 +390,7 @@ template <class T_> struct ConvWgradB2 {
         if (c.ho >= g.Ho) { c.ho -= g.Ho; ++c.n; }
         return v;
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const { ks.kb += BK; }
 };
 
@@ -464,12 +470,13 @@ template <class T_> struct ConvDgradA2P {
         c.wp = w + g.pad;
         c.nbase = n * g.Ho * g.Wo * g.Cout;
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
         const int hy = c.hp - ks.r, wy = c.wp - ks.s;   // even for the taps of this class
         const int ho = hy >> 1, wo = wy >> 1;
         const bool ok = c.ok && ks.k + V <= k_end && hy >= 0 && wy >= 0 && ho < g.Ho && wo < g.Wo;
-        return ld16_if(dy, c.nbase + (ho * g.Wo + wo) * g.Cout + ks.co, ok);
+        return at_if(dy, c.nbase + (ho * g.Wo + wo) * g.Cout + ks.co, ok);
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const {
         ks.k += BK;
         ks.co += BK;
@@ -499,13 +506,14 @@ template <class T_> struct ConvDgradB2P {
         c.ci0 = row0;
         c.kl = kl;
     }
-    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const {
+    __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
         const bool ok = c.ok && ks.kb + c.kl < k_end;
         int co = ks.co + c.kl, s = ks.s, r = ks.r;
         taps.carry(r, s, co, g);
         const int off = mul24(mul24(mul24(co, g.R) + r, g.S) + s, g.Cin) + c.ci0;
-        return ld16_if(w, off, ok);
+        return at_if(w, off, ok);
     }
+    __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const {
         ks.kb += BK;
         ks.co += BK;

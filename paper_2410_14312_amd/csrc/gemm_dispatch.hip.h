@@ -4,7 +4,7 @@
 #pragma once
 #include <hip/hip_ext.h>
 
-#include "gemm3.hip.h"
+#include "gemm4.hip.h"
 #include "gemm_small.hip.h"
 #include "kernels.h"
 #include "launch.h"
@@ -15,24 +15,22 @@ namespace tmps {
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// What a contraction runs on: tile shape of the tiled kernel and k-slices, or (bm = 32) the small kernel.
+// What a contraction runs on: tile shape of the tiled kernel, or the k-sharing kernel (by_k, 64 x 64), and k-slices.
 struct Plan2 {
     int bm, bn, slices;
+    bool by_k;
+    double cost;   // estimated cycles (2.4 GHz)
 };
 
 constexpr int kCUs = 256;   // compute units of the device the rules below are written for
 
 // ---- plans ----------------------------------------------------------------------------------------
-// fp32: the tile shape and k-slices of least estimated time.
-Plan2 plan_f32(int64_t M, int64_t N, int64_t K, bool rowsum);
-// bf16: plan_gemm's tile edge and slices; where the edge is 64 and the output tall the tiles are 128 x 64 (see there).
-Plan2 plan_bf16(int64_t M, int64_t N, int64_t K, bool rowsum);
-template <class T> static Plan2 plan_of(int64_t M, int64_t N, int64_t K, bool rowsum) {
-    if constexpr (sizeof(T) == 4) return plan_f32(M, N, K, rowsum);
-    else return plan_bf16(M, N, K, rowsum);
-}
-// Whether a dense contraction runs on the small kernel (gemm_small.hip.h) rather than on the given tiled plan.
-bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& tiled);
+// The plan of least estimated time for the tiled kernel alone (kByKNo) or for it and the k-sharing kernel, on matrices or
+// with an operand that a convolution's loader addresses.  esize: bytes of an operand element.
+enum { kByKNo = 0, kByKDense, kByKConv };
+Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k);
+// Whether a dense contraction runs on the small kernel (gemm_small.hip.h) rather than by the given plan.
+bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& other);
 
 // out[i] = sum over slices of part[slice * count + i], in slice order
 hipError_t slice_sum(const float* part, float* out, int64_t count, int slices, hipStream_t s);
@@ -70,10 +68,33 @@ template <class Op> struct IsGather { static constexpr bool value = false; };
 template <class T, bool KC, class View> struct IsGather<Gather<T, KC, View>> { static constexpr bool value = true; };
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t launch4(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
+    auto kern = gemm4_kernel<ROWSUM, AOp, BOp, Epi>;
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kGemm4Lds);
+    if (attr != hipSuccess) return attr;
+    dim3 grid(cdiv(N, 64), cdiv(M, 64), nz);
+    const int col_major = N > M ? 1 : 0;
+    return launch_timed(kc, kern, grid, dim3(256), kGemm4Lds, s, A, B, epi, M, N, K, per, col_major, (N % 8 == 0 && epi.wide_ok()) ? 1 : 0,
+                        FastDiv(grid.x * grid.y), FastDiv(col_major ? grid.y : grid.x));
+}
+
+// how the k-sharing kernel can take a pair of loaders (it needs a chunk's address)
+template <class Op> struct IsMatrix { static constexpr bool value = false; };
+template <class T> struct IsMatrix<DenseKC<T>> { static constexpr bool value = true; };
+template <class T> struct IsMatrix<DenseRC<T>> { static constexpr bool value = true; };
+template <class Op> constexpr bool has_addr() { return !IsGather<Op>::value && !Op::kSettle; }
+template <class AOp, class BOp> constexpr int by_k_mode() {
+    return !has_addr<AOp>() || !has_addr<BOp>() ? kByKNo : IsMatrix<AOp>::value && IsMatrix<BOp>::value ? kByKDense : kByKConv;
+}
+
+template <bool ROWSUM, class AOp, class BOp, class Epi>
 static hipError_t launch2_tile(int kc, const Plan2& p, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
                                int nz, hipStream_t s) {
     if constexpr (IsGather<AOp>::value || IsGather<BOp>::value) return launch2_inst<64, 64, 1, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
     else {
+        if constexpr (by_k_mode<AOp, BOp>() != kByKNo) {
+            if (p.by_k) return launch4<ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+        }
         if (p.bm == 128 && p.bn == 128) return launch2_inst<128, 128, 2, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
         if constexpr (!ROWSUM && !AOp::kSettle) {
             if (p.bm == 128) return launch2_inst<128, 64, 2, false>(kc, A, B, epi, M, N, K, per, nz, s);
@@ -90,8 +111,8 @@ template <class AOp, class BOp, class Epi>
 static hipError_t run2(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, float* ws, hipStream_t s, int tile = 0) {
     typedef typename AOp::T T;
     if (M <= 0 || N <= 0) return hipSuccess;
-    Plan2 p = plan_of<T>(M, N, K, false);
-    if (tile) p.bm = p.bn = tile;
+    Plan2 p = plan_for(M, N, K, false, sizeof(T), by_k_mode<AOp, BOp>());
+    if (tile && !p.by_k) p.bm = p.bn = tile;
     int per, nz;
     slice_geometry(K, ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
     if (nz <= 1) return launch2_tile<false>(kc, p, A, B, epi, M, N, K, per, nz, s);
@@ -110,7 +131,7 @@ static hipError_t run2(int kc, const AOp& A, const BOp& B, const Epi& epi, int M
 template <class AOp, class BOp>
 static hipError_t run2_wgrad(int kc, const AOp& A, const BOp& B, float* gw, int rows, int cols, int64_t K, float* ws, hipStream_t s) {
     typedef typename AOp::T T;
-    const Plan2 p = plan_of<T>(rows, cols, K, true);
+    const Plan2 p = plan_for(rows, cols, K, true, sizeof(T), by_k_mode<AOp, BOp>());
     int per, nz;
     slice_geometry(K, ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
     int64_t count = (int64_t)rows * cols + rows;
@@ -156,7 +177,7 @@ static inline ConvGeom2 geom2(const ConvShape& c) {
 template <class T, class Epi>
 static hipError_t dense_forward_t(int kc, const T* x, const T* w, const Epi& epi, int B, int Din, int Dout, float* ws, hipStream_t s) {
     constexpr int V = ElemTile<T>::V;
-    if (small_is_better(B, Dout, Din, sizeof(T), plan_of<T>(B, Dout, Din, false)))
+    if (small_is_better(B, Dout, Din, sizeof(T), plan_for(B, Dout, Din, false, sizeof(T), kByKDense)))
         return run_small<false>(kc, SmallOperand<T, true>{x, B, Din}, SmallOperand<T, true>{w, Dout, Din}, epi, B, Dout, Din, s);
     if (Din % V == 0 && aligned16(x) && aligned16(w))
         return run2(kc, DenseKC<T>{x, B, Din, Din}, DenseKC<T>{w, Dout, Din, Din}, epi, B, Dout, Din, ws, s);
@@ -168,7 +189,7 @@ static hipError_t dense_forward_t(int kc, const T* x, const T* w, const Epi& epi
 template <class T>
 static hipError_t dense_dgrad_t(int kc, const T* dy, const T* w, const EpiMask<T, T>& epi, int B, int Din, int Dout, float* ws, hipStream_t s) {
     constexpr int V = ElemTile<T>::V;
-    if (small_is_better(B, Din, Dout, sizeof(T), plan_of<T>(B, Din, Dout, false)))
+    if (small_is_better(B, Din, Dout, sizeof(T), plan_for(B, Din, Dout, false, sizeof(T), kByKDense)))
         return run_small<false>(kc, SmallOperand<T, true>{dy, B, Dout}, SmallOperand<T, false>{w, Din, Din}, epi, B, Din, Dout, s);
     if (Dout % V == 0 && Din % V == 0 && aligned16(dy) && aligned16(w))
         return run2(kc, DenseKC<T>{dy, B, Dout, Dout}, DenseRC<T>{w, Din, Dout, Din}, epi, B, Din, Dout, ws, s);
@@ -181,7 +202,7 @@ static hipError_t dense_dgrad_t(int kc, const T* dy, const T* w, const EpiMask<T
 template <class T>
 static hipError_t dense_wgrad_t(int kc, const T* dy, const T* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) {
     constexpr int V = ElemTile<T>::V;
-    if (small_is_better(Dout, Din, B, sizeof(T), plan_of<T>(Dout, Din, B, true)))
+    if (small_is_better(Dout, Din, B, sizeof(T), plan_for(Dout, Din, B, true, sizeof(T), kByKDense)))
         return run_small<true>(kc, SmallOperand<T, false>{dy, Dout, Dout}, SmallOperand<T, false>{x, Din, Din},
                                EpiWgrad{gw, Din, (int64_t)Dout * Din, 0}, Dout, Din, B, s);
     if (Dout % V == 0 && Din % V == 0 && aligned16(dy) && aligned16(x))
@@ -218,7 +239,7 @@ static hipError_t conv_dgrad_t(const T* dy, const T* w, const EpiMask<T, T>& epi
         // k extent of the largest class; every class a whole number of tiles; the 16-byte epilogue (the one
         // that asks the loader where a row lies in memory), also for the partial sums of a split.
         const int Kp = ((c.R + 1) / 2) * ((c.S + 1) / 2) * c.Cout;
-        const Plan2 plan = plan_of<T>(M, c.Cin, Kp, false);
+        const Plan2 plan = plan_for(M, c.Cin, Kp, false, sizeof(T), kByKConv);
         const int edge = plan.bn;   // (64 for the tall tiles: this order needs square ones)
         const int Mc = M / 4;
         int per, nz;

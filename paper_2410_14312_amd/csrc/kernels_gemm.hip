@@ -3,7 +3,7 @@
 // kernels_gemm_f32.hip, those with gathering loaders in kernels_gemm_gather.hip).
 #include <math.h>
 
-#include <cstdlib>
+#include <algorithm>
 
 #include "gemm_dispatch.hip.h"
 
@@ -46,63 +46,87 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K) {
     return p;
 }
 
-Plan2 plan_bf16(int64_t M, int64_t N, int64_t K, bool rowsum) {
-    const GemmPlan p = plan_gemm(M, N, K);
-    // Where the plan's edge is 64, the output has 512 rows or more and 128 x 64 tiles still make 192 workgroups, the tiles
-    // are 128 rows tall: a 128 x 64 tile reads a quarter less LDS per MFMA than a 64 x 64 one, and with the stages'
-    // kernels sharing the device that outweighs having half as many workgroups (measured: GPT-2 and ResNet-50 steps 1 %
-    // shorter, VGG-16 1-2 %; 128 x 128 and 64 x 128 for the same launches did worse; below 192 workgroups the launch
-    // itself gets slower and the step no faster).
-    const bool tall = p.tile == 64 && !rowsum && M >= 512 && (int64_t)cdiv(M, 128) * cdiv(N, 64) * p.slices >= 192;
-    return {tall ? 128 : p.tile, p.tile, p.slices};
+// ---- estimates (cycles at 2.4 GHz) ----
+// what a k-split costs beside its kernel: the finishing launch and the partial sums' way through memory (5 TB/s)
+static double split_cost(int64_t M, int64_t N, int64_t slices) { return slices > 1 ? 9000.0 + (double)slices * M * N * 8.0 / 2083.0 : 0.0; }
+
+// Tiled kernel in bf16: cycles of a k-tile of a workgroup alone on its unit, and of each of several that share one
+// (1024 rows x 768: 0.3 us; 1024 x 2304 and 3072 in 128 x 64 tiles and 8192 x 768 in 128 x 128: two to a unit).  With a
+// convolution's loaders a k-tile takes longer (8 x 8 x 256 -> 256 on 32 images: 1000 cycles forward, 1400 in the gradients).
+static double tiled_cost_bf16(int64_t M, int64_t N, int64_t K, int bm, int bn, int by_k, int64_t slices) {
+    const bool conv = by_k == kByKConv;
+    const double alone = bm * bn == 4096 ? (conv ? 1100.0 : 720.0) : bm * bn == 8192 ? 1140.0 : (conv ? 1800.0 : 1500.0);
+    const double shared = bm * bn == 4096 ? (conv ? 600.0 : 400.0) : alone;
+    const double rounds = (double)cdiv((int64_t)cdiv(M, bm) * cdiv(N, bn) * slices, kCUs);
+    return 5300.0 + (double)cdiv(cdiv(K, 64), slices) * fmax(alone, shared * rounds) + split_cost(M, N, slices);
 }
 
-// Estimated cycles (2.4 GHz) of an fp32 contraction on the tiled kernel: the busiest compute unit's multiplies (1024
-// cycles for a k-tile of a 64 x 64 tile; small tiles weighed up for the LDS traffic they need more of per product), what
-// a workgroup alone on its unit cannot hide, the fixed part of a launch, and the finishing launch and partial sums of a
-// split (5 TB/s).
+// fp32: the busiest compute unit's multiplies (1024 cycles for a k-tile of a 64 x 64 tile; small tiles weighed up for the
+// LDS traffic they need more of per product) and what a workgroup alone on its unit cannot hide.
 static double tiled_cost_f32(int64_t M, int64_t N, int64_t K, int bm, int bn, int64_t slices) {
     const double per_ktile = (bm / 64) * (bn / 64) * 1024.0, weight = bm * bn == 4096 ? 1.10 : bm * bn == 8192 ? 1.04 : 1.0;
     const double nk = (double)cdiv(cdiv(K, 32), slices), rounds = (double)cdiv((int64_t)cdiv(M, bm) * cdiv(N, bn) * slices, kCUs);
-    double t = rounds * nk * per_ktile * weight + (rounds <= 1.0 ? 300.0 * nk : 0.0) + 5000.0;
-    if (slices > 1) t += 8000.0 + (double)slices * M * N * 8.0 / 2083.0;
-    return t;
+    return rounds * nk * per_ktile * weight + (rounds <= 1.0 ? 300.0 * nk : 0.0) + 5000.0 + split_cost(M, N, slices);
 }
 
-Plan2 plan_f32(int64_t M, int64_t N, int64_t K, bool rowsum) {
-    static const int shape[3][2] = {{64, 64}, {128, 64}, {128, 128}};
-    Plan2 best{64, 64, 1};
-    double best_t = 0.0;
-    for (const auto& sh : shape) {
-        if (rowsum && sh[0] != sh[1]) continue;
+// k-sharing kernel: a wave's k-tile takes 1800 cycles in bf16 (80 bytes/ns into the unit; 1024 x 768 x 3072), 2500 where
+// addresses are a convolution's (8 x 8 x 256 -> 256), and 4300 in fp32 (its multiplies); one workgroup to a
+// unit, prologue and epilogue not overlapped.
+static double by_k_cost(int64_t M, int64_t N, int64_t K, int esize, int by_k, int64_t slices) {
+    const int64_t nk = cdiv(cdiv(K, 128 / esize), slices);
+    const double rounds = (double)cdiv((int64_t)cdiv(M, 64) * cdiv(N, 64) * slices, kCUs);
+    const double per_ktile = esize == 4 ? 4300.0 : by_k == kByKConv ? 2500.0 : 1800.0;
+    return 5500.0 + rounds * ((double)cdiv(nk, 4) * per_ktile + 3500.0) + split_cost(M, N, slices);
+}
+
+Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k) {
+    Plan2 best{64, 64, 1, false, 0.0};
+    auto each_split = [&](auto&& f) {   // (at most 64 MB of partial sums, at least 128 k to a slice)
         for (int64_t sl = 1; sl <= 64; sl += sl < 8 ? 1 : sl < 16 ? 2 : 8) {
-            if (sl > 1 && (K < sl * 128 || sl * M * N > (int64_t(1) << 24))) break;   // (at most 64 MB of partial sums)
-            const double t = tiled_cost_f32(M, N, K, sh[0], sh[1], sl);
-            if (best_t == 0.0 || t < best_t) {
-                best_t = t;
-                best = {sh[0], sh[1], (int)sl};
-            }
+            if (sl > 1 && (K < sl * 128 || sl * M * N > (int64_t(1) << 24))) break;
+            f(sl);
         }
+    };
+    if (esize == 4) {
+        static const int shape[3][2] = {{64, 64}, {128, 64}, {128, 128}};
+        for (const auto& sh : shape) {
+            if (rowsum && sh[0] != sh[1]) continue;
+            each_split([&](int64_t sl) {
+                const double t = tiled_cost_f32(M, N, K, sh[0], sh[1], sl);
+                if (best.cost == 0.0 || t < best.cost) best = {sh[0], sh[1], (int)sl, false, t};
+            });
+        }
+    } else {
+        const GemmPlan p = plan_gemm(M, N, K);
+        // Where the plan's edge is 64, the output has 512 rows or more and 128 x 64 tiles still make 192 workgroups, the
+        // tiles are 128 rows tall: a 128 x 64 tile reads a quarter less LDS per MFMA than a 64 x 64 one, and with the
+        // stages' kernels sharing the device that outweighs having half as many workgroups (measured: GPT-2 and ResNet-50
+        // steps 1 % shorter, VGG-16 1-2 %; 128 x 128 and 64 x 128 for the same launches did worse; below 192 workgroups
+        // the launch itself gets slower and the step no faster).
+        const bool tall = p.tile == 64 && !rowsum && M >= 512 && (int64_t)cdiv(M, 128) * cdiv(N, 64) * p.slices >= 192;
+        best = {tall ? 128 : p.tile, p.tile, p.slices, false, 0.0};
+        best.cost = tiled_cost_bf16(M, N, K, best.bm, best.bn, by_k, best.slices);
+    }
+    if (by_k != kByKNo) {
+        Plan2 k{64, 64, 1, true, 0.0};
+        each_split([&](int64_t sl) {
+            const double t = by_k_cost(M, N, K, esize, by_k, sl);
+            if (k.cost == 0.0 || t < k.cost) {
+                k.cost = t;
+                k.slices = (int)sl;
+            }
+        });
+        if (k.cost < 0.9 * best.cost) best = k;
     }
     return best;
 }
 
-// The small kernel against the tiled plan, both in estimated cycles.  Small: its fragment loads touch 32 rows each, so a
-// compute unit's L1 sets the pace: 9.5 cycles per k of a tile in bf16, 18.5 in fp32 (measured from K = 512 to 4096 on 64 to
-// 512 tiles), and a fixed part.  Tiled in bf16: 720 cycles per k-tile of a workgroup (1024 x 768 x 768: 0.3 us), up to two
-// workgroups of a unit overlapping; 9000 cycles for the finishing launch of a split.
-bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& tiled) {
+// Small kernel: its fragment loads touch 32 rows each, so a compute unit's L1 sets the pace: 9.5 cycles per k of a tile in
+// bf16, 18.5 in fp32 (measured from K = 512 to 4096 on 64 to 512 tiles), and a fixed part.
+bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& other) {
     const int64_t tiles = (int64_t)cdiv(M, 32) * cdiv(N, 32);
     if (tiles > 2 * kCUs) return false;
-    const double small = 2500.0 + (double)cdiv(tiles, kCUs) * K * (esize == 4 ? 18.5 : 9.5);
-    double t;
-    if (esize == 4) t = tiled_cost_f32(M, N, K, tiled.bm, tiled.bn, tiled.slices);
-    else {
-        const double load = (double)cdiv(M, tiled.bm) * cdiv(N, tiled.bn) * tiled.slices / (2.0 * kCUs);
-        t = 5300.0 + (double)cdiv(cdiv(K, 64), tiled.slices) * 720.0 * fmax(1.0, load);
-        if (tiled.slices > 1) t += 9000.0 + (double)tiled.slices * M * N * 8.0 / 2083.0;
-    }
-    return small < t;
+    return 2500.0 + (double)cdiv(tiles, kCUs) * K * (esize == 4 ? 18.5 : 9.5) < other.cost;
 }
 
 int g3_wgrad_slices(int64_t M, int64_t N, int64_t K);
@@ -110,16 +134,11 @@ int g3_long_k_slices(int64_t M, int64_t N, int64_t K);
 
 size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t K, int flags) {
     const bool with_rowsum = (flags & kWsRowSums) != 0;
-    int slices;
-    if (flags & kWsF32) slices = plan_f32(M, N, K, with_rowsum).slices;
-    else slices = plan_gemm(M, N, K).slices;
-    if (flags & kWsF32) {
-        // (no persistent path)
-    } else if (with_rowsum) {   // a weight gradient may go to the persistent path, with its own number of slices
-        const int s3 = g3_wgrad_slices(M, N, K);
-        if (s3 > slices) slices = s3;
-    } else {             // and so may an input gradient with a very long contraction
-        const int s3 = g3_long_k_slices(M, N, K);
+    const int esize = (flags & kWsF32) ? 4 : 2;
+    int slices = 1;   // (which plan a launch takes depends on what its operands are and on their alignment)
+    for (int by_k : {kByKNo, kByKDense, kByKConv}) slices = std::max(slices, plan_for(M, N, K, with_rowsum, esize, by_k).slices);
+    if (esize == 2) {   // a weight gradient, or an input gradient with a very long contraction, may go to the persistent path
+        const int s3 = with_rowsum ? g3_wgrad_slices(M, N, K) : g3_long_k_slices(M, N, K);
         if (s3 > slices) slices = s3;
     }
     if (slices <= 1) return 0;

@@ -45,3 +45,23 @@ CONV = [
 @pytest.mark.parametrize("h,w,cin,cout,r,stride,pad,micro,N", CONV)
 def test_conv_edges(dtype, h, w, cin, cout, r, stride, pad, micro, N):
     run_stage_case([conv(h, w, cin, cout, r, stride, pad, False)], dtype, micro, N, seed=h + cin * cout)
+
+
+# Outputs of few 64 x 64 tiles over a long k: the kernel whose waves share k (whole and partial k-tiles, fewer k-tiles
+# than waves' stages, ragged last tiles, a convolution's loaders in all passes)
+BY_K = [
+    [linear(1544, 584, False)],           # a tail of 8 in the forward pass, whole tiles in the weight gradient
+    [linear(776, 1160, False)],
+    [linear(2048, 512, False)],
+]
+BY_K_CONV = [
+    [conv(8, 8, 256, 136, 3, 1, 1, False)],
+    [conv(7, 7, 128, 264, 3, 2, 1, False)],
+    [conv(14, 14, 512, 128, 1, 1, 0, False)],
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("micro,layers", [(330, l) for l in BY_K] + [(m, l) for l in BY_K_CONV for m in (5, 16)])
+def test_few_tiles_long_k(dtype, micro, layers):
+    run_stage_case(layers, dtype, micro, 1, seed=micro)
