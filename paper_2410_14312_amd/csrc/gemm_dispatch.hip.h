@@ -221,9 +221,20 @@ static inline bool small_enough(const ConvShape& c) {
            pout * c.Cout < (int64_t(1) << 31) && wel < (int64_t(1) << 31) && c.Cin < (1 << 20) && c.Cout < (1 << 20);
 }
 
+// Convolutions on runs of rows (kernels_conv_rows.hip, bf16): the variant to launch, 0 for a convolution that the kernel cannot
+// take or where the other kernels, estimated at other_us, are quicker.
+constexpr int kMaxLds = 160 * 1024;
+int conv_rows_variant(const ConvShape& c, int64_t M, int N, int C, double other_us);
+template <bool DGRAD, class Epi>
+hipError_t conv_rows(int variant, int kc, const bf16_t* x, const bf16_t* w, const Epi& epi, const ConvShape& c, hipStream_t s);
+
 template <class T, class Epi>
 static hipError_t conv_forward_t(const T* x, const T* w, const Epi& epi, const ConvShape& c, float* ws, hipStream_t s) {
     const int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
+    if constexpr (sizeof(T) == 2) {
+        const int v = conv_rows_variant(c, M, c.Cout, c.Cin, plan_for(M, c.Cout, K, false, 2, kByKConv).cost / 2400.0);
+        if (v && epi.wide_ok() && aligned16(x) && aligned16(w)) return conv_rows<false>(v, kcConvFwd, x, w, epi, c, s);
+    }
     if (c.Cin % ElemTile<T>::V == 0 && aligned16(x) && aligned16(w) && small_enough(c))
         return run2(kcConvFwd, ConvFwdA2<T>{x, geom2(c), M, K}, DenseKC<T>{w, c.Cout, K, K}, epi, M, c.Cout, K, ws, s);
     return gather_conv_forward<T>(x, w, epi, c, ws, s);
@@ -234,6 +245,10 @@ static hipError_t conv_dgrad_t(const T* dy, const T* w, const EpiMask<T, T>& epi
     const int M = c.B * c.H * c.W, K = c.R * c.S * c.Cout;
     constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
     if (c.Cin % V != 0 || c.Cout % V != 0 || !aligned16(dy) || !aligned16(w) || !small_enough(c)) return gather_conv_dgrad<T>(dy, w, epi, c, ws, s);
+    if constexpr (sizeof(T) == 2) {
+        const int v = conv_rows_variant(c, M, c.Cin, c.Cout, plan_for(M, c.Cin, K, false, 2, kByKConv).cost / 2400.0);
+        if (v && epi.wide_ok()) return conv_rows<true>(v, kcConvDgrad, dy, w, epi, c, s);
+    }
     if (c.stride == 2 && c.H % 2 == 0 && c.W % 2 == 0 && c.Cin % 8 == 0) {
         // Rows ordered by the parity of their position, each class walking only the filter taps that reach it:
         // k extent of the largest class; every class a whole number of tiles; the 16-byte epilogue (the one
