@@ -140,9 +140,10 @@ template <class T_> struct DenseRC {
     }
     __device__ __forceinline__ const T* addr(Ctx& c, const KS& ks, int k_end) const {
         const T* q = at_if(p, c.off, c.ok && ks.kb + c.kl < k_end);
-        c.off += BK * ld;
+        skip(c);
         return q;
     }
+    __device__ __forceinline__ void skip(Ctx& c) const { c.off += BK * ld; }
     __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const { ks.kb += BK; }
 };
@@ -382,13 +383,16 @@ template <class T_> struct ConvWgradB2 {
         const int h = c.ho * g.stride + c.dr, w = c.wo * g.stride + c.ds;
         const bool ok = c.ok && ks.kb + c.kl < k_end && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
         const T* v = at_if(x, mul24(mul24(mul24(c.n, g.H) + h, g.W) + w, g.Cin) + c.ci0, ok);
-        // advance this chunk's position by BK
+        skip(c);
+        return v;
+    }
+    // advance a chunk's position by BK
+    __device__ __forceinline__ void skip(Ctx& c) const {
         c.wo += step_wo;
         c.ho += step_ho;
         c.n += step_n;
         if (c.wo >= g.Wo) { c.wo -= g.Wo; ++c.ho; }
         if (c.ho >= g.Ho) { c.ho -= g.Ho; ++c.n; }
-        return v;
     }
     __device__ __forceinline__ uint4 load(Ctx& c, const KS& ks, int k_end) const { return ld16(addr(c, ks, k_end)); }
     __device__ __forceinline__ void next(KS& ks) const { ks.kb += BK; }
@@ -723,6 +727,18 @@ __device__ __forceinline__ typename Frag<T>::type read_frag(const T* tile, int r
     }
 }
 
+// sum + the elements of a fragment.  bf16 pairs go through the dot product with (1, 1), four instructions where converting
+// and adding takes sixteen: the waves that sum A's rows for a bias gradient are on the launch's critical path (8192 x 768
+// -> 768 on the k-sharing kernel: 41 -> 37 us).
+__device__ __forceinline__ float add_frag(float sum, const bf16x8_t& v) {
+    typedef __bf16 pair_t __attribute__((ext_vector_type(2)));
+    const pair_t one = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) sum = __builtin_amdgcn_fdot2_f32_bf16(pair_t{v[e], v[e + 1]}, one, sum, false);
+    return sum;
+}
+__device__ __forceinline__ float add_frag(float sum, const f32x4v_t& v) { return sum + ((v[0] + v[1]) + (v[2] + v[3])); }
+
 // LDS bytes of one launch: two buffers of an A tile and a B tile.
 template <int BM, int BN, class AOp, class BOp> constexpr int gemm2_lds_bytes() {
     typedef typename AOp::T T;
@@ -909,9 +925,7 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
 #pragma unroll
             for (int g = 0; g < 4; ++g)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int e = 0; e < V; ++e) rsum[i] += (float)af[g][i][e];
+                for (int i = 0; i < TM; ++i) rsum[i] = add_frag(rsum[i], af[g][i]);
         }
     };
 

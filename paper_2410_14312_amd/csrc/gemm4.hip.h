@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(AOp A, BOp B, Epi epi, in
                                                         FastDiv d_plane, FastDiv d_minor) {
     typedef typename AOp::T T;
     typedef typename Frag<T>::type frag_t;
-    constexpr int BK = ElemTile<T>::BK, V = ElemTile<T>::V, NS = kGemm4Stages;
+    constexpr int BK = ElemTile<T>::BK, NS = kGemm4Stages;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     const lds_t smem = (lds_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -171,9 +171,7 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(AOp A, BOp B, Epi epi, in
             }
             if (ROWSUM && sum_rows) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int e = 0; e < V; ++e) rs[i] += (float)af[f][i][e];
+                for (int i = 0; i < 2; ++i) rs[i] = add_frag(rs[i], af[f][i]);
             }
         }
         if (fill) step();

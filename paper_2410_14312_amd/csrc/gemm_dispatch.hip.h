@@ -4,7 +4,7 @@
 #pragma once
 #include <hip/hip_ext.h>
 
-#include "gemm4.hip.h"
+#include "gemm5.hip.h"
 #include "gemm_small.hip.h"
 #include "kernels.h"
 #include "launch.h"
@@ -15,18 +15,19 @@ namespace tmps {
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// What a contraction runs on: tile shape of the tiled kernel, or the k-sharing kernel (by_k, 64 x 64), and k-slices.
+// What a contraction runs on: the tiled kernel with a tile shape, the k-sharing kernel (64 x 64) or the 128 x 128 kernel with
+// asynchronous copies, and k-slices.
+enum { kTiled = 0, kByK, kAsync };
 struct Plan2 {
-    int bm, bn, slices;
-    bool by_k;
+    int bm, bn, slices, kind;
     double cost;   // estimated cycles (2.4 GHz)
 };
 
 constexpr int kCUs = 256;   // compute units of the device the rules below are written for
 
 // ---- plans ----------------------------------------------------------------------------------------
-// The plan of least estimated time for the tiled kernel alone (kByKNo) or for it and the k-sharing kernel, on matrices or
-// with an operand that a convolution's loader addresses.  esize: bytes of an operand element.
+// The plan of least estimated time for the tiled kernel alone (kByKNo) or for it and the kernels with asynchronous copies, on matrices
+// or with an operand that a convolution's loader addresses.  esize: bytes of an operand element.
 enum { kByKNo = 0, kByKDense, kByKConv };
 Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k);
 // Whether a dense contraction runs on the small kernel (gemm_small.hip.h) rather than by the given plan.
@@ -88,12 +89,27 @@ template <class AOp, class BOp> constexpr int by_k_mode() {
 }
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t launch5(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
+    constexpr int lds = kGemm5Lds;
+    auto kern = gemm5_kernel<ROWSUM, AOp, BOp, Epi>;
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return attr;
+    dim3 grid(cdiv(N, 128), cdiv(M, 128), nz);
+    const int col_major = N > M ? 1 : 0;
+    return launch_timed(kc, kern, grid, dim3(64 * kGemm5Waves), lds, s, A, B, epi, M, N, K, per, col_major, FastDiv(grid.x * grid.y), FastDiv(col_major ? grid.y : grid.x));
+}
+
+template <bool ROWSUM, class AOp, class BOp, class Epi>
 static hipError_t launch2_tile(int kc, const Plan2& p, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
                                int nz, hipStream_t s) {
     if constexpr (IsGather<AOp>::value || IsGather<BOp>::value) return launch2_inst<64, 64, 1, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
     else {
         if constexpr (by_k_mode<AOp, BOp>() != kByKNo) {
-            if (p.by_k) return launch4<ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+            if (p.kind == kByK) return launch4<ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+            if constexpr (sizeof(typename AOp::T) == 2) {
+                // (its epilogue has only the 16-byte form)
+                if (p.kind == kAsync && N % 8 == 0 && epi.wide_ok()) return launch5<ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+            }
         }
         if (p.bm == 128 && p.bn == 128) return launch2_inst<128, 128, 2, ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
         if constexpr (!ROWSUM && !AOp::kSettle) {
@@ -112,7 +128,10 @@ static hipError_t run2(int kc, const AOp& A, const BOp& B, const Epi& epi, int M
     typedef typename AOp::T T;
     if (M <= 0 || N <= 0) return hipSuccess;
     Plan2 p = plan_for(M, N, K, false, sizeof(T), by_k_mode<AOp, BOp>());
-    if (tile && !p.by_k) p.bm = p.bn = tile;
+    if (tile && p.kind != kByK) {
+        if (tile != p.bm) p.kind = kTiled;
+        p.bm = p.bn = tile;
+    }
     int per, nz;
     slice_geometry(K, ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
     if (nz <= 1) return launch2_tile<false>(kc, p, A, B, epi, M, N, K, per, nz, s);

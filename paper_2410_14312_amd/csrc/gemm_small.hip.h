@@ -68,10 +68,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(AOp A, BOp B, Epi e
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc[e & 1], 0, 0, 0);
         }
-        if (ROWSUM) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) rsum += (float)a[e];
-        }
+        if (ROWSUM) rsum = add_frag(rsum, a);
     };
     frag_t fa[D], fb[D];   // ring: pair i of this wave in place i % D
     auto fetch = [&](int d, int i) {

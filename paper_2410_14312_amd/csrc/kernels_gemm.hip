@@ -52,11 +52,12 @@ static double split_cost(int64_t M, int64_t N, int64_t slices) { return slices >
 
 // Tiled kernel in bf16: cycles of a k-tile of a workgroup alone on its unit, and of each of several that share one
 // (1024 rows x 768: 0.3 us; 1024 x 2304 and 3072 in 128 x 64 tiles and 8192 x 768 in 128 x 128: two to a unit).  With a
-// convolution's loaders a k-tile takes longer (8 x 8 x 256 -> 256 on 32 images: 1000 cycles forward, 1400 in the gradients).
-static double tiled_cost_bf16(int64_t M, int64_t N, int64_t K, int bm, int bn, int by_k, int64_t slices) {
+// convolution's loaders a k-tile takes longer (8 x 8 x 256 -> 256 on 32 images: 1000 cycles forward, 1400 in the gradients), and
+// with both operands read across k in a weight gradient (1024 and 4096 rows x 768 -> 2304 and 3072).
+static double tiled_cost_bf16(int64_t M, int64_t N, int64_t K, int bm, int bn, bool rowsum, int by_k, int64_t slices) {
     const bool conv = by_k == kByKConv;
-    const double alone = bm * bn == 4096 ? (conv ? 1100.0 : 720.0) : bm * bn == 8192 ? 1140.0 : (conv ? 1800.0 : 1500.0);
-    const double shared = bm * bn == 4096 ? (conv ? 600.0 : 400.0) : alone;
+    const double alone = bm * bn == 4096 ? (conv ? 1100.0 : rowsum ? 880.0 : 720.0) : bm * bn == 8192 ? 1140.0 : (conv ? 1800.0 : 1500.0);
+    const double shared = bm * bn == 4096 ? (rowsum ? 670.0 : conv ? 600.0 : 400.0) : alone;
     const double rounds = (double)cdiv((int64_t)cdiv(M, bm) * cdiv(N, bn) * slices, kCUs);
     return 5300.0 + (double)cdiv(cdiv(K, 64), slices) * fmax(alone, shared * rounds) + split_cost(M, N, slices);
 }
@@ -69,18 +70,25 @@ static double tiled_cost_f32(int64_t M, int64_t N, int64_t K, int bm, int bn, in
     return rounds * nk * per_ktile * weight + (rounds <= 1.0 ? 300.0 * nk : 0.0) + 5000.0 + split_cost(M, N, slices);
 }
 
-// k-sharing kernel: a wave's k-tile takes 1800 cycles in bf16 (80 bytes/ns into the unit; 1024 x 768 x 3072), 2500 where
-// addresses are a convolution's (8 x 8 x 256 -> 256), and 4300 in fp32 (its multiplies); one workgroup to a
-// unit, prologue and epilogue not overlapped.
-static double by_k_cost(int64_t M, int64_t N, int64_t K, int esize, int by_k, int64_t slices) {
+// k-sharing kernel: a wave's k-tile takes 1800 cycles in bf16 (80 bytes/ns into the unit; 1024 x 768 x 3072), 2250 in a weight
+// gradient (8192 x 768 -> 768), 2500 where addresses are a convolution's (8 x 8 x 256 -> 256), and 4300 in fp32 (its multiplies);
+// one workgroup to a unit, prologue and epilogue not overlapped.
+static double by_k_cost(int64_t M, int64_t N, int64_t K, int esize, bool rowsum, int by_k, int64_t slices) {
     const int64_t nk = cdiv(cdiv(K, 128 / esize), slices);
     const double rounds = (double)cdiv((int64_t)cdiv(M, 64) * cdiv(N, 64) * slices, kCUs);
-    const double per_ktile = esize == 4 ? 4300.0 : by_k == kByKConv ? 2500.0 : 1800.0;
+    const double per_ktile = esize == 4 ? 4300.0 : by_k == kByKConv ? 2500.0 : rowsum ? 2250.0 : 1800.0;
     return 5500.0 + rounds * ((double)cdiv(nk, 4) * per_ktile + 3500.0) + split_cost(M, N, slices);
 }
 
+// 128 x 128 kernel with asynchronous copies: two k-tiles a step, one workgroup to a unit (1024 and 4096 rows x 768 to 3072).
+static double async_cost(int64_t M, int64_t N, int64_t K, int by_k, int64_t slices) {
+    const double steps = (double)cdiv(cdiv(cdiv(K, 64), slices), 2);
+    const double rounds = (double)cdiv((int64_t)cdiv(M, 128) * cdiv(N, 128) * slices, kCUs);
+    return rounds * (11300.0 + steps * (by_k == kByKConv ? 2900.0 : 2470.0)) + split_cost(M, N, slices);
+}
+
 Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k) {
-    Plan2 best{64, 64, 1, false, 0.0};
+    Plan2 best{64, 64, 1, kTiled, 0.0};
     auto each_split = [&](auto&& f) {   // (at most 64 MB of partial sums, at least 128 k to a slice)
         for (int64_t sl = 1; sl <= 64; sl += sl < 8 ? 1 : sl < 16 ? 2 : 8) {
             if (sl > 1 && (K < sl * 128 || sl * M * N > (int64_t(1) << 24))) break;
@@ -93,7 +101,7 @@ Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k
             if (rowsum && sh[0] != sh[1]) continue;
             each_split([&](int64_t sl) {
                 const double t = tiled_cost_f32(M, N, K, sh[0], sh[1], sl);
-                if (best.cost == 0.0 || t < best.cost) best = {sh[0], sh[1], (int)sl, false, t};
+                if (best.cost == 0.0 || t < best.cost) best = {sh[0], sh[1], (int)sl, kTiled, t};
             });
         }
     } else {
@@ -104,17 +112,16 @@ Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k
         // steps 1 % shorter, VGG-16 1-2 %; 128 x 128 and 64 x 128 for the same launches did worse; below 192 workgroups
         // the launch itself gets slower and the step no faster).
         const bool tall = p.tile == 64 && !rowsum && M >= 512 && (int64_t)cdiv(M, 128) * cdiv(N, 64) * p.slices >= 192;
-        best = {tall ? 128 : p.tile, p.tile, p.slices, false, 0.0};
-        best.cost = tiled_cost_bf16(M, N, K, best.bm, best.bn, by_k, best.slices);
+        best = {tall ? 128 : p.tile, p.tile, p.slices, kTiled, 0.0};
+        best.cost = tiled_cost_bf16(M, N, K, best.bm, best.bn, rowsum, by_k, best.slices);
     }
     if (by_k != kByKNo) {
-        Plan2 k{64, 64, 1, true, 0.0};
+        Plan2 k{64, 64, 1, kByK, 0.0};
         each_split([&](int64_t sl) {
-            const double t = by_k_cost(M, N, K, esize, by_k, sl);
-            if (k.cost == 0.0 || t < k.cost) {
-                k.cost = t;
-                k.slices = (int)sl;
-            }
+            const double t = by_k_cost(M, N, K, esize, rowsum, by_k, sl);
+            if (k.cost == 0.0 || t < k.cost) k = {64, 64, (int)sl, kByK, t};
+            const double ta = esize == 2 ? async_cost(M, N, K, by_k, sl) : t;
+            if (ta < k.cost) k = {128, 128, (int)sl, kAsync, ta};
         });
         if (k.cost < 0.9 * best.cost) best = k;
     }

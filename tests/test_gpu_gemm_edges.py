@@ -65,3 +65,16 @@ BY_K_CONV = [
 @pytest.mark.parametrize("micro,layers", [(330, l) for l in BY_K] + [(m, l) for l in BY_K_CONV for m in (5, 16)])
 def test_few_tiles_long_k(dtype, micro, layers):
     run_stage_case(layers, dtype, micro, 1, seed=micro)
+
+
+# Outputs of some 100 to 250 tiles of 128 x 128: the kernel with asynchronous copies whose two groups of waves take the k-tiles in
+# turn (ragged last tiles, an odd number of k-tiles, a k tail, row sums over many column tiles)
+@pytest.mark.parametrize("layers,micro,N", [
+    ([linear(776, 2312, False)], 500, 2),
+    ([linear(1160, 1544, False)], 1030, 1),
+    ([linear(64, 3080, False)], 520, 1),
+    ([conv(30, 30, 64, 264, 3, 2, 1, False)], 10, 2),
+    ([conv(15, 15, 72, 520, 3, 1, 1, False)], 24, 1),
+])
+def test_tiles_of_128(layers, micro, N):
+    run_stage_case(layers, "bf16", micro, N, seed=micro)
