@@ -173,6 +173,9 @@ template <class T, int DH> struct Attn {
     static constexpr int NF = DH / (2 * V);           // fragments of a row: 16 features each in bf16, 8 in fp32
     static constexpr int P = DH + V;                  // LDS row pitch (16 bytes over: rows of a fragment on other banks)
     static constexpr int R = BF ? 64 : 32;            // rows of an LDS tile
+    // bf16: the probabilities (and their gradients) enter the second product rounded to bf16 for 64 features per head; for 32, where
+    // the kernels by rows used to take them in fp32, as the sum of three bf16 terms, which is as exact.
+    static constexpr int TERMS = DH == 32 ? 3 : 1;
     typedef typename Frag<T>::type frag_t;
 
     // Fragment t of 32 rows (lane: row lane % 32, V features from 2 V t + V (lane / 32)): from global memory (rows
@@ -201,9 +204,16 @@ template <class T, int DH> struct Attn {
             typedef __attribute__((address_space(3))) s16x4_t* lds_ptr_t;
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                bf16x8_t pf;
+                bf16x8_t pf[TERMS];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[e] = (bf16_t)p[8 * t + e];
+                for (int e = 0; e < 8; ++e) {
+                    float rest = p[8 * t + e];
+#pragma unroll
+                    for (int k = 0; k < TERMS; ++k) {
+                        pf[k][e] = (bf16_t)rest;
+                        rest -= (float)pf[k][e];
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < FT; ++i) {
                     // two transpose reads of 4 rows each: slot (half, e) is row r0 + 16 t + 8 (e / 4) + 4 half + e % 4
@@ -213,7 +223,8 @@ template <class T, int DH> struct Attn {
                     union { s16x4_t h[2]; bf16x8_t v; } u;
                     u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p0));
                     u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p0 + 8 * P));
-                    out[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u.v, pf, out[i], 0, 0, 0);
+#pragma unroll
+                    for (int k = TERMS - 1; k >= 0; --k) out[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u.v, pf[k], out[i], 0, 0, 0);
                 }
             }
         } else {
