@@ -160,9 +160,9 @@ __global__ __launch_bounds__(256) void layernorm_pgrad_kernel(const T* __restric
 }
 
 // Input gradient AND the per-slab partial sums of the gain / shift gradients in one pass over dy and x: bf16, 8 features
-// per lane and access, D % 8 == 0 and D <= 1024 (at most two 8-feature chunks per lane).  A wave walks over 8 rows of
-// its workgroup's slab of 4 * kLnRowsPerWave rows; the four waves' partial sums are combined through LDS.
-constexpr int kLnRowsPerWave = 4;
+// per lane and access, D % 8 == 0 and D <= 1024 (at most two 8-feature chunks per lane).  A wave takes R rows of its
+// workgroup's slab of 4 R rows; the four waves' partial sums are combined through LDS.
+template <int R>
 __global__ __launch_bounds__(256) void layernorm_bwd_fused_bf16x8_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                          const float* __restrict__ stats,
                                                                          const float* __restrict__ gamma, const bf16_t* __restrict__ add,
@@ -179,9 +179,9 @@ __global__ __launch_bounds__(256) void layernorm_bwd_fused_bf16x8_kernel(const b
 #pragma unroll
         for (int e = 0; e < 8; ++e) ag[i][e] = ab[i][e] = 0.0f;
     }
-    const int64_t r0 = (int64_t)blockIdx.x * (4 * kLnRowsPerWave) + wave * kLnRowsPerWave;
+    const int64_t r0 = (int64_t)blockIdx.x * (4 * R) + wave * R;
 #pragma unroll
-    for (int rr = 0; rr < kLnRowsPerWave; ++rr) {
+    for (int rr = 0; rr < R; ++rr) {
         const int64_t row = r0 + rr;
         if (row >= rows) break;   // uniform per wave
         const float mean = stats[2 * row], rstd = stats[2 * row + 1];
@@ -278,11 +278,14 @@ __global__ __launch_bounds__(1024) void slab_sum_kernel(const float* __restrict_
     }
 }
 
+// Rows per wave of the fused backward kernel: its workgroups are to cover the device (1024 rows in slabs of 16 are 64 of them:
+// both passes of 1024 x 768 18.2 us, in slabs of 4 12.6 us), and every slab costs a row of partial sums.
+static int ln_rows_per_wave(int64_t rows) { return rows >= 4096 ? 4 : rows >= 2048 ? 2 : 1; }
 static int ln_slab_rows(int64_t rows) { return rows > 4096 ? 128 : 32; }
 
 size_t layernorm_workspace_elems(int64_t rows, int D) {
-    // the fused backward kernel works on slabs of 4 * kLnRowsPerWave rows whatever the row count
-    return (size_t)cdiv_tf(rows, 4 * kLnRowsPerWave) * 2 * (size_t)D;
+    // (the slabs of the fused backward kernel; those of the others are longer)
+    return (size_t)cdiv_tf(rows, 4 * ln_rows_per_wave(rows)) * 2 * (size_t)D;
 }
 
 hipError_t layernorm_forward(int dtype, const void* x, const float* gamma, const float* beta, void* y, float* stats,
@@ -310,12 +313,13 @@ hipError_t layernorm_backward(int dtype, const void* dy, const void* x, const fl
     if (dtype == kBF16 && D % 8 == 0 && D <= 1024 &&
         ((reinterpret_cast<uintptr_t>(dy) | reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(gamma) |
           reinterpret_cast<uintptr_t>(add) | reinterpret_cast<uintptr_t>(dx)) & 15) == 0) {
-        const int slabs32 = cdiv_tf(rows, 4 * kLnRowsPerWave);
-        e = launch_timed(kcLayerNorm, layernorm_bwd_fused_bf16x8_kernel, dim3(slabs32), dim3(256), 0, s, (const bf16_t*)dy,
-                         (const bf16_t*)x, stats, gamma, (const bf16_t*)add, (bf16_t*)dx, ws, rows, D);
+        const int per_wave = ln_rows_per_wave(rows), slabs = cdiv_tf(rows, 4 * per_wave);
+        auto kern = per_wave == 4 ? layernorm_bwd_fused_bf16x8_kernel<4> : per_wave == 2 ? layernorm_bwd_fused_bf16x8_kernel<2> : layernorm_bwd_fused_bf16x8_kernel<1>;
+        e = launch_timed(kcLayerNorm, kern, dim3(slabs), dim3(256), 0, s, (const bf16_t*)dy, (const bf16_t*)x, stats, gamma, (const bf16_t*)add,
+                         (bf16_t*)dx, ws, rows, D);
         if (e != hipSuccess) return e;
         return launch_timed(kcLayerNorm, slab_sum_kernel, dim3(cdiv_tf(2 * D, 64)), dim3(1024), 0, s, (const float*)ws,
-                            dgamma_dbeta, 2 * D, slabs32);
+                            dgamma_dbeta, 2 * D, slabs);
     }
     const int slab = ln_slab_rows(rows);
     const int slabs = cdiv_tf(rows, slab);
