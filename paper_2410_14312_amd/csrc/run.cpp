@@ -253,7 +253,14 @@ int issue_all(RunCtx& c) {
             c.for_each_dependency(n, [&](size_t e) { ready = ready && c.recorded[e].load(std::memory_order_relaxed); });
             if (ready && (!best || n.first_task < best->first_task)) best = &n;
         }
-        if (!best) return TMPS_OK;   // (all issued: a node whose predecessors are issued is always there before that)
+        if (!best) {
+            // nothing is ready: everything has been issued, or the order asks for a pass that never comes
+            for (int s = 0; s < c.K; ++s)
+                if (head[s] < c.nodes[s].size())
+                    return fail(TMPS_EINVAL, "the schedule's order cannot be satisfied: stage %d is left with %zu of %zu passes", s,
+                                c.nodes[s].size() - head[s], c.nodes[s].size());
+            return TMPS_OK;
+        }
         const int rc = issue(c, *best);
         if (rc != TMPS_OK) return rc;
         ++head[best->stage];
