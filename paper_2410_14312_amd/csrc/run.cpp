@@ -314,10 +314,6 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
     c.groups.resize(K);
     for (int s = 0; s < K; ++s) c.groups[s] = stages[s]->cfg.max_stash / N;
     const size_t n_events = c.n_fwd_ev + (size_t)K * n_minibatches;
-    for (int s = 0; s < K; ++s) {
-        int rc = grow_events(stages[s], c.total_micro + (size_t)n_minibatches);
-        if (rc != TMPS_OK) return rc;
-    }
     c.recorded = std::vector<std::atomic<unsigned char>>(n_events);
     for (auto& f : c.recorded) f.store(0, std::memory_order_relaxed);
 
@@ -330,11 +326,18 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
         for (int s = 1; s < K; ++s) {
             if (hip_streams[s] == hip_streams[0] || hipStreamQuery((hipStream_t)hip_streams[s]) == hipSuccess) continue;
             (void)hipGetLastError();   // ("not ready" is an answer, not an error)
+            const int rc = grow_events(stages[s], 1);
+            if (rc != TMPS_OK) return rc;
             TMPS_HIP(hipEventRecord(stages[s]->events[0], (hipStream_t)hip_streams[s]));
             TMPS_HIP(hipStreamWaitEvent((hipStream_t)hip_streams[0], stages[s]->events[0], 0));
         }
         c.one_queue = true;
     }
+    if (!c.one_queue)
+        for (int s = 0; s < K; ++s) {
+            const int rc = grow_events(stages[s], c.total_micro + (size_t)n_minibatches);
+            if (rc != TMPS_OK) return rc;
+        }
 
     const char* env = getenv("TMPS_ISSUE_THREADS");
     const bool threaded = K > 1 && !(env && env[0] == '0') && !c.one_queue;

@@ -8,3 +8,7 @@ RUNNER = ["tests/host/kernel_stubs.cpp", "tests/host/runtime_stubs.cpp", "paper_
 
 def test_an_order_that_cannot_be_satisfied_is_an_error(tmp_path_factory):
     run_clean(build(tmp_path_factory, "unsatisfiable_order", ["tests/host/unsatisfiable_order.cpp"] + RUNNER))
+
+
+def test_runner_is_clean_under_sanitizers(tmp_path_factory):
+    run_clean(build(tmp_path_factory, "sanitize_run", ["tests/host/sanitize_run.cpp", "paper_2410_14312_amd/csrc/schedule.cpp"] + RUNNER))
