@@ -281,10 +281,18 @@ int tmps_version_diff_simulated(int W, int N);
  * run started, so that a second run, or a run resumed from a checkpoint, logs the same numbers as the plan); may be NULL.
  * If a task fails, the call still waits for the streams, frees the stash slots of every stage (the mini-batches in
  * flight are lost; updates already applied stay) and returns the first error.
- * Cross-stage dependencies are HIP events.  Each stage's tasks are issued by a host thread of its
- * own (one per stage, joined before the call returns; set the environment variable
- * TMPS_ISSUE_THREADS=0 to issue everything from the calling thread).  The call returns after all K
- * streams are idle. */
+ * Consecutive forward tasks of one stage and mini-batch that read the same weights are issued as one pass over their
+ * rows (the log lists them one by one as planned).  The run takes one of two forms, with the same results bit for bit:
+ *   K streams  every stage's tasks are issued on its stream by a host thread of its own (joined before the call
+ *              returns); cross-stage dependencies are HIP events.
+ *   one stream everything is issued by the calling thread on hip_streams[0], whose order stands for the events; work
+ *              that the caller has pending on the other streams comes first.  Chosen where an estimate of the run's
+ *              device time says that overlap would gain less than hand-overs between streams and threads cost (short
+ *              runs), and where all K streams are the same.
+ * The environment variable TMPS_ISSUE_THREADS, read by every call, overrides the choice: 1 asks for K streams and a thread
+ * per stage whatever the estimate says (streams that are all the same stay one stream), 0 issues from the calling thread
+ * in either form.  The call returns after all
+ * streams it used are idle. */
 int tmps_schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, const void* inputs,
                       const int32_t* labels, void** hip_streams, float* losses_out,
                       int32_t* version_log_out);

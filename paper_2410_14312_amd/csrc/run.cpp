@@ -321,7 +321,9 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
     build_nodes(c, tasks);
     c.one_queue = true;
     for (int s = 1; s < K; ++s) c.one_queue = c.one_queue && hip_streams[s] == hip_streams[0];
-    if (!c.one_queue && serial_is_quicker(c)) {
+    const char* env = getenv("TMPS_ISSUE_THREADS");   // (0: issue from the calling thread; 1: K streams, a thread for each)
+    const bool ask_streams = env && env[0] == '1';
+    if (!c.one_queue && !ask_streams && serial_is_quicker(c)) {
         // (what the caller has pending on the other streams comes first)
         for (int s = 1; s < K; ++s) {
             if (hip_streams[s] == hip_streams[0] || hipStreamQuery((hipStream_t)hip_streams[s]) == hipSuccess) continue;
@@ -339,7 +341,6 @@ static int schedule_run(tmps_stage** stages, int K, int N, int n_minibatches, co
             if (rc != TMPS_OK) return rc;
         }
 
-    const char* env = getenv("TMPS_ISSUE_THREADS");
     const bool threaded = K > 1 && !(env && env[0] == '0') && !c.one_queue;
     const bool report = getenv("TMPS_REPORT_ISSUE_TIME") != nullptr;
     const auto t0 = std::chrono::steady_clock::now();

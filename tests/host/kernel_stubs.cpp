@@ -2,15 +2,23 @@
 // the stage executor: nothing is launched, every launcher reports success, and the workspace sizes are small fixed
 // functions of the shape.  Only the host logic of csrc/stage.cpp (layout, argument checks, slot and buffer
 // bookkeeping) is exercised by such a build.
+#include "kernel_stubs.h"
+
 #include <string.h>
 
 #include "../../paper_2410_14312_amd/csrc/kernels.h"
+
+KernelStubs kernel_stubs;
 
 namespace tmps {
 hipError_t dense_forward(int dtype, const void* x, const void* w, const float* bias, void* y, int B, int Din, int Dout, int act, int out_f32, const void* res, void* zout, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, int mask_mode, const void* add, int B, int Din, int Dout, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) { return hipSuccess; }
-hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y, const ConvShape& c, int relu, float* ws, hipStream_t s) { return hipSuccess; }
+hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y, const ConvShape& c, int relu, float* ws, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(kernel_stubs.m);
+    kernel_stubs.conv_samples.push_back(c.B);
+    return hipSuccess;
+}
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain, const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
@@ -27,7 +35,9 @@ hipError_t attention_forward(int dtype, const void* qkv, void* o, float* lse, in
 hipError_t attention_backward(int dtype, const void* qkv, const void* o, const void* dout, const float* lse, float* delta, void* dqkv, int B, int S, int D, int H, hipStream_t s) { return hipSuccess; }
 hipError_t embedding_forward(int dtype, const int32_t* tok, const void* wte, const void* wpe, void* y, int64_t rows, int S, int D, int vocab, hipStream_t s) { return hipSuccess; }
 hipError_t embedding_backward(int dtype, const int32_t* tok, const void* dy, float* dwte, float* dwpe, int64_t B, int S, int D, int vocab, hipStream_t s) { return hipSuccess; }
-hipError_t softmax_ce(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* row_loss, int rows, int C, float inv_M, hipStream_t s) { return hipSuccess; }
+hipError_t softmax_ce(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* row_loss, int rows, int C, float inv_M, hipStream_t s) {
+    return kernel_stubs.losses_until_failure-- == 0 ? hipErrorLaunchFailure : hipSuccess;
+}
 hipError_t reduce_scaled_sum(const float* in, int n, float scale, float* out, hipStream_t s) { return hipSuccess; }
 hipError_t relu_mask(int dtype, const void* dy, const void* y, void* dz, int64_t n, hipStream_t s) { return hipSuccess; }
 hipError_t sgd_momentum(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu, hipStream_t s) { return hipSuccess; }

@@ -19,11 +19,11 @@ from oracle import schedule as S
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def build(tmp_path_factory, name, sources):
+def build(tmp_path_factory, name, sources, sanitizers="address,undefined"):
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     exe = str(tmp_path_factory.mktemp("san") / name)
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=" + sanitizers, "-fno-sanitize-recover=all",
            "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-pthread"] + [os.path.join(ROOT, s) for s in sources] + ["-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
