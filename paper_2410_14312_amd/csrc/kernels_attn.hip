@@ -319,6 +319,94 @@ __device__ __forceinline__ void softmax_block(f32x16_t& st, int kb, int q, int h
         for (int r = 0; r < 16; ++r) ot[i][r] *= alpha;
 }
 
+// ---- results that are not finite ----
+// The kernels below multiply whole 32 x 32 blocks: on the diagonal, and past the end of the sequence, a probability of zero
+// meets rows that the query (or key) does not see, and an infinity or a NaN there (0 * inf) would reach results that do not
+// depend on it; where probabilities are a sum of bf16 terms, a term of zero does the same to a row that is seen.  Rows of the
+// result that are not finite although their statistics are (not_finite_rows) are therefore formed again, by rows
+// and over the visible pairs alone, with the probabilities in fp32.  Finite data pay one three-operand maximum (the kind that
+// keeps a NaN) for two result registers.
+template <int FT> __device__ __forceinline__ uint32_t not_finite_rows(const f32x16_t (&v)[FT], bool statistics_ok) {
+    float z[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < FT; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)
+            z[(r >> 1) & 1] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(z[(r >> 1) & 1], __builtin_fabsf(v[i][r])), __builtin_fabsf(v[i][r + 1]));
+    const uint64_t lanes = __ballot(!(__builtin_elementwise_maximum(z[0], z[1]) < INFINITY) && statistics_ok);
+    return (uint32_t)(lanes | (lanes >> 32));   // (a lane pair holds a row)
+}
+
+template <class T, int DH> __device__ __forceinline__ float row_dot(const T* a, const T* b) {
+    typedef Attn<T, DH> X;
+    float s = 0.0f;
+#pragma unroll 1
+    for (int c = 0; c < DH; c += X::V) {
+        const typename X::frag_t x = *reinterpret_cast<const typename X::frag_t*>(a + c), y = *reinterpret_cast<const typename X::frag_t*>(b + c);
+#pragma unroll
+        for (int e = 0; e < X::V; ++e) s = fmaf((float)x[e], (float)y[e], s);
+    }
+    return s;
+}
+
+// One query's output by a whole wave: a lane to each key of 64, then a lane to each feature.  m (in units of log 2) and l: the
+// query's maximum and sum.
+template <class T, int DH>
+__device__ __forceinline__ void output_row(const T* base, int64_t ld, int D, int q, float scale2, float m, float l, T* out, int lane) {
+    const int f = lane % DH;
+    float a = 0.0f;
+#pragma unroll 1
+    for (int j0 = 0; j0 <= q; j0 += 64) {
+        const int n = min(64, q + 1 - j0);
+        const float p = exp2_hw(fmaf(row_dot<T, DH>(base + q * ld, base + D + (j0 + min(lane, n - 1)) * ld), scale2, -m));
+#pragma unroll 1
+        for (int t = 0; t < n; ++t) a = fmaf(__shfl(p, t, 64), (float)base[2 * D + (j0 + t) * ld + f], a);
+    }
+    if (lane < DH) out[f] = (T)(a / l);
+}
+
+// One query's gradient.  dout: the output gradient's rows of this (batch, head), D elements apart; L2: log-sum-exp in units of log 2.
+template <class T, int DH>
+__device__ __forceinline__ void query_gradient_row(const T* base, const T* dout, int64_t ld, int D, int q, float scale, float L2, float dl, T* dq, int lane) {
+    const int f = lane % DH;
+    const float scale2 = scale * kLog2e;
+    float a = 0.0f;
+#pragma unroll 1
+    for (int j0 = 0; j0 <= q; j0 += 64) {
+        const int n = min(64, q + 1 - j0);
+        const T* kj = base + D + (j0 + min(lane, n - 1)) * ld;
+        const float p = exp2_hw(fmaf(row_dot<T, DH>(base + q * ld, kj), scale2, -L2));
+        const float ds = p * (row_dot<T, DH>(dout + (int64_t)q * D, kj + D) - dl);
+#pragma unroll 1
+        for (int t = 0; t < n; ++t) a = fmaf(__shfl(ds, t, 64), (float)base[D + (j0 + t) * ld + f], a);
+    }
+    if (lane < DH) dq[f] = (T)(a * scale);
+}
+
+// One key's and value's gradients, over the queries from that position on.  lse, delta: the statistics of this (batch, head).
+template <class T, int DH>
+__device__ __forceinline__ void key_value_gradient_row(const T* base, const T* dout, int64_t ld, int D, int S, int key, float scale, const float* lse,
+                                                       const float* delta, T* dk_row, T* dv_row, int lane) {
+    const int f = lane % DH;
+    const float scale2 = scale * kLog2e;
+    float dk = 0.0f, dv = 0.0f;
+#pragma unroll 1
+    for (int i0 = key; i0 < S; i0 += 64) {
+        const int n = min(64, S - i0), i = i0 + min(lane, n - 1);
+        const float p = exp2_hw(fmaf(row_dot<T, DH>(base + D + key * ld, base + i * ld), scale2, -lse[i] * kLog2e));
+        const float ds = p * (row_dot<T, DH>(base + 2 * D + key * ld, dout + (int64_t)i * D) - delta[i]);
+#pragma unroll 1
+        for (int t = 0; t < n; ++t) {
+            dk = fmaf(__shfl(ds, t, 64), (float)base[(i0 + t) * ld + f], dk);
+            dv = fmaf(__shfl(p, t, 64), (float)dout[(int64_t)(i0 + t) * D + f], dv);
+        }
+    }
+    if (lane < DH) {
+        dk_row[f] = (T)(dk * scale);
+        dv_row[f] = (T)dv;
+    }
+}
+
 // Workgroups go to the 8 XCDs (each with its own L2) round-robin in launch order (x fastest, then y, then z).  Hand
 // every XCD a contiguous run of that order instead: the query (or key) blocks of one (batch, head) then sit on one XCD,
 // and the keys and values (queries and output gradients) they all read come in from memory once, not once per XCD.
@@ -389,9 +477,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma_kernel(const T* __re
         __syncthreads();
     }
     const float l = l_run + __shfl_xor(l_run, 32, 64);
+    const uint32_t redo = not_finite_rows(ot, l > 0.0f);
     if (q < S) {
-        X::store_row(o + ((int64_t)b * S + q) * D + h * DH, ot, 1.0f / l, half);
-        if (half == 0) lse[((int64_t)b * H + h) * S + q] = m_run * kLn2 + logf(l);
+        if (!((redo >> (lane & 31)) & 1)) X::store_row(o + ((int64_t)b * S + q) * D + h * DH, ot, 1.0f / l, half);
+        if (half == 0) lse[((int64_t)b * H + h) * S + q] = fmaf(m_run, kLn2, logf(l));
+    }
+    for (uint32_t todo = redo; todo; todo &= todo - 1) {
+        const int r = __builtin_ctz(todo);
+        if (q0 + r < S) output_row<T, DH>(base, ld, D, q0 + r, scale2, __shfl(m_run, r, 64), __shfl(l, r, 64), o + ((int64_t)b * S + q0 + r) * D + h * DH, lane);
     }
 }
 
@@ -402,7 +495,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma_kernel(const T* __re
 // Nothing is shared between the waves inside the loop, so there is no workgroup barrier in it: K fragments come
 // straight from global memory, V passes through a wave-private LDS tile.
 template <class T, int DH, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_fwd_split_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int S,
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 2 ? 3 : 1) void attn_fwd_split_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int S,
                                                                  int D, int H, float scale) {
     typedef Attn<T, DH> X;
     constexpr int FT = X::FT, C = DH / X::V, NV = 32 * C / 64;   // 16-byte chunks of a row, chunks per lane of 32 rows
@@ -493,9 +586,14 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_split_kernel(const T* __rest
 #pragma unroll
             for (int r = 0; r < 16; ++r) ot[i][r] += fw * sOw[w][16 * i + r][lane];
     }
+    const uint32_t redo = not_finite_rows(ot, l > 0.0f);
     if (q < S) {
-        X::store_row(o + ((int64_t)b * S + q) * D + h * DH, ot, 1.0f / l, half);
-        if (half == 0) lse[((int64_t)b * H + h) * S + q] = m * kLn2 + logf(l);
+        if (!((redo >> (lane & 31)) & 1)) X::store_row(o + ((int64_t)b * S + q) * D + h * DH, ot, 1.0f / l, half);
+        if (half == 0) lse[((int64_t)b * H + h) * S + q] = fmaf(m, kLn2, logf(l));
+    }
+    for (uint32_t todo = redo; todo; todo &= todo - 1) {
+        const int r = __builtin_ctz(todo);
+        if (q0 + r < S) output_row<T, DH>(base, ld, D, q0 + r, scale2, __shfl(m, r, 64), __shfl(l, r, 64), o + ((int64_t)b * S + q0 + r) * D + h * DH, lane);
     }
 }
 
@@ -579,7 +677,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_q_mfma_kernel(const T* __
         fv.put(sVb[(it + 1) & 1], tid);
         __syncthreads();
     }
-    if (q < S) X::store_row(dqkv + ((int64_t)b * S + q) * ld + h * DH, dq, scale, half);
+    // (a log-sum-exp that is not finite, or a delta that is NaN, stands in every term of the row)
+    const uint32_t redo = not_finite_rows(dq, fabsf(L2) < INFINITY && dl == dl);
+    if (q < S && !((redo >> (lane & 31)) & 1)) X::store_row(dqkv + ((int64_t)b * S + q) * ld + h * DH, dq, scale, half);
+    for (uint32_t todo = redo; todo; todo &= todo - 1) {
+        const int r = __builtin_ctz(todo);
+        if (q0 + r < S)
+            query_gradient_row<T, DH>(base, dob, ld, D, q0 + r, scale, __shfl(L2, r, 64), __shfl(dl, r, 64),
+                                      dqkv + ((int64_t)b * S + q0 + r) * ld + h * DH, lane);
+    }
 }
 
 // Key and value gradients.  A wave owns 32 keys (lanes); queries run along the accumulator registers, so the
@@ -681,10 +787,25 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 1 : 2) void attn_bwd_kv_m
         put_stats((it + 1) & 1);
         __syncthreads();
     }
-    if (key < S) {
+    const float* const lse_bh = lse + ((int64_t)b * H + h) * S;
+    const float* const delta_bh = delta + ((int64_t)b * H + h) * S;
+    const uint32_t dk_rows = not_finite_rows(dk, true), dv_rows = not_finite_rows(dv, true);
+    uint32_t redo = dk_rows | dv_rows;
+    if (redo) {
+        // every key sees the last query: a NaN in that one's log-sum-exp stands in every row of both gradients, one in its delta
+        // in every row of the key gradient
+        const bool lse_ok = lse_bh[S - 1] == lse_bh[S - 1], delta_ok = delta_bh[S - 1] == delta_bh[S - 1];
+        redo = (lse_ok && delta_ok ? dk_rows : 0) | (lse_ok ? dv_rows : 0);
+    }
+    if (key < S && !((redo >> (lane & 31)) & 1)) {
         T* drow = dqkv + ((int64_t)b * S + key) * ld + h * DH;
         X::store_row(drow + D, dk, scale, half);
         X::store_row(drow + 2 * D, dv, 1.0f, half);
+    }
+    for (uint32_t todo = redo; todo; todo &= todo - 1) {
+        const int r = __builtin_ctz(todo);
+        T* drow = dqkv + ((int64_t)b * S + k0 + r) * ld + h * DH;
+        if (k0 + r < S) key_value_gradient_row<T, DH>(base, dob, ld, D, S, k0 + r, scale, lse_bh, delta_bh, drow + D, drow + 2 * D, lane);
     }
 }
 
