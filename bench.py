@@ -3,8 +3,9 @@
 
 A step is one mini-batch through the whole path: on each of the K stages the N micro-batch forward
 passes, the single backward pass with the latest weights and the in-place momentum update, issued
-in nF1B order on K HIP streams by tmps_schedule_run.  Inputs are synthetic (seeded Gaussian inputs,
-uniform labels, He-normal weights) and resident in HBM before the timed region.
+in nF1B order by tmps_schedule_run, on K HIP streams or on one where that is quicker.  Inputs are
+synthetic (seeded Gaussian inputs, uniform labels, He-normal weights) and resident in HBM before the
+timed region.
 
 Prints ONE JSON line: whole-job samples/s, the roofline of the dominant kernel class (measured
 with HIP events on the kernels' own streams in a second pass of the same workload), samples/s of
@@ -24,15 +25,19 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 
 
-def algorithmic_work(cfg, only_stage=None):
+def algorithmic_work(cfg, only_stage=None, passes=None):
     """Per kernel class and per mini-batch: (launches, FLOPs, algorithmic bytes) from the shapes alone
     (of every stage, or of stage `only_stage` alone).
+
+    passes: forward passes that a mini-batch is made in, on average over the layers.  A pass over one micro-batch each
+    (the default, N passes) and a pass over several make the same FLOPs and move the same rows; each pass launches a layer's
+    kernel once and reads its weights once.
 
     Dense GEMMs count 2*rows*Din*Dout FLOPs and their operand/result bytes once; the update counts
     22 bytes per parameter in bf16 stages (read w, buf, g fp32; write w, buf fp32 and the bf16 copy)
     or 20 in fp32 stages."""
     asz = 2 if cfg.dtype == "bf16" else 4
-    M, N, mb = cfg.M, cfg.N, cfg.micro
+    M, F = cfg.M, cfg.N if passes is None else passes
     work = {}
 
     def add(k, launches, flops, nbytes):
@@ -49,11 +54,10 @@ def algorithmic_work(cfg, only_stage=None):
             if sp["kind"] == "linear":
                 din, dout, rows = sp["din"], sp["dout"], sp.get("rows", 1)
                 P += din * dout + dout
-                rf, rb = mb * rows, M * rows        # GEMM rows of a forward pass and of the backward pass
+                rb = M * rows                       # GEMM rows of a mini-batch
                 osz = 4 if (li + 1 < len(st) and st[li + 1]["kind"] == "softmax_ce") else asz
                 extra = (1 if sp.get("skip") else 0) + (1 if sp.get("act") == "gelu" else 0)   # residual read, z write
-                add("dense_fwd", N, N * 2.0 * rf * din * dout,
-                    N * (rf * din * asz + din * dout * asz + rf * dout * (osz + extra * asz)))
+                add("dense_fwd", F, 2.0 * rb * din * dout, F * din * dout * asz + rb * (din * asz + dout * (osz + extra * asz)))
                 add("dense_wgrad", 1, 2.0 * rb * din * dout, rb * (din + dout) * asz + (din * dout + dout) * 4)
                 if not (si == 0 and li == 0):
                     add("dense_dgrad", 1, 2.0 * rb * din * dout, rb * (din + dout) * asz + din * dout * asz)
@@ -61,25 +65,25 @@ def algorithmic_work(cfg, only_stage=None):
                 d, rows = sp["d"], sp["rows"]
                 P += 2 * d
                 # forward: read x, write y (+ statistics); backward: read dy, x (+ joined residual gradient), write dx
-                add("layernorm", N + 3, 0.0, N * mb * rows * (2 * d * asz + 8) + M * rows * (4 * d * asz + 8) + M * rows * 2 * d * asz)
+                add("layernorm", F + 3, 0.0, M * rows * (2 * d * asz + 8) + M * rows * (4 * d * asz + 8) + M * rows * 2 * d * asz)
             elif sp["kind"] == "attention":
                 s_, d, h = sp["s"], sp["d"], sp["heads"]
                 dh = d // h
                 pairs = s_ * (s_ + 1) // 2          # causal: query i sees keys 0..i
                 # forward: QK^T and PV; backward: QK^T, dO V^T, dV, dQ, dK: 2 and 5 products of 2*dh FLOPs per (query, key)
-                add("attn_fwd", N, N * mb * h * pairs * 2.0 * dh * 2, N * mb * s_ * (4 * d * asz + h * 4))
-                add("attn_bwd", 3, M * h * pairs * 2.0 * dh * 5, M * s_ * (8 * d * asz + 3 * h * 4))
+                add("attn_fwd", F, M * h * pairs * 2.0 * dh * 2, M * s_ * (4 * d * asz + h * 4))
+                add("attn_bwd", 2, M * h * pairs * 2.0 * dh * 5, M * s_ * (8 * d * asz + 3 * h * 4))
             elif sp["kind"] == "embedding":
                 v, s_, d = sp["vocab"], sp["s"], sp["d"]
                 P += v * d + s_ * d
-                add("embedding", N + 3, 0.0, N * mb * s_ * (4 + 2 * d * asz) + v * d * 4 + M * s_ * (d * asz + 4 + 8 * d) + s_ * d * 4)
+                add("embedding", F + 3, 0.0, M * s_ * (4 + 2 * d * asz) + v * d * 4 + M * s_ * (d * asz + 4 + 8 * d) + s_ * d * 4)
             elif sp["kind"] == "conv":
                 ho = (sp["h"] + 2 * sp["pad"] - sp["r"]) // sp["stride"] + 1
                 wo = (sp["w"] + 2 * sp["pad"] - sp["s"]) // sp["stride"] + 1
                 kk = sp["r"] * sp["s"] * sp["cin"]
                 P += kk * sp["cout"] + sp["cout"]
                 x_e, y_e = sp["h"] * sp["w"] * sp["cin"], ho * wo * sp["cout"]
-                add("conv_fwd", N, N * 2.0 * mb * ho * wo * kk * sp["cout"], N * (mb * (x_e + y_e) * asz + kk * sp["cout"] * asz))
+                add("conv_fwd", F, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + F * kk * sp["cout"] * asz)
                 add("conv_wgrad", 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * 4)
                 if not (si == 0 and li == 0):
                     add("conv_dgrad", 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * asz)
@@ -91,20 +95,20 @@ def algorithmic_work(cfg, only_stage=None):
                 add("affine", 2, 0.0, M * 3 * e * asz)
             elif sp["kind"] == "resadd":
                 e = sp["h"] * sp["w"] * sp["c"]
-                add("resadd", N, 0.0, N * mb * 3 * e * asz)
+                add("resadd", F, 0.0, M * 3 * e * asz)
             elif sp["kind"] == "avgpool":
                 e = sp["h"] * sp["w"] * sp["c"]
-                add("pool_fwd", N, 0.0, N * mb * (e + sp["c"]) * asz)
+                add("pool_fwd", F, 0.0, M * (e + sp["c"]) * asz)
                 add("pool_bwd", 1, 0.0, M * (2 * e + sp["c"]) * asz)
             elif sp["kind"] == "maxpool":
                 pad = sp.get("pad", 0)
                 ho, wo = (sp["h"] + 2 * pad - sp["k"]) // sp["stride"] + 1, (sp["w"] + 2 * pad - sp["k"]) // sp["stride"] + 1
                 x_e, y_e = sp["h"] * sp["w"] * sp["c"], ho * wo * sp["c"]
-                add("pool_fwd", N, 0.0, N * mb * (x_e + y_e) * asz)
+                add("pool_fwd", F, 0.0, M * (x_e + y_e) * asz)
                 add("pool_bwd", 1, 0.0, M * (2 * x_e + y_e) * asz)
             elif sp["kind"] == "softmax_ce":
                 c, rows = sp["classes"], sp.get("rows", 1)
-                add("softmax_ce", N, 0.0, N * mb * rows * (c * 4 + c * asz + 8))
+                add("softmax_ce", F, 0.0, M * rows * (c * 4 + c * asz + 8))
         add("update", 1, 0.0, P * (22 if cfg.dtype == "bf16" else 20))
     return work
 
@@ -112,6 +116,21 @@ def algorithmic_work(cfg, only_stage=None):
 # classes whose kernels carry their own start/stop timestamps (no bracket overhead)
 KERNEL_STAMPED = ("dense_fwd", "dense_dgrad", "dense_wgrad", "conv_fwd", "conv_dgrad", "conv_wgrad", "splitk_finish",
                   "slice_sum", "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd")
+
+
+def class_entry(cfg, klass, ms, launches):
+    """What a kernel class takes and does per mini-batch, from its measured time (ms) and number of launches.  The work of a
+    class comes from the shapes and not from the launches: consecutive micro-batches may be forwarded in one pass."""
+    ent = {"class": klass, "launches_per_step": launches, "avg_us": 1e3 * ms / launches, "ms_per_step": ms}
+    per = algorithmic_work(cfg).get(klass)
+    if per and per[0]:
+        if klass in ("dense_fwd", "conv_fwd"):   # launches of a layer = passes; each reads the layer's weights
+            per = algorithmic_work(cfg, passes=cfg.N * launches / per[0])[klass]
+        ent["gflop_per_launch"] = per[1] / launches / 1e9
+        ent["mbytes_per_launch"] = per[2] / launches / 1e6
+        ent["tflops"] = per[1] / (ms / 1e3) / 1e12
+        ent["gbs"] = per[2] / (ms / 1e3) / 1e9
+    return ent
 
 
 def measured_traffic(workload, kernel_class):
@@ -332,16 +351,9 @@ def main():
         for k, (ms, cnt) in prof.items():
             if cnt == 0:
                 continue
-            per = work.get(k)
             if k not in KERNEL_STAMPED:      # bracketed classes also contain the cost of the event pair
                 ms = max(ms - cnt * pair_us / 1e3, 0.05 * ms)
-            ent = {"class": k, "launches_per_step": cnt / args.steps, "avg_us": 1e3 * ms / cnt, "ms_per_step": ms / args.steps}
-            if per and per[0]:
-                ent["gflop_per_launch"] = per[1] / per[0] / 1e9
-                ent["mbytes_per_launch"] = per[2] / per[0] / 1e6
-                sec = ms / cnt / 1e3
-                ent["tflops"] = per[1] / per[0] / sec / 1e12
-                ent["gbs"] = per[2] / per[0] / sec / 1e9
+            ent = class_entry(cfg, k, ms / args.steps, cnt / args.steps)
             out.append(ent)
         out.sort(key=lambda e: -e["ms_per_step"])
         return out, pair_us
@@ -480,7 +492,7 @@ def main():
         "ms_per_step": 1e3 * dt / args.steps, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16" if cfg.dtype == "bf16" else "f32", "data": "synthetic",
         "config": {"workload": cfg.name, "mini_batch": cfg.M, "micro_batches": cfg.N, "stages": cfg.K,
-                   "measured": "K stages in nF1B order on K streams of one GPU (every stage processes every sample)",
+                   "measured": "K stages in nF1B order on one GPU, given K streams (short runs are issued on one of them; every stage processes every sample)",
                    "version_difference": T.version_diff_simulated(cfg.K, cfg.N),
                    "weight_policy": "vertical weight stashing" if args.vertical_sync else "in place",
                    "shadow_weight_bytes": shadow_bytes,

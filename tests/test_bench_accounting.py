@@ -95,3 +95,27 @@ def test_training_flops_are_three_forward_passes_minus_the_first_input_gradient(
     else:
         assert dgrad < fwd                              # the first layer has no input gradient
         assert dgrad > 0.9 * fwd or name == "mlp4x1024_bf16"   # (the MLP's first layer is half of its work)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_rates_do_not_depend_on_how_micro_batches_are_grouped(name):
+    """A forward pass over several micro-batches is one launch per layer: the same FLOPs in the same time are the same rate,
+    and only the weights are read less often."""
+    cfg = get_config(name)
+    for klass, (launches, flops, nbytes) in bench.algorithmic_work(cfg).items():
+        apart = bench.class_entry(cfg, klass, 2.0, launches)
+        assert apart["gbs"] == pytest.approx(nbytes / 2e-3 / 1e9, rel=1e-12)
+        for merged in (launches / 2, launches / 1.5, launches / cfg.N):
+            e = bench.class_entry(cfg, klass, 2.0, merged)
+            assert e["tflops"] == pytest.approx(flops / 2e-3 / 1e12, rel=1e-12)
+            assert e["gflop_per_launch"] * merged == pytest.approx(flops / 1e9, rel=1e-12)
+            assert e["gbs"] <= apart["gbs"] * (1 + 1e-12)
+            if klass not in ("dense_fwd", "conv_fwd"):
+                assert e["gbs"] == pytest.approx(apart["gbs"], rel=1e-12)
+
+
+def test_weights_are_read_once_by_every_pass():
+    cfg = get_config("tiny_mlp_f32")
+    weights = (64 * 128 + 128 * 128 + 128 * 10) * 4
+    by_pass = [bench.algorithmic_work(cfg, passes=p)["dense_fwd"][2] for p in (1, 2, 4)]
+    assert by_pass[1] - by_pass[0] == weights and by_pass[2] - by_pass[0] == 3 * weights
