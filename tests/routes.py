@@ -1,0 +1,67 @@
+"""Which kernel a contraction of a layer runs on, asked of the library's own planning functions (host code, no GPU): tests that
+name a kernel check with it that their cases still reach that kernel when the rules change."""
+import ctypes as C
+
+from paper_2410_14312_amd import load_library
+
+
+class _Plan(C.Structure):
+    _fields_ = [("bm", C.c_int), ("bn", C.c_int), ("slices", C.c_int), ("kind", C.c_int), ("cost", C.c_double)]
+
+
+class _Conv(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("B", "H", "W", "Cin", "Ho", "Wo", "Cout", "R", "S", "stride", "pad")]
+
+
+def _functions():
+    lib = load_library()
+    plan, small, rows, wg3 = (getattr(lib, n) for n in ("_ZN4tmps8plan_forElllbii", "_ZN4tmps15small_is_betterEllliRKNS_5Plan2E",
+                                                        "_ZN4tmps17conv_rows_variantERKNS_9ConvShapeEliid", "_ZN4tmps15g3_wgrad_slicesElll"))
+    plan.restype, plan.argtypes = _Plan, [C.c_long, C.c_long, C.c_long, C.c_bool, C.c_int, C.c_int]
+    small.restype, small.argtypes = C.c_bool, [C.c_long, C.c_long, C.c_long, C.c_int, C.POINTER(_Plan)]
+    rows.restype, rows.argtypes = C.c_int, [C.POINTER(_Conv), C.c_long, C.c_int, C.c_int, C.c_double]
+    wg3.restype, wg3.argtypes = C.c_int, [C.c_long, C.c_long, C.c_long]
+    return plan, small, rows, wg3
+
+
+KINDS = ("tiled", "by_k", "async")
+DENSE, CONV = 1, 2   # operands that a kernel with asynchronous copies can address: matrices, a convolution's
+
+
+def _route(M, N, K, wgrad, esize, operands):
+    plan, small, _, wg3 = _functions()
+    p = plan(M, N, K, wgrad, esize, operands)
+    if operands == DENSE and esize == 2:
+        # (the persistent kernel comes first: outputs of 128 tiles of 256 x 128 or more, very long contractions, large weight gradients)
+        units = -(-M // 256) * -(-N // 128)
+        if (wg3(M, N, K) > 0) if wgrad else (units >= 128 or K >= 8192):
+            return "persistent?"
+    if operands == DENSE and small(M, N, K, esize, C.byref(p)):
+        return "small"
+    if p.kind == 2 and N % 8:
+        return "tiled"
+    return KINDS[p.kind] + (" split" if p.slices > 1 else "")
+
+
+def dense_routes(sp, dtype, micro, N):
+    """(forward, input gradient, weight gradient) of a linear layer whose widths are whole 16-byte chunks."""
+    e, rows = 2 if dtype == "bf16" else 4, sp.get("rows", 1)
+    din, dout, mb, M = sp["din"], sp["dout"], micro * rows, micro * N * rows
+    assert din % (16 // e) == 0 and dout % (16 // e) == 0
+    return _route(mb, dout, din, False, e, DENSE), _route(M, din, dout, False, e, DENSE), _route(dout, din, M, True, e, DENSE)
+
+
+def conv_routes(sp, dtype, micro, N):
+    """The same of a convolution with more than one tap (in the natural row order); "rows 443" and the like are the variants
+    of the kernel that keeps runs of input rows in LDS."""
+    plan, _, rows, _ = _functions()
+    e = 2 if dtype == "bf16" else 4
+    ho, wo = ((sp[k] + 2 * sp["pad"] - sp[f]) // sp["stride"] + 1 for k, f in (("h", "r"), ("w", "s")))
+    taps, cin, cout = sp["r"] * sp["s"], sp["cin"], sp["cout"]
+    assert taps > 1 and cin % 8 == 0 and cout % 8 == 0
+    out = []
+    for B, m, n, c in ((micro, micro * ho * wo, cout, cin), (micro * N, micro * N * sp["h"] * sp["w"], cin, cout)):
+        shape = _Conv(B, sp["h"], sp["w"], cin, ho, wo, cout, sp["r"], sp["s"], sp["stride"], sp["pad"])
+        v = rows(C.byref(shape), m, n, c, plan(m, n, taps * c, False, 2, CONV).cost / 2400.0) if dtype == "bf16" else 0
+        out.append("rows %d" % v if v else _route(m, n, taps * c, False, e, CONV))
+    return out[0], out[1], _route(cout, taps * cin, micro * N * ho * wo, True, e, CONV)

@@ -47,8 +47,8 @@ def test_conv_edges(dtype, h, w, cin, cout, r, stride, pad, micro, N):
     run_stage_case([conv(h, w, cin, cout, r, stride, pad, False)], dtype, micro, N, seed=h + cin * cout)
 
 
-# Outputs of few 64 x 64 tiles over a long k: the kernel whose waves share k (whole and partial k-tiles, fewer k-tiles
-# than waves' stages, ragged last tiles, a convolution's loaders in all passes)
+# Outputs of few 64 x 64 tiles over a long k (whole and partial k-tiles, ragged last tiles, a convolution's loaders in all
+# passes).  tests/test_gpu_contraction_routes.py holds the kernel whose waves share k to sizes that are known to reach it.
 BY_K = [
     [linear(1544, 584, False)],           # a tail of 8 in the forward pass, whole tiles in the weight gradient
     [linear(776, 1160, False)],
@@ -67,8 +67,8 @@ def test_few_tiles_long_k(dtype, micro, layers):
     run_stage_case(layers, dtype, micro, 1, seed=micro)
 
 
-# Outputs of some 100 to 250 tiles of 128 x 128: the kernel with asynchronous copies whose two groups of waves take the k-tiles in
-# turn (ragged last tiles, an odd number of k-tiles, a k tail, row sums over many column tiles)
+# Outputs of some 100 to 250 tiles of 128 x 128 (ragged last tiles, an odd number of k-tiles, a k tail, row sums over many
+# column tiles).  tests/test_gpu_contraction_routes.py holds the kernel with asynchronous copies to sizes that reach it.
 @pytest.mark.parametrize("layers,micro,N", [
     ([linear(776, 2312, False)], 500, 2),
     ([linear(1160, 1544, False)], 1030, 1),
