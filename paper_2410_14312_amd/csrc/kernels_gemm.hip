@@ -233,19 +233,20 @@ int g3_wgrad_slices(int64_t M, int64_t N, int64_t K) {
 // Not for a contraction of a single k-tile, which is all epilogue (many small workgroups keep more memory requests in
 // flight than one persistent workgroup per compute unit), nor when more than a quarter of the 256-wide tiles would be
 // padding (measured on the 1x1 convolutions of the residual networks).
-static bool g3_forward_ok(int64_t M, int64_t N, int64_t K) {
+bool g3_forward_ok(int64_t M, int64_t N, int64_t K) {
     return K % 64 == 0 && K >= 128 && N % 8 == 0 && g3_tiles(M, N) >= 192 && (int64_t)cdiv(N, 256) * 256 * 3 <= N * 4;
 }
 
 // A tall, narrow output (the 8192 x 768 input gradients of a transformer block: 96 tiles of 256 x 256, which leave most
-// of the device idle) goes to the persistent kernel in 256 x 128 tiles with four waves of 128 x 64 each: at least half the
-// compute units get a unit, none gets two, and a k-loop of at least 8 k-tiles carries the unit's prologue and epilogue.
-// Measured against the 128 x 128 tiles of the other kernel (384 workgroups, two on half the compute units): 45 / 21 /
-// 57 us against 52 / 23 / 67 for the contractions over 2304 / 768 / 3072.
-static bool g3_narrow_ok(int64_t M, int64_t N, int64_t K) {
+// of the device idle) goes to the persistent kernel in 256 x 128 tiles with four waves of 128 x 64 each, where every unit has a
+// compute unit to itself, the same output in 128 x 128 tiles would not (then the kernel with asynchronous copies walks it in
+// one round: 256 tiles of 4096 x 1024, contraction 1024, 14 us against 21, 215 tiles of 640 x 5504 13 against 24), and a k-loop of at least 8
+// k-tiles carries the unit's prologue and epilogue.  Input gradients, persistent and other kernels (us), contractions over 512 /
+// 1024 / 2048 / 4096: 8448 x 512 (264 tiles of 128 x 128) 15.6 / 20.6 / 33 / 61 and 14.8 / 22 / 44 / 78, 16384 x 512 (512 tiles)
+// 17.9 / 24 / 40 / 69 and 16.3 / 25 / 47 / 81; the 8192 x 768 of a transformer block, over 2304 / 768 / 3072, 45 / 21 / 57 and 52 / 23 / 67.
+bool g3_narrow_ok(int64_t M, int64_t N, int64_t K) {
     if (K % 64 != 0 || K < 512 || N % 128 != 0) return false;
-    const int64_t units = (int64_t)cdiv(M, 256) * (N / 128);
-    return units >= compute_units() / 2 && units <= compute_units();
+    return (int64_t)cdiv(M, 256) * (N / 128) <= compute_units() && (int64_t)cdiv(M, 128) * (N / 128) > compute_units();
 }
 
 // An output of few 256-wide tiles with a very long contraction (the input gradient of a vocabulary-wide output layer:
@@ -334,7 +335,9 @@ static hipError_t dense_forward_bf16(int kc, const bf16_t* x, const bf16_t* w, c
         G3Operand<true> Bv{w, Dout, Din};
         return launch3<true, true, false>(kc, A, Bv, epi, B, Dout, Din, g3_plan(B, Dout, Din, 1), s);
     }
-    // (from 1024 on: below that the 128 x 128 tiles of the tiled kernel are as quick; 8192 x 768 x 3072 62 -> 57 us)
+    // (from 1024 on.  Forward passes, persistent and other kernels (us), over 512 / 768 / 1024 / 2048 / 4096: 8192 x 768 16.4 / 19.0 / 22.0 /
+    // 35 / 59 and 15.7 / 19.7 / 22.9 / 39 / 70, 6144 x 768 15.3 / 18.6 / 21.1 / 34 / 58 and 15.0 / 19.2 / 22.6 / 37 / 69, 4096 x 1280
+    // 17.0 / - / 22.5 / 36 / 62 and 14.8 / - / 22.2 / 37 / 77)
     if (aligned && Din >= 1024 && g3_narrow_ok(B, Dout, Din) && aligned16(x) && aligned16(w))
         return launch3_inst<256, 128, 2, 2, 2, 1, true, true, false>(kc, G3Operand<true>{x, B, Din}, G3Operand<true>{w, Dout, Din}, epi, B, Dout, Din,
                                                                      g3_plan(B, Dout, Din, 1, 256, 128), s);

@@ -15,27 +15,35 @@ class _Conv(C.Structure):
 
 def _functions():
     lib = load_library()
-    plan, small, rows, wg3 = (getattr(lib, n) for n in ("_ZN4tmps8plan_forElllbii", "_ZN4tmps15small_is_betterEllliRKNS_5Plan2E",
-                                                        "_ZN4tmps17conv_rows_variantERKNS_9ConvShapeEliid", "_ZN4tmps15g3_wgrad_slicesElll"))
+    plan, small, rows = (getattr(lib, n) for n in ("_ZN4tmps8plan_forElllbii", "_ZN4tmps15small_is_betterEllliRKNS_5Plan2E",
+                                                   "_ZN4tmps17conv_rows_variantERKNS_9ConvShapeEliid"))
+    persistent = {}   # the rules of the persistent kernel
+    for name, result in (("g3_forward_ok", C.c_bool), ("g3_narrow_ok", C.c_bool), ("g3_wgrad_slices", C.c_int), ("g3_long_k_slices", C.c_int)):
+        f = persistent[name] = getattr(lib, "_ZN4tmps%d%sElll" % (len(name), name))
+        f.restype, f.argtypes = result, [C.c_long, C.c_long, C.c_long]
     plan.restype, plan.argtypes = _Plan, [C.c_long, C.c_long, C.c_long, C.c_bool, C.c_int, C.c_int]
     small.restype, small.argtypes = C.c_bool, [C.c_long, C.c_long, C.c_long, C.c_int, C.POINTER(_Plan)]
     rows.restype, rows.argtypes = C.c_int, [C.POINTER(_Conv), C.c_long, C.c_int, C.c_int, C.c_double]
-    wg3.restype, wg3.argtypes = C.c_int, [C.c_long, C.c_long, C.c_long]
-    return plan, small, rows, wg3
+    return plan, small, rows, persistent
 
 
 KINDS = ("tiled", "by_k", "async")
 DENSE, CONV = 1, 2   # operands that a kernel with asynchronous copies can address: matrices, a convolution's
 
 
-def _route(M, N, K, wgrad, esize, operands):
-    plan, small, _, wg3 = _functions()
-    p = plan(M, N, K, wgrad, esize, operands)
-    if operands == DENSE and esize == 2:
-        # (the persistent kernel comes first: outputs of 128 tiles of 256 x 128 or more, very long contractions, large weight gradients)
-        units = -(-M // 256) * -(-N // 128)
-        if (wg3(M, N, K) > 0) if wgrad else (units >= 128 or K >= 8192):
-            return "persistent?"
+FORWARD, INPUT, WEIGHT = range(3)
+
+
+def _route(M, N, K, which, esize, operands):
+    plan, small, _, g3 = _functions()
+    p = plan(M, N, K, which == WEIGHT, esize, operands)
+    if operands == DENSE and esize == 2:   # (the persistent kernel's rules come first)
+        if g3["g3_wgrad_slices"](M, N, K) if which == WEIGHT else g3["g3_forward_ok"](M, N, K):
+            return "persistent"
+        if which == INPUT and g3["g3_long_k_slices"](M, N, K) > 1:
+            return "persistent split"
+        if (which == INPUT or which == FORWARD and K >= 1024) and g3["g3_narrow_ok"](M, N, K):
+            return "persistent narrow"
     if operands == DENSE and small(M, N, K, esize, C.byref(p)):
         return "small"
     if p.kind == 2 and N % 8:
@@ -48,7 +56,7 @@ def dense_routes(sp, dtype, micro, N):
     e, rows = 2 if dtype == "bf16" else 4, sp.get("rows", 1)
     din, dout, mb, M = sp["din"], sp["dout"], micro * rows, micro * N * rows
     assert din % (16 // e) == 0 and dout % (16 // e) == 0
-    return _route(mb, dout, din, False, e, DENSE), _route(M, din, dout, False, e, DENSE), _route(dout, din, M, True, e, DENSE)
+    return _route(mb, dout, din, FORWARD, e, DENSE), _route(M, din, dout, INPUT, e, DENSE), _route(dout, din, M, WEIGHT, e, DENSE)
 
 
 def conv_routes(sp, dtype, micro, N):
@@ -63,5 +71,5 @@ def conv_routes(sp, dtype, micro, N):
     for B, m, n, c in ((micro, micro * ho * wo, cout, cin), (micro * N, micro * N * sp["h"] * sp["w"], cin, cout)):
         shape = _Conv(B, sp["h"], sp["w"], cin, ho, wo, cout, sp["r"], sp["s"], sp["stride"], sp["pad"])
         v = rows(C.byref(shape), m, n, c, plan(m, n, taps * c, False, 2, CONV).cost / 2400.0) if dtype == "bf16" else 0
-        out.append("rows %d" % v if v else _route(m, n, taps * c, False, e, CONV))
-    return out[0], out[1], _route(cout, taps * cin, micro * N * ho * wo, True, e, CONV)
+        out.append("rows %d" % v if v else _route(m, n, taps * c, FORWARD, e, CONV))
+    return out[0], out[1], _route(cout, taps * cin, micro * N * ho * wo, WEIGHT, e, CONV)

@@ -24,6 +24,10 @@ DENSE = [
     ("bf16", 1000, 776, 2952, ("async", "by_k", "async")),     # 13 k-tiles, the last one short
     ("bf16", 1003, 2952, 776, ("by_k", "async", "async")),
     ("bf16", 3745, 3464, 72, (None, None, "async split")),
+    ("bf16", 4096, 1024, 512, (None, "async", None)),            # outputs of 256 tiles of 128 x 128 ...
+    ("bf16", 4096, 1024, 1024, ("async", "async", None)),
+    ("bf16", 640, 1024, 5504, ("async", None, None)),           # ... or fewer, but more than 128 of 256 x 128
+    ("bf16", 4224, 1024, 1024, ("persistent narrow", "persistent narrow", None)),   # and of more
 ]
 CONV = [
     # (dtype, h, w, cin, cout, stride, samples, (forward, input gradient, weight gradient))
