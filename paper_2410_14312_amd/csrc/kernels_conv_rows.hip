@@ -48,7 +48,11 @@ static double rows_us(int nw, int wm, int ns, const ConvShape& c, int64_t M, int
 int conv_rows_variant(const ConvShape& c, int64_t M, int N, int C, double other_us) {
     if (c.stride != 1 || c.R != 2 * c.pad + 1 || c.S != 2 * c.pad + 1 || c.R * c.S < 9 || c.R * c.S > 32 || C % 64 != 0 || N % 8 != 0 || !small_enough(c)) return 0;
     int best = 0;
-    double best_us = 1.3 * other_us;   // (what the other kernels' plan estimates is too low by that for convolutions)
+    // What the other kernels' plan estimates is too low for convolutions: over 84 passes of 3 x 3 filters (42 shapes, 3 to 128 images of
+    // 2 x 2 to 100 x 100, 64 to 512 channels) they took 0.8 to 2.1 times as long, quartiles 1.07, 1.34 and 1.45.  The factor stands here
+    // because the choice among those kernels was fitted to the estimates as they are.  With it the kernel taken was within 1 % of the
+    // best one in nine passes of ten, at worst 16 % off (64 images of 2 x 2 x 512: 18.6 us against 16.1).
+    double best_us = 1.3 * other_us;
     for (int v : {413, 422, 443, 823}) {
         const double us = rows_us(v / 100, v / 10 % 10, v % 10, c, M, N, C);
         if (us < best_us) {

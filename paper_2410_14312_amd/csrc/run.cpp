@@ -37,9 +37,11 @@ int grow_events(tmps_stage* st, size_t n) {
 // What a worker issues in one go: a backward pass with its update, or the forward passes of `count` consecutive
 // micro-batches of one mini-batch that stand next to each other in the worker's order and read the same weights.
 // Their rows are consecutive in the stash, so they are one pass over `count` times the rows: the layers' kernels then
-// have the rows to fill the device and are launched once.  (A micro-batch of the GPT-2 configuration is 1024 rows: its
-// forward GEMMs ran at 260 TFLOP/s and were bound by launches and latency, 8192 rows reach 700; a mini-batch took 13.1 ms
-// pass by pass and takes 11.9 ms, the tiny fp32 MLP 283 and 185 us, VGG-16 1.47 and 1.26 ms, ResNet-50 8.9 and 8.3 ms.)
+// have the rows to fill the device and are launched once.  (The GEMMs of a GPT-2 micro-batch, 1024 rows, reach 180 to 400
+// TFLOP/s, those of 8192 rows 520 to 750.  Time per mini-batch pass by pass and merged, in runs of 20: GPT-2 13.6 and 11.8 ms on
+// four streams, 16.0 and 12.3 on one; ResNet-50 8.3 and 7.4, 10.1 and 7.5; VGG-16 1.30 and 1.13, 1.59 and 1.15; the tiny fp32
+// MLP on one stream 76 and 46 us.  The backward passes that fall between a mini-batch's micro-batches cut its forward into
+// 1.7 passes of GPT-2 on average.)
 // No dependency is added that could close a circle: whatever follows from one member and precedes a later one would
 // have to pass through a backward pass of this worker between the two.
 struct Node {
@@ -207,7 +209,9 @@ void build_nodes(RunCtx& c, const std::vector<Task>& tasks) {
 
 // Device time of a pass over `rows` samples, roughly: 5 us for every launch it is expected to make (a contraction one
 // forward and a split now and then, two to three backward; other layers one and two), its operations at the rates that
-// mid-sized contractions reach, and the update at 4 TB/s.
+// mid-sized contractions reach, and the update at 4 TB/s.  Whole runs take less than their estimate: two mini-batches on one
+// stream 100 us of 166 (tiny fp32 MLP), 285 of 408 (bf16 MLP), 2.2 ms of 3.3 (VGG-16), 14.8 of 17.9 (ResNet-50), 24.2 of 47.8 (GPT-2;
+// 64.7 of 77.9 in 1F1B order).
 double pass_us(const tmps_stage& st, int rows, bool backward) {
     double us = 0.0;
     for (const LayerRT& L : st.layers) {
@@ -226,8 +230,11 @@ double pass_us(const tmps_stage& st, int rows, bool backward) {
 // (about 100 us a run) and for every hand-over from stream to stream (about 25 us in a chain of short passes) and gains
 // what the workers' passes overlap: nothing within a single mini-batch, some 5 % of the work where a mini-batch's
 // micro-batches are forwarded together, some 20 % where mini-batches are short against the pipeline (N <= 2) and in 1F1B
-// order (measured over the four kinds of networks, K = 2 to 4: the tiny fp32 MLP 254 us per two mini-batches on two streams
-// and 113 on one, the bf16 MLP 830 and 600 for four; GPT-2 2 % and its 1F1B run 25 % quicker on four).
+// order.  Measured on K streams and on one: two mini-batches of the tiny fp32 MLP 277 and 100 us, the bf16 MLP 511 and 285,
+// the tiny fp32 transformer 611 and 485, VGG-16 2.28 and 2.19 ms, ResNet-50 15.1 and 14.8, GPT-2 23.9 and 24.2; twenty of VGG-16 22.5 and
+// 22.9 ms, ResNet-50 147.7 and 150.7, GPT-2 236 and 247; 1F1B order, VGG-16 5.4 and 6.7 ms, ResNet-50 27.3 and 42.5, GPT-2 50.5 and
+// 64.7.  Not in the estimate: a hand-over costs a short pass some 8 us of every run, however long; twenty mini-batches of
+// the bf16 MLP (4.2 and 2.8 ms) or the tiny transformer (6.2 and 4.7) are left on K streams.
 bool serial_is_quicker(const RunCtx& c) {
     double total = 0.0;
     size_t nodes = 0;
