@@ -881,13 +881,15 @@ extern "C" int tmps_update(tmps_stage* st, void* hip_stream) {
         ProfileScope empty(kcEventPair, s);
     }
     if (st->shadow_n > 0) {
-        // vertical weight stashing: the version about to be superseded is kept for the forward passes tagged with it
+        // the version about to be superseded is kept for the passes tagged with it: the update stores what it replaces
         const int slot = (int)(st->version % st->shadow_n);
-        TMPS_RUN(kcCopy, s, hipMemcpyAsync(st->shadow + (size_t)slot * st->param_bytes, st->params, st->param_bytes,
-                                           hipMemcpyDeviceToDevice, s));
+        float* const kept = reinterpret_cast<float*>(st->shadow + (size_t)slot * st->param_bytes);
+        TMPS_RUN(kcUpdate, s, sgd_momentum_keeping(st->master, st->mom, st->grad, st->wcopy, st->P, st->cfg.lr, st->cfg.momentum, kept,
+                                                   st->wcopy ? (void*)(kept + st->P) : nullptr, s));
         st->shadow_ver[slot] = st->version;
+    } else {
+        TMPS_RUN(kcUpdate, s, sgd_momentum(st->master, st->mom, st->grad, st->wcopy, st->P, st->cfg.lr, st->cfg.momentum, s));
     }
-    TMPS_RUN(kcUpdate, s, sgd_momentum(st->master, st->mom, st->grad, st->wcopy, st->P, st->cfg.lr, st->cfg.momentum, s));
     ++st->version;
     return TMPS_OK;
 }

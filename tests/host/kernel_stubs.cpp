@@ -41,6 +41,11 @@ hipError_t softmax_ce(int dtype, const float* logits, const int32_t* labels, voi
 hipError_t reduce_scaled_sum(const float* in, int n, float scale, float* out, hipStream_t s) { return hipSuccess; }
 hipError_t relu_mask(int dtype, const void* dy, const void* y, void* dz, int64_t n, hipStream_t s) { return hipSuccess; }
 hipError_t sgd_momentum(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu, hipStream_t s) { return hipSuccess; }
+hipError_t sgd_momentum_keeping(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu, float* kept_w, void* kept_wcopy, hipStream_t s) {
+    memcpy(kept_w, w, (size_t)n * 4);
+    if (wcopy_bf16) memcpy(kept_wcopy, wcopy_bf16, (size_t)n * 2);
+    return hipSuccess;
+}
 hipError_t cast_f32_to_bf16(const float* in, void* out, int64_t n, hipStream_t s) { return hipSuccess; }
 hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t) { memcpy(dst, src, bytes); return hipSuccess; }
 GemmPlan plan_gemm(int64_t, int64_t, int64_t) { return GemmPlan{64, 1}; }
