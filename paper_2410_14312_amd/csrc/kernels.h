@@ -112,6 +112,12 @@ hipError_t embedding_backward(int dtype, const int32_t* tok, const void* dy, flo
 // dlogits[rows, C] = (softmax - onehot) * inv_M in the gradient dtype.
 hipError_t softmax_ce(int dtype, const float* logits, const int32_t* labels, void* dlogits,
                       float* row_loss, int rows, int C, float inv_M, hipStream_t s);
+// The same for few rows (softmax_ce_small_takes(rows of the loss, C)) in one workgroup, together with what else the loss layer hands out:
+// y (may be null) a copy of the logits; loss_out (may be null) = scale times the sum of row_loss, whose first `before` values other
+// passes have left there (this pass's rows follow them).
+bool softmax_ce_small_takes(int64_t rows, int C);
+hipError_t softmax_ce_small(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* y, float* row_loss, int rows,
+                            int C, int before, float inv_M, float scale, float* loss_out, hipStream_t s);
 // out[0] = scale * sum(in[0..n))   (deterministic single-block tree)
 hipError_t reduce_scaled_sum(const float* in, int n, float scale, float* out, hipStream_t s);
 

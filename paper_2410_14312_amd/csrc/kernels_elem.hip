@@ -289,6 +289,102 @@ hipError_t reduce_scaled_sum(const float* in, int n, float scale, float* out, hi
     return hipGetLastError();
 }
 
+// Few rows: one 1024-thread workgroup, LPR lanes to a row with up to 8 of its values each in registers, so that 1024 / LPR rows are
+// in flight at once; then the mean over all rows of the loss, summed in the order of reduce_scaled_sum_kernel.  What such a launch
+// takes is latency: 47 rows of 10 classes run as long as one row does, and the launch replaces two or three of 4 to 5 us each
+// (five micro-batches of a four-layer fp32 MLP, backward pass and update: 269 -> 257 us).
+template <typename TG, int LPR>
+__global__ __launch_bounds__(1024) void softmax_ce_small_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
+                                                                TG* __restrict__ dlogits, float* __restrict__ y, float* row_loss,
+                                                                int rows, int C, int before, float inv_M, float scale,
+                                                                float* __restrict__ loss_out) {
+    const int tid = threadIdx.x, sub = tid & (LPR - 1);
+    for (int row = tid / LPR; row < rows; row += 1024 / LPR) {
+        const float* z = logits + (int64_t)row * C;
+        float v[8];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int c = sub + e * LPR;
+            v[e] = c < C ? z[c] : -INFINITY;
+            mx = fmaxf(mx, v[e]);
+        }
+        if (y) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int c = sub + e * LPR;
+                if (c < C) y[(int64_t)row * C + c] = v[e];
+            }
+        }
+#pragma unroll
+        for (int o = LPR / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        const int label = labels[row];
+        const bool label_ok = label >= 0 && label < C;  // an out-of-range label gives a NaN loss, never a wild read
+        float sum = 0.0f, hit = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int c = sub + e * LPR;
+            if (c < C) {
+                v[e] -= mx;
+                if (c == label) hit = v[e];
+                v[e] = expf(v[e]);
+                sum += v[e];
+            }
+        }
+#pragma unroll
+        for (int o = LPR / 2; o > 0; o >>= 1) {
+            sum += __shfl_xor(sum, o, 64);
+            hit += __shfl_xor(hit, o, 64);   // (one lane's value and zeros)
+        }
+        const float inv = 1.0f / sum;
+        TG* g = dlogits + (int64_t)row * C;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int c = sub + e * LPR;
+            if (c < C) g[c] = from_f32<TG>((v[e] * inv - (c == label ? 1.0f : 0.0f)) * inv_M);
+        }
+        if (sub == 0) row_loss[before + row] = label_ok ? logf(sum) - hit : NAN;
+    }
+    if (!loss_out) return;
+    __shared__ float part[4];
+    __syncthreads();   // (the row losses are this workgroup's own stores, or an earlier launch's)
+    if (tid < 256) {
+        float a = 0.0f;
+        for (int i = tid; i < before + rows; i += 256) a += row_loss[i];
+        a = wave_sum(a);
+        if ((tid & 63) == 0) part[tid >> 6] = a;
+    }
+    __syncthreads();
+    if (tid == 0) loss_out[0] = (part[0] + part[1] + part[2] + part[3]) * scale;
+}
+
+// Up to 1024 rows of the loss in all, 512 classes and 32768 logits: four rounds of the workgroup's registers.
+bool softmax_ce_small_takes(int64_t rows, int C) { return rows <= 1024 && C <= 512 && rows * C <= 32768; }
+
+template <typename TG, int LPR>
+static hipError_t launch_ce_small(const float* logits, const int32_t* labels, void* dlogits, float* y, float* row_loss, int rows, int C,
+                                  int before, float inv_M, float scale, float* loss_out, hipStream_t s) {
+    hipLaunchKernelGGL((softmax_ce_small_kernel<TG, LPR>), dim3(1), dim3(1024), 0, s, logits, labels, (TG*)dlogits, y, row_loss, rows, C, before,
+                       inv_M, scale, loss_out);
+    return hipGetLastError();
+}
+
+template <typename TG>
+static hipError_t ce_small_of(const float* logits, const int32_t* labels, void* dlogits, float* y, float* row_loss, int rows, int C, int before,
+                              float inv_M, float scale, float* loss_out, hipStream_t s) {
+    if (C <= 16) return launch_ce_small<TG, 2>(logits, labels, dlogits, y, row_loss, rows, C, before, inv_M, scale, loss_out, s);
+    if (C <= 64) return launch_ce_small<TG, 8>(logits, labels, dlogits, y, row_loss, rows, C, before, inv_M, scale, loss_out, s);
+    if (C <= 128) return launch_ce_small<TG, 16>(logits, labels, dlogits, y, row_loss, rows, C, before, inv_M, scale, loss_out, s);
+    return launch_ce_small<TG, 64>(logits, labels, dlogits, y, row_loss, rows, C, before, inv_M, scale, loss_out, s);
+}
+
+hipError_t softmax_ce_small(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* y, float* row_loss, int rows,
+                            int C, int before, float inv_M, float scale, float* loss_out, hipStream_t s) {
+    if (rows <= 0) return hipSuccess;
+    if (dtype == kBF16) return ce_small_of<bf16_t>(logits, labels, dlogits, y, row_loss, rows, C, before, inv_M, scale, loss_out, s);
+    return ce_small_of<float>(logits, labels, dlogits, y, row_loss, rows, C, before, inv_M, scale, loss_out, s);
+}
+
 // ------------------------------------------------------------------------------- ReLU gradient
 template <typename T>
 __global__ void relu_mask_kernel(const T* __restrict__ dy, const T* __restrict__ y, T* __restrict__ dz,

@@ -52,5 +52,5 @@ extern "C" int tmps_forward_micro_static(tmps_stage* st, int slot, const void* x
     if (rc != TMPS_OK) return rc;
     // Nothing in the workspace has to start at zero: every k-slice writes its whole partial tile before the finishing
     // kernel of the same launch sequence reads it, so what an earlier call left behind is never read.
-    return forward_with_workspace(st, slot, 1, x, y, labels, loss_out, hip_stream, ws);
+    return forward_with_workspace(st, slot, 1, x, y, labels, loss_out, hip_stream, ws, 0);
 }

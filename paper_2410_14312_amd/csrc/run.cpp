@@ -158,9 +158,13 @@ int issue(RunCtx& c, const Node& n) {
                                      : tmps_stage_output_ptr(c.stages[n.stage - 1], (b0 % c.groups[n.stage - 1]) * N + n.j0);
         const int32_t* lab = st->cfg.is_last ? c.labels + row * st->label_rps : nullptr;
         const long version = c.vsync ? c.base_version[n.stage] + n.net_version : st->version;
-        if ((rc = forward_run_at(st, version, slot, n.count, x, nullptr, lab, nullptr, s)) != TMPS_OK) return rc;
+        // The pass over a mini-batch's last micro-batches also forms its loss.  (Not on a stage that replays graphs: the address
+        // of the loss is another one for every mini-batch.)
+        const bool ends = st->cfg.is_last && n.j0 + n.count == N && c.losses_out;
+        float* const loss = ends && !st->use_graphs ? c.losses_out + b0 : nullptr;
+        if ((rc = forward_run_at(st, version, slot, n.count, x, nullptr, lab, loss, s, loss ? n.j0 : 0)) != TMPS_OK) return rc;
         if (n.stage < K - 1 && (rc = c.record(c.fwd_ev(n.stage, (size_t)b0 * N + n.j0 + n.count - 1), s)) != TMPS_OK) return rc;
-        if (st->cfg.is_last && n.j0 + n.count == N && c.losses_out) {
+        if (ends && !loss) {
             ProfileScope scope(kcReduce, s);
             const int rows = c.M * st->label_rps;
             TMPS_HIP(reduce_scaled_sum(stage_row_loss(st, group * N), rows, 1.0f / (float)rows, c.losses_out + b0, s));

@@ -474,11 +474,11 @@ static const void* layer_input(const tmps_stage* st, int li, const void* x0, int
 extern "C" int tmps_forward_micro(tmps_stage* st, int slot, const void* x, void* y, const int32_t* labels,
                                   float* loss_out, void* hip_stream) {
     if (!st) return fail(TMPS_EINVAL, "stage or x is null");
-    return forward_with_workspace(st, slot, 1, x, y, labels, loss_out, hip_stream, reinterpret_cast<float*>(st->scratch + st->ws_off));
+    return forward_with_workspace(st, slot, 1, x, y, labels, loss_out, hip_stream, reinterpret_cast<float*>(st->scratch + st->ws_off), 0);
 }
 
 int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void* x, void* y, const int32_t* labels,
-                                 float* loss_out, void* hip_stream, float* ws) {
+                                 float* loss_out, void* hip_stream, float* ws, int before) {
     if (!st || !x) return fail(TMPS_EINVAL, "stage or x is null");
     if (slot < 0 || slot >= st->cfg.max_stash) return fail(TMPS_ESLOT, "slot %d outside 0..%d", slot, st->cfg.max_stash - 1);
     if (slot % st->cfg.n_micro + count > st->cfg.n_micro) return fail(TMPS_ESLOT, "slots %d..%d are not of one mini-batch group", slot, slot + count - 1);
@@ -503,8 +503,11 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
         TMPS_RUN(kcCopy, s, hipMemcpyAsync(lab, labels, (size_t)mb * st->label_rps * 4, hipMemcpyDeviceToDevice, s));
         labels = lab;
     }
-    const tmps_stage::GraphKey key = {1 + 2 * (uintptr_t)count, (uintptr_t)slot, (uintptr_t)x0, (uintptr_t)labels, (uintptr_t)loss_out, (uintptr_t)ws,
+    const tmps_stage::GraphKey key = {1 + 2 * ((uintptr_t)count + 128 * (uintptr_t)before), (uintptr_t)slot, (uintptr_t)x0, (uintptr_t)labels, (uintptr_t)loss_out, (uintptr_t)ws,
                                       (uintptr_t)st->master, (uintptr_t)st->wcopy};
+    // (asked of a whole mini-batch's rows: all of its passes then run the same kernel, however they are cut)
+    const bool small_loss = st->cfg.is_last && softmax_ce_small_takes((int64_t)st->M() * st->label_rps, st->layers.back().d.dims[0]);
+    float* const y_by_loss = small_loss && !st->use_graphs ? static_cast<float*>(y) : nullptr;
     const int rc = run_or_replay(st, key, s, [&]() -> int {
     for (size_t li = 0; li < st->layers.size(); ++li) {
         const LayerRT& L = st->layers[li];
@@ -579,11 +582,16 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
                                             d[2], d[0], s));
                 break;
             case TMPS_SOFTMAX_CE: {
-                float* rl = stage_row_loss(st, slot);
-                const int rows = mb * L.rps;
-                TMPS_RUN(kcSoftmaxCE, s, softmax_ce(dt, (const float*)in, labels, out, rl, rows, d[0],
+                const int rows = mb * L.rps, rows_before = before * st->cfg.micro_batch * L.rps, all = rows_before + rows;
+                float* rl = stage_row_loss(st, slot - before);   // (of the rows before, then this pass's)
+                if (small_loss) {
+                    TMPS_RUN(kcSoftmaxCE, s, softmax_ce_small(dt, (const float*)in, labels, out, y_by_loss, rl, rows, d[0], rows_before,
+                                                              1.0f / ((float)st->M() * (float)L.rps), 1.0f / (float)all, loss_out, s));
+                    break;
+                }
+                TMPS_RUN(kcSoftmaxCE, s, softmax_ce(dt, (const float*)in, labels, out, rl + rows_before, rows, d[0],
                                                     1.0f / ((float)st->M() * (float)L.rps), s));
-                if (loss_out) TMPS_RUN(kcReduce, s, reduce_scaled_sum(rl, rows, 1.0f / (float)rows, loss_out, s));
+                if (loss_out) TMPS_RUN(kcReduce, s, reduce_scaled_sum(rl, all, 1.0f / (float)all, loss_out, s));
                 break;
             }
         }
@@ -591,7 +599,7 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
     return TMPS_OK;
     });
     if (rc != TMPS_OK) return rc;
-    if (y) {
+    if (y && !y_by_loss) {
         const LayerRT& L = st->cfg.is_last ? st->layers[st->layers.size() - 2] : st->layers.back();
         TMPS_RUN(kcCopy, s, hipMemcpyAsync(y, st->out_ptr(L, row0), (size_t)mb * L.out_elems * L.out_esize,
                                 hipMemcpyDeviceToDevice, s));
@@ -918,9 +926,9 @@ extern "C" int tmps_backward_at(tmps_stage* st, long version, const int* slots, 
 }
 
 int tmps::forward_run_at(tmps_stage* st, long version, int slot, int count, const void* x, void* y, const int32_t* labels,
-                         float* loss_out, void* hip_stream) {
+                         float* loss_out, void* hip_stream, int before) {
     float* const ws = reinterpret_cast<float*>(st->scratch + st->ws_off);
-    if (version == st->version) return forward_with_workspace(st, slot, count, x, y, labels, loss_out, hip_stream, ws);
+    if (version == st->version) return forward_with_workspace(st, slot, count, x, y, labels, loss_out, hip_stream, ws, before);
     int found = -1;
     for (int k = 0; k < st->shadow_n; ++k)
         if (st->shadow_ver[k] == version) found = k;
@@ -934,7 +942,7 @@ int tmps::forward_run_at(tmps_stage* st, long version, int slot, int count, cons
     char* base = st->shadow + (size_t)found * st->param_bytes;
     st->master = reinterpret_cast<float*>(base);
     if (live_wcopy) st->wcopy = base + (size_t)st->P * 4;
-    const int rc = forward_with_workspace(st, slot, count, x, y, labels, loss_out, hip_stream, ws);
+    const int rc = forward_with_workspace(st, slot, count, x, y, labels, loss_out, hip_stream, ws, before);
     st->master = live_master;
     st->wcopy = live_wcopy;
     return rc;
@@ -943,5 +951,5 @@ int tmps::forward_run_at(tmps_stage* st, long version, int slot, int count, cons
 extern "C" int tmps_forward_micro_at(tmps_stage* st, long version, int slot, const void* x, void* y, const int32_t* labels,
                                      float* loss_out, void* hip_stream) {
     if (!st) return fail(TMPS_EINVAL, "stage is null");
-    return forward_run_at(st, version, slot, 1, x, y, labels, loss_out, hip_stream);
+    return forward_run_at(st, version, slot, 1, x, y, labels, loss_out, hip_stream, 0);
 }

@@ -106,11 +106,11 @@ void* stage_dxout(tmps_stage* st, int which);
 float* stage_row_loss(tmps_stage* st, int slot);
 // The forward passes of `count` micro-batches in the slots from `slot` on (of one mini-batch group, their inputs
 // consecutive in memory) as ONE pass over their rows with the current weights; `ws`: the fp32 workspace of its
-// contractions (st->ws_fwd_bytes for count = 1; the part of the scratch region is large enough for any count).  y and
-// loss_out belong to count = 1.
+// contractions (st->ws_fwd_bytes for count = 1; the part of the scratch region is large enough for any count).  y
+// belongs to count = 1; loss_out receives the mean loss of this pass's rows and of those of the `before` slots in front of `slot`.
 int forward_with_workspace(tmps_stage* st, int slot, int count, const void* x, void* y, const int32_t* labels,
-                           float* loss_out, void* hip_stream, float* ws);
+                           float* loss_out, void* hip_stream, float* ws, int before);
 // The same in the stage's own workspace on the weights as they were after `version` updates (tmps_forward_micro_at).
 int forward_run_at(tmps_stage* st, long version, int slot, int count, const void* x, void* y, const int32_t* labels,
-                   float* loss_out, void* hip_stream);
+                   float* loss_out, void* hip_stream, int before);
 }  // namespace tmps

@@ -38,6 +38,8 @@ hipError_t embedding_backward(int dtype, const int32_t* tok, const void* dy, flo
 hipError_t softmax_ce(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* row_loss, int rows, int C, float inv_M, hipStream_t s) {
     return kernel_stubs.losses_until_failure-- == 0 ? hipErrorLaunchFailure : hipSuccess;
 }
+bool softmax_ce_small_takes(int64_t, int) { return false; }
+hipError_t softmax_ce_small(int, const float*, const int32_t*, void*, float*, float*, int, int, int, float, float, float*, hipStream_t) { return hipSuccess; }
 hipError_t reduce_scaled_sum(const float* in, int n, float scale, float* out, hipStream_t s) { return hipSuccess; }
 hipError_t relu_mask(int dtype, const void* dy, const void* y, void* dz, int64_t n, hipStream_t s) { return hipSuccess; }
 hipError_t sgd_momentum(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu, hipStream_t s) { return hipSuccess; }
