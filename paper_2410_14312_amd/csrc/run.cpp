@@ -174,10 +174,15 @@ int issue(RunCtx& c, const Node& n) {
         void* dx = n.stage > 0 ? stage_dxout(st, b0 & 1) : nullptr;
         int slots[64];
         for (int j = 0; j < N; ++j) slots[j] = group * N + j;
+        // does worker a pass a gradient down through the ReLU that ends the worker below it?
+        auto masked_above = [&](int below) {
+            return below >= 0 && below < K - 1 && c.stages[below]->layers.back().relu && can_mask_dx(*c.stages[below + 1]);
+        };
+        const int flags = (masked_above(n.stage - 1) ? kMaskDx : 0) | (masked_above(n.stage) ? kDyMasked : 0);
         if (c.one_f1b)   // horizontal weight stashing: differentiate at the weights the forward pass read
-            rc = tmps_backward_at(st, c.base_version[n.stage] + n.stage_version, slots, N, dy, dx, s);
+            rc = backward_between_at(st, c.base_version[n.stage] + n.stage_version, slots, N, dy, dx, s, flags);
         else
-            rc = tmps_backward(st, slots, N, dy, dx, s);
+            rc = backward_between(st, slots, N, dy, dx, s, flags);
         if (rc != TMPS_OK) return rc;
         if ((rc = c.record(c.bwd_ev(n.stage, b0), s)) != TMPS_OK) return rc;
         if ((rc = tmps_update(st, s)) != TMPS_OK) return rc;

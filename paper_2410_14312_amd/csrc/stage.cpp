@@ -610,6 +610,21 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
 
 extern "C" int tmps_backward(tmps_stage* st, const int* slots, int n_slots, const void* dy, void* dx,
                              void* hip_stream) {
+    return backward_between(st, slots, n_slots, dy, dx, hip_stream, 0);
+}
+
+bool tmps::can_mask_dx(const tmps_stage& st) {
+    bool reads = false;
+    for (const LayerRT& L : st.layers) {
+        const bool first = L.in_t < 0, joins = L.d.kind == TMPS_RESADD && L.in_b < 0;
+        if (joins || (first && L.d.kind != TMPS_LINEAR && L.d.kind != TMPS_CONV2D)) return false;
+        reads = reads || first;
+        // (a residual connection from the stage input starts at a layer normalisation, which is no such reader)
+    }
+    return reads;
+}
+
+int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const void* dy, void* dx, void* hip_stream, int flags) {
     if (!st || !slots) return fail(TMPS_EINVAL, "stage or slots is null");
     const int N = st->cfg.n_micro, mb = st->cfg.micro_batch, M = st->M();
     if (n_slots != N)
@@ -649,7 +664,7 @@ extern "C" int tmps_backward(tmps_stage* st, const int* slots, int n_slots, cons
         }
     } free_slots{st, g0, N};
 
-    const tmps_stage::GraphKey key = {2, (uintptr_t)g0, (uintptr_t)x0, (uintptr_t)dy, (uintptr_t)dx, 0,
+    const tmps_stage::GraphKey key = {2, (uintptr_t)g0, (uintptr_t)x0, (uintptr_t)dy, (uintptr_t)dx, (uintptr_t)flags,
                                       (uintptr_t)st->master, (uintptr_t)st->wcopy};
     return run_or_replay(st, key, s, [&]() -> int {
     // Gradients are kept per result: grads[t + 1] is the gradient w.r.t. the result of layer t (t = -1: the stage
@@ -683,7 +698,7 @@ extern "C" int tmps_backward(tmps_stage* st, const int* slots, int n_slots, cons
     // the stored activation that a gradient written for result t has to pass through (mode 1: ReLU, 2: GELU)
     auto mask_of = [&](int t, int& mode) -> const void* {
         mode = 1;
-        if (t < 0) return nullptr;
+        if (t < 0) return (flags & kMaskDx) ? (const void*)x0 : nullptr;   // (the stage input is that activation's result)
         const LayerRT& P = st->layers[t];
         if (P.act == 1) return st->out_ptr(P, row0);
         if (P.act == 2) {
@@ -769,7 +784,7 @@ extern "C" int tmps_backward(tmps_stage* st, const int* slots, int n_slots, cons
         G.buf = -1;
         G.set = true;
         const LayerRT& T = st->layers[top];
-        if (T.relu) {
+        if (T.relu && !(flags & kDyMasked)) {
             const int k = take();
             TMPS_RUN(kcReluMask, s, relu_mask(dt, dy, st->out_ptr(T, row0), gbuf[k], (int64_t)M * T.out_elems, s));
             G.ptr = gbuf[k];
@@ -904,8 +919,12 @@ extern "C" int tmps_update(tmps_stage* st, void* hip_stream) {
 
 extern "C" int tmps_backward_at(tmps_stage* st, long version, const int* slots, int n_slots, const void* dy, void* dx,
                                 void* hip_stream) {
+    return backward_between_at(st, version, slots, n_slots, dy, dx, hip_stream, 0);
+}
+
+int tmps::backward_between_at(tmps_stage* st, long version, const int* slots, int n_slots, const void* dy, void* dx, void* hip_stream, int flags) {
     if (!st) return fail(TMPS_EINVAL, "stage is null");
-    if (version == st->version) return tmps_backward(st, slots, n_slots, dy, dx, hip_stream);
+    if (version == st->version) return backward_between(st, slots, n_slots, dy, dx, hip_stream, flags);
     int found = -1;
     for (int k = 0; k < st->shadow_n; ++k)
         if (st->shadow_ver[k] == version) found = k;
@@ -919,7 +938,7 @@ extern "C" int tmps_backward_at(tmps_stage* st, long version, const int* slots, 
     char* base = st->shadow + (size_t)found * st->param_bytes;
     st->master = reinterpret_cast<float*>(base);
     if (live_wcopy) st->wcopy = base + (size_t)st->P * 4;
-    const int rc = tmps_backward(st, slots, n_slots, dy, dx, hip_stream);
+    const int rc = backward_between(st, slots, n_slots, dy, dx, hip_stream, flags);
     st->master = live_master;
     st->wcopy = live_wcopy;
     return rc;

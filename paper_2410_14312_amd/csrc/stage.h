@@ -113,4 +113,11 @@ int forward_with_workspace(tmps_stage* st, int slot, int count, const void* x, v
 // The same in the stage's own workspace on the weights as they were after `version` updates (tmps_forward_micro_at).
 int forward_run_at(tmps_stage* st, long version, int slot, int count, const void* x, void* y, const int32_t* labels,
                    float* loss_out, void* hip_stream, int before);
+// tmps_backward / tmps_backward_at between two workers of a run.  kMaskDx: the worker below ends in a ReLU, whose result is this
+// stage's input: dx leaves already passed through it, by the kernels that write it (can_mask_dx: all of them can), and that worker's own
+// pass is told so (kDyMasked) and makes no pass over the gradient for it.
+enum { kMaskDx = 1, kDyMasked = 2 };
+bool can_mask_dx(const tmps_stage& st);
+int backward_between(tmps_stage* st, const int* slots, int n_slots, const void* dy, void* dx, void* hip_stream, int flags);
+int backward_between_at(tmps_stage* st, long version, const int* slots, int n_slots, const void* dy, void* dx, void* hip_stream, int flags);
 }  // namespace tmps
