@@ -177,12 +177,49 @@ struct G3Plan {
     FastDiv d_blk, d_gn, d_nbn;                 // by 32, by gn, by tiles_n / gn
 };
 
+// One work unit as the kernel walks it: the first row and column of its tile, its k range and what its epilogue needs to know.
+struct G3Unit {
+    int m0, n0, k0, nk;   // nk: k-tiles of BK
+    int z, job, part_tile;   // k-slice; which contraction of a group and which of its cut tiles
+    bool first_col;       // a tile of the first column of tiles
+};
+
+// The units of one contraction.
+template <int BM, int BN, int BK, bool AKC, bool BKC, class Epi_> struct G3One {
+    typedef Epi_ Epi;
+    G3Operand<AKC> A;
+    G3Operand<BKC> B;
+    Epi_ e;
+    int rows, cols, k_total;
+    G3Plan plan;
+    __device__ __forceinline__ int units() const { return plan.units; }
+    __device__ __forceinline__ G3Unit unit(int u) const {
+        uint32_t zz, rem, m_, n_;
+        plan.d_tiles.divmod((uint32_t)u, zz, rem);
+        if (plan.gm) {
+            uint32_t blk, w, bm, bn, i, j;
+            plan.d_blk.divmod(rem, blk, w);
+            plan.d_nbn.divmod(blk, bm, bn);
+            plan.d_gn.divmod(w, i, j);
+            m_ = bm * plan.gm + i;
+            n_ = bn * plan.gn + j;
+        } else if (plan.col_major) plan.d_tn.divmod(rem, n_, m_);
+        else plan.d_tn.divmod(rem, m_, n_);
+        const int z = (int)zz, k0 = z * plan.k_per_slice, k1 = min(k_total, k0 + plan.k_per_slice);
+        return G3Unit{(int)m_ * BM, (int)n_ * BN, k0, (k1 - k0) / BK, z, 0, 0, n_ == 0};
+    }
+    __device__ __forceinline__ const G3Operand<AKC>& a(const G3Unit&) const { return A; }
+    __device__ __forceinline__ const G3Operand<BKC>& b(const G3Unit&) const { return B; }
+    __device__ __forceinline__ const Epi_& epi(const G3Unit&) const { return e; }
+    __device__ __forceinline__ int M(const G3Unit&) const { return rows; }
+    __device__ __forceinline__ int N(const G3Unit&) const { return cols; }
+};
+
 // ROWSUM: units of the first tile column also sum A over k (bias gradient of a weight-gradient GEMM, whose
 // A operand is dY, row-contiguous), from the fragments in registers; the sums go to epi.rowsum(m, v, slice).
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool AKC, bool BKC, bool ROWSUM, class Epi>
-__global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G3Operand<BKC> B, Epi epi, int M, int N,
-                                                              int K, G3Plan plan) {
-    constexpr int NW = WM * WN, NT = 64 * NW;
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool AKC, bool BKC, bool ROWSUM, class Work>
+__device__ __forceinline__ void gemm3_walk(const Work& work) {
+    constexpr int NW = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int KK = BK / 16;
     constexpr int A_BYTES = BM * BK * 2, STAGE = (BM + BN) * BK * 2;
@@ -211,46 +248,31 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G
         vb = xcd * q + min(xcd, r) + idx;
     }
 
-    auto unit_coords = [&](int u, int& tm, int& tn, int& z) {
-        uint32_t zz, rem, m_, n_;
-        plan.d_tiles.divmod((uint32_t)u, zz, rem);
-        if (plan.gm) {
-            uint32_t blk, w, bm, bn, i, j;
-            plan.d_blk.divmod(rem, blk, w);
-            plan.d_nbn.divmod(blk, bm, bn);
-            plan.d_gn.divmod(w, i, j);
-            m_ = bm * plan.gm + i;
-            n_ = bn * plan.gn + j;
-        } else if (plan.col_major) plan.d_tn.divmod(rem, n_, m_);
-        else plan.d_tn.divmod(rem, m_, n_);
-        z = (int)zz; tm = (int)m_; tn = (int)n_;
-    };
-    auto unit_nk = [&](int z) {
-        const int kb = z * plan.k_per_slice;
-        const int ke = min(K, kb + plan.k_per_slice);
-        return (ke - kb) / BK;
-    };
-
     // ---- copy cursor: runs NS-1 k-tiles ahead of the multiply cursor ----
     LoaderA la;
     LoaderB lb;
+    const int units = work.units();
     int iu = vb, ikt = 0, ink = 0, istage = 0;
+    int64_t ild_a = 0, ild_b = 0;   // leading dimensions of the cursor's operands
     auto seek_unit = [&]() {
-        if (iu < plan.units) {
-            int tm, tn, z;
-            unit_coords(iu, tm, tn, z);
-            ink = unit_nk(z);
-            la.seek(A, tm * BM, z * plan.k_per_slice, wave, lane);
-            lb.seek(B, tn * BN, z * plan.k_per_slice, wave, lane);
+        if (iu < units) {
+            const G3Unit t = work.unit(iu);
+            const auto& A = work.a(t);
+            const auto& B = work.b(t);
+            ink = t.nk;
+            ild_a = A.ld;
+            ild_b = B.ld;
+            la.seek(A, t.m0, t.k0, wave, lane);
+            lb.seek(B, t.n0, t.k0, wave, lane);
         }
         ikt = 0;
     };
-    auto copies_left = [&]() { return iu < plan.units; };
+    auto copies_left = [&]() { return iu < units; };
     // copy group g (of G) of the cursor's k-tile into stage `istage`
     auto issue_group = [&](int g) {
         const lds_t st = smem + istage * STAGE;
-        if (g < LoaderA::GROUPS) la.issue_group(st, A.ld, wave, g);
-        else lb.issue_group(st + A_BYTES, B.ld, wave, g - LoaderA::GROUPS);
+        if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g);
+        else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS);
     };
     // all G groups of the cursor's k-tile are issued: step the cursor
     auto advance = [&]() {
@@ -305,11 +327,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G
         }
     }
 
-    for (int cu = vb; cu < plan.units; cu += grid) {
-        int tm, tn, z;
-        unit_coords(cu, tm, tn, z);
-        const int nk = unit_nk(z);
-        const int m0 = tm * BM, n0 = tn * BN;
+    for (int cu = vb; cu < units; cu += grid) {
+        const G3Unit cur = work.unit(cu);
+        const int nk = cur.nk, m0 = cur.m0, n0 = cur.n0, z = cur.z;
+        const auto& epi = work.epi(cur);
+        const int M = work.M(cur), N = work.N(cur);
         f32x16_t acc[TM][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -323,14 +345,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G
         float rs[TM];
 #pragma unroll
         for (int i = 0; i < TM; ++i) rs[i] = 0.0f;
-        const bool sum_rows = ROWSUM && tn == 0;
+        const bool sum_rows = ROWSUM && cur.first_col;
 
         // What the epilogue reads from memory (a bias per column, a residual source or a mask per element), block by
         // block of 32 rows x 64 columns of this wave's results (block b: rows 32 (b / (TN / 2)), columns 64 (b % (TN / 2))).
         constexpr int NB = TM * (TN / 2);
         const int64_t epi_ld = epi.ld;
-        typename Epi::Col8 pcol[TN / 2];
-        typename Epi::Row8 prow[NB][4];
+        typename Work::Epi::Col8 pcol[TN / 2];
+        typename Work::Epi::Row8 prow[NB][4];
         // (ln: the lane's index as the caller has it; see the epilogue)
         auto epi_n = [&](int jp, int ln) { return n0 + wn * (BN / WN) + jp * 64 + (ln & 7) * 8; };
         auto epi_request = [&](int b, int ln) {
@@ -508,7 +530,84 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G
             cstage = cstage + 1 == NS ? 0 : cstage + 1;
         }
     }
-    (void)NT;
 }
+
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool AKC, bool BKC, bool ROWSUM, class Epi>
+__global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G3Operand<BKC> B, Epi epi, int M, int N,
+                                                              int K, G3Plan plan) {
+    const G3One<BM, BN, BK, AKC, BKC, Epi> work{A, B, epi, M, N, K, plan};
+    gemm3_walk<BM, BN, BK, WM, WN, NS, AKC, BKC, ROWSUM>(work);
+}
+
+// ---- several weight gradients in one launch ----------------------------------------------------------------------------
+// The weight gradients of a stage's dense layers contract over the same rows and depend on nothing but stored activations and
+// gradients, so they can be one launch at the end of the backward pass.  A single one has too few tiles for the device (36 of 256 x 256 for
+// 3072 x 768) and runs in k-slices, whose fp32 partial sums cost as much as a third of its multiplies to write and add
+// up.  Together their tiles are walked in whole rounds of the device with no slices at all; only the tiles beyond the last whole round are cut
+// along k, into as many slices as fill a round, and summed by g3_group_sum_kernel.
+// The four layers of a transformer block of 768 features over 8192 / 1024 rows, one block, two, three, four (us, launches of their own and one):
+// 196 and 135, 407 and 243, 611 and 362, 813 and 481 / 52 and 33, 105 and 40, 157 and 78, 214 and 80; the 32000 x 768 of a vocabulary over 8192 rows
+// 448 and 395.  Two mini-batches of GPT-2 small 24.2 -> 22.0 ms, three of its blocks as a stage 3.32 -> 3.04 ms, 1F1B order 23.3 -> 21.4 ms.
+// Sums over 8192 rows in one fp32 chain are 5.7e-7 (2-norm) from those in 64 bits, as the vocabulary's always were; those of 7 or 8 slices 1.9e-7.
+constexpr int kG3GroupMax = 32;   // contractions of a launch (kernel arguments hold 4 KB)
+struct G3Job {
+    const bf16_t* a;   // dY [K][M]
+    const bf16_t* b;   // X [K][N]
+    float* out;        // [M][N], then M row sums
+    int M, N, first_tile, col_major;
+    FastDiv d_minor;   // by the tiles along the direction walked first
+};
+struct G3Group {
+    typedef EpiWgrad Epi;
+    static constexpr int kTile = 256, kPart = kTile * kTile + kTile;   // floats of a partial tile: results, then row sums
+    G3Job job[kG3GroupMax];
+    int jobs, k_total, tiles, whole;   // tiles of all jobs; the first `whole` of them are not sliced
+    int slices, k_per_slice;           // of the others
+    float* part;                       // [tiles - whole][slices][kPart]
+    FastDiv d_cut;                     // by tiles - whole
+
+    __device__ __forceinline__ int units() const { return whole + (tiles - whole) * slices; }
+    // job and coordinates of a tile
+    __device__ __forceinline__ int place(int t, int& m0, int& n0) const {
+        int j = 0;
+        while (j + 1 < jobs && t >= job[j + 1].first_tile) ++j;
+        uint32_t major, minor;
+        job[j].d_minor.divmod((uint32_t)(t - job[j].first_tile), major, minor);
+        m0 = (int)(job[j].col_major ? minor : major) * kTile;
+        n0 = (int)(job[j].col_major ? major : minor) * kTile;
+        return j;
+    }
+    __device__ __forceinline__ G3Unit unit(int u) const {
+        G3Unit g;
+        int t = u;
+        g.z = -1;   // (not sliced)
+        g.k0 = 0;
+        int k1 = k_total;
+        if (u >= whole) {
+            uint32_t z, r;
+            d_cut.divmod((uint32_t)(u - whole), z, r);
+            t = whole + (int)r;
+            g.z = (int)z;
+            g.k0 = g.z * k_per_slice;
+            k1 = min(k_total, g.k0 + k_per_slice);
+        }
+        g.nk = (k1 - g.k0) >> 6;
+        g.job = place(t, g.m0, g.n0);
+        g.first_col = g.n0 == 0;
+        g.part_tile = t - whole;
+        return g;
+    }
+    __device__ __forceinline__ G3Operand<false> a(const G3Unit& g) const { return G3Operand<false>{job[g.job].a, job[g.job].M, job[g.job].M}; }
+    __device__ __forceinline__ G3Operand<false> b(const G3Unit& g) const { return G3Operand<false>{job[g.job].b, job[g.job].N, job[g.job].N}; }
+    __device__ __forceinline__ int M(const G3Unit& g) const { return job[g.job].M; }
+    __device__ __forceinline__ int N(const G3Unit& g) const { return job[g.job].N; }
+    // (addressed as the whole matrix is: a partial tile's base lies as far in front of it as the tile's first element lies inside the matrix)
+    __device__ __forceinline__ EpiWgrad epi(const G3Unit& g) const {
+        const G3Job& j = job[g.job];
+        if (g.z < 0) return EpiWgrad{j.out, j.N, (int64_t)j.M * j.N, 0};
+        const int64_t first = (int64_t)g.m0 * kTile + g.n0;
+        return EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kTile, first + kTile * kTile - g.m0, 0};
+    }
+};
 
 }  // namespace tmps

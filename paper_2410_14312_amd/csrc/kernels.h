@@ -45,6 +45,20 @@ hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const
 hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout,
                        float* ws, hipStream_t s);
 
+// The weight gradients of several dense layers over the same `rows` rows in one launch at the end of a backward pass.
+// dense_wgrad_groups: whether a layer's can be part of one.  dense_wgrad_group_elems: fp32 workspace elements of the launch that
+// takes these n layers (dims: Din, Dout), -1 where launches of their own are quicker.  In dense_wgrad_group, ws holds ws_elems.
+constexpr int kWgradGroupMax = 32;
+struct DenseWgradJob {
+    const void* dy;
+    const void* x;
+    float* gw;
+    int Din, Dout;
+};
+bool dense_wgrad_groups(int dtype, int64_t rows, int Din, int Dout);
+int64_t dense_wgrad_group_elems(int64_t rows, const int (*dims)[2], int n);
+hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_t rows, float* ws, int64_t ws_elems, hipStream_t s);
+
 hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y,
                         const ConvShape& c, int relu, float* ws, hipStream_t s);
 // Convolution (no activation of its own) fused with the per-channel affine layer that follows it and, when res or

@@ -283,6 +283,30 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
     }
     st.stash_bytes = soff;
 
+    // Weight gradients that the backward pass leaves to its end, in groups of one launch each.  The gradient of such a layer's
+    // result then has to last that long: it gets memory of its own, unless it is the upstream gradient or the loss's.
+    std::vector<int> group;
+    auto close_group = [&]() {
+        int dims[kWgradGroupMax][2];
+        for (size_t k = 0; k < group.size(); ++k) {
+            dims[k][0] = st.layers[group[k]].d.dims[0];
+            dims[k][1] = st.layers[group[k]].d.dims[1];
+        }
+        const int64_t elems = group.empty() ? -1 : dense_wgrad_group_elems((int64_t)M * st.layers[group[0]].rps, dims, (int)group.size());
+        if (elems >= 0) {
+            ws = std::max(ws, (size_t)elems);
+            for (int i : group) st.layers[i].grouped = true;
+        }
+        group.clear();
+    };
+    for (int i = n_layers - 1; i >= 0; --i) {
+        const LayerRT& L = st.layers[i];
+        if (L.d.kind != TMPS_LINEAR || !dense_wgrad_groups(cfg->dtype, (int64_t)M * L.rps, L.d.dims[0], L.d.dims[1])) continue;
+        if (!group.empty() && (L.rps != st.layers[group[0]].rps || (int)group.size() == kWgradGroupMax)) close_group();
+        group.push_back(i);
+    }
+    close_group();
+
     // scratch: gradient buffers of M rows, two boundary-gradient buffers, fp32 workspace
     size_t o = 0;
     st.n_gbuf = any_join ? 6 : (any_skip ? 4 : 2);
@@ -300,7 +324,12 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
     st.dxout_bytes = align_up((size_t)M * st.in_elems * st.asz, 256);
     st.dxout_off[0] = o; o += st.dxout_bytes;
     st.dxout_off[1] = o; o += st.dxout_bytes;
-    st.ws_off = o; o += align_up(ws * 4, 256);
+    for (int i = 0; i < n_layers; ++i)
+        if (st.layers[i].grouped && !(i == n_layers - 1 || (cfg->is_last && i == n_layers - 2))) {
+            st.layers[i].keep_off = o;   // (not 0: the gradient buffers come first)
+            o += align_up((size_t)M * st.layers[i].out_elems * st.asz, 256);
+        }
+    st.ws_off = o; st.ws_bytes = align_up(ws * 4, 256); o += st.ws_bytes;
     st.scratch_bytes = o;
     return TMPS_OK;
 }
@@ -725,6 +754,11 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             return TMPS_OK;
         }
         T.wanted = true;
+        if (st->layers[t].keep_off) {   // memory of its own
+            T.dst = st->scratch + st->layers[t].keep_off;
+            T.add = G.set ? G.ptr : nullptr;
+            return TMPS_OK;
+        }
         if (G.set && G.buf >= 0 && refs[G.buf] == 1) {   // ours alone: add in place
             T.dst = gbuf[G.buf];
             T.add = G.ptr;
@@ -769,6 +803,15 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         return TMPS_OK;
     };
 
+    std::vector<DenseWgradJob> waiting;
+    int waiting_rows = 0;
+    auto flush_group = [&]() -> int {
+        if (waiting.empty()) return TMPS_OK;
+        TMPS_GEMM(dense_wgrad_group(dt, waiting.data(), (int)waiting.size(), waiting_rows, ws, (int64_t)(st->ws_bytes / 4), s));
+        waiting.clear();
+        return TMPS_OK;
+    };
+
     int top = nl - 1;
     if (st->cfg.is_last) {
         // the loss layer's contribution to the logits: the softmax error signal stored by the forward passes
@@ -807,7 +850,16 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             case TMPS_LINEAR: {
                 const int rows = M * L.rps;
                 if (L.skip && (rc = share(st->layers[li - L.skip].in_t, g)) != TMPS_OK) return rc;
-                TMPS_GEMM(dense_wgrad(dt, g.ptr, in, gw, rows, d[0], d[1], ws, s));
+                // (the gradient in a buffer that is about to be used again, or an operand that a user has put at an odd address: at once)
+                if (L.grouped && g.buf < 0 && ((reinterpret_cast<uintptr_t>(g.ptr) | reinterpret_cast<uintptr_t>(in)) & 15) == 0) {
+                    if (waiting_rows != rows || (int)waiting.size() == kWgradGroupMax) {
+                        if ((rc = flush_group()) != TMPS_OK) return rc;
+                    }
+                    waiting_rows = rows;
+                    waiting.push_back(DenseWgradJob{g.ptr, in, gw, d[0], d[1]});
+                } else {
+                    TMPS_GEMM(dense_wgrad(dt, g.ptr, in, gw, rows, d[0], d[1], ws, s));
+                }
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 if (T.wanted) {
                     TMPS_GEMM(dense_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
@@ -892,7 +944,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         if (L.d.kind == TMPS_RESADD && L.in_b >= 0 && remaining[L.in_b + 1] == 0 && st->layers[L.in_b].act != 0)
             return fail(TMPS_EUNSUPPORTED, "a residual connection must start at a result that another, earlier layer reads too");
     }
-    return TMPS_OK;
+    return flush_group();
     });   // (free_slots releases the group)
 }
 

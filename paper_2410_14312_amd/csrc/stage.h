@@ -24,6 +24,8 @@ struct LayerRT {
     int in_t = -1;         // which result the layer reads: index of the producing layer, -1 = the stage input
     int in_b = -1;         // residual join: the second result it reads
     bool out_f32 = false;  // the logits layer (followed by softmax-CE) writes fp32
+    bool grouped = false;  // linear: its weight gradient waits for the end of the backward pass, to be one launch with others'
+    size_t keep_off = 0;   // scratch byte offset of the gradient of its result, kept until then (0: memory that lasts anyway)
     size_t ws_elems = 0;   // fp32 workspace elements (split-k partial sums, reductions)
     size_t ws_fwd_elems = 0;  // the part of it the forward pass needs
 };
@@ -51,7 +53,7 @@ struct tmps_stage {
     size_t stash_bytes = 0, scratch_bytes = 0;
     size_t gbuf_off[8] = {0, 0, 0, 0, 0, 0, 0, 0}, gbuf_bytes = 0;  // gradient buffers (M rows each)
     size_t dxout_off[2] = {0, 0}, dxout_bytes = 0;  // boundary gradient buffers used by the scheduler
-    size_t ws_off = 0;
+    size_t ws_off = 0, ws_bytes = 0;
     size_t ws_fwd_bytes = 0;  // fp32 workspace bytes a forward pass needs (the k-split partial sums of its contractions)
     std::vector<char> slot_used;
     std::vector<const void*> slot_x;
