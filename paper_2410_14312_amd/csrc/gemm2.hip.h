@@ -756,9 +756,10 @@ template <int BM, int BN, class AOp, class BOp> constexpr int gemm2_lds_bytes() 
 // The 64 x 64 tiles are compiled for three waves per SIMD (168 registers, nothing spilled): launches of 500 to 800
 // tiles, as the 1024-row transformer GEMMs are, then have all their workgroups resident at once instead of running
 // a second, nearly empty round.
+// Workgroup (tile_x, tile_y, z) of a gx x gy x gz grid.
 template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
-__global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice,
-                                                    int col_major, int wide, FastDiv d_plane, FastDiv d_minor) {
+__device__ __forceinline__ void gemm2_tile(AOp A, BOp B, const Epi& epi, int M, int N, int K, int k_per_slice, int col_major, int wide,
+                                           const FastDiv& d_plane, const FastDiv& d_minor, int tile_x, int tile_y, int z, int gx, int gy, int gz) {
     constexpr bool AKC = AOp::kContig, BKC = BOp::kContig;
     typedef typename AOp::T T;
     constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
@@ -778,9 +779,8 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
     // from memory once instead of once per XCD.  Within a k-slice, in row-major order the tiles of a row share their
     // A panel and find it in their own L2, but every XCD fetches all of B; in column-major order (col_major, chosen
     // by the host when B is the larger operand) it is the other way round.
-    int tile_x = blockIdx.x, tile_y = blockIdx.y, z = blockIdx.z;
     {
-        const int gx = gridDim.x, gy = gridDim.y, nb = gx * gy, total = nb * gridDim.z;
+        const int nb = gx * gy, total = nb * gz;
         if (total >= 16) {
             const int lin = (z * gy + tile_y) * gx + tile_x;
             const int xcd = lin & 7, idx = lin >> 3;
@@ -1036,6 +1036,36 @@ __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_ker
             const int m = m0 + wm * (BM / 2) + i * 32 + (lane & 31);
             if (lane < 32 && m < M) epi.rowsum(m, total, z);
         }
+    }
+}
+
+template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
+__global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice,
+                                                    int col_major, int wide, FastDiv d_plane, FastDiv d_minor) {
+    gemm2_tile<BM, BN, D, ROWSUM>(A, B, epi, M, N, K, k_per_slice, col_major, wide, d_plane, d_minor, blockIdx.x, blockIdx.y, blockIdx.z,
+                                  gridDim.x, gridDim.y, gridDim.z);
+}
+
+// Input and weight gradient of a dense layer in one launch of 64 x 64 tiles, unsliced: dx[B, Din] = dy w by the first `split` workgroups, then
+// gw[Dout, Din] = dy^T x.  A batch of a few hundred rows leaves dx few tiles with a long contraction, which take the launch's
+// time whatever else runs, and the short contractions of gw fit around them: 256 x 1024 -> 1024 in bf16 is 64 and 256 workgroups, 9.6 us
+// against 10.6 in two launches, 1024 x 768 -> 768 11.8 against 17.1 (the rule, backward_kind, has the others).
+template <int D, class T>
+__global__ __launch_bounds__(256, 3) void gemm2_backward_kernel(const T* dy, const T* x, const T* w, EpiMask<T, T> ex, EpiWgrad ew, int rows,
+                                                                int Din, int Dout, int split, FastDiv d_n, FastDiv d_x, FastDiv d_w, int wide) {
+    const int b = blockIdx.x, gx = (int)d_n.d;
+    if (b < split) {
+        uint32_t by, bx;
+        d_n.divmod((uint32_t)b, by, bx);
+        const int gy = (rows + 63) >> 6;
+        gemm2_tile<64, 64, D, false>(DenseKC<T>{dy, rows, Dout, Dout}, DenseRC<T>{w, Din, Dout, Din}, ex, rows, Din, Dout, Dout, 0, wide, d_x, d_n,
+                                     (int)bx, (int)by, 0, gx, gy, 1);
+    } else {
+        uint32_t by, bx;
+        d_n.divmod((uint32_t)(b - split), by, bx);
+        const int gy = (Dout + 63) >> 6;
+        gemm2_tile<64, 64, D, true>(DenseRC<T>{dy, Dout, rows, Dout}, DenseRC<T>{x, Din, rows, Din}, ew, Dout, Din, rows, rows, 0, wide, d_w, d_n,
+                                    (int)bx, (int)by, 0, gx, gy, 1);
     }
 }
 

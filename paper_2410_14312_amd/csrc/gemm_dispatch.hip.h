@@ -231,6 +231,20 @@ static hipError_t dense_wgrad_t(int kc, const T* dy, const T* x, float* gw, int 
     return gather_dense_wgrad<T>(kc, dy, x, gw, Dout, Din, B, ws, s);
 }
 
+// Both gradients of a dense layer in one launch of the small kernel.
+enum { kTwo = 0, kOneSmall, kOneTiled };
+int backward_kind(int64_t B, int64_t Din, int64_t Dout, int esize);
+template <class T>
+static hipError_t small_backward_t(int kc, const T* dy, const T* x, const T* w, float* gw, const EpiMask<T, T>& epi, int B, int Din, int Dout, hipStream_t s) {
+    constexpr int GK = 2 * ElemTile<T>::V;
+    const int split = cdiv(Din, 32) * cdiv(B, 32), grid = split + cdiv(Din, 32) * cdiv(Dout, 32);
+    const EpiWgrad ew{gw, Din, (int64_t)Dout * Din, 0};
+    const int groups = cdiv(B > Dout ? B : Dout, GK);
+    if (groups > 32) return launch_timed(kc, gemm_small_backward_kernel<16, T>, dim3(grid), dim3(1024), 16 * 1056 * 4, s, dy, x, w, epi, ew, B, Din, Dout, split);
+    if (groups > 8) return launch_timed(kc, gemm_small_backward_kernel<8, T>, dim3(grid), dim3(512), 8 * 1056 * 4, s, dy, x, w, epi, ew, B, Din, Dout, split);
+    return launch_timed(kc, gemm_small_backward_kernel<4, T>, dim3(grid), dim3(256), 4 * 1056 * 4, s, dy, x, w, epi, ew, B, Din, Dout, split);
+}
+
 // ---- convolution passes -------------------------------------------------------------------------------
 // The chunked loaders index positions with 24-bit multiplies and tensors with 32-bit element offsets.
 static inline bool small_enough(const ConvShape& c) {
@@ -316,6 +330,7 @@ static inline bool pointwise(const ConvShape& c) {
 hipError_t dense_forward_f32(int kc, const float* x, const float* w, const EpiBiasAct<float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
 hipError_t dense_dgrad_f32(int kc, const float* dy, const float* w, const EpiMask<float, float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
 hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s);
+hipError_t small_backward_f32(int kc, const float* dy, const float* x, const float* w, float* gw, const EpiMask<float, float>& epi, int B, int Din, int Dout, hipStream_t s);
 hipError_t conv_forward_f32(const float* x, const float* w, const EpiBiasAct<float>& epi, const ConvShape& c, float* ws, hipStream_t s);
 hipError_t conv_affine_f32(const float* x, const float* w, const EpiConvAffine<float>& epi, const ConvShape& c, float* ws, hipStream_t s);
 hipError_t conv_dgrad_f32(const float* dy, const float* w, const EpiMask<float, float>& epi, const ConvShape& c, float* ws, hipStream_t s);

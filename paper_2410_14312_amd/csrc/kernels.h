@@ -45,6 +45,9 @@ hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const
 hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout,
                        float* ws, hipStream_t s);
 
+// dense_wgrad and dense_dgrad (neither's result may overlap an operand of the other), in one launch where that is quicker.
+hipError_t dense_backward(int dtype, const void* dy, const void* x, const void* w, float* gw, void* dx, const void* mask, int mask_mode,
+                          const void* add, int B, int Din, int Dout, float* ws, hipStream_t s);
 // The weight gradients of several dense layers over the same `rows` rows in one launch at the end of a backward pass.
 // dense_wgrad_groups: whether a layer's can be part of one.  dense_wgrad_group_elems: fp32 workspace elements of the launch that
 // takes these n layers (dims: Din, Dout), -1 where launches of their own are quicker.  In dense_wgrad_group, ws holds ws_elems.

@@ -544,6 +544,67 @@ hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int 
     return dense_wgrad_as(tmps::kcDenseWgrad, dtype, dy, x, gw, B, Din, Dout, ws, s);
 }
 
+// ---- both gradients of a dense layer in one launch: estimates in us ----
+// Small kernel: as long as a compute unit needs for its share of the tiles, 4000 cycles each and 14 per k in fp32, 4400 and 3.6 in bf16, or as
+// the longest tile alone, 19.5 and 9.5 per k.  Fitted on 32 to 2048 rows, widths of 64 to 1024 (one launch and two): fp32 32 x 128 -> 128
+// 4.2 and 7.5, 235 x 1000 -> 10 5.4 and 7.2, 64 x 1000 -> 1000 11.6 and 14.7, 256 x 1024 -> 1024 21.1 and 19.4; bf16 256 x 1024 -> 10
+// 4.8 and 7.5, 512 x 512 -> 512 7.2 and 8.0, 256 x 1024 -> 1024 13.3 and 10.6.
+double small_backward_us(int64_t B, int64_t Din, int64_t Dout, int esize) {
+    const int64_t n = cdiv(Din, 32), tx = n * cdiv(B, 32), tw = n * cdiv(Dout, 32);
+    const double tiles = (double)(tx + tw) / kCUs, work = ((double)tx * Dout + (double)tw * B) / kCUs, longest = (double)(Dout > B ? Dout : B);
+    const double all = esize == 4 ? tiles * 4000.0 + work * 14.0 : tiles * 4400.0 + work * 3.6;
+    const double one = esize == 4 ? 4000.0 + longest * 19.5 : 4400.0 + longest * 9.5;
+    return (2500.0 + (all > one ? all : one)) / 2400.0;
+}
+// Tiled kernel in bf16, 64 x 64 tiles: a k-tile takes 0.33 us, alone on its unit or sharing it, and the weight gradient is written at 6 TB/s
+// (one launch and two): 64 x 1024 -> 1024 9.6 and 10.6, 256 x 1024 -> 1024 9.6 and 10.7, 512 x 1024 -> 1024 10.3 and 15.6, 1024 x 768 -> 768 11.8
+// and 17.1, 256 x 2048 -> 2048 17.0 and 21.9, 256 x 1024 -> 2048 15.3 and 14.7, 512 x 2048 -> 2048 25.4 and 24.7.
+double tiled_backward_us(int64_t B, int64_t Din, int64_t Dout) {
+    const int64_t n = cdiv(Din, 64), tx = n * cdiv(B, 64), tw = n * cdiv(Dout, 64), kx = cdiv(Dout, 64), kw = cdiv(B, 64);
+    const double share = (double)(tx * kx + tw * kw) / kCUs, chain = (double)(kx > kw ? kx : kw);
+    return 3.7 + 0.335 * (share > chain ? share : chain) + (double)Din * Dout * 4.0 / 6e6;
+}
+// Two launches with 2 us between and around them; 0 where one of them is the persistent kernel's.
+double two_backward_us(int64_t B, int64_t Din, int64_t Dout, int esize) {
+    if (esize == 2 && (g3_forward_ok(B, Din, Dout) || g3_narrow_ok(B, Din, Dout) || g3_long_k_slices(B, Din, Dout) || g3_wgrad_slices(Dout, Din, B))) return 0.0;
+    auto alone = [&](int64_t M, int64_t N, int64_t K, bool rowsum) {
+        const Plan2 p = plan_for(M, N, K, rowsum, esize, kByKDense);
+        if (!small_is_better(M, N, K, esize, p)) return p.cost / 2400.0;
+        return (2500.0 + (double)cdiv((int64_t)cdiv(M, 32) * cdiv(N, 32), kCUs) * K * (esize == 4 ? 18.5 : 9.5)) / 2400.0;
+    };
+    return alone(B, Din, Dout, false) + 2.0 + alone(Dout, Din, B, true) + (double)Din * Dout * 4.0 / 6e6;
+}
+
+// What the gradients of a dense layer run on: kTwo launches, or one of the small or of the tiled kernel.
+int backward_kind(int64_t B, int64_t Din, int64_t Dout, int esize) {
+    const double two = 0.95 * two_backward_us(B, Din, Dout, esize), small = small_backward_us(B, Din, Dout, esize);
+    const double tiled = esize == 2 && Din % 8 == 0 && Dout % 8 == 0 ? tiled_backward_us(B, Din, Dout) : 1e9;
+    if (small >= two && tiled >= two) return kTwo;
+    return small <= tiled ? kOneSmall : kOneTiled;
+}
+
+hipError_t dense_backward(int dtype, const void* dy, const void* x, const void* w, float* gw, void* dx, const void* mask, int mask_mode,
+                          const void* add, int B, int Din, int Dout, float* ws, hipStream_t s) {
+    const int kind = backward_kind(B, Din, Dout, dtype == kBF16 ? 2 : 4);
+    const EpiMask<bf16_t, bf16_t> ex{(bf16_t*)dx, (const bf16_t*)mask, Din, mask_mode, (const bf16_t*)add};
+    if (kind == kOneSmall) {
+        if (dtype != kBF16)
+            return small_backward_f32(kcDenseWgrad, (const float*)dy, (const float*)x, (const float*)w, gw,
+                                      EpiMask<float, float>{(float*)dx, (const float*)mask, Din, mask_mode, (const float*)add}, B, Din, Dout, s);
+        return small_backward_t<bf16_t>(kcDenseWgrad, (const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)w, gw, ex, B, Din, Dout, s);
+    }
+    if (kind == kOneTiled && aligned16(dy) && aligned16(x) && aligned16(w)) {
+        typedef bf16_t T;
+        const EpiWgrad ew{gw, Din, (int64_t)Dout * Din, 0};
+        constexpr int lds_x = gemm2_lds_bytes<64, 64, DenseKC<T>, DenseRC<T>>(), lds_w = gemm2_lds_bytes<64, 64, DenseRC<T>, DenseRC<T>>();
+        const int n = cdiv(Din, 64), split = n * cdiv(B, 64), tw = n * cdiv(Dout, 64);
+        return launch_timed(kcDenseWgrad, gemm2_backward_kernel<4, T>, dim3(split + tw), dim3(256), lds_x > lds_w ? lds_x : lds_w, s, (const T*)dy, (const T*)x,
+                            (const T*)w, ex, ew, B, Din, Dout, split, FastDiv(n), FastDiv(split), FastDiv(tw), ex.wide_ok() && ew.wide_ok() ? 1 : 0);
+    }
+    const hipError_t e = dense_wgrad(dtype, dy, x, gw, B, Din, Dout, ws, s);
+    return e != hipSuccess ? e : dense_dgrad(dtype, dy, w, dx, mask, mask_mode, add, B, Din, Dout, ws, s);
+}
+
 // ---------------------------------------------------------------------------------- convolution
 hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y, const ConvShape& c,
                         int relu, float* ws, hipStream_t s) {

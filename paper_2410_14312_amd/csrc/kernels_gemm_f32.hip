@@ -12,6 +12,9 @@ hipError_t dense_dgrad_f32(int kc, const float* dy, const float* w, const EpiMas
 hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) {
     return dense_wgrad_t<float>(kc, dy, x, gw, B, Din, Dout, ws, s);
 }
+hipError_t small_backward_f32(int kc, const float* dy, const float* x, const float* w, float* gw, const EpiMask<float, float>& epi, int B, int Din, int Dout, hipStream_t s) {
+    return small_backward_t<float>(kc, dy, x, w, gw, epi, B, Din, Dout, s);
+}
 hipError_t conv_forward_f32(const float* x, const float* w, const EpiBiasAct<float>& epi, const ConvShape& c, float* ws, hipStream_t s) {
     if (pointwise(c)) return dense_forward_t<float>(kcConvFwd, x, w, epi, c.B * c.H * c.W, c.Cin, c.Cout, ws, s);
     return conv_forward_t<float>(x, w, epi, c, ws, s);

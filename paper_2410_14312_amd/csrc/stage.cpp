@@ -803,6 +803,14 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         return TMPS_OK;
     };
 
+    // A caller may have the gradient w.r.t. the input written over the upstream gradient or the input: then every kernel that reads
+    // those comes, as they are called, before the one that writes.
+    auto overlap = [](const void* a, size_t na, const void* b, size_t nb) {
+        const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+        return p && q && p < q + nb && q < p + na;
+    };
+    const size_t dx_bytes = (size_t)M * st->in_elems * st->asz;
+    const bool in_order = overlap(dx, dx_bytes, dy, (size_t)M * st->out_elems * st->asz) || overlap(dx, dx_bytes, x0, (size_t)M * st->in_elems * st->in_esize);
     std::vector<DenseWgradJob> waiting;
     int waiting_rows = 0;
     auto flush_group = [&]() -> int {
@@ -850,21 +858,23 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             case TMPS_LINEAR: {
                 const int rows = M * L.rps;
                 if (L.skip && (rc = share(st->layers[li - L.skip].in_t, g)) != TMPS_OK) return rc;
+                if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 // (the gradient in a buffer that is about to be used again, or an operand that a user has put at an odd address: at once)
-                if (L.grouped && g.buf < 0 && ((reinterpret_cast<uintptr_t>(g.ptr) | reinterpret_cast<uintptr_t>(in)) & 15) == 0) {
+                const bool later = L.grouped && !in_order && g.buf < 0 && ((reinterpret_cast<uintptr_t>(g.ptr) | reinterpret_cast<uintptr_t>(in)) & 15) == 0;
+                if (later) {
                     if (waiting_rows != rows || (int)waiting.size() == kWgradGroupMax) {
                         if ((rc = flush_group()) != TMPS_OK) return rc;
                     }
                     waiting_rows = rows;
                     waiting.push_back(DenseWgradJob{g.ptr, in, gw, d[0], d[1]});
+                    if (T.wanted) TMPS_GEMM(dense_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
+                } else if (T.wanted && !in_order) {
+                    TMPS_GEMM(dense_backward(dt, g.ptr, in, st->wptr(L), gw, T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
                 } else {
                     TMPS_GEMM(dense_wgrad(dt, g.ptr, in, gw, rows, d[0], d[1], ws, s));
+                    if (T.wanted) TMPS_GEMM(dense_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
                 }
-                if ((rc = target(t_in, T)) != TMPS_OK) return rc;
-                if (T.wanted) {
-                    TMPS_GEMM(dense_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
-                    commit(t_in, T);
-                }
+                if (T.wanted) commit(t_in, T);
                 break;
             }
             case TMPS_CONV2D: {

@@ -14,6 +14,7 @@ namespace tmps {
 hipError_t dense_forward(int dtype, const void* x, const void* w, const float* bias, void* y, int B, int Din, int Dout, int act, int out_f32, const void* res, void* zout, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, int mask_mode, const void* add, int B, int Din, int Dout, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) { return hipSuccess; }
+hipError_t dense_backward(int, const void*, const void*, const void*, float*, void*, const void*, int, const void*, int, int, int, float*, hipStream_t) { return hipSuccess; }
 bool dense_wgrad_groups(int, int64_t, int, int) { return true; }
 int64_t dense_wgrad_group_elems(int64_t, const int (*)[2], int n) { return n > 1 ? 1000 : -1; }
 hipError_t dense_wgrad_group(int, const DenseWgradJob*, int, int64_t, float*, int64_t, hipStream_t) { return hipSuccess; }

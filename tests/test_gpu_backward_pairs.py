@@ -1,0 +1,42 @@
+"""Input and weight gradient of a dense layer in one launch, on the small and on the tiled kernel, against the oracle: single rows and
+columns, remainders of tiles and of fragments, both halves of a launch longer than the other, masks of ReLU and GELU layers below and a
+residual connection's gradient to join; and which kernel the sizes take."""
+import ctypes as C
+
+import pytest
+
+from paper_2410_14312_amd import load_library
+from tests.test_gpu_stage import run_stage_case
+from workloads.configs import layernorm, linear
+
+TWO, SMALL, TILED = range(3)
+
+
+def kind(rows, din, dout, dtype):
+    f = getattr(load_library(), "_ZN4tmps13backward_kindEllli")
+    return f(C.c_long(rows), C.c_long(din), C.c_long(dout), 2 if dtype == "bf16" else 4)
+
+
+# rows, input, output features
+SIZES = [("f32", 2, 3, 1, SMALL), ("f32", 34, 31, 65, SMALL), ("f32", 236, 100, 10, SMALL), ("f32", 64, 512, 512, SMALL), ("f32", 512, 257, 130, SMALL),
+         ("f32", 256, 1024, 1024, TWO), ("bf16", 2, 1, 3, SMALL), ("bf16", 34, 33, 95, SMALL), ("bf16", 256, 1024, 10, SMALL), ("bf16", 130, 520, 500, SMALL),
+         ("bf16", 100, 1000, 1000, TILED), ("bf16", 512, 776, 712, TILED), ("bf16", 258, 1032, 1096, TILED), ("bf16", 40, 2048, 1024, TILED),
+         ("bf16", 1024, 712, 648, TILED), ("bf16", 2048, 1024, 1024, TWO)]
+
+
+@pytest.mark.parametrize("dtype,rows,din,dout,want", SIZES)
+def test_the_rule(dtype, rows, din, dout, want):
+    assert kind(rows, din, dout, dtype) == want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,rows,din,dout,want", [c for c in SIZES if c[-1] != TWO])
+def test_both_gradients_in_one_launch(dtype, rows, din, dout, want):
+    # (the second layer's input gradient passes the first one's ReLU; the first one's goes to the worker below)
+    run_stage_case([linear(24, din, True), linear(din, dout, False)], dtype, rows // 2, 2, seed=rows + din)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d,ffn,s", [("f32", 36, 72, 6), ("bf16", 40, 88, 5), ("bf16", 264, 712, 64)])
+def test_gelu_and_residual_connections(dtype, d, ffn, s):
+    run_stage_case([layernorm(d, s), linear(d, ffn, False, act="gelu", rows=s), linear(ffn, d, False, rows=s, skip=2)], dtype, 3, 4, seed=d)
