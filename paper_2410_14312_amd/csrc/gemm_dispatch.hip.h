@@ -33,9 +33,6 @@ Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k
 // Whether a dense contraction runs on the small kernel (gemm_small.hip.h) rather than by the given plan.
 bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& other);
 
-// out[i] = sum over slices of part[slice * count + i], in slice order
-hipError_t slice_sum(const float* part, float* out, int64_t count, int slices, hipStream_t s);
-
 // slice length (whole k-tiles) and the number of slices really launched
 static void slice_geometry(int64_t K, int want, int ktile, int& per, int& nz) {
     if (want < 1) want = 1;
@@ -148,16 +145,16 @@ static hipError_t run2(int kc, const AOp& A, const BOp& B, const Epi& epi, int M
 
 // Weight-gradient style GEMM: fp32 result [rows x cols] followed by the row sums of A (bias gradient).
 template <class AOp, class BOp>
-static hipError_t run2_wgrad(int kc, const AOp& A, const BOp& B, float* gw, int rows, int cols, int64_t K, float* ws, hipStream_t s) {
+static hipError_t run2_wgrad(int kc, const AOp& A, const BOp& B, float* gw, int rows, int cols, int64_t K, const Partials& ws, hipStream_t s) {
     typedef typename AOp::T T;
     const Plan2 p = plan_for(rows, cols, K, true, sizeof(T), by_k_mode<AOp, BOp>());
     int per, nz;
-    slice_geometry(K, ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
+    slice_geometry(K, ws.ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
     int64_t count = (int64_t)rows * cols + rows;
-    EpiWgrad epi{nz > 1 ? ws : gw, cols, (int64_t)rows * cols, count};
+    EpiWgrad epi{nz > 1 ? ws.ws : gw, cols, (int64_t)rows * cols, count};
     hipError_t e = launch2_tile<true>(kc, p, A, B, epi, rows, cols, (int)K, per, nz, s);
     if (e != hipSuccess || nz <= 1) return e;
-    return slice_sum((const float*)ws, gw, count, nz, s);
+    return ws.finish(Reduction{ws.ws, gw, count, nz, false}, s);
 }
 
 // Small kernel: as many waves as the contraction has fragment pairs for, in powers of two up to 16.
@@ -174,10 +171,10 @@ static hipError_t run_small(int kc, const AOp& A, const BOp& B, const Epi& epi, 
 // ---- element-wise gathering instances (kernels_gemm_gather.hip, both types) ------------------------------
 template <class T, class Epi> hipError_t gather_dense_kc_kc(int kc, const T* a, const T* b, const Epi& epi, int M, int N, int K, float* ws, hipStream_t s);
 template <class T> hipError_t gather_dense_dgrad(int kc, const T* dy, const T* w, const EpiMask<T, T>& epi, int M, int N, int K, float* ws, hipStream_t s);
-template <class T> hipError_t gather_dense_wgrad(int kc, const T* dy, const T* x, float* gw, int rows, int cols, int K, float* ws, hipStream_t s);
+template <class T> hipError_t gather_dense_wgrad(int kc, const T* dy, const T* x, float* gw, int rows, int cols, int K, const Partials& ws, hipStream_t s);
 template <class T, class Epi> hipError_t gather_conv_forward(const T* x, const T* w, const Epi& epi, const ConvShape& c, float* ws, hipStream_t s);
 template <class T> hipError_t gather_conv_dgrad(const T* dy, const T* w, const EpiMask<T, T>& epi, const ConvShape& c, float* ws, hipStream_t s);
-template <class T> hipError_t gather_conv_wgrad(const T* dy, const T* x, float* gw, const ConvShape& c, float* ws, hipStream_t s);
+template <class T> hipError_t gather_conv_wgrad(const T* dy, const T* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s);
 
 static inline ConvGeom2 geom2(const ConvShape& c) {
     ConvGeom2 g;
@@ -219,7 +216,7 @@ static hipError_t dense_dgrad_t(int kc, const T* dy, const T* w, const EpiMask<T
 
 // gw[m, n] = sum_k dy[k, m] * x[k, n]: both operands row-contiguous, contraction over the batch
 template <class T>
-static hipError_t dense_wgrad_t(int kc, const T* dy, const T* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) {
+static hipError_t dense_wgrad_t(int kc, const T* dy, const T* x, float* gw, int B, int Din, int Dout, const Partials& ws, hipStream_t s) {
     constexpr int V = ElemTile<T>::V;
     if (small_is_better(Dout, Din, B, sizeof(T), plan_for(Dout, Din, B, true, sizeof(T), kByKDense)))
         return run_small<true>(kc, SmallOperand<T, false>{dy, Dout, Dout}, SmallOperand<T, false>{x, Din, Din},
@@ -310,7 +307,7 @@ static hipError_t conv_dgrad_t(const T* dy, const T* w, const EpiMask<T, T>& epi
     return run2(kcConvDgrad, ConvDgradA2<T>{dy, geom2(c), M, K}, ConvDgradB2<T>{w, geom2(c), c.Cin, K}, epi, M, c.Cin, K, ws, s);
 }
 
-template <class T> static hipError_t conv_wgrad_t(const T* dy, const T* x, float* gw, const ConvShape& c, float* ws, hipStream_t s) {
+template <class T> static hipError_t conv_wgrad_t(const T* dy, const T* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) {
     const int rows = c.Cout, cols = c.R * c.S * c.Cin;
     const int64_t K = (int64_t)c.B * c.Ho * c.Wo;
     constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
@@ -329,11 +326,11 @@ static inline bool pointwise(const ConvShape& c) {
 // fp32 passes (kernels_gemm_f32.hip)
 hipError_t dense_forward_f32(int kc, const float* x, const float* w, const EpiBiasAct<float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
 hipError_t dense_dgrad_f32(int kc, const float* dy, const float* w, const EpiMask<float, float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
-hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s);
+hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, const Partials& ws, hipStream_t s);
 hipError_t small_backward_f32(int kc, const float* dy, const float* x, const float* w, float* gw, const EpiMask<float, float>& epi, int B, int Din, int Dout, hipStream_t s);
 hipError_t conv_forward_f32(const float* x, const float* w, const EpiBiasAct<float>& epi, const ConvShape& c, float* ws, hipStream_t s);
 hipError_t conv_affine_f32(const float* x, const float* w, const EpiConvAffine<float>& epi, const ConvShape& c, float* ws, hipStream_t s);
 hipError_t conv_dgrad_f32(const float* dy, const float* w, const EpiMask<float, float>& epi, const ConvShape& c, float* ws, hipStream_t s);
-hipError_t conv_wgrad_f32(const float* dy, const float* x, float* gw, const ConvShape& c, float* ws, hipStream_t s);
+hipError_t conv_wgrad_f32(const float* dy, const float* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s);
 
 }  // namespace tmps

@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace tmps {
 
 // dtype codes match TMPS_F32 / TMPS_BF16_F32MASTER
@@ -11,6 +13,32 @@ constexpr int kF32 = 0;
 constexpr int kBF16 = 1;
 
 inline size_t act_bytes(int dtype) { return dtype == kBF16 ? 2 : 4; }
+
+// Sum of partial results: out[i] = sum over z < slices of part[z * count + i], i < count: in order (k-slices of a contraction) or, where
+// many short rows are added up (slabs of a normalisation or affine layer), sixteen rows at a time.  What a backward pass adds up of its
+// parameter gradients can wait for its end and be one launch: a launcher that is given a list to put its sum on leaves it to
+// reduce_all, and its partial results stay in memory of their own until then.
+struct Reduction {
+    const float* part;
+    float* out;
+    int64_t count;
+    int slices;
+    bool rows;
+};
+typedef std::vector<Reduction> Reductions;
+hipError_t reduce_all(const Reductions& list, hipStream_t s);
+
+// Memory for partial results (may be null: then nothing is split) and, if their sum can wait, the list to put it on.
+struct Partials {
+    float* ws;
+    Reductions* later;
+    Partials(float* p, Reductions* l = nullptr) : ws(p), later(l) {}
+    hipError_t finish(const Reduction& r, hipStream_t s) const {
+        if (!later) return reduce_all(Reductions(1, r), s);
+        later->push_back(r);
+        return hipSuccess;
+    }
+};
 
 struct ConvShape {
     int B, H, W, Cin, Ho, Wo, Cout, R, S, stride, pad;
@@ -43,11 +71,11 @@ hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const
 // gradient that other readers of the same input have already contributed.
 // gw[Dout, Din] = dy^T x and gb[Dout] = column sums of dy, with gb stored right after gw.
 hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout,
-                       float* ws, hipStream_t s);
+                       const Partials& ws, hipStream_t s);
 
 // dense_wgrad and dense_dgrad (neither's result may overlap an operand of the other), in one launch where that is quicker.
 hipError_t dense_backward(int dtype, const void* dy, const void* x, const void* w, float* gw, void* dx, const void* mask, int mask_mode,
-                          const void* add, int B, int Din, int Dout, float* ws, hipStream_t s);
+                          const void* add, int B, int Din, int Dout, float* ws, const Partials& ws_w, hipStream_t s);
 // The weight gradients of several dense layers over the same `rows` rows in one launch at the end of a backward pass.
 // dense_wgrad_groups: whether a layer's can be part of one.  dense_wgrad_group_elems: fp32 workspace elements of the launch that
 // takes these n layers (dims: Din, Dout), -1 where launches of their own are quicker.  In dense_wgrad_group, ws holds ws_elems.
@@ -73,7 +101,7 @@ hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const fl
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add,
                       const ConvShape& c, float* ws, hipStream_t s);
 hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c,
-                      float* ws, hipStream_t s);
+                      const Partials& ws, hipStream_t s);
 
 // 2-D max pooling, channels-last, no padding.  Backward recomputes the winner (first maximum in
 // row-major window order) from the stored input; relu_mask: also zero where the input is <= 0.
@@ -88,7 +116,7 @@ hipError_t affine_forward(int dtype, const void* x, const float* gain, const flo
 // dx (may be null) = gain * dy; dgain_dshift: C gain gradients (sum of dy * x) followed by C shift gradients (sum
 // of dy); dy has already passed through the layer's own ReLU; ws: affine_workspace_elems.
 hipError_t affine_backward(int dtype, const void* dy, const void* x, const float* gain, void* dx, float* dgain_dshift,
-                           float* ws, int64_t rows, int C, hipStream_t s);
+                           const Partials& ws, int64_t rows, int C, hipStream_t s);
 size_t affine_workspace_elems(int64_t rows, int C);
 
 // y = act(a + b), n elements.
@@ -105,7 +133,7 @@ hipError_t layernorm_forward(int dtype, const void* x, const float* gamma, const
 // dx (may be null) = gradient w.r.t. x, plus `add` (may be null: gradient of a residual connection that
 // joins x); dgamma_dbeta: D gain gradients followed by D shift gradients; ws: layernorm_workspace_elems.
 hipError_t layernorm_backward(int dtype, const void* dy, const void* x, const float* stats, const float* gamma,
-                              const void* add, void* dx, float* dgamma_dbeta, float* ws, int64_t rows, int D,
+                              const void* add, void* dx, float* dgamma_dbeta, const Partials& ws, int64_t rows, int D,
                               hipStream_t s);
 size_t layernorm_workspace_elems(int64_t rows, int D);
 

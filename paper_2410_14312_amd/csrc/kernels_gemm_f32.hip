@@ -9,7 +9,7 @@ hipError_t dense_forward_f32(int kc, const float* x, const float* w, const EpiBi
 hipError_t dense_dgrad_f32(int kc, const float* dy, const float* w, const EpiMask<float, float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s) {
     return dense_dgrad_t<float>(kc, dy, w, epi, B, Din, Dout, ws, s);
 }
-hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) {
+hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, const Partials& ws, hipStream_t s) {
     return dense_wgrad_t<float>(kc, dy, x, gw, B, Din, Dout, ws, s);
 }
 hipError_t small_backward_f32(int kc, const float* dy, const float* x, const float* w, float* gw, const EpiMask<float, float>& epi, int B, int Din, int Dout, hipStream_t s) {
@@ -29,7 +29,7 @@ hipError_t conv_dgrad_f32(const float* dy, const float* w, const EpiMask<float, 
     if (pointwise(c)) return dense_dgrad_t<float>(kcConvDgrad, dy, w, epi, c.B * c.H * c.W, c.Cin, c.Cout, ws, s);
     return conv_dgrad_t<float>(dy, w, epi, c, ws, s);
 }
-hipError_t conv_wgrad_f32(const float* dy, const float* x, float* gw, const ConvShape& c, float* ws, hipStream_t s) {
+hipError_t conv_wgrad_f32(const float* dy, const float* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) {
     if (pointwise(c)) return dense_wgrad_t<float>(kcConvWgrad, dy, x, gw, c.B * c.H * c.W, c.Cin, c.Cout, ws, s);
     return conv_wgrad_t<float>(dy, x, gw, c, ws, s);
 }

@@ -124,41 +124,6 @@ __global__ __launch_bounds__(256) void affine_bwd_bf16x8_kernel(const bf16_t* __
     }
 }
 
-// out[i] = sum over the slabs of part[slab][i]: 64 outputs per workgroup, sixteen lanes of slabs each, combined through LDS
-__global__ __launch_bounds__(1024) void affine_slab_sum_kernel(const float* __restrict__ part, float* __restrict__ out, int count,
-                                                               int slabs) {
-    __shared__ float sp[16][64];
-    const int cl = threadIdx.x & 63, sl = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + cl;
-    float a = 0.0f;
-    if (i < count) {
-        // eight loads in flight per lane, added in slab order
-        const float* p = part + (int64_t)sl * count + i;
-        const int64_t step = (int64_t)16 * count;
-        int z = sl;
-        for (; z + 7 * 16 < slabs; z += 8 * 16) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = p[u * step];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a += v[u];
-            p += 8 * step;
-        }
-        for (; z < slabs; z += 16) {
-            a += *p;
-            p += step;
-        }
-    }
-    sp[sl][cl] = a;
-    __syncthreads();
-    if (sl == 0 && i < count) {
-        float t = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) t += sp[k][cl];
-        out[i] = t;
-    }
-}
-
 static int affine_slab_rows(int64_t rows) {
     // a few thousand workgroups at most, 64 rows at least (swept 32..1024 on the ResNet-50 workload)
     int64_t r = (rows + 2047) / 2048;
@@ -190,7 +155,8 @@ hipError_t affine_forward(int dtype, const void* x, const float* gain, const flo
 }
 
 hipError_t affine_backward(int dtype, const void* dy, const void* x, const float* gain, void* dx, float* dgain_dshift,
-                           float* ws, int64_t rows, int C, hipStream_t s) {
+                           const Partials& partials, int64_t rows, int C, hipStream_t s) {
+    float* const ws = partials.ws;
     if (rows <= 0 || C <= 0) return hipSuccess;
     const int slab = affine_slab_rows(rows);
     const int slabs = cdiv_res(rows, slab);
@@ -206,8 +172,7 @@ hipError_t affine_backward(int dtype, const void* dy, const void* x, const float
         e = launch_timed(kcAffine, affine_bwd_kernel<float>, grid, dim3(256), 0, s, (const float*)dy, (const float*)x, gain,
                          (float*)dx, ws, rows, C, slab);
     if (e != hipSuccess) return e;
-    return launch_timed(kcAffine, affine_slab_sum_kernel, dim3(cdiv_res(2 * C, 64)), dim3(1024), 0, s, (const float*)ws,
-                        dgain_dshift, 2 * C, slabs);
+    return partials.finish(Reduction{ws, dgain_dshift, 2 * C, slabs, true}, s);
 }
 
 // ---------------------------------------------------------------------------------- residual join

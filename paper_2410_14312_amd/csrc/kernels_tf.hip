@@ -243,41 +243,6 @@ __global__ __launch_bounds__(256) void layernorm_bwd_fused_bf16x8_kernel(const b
     }
 }
 
-// out[i] = sum over the slabs of part[slab][i]: 64 outputs per workgroup, sixteen lanes of slabs each, combined through LDS
-__global__ __launch_bounds__(1024) void slab_sum_kernel(const float* __restrict__ part, float* __restrict__ out, int count,
-                                                        int slabs) {
-    __shared__ float sp[16][64];
-    const int cl = threadIdx.x & 63, sl = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + cl;
-    float a = 0.0f;
-    if (i < count) {
-        // eight loads in flight per lane, added in slab order
-        const float* p = part + (int64_t)sl * count + i;
-        const int64_t step = (int64_t)16 * count;
-        int z = sl;
-        for (; z + 7 * 16 < slabs; z += 8 * 16) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = p[u * step];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a += v[u];
-            p += 8 * step;
-        }
-        for (; z < slabs; z += 16) {
-            a += *p;
-            p += step;
-        }
-    }
-    sp[sl][cl] = a;
-    __syncthreads();
-    if (sl == 0 && i < count) {
-        float t = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) t += sp[k][cl];
-        out[i] = t;
-    }
-}
-
 // Rows per wave of the fused backward kernel: its workgroups are to cover the device (1024 rows in slabs of 16 are 64 of them:
 // both passes of 1024 x 768 18.2 us, in slabs of 4 12.6 us), and every slab costs a row of partial sums.
 static int ln_rows_per_wave(int64_t rows) { return rows >= 4096 ? 4 : rows >= 2048 ? 2 : 1; }
@@ -306,8 +271,9 @@ hipError_t layernorm_forward(int dtype, const void* x, const float* gamma, const
 }
 
 hipError_t layernorm_backward(int dtype, const void* dy, const void* x, const float* stats, const float* gamma,
-                              const void* add, void* dx, float* dgamma_dbeta, float* ws, int64_t rows, int D,
+                              const void* add, void* dx, float* dgamma_dbeta, const Partials& partials, int64_t rows, int D,
                               hipStream_t s) {
+    float* const ws = partials.ws;
     if (rows <= 0) return hipSuccess;
     hipError_t e;
     if (dtype == kBF16 && D % 8 == 0 && D <= 1024 &&
@@ -318,8 +284,7 @@ hipError_t layernorm_backward(int dtype, const void* dy, const void* x, const fl
         e = launch_timed(kcLayerNorm, kern, dim3(slabs), dim3(256), 0, s, (const bf16_t*)dy, (const bf16_t*)x, stats, gamma, (const bf16_t*)add,
                          (bf16_t*)dx, ws, rows, D);
         if (e != hipSuccess) return e;
-        return launch_timed(kcLayerNorm, slab_sum_kernel, dim3(cdiv_tf(2 * D, 64)), dim3(1024), 0, s, (const float*)ws,
-                            dgamma_dbeta, 2 * D, slabs);
+        return partials.finish(Reduction{ws, dgamma_dbeta, 2 * D, slabs, true}, s);
     }
     const int slab = ln_slab_rows(rows);
     const int slabs = cdiv_tf(rows, slab);
@@ -342,8 +307,7 @@ hipError_t layernorm_backward(int dtype, const void* dy, const void* x, const fl
                          stats, ws, rows, D, slab);
     }
     if (e != hipSuccess) return e;
-    return launch_timed(kcLayerNorm, slab_sum_kernel, dim3(cdiv_tf(2 * D, 64)), dim3(1024), 0, s, (const float*)ws,
-                        dgamma_dbeta, 2 * D, slabs);
+    return partials.finish(Reduction{ws, dgamma_dbeta, 2 * D, slabs, true}, s);
 }
 
 // ----------------------------------------------------------------------------------------- embedding

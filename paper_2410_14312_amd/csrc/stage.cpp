@@ -45,6 +45,9 @@ int fail(int code, const char* fmt, ...) {
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Partial results of one layer's parameter gradient that may wait for the end of the backward pass.
+static constexpr size_t kLatePartBytes = size_t(16) << 20;
+
 static ConvShape conv_shape(const tmps_layer_desc& d, int B) {
     ConvShape c;
     c.B = B; c.H = d.dims[0]; c.W = d.dims[1]; c.Cin = d.dims[2]; c.Cout = d.dims[3];
@@ -122,7 +125,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 const int64_t rf = (int64_t)mb * L.rps, rb = (int64_t)M * L.rps;
                 L.ws_fwd_elems = gemm_workspace_elems(rf, d[1], d[0], f32);
                 L.ws_elems = std::max({L.ws_fwd_elems, gemm_workspace_elems(rb, d[0], d[1], f32),
-                                       gemm_workspace_elems(d[1], d[0], rb, kWsRowSums | f32)});
+                                       L.part_elems = gemm_workspace_elems(d[1], d[0], rb, kWsRowSums | f32)});
                 for (int r = 2; r <= cfg->n_micro; ++r)   // (micro-batches forwarded together)
                     L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems(r * rf, d[1], d[0], f32));
                 break;
@@ -142,7 +145,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 L.ws_fwd_elems = gemm_workspace_elems((int64_t)mb * c.Ho * c.Wo, c.Cout, kf, f32);
                 L.ws_elems = std::max({L.ws_fwd_elems,
                                        gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin, kd, f32),
-                                       gemm_workspace_elems(c.Cout, kf, (int64_t)M * c.Ho * c.Wo, kWsRowSums | f32)});
+                                       L.part_elems = gemm_workspace_elems(c.Cout, kf, (int64_t)M * c.Ho * c.Wo, kWsRowSums | f32)});
                 if (c.stride == 2)   // (the input gradient may walk each position's own taps only)
                     L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin,
                                                                            (int64_t)((c.R + 1) / 2) * ((c.S + 1) / 2) * c.Cout, f32));
@@ -167,7 +170,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                     return fail(TMPS_EUNSUPPORTED, "layer %d: an affine layer must follow a layer without activation", i);
                 L.in_elems = L.out_elems = (int64_t)d[0] * d[1] * d[2];
                 L.w_count = d[2]; L.b_count = d[2];
-                L.ws_elems = affine_workspace_elems((int64_t)M * d[0] * d[1], d[2]);
+                L.ws_elems = L.part_elems = affine_workspace_elems((int64_t)M * d[0] * d[1], d[2]);
                 break;
             case TMPS_RESADD:
                 if (d[0] < 1 || d[1] < 1 || d[2] < 1 || d[3] < 1) return fail(TMPS_EINVAL, "layer %d: bad residual join", i);
@@ -191,7 +194,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 L.in_elems = L.out_elems = (int64_t)L.rps * d[0];
                 L.w_count = d[0]; L.b_count = d[0];
                 L.relu = false; L.act = 0;
-                L.ws_elems = layernorm_workspace_elems((int64_t)M * L.rps, d[0]);
+                L.ws_elems = L.part_elems = layernorm_workspace_elems((int64_t)M * L.rps, d[0]);
                 break;
             case TMPS_ATTENTION:
                 if (d[0] < 1 || d[1] < 1 || d[2] < 1 || d[1] % d[2] != 0)
@@ -329,6 +332,13 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
             st.layers[i].keep_off = o;   // (not 0: the gradient buffers come first)
             o += align_up((size_t)M * st.layers[i].out_elems * st.asz, 256);
         }
+    // (larger ones had better be added up while the caches hold them)
+    for (LayerRT& L : st.layers) {
+        if (L.grouped || L.part_elems * 4 > kLatePartBytes) L.part_elems = 0;
+        if (!L.part_elems) continue;
+        L.part_off = o;
+        o += align_up(L.part_elems * 4, 256);
+    }
     st.ws_off = o; st.ws_bytes = align_up(ws * 4, 256); o += st.ws_bytes;
     st.scratch_bytes = o;
     return TMPS_OK;
@@ -811,6 +821,10 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
     };
     const size_t dx_bytes = (size_t)M * st->in_elems * st->asz;
     const bool in_order = overlap(dx, dx_bytes, dy, (size_t)M * st->out_elems * st->asz) || overlap(dx, dx_bytes, x0, (size_t)M * st->in_elems * st->in_esize);
+    Reductions sums;   // left to the end of the pass
+    auto partials = [&](const LayerRT& L) {
+        return L.part_elems ? Partials(reinterpret_cast<float*>(st->scratch + L.part_off), &sums) : Partials(ws);
+    };
     std::vector<DenseWgradJob> waiting;
     int waiting_rows = 0;
     auto flush_group = [&]() -> int {
@@ -869,9 +883,9 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                     waiting.push_back(DenseWgradJob{g.ptr, in, gw, d[0], d[1]});
                     if (T.wanted) TMPS_GEMM(dense_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
                 } else if (T.wanted && !in_order) {
-                    TMPS_GEMM(dense_backward(dt, g.ptr, in, st->wptr(L), gw, T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
+                    TMPS_GEMM(dense_backward(dt, g.ptr, in, st->wptr(L), gw, T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, partials(L), s));
                 } else {
-                    TMPS_GEMM(dense_wgrad(dt, g.ptr, in, gw, rows, d[0], d[1], ws, s));
+                    TMPS_GEMM(dense_wgrad(dt, g.ptr, in, gw, rows, d[0], d[1], partials(L), s));
                     if (T.wanted) TMPS_GEMM(dense_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, mask_mode, T.add, rows, d[0], d[1], ws, s));
                 }
                 if (T.wanted) commit(t_in, T);
@@ -879,7 +893,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             }
             case TMPS_CONV2D: {
                 ConvShape c = conv_shape(L.d, M);
-                TMPS_GEMM(conv_wgrad(dt, g.ptr, in, gw, c, ws, s));
+                TMPS_GEMM(conv_wgrad(dt, g.ptr, in, gw, c, partials(L), s));
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 if (T.wanted) {
                     if (mask_mode == 2) return fail(TMPS_EUNSUPPORTED, "a convolution directly after a GELU layer");
@@ -908,7 +922,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                 // the layer before has no activation (checked at creation): nothing to pass through
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 if (T.add) return fail(TMPS_EUNSUPPORTED, "an affine layer on a shared input");
-                TMPS_GEMM(affine_backward(dt, g.ptr, in, st->master + L.w_off, T.wanted ? T.dst : nullptr, gw, ws,
+                TMPS_GEMM(affine_backward(dt, g.ptr, in, st->master + L.w_off, T.wanted ? T.dst : nullptr, gw, partials(L),
                                           (int64_t)M * d[0] * d[1], d[2], s));
                 if (T.wanted) commit(t_in, T);
                 break;
@@ -921,7 +935,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                 if (mask) return fail(TMPS_EUNSUPPORTED, "layer normalisation directly after an activation");
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 TMPS_GEMM(layernorm_backward(dt, g.ptr, in, reinterpret_cast<const float*>(st->stash + L.aux_off) + (size_t)row0 * L.rps * 2,
-                                             st->master + L.w_off, T.add, T.wanted ? T.dst : nullptr, gw, ws, (int64_t)M * L.rps,
+                                             st->master + L.w_off, T.add, T.wanted ? T.dst : nullptr, gw, partials(L), (int64_t)M * L.rps,
                                              d[0], s));
                 if (T.wanted) commit(t_in, T);
                 break;
@@ -954,7 +968,10 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         if (L.d.kind == TMPS_RESADD && L.in_b >= 0 && remaining[L.in_b + 1] == 0 && st->layers[L.in_b].act != 0)
             return fail(TMPS_EUNSUPPORTED, "a residual connection must start at a result that another, earlier layer reads too");
     }
-    return flush_group();
+    int rc = flush_group();
+    if (rc != TMPS_OK) return rc;
+    TMPS_GEMM(reduce_all(sums, s));
+    return TMPS_OK;
     });   // (free_slots releases the group)
 }
 

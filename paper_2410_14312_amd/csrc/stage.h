@@ -26,6 +26,8 @@ struct LayerRT {
     bool out_f32 = false;  // the logits layer (followed by softmax-CE) writes fp32
     bool grouped = false;  // linear: its weight gradient waits for the end of the backward pass, to be one launch with others'
     size_t keep_off = 0;   // scratch byte offset of the gradient of its result, kept until then (0: memory that lasts anyway)
+    size_t part_off = 0;   // scratch byte offset of partial results of its parameter gradient that are added up at the end of the
+    size_t part_elems = 0; // backward pass, and how many fp32 elements (0: none, or so many that they are added up at once)
     size_t ws_elems = 0;   // fp32 workspace elements (split-k partial sums, reductions)
     size_t ws_fwd_elems = 0;  // the part of it the forward pass needs
 };

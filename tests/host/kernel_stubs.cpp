@@ -13,8 +13,9 @@ KernelStubs kernel_stubs;
 namespace tmps {
 hipError_t dense_forward(int dtype, const void* x, const void* w, const float* bias, void* y, int B, int Din, int Dout, int act, int out_f32, const void* res, void* zout, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, int mask_mode, const void* add, int B, int Din, int Dout, float* ws, hipStream_t s) { return hipSuccess; }
-hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout, float* ws, hipStream_t s) { return hipSuccess; }
-hipError_t dense_backward(int, const void*, const void*, const void*, float*, void*, const void*, int, const void*, int, int, int, float*, hipStream_t) { return hipSuccess; }
+hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout, const Partials& ws, hipStream_t s) { return hipSuccess; }
+hipError_t reduce_all(const Reductions&, hipStream_t) { return hipSuccess; }
+hipError_t dense_backward(int, const void*, const void*, const void*, float*, void*, const void*, int, const void*, int, int, int, float*, const Partials&, hipStream_t) { return hipSuccess; }
 bool dense_wgrad_groups(int, int64_t, int, int) { return true; }
 int64_t dense_wgrad_group_elems(int64_t, const int (*)[2], int n) { return n > 1 ? 1000 : -1; }
 hipError_t dense_wgrad_group(int, const DenseWgradJob*, int, int64_t, float*, int64_t, hipStream_t) { return hipSuccess; }
@@ -25,16 +26,16 @@ hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bi
 }
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain, const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
-hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
+hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) { return hipSuccess; }
 hipError_t maxpool_forward(int dtype, const void* x, void* y, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) { return hipSuccess; }
 hipError_t maxpool_backward(int dtype, const void* x, const void* dy, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) { return hipSuccess; }
 hipError_t affine_forward(int dtype, const void* x, const float* gain, const float* shift, void* y, int64_t rows, int C, int relu, hipStream_t s) { return hipSuccess; }
-hipError_t affine_backward(int dtype, const void* dy, const void* x, const float* gain, void* dx, float* dgain_dshift, float* ws, int64_t rows, int C, hipStream_t s) { return hipSuccess; }
+hipError_t affine_backward(int dtype, const void* dy, const void* x, const float* gain, void* dx, float* dgain_dshift, const Partials& ws, int64_t rows, int C, hipStream_t s) { return hipSuccess; }
 hipError_t resadd_forward(int dtype, const void* a, const void* b, void* y, int64_t n, int relu, hipStream_t s) { return hipSuccess; }
 hipError_t avgpool_forward(int dtype, const void* x, void* y, int B, int HW, int C, hipStream_t s) { return hipSuccess; }
 hipError_t avgpool_backward(int dtype, const void* dy, const void* x, void* dx, int B, int HW, int C, int relu_mask, hipStream_t s) { return hipSuccess; }
 hipError_t layernorm_forward(int dtype, const void* x, const float* gamma, const float* beta, void* y, float* stats, int64_t rows, int D, float eps, hipStream_t s) { return hipSuccess; }
-hipError_t layernorm_backward(int dtype, const void* dy, const void* x, const float* stats, const float* gamma, const void* add, void* dx, float* dgamma_dbeta, float* ws, int64_t rows, int D, hipStream_t s) { return hipSuccess; }
+hipError_t layernorm_backward(int dtype, const void* dy, const void* x, const float* stats, const float* gamma, const void* add, void* dx, float* dgamma_dbeta, const Partials& ws, int64_t rows, int D, hipStream_t s) { return hipSuccess; }
 hipError_t attention_forward(int dtype, const void* qkv, void* o, float* lse, int B, int S, int D, int H, hipStream_t s) { return hipSuccess; }
 hipError_t attention_backward(int dtype, const void* qkv, const void* o, const void* dout, const float* lse, float* delta, void* dqkv, int B, int S, int D, int H, hipStream_t s) { return hipSuccess; }
 hipError_t embedding_forward(int dtype, const int32_t* tok, const void* wte, const void* wpe, void* y, int64_t rows, int S, int D, int vocab, hipStream_t s) { return hipSuccess; }

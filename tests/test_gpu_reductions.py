@@ -1,0 +1,62 @@
+"""Sums of partial results in one launch, any number and mix of them: outputs in 16-byte pieces and ragged ones, few slices and many rows,
+more sums than a launch takes.  Each is a sum of fp32 values in a fixed order: against fp64, the error of n additions, n 2^-24 relative to the sum of
+the absolute values; and a sum among others equals the same sum alone bit for bit."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+class _Reduction(C.Structure):
+    _fields_ = [("part", C.c_void_p), ("out", C.c_void_p), ("count", C.c_int64), ("slices", C.c_int), ("rows", C.c_bool)]
+
+
+class _Vector(C.Structure):   # a std::vector's begin, end and end of storage
+    _fields_ = [(n, C.c_void_p) for n in ("begin", "end", "cap")]
+
+
+def reduce_all(jobs):
+    import torch
+    from paper_2410_14312_amd import load_library
+
+    a = (_Reduction * max(1, len(jobs)))(*jobs)
+    at = C.addressof(a)
+    end = at + C.sizeof(_Reduction) * len(jobs)
+    f = getattr(load_library(), "_ZN4tmps10reduce_allERKSt6vectorINS_9ReductionESaIS1_EEP12ihipStream_t")
+    assert f(C.byref(_Vector(at, end, end)), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+
+
+SHAPES = [(1, 1), (3, 2), (4, 7), (1023, 8), (1024, 9), (1028, 64), (4100, 17), (255, 16), (16, 1), (128, 2048), (66, 33), (512, 143), (2, 127), (18, 128)]
+
+
+@pytest.mark.parametrize("n", [0, 1, 14, 64, 65, 130])
+def test_sums(n):
+    import torch
+
+    rng = np.random.default_rng(n)
+    jobs, keep = [], []
+    for k in range(n):
+        count, slices = SHAPES[(k * 5 + n) % len(SHAPES)]
+        odd = k % 3 == 1                     # not 16-byte aligned
+        host = rng.standard_normal((slices, count)).astype(np.float32)
+        part = torch.zeros(slices * count + 1, device="cuda:0")
+        part[odd:odd + slices * count] = torch.from_numpy(host.reshape(-1)).to("cuda:0")
+        out = torch.full((count + 2,), 7.0, device="cuda:0")
+        rows = k % 2 == 0
+        jobs.append(_Reduction(part.data_ptr() + 4 * odd, out.data_ptr() + 4 * odd, count, slices, rows))
+        keep.append((part, out, host, odd))
+    reduce_all(jobs)
+    for part, out, host, odd in keep:
+        got = out.cpu().numpy()
+        count = host.shape[1]
+        assert np.all(got[:odd] == 7.0) and np.all(got[odd + count:] == 7.0)
+        want, size = host.sum(0, dtype=np.float64), np.abs(host).sum(0, dtype=np.float64)
+        assert np.all(np.abs(got[odd:odd + count] - want) <= host.shape[0] * 2.0 ** -24 * size)
+    for k in range(0, n, 13):
+        before = keep[k][1].clone()
+        keep[k][1].fill_(7.0)
+        reduce_all([jobs[k]])
+        assert torch.equal(before, keep[k][1])
