@@ -30,7 +30,13 @@ constexpr int kCUs = 256;   // compute units of the device the rules below are w
 // or with an operand that a convolution's loader addresses.  esize: bytes of an operand element.
 enum { kByKNo = 0, kByKDense, kByKConv };
 Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k);
-// Whether a dense contraction runs on the small kernel (gemm_small.hip.h) rather than by the given plan.
+// Tiles (16 tm x 16 tn) of the small kernel (gemm_small.hip.h) for a contraction and its estimated cycles; whether a dense contraction
+// runs on it rather than by the given plan.
+struct SmallPlan {
+    int tm, tn;
+    double cost;
+};
+SmallPlan small_plan(int64_t M, int64_t N, int64_t K, int esize);
 bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& other);
 
 // slice length (whole k-tiles) and the number of slices really launched
@@ -157,15 +163,24 @@ static hipError_t run2_wgrad(int kc, const AOp& A, const BOp& B, float* gw, int 
     return ws.finish(Reduction{ws.ws, gw, count, nz, false}, s);
 }
 
-// Small kernel: as many waves as the contraction has fragment pairs for, in powers of two up to 16.
+// Small kernel: eight waves; four for a contraction of at most four steps and for 32 x 32 outputs in fp32 (256 x 1024 x 1024 10.3 us against 10.9).
+template <int NW, int TM, int TN, bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t small_inst(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, hipStream_t s) {
+    return launch_timed(kc, gemm_small_kernel<NW, TM, TN, ROWSUM, AOp, BOp, Epi>, dim3(cdiv(N, 16 * TN), cdiv(M, 16 * TM)), dim3(64 * NW),
+                        small_lds_floats(NW, TM, TN) * 4, s, A, B, epi, M, N, K);
+}
 template <bool ROWSUM, class AOp, class BOp, class Epi>
 static hipError_t run_small(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, hipStream_t s) {
-    constexpr int GK = 2 * ElemTile<typename AOp::T>::V;
-    const dim3 grid(cdiv(N, 32), cdiv(M, 32));
-    const int groups = cdiv(K, GK);
-    if (groups > 32) return launch_timed(kc, gemm_small_kernel<16, ROWSUM, AOp, BOp, Epi>, grid, dim3(1024), 16 * 1056 * 4, s, A, B, epi, M, N, K);
-    if (groups > 8) return launch_timed(kc, gemm_small_kernel<8, ROWSUM, AOp, BOp, Epi>, grid, dim3(512), 8 * 1056 * 4, s, A, B, epi, M, N, K);
-    return launch_timed(kc, gemm_small_kernel<4, ROWSUM, AOp, BOp, Epi>, grid, dim3(256), 4 * 1056 * 4, s, A, B, epi, M, N, K);
+    const SmallPlan p = small_plan(M, N, K, sizeof(typename AOp::T));
+    constexpr int esize = sizeof(typename AOp::T);
+    if (p.tm == 2 && (esize == 4 || K <= 4 * (64 / esize))) return small_inst<4, 2, 2, ROWSUM>(kc, A, B, epi, M, N, K, s);
+    if (K <= 4 * (64 / esize)) {
+        if (p.tn == 2) return small_inst<4, 1, 2, ROWSUM>(kc, A, B, epi, M, N, K, s);
+        return small_inst<4, 1, 1, ROWSUM>(kc, A, B, epi, M, N, K, s);
+    }
+    if (p.tm == 2) return small_inst<8, 2, 2, ROWSUM>(kc, A, B, epi, M, N, K, s);
+    if (p.tn == 2) return small_inst<8, 1, 2, ROWSUM>(kc, A, B, epi, M, N, K, s);
+    return small_inst<8, 1, 1, ROWSUM>(kc, A, B, epi, M, N, K, s);
 }
 
 // ---- element-wise gathering instances (kernels_gemm_gather.hip, both types) ------------------------------
@@ -231,15 +246,21 @@ static hipError_t dense_wgrad_t(int kc, const T* dy, const T* x, float* gw, int 
 // Both gradients of a dense layer in one launch of the small kernel.
 enum { kTwo = 0, kOneSmall, kOneTiled };
 int backward_kind(int64_t B, int64_t Din, int64_t Dout, int esize);
+int small_backward_tile(int64_t M, int64_t N, int esize);   // 1 or 2: tiles of 16 x 16 or 32 x 32 outputs
+template <int TX, int TW, class T>
+static hipError_t small_backward_inst(int kc, const T* dy, const T* x, const T* w, float* gw, const EpiMask<T, T>& epi, int B, int Din, int Dout, hipStream_t s) {
+    const int split = cdiv(Din, 16 * TX) * cdiv(B, 16 * TX), grid = split + cdiv(Din, 16 * TW) * cdiv(Dout, 16 * TW);
+    constexpr int lx = small_lds_floats(4, TX, TX), lw = small_lds_floats(4, TW, TW);
+    return launch_timed(kc, gemm_small_backward_kernel<4, TX, TW, T>, dim3(grid), dim3(256), (lx > lw ? lx : lw) * 4, s, dy, x, w, epi,
+                        EpiWgrad{gw, Din, (int64_t)Dout * Din, 0}, B, Din, Dout, split);
+}
 template <class T>
 static hipError_t small_backward_t(int kc, const T* dy, const T* x, const T* w, float* gw, const EpiMask<T, T>& epi, int B, int Din, int Dout, hipStream_t s) {
-    constexpr int GK = 2 * ElemTile<T>::V;
-    const int split = cdiv(Din, 32) * cdiv(B, 32), grid = split + cdiv(Din, 32) * cdiv(Dout, 32);
-    const EpiWgrad ew{gw, Din, (int64_t)Dout * Din, 0};
-    const int groups = cdiv(B > Dout ? B : Dout, GK);
-    if (groups > 32) return launch_timed(kc, gemm_small_backward_kernel<16, T>, dim3(grid), dim3(1024), 16 * 1056 * 4, s, dy, x, w, epi, ew, B, Din, Dout, split);
-    if (groups > 8) return launch_timed(kc, gemm_small_backward_kernel<8, T>, dim3(grid), dim3(512), 8 * 1056 * 4, s, dy, x, w, epi, ew, B, Din, Dout, split);
-    return launch_timed(kc, gemm_small_backward_kernel<4, T>, dim3(grid), dim3(256), 4 * 1056 * 4, s, dy, x, w, epi, ew, B, Din, Dout, split);
+    const int tx = small_backward_tile(B, Din, sizeof(T)), tw = small_backward_tile(Dout, Din, sizeof(T));
+    if (tx == 2 && tw == 2) return small_backward_inst<2, 2>(kc, dy, x, w, gw, epi, B, Din, Dout, s);
+    if (tx == 2) return small_backward_inst<2, 1>(kc, dy, x, w, gw, epi, B, Din, Dout, s);
+    if (tw == 2) return small_backward_inst<1, 2>(kc, dy, x, w, gw, epi, B, Din, Dout, s);
+    return small_backward_inst<1, 1>(kc, dy, x, w, gw, epi, B, Din, Dout, s);
 }
 
 // ---- convolution passes -------------------------------------------------------------------------------

@@ -1,13 +1,15 @@
-// Dense contractions of few output tiles, bound by latency: C[m, n] = sum_k A(m, k) * B(n, k).
+// Dense contractions of few outputs, bound by latency: C[m, n] = sum_k A(m, k) * B(n, k).
 //
-// A workgroup owns a 32 x 32 tile of C and its NW waves share the k range, each with fragments fetched straight from
-// global memory into registers (no LDS tile, no barrier in the k-loop; the loads of the next D fragment pairs are in
+// A workgroup owns 16 TM x 16 TN outputs and its NW waves share the k range, each with fragments fetched straight from
+// global memory into registers (no LDS tile, no barrier in the k-loop; the loads of the next D steps are in
 // flight), so that a short contraction costs about one memory latency and a long one is walked
 // NW times as fast; the partial tiles are added through LDS in the order of the waves and the epilogue follows in the
 // same launch.  The tiled kernel needs k-slices and a second launch for such shapes, or walks the whole k range in one
-// workgroup: 47 x 1000 x 1000 in fp32 took 132 us there with a k-loop on the vector units.
-// A 32 x 32 tile reads 64 elements per k for 2048 operations, so this pays while the tiles are few (the rule is in
-// gemm_dispatch.hip.h).
+// workgroup.  What bounds it is the number of cache lines that the fragment loads of a compute unit touch: multiplies of 16 x 16 read 64
+// consecutive bytes of a row with four lanes (those of 32 x 32 only 32 bytes), and an output of few rows is cut into the smallest tiles
+// that the device has units for, which each load the least.  Launch to launch, with 32 x 32 multiplies and with these (us): fp32
+// 32 x 64 -> 128 3.1 and 2.2, 47 x 1000 -> 1000 8.9 and 4.8, 128 x 1024 -> 1024 9.8 and 7.7, 256 x 1024 -> 1024 10.1 and 10.3; bf16 64 x 1024 -> 1024 5.7 and
+// 3.8, 64 x 3072 -> 1024 11.7 (in k-slices) and 7.4, 256 x 1024 -> 1024 5.9 and 5.8.
 #pragma once
 #include "gemm2.hip.h"
 
@@ -22,7 +24,7 @@ template <class T_, bool KC> struct SmallOperand {
     int64_t ld;
 };
 
-// Fragment of lane (row lane % 32, half lane / 32): V elements from k on, at p (k-contiguous) or p, p + ld, ...
+// Fragment of a lane (row lane % 16, quarter lane / 16): V elements from k on, at p (k-contiguous) or p, p + ld, ...
 template <class T, bool KC> __device__ __forceinline__ typename Frag<T>::type small_frag(const T* p, int64_t ld) {
     constexpr int V = ElemTile<T>::V;
     union { typename Frag<T>::type f; T e[V]; } r;
@@ -42,47 +44,79 @@ template <class T, bool KC> __device__ __forceinline__ typename Frag<T>::type sm
     return r.f;
 }
 
+constexpr int small_lds_floats(int nw, int tm, int tn) { return nw * (tm * tn * 256 + tm * 16); }
+
 // Tile (bx, by) of the contraction by a workgroup of NW waves.
-template <int NW, bool ROWSUM, class AOp, class BOp, class Epi>
+template <int NW, int TM, int TN, bool ROWSUM, class AOp, class BOp, class Epi>
 __device__ __forceinline__ void gemm_small_tile(const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int bx, int by) {
     typedef typename AOp::T T;
     typedef typename Frag<T>::type frag_t;
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
     constexpr bool AKC = AOp::kContig, BKC = BOp::kContig;
-    constexpr int V = ElemTile<T>::V, GK = 2 * V;     // k of a fragment pair
-    // pairs in flight (16 waves leave 128 registers per lane, and row-contiguous fragments need more addresses)
-    constexpr int D = NW == 16 && !(AKC && BKC) ? 4 : 6;
-    extern __shared__ __attribute__((aligned(16))) float part[];   // [NW][32][32], then [NW][32] row sums
-    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    constexpr int V = ElemTile<T>::V, GK = 4 * V;     // k of a step
+    constexpr int BM = 16 * TM, BN = 16 * TN;
+    // steps in flight (16 waves leave 128 registers per lane, and row-contiguous fragments need more addresses)
+    constexpr int D = TM + TN <= 2 ? 6 : NW == 16 && !(AKC && BKC) ? 2 : 4;
+    extern __shared__ __attribute__((aligned(16))) float part[];   // [NW][BM][BN], then [NW][BM] row sums
+    const int tid = threadIdx.x, lane = tid & 63, quarter = lane >> 4, row = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int m0 = by * 32, n0 = bx * 32;
-    const int ra = min(m0 + (lane & 31), M - 1), rb = min(n0 + (lane & 31), N - 1);
-    const T* const pa = AKC ? A.p + (int64_t)ra * A.ld + half * V : A.p + (int64_t)(half * V) * A.ld + ra;
-    const T* const pb = BKC ? B.p + (int64_t)rb * B.ld + half * V : B.p + (int64_t)(half * V) * B.ld + rb;
-    const int groups = K / GK;   // whole fragment pairs; wave w takes w, w + NW, ...
-    f32x16_t acc[2];
+    const int m0 = by * BM, n0 = bx * BN;
+    const T *pa[TM], *pb[TN];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
-    float rsum = 0.0f;
-    auto multiply = [&](const frag_t& a, const frag_t& b, int d) {
-        if constexpr (sizeof(T) == 2) acc[d & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[d & 1], 0, 0, 0);
-        else {
+    for (int i = 0; i < TM; ++i) {
+        const int r = min(m0 + 16 * i + row, M - 1);
+        pa[i] = AKC ? A.p + (int64_t)r * A.ld + quarter * V : A.p + (int64_t)(quarter * V) * A.ld + r;
+    }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc[e & 1], 0, 0, 0);
+    for (int j = 0; j < TN; ++j) {
+        const int r = min(n0 + 16 * j + row, N - 1);
+        pb[j] = BKC ? B.p + (int64_t)r * B.ld + quarter * V : B.p + (int64_t)(quarter * V) * B.ld + r;
+    }
+    const int groups = K / GK;   // whole steps; wave w takes w, w + NW, ...
+    // (a single 16 x 16 output alternates between two accumulators, so that multiplies do not wait for each other)
+    constexpr int NACC = TM * TN == 1 ? 2 : 1;
+    f32x4_t acc[NACC][TM][TN];
+#pragma unroll
+    for (int a = 0; a < NACC; ++a)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[a][i][j][r] = 0.0f;
+    float rsum[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) rsum[i] = 0.0f;
+    auto multiply = [&](const frag_t (&a)[TM], const frag_t (&b)[TN], int d) {
+#pragma unroll
+        for (int e = 0; e < (sizeof(T) == 2 ? 1 : 4); ++e)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    f32x4_t& c = acc[(sizeof(T) == 2 ? d : e) % NACC][i][j];
+                    if constexpr (sizeof(T) == 2) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], c, 0, 0, 0);
+                    else c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], c, 0, 0, 0);
+                }
+        if (ROWSUM) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) rsum[i] = add_frag(rsum[i], a[i]);
         }
-        if (ROWSUM) rsum = add_frag(rsum, a);
     };
-    frag_t fa[D], fb[D];   // ring: pair i of this wave in place i % D
+    frag_t fa[D][TM], fb[D][TN];   // ring: step i of this wave in place i % D
     auto fetch = [&](int d, int i) {
         const int64_t k = (int64_t)(wave + i * NW) * GK;
-        fa[d] = small_frag<T, AKC>(pa + (AKC ? k : k * A.ld), A.ld);
-        fb[d] = small_frag<T, BKC>(pb + (BKC ? k : k * B.ld), B.ld);
+#pragma unroll
+        for (int t = 0; t < TM; ++t) fa[d][t] = small_frag<T, AKC>(pa[t] + (AKC ? k : k * A.ld), A.ld);
+#pragma unroll
+        for (int t = 0; t < TN; ++t) fb[d][t] = small_frag<T, BKC>(pb[t] + (BKC ? k : k * B.ld), B.ld);
     };
     const int mine_n = wave < groups ? (groups - wave + NW - 1) / NW : 0;
 #pragma unroll
     for (int d = 0; d < D; ++d)
         if (d < mine_n) fetch(d, d);
     int i = 0;
-    // (no branch around a load here: the compiler then waits for a pair with the younger ones still in flight)
+    // (no branch around a load here: the compiler then waits for a step with the younger ones still in flight)
     for (; i + 2 * D <= mine_n; i += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -98,54 +132,72 @@ __device__ __forceinline__ void gemm_small_tile(const AOp& A, const BOp& B, cons
         }
     }
     if (groups * GK < K && groups % NW == wave) {
-        const int k = groups * GK, n = K - k - half * V;
-        const frag_t a = small_frag_tail<T, AKC>(pa + (AKC ? (int64_t)k : k * A.ld), A.ld, n);
-        const frag_t b = small_frag_tail<T, BKC>(pb + (BKC ? (int64_t)k : k * B.ld), B.ld, n);
+        const int k = groups * GK, n = K - k - quarter * V;
+        frag_t a[TM], b[TN];
+#pragma unroll
+        for (int t = 0; t < TM; ++t) a[t] = small_frag_tail<T, AKC>(pa[t] + (AKC ? (int64_t)k : k * A.ld), A.ld, n);
+#pragma unroll
+        for (int t = 0; t < TN; ++t) b[t] = small_frag_tail<T, BKC>(pb[t] + (BKC ? (int64_t)k : k * B.ld), B.ld, n);
         multiply(a, b, 0);
     }
-    float* const mine = part + wave * 1024;
+    // accumulator register r of a lane: row 4 (lane / 16) + r, column lane % 16
+    float* const mine = part + wave * (BM * BN);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mine[(8 * (r >> 2) + 4 * half + (r & 3)) * 32 + (lane & 31)] = acc[0][r] + acc[1][r];
-    float* const sums = part + NW * 1024;
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float v = acc[0][t][j][r];
+                if (NACC == 2) v += acc[NACC - 1][t][j][r];
+                mine[(16 * t + 4 * quarter + r) * BN + 16 * j + row] = v;
+            }
+    float* const sums = part + NW * (BM * BN);
     if (ROWSUM) {
-        const float both = rsum + __shfl_xor(rsum, 32, 64);
-        if (lane < 32) sums[wave * 32 + lane] = both;
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            float all = rsum[t] + __shfl_xor(rsum[t], 16, 64);
+            all += __shfl_xor(all, 32, 64);
+            if (lane < 16) sums[wave * BM + 16 * t + lane] = all;
+        }
     }
     __syncthreads();
 #pragma unroll
-    for (int i = tid; i < 1024; i += 64 * NW) {
+    for (int o = tid; o < BM * BN; o += 64 * NW) {
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) v += part[w * 1024 + i];
-        const int m = m0 + (i >> 5), n = n0 + (i & 31);
+        for (int w = 0; w < NW; ++w) v += part[w * (BM * BN) + o];
+        const int m = m0 + o / BN, n = n0 + o % BN;
         if (m < M && n < N) epi.at(epi.column(n), (int64_t)m * epi.ld + n, v, 0);
     }
-    if (ROWSUM && bx == 0 && tid < 32 && m0 + tid < M) {
+    if (ROWSUM && bx == 0 && tid < BM && m0 + tid < M) {
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) v += sums[w * 32 + tid];
+        for (int w = 0; w < NW; ++w) v += sums[w * BM + tid];
         epi.rowsum(m0 + tid, v, 0);
     }
 }
 
-template <int NW, bool ROWSUM, class AOp, class BOp, class Epi>
+template <int NW, int TM, int TN, bool ROWSUM, class AOp, class BOp, class Epi>
 __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(AOp A, BOp B, Epi epi, int M, int N, int K) {
-    gemm_small_tile<NW, ROWSUM>(A, B, epi, M, N, K, blockIdx.x, blockIdx.y);
+    gemm_small_tile<NW, TM, TN, ROWSUM>(A, B, epi, M, N, K, blockIdx.x, blockIdx.y);
 }
 
 // Input and weight gradient of a dense layer in one launch: dx[B, Din] = dy w (the first `split` workgroups, the longer contractions
 // where a batch is small) and gw[Dout, Din] = dy^T x.  Neither depends on the other, and a launch of its own costs each more than its work:
-// 32 x 128 -> 128 in fp32 4.2 us against 7.5 in two launches (the rule, backward_kind, has the others).
-template <int NW, class T>
+// 32 x 64 -> 128 in fp32 2.5 us against 4.4 in two launches (the rule, backward_kind, has the others).
+// (TX, TW: tiles of 16 TX square outputs of dx and 16 TW square ones of gw)
+template <int NW, int TX, int TW, class T>
 __global__ __launch_bounds__(64 * NW) void gemm_small_backward_kernel(const T* dy, const T* x, const T* w, EpiMask<T, T> ex, EpiWgrad ew,
                                                                       int rows, int Din, int Dout, int split) {
-    const int tiles_n = (Din + 31) >> 5;   // (both outputs have Din columns)
-    const int b = blockIdx.x, i = b < split ? b : b - split;
-    const int by = i / tiles_n, bx = i - by * tiles_n;
-    if (b < split)
-        gemm_small_tile<NW, false>(SmallOperand<T, true>{dy, rows, Dout}, SmallOperand<T, false>{w, Din, Din}, ex, rows, Din, Dout, bx, by);
-    else
-        gemm_small_tile<NW, true>(SmallOperand<T, false>{dy, Dout, Dout}, SmallOperand<T, false>{x, Din, Din}, ew, Dout, Din, rows, bx, by);
+    const int b = blockIdx.x;
+    if (b < split) {
+        const int tiles_n = (Din + 16 * TX - 1) / (16 * TX), by = b / tiles_n, bx = b - by * tiles_n;
+        gemm_small_tile<NW, TX, TX, false>(SmallOperand<T, true>{dy, rows, Dout}, SmallOperand<T, false>{w, Din, Din}, ex, rows, Din, Dout, bx, by);
+    } else {
+        const int tiles_n = (Din + 16 * TW - 1) / (16 * TW), i = b - split, by = i / tiles_n, bx = i - by * tiles_n;
+        gemm_small_tile<NW, TW, TW, true>(SmallOperand<T, false>{dy, Dout, Dout}, SmallOperand<T, false>{x, Din, Din}, ew, Dout, Din, rows, bx, by);
+    }
 }
 
 }  // namespace tmps

@@ -128,12 +128,19 @@ Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k
     return best;
 }
 
-// Small kernel: its fragment loads touch 32 rows each, so a compute unit's L1 sets the pace: 9.5 cycles per k of a tile in
-// bf16, 18.5 in fp32 (measured from K = 512 to 4096 on 64 to 512 tiles), and a fixed part.
+// Small kernel: the smallest tiles that are no more than the compute units.  What a unit's fragment loads touch sets the pace: cycles per k
+// of 16 x 16, 16 x 32 and 32 x 32 outputs 9, 14 and 20 in fp32, 4.2, 6.2 and 9.2 in bf16 (64 to 256 rows x 768 to 1024, K = 64 to 3072), and a fixed part.
+SmallPlan small_plan(int64_t M, int64_t N, int64_t K, int esize) {
+    static const int shape[3][2] = {{1, 1}, {1, 2}, {2, 2}};
+    static const double per_k[2][3] = {{9.0, 14.0, 20.0}, {4.2, 6.2, 9.2}};
+    for (int i = 0;; ++i) {
+        const int64_t tiles = (int64_t)cdiv(M, 16 * shape[i][0]) * cdiv(N, 16 * shape[i][1]);
+        if (i == 2 || tiles <= kCUs) return SmallPlan{shape[i][0], shape[i][1], 2500.0 + (double)cdiv(tiles, kCUs) * K * per_k[esize == 4 ? 0 : 1][i]};
+    }
+}
 bool small_is_better(int64_t M, int64_t N, int64_t K, int esize, const Plan2& other) {
-    const int64_t tiles = (int64_t)cdiv(M, 32) * cdiv(N, 32);
-    if (tiles > 2 * kCUs) return false;
-    return 2500.0 + (double)cdiv(tiles, kCUs) * K * (esize == 4 ? 18.5 : 9.5) < other.cost;
+    if ((int64_t)cdiv(M, 32) * cdiv(N, 32) > 2 * kCUs) return false;
+    return small_plan(M, N, K, esize).cost < other.cost;
 }
 
 int g3_wgrad_slices(int64_t M, int64_t N, int64_t K);
@@ -594,16 +601,18 @@ hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int 
 }
 
 // ---- both gradients of a dense layer in one launch: estimates in us ----
-// Small kernel: as long as a compute unit needs for its share of the tiles, 4000 cycles each and 14 per k in fp32, 4400 and 3.6 in bf16, or as
-// the longest tile alone, 19.5 and 9.5 per k.  Fitted on 32 to 2048 rows, widths of 64 to 1024 (one launch and two): fp32 32 x 128 -> 128
-// 4.2 and 7.5, 235 x 1000 -> 10 5.4 and 7.2, 64 x 1000 -> 1000 11.6 and 14.7, 256 x 1024 -> 1024 21.1 and 19.4; bf16 256 x 1024 -> 10
-// 4.8 and 7.5, 512 x 512 -> 512 7.2 and 8.0, 256 x 1024 -> 1024 13.3 and 10.6.
+// Small kernel, four waves to a tile: half a microsecond for every tile of a compute unit's share, and the longer of its share of the multiplies
+// and the longest tile alone, per k of a 16 x 16 or a 32 x 32 tile.  Fitted on 32 to 1024 rows, widths of 10 to 1000 (one launch, two; us):
+// fp32 32 x 64 -> 128 2.5 and 4.4, 235 x 1000 -> 10 3.5 and 6.2, 64 x 1000 -> 1000 8.3 and 10.6, 512 x 768 -> 768 21.1 and 32.3,
+// 235 x 1000 -> 1000 20.2 and 19.5; bf16 32 x 64 -> 128 2.3 and 4.3, 512 x 512 -> 512 5.7 and 8.0, 256 x 768 -> 768 7.3 and 9.5, 235 x 1000 -> 1000 11.8 and 11.4.
+int small_backward_tile(int64_t M, int64_t N, int esize) { return (int64_t)cdiv(M, 16) * cdiv(N, 16) <= (esize == 4 ? 2 : 1) * kCUs ? 1 : 2; }
 double small_backward_us(int64_t B, int64_t Din, int64_t Dout, int esize) {
-    const int64_t n = cdiv(Din, 32), tx = n * cdiv(B, 32), tw = n * cdiv(Dout, 32);
-    const double tiles = (double)(tx + tw) / kCUs, work = ((double)tx * Dout + (double)tw * B) / kCUs, longest = (double)(Dout > B ? Dout : B);
-    const double all = esize == 4 ? tiles * 4000.0 + work * 14.0 : tiles * 4400.0 + work * 3.6;
-    const double one = esize == 4 ? 4000.0 + longest * 19.5 : 4400.0 + longest * 9.5;
-    return (2500.0 + (all > one ? all : one)) / 2400.0;
+    const int tx = small_backward_tile(B, Din, esize), tw = small_backward_tile(Dout, Din, esize);
+    const double nx = (double)cdiv(B, 16 * tx) * cdiv(Din, 16 * tx), nw = (double)cdiv(Dout, 16 * tw) * cdiv(Din, 16 * tw);
+    auto shared = [&](int t) { return esize == 4 ? (t == 1 ? 0.0027 : 0.0085) : (t == 1 ? 0.0011 : 0.0035); };
+    auto alone = [&](int t) { return esize == 4 ? (t == 1 ? 0.0030 : 0.0080) : (t == 1 ? 0.0017 : 0.0037); };
+    const double share = (nx * Dout * shared(tx) + nw * B * shared(tw)) / kCUs, cx = Dout * alone(tx), cw = B * alone(tw), chain = cx > cw ? cx : cw;
+    return 2.05 + 0.5 * (nx + nw) / kCUs + (share > chain ? share : chain);
 }
 // Tiled kernel in bf16, 64 x 64 tiles: a k-tile takes 0.33 us, alone on its unit or sharing it, and the weight gradient is written at 6 TB/s
 // (one launch and two): 64 x 1024 -> 1024 9.6 and 10.6, 256 x 1024 -> 1024 9.6 and 10.7, 512 x 1024 -> 1024 10.3 and 15.6, 1024 x 768 -> 768 11.8
@@ -618,16 +627,15 @@ double two_backward_us(int64_t B, int64_t Din, int64_t Dout, int esize) {
     if (esize == 2 && (g3_forward_ok(B, Din, Dout) || g3_narrow_ok(B, Din, Dout) || g3_long_k_slices(B, Din, Dout) || g3_wgrad_slices(Dout, Din, B))) return 0.0;
     auto alone = [&](int64_t M, int64_t N, int64_t K, bool rowsum) {
         const Plan2 p = plan_for(M, N, K, rowsum, esize, kByKDense);
-        if (!small_is_better(M, N, K, esize, p)) return p.cost / 2400.0;
-        return (2500.0 + (double)cdiv((int64_t)cdiv(M, 32) * cdiv(N, 32), kCUs) * K * (esize == 4 ? 18.5 : 9.5)) / 2400.0;
+        return (small_is_better(M, N, K, esize, p) ? small_plan(M, N, K, esize).cost : p.cost) / 2400.0;
     };
     return alone(B, Din, Dout, false) + 2.0 + alone(Dout, Din, B, true) + (double)Din * Dout * 4.0 / 6e6;
 }
 
 // What the gradients of a dense layer run on: kTwo launches, or one of the small or of the tiled kernel.
 int backward_kind(int64_t B, int64_t Din, int64_t Dout, int esize) {
-    const double two = 0.95 * two_backward_us(B, Din, Dout, esize), small = small_backward_us(B, Din, Dout, esize);
-    const double tiled = esize == 2 && Din % 8 == 0 && Dout % 8 == 0 ? tiled_backward_us(B, Din, Dout) : 1e9;
+    const double two = two_backward_us(B, Din, Dout, esize), small = small_backward_us(B, Din, Dout, esize);
+    const double tiled = esize == 2 && Din % 8 == 0 && Dout % 8 == 0 ? tiled_backward_us(B, Din, Dout) / 0.95 : 1e9;
     if (small >= two && tiled >= two) return kTwo;
     return small <= tiled ? kOneSmall : kOneTiled;
 }

@@ -18,9 +18,9 @@ def kind(rows, din, dout, dtype):
 
 
 # rows, input, output features
-SIZES = [("f32", 2, 3, 1, SMALL), ("f32", 34, 31, 65, SMALL), ("f32", 236, 100, 10, SMALL), ("f32", 64, 512, 512, SMALL), ("f32", 512, 257, 130, SMALL),
+SIZES = [("f32", 2, 3, 1, SMALL), ("f32", 34, 31, 65, SMALL), ("f32", 236, 100, 10, SMALL), ("f32", 64, 512, 512, SMALL), ("f32", 512, 257, 130, SMALL), ("f32", 64, 1000, 1000, SMALL), ("f32", 300, 17, 530, SMALL),
          ("f32", 256, 1024, 1024, TWO), ("bf16", 2, 1, 3, SMALL), ("bf16", 34, 33, 95, SMALL), ("bf16", 256, 1024, 10, SMALL), ("bf16", 130, 520, 500, SMALL),
-         ("bf16", 100, 1000, 1000, TILED), ("bf16", 512, 776, 712, TILED), ("bf16", 258, 1032, 1096, TILED), ("bf16", 40, 2048, 1024, TILED),
+         ("bf16", 100, 1000, 1000, SMALL), ("bf16", 236, 1000, 1000, TILED), ("bf16", 512, 776, 712, TILED), ("bf16", 258, 1032, 1096, TILED), ("bf16", 40, 4096, 1024, TILED),
          ("bf16", 1024, 712, 648, TILED), ("bf16", 2048, 1024, 1024, TWO)]
 
 
