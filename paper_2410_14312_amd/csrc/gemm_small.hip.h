@@ -3,7 +3,7 @@
 // A workgroup owns 16 TM x 16 TN outputs and its NW waves share the k range, each with fragments fetched straight from
 // global memory into registers (no LDS tile, no barrier in the k-loop; the loads of the next D steps are in
 // flight), so that a short contraction costs about one memory latency and a long one is walked
-// NW times as fast; the partial tiles are added through LDS in the order of the waves and the epilogue follows in the
+// NW times as fast; the partial tiles are added through LDS in a fixed order and the epilogue follows in the
 // same launch.  The tiled kernel needs k-slices and a second launch for such shapes, or walks the whole k range in one
 // workgroup.  What bounds it is the number of cache lines that the fragment loads of a compute unit touch: multiplies of 16 x 16 read 64
 // consecutive bytes of a row with four lanes (those of 32 x 32 only 32 bytes), and an output of few rows is cut into the smallest tiles
@@ -166,7 +166,7 @@ __device__ __forceinline__ void gemm_small_tile(const AOp& A, const BOp& B, cons
     for (int o = tid; o < BM * BN; o += 64 * NW) {
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) v += part[w * (BM * BN) + o];
+        for (int w = 0; w < NW; w += 2) v += part[w * (BM * BN) + o] + part[(w + 1) * (BM * BN) + o];   // (half the chain of additions)
         const int m = m0 + o / BN, n = n0 + o % BN;
         if (m < M && n < N) epi.at(epi.column(n), (int64_t)m * epi.ld + n, v, 0);
     }

@@ -42,9 +42,9 @@ def test_sums(n):
         count, slices = SHAPES[(k * 5 + n) % len(SHAPES)]
         odd = k % 3 == 1                     # not 16-byte aligned
         host = rng.standard_normal((slices, count)).astype(np.float32)
-        part = torch.zeros(slices * count + 1, device="cuda:0")
+        part = torch.zeros(slices * count + 1, dtype=torch.float32, device="cuda:0")
         part[odd:odd + slices * count] = torch.from_numpy(host.reshape(-1)).to("cuda:0")
-        out = torch.full((count + 2,), 7.0, device="cuda:0")
+        out = torch.full((count + 2,), 7.0, dtype=torch.float32, device="cuda:0")
         rows = k % 2 == 0
         jobs.append(_Reduction(part.data_ptr() + 4 * odd, out.data_ptr() + 4 * odd, count, slices, rows))
         keep.append((part, out, host, odd))
