@@ -358,8 +358,10 @@ __global__ __launch_bounds__(1024) void softmax_ce_small_kernel(const float* __r
     if (tid == 0) loss_out[0] = (part[0] + part[1] + part[2] + part[3]) * scale;
 }
 
-// Up to 1024 rows of the loss in all, 512 classes and 32768 logits: four rounds of the workgroup's registers.
-bool softmax_ce_small_takes(int64_t rows, int C) { return rows <= 1024 && C <= 512 && rows * C <= 32768; }
+// Lanes to a row, and what is taken: all rows of the loss at once.  (256 rows of 96 in four rounds take 12 us, a wave to a row in 64 workgroups and the mean in
+// a launch of its own 7.)
+static constexpr int ce_small_lanes(int C) { return C <= 16 ? 2 : C <= 64 ? 8 : C <= 128 ? 16 : 64; }
+bool softmax_ce_small_takes(int64_t rows, int C) { return C <= 512 && rows * ce_small_lanes(C) <= 1024; }
 
 template <typename TG, int LPR>
 static hipError_t launch_ce_small(const float* logits, const int32_t* labels, void* dlogits, float* y, float* row_loss, int rows, int C,
