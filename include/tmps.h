@@ -111,7 +111,8 @@ typedef struct {
  *   params : [P fp32 master values][P bf16 working copy, TMPS_BF16_F32MASTER only]
  *   state  : [P fp32 momentum][P fp32 weight gradient]
  *   stash  : activations of max_stash micro-batches kept for the backward pass
- *   scratch: gradient ping-pong buffers of one mini-batch and reduction workspace
+ *   scratch: gradient buffers of one mini-batch, those of the layers whose weight gradients wait for the end of the
+ *            backward pass, and reduction workspace (no initial values)
  * P = tmps_stage_param_count().  All regions must be 256-byte aligned.  Any out pointer may be
  * NULL.  Errors: TMPS_EINVAL, TMPS_ESHAPE (layers do not chain), TMPS_EMICRO, TMPS_EUNSUPPORTED. */
 int tmps_stage_bytes(const tmps_layer_desc* layers, int n_layers, const tmps_stage_cfg* cfg,

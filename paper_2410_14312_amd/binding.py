@@ -221,7 +221,9 @@ class Stage:
         self.act_dtype = torch.bfloat16 if dtype == "bf16" else torch.float32
         self.descs = layer_descs(specs)
         sizes = stage_bytes(specs, self.cfg)
-        self.regions = [torch.zeros(max(s, 256), dtype=torch.uint8, device=self.device) for s in sizes]
+        # (nothing in the scratch region is read before a kernel has written it)
+        self.regions = [torch.zeros(max(s, 256), dtype=torch.uint8, device=self.device) for s in sizes[:3]]
+        self.regions.append(torch.empty(max(sizes[3], 256), dtype=torch.uint8, device=self.device))
         h = C.c_void_p()
         _check(lib().tmps_stage_create(C.byref(h), self.descs, len(specs), C.byref(self.cfg),
                                        *[C.c_void_p(r.data_ptr()) for r in self.regions]))

@@ -243,8 +243,6 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
             L.b_off = poff + L.w_count;
             poff = (int64_t)align_up((size_t)(L.b_off + L.b_count), 64);
         }
-        // the gradient w.r.t. this layer's input lives in a gradient buffer (the loss layer's is kept in the stash)
-        if (i > 0 && L.d.kind != TMPS_SOFTMAX_CE) gmax = std::max(gmax, L.in_elems);
         ws = std::max(ws, L.ws_elems);
         st.ws_fwd_bytes = std::max(st.ws_fwd_bytes, L.ws_fwd_elems * 4);
         st.layers.push_back(L);
@@ -254,7 +252,6 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
     if (cfg->is_last) st.layers[n_layers - 2].out_f32 = true;
     if (!cfg->is_last) {
         if (st.layers.back().act == 2) return fail(TMPS_EUNSUPPORTED, "a stage cannot end in a GELU layer");
-        if (st.layers.back().relu) gmax = std::max(gmax, st.layers.back().out_elems);
     }
     st.P = poff;
     st.in_elems = st.layers.front().in_elems;
@@ -310,6 +307,16 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
     }
     close_group();
 
+    // The gradient w.r.t. a layer's input lives in a gradient buffer, unless its memory is its own (the loss layer's is kept in the stash).
+    auto kept = [&](int t) { return st.layers[t].grouped && !(t == n_layers - 1 || (cfg->is_last && t == n_layers - 2)); };
+    if (!cfg->is_last && st.layers.back().relu) gmax = st.layers.back().out_elems;
+    for (int i = 1; i < n_layers; ++i) {
+        const LayerRT& L = st.layers[i];
+        if (L.d.kind == TMPS_SOFTMAX_CE) continue;
+        for (int t : {L.in_t, L.d.kind == TMPS_RESADD ? L.in_b : L.in_t})
+            if (t >= 0 && !kept(t)) gmax = std::max(gmax, st.layers[t].out_elems);
+    }
+
     // scratch: gradient buffers of M rows, two boundary-gradient buffers, fp32 workspace
     size_t o = 0;
     st.n_gbuf = any_join ? 6 : (any_skip ? 4 : 2);
@@ -328,7 +335,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
     st.dxout_off[0] = o; o += st.dxout_bytes;
     st.dxout_off[1] = o; o += st.dxout_bytes;
     for (int i = 0; i < n_layers; ++i)
-        if (st.layers[i].grouped && !(i == n_layers - 1 || (cfg->is_last && i == n_layers - 2))) {
+        if (kept(i)) {
             st.layers[i].keep_off = o;   // (not 0: the gradient buffers come first)
             o += align_up((size_t)M * st.layers[i].out_elems * st.asz, 256);
         }
