@@ -165,6 +165,11 @@ constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 // 16 bytes in flight between global memory and LDS (a native vector: arrays of it stay in registers)
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
+// v plus another lane's (CTRL: the data-parallel-primitive control that names it)
+template <int CTRL> __device__ __forceinline__ float add_lanes(float v) {
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+
 // What depends on the element type and the features per head.
 template <class T, int DH> struct Attn {
     static constexpr bool BF = sizeof(T) == 2;
@@ -272,6 +277,22 @@ template <class T, int DH> struct Attn {
             for (int i = 0; i < N; ++i) {
                 const int c = tid + i * NT;
                 if (R * C % NT == 0 || c < R * C) *reinterpret_cast<u32x4_t*>(tile + (c / C) * P + (c % C) * V) = r[i];
+            }
+        }
+        // dots[row] = the row times the other one's, summed over the C neighbouring lanes that hold it
+        __device__ __forceinline__ void put_dots(const Fetch& other, float* dots, int tid) const {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const frag_t x = __builtin_bit_cast(frag_t, r[i]), y = __builtin_bit_cast(frag_t, other.r[i]);
+                float d = 0.0f;
+#pragma unroll
+                for (int e = 0; e < V; ++e) d = fmaf((float)x[e], (float)y[e], d);
+                d = add_lanes<0xB1>(d);                       // lanes 1 apart
+                d = add_lanes<0x4E>(d);                       // 2 apart
+                if constexpr (C >= 8) d = add_lanes<0x141>(d);    // the other four of eight
+                if constexpr (C >= 16) d = add_lanes<0x140>(d);   // the other eight of sixteen
+                const int c = tid + i * NT;
+                if (c % C == 0 && (R * C % NT == 0 || c < R * C)) dots[c / C] = d;
             }
         }
     };
@@ -383,10 +404,10 @@ __device__ __forceinline__ void query_gradient_row(const T* base, const T* dout,
     if (lane < DH) dq[f] = (T)(a * scale);
 }
 
-// One key's and value's gradients, over the queries from that position on.  lse, delta: the statistics of this (batch, head).
+// One key's and value's gradients, over the queries from that position on.  o: the outputs' rows, as dout's; lse: the statistics of this (batch, head).
 template <class T, int DH>
-__device__ __forceinline__ void key_value_gradient_row(const T* base, const T* dout, int64_t ld, int D, int S, int key, float scale, const float* lse,
-                                                       const float* delta, T* dk_row, T* dv_row, int lane) {
+__device__ __forceinline__ void key_value_gradient_row(const T* base, const T* o, const T* dout, int64_t ld, int D, int S, int key, float scale,
+                                                       const float* lse, T* dk_row, T* dv_row, int lane) {
     const int f = lane % DH;
     const float scale2 = scale * kLog2e;
     float dk = 0.0f, dv = 0.0f;
@@ -394,7 +415,7 @@ __device__ __forceinline__ void key_value_gradient_row(const T* base, const T* d
     for (int i0 = key; i0 < S; i0 += 64) {
         const int n = min(64, S - i0), i = i0 + min(lane, n - 1);
         const float p = exp2_hw(fmaf(row_dot<T, DH>(base + D + key * ld, base + i * ld), scale2, -lse[i] * kLog2e));
-        const float ds = p * (row_dot<T, DH>(base + 2 * D + key * ld, dout + (int64_t)i * D) - delta[i]);
+        const float ds = p * (row_dot<T, DH>(base + 2 * D + key * ld, dout + (int64_t)i * D) - row_dot<T, DH>(o + (int64_t)i * D, dout + (int64_t)i * D));
 #pragma unroll 1
         for (int t = 0; t < n; ++t) {
             dk = fmaf(__shfl(ds, t, 64), (float)base[(i0 + t) * ld + f], dk);
@@ -597,24 +618,29 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 2 ? 3 : 1) void attn_fwd_spli
     }
 }
 
-// Query gradient.  Same arrangement as the forward pass: P^T and dS^T have keys along the registers.  The workgroup also
-// forms delta[q] = dO[q] . O[q] of its queries, from the dO fragments it holds anyway, for itself and for the
-// key/value-gradient kernel that follows (as a kernel of its own it took 6 us per layer of the GPT-2 configuration).
-template <class T, int DH, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_q_mfma_kernel(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dout,
-                                                                  const float* __restrict__ lse, float* __restrict__ delta,
-                                                                  T* __restrict__ dqkv, int S, int D, int H, float scale) {
+// Gradients: one launch, in which a workgroup of NW waves forms the gradient of 32 NW queries or those of 32 NW keys and values.  Both read
+// tiles of R rows through LDS, the next one's loads in flight; both form delta[q] = dO[q] . O[q] for themselves, which costs the keys' workgroups
+// a sixth more vector work and spares the pass a second launch behind the first, with its own way to the end of the longest diagonal.
+// What bounds them is latency: products, exponentials and products again that depend on each other, in two waves per SIMD, all that the
+// registers allow (28 multiplies and about 260 vector instructions for 32 x 32 pairs take 10 and 13 us of the 55 for 16 x 12 heads over 512 positions).
+// So the two 32-row blocks of a bf16 tile go side by side, whose chains fill each other's gaps, a workgroup has four waves
+// (eight wait for the one with the longest way), and the workgroups with the longest way start first.  Two kernels with the blocks one after the
+// other and eight / four / two waves, and this (us), bf16, positions x heads x sequences: 512 x 12 x 16 87 and 55, x 2 33 and 20; 1024 x 12 x 2 59 and
+// 35; 2048 x 8 x 8 255 and 169; 333 x 8 x 12 35 and 23; 96 x 8 x 64 32 and 24; 32 features per head, 512 x 8 x 16 53 and 36, 128 x 4 x 16 13.2 and 7.9;
+// fp32, 512 x 4 x 4, 32 features 83 and 48; 256 x 8 x 8, 64 features 75 and 49; 32 x 2 x 16 10.4 and 6.2.
+template <class T, int DH, int NW> struct AttnBwdTiles {
     typedef Attn<T, DH> X;
-    __shared__ __attribute__((aligned(16))) T sKb[2][X::R * X::P];
-    __shared__ __attribute__((aligned(16))) T sVb[2][X::R * X::P];
+    T a[2][X::R * X::P], b[2][X::R * X::P];   // keys and values, or queries and output gradients
+    float L2[2][X::R], delta[2][X::R];        // log-sum-exp (in units of log 2) and delta of the queries
+};
+
+// Query gradient.  Same arrangement as the forward pass: P^T and dS^T have keys along the registers.
+template <class T, int DH, int NW>
+__device__ __forceinline__ void attn_bwd_q(AttnBwdTiles<T, DH, NW>& sm, const T* __restrict__ base, const T* __restrict__ ob, const T* __restrict__ dob,
+                                           const float* __restrict__ lse, T* __restrict__ dbase, int qb, int S, int D, float scale) {
+    typedef Attn<T, DH> X;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
-    int bx, h, b;
-    xcd_local_block(bx, h, b);
-    const int qb = gridDim.x - 1 - bx;
     const int64_t ld = 3 * (int64_t)D;
-    const T* base = qkv + (int64_t)b * S * ld + h * DH;
-    const T* dob = dout + (int64_t)b * S * D + h * DH;
-    const T* ob = o + (int64_t)b * S * D + h * DH;
     typename X::template Fetch<64 * NW> fk, fv;
     fk.fetch(base + D, ld, 0, S, tid);
     fv.fetch(base + 2 * D, ld, 0, S, tid);
@@ -628,82 +654,77 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_q_mfma_kernel(const T* __
         dof[t] = X::gfrag(dob, D, q0, S, t, lane);
         of[t] = X::gfrag(ob, D, q0, S, t, lane);
     }
-    const float L2 = lse[((int64_t)b * H + h) * S + qc] * kLog2e;
+    const float L2 = lse[qc] * kLog2e;
     float dl = 0.0f;
 #pragma unroll
     for (int t = 0; t < X::NF; ++t)
 #pragma unroll
         for (int e = 0; e < X::V; ++e) dl += (float)of[t][e] * (float)dof[t][e];
     dl += __shfl_xor(dl, 32, 64);
-    if (half == 0 && q < S) delta[((int64_t)b * H + h) * S + q] = dl;
     const float scale2 = scale * kLog2e;
     f32x16_t dq[X::FT];
     clear(dq);
     const int kv_end = min(S, (qb + 1) * NW * 32);
-    fk.put(sKb[0], tid);
-    fv.put(sVb[0], tid);
+    fk.put(sm.a[0], tid);
+    fv.put(sm.b[0], tid);
     __syncthreads();
     for (int kv0 = 0, it = 0; kv0 < kv_end; kv0 += X::R, ++it) {
-        const T* sK = sKb[it & 1];
-        const T* sV = sVb[it & 1];
+        const T* sK = sm.a[it & 1];
+        const T* sV = sm.b[it & 1];
         fk.fetch(base + D, ld, kv0 + X::R, S, tid);
         fv.fetch(base + 2 * D, ld, kv0 + X::R, S, tid);
+        // the first N blocks of 32 keys of the tile; MASK: the last of them straddles the diagonal
+        auto blocks = [&](auto nc, auto maskc) {
+            constexpr int N = decltype(nc)::value;
+            constexpr bool MASK = decltype(maskc)::value;
+            f32x16_t st[N], dp[N];
+            clear(st);
+            clear(dp);
 #pragma unroll
-        for (int sub = 0; sub < X::R / 32; ++sub) {
-            const int kb = kv0 + 32 * sub;
-            if (kb > q0 + 31) continue;
-            f32x16_t st, dp;
+            for (int n = 0; n < N; ++n)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) st[r] = dp[r] = 0.0f;
+                for (int t = 0; t < X::NF; ++t) {
+                    st[n] = X::mul(X::lfrag(sK, 32 * n, t, lane), qf[t], st[n]);
+                    dp[n] = X::mul(X::lfrag(sV, 32 * n, t, lane), dof[t], dp[n]);
+                }
 #pragma unroll
-            for (int t = 0; t < X::NF; ++t) {
-                st = X::mul(X::lfrag(sK, 32 * sub, t, lane), qf[t], st);
-                dp = X::mul(X::lfrag(sV, 32 * sub, t, lane), dof[t], dp);
-            }
-            if (kb + 31 <= q0) {   // below the diagonal: no key is excluded
-#pragma unroll
-                for (int r = 0; r < 16; ++r) st[r] = exp2_hw(fmaf(st[r], scale2, -L2)) * (dp[r] - dl);
-            } else {
+            for (int n = 0; n < N; ++n) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
-                    const float p = key <= q ? exp2_hw(fmaf(st[r], scale2, -L2)) : 0.0f;
-                    st[r] = p * (dp[r] - dl);
+                    float p = exp2_hw(fmaf(st[n][r], scale2, -L2));
+                    if (MASK && n == N - 1) p = kv0 + 32 * n + 8 * (r >> 2) + 4 * half + (r & 3) <= q ? p : 0.0f;
+                    st[n][r] = p * (dp[n][r] - dl);
                 }
+                X::mul_t(sK, 32 * n, st[n], dq, lane);
             }
-            X::mul_t(sK, 32 * sub, st, dq, lane);
-        }
-        fk.put(sKb[(it + 1) & 1], tid);
-        fv.put(sVb[(it + 1) & 1], tid);
+        };
+        constexpr int NB = X::R / 32;
+        const std::integral_constant<int, NB> all;
+        if (kv0 + X::R <= q0) blocks(all, std::false_type());
+        else if (kv0 + X::R - 32 == q0) blocks(all, std::true_type());
+        else if (NB == 2 && kv0 == q0) blocks(std::integral_constant<int, 1>(), std::true_type());
+        fk.put(sm.a[(it + 1) & 1], tid);
+        fv.put(sm.b[(it + 1) & 1], tid);
         __syncthreads();
     }
     // (a log-sum-exp that is not finite, or a delta that is NaN, stands in every term of the row)
     const uint32_t redo = not_finite_rows(dq, fabsf(L2) < INFINITY && dl == dl);
-    if (q < S && !((redo >> (lane & 31)) & 1)) X::store_row(dqkv + ((int64_t)b * S + q) * ld + h * DH, dq, scale, half);
+    if (q < S && !((redo >> (lane & 31)) & 1)) X::store_row(dbase + q * ld, dq, scale, half);
     for (uint32_t todo = redo; todo; todo &= todo - 1) {
         const int r = __builtin_ctz(todo);
         if (q0 + r < S)
-            query_gradient_row<T, DH>(base, dob, ld, D, q0 + r, scale, __shfl(L2, r, 64), __shfl(dl, r, 64),
-                                      dqkv + ((int64_t)b * S + q0 + r) * ld + h * DH, lane);
+            query_gradient_row<T, DH>(base, dob, ld, D, q0 + r, scale, __shfl(L2, r, 64), __shfl(dl, r, 64), dbase + (q0 + r) * ld, lane);
     }
 }
 
 // Key and value gradients.  A wave owns 32 keys (lanes); queries run along the accumulator registers, so the
 // per-query statistics (log-sum-exp, delta) are read per register from LDS.
 template <class T, int DH, int NW>
-__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 1 : 2) void attn_bwd_kv_mfma_kernel(const T* __restrict__ qkv, const T* __restrict__ dout,
-                                                                   const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                   T* __restrict__ dqkv, int S, int D, int H, float scale) {
+__device__ __forceinline__ void attn_bwd_kv(AttnBwdTiles<T, DH, NW>& sm, const T* __restrict__ base, const T* __restrict__ ob, const T* __restrict__ dob,
+                                            const float* __restrict__ lse, T* __restrict__ dbase, int kblk, int S, int D, float scale) {
     typedef Attn<T, DH> X;
-    __shared__ __attribute__((aligned(16))) T sQb[2][X::R * X::P];
-    __shared__ __attribute__((aligned(16))) T sOb[2][X::R * X::P];
-    __shared__ __attribute__((aligned(16))) float sLb[2][X::R], sDlb[2][X::R];   // log-sum-exp (in units of log 2) and delta
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
-    int kblk, h, b;
-    xcd_local_block(kblk, h, b);
     const int64_t ld = 3 * (int64_t)D;
-    const T* base = qkv + (int64_t)b * S * ld + h * DH;
-    const T* dob = dout + (int64_t)b * S * D + h * DH;
     const int k0 = (kblk * NW + wave) * 32;
     const int key = k0 + (lane & 31);
     const float scale2 = scale * kLog2e;
@@ -717,96 +738,117 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 1 : 2) void attn_bwd_kv_m
     clear(dk);
     clear(dv);
     const int qstart = (kblk * NW * 32) / X::R * X::R;   // first query block that can see a key of this workgroup
-    typename X::template Fetch<64 * NW> fq, fo;
-    float pl = 0.0f, pd = 0.0f;   // statistics of query qb0 + tid (threads 0 .. R-1)
-    auto fetch_stats = [&](int qb0) {
-        if (tid < X::R) {
-            const int qq = qb0 + tid < S ? qb0 + tid : S - 1;
-            pl = lse[((int64_t)b * H + h) * S + qq];
-            pd = delta[((int64_t)b * H + h) * S + qq];
-        }
+    typename X::template Fetch<64 * NW> fq, fg, fo;
+    float pl = 0.0f;   // log-sum-exp of query qb0 + tid (threads 0 .. R-1)
+    auto fetch = [&](int qb0) {
+        fq.fetch(base, ld, qb0, S, tid);
+        fg.fetch(dob, D, qb0, S, tid);
+        fo.fetch(ob, D, qb0, S, tid);
+        if (tid < X::R) pl = lse[qb0 + tid < S ? qb0 + tid : S - 1];
     };
-    auto put_stats = [&](int buf) {
-        if (tid < X::R) {
-            sLb[buf][tid] = pl * kLog2e;
-            sDlb[buf][tid] = pd;
-        }
+    auto put = [&](int buf) {
+        fq.put(sm.a[buf], tid);
+        fg.put(sm.b[buf], tid);
+        fo.put_dots(fg, sm.delta[buf], tid);
+        if (tid < X::R) sm.L2[buf][tid] = pl * kLog2e;
     };
-    fq.fetch(base, ld, qstart, S, tid);
-    fo.fetch(dob, D, qstart, S, tid);
-    fetch_stats(qstart);
-    fq.put(sQb[0], tid);
-    fo.put(sOb[0], tid);
-    put_stats(0);
+    fetch(qstart);
+    put(0);
     __syncthreads();
     for (int qb0 = qstart, it = 0; qb0 < S; qb0 += X::R, ++it) {
-        const T* sQ = sQb[it & 1];
-        const T* sO = sOb[it & 1];
-        const float* sL = sLb[it & 1];
-        const float* sDl = sDlb[it & 1];
-        fq.fetch(base, ld, qb0 + X::R, S, tid);
-        fo.fetch(dob, D, qb0 + X::R, S, tid);
-        fetch_stats(qb0 + X::R);
+        const T* sQ = sm.a[it & 1];
+        const T* sO = sm.b[it & 1];
+        const float* sL = sm.L2[it & 1];
+        const float* sDl = sm.delta[it & 1];
+        fetch(qb0 + X::R);
+        // the last N blocks of 32 queries of the tile; MASK: some of their queries do not see all keys of this wave, or do not exist
+        auto blocks = [&](auto nc, auto maskc) {
+            constexpr int N = decltype(nc)::value, B0 = X::R / 32 - N;
+            constexpr bool MASK = decltype(maskc)::value;
+            f32x16_t st[N], dp[N];
+            clear(st);
+            clear(dp);
 #pragma unroll
-        for (int sub = 0; sub < X::R / 32; ++sub) {
-            const int qs = qb0 + 32 * sub;
-            if (qs + 31 < k0) continue;   // every query of the tile lies before every key of this wave
-            f32x16_t st, dp;
+            for (int n = 0; n < N; ++n)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) st[r] = dp[r] = 0.0f;
-#pragma unroll
-            for (int t = 0; t < X::NF; ++t) {
-                st = X::mul(X::lfrag(sQ, 32 * sub, t, lane), kf[t], st);
-                dp = X::mul(X::lfrag(sO, 32 * sub, t, lane), vf[t], dp);
-            }
-            // statistics of the 4 consecutive queries of a register group in one LDS read each
-            float4 l4[4], d4[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                l4[g] = *reinterpret_cast<const float4*>(sL + 32 * sub + 8 * g + 4 * half);
-                d4[g] = *reinterpret_cast<const float4*>(sDl + 32 * sub + 8 * g + 4 * half);
-            }
-            const bool inner = k0 + 31 <= qs && qs + 32 <= S;   // every query of the block sees every key of this wave
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float Lq = (r & 3) == 0 ? l4[r >> 2].x : (r & 3) == 1 ? l4[r >> 2].y : (r & 3) == 2 ? l4[r >> 2].z : l4[r >> 2].w;
-                const float Dq = (r & 3) == 0 ? d4[r >> 2].x : (r & 3) == 1 ? d4[r >> 2].y : (r & 3) == 2 ? d4[r >> 2].z : d4[r >> 2].w;
-                float p = exp2_hw(fmaf(st[r], scale2, -Lq));
-                if (!inner) {
-                    const int qq = qs + 8 * (r >> 2) + 4 * half + (r & 3);
-                    p = (key <= qq && qq < S) ? p : 0.0f;
+                for (int t = 0; t < X::NF; ++t) {
+                    st[n] = X::mul(X::lfrag(sQ, 32 * (B0 + n), t, lane), kf[t], st[n]);
+                    dp[n] = X::mul(X::lfrag(sO, 32 * (B0 + n), t, lane), vf[t], dp[n]);
                 }
-                st[r] = p;
-                dp[r] = p * (dp[r] - Dq);
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const int row = 32 * (B0 + n);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    // statistics of the 4 consecutive queries of a register group in one LDS read each
+                    const float4 l4 = *reinterpret_cast<const float4*>(sL + row + 8 * g + 4 * half);
+                    const float4 d4 = *reinterpret_cast<const float4*>(sDl + row + 8 * g + 4 * half);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = 4 * g + e;
+                        const float Lq = e == 0 ? l4.x : e == 1 ? l4.y : e == 2 ? l4.z : l4.w;
+                        const float Dq = e == 0 ? d4.x : e == 1 ? d4.y : e == 2 ? d4.z : d4.w;
+                        float p = exp2_hw(fmaf(st[n][r], scale2, -Lq));
+                        if (MASK) {
+                            const int qq = qb0 + row + 8 * g + 4 * half + e;
+                            p = (key <= qq && qq < S) ? p : 0.0f;
+                        }
+                        st[n][r] = p;
+                        dp[n][r] = p * (dp[n][r] - Dq);
+                    }
+                }
+                X::mul_t(sO, row, st[n], dv, lane);
+                X::mul_t(sQ, row, dp[n], dk, lane);
             }
-            X::mul_t(sO, 32 * sub, st, dv, lane);
-            X::mul_t(sQ, 32 * sub, dp, dk, lane);
-        }
-        fq.put(sQb[(it + 1) & 1], tid);
-        fo.put(sOb[(it + 1) & 1], tid);
-        put_stats((it + 1) & 1);
+        };
+        constexpr int NB = X::R / 32;
+        const std::integral_constant<int, NB> all;
+        if (qb0 > k0 && qb0 + X::R <= S) blocks(all, std::false_type());
+        else if (qb0 >= k0) blocks(all, std::true_type());
+        else if (NB == 2 && qb0 + 32 == k0) blocks(std::integral_constant<int, 1>(), std::true_type());
+        put((it + 1) & 1);
         __syncthreads();
     }
-    const float* const lse_bh = lse + ((int64_t)b * H + h) * S;
-    const float* const delta_bh = delta + ((int64_t)b * H + h) * S;
     const uint32_t dk_rows = not_finite_rows(dk, true), dv_rows = not_finite_rows(dv, true);
     uint32_t redo = dk_rows | dv_rows;
     if (redo) {
         // every key sees the last query: a NaN in that one's log-sum-exp stands in every row of both gradients, one in its delta
         // in every row of the key gradient
-        const bool lse_ok = lse_bh[S - 1] == lse_bh[S - 1], delta_ok = delta_bh[S - 1] == delta_bh[S - 1];
+        const float dl = row_dot<T, DH>(ob + (int64_t)(S - 1) * D, dob + (int64_t)(S - 1) * D);
+        const bool lse_ok = lse[S - 1] == lse[S - 1], delta_ok = dl == dl;
         redo = (lse_ok && delta_ok ? dk_rows : 0) | (lse_ok ? dv_rows : 0);
     }
     if (key < S && !((redo >> (lane & 31)) & 1)) {
-        T* drow = dqkv + ((int64_t)b * S + key) * ld + h * DH;
+        T* drow = dbase + key * ld;
         X::store_row(drow + D, dk, scale, half);
         X::store_row(drow + 2 * D, dv, 1.0f, half);
     }
     for (uint32_t todo = redo; todo; todo &= todo - 1) {
         const int r = __builtin_ctz(todo);
-        T* drow = dqkv + ((int64_t)b * S + k0 + r) * ld + h * DH;
-        if (k0 + r < S) key_value_gradient_row<T, DH>(base, dob, ld, D, S, k0 + r, scale, lse_bh, delta_bh, drow + D, drow + 2 * D, lane);
+        T* drow = dbase + (k0 + r) * ld;
+        if (k0 + r < S) key_value_gradient_row<T, DH>(base, ob, dob, ld, D, S, k0 + r, scale, lse, drow + D, drow + 2 * D, lane);
     }
+}
+
+// The workgroups of the pairs (batch, head) are numbered in groups of an eighth of the pairs, which one XCD gets (as in xcd_local_block);
+// within a group those with the longest way along the diagonal come first.
+template <class T, int DH, int NW>
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 1 : 2) void attn_bwd_mfma_kernel(const T* __restrict__ qkv, const T* __restrict__ o,
+                                                                   const T* __restrict__ dout, const float* __restrict__ lse, T* __restrict__ dqkv, int S, int D, int H,
+                                                                   int blocks, float scale) {
+    __shared__ __attribute__((aligned(16))) AttnBwdTiles<T, DH, NW> sm;
+    const int total = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x, xcd = lin & 7;
+    const int u = total < 16 ? lin : xcd * (total >> 3) + min(xcd, total & 7) + (lin >> 3);
+    const int pairs = gridDim.y * H, group = max(1, pairs >> 3), per = 2 * blocks * group;
+    const int g = u / per, r = u - g * per, n = min(group, pairs - g * group);
+    const int slot = r / n, pair = g * group + (r - slot * n), b = pair / H, h = pair - b * H;
+    const T* base = qkv + (int64_t)b * S * 3 * D + h * DH;
+    const T* ob = o + (int64_t)b * S * D + h * DH;
+    const T* dob = dout + (int64_t)b * S * D + h * DH;
+    T* dbase = dqkv + (int64_t)b * S * 3 * D + h * DH;
+    lse += (int64_t)pair * S;
+    if (slot & 1) attn_bwd_q<T, DH, NW>(sm, base, ob, dob, lse, dbase, blocks - 1 - (slot >> 1), S, D, scale);
+    else attn_bwd_kv<T, DH, NW>(sm, base, ob, dob, lse, dbase, slot >> 1, S, D, scale);
 }
 
 // Waves per workgroup of the tiled kernels.  bf16: every workgroup streams the whole key (query) range of its
@@ -838,21 +880,19 @@ static hipError_t forward_mfma(const T* qkv, T* o, float* lse, int B, int S, int
     }
 }
 
+// Four waves per workgroup, or two where four would leave compute units without one (128 positions x 4 heads x 16 sequences in bf16 7.9 us
+// against 8.8) and registers allow it: bf16 rows of 64 features are staged in twice the registers by half the waves, and spill (512 x 12 x 2 33 us against 20).
 template <class T, int DH>
-static hipError_t backward_mfma(const T* qkv, const T* o, const T* dout, const float* lse, float* delta, T* dqkv, int B, int S, int D, int H,
-                                float scale, hipStream_t s) {
+static hipError_t backward_mfma(const T* qkv, const T* o, const T* dout, const float* lse, T* dqkv, int B, int S, int D, int H, float scale, hipStream_t s) {
     auto go = [&](auto nwc) {
         constexpr int NW = decltype(nwc)::value;
-        const dim3 grid(cdiv_at(S, 32 * NW), H, B);
-        hipError_t e = launch_timed(kcAttnBwd, attn_bwd_q_mfma_kernel<T, DH, NW>, grid, dim3(64 * NW), 0, s, qkv, o, dout, lse, delta, dqkv, S, D, H, scale);
-        if (e != hipSuccess) return e;
-        return launch_timed(kcAttnBwd, attn_bwd_kv_mfma_kernel<T, DH, NW>, grid, dim3(64 * NW), 0, s, qkv, dout, lse, (const float*)delta, dqkv, S, D, H, scale);
+        const int blocks = cdiv_at(S, 32 * NW);
+        return launch_timed(kcAttnBwd, attn_bwd_mfma_kernel<T, DH, NW>, dim3(2 * blocks * H, B), dim3(64 * NW), 0, s, qkv, o, dout, lse, dqkv, S, D, H,
+                            blocks, scale);
     };
-    switch (attn_waves<T>(B, S, H)) {
-        case 8: return go(std::integral_constant<int, sizeof(T) == 2 ? 8 : 4>{});
-        case 4: return go(std::integral_constant<int, 4>{});
-        default: return go(std::integral_constant<int, 2>{});
-    }
+    if constexpr (sizeof(T) == 4 || DH == 32)
+        if ((int64_t)2 * cdiv_at(S, 128) * B * H < 256) return go(std::integral_constant<int, 2>{});
+    return go(std::integral_constant<int, 4>{});
 }
 
 template <class T> static hipError_t forward_t(const T* qkv, T* o, float* lse, int B, int S, int D, int H, hipStream_t s) {
@@ -868,8 +908,8 @@ static hipError_t backward_t(const T* qkv, const T* o, const T* dout, const floa
     const float scale = 1.0f / sqrtf((float)(D / H));
     const bool aligned = ((reinterpret_cast<uintptr_t>(qkv) | reinterpret_cast<uintptr_t>(o) | reinterpret_cast<uintptr_t>(dout) |
                            reinterpret_cast<uintptr_t>(dqkv)) & 15) == 0;
-    if (aligned && D == 64 * H) return backward_mfma<T, 64>(qkv, o, dout, lse, delta, dqkv, B, S, D, H, scale, s);
-    if (aligned && D == 32 * H) return backward_mfma<T, 32>(qkv, o, dout, lse, delta, dqkv, B, S, D, H, scale, s);
+    if (aligned && D == 64 * H) return backward_mfma<T, 64>(qkv, o, dout, lse, dqkv, B, S, D, H, scale, s);
+    if (aligned && D == 32 * H) return backward_mfma<T, 32>(qkv, o, dout, lse, dqkv, B, S, D, H, scale, s);
     const int64_t BS = (int64_t)B * S;
     hipError_t e = launch_timed(kcAttnBwd, attn_delta_kernel<T>, dim3(cdiv_at(BS * H, 4)), dim3(256), 0, s, o, dout, delta, BS, S, D, H);
     if (e != hipSuccess) return e;
