@@ -305,34 +305,41 @@ template <int FT> __device__ __forceinline__ void clear(f32x16_t (&v)[FT]) {
         for (int r = 0; r < 16; ++r) v[i][r] = 0.0f;
 }
 
-// One 32-key block of the running softmax of 32 queries (one per lane pair; keys along the registers).  st holds the
+// N 32-key blocks of the running softmax of 32 queries (one per lane pair; keys along the registers).  st holds the
 // raw scores q.k and leaves as unnormalised probabilities; m_run (in units of log 2) and l_run are the running
-// maximum and sum, ot the running output, rescaled here.  MASK: the block straddles the diagonal (or the end of
-// the sequence): keys after the query are excluded.  Blocks below the diagonal skip the three mask instructions
-// per element.
-template <bool MASK, int FT>
-__device__ __forceinline__ void softmax_block(f32x16_t& st, int kb, int q, int half, float scale2, float& m_run, float& l_run,
-                                              f32x16_t (&ot)[FT]) {
-    float mt = -INFINITY;
+// maximum and sum, ot the running output, rescaled here.  MASK: keys after the query are excluded (the first block's
+// first key is kb).  Blocks below the diagonal skip the three mask instructions per element.
+template <bool MASK, int N, int FT>
+__device__ __forceinline__ void softmax_blocks(f32x16_t (&st)[N], int kb, int q, int half, float scale2, float& m_run, float& l_run,
+                                               f32x16_t (&ot)[FT]) {
+    float mx[N], ls[N];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        if constexpr (MASK) {
-            const int key = kb + 8 * (r >> 2) + 4 * half + (r & 3);
-            st[r] = key <= q ? st[r] : -INFINITY;
+    for (int n = 0; n < N; ++n) {
+        mx[n] = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if constexpr (MASK) {
+                const int key = kb + 32 * n + 8 * (r >> 2) + 4 * half + (r & 3);
+                st[n][r] = key <= q ? st[n][r] : -INFINITY;
+            }
+            mx[n] = fmaxf(mx[n], st[n][r]);
         }
-        mt = fmaxf(mt, st[r]);
     }
+    float mt = N == 2 ? fmaxf(mx[0], mx[N - 1]) : mx[0];
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
     const float m_new = fmaxf(m_run, mt * scale2);       // scale2 > 0: the maximum commutes with the scaling
     const float m_use = m_new == -INFINITY ? 0.0f : m_new;   // a query with no key yet keeps zeros
     const float alpha = exp2_hw(m_run - m_use);
-    float ls = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        st[r] = exp2_hw(fmaf(st[r], scale2, -m_use));
-        ls += st[r];
+    for (int n = 0; n < N; ++n) {
+        ls[n] = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            st[n][r] = exp2_hw(fmaf(st[n][r], scale2, -m_use));
+            ls[n] += st[n][r];
+        }
     }
-    l_run = l_run * alpha + ls;
+    l_run = l_run * alpha + (N == 2 ? ls[0] + ls[N - 1] : ls[0]);
     m_run = m_new;
 #pragma unroll
     for (int i = 0; i < FT; ++i)
@@ -444,17 +451,34 @@ __device__ __forceinline__ void xcd_local_block(int& x, int& y, int& z) {
     x = moved - y * gx;
 }
 
-// Forward.  Block = NW waves = 32*NW query rows of one (batch, head).
+// The same for grids of (slots per (batch, head) pair x heads, batches), whose workgroups differ in their way along the diagonal: an XCD gets
+// an eighth of the pairs, and slot 0, which has the longest way, of all of them first.
+__device__ __forceinline__ void longest_first(int slots, int H, int& slot, int& h, int& b) {
+    const int total = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x, xcd = lin & 7;
+    const int u = total < 16 ? lin : xcd * (total >> 3) + min(xcd, total & 7) + (lin >> 3);
+    const int pairs = gridDim.y * H, group = max(1, pairs >> 3), per = slots * group;
+    const int g = u / per, r = u - g * per, n = min(group, pairs - g * group);
+    slot = r / n;
+    const int pair = g * group + (r - slot * n);
+    b = pair / H;
+    h = pair - b * H;
+}
+
+// Forward.  A workgroup's NW waves own 32 * NW query rows of one (batch, head).  Bound by latency, as the gradients below, and for the same
+// reasons: a bf16 tile's two blocks of 32 keys go side by side, with one rescaling of the output for both, and the longest way comes first.  Blocks one
+// after the other in eight waves, and this (us), positions x heads x sequences: 512 x 12 x 16 27 and 19, x 8 17.0 and 13.3; 2048 x 8 x 8 86 and 58;
+// 333 x 8 x 12 12.7 and 10.3; 512 x 8 x 16 of 32 features 19.5 and 15.0.  (Side by side in the kernel below: 9.9 and 12.1 for 512 x 12 x 2, whose waves
+// have four blocks each at most and would have two pairs.)
 template <class T, int DH, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int S,
-                                                                int D, int H, float scale) {
+                                                                int D, int H, int blocks, float scale) {
     typedef Attn<T, DH> X;
     __shared__ __attribute__((aligned(16))) T sKb[2][X::R * X::P];
     __shared__ __attribute__((aligned(16))) T sVb[2][X::R * X::P];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
-    int bx, h, b;
-    xcd_local_block(bx, h, b);
-    const int qb = gridDim.x - 1 - bx;
+    int slot, h, b;
+    longest_first(blocks, H, slot, h, b);
+    const int qb = blocks - 1 - slot;
     const int64_t ld = 3 * (int64_t)D;
     const T* base = qkv + (int64_t)b * S * ld + h * DH;
     const int q0 = (qb * NW + wave) * 32;
@@ -480,19 +504,24 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma_kernel(const T* __re
         // and the copy lands in the buffer that nobody reads again)
         fk.fetch(base + D, ld, kv0 + X::R, S, tid);
         fv.fetch(base + 2 * D, ld, kv0 + X::R, S, tid);
+        // the first N blocks of 32 keys of the tile; MASK: the last of them straddles the diagonal
+        auto key_blocks = [&](auto nc, auto maskc) {
+            constexpr int N = decltype(nc)::value;
+            f32x16_t st[N];
+            clear(st);
 #pragma unroll
-        for (int sub = 0; sub < X::R / 32; ++sub) {
-            const int kb = kv0 + 32 * sub;
-            if (kb > q0 + 31) continue;   // every key of the tile lies after every query of this wave
-            f32x16_t st;
+            for (int n = 0; n < N; ++n)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) st[r] = 0.0f;
+                for (int t = 0; t < X::NF; ++t) st[n] = X::mul(X::lfrag(sK, 32 * n, t, lane), qf[t], st[n]);
+            softmax_blocks<decltype(maskc)::value>(st, kv0, q, half, scale2, m_run, l_run, ot);
 #pragma unroll
-            for (int t = 0; t < X::NF; ++t) st = X::mul(X::lfrag(sK, 32 * sub, t, lane), qf[t], st);
-            if (kb + 31 <= q0) softmax_block<false>(st, kb, q, half, scale2, m_run, l_run, ot);
-            else softmax_block<true>(st, kb, q, half, scale2, m_run, l_run, ot);
-            X::mul_t(sV, 32 * sub, st, ot, lane);
-        }
+            for (int n = 0; n < N; ++n) X::mul_t(sV, 32 * n, st[n], ot, lane);
+        };
+        constexpr int NB = X::R / 32;
+        const std::integral_constant<int, NB> all;
+        if (kv0 + X::R <= q0) key_blocks(all, std::false_type());
+        else if (kv0 + X::R - 32 == q0) key_blocks(all, std::true_type());
+        else if (NB == 2 && kv0 == q0) key_blocks(std::integral_constant<int, 1>(), std::true_type());
         fk.put(sKb[(it + 1) & 1], tid);   // the other buffer was last read before the previous barrier
         fv.put(sVb[(it + 1) & 1], tid);
         __syncthreads();
@@ -566,14 +595,13 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 2 ? 3 : 1) void attn_fwd_spli
         __builtin_amdgcn_wave_barrier();
         fetch(j + NW);
         const int kb = 32 * j;
-        f32x16_t st;
+        f32x16_t st[1];
+        clear(st);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = 0.0f;
-#pragma unroll
-        for (int t = 0; t < X::NF; ++t) st = X::mul(kf[t], qf[t], st);
-        if (kb + 31 <= q0) softmax_block<false>(st, kb, q, half, scale2, m_run, l_run, ot);
-        else softmax_block<true>(st, kb, q, half, scale2, m_run, l_run, ot);
-        X::mul_t(sV, 0, st, ot, lane);
+        for (int t = 0; t < X::NF; ++t) st[0] = X::mul(kf[t], qf[t], st[0]);
+        if (kb + 31 <= q0) softmax_blocks<false>(st, kb, q, half, scale2, m_run, l_run, ot);
+        else softmax_blocks<true>(st, kb, q, half, scale2, m_run, l_run, ot);
+        X::mul_t(sV, 0, st[0], ot, lane);
     }
     float l = l_run + __shfl_xor(l_run, 32, 64);
     if (wave > 0) {
@@ -830,54 +858,43 @@ __device__ __forceinline__ void attn_bwd_kv(AttnBwdTiles<T, DH, NW>& sm, const T
     }
 }
 
-// The workgroups of the pairs (batch, head) are numbered in groups of an eighth of the pairs, which one XCD gets (as in xcd_local_block);
-// within a group those with the longest way along the diagonal come first.
 template <class T, int DH, int NW>
 __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 1 : 2) void attn_bwd_mfma_kernel(const T* __restrict__ qkv, const T* __restrict__ o,
                                                                    const T* __restrict__ dout, const float* __restrict__ lse, T* __restrict__ dqkv, int S, int D, int H,
                                                                    int blocks, float scale) {
     __shared__ __attribute__((aligned(16))) AttnBwdTiles<T, DH, NW> sm;
-    const int total = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x, xcd = lin & 7;
-    const int u = total < 16 ? lin : xcd * (total >> 3) + min(xcd, total & 7) + (lin >> 3);
-    const int pairs = gridDim.y * H, group = max(1, pairs >> 3), per = 2 * blocks * group;
-    const int g = u / per, r = u - g * per, n = min(group, pairs - g * group);
-    const int slot = r / n, pair = g * group + (r - slot * n), b = pair / H, h = pair - b * H;
+    int slot, h, b;
+    longest_first(2 * blocks, H, slot, h, b);
     const T* base = qkv + (int64_t)b * S * 3 * D + h * DH;
     const T* ob = o + (int64_t)b * S * D + h * DH;
     const T* dob = dout + (int64_t)b * S * D + h * DH;
     T* dbase = dqkv + (int64_t)b * S * 3 * D + h * DH;
-    lse += (int64_t)pair * S;
+    lse += ((int64_t)b * H + h) * S;
     if (slot & 1) attn_bwd_q<T, DH, NW>(sm, base, ob, dob, lse, dbase, blocks - 1 - (slot >> 1), S, D, scale);
     else attn_bwd_kv<T, DH, NW>(sm, base, ob, dob, lse, dbase, slot >> 1, S, D, scale);
 }
 
-// Waves per workgroup of the tiled kernels.  bf16: every workgroup streams the whole key (query) range of its
-// (batch, head) pair through LDS, so the traffic from L2 falls with the number of rows that share a tile: the widest
-// workgroup that still leaves about one per compute unit.  fp32: the MFMAs take sixteen times as long and the traffic is
-// no matter, so workgroups stay small, for balance along the diagonal.
-template <class T> static int attn_waves(int B, int S, int H) {
-    const int64_t bh = (int64_t)B * H;
-    if (sizeof(T) == 4) return cdiv_at(S, 128) * bh >= 1024 ? 4 : 2;
-    if (cdiv_at(S, 256) * bh >= 192) return 8;
-    if (cdiv_at(S, 128) * bh >= 192) return 4;
-    return 2;
-}
-
 size_t attention_workspace_elems(int B, int S, int H) { return (size_t)B * S * H; }
 
+// The kernel with the key range split over a workgroup's waves, where the tiled one has too few workgroups: its time is that of the longest way (3.5 us
+// and 1 us per 64 keys in bf16) until there are more than a round of them.  Split and tiled (us), bf16, positions x heads x sequences: 512 x 12 x 1
+// 6.6 and -, x 2 9.9 and 11.5, x 4 13.8 and 11.8, x 5 16.5 and 12.1; 1024 x 12 x 2 20.7 and 19.6; 2048 x 12 x 1 30.7 and 35; 128 x 4 x 16 with 32 features
+// 4.0 and 5.5; fp32, 256 x 8 x 8 17.2 and 23.6, 512 x 4 x 4 9.9 and 25.5.  A single block of 32 keys leaves nothing to split: 32 x 2 x 16, fp32, 4.4 and 3.9.
+// Four waves per workgroup of the tiled kernel in bf16 (two cover 64 rows; 8 and 4: 512 x 12 x 16 20.8 and 19.3, x 8 16.7 and 13.3, 2048 x 8 x 8 63
+// and 58, 96 x 8 x 64 10.4 and 8.1).  fp32: the MFMAs take sixteen times as long, and workgroups stay small for balance along the diagonal.
 template <class T, int DH>
 static hipError_t forward_mfma(const T* qkv, T* o, float* lse, int B, int S, int D, int H, float scale, hipStream_t s) {
-    if ((int64_t)cdiv_at(S, 64) * H * B < 512)   // too few workgroups of the tiled kernel to fill the chip
+    const int64_t tiles = (int64_t)cdiv_at(S, 64) * B * H;
+    const bool split = S > 32 && (sizeof(T) == 2 && S <= 1024 ? tiles < 256 : tiles < 512);
+    if (split)
         return launch_timed(kcAttnFwd, attn_fwd_split_kernel<T, DH, 4>, dim3(cdiv_at(S, 32), H, B), dim3(256), 0, s, qkv, o, lse, S, D, H, scale);
     auto go = [&](auto nwc) {
         constexpr int NW = decltype(nwc)::value;
-        return launch_timed(kcAttnFwd, attn_fwd_mfma_kernel<T, DH, NW>, dim3(cdiv_at(S, 32 * NW), H, B), dim3(64 * NW), 0, s, qkv, o, lse, S, D, H, scale);
+        const int blocks = cdiv_at(S, 32 * NW);
+        return launch_timed(kcAttnFwd, attn_fwd_mfma_kernel<T, DH, NW>, dim3(blocks * H, B), dim3(64 * NW), 0, s, qkv, o, lse, S, D, H, blocks, scale);
     };
-    switch (attn_waves<T>(B, S, H)) {
-        case 8: return go(std::integral_constant<int, sizeof(T) == 2 ? 8 : 4>{});
-        case 4: return go(std::integral_constant<int, 4>{});
-        default: return go(std::integral_constant<int, 2>{});
-    }
+    if (S <= 64 || (sizeof(T) == 4 && (int64_t)cdiv_at(S, 128) * B * H < 1024)) return go(std::integral_constant<int, 2>{});
+    return go(std::integral_constant<int, 4>{});
 }
 
 // Four waves per workgroup, or two where four would leave compute units without one (128 positions x 4 heads x 16 sequences in bf16 7.9 us
