@@ -38,7 +38,6 @@ template <int NW, int WM> constexpr int conv_rows_stage_bytes() { return NW / WM
 template <int NW, int WM, int NS, bool DGRAD, class Epi>
 __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi epi, FastDiv d_tn) {
     constexpr int KG = NW / WM, BM = 64 * WM, CPW = 8 / WM, STAGE = conv_rows_stage_bytes<NW, WM>();
-    typedef WaveTile<typename std::conditional<DGRAD, DenseRC<bf16_t>, DenseKC<bf16_t>>::type> BTile;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     const lds_t smem = (lds_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
     const lds_t patches = smem + NS * STAGE, zeros = patches + cv.patch_rows * 128;
@@ -72,43 +71,44 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
             copy16_to_lds(at_if(src, (int64_t)row * cv.C, g * 8 + (lane >> 3) < cv.patch_rows), dst + g * 1024);
         }
     };
-    // Copies of a tap's 64 x 64 weights: CPW of 8 groups by each wave of the tap's own group.
-    int woff[CPW];
+    // Copies of a tap's 64 x 64 weights: CPW of 8 groups by each wave of the tap's own group, from offsets (bytes) behind the tap's first weight.
+    const int my_taps = (taps - kg + KG - 1) / KG;   // (R S > KG: at least one)
+    uint32_t woff[CPW];
 #pragma unroll
     for (int g = 0; g < CPW; ++g) {
         const int grp = wm * CPW + g;
         if constexpr (DGRAD) {   // LDS [64 c][8 chunks of n]
             int n = n0 + ((lane & 7) ^ (((lane >> 4) & 1) << 2)) * 8;
             n = n + 8 <= cv.N ? n : cv.N - 8;
-            woff[g] = (grp * 8 + (lane >> 3)) * cv.RS * cv.N + n;
+            woff[g] = (uint32_t)((grp * 8 + (lane >> 3)) * cv.RS * cv.N + n) * 2;
         } else {                 // LDS [64 n][8 chunks of c]
             int n = n0 + grp * 8 + (lane >> 3);
             n = n < cv.N ? n : cv.N - 1;
-            woff[g] = n * cv.RS * cv.C + chunk_of(grp);
+            woff[g] = (uint32_t)((n - n0) * cv.RS * cv.C + chunk_of(grp)) * 2;
         }
     }
-    int ctap = kg, cchunk = 0;   // the tap whose weights are copied next
-    while (ctap >= cv.RS) { ctap -= cv.RS; ++cchunk; }
-    // (past the last tap zeros are copied: the number of copies in flight is what the waits count, and a group without a tap in
-    // the last step multiplies zeros)
-    const bf16_t* wsrc;
-    lds_t wdst;
-    bool wok;
-    auto next_weights = [&](int stage) {
-        wok = cchunk < chunks;
-        wsrc = DGRAD ? cv.w + ((int64_t)cchunk * 64 * cv.RS + (cv.RS - 1 - ctap)) * cv.N : cv.w + (int64_t)ctap * cv.C + cchunk * 64;
-        wdst = smem + stage * STAGE + kg * 8192 + wm * CPW * 1024;
+    const bf16_t* wsrc = cv.w + (DGRAD ? (int64_t)(cv.RS - 1 - kg) * cv.N : (int64_t)n0 * cv.RS * cv.C + (int64_t)kg * cv.C);   // of the tap copied next
+    const int64_t wstep = DGRAD ? -(int64_t)KG * cv.N : (int64_t)KG * cv.C;   // to the group's next tap, in the same 64 channels or in the next
+    const int64_t wwrap = DGRAD ? (int64_t)(65 * cv.RS - KG) * cv.N : 64 - (int64_t)(cv.RS - KG) * cv.C;
+    int ctap = kg, wleft = my_taps, fill = 0;    // (past the group's last tap its weights are copied again: the waits count copies)
+    lds_t wdst = smem + kg * 8192 + wm * CPW * 1024;
+    auto copy_weights = [&](int g) { copy16_to_lds(wsrc, woff[g], wdst + g * 1024); };
+    auto next_weights = [&]() {
         ctap += KG;
-        while (ctap >= cv.RS) { ctap -= cv.RS; ++cchunk; }
+        const bool wrap = ctap >= cv.RS;
+        const int64_t by = wrap ? wwrap : wstep;
+        ctap = wrap ? ctap - cv.RS : ctap;
+        wsrc += --wleft > 0 ? by : 0;
+        fill = fill + 1 == NS ? 0 : fill + 1;
+        wdst = smem + fill * STAGE + kg * 8192 + wm * CPW * 1024;
     };
-    auto copy_weights = [&](int g) { copy16_to_lds(at_if(wsrc, woff[g], wok), wdst + g * 1024); };
 
     copy_patch(0);
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
-        next_weights(st);
 #pragma unroll
         for (int g = 0; g < CPW; ++g) copy_weights(g);
+        next_weights();
     }
 
     // This lane's two rows: which taps lie on the map.
@@ -143,32 +143,48 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
     // weights are there (everyone has waited for its copies) and the stage of the step being multiplied is free (everyone has
     // its fragments in registers).  Reads and copies are issued one after each multiply: all at once they would occupy the
     // wave until the LDS has served most of them, and the multiplies would come after that instead of meanwhile.
+    // So are the addresses of the reads after those, and a copy of weights costs two scalar instructions (a base that all lanes share, one offset per
+    // lane and group): computed behind the barrier, with nothing to multiply meanwhile, and with a 64-bit select for each copy, they took as long
+    // as the multiplies (3 x 3 over 512 channels, forward / gradient, before and after, us: 128 images of 2 x 2 17.4 / 17.5 and 15.2 / 16.3, of
+    // 4 x 4 19.2 / 19.0 and 17.5 / 18.1, 64 of 7 x 7 24.7 / 25.2 and 22.6 / 24.1; 256 channels, 64 images of 8 x 8 12.1 / 12.2 and 11.0 / 11.1).
     struct Frags { bf16x8_t a[4][2], b[4][2]; };
-    int tap = kg, chunk = 0, stage = 0;          // of the step whose fragments are read next
-    while (tap >= cv.RS) { tap -= cv.RS; ++chunk; }
+    int tap = kg, run = 0, stage = 0;            // of the step whose addresses are computed next
+    const int run_bytes = cv.two ? cv.patch_bytes : 0, inv_s = 65536 / cv.S + 1, row_step = cv.W - cv.S;   // (tap / S: at most 31 taps)
     lds_t pa[2], pb;
-    auto next_read = [&]() {
-        uint32_t r, s;
-        cv.d_s.divmod(tap, r, s);
-        const int shift = (int)r * cv.W + (int)s;
-        const bool on = chunk < chunks;
-        const lds_t run = patches + (chunk & 1 & cv.two) * cv.patch_bytes;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int row = lrow[i] + shift;
-            pa[i] = (on && ((valid[i] >> tap) & 1) ? run + row * 128 : zeros) + ((half ^ ((row >> 1) & 7)) << 4);
-        }
-        pb = smem + stage * STAGE + kg * 8192;
+    const int bl = DGRAD ? (half * 8 + ((lane & 15) >> 2)) * 128 + ((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ (((lane >> 3) & 1) << 2)) * 16 + (lane & 1) * 8
+                         : (lane & 31) * 128 + ((half ^ ((lane >> 1) & 7)) << 4);
+    // two parts, for between multiplies
+    int shift;
+    lds_t next_run, next_pb;
+    uint32_t tap_bit;
+    auto address_tap = [&]() {
+        shift = tap + ((tap * inv_s) >> 16) * row_step;   // r W + s
+        tap_bit = 1u << tap;
+        next_run = patches + run;
+        next_pb = smem + stage * STAGE + kg * 8192 + bl;
         tap += KG;
-        while (tap >= cv.RS) { tap -= cv.RS; ++chunk; }
+        const bool wrap = tap >= cv.RS;
+        tap = wrap ? tap - cv.RS : tap;
+        run = wrap ? run_bytes - run : run;
         stage = stage + 1 == NS ? 0 : stage + 1;
+    };
+    auto address_rows = [&]() {
+        const int row = lrow[0] + shift;   // (the other one lies 32 rows on)
+        const int at = row * 128 + next_run, sw = (half ^ ((row >> 1) & 7)) << 4;
+        pa[0] = (valid[0] & tap_bit ? at : zeros) + sw;
+        pa[1] = (valid[1] & tap_bit ? at + 4096 : zeros) + sw;
+        pb = next_pb;
     };
     auto read_a = [&](Frags& q, int f, int i) { q.a[f][i] = *lds_ptr<const bf16x8_t>(pa[i] ^ (f << 5)); };
     auto read_b = [&](Frags& q, int f, int i) {
-        if constexpr (DGRAD) q.b[f][i] = BTile::read(pb, i, f, lane);
-        else q.b[f][i] = *lds_ptr<const bf16x8_t>(pb + (32 * i + (lane & 31)) * 128 + (((2 * f + half) ^ ((lane >> 1) & 7)) << 4));
+        if constexpr (DGRAD) {   // (rows 32 i .. of the 16 channels 16 f .., as in WaveTile; 4 channels further lie 512 bytes on)
+            const lds_t p = (pb ^ (i << 6)) + f * 2048;
+            union { s16x4_t h[2]; bf16x8_t v; } u;
+            u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p));
+            u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p + 512));
+            q.b[f][i] = u.v;
+        } else q.b[f][i] = *lds_ptr<const bf16x8_t>((pb ^ (f << 5)) + 4096 * i);
     };
-    int fill = 0;                                // the stage that is copied next
     int next_patch = 2;                          // the next run of rows to copy, into the buffer of run next_patch - 2 ...
     int last_use = (cv.RS - 1) / KG;             // ... whose last tap is in this step
     auto one_step = [&](int step, const Frags& cur, Frags& next) {
@@ -182,9 +198,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
             last_use = (next_patch * cv.RS - 1) / KG;
             ++next_patch;
         }
-        next_read();
-        next_weights(fill);
-        fill = fill + 1 == NS ? 0 : fill + 1;
+        if (step >= my_taps) return;   // (the last step, of a group without a tap in it)
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
 #pragma unroll
@@ -194,17 +208,21 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[f][i], cur.b[f][j], acc[i][j], 0, 0, 0);
                     if (i == j) read_a(next, f, i);
                     else read_b(next, f, j);
+                    if (f == 3 && i == 0 && j == 1) address_tap();
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
             for (int g = f * CPW / 4; g < (f + 1) * CPW / 4; ++g) copy_weights(g);
         }
+        address_rows();
+        next_weights();
     };
     Frags f0, f1;
+    address_tap();
+    address_rows();
     wait_vmcnt<(NS - 1) * CPW>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    next_read();
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
@@ -212,6 +230,8 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
             read_a(f0, f, i);
             read_b(f0, f, i);
         }
+    address_tap();
+    address_rows();
     for (int step = 0; step < steps; step += 2) {
         one_step(step, f0, f1);
         if (step + 1 < steps) one_step(step + 1, f1, f0);

@@ -63,6 +63,11 @@ __device__ __forceinline__ void copy16_to_lds(const void* src, lds_t dst) {
     const uint32_t lds = __builtin_amdgcn_readfirstlane(dst);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
 }
+// the same from `off` bytes (of each lane) behind a base that all lanes share
+__device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t off, lds_t dst) {
+    const uint32_t lds = __builtin_amdgcn_readfirstlane(dst);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // Makes the compiler treat every 32-bit word of `t` (values requested from memory earlier) as read here, on every
