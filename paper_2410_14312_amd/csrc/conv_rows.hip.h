@@ -7,15 +7,14 @@
 //
 // The tiled kernel fetches each tap's rows anew and computes their addresses chunk by chunk: nine copies of X through L2 and
 // LDS for a 3 x 3 filter and a k-tile of 1100 to 1800 cycles, three times what its multiplies take.  Here only the weights'
-// tiles (64 x 64 per tap) are streamed.  Forward / input gradient, 3 x 3, before and after (us): 64 images of 56 x 56 x 64
-// 47 / 56 and 31 / 29 (510 TFLOP/s), of 28 x 28 x 128 37 / 44 and 27 / 27, of 14 x 14 x 256 33 / 39 and 22 / 23, of 7 x 7 x 512
-// 29 / 32 and 22 / 22; 128 images of 8 x 8 x 256 26 / 33 and 15 / 15, of 4 x 4 x 512 22 / 32 and 18 / 18.
+// tiles (64 channels x 64 or 32 columns per tap) are streamed.  Forward / input gradient, 3 x 3, on the tiled kernel and here (us): 64 images
+// of 56 x 56 x 64 47 / 56 and 29 / 27, of 28 x 28 x 128 37 / 44 and 26 / 25, of 14 x 14 x 256 33 / 39 and 21 / 21, of 7 x 7 x 512
+// 29 / 32 and 21 / 22; 128 images of 8 x 8 x 256 26 / 33 and 15 / 15, of 4 x 4 x 512 22 / 32 and 16 / 17, of 2 x 2 x 512 19 / 23 and 12 / 14.
 //
-// NW waves, WM of them along the 64 WM positions of a tile; the NW / WM groups take the taps in turn, each wave a 64 x 64
-// tile over its group's taps; the groups' partial tiles are added through LDS at the end.  A step (one tap for every wave) takes
-// 0.6 to 0.9 us where its multiplies take 0.3 (four waves on a unit) or 0.56 (eight): the copies of the weights have to come from
-// L2 in 0.5 to 1 us, which bounds it with the 32 to 96 KB that are under way, and LDS serves 16 KB for every wave's 16 MFMAs.
-// Contractions over 64 channels are bound by what is not overlapped around their few steps.
+// NW waves, WM of them along the 64 WM positions of a tile; the NW / WM groups take the taps in turn, each wave a tile of 64 x 32 TN
+// over its group's taps; the groups' partial tiles are added through LDS at the end.  A step (one tap for every wave) takes
+// 0.44 to 0.75 us where its multiplies take 0.25 (four waves on a unit) or 0.5 (eight): LDS serves 16 KB for every wave's 16 MFMAs, as long as these
+// take, and receives the copies besides.  Contractions over 64 channels are bound by what is not overlapped around their few steps.
 #pragma once
 #include "gemm4.hip.h"
 
@@ -32,12 +31,12 @@ struct ConvRows {
     FastDiv d_hw, d_w, d_s;
 };
 
-template <int NW, int WM> constexpr int conv_rows_stage_bytes() { return NW / WM * 8192; }
+template <int NW, int WM, int TN> constexpr int conv_rows_stage_bytes() { return NW / WM * TN * 4096; }
 
 // DGRAD: X is the gradient of the result, N = Cin, C = Cout, and B(n, r, s, c) = w[c][R - 1 - r][S - 1 - s][n]; else w[n][r][s][c].
-template <int NW, int WM, int NS, bool DGRAD, class Epi>
+template <int NW, int WM, int TN, int NS, bool DGRAD, class Epi>
 __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi epi, FastDiv d_tn) {
-    constexpr int KG = NW / WM, BM = 64 * WM, CPW = 8 / WM, STAGE = conv_rows_stage_bytes<NW, WM>();
+    constexpr int KG = NW / WM, BM = 64 * WM, BN = 32 * TN, CPW = 4 * TN / WM, STAGE = conv_rows_stage_bytes<NW, WM, TN>(), WTILE = STAGE / KG;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     const lds_t smem = (lds_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
     const lds_t patches = smem + NS * STAGE, zeros = patches + cv.patch_rows * 128;
@@ -51,7 +50,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
         tile_m = (int)a;
         tile_n = (int)b;
     }
-    const int m0 = tile_m * BM, n0 = tile_n * 64;
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
     // (R S + 1 >= 2 KG: a run is copied during the last step of the one two before it, and first read two steps later)
     const int chunks = cv.C >> 6, taps = chunks * cv.RS, steps = (taps + KG - 1) / KG;
 
@@ -71,17 +70,17 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
             copy16_to_lds(at_if(src, (int64_t)row * cv.C, g * 8 + (lane >> 3) < cv.patch_rows), dst + g * 1024);
         }
     };
-    // Copies of a tap's 64 x 64 weights: CPW of 8 groups by each wave of the tap's own group, from offsets (bytes) behind the tap's first weight.
+    // Copies of a tap's 64 x BN weights: CPW of 4 TN groups by each wave of the tap's own group, from offsets (bytes) behind the tap's first weight.
     const int my_taps = (taps - kg + KG - 1) / KG;   // (R S > KG: at least one)
     uint32_t woff[CPW];
 #pragma unroll
     for (int g = 0; g < CPW; ++g) {
         const int grp = wm * CPW + g;
-        if constexpr (DGRAD) {   // LDS [64 c][8 chunks of n]
-            int n = n0 + ((lane & 7) ^ (((lane >> 4) & 1) << 2)) * 8;
+        if constexpr (DGRAD) {   // LDS [64 c][8 or 4 chunks of n]
+            int n = n0 + (TN == 2 ? (lane & 7) ^ (((lane >> 4) & 1) << 2) : lane & 3) * 8;
             n = n + 8 <= cv.N ? n : cv.N - 8;
-            woff[g] = (uint32_t)((grp * 8 + (lane >> 3)) * cv.RS * cv.N + n) * 2;
-        } else {                 // LDS [64 n][8 chunks of c]
+            woff[g] = (uint32_t)((TN == 2 ? grp * 8 + (lane >> 3) : grp * 16 + (lane >> 2)) * cv.RS * cv.N + n) * 2;
+        } else {                 // LDS [BN n][8 chunks of c]
             int n = n0 + grp * 8 + (lane >> 3);
             n = n < cv.N ? n : cv.N - 1;
             woff[g] = (uint32_t)((n - n0) * cv.RS * cv.C + chunk_of(grp)) * 2;
@@ -91,7 +90,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
     const int64_t wstep = DGRAD ? -(int64_t)KG * cv.N : (int64_t)KG * cv.C;   // to the group's next tap, in the same 64 channels or in the next
     const int64_t wwrap = DGRAD ? (int64_t)(65 * cv.RS - KG) * cv.N : 64 - (int64_t)(cv.RS - KG) * cv.C;
     int ctap = kg, wleft = my_taps, fill = 0;    // (past the group's last tap its weights are copied again: the waits count copies)
-    lds_t wdst = smem + kg * 8192 + wm * CPW * 1024;
+    lds_t wdst = smem + kg * WTILE + wm * CPW * 1024;
     auto copy_weights = [&](int g) { copy16_to_lds(wsrc, woff[g], wdst + g * 1024); };
     auto next_weights = [&]() {
         ctap += KG;
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
         ctap = wrap ? ctap - cv.RS : ctap;
         wsrc += --wleft > 0 ? by : 0;
         fill = fill + 1 == NS ? 0 : fill + 1;
-        wdst = smem + fill * STAGE + kg * 8192 + wm * CPW * 1024;
+        wdst = smem + fill * STAGE + kg * WTILE + wm * CPW * 1024;
     };
 
     copy_patch(0);
@@ -131,11 +130,11 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
         valid[i] = v;
     }
 
-    f32x16_t acc[2][2];
+    f32x16_t acc[2][TN];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
@@ -147,11 +146,12 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
     // lane and group): computed behind the barrier, with nothing to multiply meanwhile, and with a 64-bit select for each copy, they took as long
     // as the multiplies (3 x 3 over 512 channels, forward / gradient, before and after, us: 128 images of 2 x 2 17.4 / 17.5 and 15.2 / 16.3, of
     // 4 x 4 19.2 / 19.0 and 17.5 / 18.1, 64 of 7 x 7 24.7 / 25.2 and 22.6 / 24.1; 256 channels, 64 images of 8 x 8 12.1 / 12.2 and 11.0 / 11.1).
-    struct Frags { bf16x8_t a[4][2], b[4][2]; };
+    struct Frags { bf16x8_t a[4][2], b[4][TN]; };
     int tap = kg, run = 0, stage = 0;            // of the step whose addresses are computed next
     const int run_bytes = cv.two ? cv.patch_bytes : 0, inv_s = 65536 / cv.S + 1, row_step = cv.W - cv.S;   // (tap / S: at most 31 taps)
     lds_t pa[2], pb;
-    const int bl = DGRAD ? (half * 8 + ((lane & 15) >> 2)) * 128 + ((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ (((lane >> 3) & 1) << 2)) * 16 + (lane & 1) * 8
+    constexpr int CP = TN * 64;                  // bytes of a channel's row of columns
+    const int bl = DGRAD ? (half * 8 + ((lane & 15) >> 2)) * CP + ((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ (TN == 2 ? ((lane >> 3) & 1) << 2 : 0)) * 16 + (lane & 1) * 8
                          : (lane & 31) * 128 + ((half ^ ((lane >> 1) & 7)) << 4);
     // two parts, for between multiplies
     int shift;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
         shift = tap + ((tap * inv_s) >> 16) * row_step;   // r W + s
         tap_bit = 1u << tap;
         next_run = patches + run;
-        next_pb = smem + stage * STAGE + kg * 8192 + bl;
+        next_pb = smem + stage * STAGE + kg * WTILE + bl;
         tap += KG;
         const bool wrap = tap >= cv.RS;
         tap = wrap ? tap - cv.RS : tap;
@@ -177,11 +177,11 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
     };
     auto read_a = [&](Frags& q, int f, int i) { q.a[f][i] = *lds_ptr<const bf16x8_t>(pa[i] ^ (f << 5)); };
     auto read_b = [&](Frags& q, int f, int i) {
-        if constexpr (DGRAD) {   // (rows 32 i .. of the 16 channels 16 f .., as in WaveTile; 4 channels further lie 512 bytes on)
-            const lds_t p = (pb ^ (i << 6)) + f * 2048;
+        if constexpr (DGRAD) {   // (rows 32 i .. of the 16 channels 16 f .., as in WaveTile)
+            const lds_t p = (pb ^ (i << 6)) + f * 16 * CP;
             union { s16x4_t h[2]; bf16x8_t v; } u;
             u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p));
-            u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p + 512));
+            u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p + 4 * CP));
             q.b[f][i] = u.v;
         } else q.b[f][i] = *lds_ptr<const bf16x8_t>((pb ^ (f << 5)) + 4096 * i);
     };
@@ -204,11 +204,11 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < TN; ++j) {
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[f][i], cur.b[f][j], acc[i][j], 0, 0, 0);
-                    if (i == j) read_a(next, f, i);
-                    else read_b(next, f, j);
-                    if (f == 3 && i == 0 && j == 1) address_tap();
+                    if (TN == 1 || i == j) read_a(next, f, i);
+                    if (TN == 1 ? i == 0 : i != j) read_b(next, f, j);
+                    if (f == 3 && i == 0 && j == TN - 1) address_tap();
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             read_a(f0, f, i);
-            read_b(f0, f, i);
+            if (i < TN) read_b(f0, f, i);
         }
     address_tap();
     address_rows();
@@ -240,34 +240,35 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_rows_kernel(ConvRows cv, Epi 
 
     // ---- the groups' partial tiles are added through LDS, 8 consecutive columns of a row per lane ----
     const int64_t ld = epi.ld;
-    const int n = n0 + (tid & 7) * 8;
+    constexpr int OCT = 4 * TN;   // lanes to a row
+    const int n = n0 + tid % OCT * 8;
     const typename Epi::Col8 pcol = epi.col8(n < cv.N ? n : 0);
-    constexpr int PASS = 8 * NW, NP = BM / PASS;   // rows of a pass
+    constexpr int PASS = 64 * NW / OCT, NP = BM / PASS;   // rows of a pass
     typename Epi::Row8 prow[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        const int m = m0 + p * PASS + (tid >> 3);
+        const int m = m0 + p * PASS + tid / OCT;
         prow[p] = epi.row8((int64_t)(m < cv.M ? m : 0) * ld + n, m < cv.M && n < cv.N);
     }
     __syncthreads();   // every wave is past its last read: the stages may be overwritten
-    float* const part = reinterpret_cast<float*>(smem_raw);   // [NW][64][64]
+    float* const part = reinterpret_cast<float*>(smem_raw);   // [NW][64][BN]
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                part[(wave * 64 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * 64 + j * 32 + (lane & 31)] = acc[i][j][r];
+                part[(wave * 64 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * BN + j * 32 + (lane & 31)] = acc[i][j][r];
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        const int row = p * PASS + (tid >> 3), m = m0 + row;
+        const int row = p * PASS + tid / OCT, m = m0 + row;
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = 0.0f;
 #pragma unroll
         for (int k = 0; k < KG; ++k) {
-            const float* q = part + ((k * WM + (row >> 6)) * 64 + (row & 63)) * 64 + (tid & 7) * 8;
+            const float* q = part + ((k * WM + (row >> 6)) * 64 + (row & 63)) * BN + tid % OCT * 8;
             const float4 lo = *reinterpret_cast<const float4*>(q), hi = *reinterpret_cast<const float4*>(q + 4);
             v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
             v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;

@@ -8,40 +8,50 @@ namespace tmps {
 
 // LDS of a variant
 static int rows_patch_bytes(int wm, const ConvShape& c) { return ((64 * wm + (c.R - 1) * c.W + c.S - 1) / 8 + 1) * 1024; }   // (a zero row behind the run)
-static int rows_lds(int nw, int wm, int ns, const ConvShape& c, int C) {
-    const int main = ns * (nw / wm) * 8192 + (C > 64 ? 2 : 1) * rows_patch_bytes(wm, c);
-    return main > nw * 16384 ? main : nw * 16384;
+static int rows_lds(int nw, int wm, int tn, int ns, const ConvShape& c, int C) {
+    const int main = ns * (nw / wm) * tn * 4096 + (C > 64 ? 2 : 1) * rows_patch_bytes(wm, c), sums = nw * tn * 8192;
+    return main > sums ? main : sums;
 }
 
-template <int NW, int WM, int NS, bool DGRAD, class Epi>
+template <int NW, int WM, int TN, int NS, bool DGRAD, class Epi>
 static hipError_t launch_rows(int kc, ConvRows cv, const Epi& epi, const ConvShape& c, hipStream_t s) {
     constexpr int BM = 64 * WM;
     cv.patch_rows = BM + (c.R - 1) * c.W + c.S - 1;
     cv.patch_bytes = rows_patch_bytes(WM, c);
-    auto kern = conv_rows_kernel<NW, WM, NS, DGRAD, Epi>;
+    auto kern = conv_rows_kernel<NW, WM, TN, NS, DGRAD, Epi>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
     if (attr != hipSuccess) return attr;
-    const int tn = cdiv(cv.N, 64);
-    return launch_timed(kc, kern, dim3(cdiv(cv.M, BM) * tn), dim3(64 * NW), rows_lds(NW, WM, NS, c, cv.C), s, cv, epi, FastDiv(tn));
+    const int tn = cdiv(cv.N, 32 * TN);
+    return launch_timed(kc, kern, dim3(cdiv(cv.M, BM) * tn), dim3(64 * NW), rows_lds(NW, WM, TN, NS, c, cv.C), s, cv, epi, FastDiv(tn));
 }
 
-// Variants (waves, of them along the positions, stages of weights), by what bounds their tiles:
+// Variants (waves, of them along the positions, stages of weights; in front, a 1 for tiles of 32 columns instead of 64), by what bounds their tiles:
 //   443  256 positions, every wave all taps: the fewest copies of weights; two workgroups to a unit with one run of rows
 //   422  128 positions, two groups of waves: two workgroups to a unit
 //   823  128 positions, four groups: one workgroup with eight waves, for about as many tiles as units
 //   413  64 positions, four groups: for fewer tiles than that
+//  1413  the same in tiles of 32 columns, for at most half as many: twice the workgroups, with half as many copies, reads and multiplies in
+//        a step each (3 x 3 over 512 channels, forward / input gradient, 413 and 1413, us: 128 images of 2 x 2 15.0 / 16.4 and 12.1 / 14.5, 64 of
+//        4 x 4 15.5 / 16.3 and 12.5 / 14.8; over 256, 32 of 4 x 4 10.1 / 10.2 and 8.0 / 8.3; the gradient's copies are of 64 bytes in a row)
 // Estimated time (us) of a variant: rounds of the device (a last round that is not full counts half way) times a fixed part
-// (launch, the first copies, the sum of the groups' partial tiles, the epilogue) and the steps.  Fitted to 3 x 3 filters over 64 to 512
-// channels and 1 to 300 images of 2 x 2 to 224 x 224; the variant chosen is within 5 % of the best almost everywhere.
-static double rows_us(int nw, int wm, int ns, const ConvShape& c, int64_t M, int N, int C) {
-    const int lds = rows_lds(nw, wm, ns, c, C), kg = nw / wm;
+// (launch, the first copies, the sum of the groups' partial tiles, the epilogue) and the steps.  Fitted to 110 passes of 3 x 3 filters
+// (55 shapes, 64 to 512 channels, 1 to 512 images of 2 x 2 to 56 x 56); the variant chosen is within 0.2 % of the best of the five on average, at worst 5 %.
+static double rows_us(int variant, const ConvShape& c, int64_t M, int N, int C) {
+    const int tn = variant > 1000 ? 1 : 2, nw = variant / 100 % 10, wm = variant / 10 % 10, ns = variant % 10;
+    const int lds = rows_lds(nw, wm, tn, ns, c, C), kg = nw / wm;
     if (lds > kMaxLds) return 1e9;
-    const int per_cu = nw == 4 && wm > 1 && 2 * lds <= kMaxLds ? 2 : 1;
-    const double tiles = (double)cdiv(M, 64 * wm) * cdiv(N, 64), x = tiles / (kCUs * per_cu);
+    const int per_cu = nw == 4 && (wm > 1 || tn == 1) && 2 * lds <= kMaxLds ? 2 : 1;
+    const double tiles = (double)cdiv(M, 64 * wm) * cdiv(N, 32 * tn), x = tiles / (kCUs * per_cu);
     const double rounds = x <= 1.0 ? 1.0 : 0.5 * (x + ceil(x)), steps = (double)cdiv((int64_t)C / 64 * c.R * c.S, kg);
     const bool shared = per_cu == 2 && tiles > kCUs;
-    const double fixed = wm == 1 ? 5.0 : nw == 8 ? 6.0 : wm == 4 ? (shared ? 8.0 : 5.0) : (shared ? 7.0 : 3.0);
-    const double step = wm == 1 ? 0.68 : nw == 8 ? 0.88 : wm == 4 ? (shared ? 1.1 : 0.75) : 0.9;
+    double fixed, step;
+    switch (variant) {
+        case 1413: fixed = shared ? 3.4 : 3.9; step = shared ? 0.82 : 0.50; break;
+        case 413: fixed = 4.8; step = 0.62; break;
+        case 422: fixed = shared ? 6.3 : 4.5; step = shared ? 0.88 : 0.69; break;
+        case 443: fixed = shared ? 8.0 : 6.8; step = shared ? 0.95 : 0.44; break;
+        default: fixed = tiles > 0.875 * kCUs ? 8.5 : 6.0; step = 0.75; break;   // (a full round of them pays for copies that wait for each other)
+    }
     return rounds * (fixed + step * steps);
 }
 
@@ -50,11 +60,11 @@ int conv_rows_variant(const ConvShape& c, int64_t M, int N, int C, double other_
     int best = 0;
     // What the other kernels' plan estimates is too low for convolutions: over 84 passes of 3 x 3 filters (42 shapes, 3 to 128 images of
     // 2 x 2 to 100 x 100, 64 to 512 channels) they took 0.8 to 2.1 times as long, quartiles 1.07, 1.34 and 1.45.  The factor stands here
-    // because the choice among those kernels was fitted to the estimates as they are.  With it the kernel taken was within 1 % of the
-    // best one in nine passes of ten, at worst 16 % off (64 images of 2 x 2 x 512: 18.6 us against 16.1).
-    double best_us = 1.3 * other_us;
-    for (int v : {413, 422, 443, 823}) {
-        const double us = rows_us(v / 100, v / 10 % 10, v % 10, c, M, N, C);
+    // because the choice among those kernels was fitted to the estimates as they are.  In the 110 passes above the best variant
+    // took 0.41 to 0.95 of what they did.
+    double best_us = 2.0 * other_us;
+    for (int v : {1413, 413, 422, 443, 823}) {
+        const double us = rows_us(v, c, M, N, C);
         if (us < best_us) {
             best_us = us;
             best = v;
@@ -77,10 +87,11 @@ hipError_t conv_rows(int variant, int kc, const bf16_t* x, const bf16_t* w, cons
     cv.d_w = FastDiv(c.W);
     cv.d_s = FastDiv(c.S);
     switch (variant) {
-        case 413: return launch_rows<4, 1, 3, DGRAD>(kc, cv, epi, c, s);
-        case 443: return launch_rows<4, 4, 3, DGRAD>(kc, cv, epi, c, s);
-        case 823: return launch_rows<8, 2, 3, DGRAD>(kc, cv, epi, c, s);
-        default: return launch_rows<4, 2, 2, DGRAD>(kc, cv, epi, c, s);
+        case 413: return launch_rows<4, 1, 2, 3, DGRAD>(kc, cv, epi, c, s);
+        case 1413: return launch_rows<4, 1, 1, 3, DGRAD>(kc, cv, epi, c, s);
+        case 443: return launch_rows<4, 4, 2, 3, DGRAD>(kc, cv, epi, c, s);
+        case 823: return launch_rows<8, 2, 2, 3, DGRAD>(kc, cv, epi, c, s);
+        default: return launch_rows<4, 2, 2, 2, DGRAD>(kc, cv, epi, c, s);
     }
 }
 template hipError_t conv_rows<false, EpiBiasAct<bf16_t>>(int, int, const bf16_t*, const bf16_t*, const EpiBiasAct<bf16_t>&, const ConvShape&, hipStream_t);
