@@ -44,13 +44,14 @@ static double rows_us(int variant, const ConvShape& c, int64_t M, int N, int C) 
     const double tiles = (double)cdiv(M, 64 * wm) * cdiv(N, 32 * tn), x = tiles / (kCUs * per_cu);
     const double rounds = x <= 1.0 ? 1.0 : 0.5 * (x + ceil(x)), steps = (double)cdiv((int64_t)C / 64 * c.R * c.S, kg);
     const bool shared = per_cu == 2 && tiles > kCUs;
+    if (tn == 1 && tiles > 2 * kCUs) return 1e9;   // (a second round of half as much work each: never the best)
     double fixed, step;
     switch (variant) {
         case 1413: fixed = shared ? 3.4 : 3.9; step = shared ? 0.82 : 0.50; break;
         case 413: fixed = 4.8; step = 0.62; break;
         case 422: fixed = shared ? 6.3 : 4.5; step = shared ? 0.88 : 0.69; break;
         case 443: fixed = shared ? 8.0 : 6.8; step = shared ? 0.95 : 0.44; break;
-        default: fixed = tiles > 0.875 * kCUs ? 8.5 : 6.0; step = 0.75; break;   // (a full round of them pays for copies that wait for each other)
+        default: fixed = tiles > 0.95 * kCUs ? 8.5 : 6.0; step = 0.75; break;   // (a full round of them pays for copies that wait for each other)
     }
     return rounds * (fixed + step * steps);
 }
