@@ -279,6 +279,13 @@ int conv_rows_variant(const ConvShape& c, int64_t M, int N, int C, double other_
 template <bool DGRAD, class Epi>
 hipError_t conv_rows(int variant, int kc, const bf16_t* x, const bf16_t* w, const Epi& epi, const ConvShape& c, hipStream_t s);
 
+// Weight gradients on runs of rows (there too): k-slices (0: not to be taken) and the positions of each.
+struct WgradRowsPlan {
+    int slices, per_slice;
+};
+WgradRowsPlan conv_wgrad_rows_plan(const ConvShape& c, double other_us);
+hipError_t conv_wgrad_rows(const WgradRowsPlan& p, const bf16_t* dy, const bf16_t* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s);
+
 template <class T, class Epi>
 static hipError_t conv_forward_t(const T* x, const T* w, const Epi& epi, const ConvShape& c, float* ws, hipStream_t s) {
     const int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
@@ -333,6 +340,10 @@ template <class T> static hipError_t conv_wgrad_t(const T* dy, const T* x, float
     const int64_t K = (int64_t)c.B * c.Ho * c.Wo;
     constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
     if (c.Cin % V != 0 || c.Cout % V != 0 || !aligned16(dy) || !aligned16(x) || !small_enough(c)) return gather_conv_wgrad<T>(dy, x, gw, c, ws, s);
+    if constexpr (sizeof(T) == 2) {
+        const WgradRowsPlan p = conv_wgrad_rows_plan(c, plan_for(rows, cols, K, true, 2, kByKConv).cost / 2400.0);
+        if (p.slices && (p.slices == 1 ? aligned16(gw) : ws.ws && aligned16(ws.ws))) return conv_wgrad_rows(p, dy, x, gw, c, ws, s);
+    }
     const int rows_bk = BK / c.Wo;
     ConvWgradB2<T> Bv{x, geom2(c), cols, (int)K, BK % c.Wo, rows_bk % c.Ho, rows_bk / c.Ho};
     return run2_wgrad(kcConvWgrad, DenseRC<T>{dy, rows, (int)K, c.Cout}, Bv, gw, rows, cols, K, ws, s);

@@ -102,6 +102,7 @@ hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const 
                       const ConvShape& c, float* ws, hipStream_t s);
 hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c,
                       const Partials& ws, hipStream_t s);
+size_t conv_wgrad_workspace_elems(int dtype, const ConvShape& c);   // fp32, for its partial results
 
 // 2-D max pooling, channels-last, no padding.  Backward recomputes the winner (first maximum in
 // row-major window order) from the stored input; relu_mask: also zero where the input is <= 0.

@@ -2,6 +2,7 @@
 #include <math.h>
 
 #include "conv_rows.hip.h"
+#include "conv_wgrad_rows.hip.h"
 #include "gemm_dispatch.hip.h"
 
 namespace tmps {
@@ -98,5 +99,56 @@ hipError_t conv_rows(int variant, int kc, const bf16_t* x, const bf16_t* w, cons
 template hipError_t conv_rows<false, EpiBiasAct<bf16_t>>(int, int, const bf16_t*, const bf16_t*, const EpiBiasAct<bf16_t>&, const ConvShape&, hipStream_t);
 template hipError_t conv_rows<false, EpiConvAffine<bf16_t>>(int, int, const bf16_t*, const bf16_t*, const EpiConvAffine<bf16_t>&, const ConvShape&, hipStream_t);
 template hipError_t conv_rows<true, EpiMask<bf16_t, bf16_t>>(int, int, const bf16_t*, const bf16_t*, const EpiMask<bf16_t, bf16_t>&, const ConvShape&, hipStream_t);
+
+
+// Weight gradients: the number of k-slices with the least estimated time, which is rounds of the device times a fixed part and 128 positions at a time, and
+// what slices write and are added up for (5 TB/s).  Estimated, on this kernel and on the others (us): 128 images of 2 x 2 x 512 10.0, 10.6, 13.8, of
+// 4 x 4 x 512 21, 22, 29, of 8 x 8 x 256 27, 26, 30, of 16 x 16 x 128 27, 28, 31, of 32 x 32 x 64 27, 28, 40; 64 images of 56 x 56 x 64 32, 34,
+// 53, of 14 x 14 x 512 97, 94, 105, of 28 x 28 x 512 311, 300, 337; 8 of 7 x 7 x 512 10.0, 9.9, 12.6.  The other kernels' plan estimates up to 1.4 times
+// too little (see conv_rows_variant); with 1.5 the one taken is within 3 % of the better one in 29 of 30 shapes, in the other one 9 % off (7.5 us against 6.9).
+static int wgrad_run_groups(const ConvShape& c) { return (128 + 2 * c.W + 2 + 7) / 8; }
+
+WgradRowsPlan conv_wgrad_rows_plan(const ConvShape& c, double other_us) {
+    WgradRowsPlan best{0, 0};
+    if (c.R != 3 || c.S != 3 || c.stride != 1 || c.pad != 1 || c.Cin % 64 != 0 || c.Cout % 64 != 0 || !small_enough(c)) return best;
+    if (conv_wgrad_rows_lds(wgrad_run_groups(c)) > kMaxLds) return best;
+    const int64_t M = (int64_t)c.B * c.H * c.W, count = (int64_t)c.Cout * (9 * c.Cin + 1);
+    const int chunks = cdiv(M, 128), tiles = c.Cout / 64 * (c.Cin / 64) * 3;
+    double best_us = 1e9;
+    for (int s = 1; s <= 128 && s <= chunks; ++s) {
+        const int per = cdiv(chunks, s);
+        if (cdiv(chunks, per) != s) continue;
+        const double us = cdiv((int64_t)tiles * s, kCUs) * (6.3 + 0.93 * per) + (s > 1 ? 3.5 + s * count * 8.0 / 5e6 : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = WgradRowsPlan{s, per * 128};
+        }
+    }
+    return best_us < 1.5 * other_us ? best : WgradRowsPlan{0, 0};
+}
+
+hipError_t conv_wgrad_rows(const WgradRowsPlan& p, const bf16_t* dy, const bf16_t* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) {
+    ConvWgradRows cv;
+    cv.dy = dy;
+    cv.x = x;
+    cv.M = c.B * c.H * c.W;
+    cv.N = c.Cout; cv.C = c.Cin; cv.H = c.H; cv.W = c.W;
+    cv.run_groups = wgrad_run_groups(c);
+    cv.per_slice = p.per_slice;
+    const int per_row = c.Cin / 64 * 3, tiles = c.Cout / 64 * per_row;
+    cv.d_tiles = FastDiv(tiles);
+    cv.d_row = FastDiv(per_row);
+    cv.d_w = FastDiv(c.W);
+    cv.d_h = FastDiv(c.H);
+    const int64_t cols = (int64_t)9 * c.Cin, count = cols * c.Cout + c.Cout;
+    const EpiWgrad epi{p.slices > 1 ? ws.ws : gw, cols, cols * c.Cout, count};
+    const int lds = conv_wgrad_rows_lds(cv.run_groups);
+    auto kern = conv_wgrad_rows_kernel<kWgradStages>;
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+    if (attr != hipSuccess) return attr;
+    hipError_t e = launch_timed(kcConvWgrad, kern, dim3(tiles * p.slices), dim3(512), lds, s, cv, epi);
+    if (e != hipSuccess || p.slices <= 1) return e;
+    return ws.finish(Reduction{ws.ws, gw, count, p.slices, false}, s);
+}
 
 }  // namespace tmps

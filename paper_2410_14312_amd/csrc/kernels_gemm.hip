@@ -702,6 +702,14 @@ hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const 
                                 EpiMask<bf16_t, bf16_t>{(bf16_t*)dx, (const bf16_t*)mask, c.Cin, kActRelu, (const bf16_t*)add}, c, ws, s);
 }
 
+size_t conv_wgrad_workspace_elems(int dtype, const ConvShape& c) {
+    const int64_t cols = (int64_t)c.R * c.S * c.Cin, K = (int64_t)c.B * c.Ho * c.Wo;
+    const size_t n = gemm_workspace_elems(c.Cout, cols, K, kWsRowSums | (dtype == kBF16 ? 0 : kWsF32));
+    if (dtype != kBF16) return n;
+    const int slices = conv_wgrad_rows_plan(c, plan_for(c.Cout, (int)cols, K, true, 2, kByKConv).cost / 2400.0).slices;
+    return slices > 1 ? std::max(n, (size_t)slices * (size_t)(c.Cout * cols + c.Cout)) : n;
+}
+
 hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) {
     if (dtype != kBF16) return conv_wgrad_f32((const float*)dy, (const float*)x, gw, c, ws, s);
     if (pointwise(c)) return dense_wgrad_as(kcConvWgrad, dtype, dy, x, gw, c.B * c.Ho * c.Wo, c.Cin, c.Cout, ws, s);

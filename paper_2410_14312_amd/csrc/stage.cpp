@@ -145,7 +145,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 L.ws_fwd_elems = gemm_workspace_elems((int64_t)mb * c.Ho * c.Wo, c.Cout, kf, f32);
                 L.ws_elems = std::max({L.ws_fwd_elems,
                                        gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin, kd, f32),
-                                       L.part_elems = gemm_workspace_elems(c.Cout, kf, (int64_t)M * c.Ho * c.Wo, kWsRowSums | f32)});
+                                       L.part_elems = conv_wgrad_workspace_elems(cfg->dtype, c)});
                 if (c.stride == 2)   // (the input gradient may walk each position's own taps only)
                     L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin,
                                                                            (int64_t)((c.R + 1) / 2) * ((c.S + 1) / 2) * c.Cout, f32));

@@ -56,6 +56,7 @@ hipError_t sgd_momentum_keeping(float* w, float* buf, const float* g, void* wcop
 hipError_t cast_f32_to_bf16(const float* in, void* out, int64_t n, hipStream_t s) { return hipSuccess; }
 hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t) { memcpy(dst, src, bytes); return hipSuccess; }
 GemmPlan plan_gemm(int64_t, int64_t, int64_t) { return GemmPlan{64, 1}; }
+size_t conv_wgrad_workspace_elems(int, const ConvShape& c) { return (size_t)(2 * ((int64_t)c.Cout * c.R * c.S * c.Cin + c.Cout)); }
 size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t, int with_rowsum) { return (size_t)(2 * (M * N + (with_rowsum ? M : 0))); }
 size_t affine_workspace_elems(int64_t, int C) { return (size_t)(2 * C * 8); }
 size_t layernorm_workspace_elems(int64_t, int D) { return (size_t)(2 * D * 8); }
