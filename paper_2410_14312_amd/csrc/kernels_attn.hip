@@ -1,7 +1,7 @@
 // Causal multi-head self-attention for gfx950: forward and the query and key/value gradients.
 //
 // The MFMA path (32 or 64 features per head, bf16 or fp32) is a flash-style kernel: a wave owns 32 query rows (or 32 key
-// rows in the key/value-gradient kernel), streams blocks of keys (queries) through LDS and keeps running softmax
+// rows where the gradients of keys and values are formed), streams blocks of keys (queries) through LDS and keeps running softmax
 // statistics, so the S x S score matrix never exists in memory.  Products are arranged so that the softmax reduction runs
 // over a lane's own registers: scores are computed TRANSPOSED (keys along the accumulator registers, queries along the
 // lanes), and the probabilities leave the accumulators straight into the B operand of the next MFMA with no shuffle.
