@@ -192,6 +192,7 @@ struct G3Unit {
 // The units of one contraction.
 template <int BM, int BN, int BK, bool AKC, bool BKC, class Epi_> struct G3One {
     typedef Epi_ Epi;
+    static constexpr bool kTotals = false;
     G3Operand<AKC> A;
     G3Operand<BKC> B;
     Epi_ e;
@@ -351,6 +352,47 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) rs[i] = 0.0f;
         const bool sum_rows = ROWSUM && cur.first_col;
+        // kTotals: every `chain` k-tiles an accumulator is added to a second sum and starts again at zero, so that no sum takes a rounding for every
+        // multiply of a long contraction.  A row of accumulators at a time, in the first step of a k-tile, in front of its multiplies.
+        constexpr bool TOT = Work::kTotals;
+        f32x16_t tot[TOT ? TM : 1][TOT ? TN : 1];
+        float rs_tot[TOT ? TM : 1];
+        int chain = 1;
+        if constexpr (TOT) {
+            chain = work.chain;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                rs_tot[i] = 0.0f;
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) tot[i][j][r] = 0.0f;
+            }
+        }
+        auto add_to_totals = [&](int i) {
+            if constexpr (TOT) {
+                rs_tot[i] += rs[i];
+                rs[i] = 0.0f;
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; r += 4) {
+                        // Written out so that the accumulators stay in accumulation registers: left to itself the compiler moves all of them
+                        // back and forth in every k-tile.  (The multiplies that wrote them lie six multiplies back; a multiply that reads
+                        // them may follow two instructions behind.)
+                        float v[4], a[4] = {acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2], acc[i][j][r + 3]};
+                        asm volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\tv_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7\n\t"
+                                     "v_accvgpr_write_b32 %4, 0\n\tv_accvgpr_write_b32 %5, 0\n\tv_accvgpr_write_b32 %6, 0\n\tv_accvgpr_write_b32 %7, 0\n\t"
+                                     "s_nop 1"
+                                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "+a"(a[0]), "+a"(a[1]), "+a"(a[2]), "+a"(a[3]));
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            tot[i][j][r + q] += v[q];
+                            acc[i][j][r + q] = a[q];
+                        }
+                    }
+            }
+        };
 
         // What the epilogue reads from memory (a bias per column, a residual source or a mask per element), block by
         // block of 32 rows x 64 columns of this wave's results (block b: rows 32 (b / (TN / 2)), columns 64 (b % (TN / 2))).
@@ -427,6 +469,9 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
                             for (int c = g * CPS / NM; c < (g + 1) * CPS / NM; ++c) issue_group((nx - KK) * CPS + c);
                         }
                     }
+                    if constexpr (TOT) {
+                        if (kk == 0 && g % TN == 0 && ((kt - (g / TN) * chain / TM) & (chain - 1)) == 0) add_to_totals(g / TN);
+                    }
                     acc[g / TN][g % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk % NBUF][g / TN], bfr[kk % NBUF][g % TN], acc[g / TN][g % TN], 0, 0, 0);
                     if constexpr (ROWSUM) {
                         // Behind the fragment's first multiply, so that it is issued while that one runs; written as
@@ -452,6 +497,16 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
                 cstage = nstage;
             }
             asm volatile("; tmps k-tile end");
+        }
+        if constexpr (TOT) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                rs[i] += rs_tot[i];
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] += tot[i][j][r];
+            }
         }
 
         // ---- results ----
@@ -550,10 +605,17 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G
 // 3072 x 768) and runs in k-slices, whose fp32 partial sums cost as much as a third of its multiplies to write and add
 // up.  Together their tiles are walked in whole rounds of the device with no slices at all; only the tiles beyond the last whole round are cut
 // along k, into as many slices as fill a round, and summed by g3_group_sum_kernel.
+//
+// Precision: a sum that is added to once per multiply (16 rows) is, after n of them, 2^-24 sqrt(n / 6) (2-norm) from the sum in 64 bits: 5.7e-7 over
+// 8192 rows in one chain.  The slices of the launches this one replaces were chains of some 1000 rows (1.5 to 2.1e-7), so it has a second set of sums
+// (see kTotals): with chains of 2, 4 and 8 k-tiles below 1024, below 4096 and from 4096 rows on its errors are 0.7, 0.9, 1.0, 1.4, 1.5 and 1.6e-7 over 512,
+// 1024, .. 16384 rows, those of the layers' own launches 0.9, 1.3, 1.3 to 1.9, 1.9 to 2.7, 1.5 to 2.1 and 2.1 to 3.0e-7.  Two sets fit where there is one
+// wave to a SIMD: 256 x 128 tiles, four waves of 128 x 64, three stages (two: 8 % slower, the copies of a k-tile then have less than one to
+// arrive in).  Against 256 x 256 tiles with eight waves and one set that is 6 % for the totals and 16 % for copies and transposed reads, which LDS serves for half as
+// many multiplies: 12 layers of 768 features over 8192 rows 450 us instead of 356.  Totals in memory instead were estimated at the same.
+//
 // The four layers of a transformer block of 768 features over 8192 / 1024 rows, one block, two, three, four (us, launches of their own and one):
-// 196 and 135, 407 and 243, 611 and 362, 813 and 481 / 52 and 33, 105 and 40, 157 and 78, 214 and 80; the 32000 x 768 of a vocabulary over 8192 rows
-// 448 and 395.  Two mini-batches of GPT-2 small 24.2 -> 22.0 ms, three of its blocks as a stage 3.32 -> 3.04 ms, 1F1B order 23.3 -> 21.4 ms.
-// Sums over 8192 rows in one fp32 chain are 5.7e-7 (2-norm) from those in 64 bits, as the vocabulary's always were; those of 7 or 8 slices 1.9e-7.
+// 199 and 159, 413 and 316, 623 and 450, 828 and 580 / 52 and 32, 105 and 59, 157 and 84, 214 and 114; 20 of 1024 x 1024 over 1024 rows 195 and 89.
 constexpr int kG3GroupMax = 32;   // contractions of a launch (kernel arguments hold 4 KB)
 struct G3Job {
     const bf16_t* a;   // dY [K][M]
@@ -564,10 +626,12 @@ struct G3Job {
 };
 struct G3Group {
     typedef EpiWgrad Epi;
-    static constexpr int kTile = 256, kPart = kTile * kTile + kTile;   // floats of a partial tile: results, then row sums
+    static constexpr bool kTotals = true;
+    static constexpr int kRows = 256, kCols = 128, kPart = kRows * kCols + kRows;   // a tile; floats of a partial one: results, then row sums
     G3Job job[kG3GroupMax];
     int jobs, k_total, tiles, whole;   // tiles of all jobs; the first `whole` of them are not sliced
     int slices, k_per_slice;           // of the others
+    int chain;                         // k-tiles summed in one go, a power of two
     float* part;                       // [tiles - whole][slices][kPart]
     FastDiv d_cut;                     // by tiles - whole
 
@@ -578,8 +642,8 @@ struct G3Group {
         while (j + 1 < jobs && t >= job[j + 1].first_tile) ++j;
         uint32_t major, minor;
         job[j].d_minor.divmod((uint32_t)(t - job[j].first_tile), major, minor);
-        m0 = (int)(job[j].col_major ? minor : major) * kTile;
-        n0 = (int)(job[j].col_major ? major : minor) * kTile;
+        m0 = (int)(job[j].col_major ? minor : major) * kRows;
+        n0 = (int)(job[j].col_major ? major : minor) * kCols;
         return j;
     }
     __device__ __forceinline__ G3Unit unit(int u) const {
@@ -610,8 +674,8 @@ struct G3Group {
     __device__ __forceinline__ EpiWgrad epi(const G3Unit& g) const {
         const G3Job& j = job[g.job];
         if (g.z < 0) return EpiWgrad{j.out, j.N, (int64_t)j.M * j.N, 0};
-        const int64_t first = (int64_t)g.m0 * kTile + g.n0;
-        return EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kTile, first + kTile * kTile - g.m0, 0};
+        const int64_t first = (int64_t)g.m0 * kCols + g.n0;
+        return EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kCols, first + kRows * kCols - g.m0, 0};
     }
 };
 

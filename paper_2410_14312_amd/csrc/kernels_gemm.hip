@@ -381,62 +381,73 @@ static hipError_t launch3(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>&
 }
 
 // ---- weight gradients of several layers in one persistent launch (G3Group) --------------------------------------------------
-__global__ __launch_bounds__(512) void gemm3_kernel(G3Group work) { gemm3_walk<256, 256, 64, 2, 4, 2, false, false, true>(work); }
+constexpr int kG3GroupStages = 3;
+__global__ __launch_bounds__(256) void gemm3_kernel(G3Group work) {
+    gemm3_walk<G3Group::kRows, G3Group::kCols, 64, 2, 2, kG3GroupStages, false, false, true>(work);
+}
 
-// Adds up the slices of the cut tiles, in slice order: workgroup (r, y) takes 16 rows of cut tile r, a thread 4 columns of 4 rows.
+// Adds up the slices of the cut tiles, in slice order: workgroup (r, y) takes 32 rows of cut tile r, a thread 4 columns of 4 rows.
 __global__ __launch_bounds__(256) void g3_group_sum_kernel(G3Group work) {
+    constexpr int L = G3Group::kCols / 4, R = 256 / L;   // threads of a row, rows at a time
     const int r = blockIdx.x, tid = threadIdx.x;
     int m0, n0;
     const G3Job& j = work.job[work.place(work.whole + r, m0, n0)];
     const float* const p = work.part + (int64_t)r * work.slices * G3Group::kPart;
-    const int n = n0 + (tid & 63) * 4, row0 = blockIdx.y * 16 + (tid >> 6);
+    const int n = n0 + tid % L * 4, row0 = blockIdx.y * (4 * R) + tid / L;
     if (n < j.N) {
         float4 v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4*>(p + (row0 + 4 * i) * G3Group::kTile + (tid & 63) * 4);
+        for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4*>(p + (row0 + R * i) * G3Group::kCols + tid % L * 4);
         for (int z = 1; z < work.slices; ++z) {
             const float* const q = p + (int64_t)z * G3Group::kPart;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float4 w = *reinterpret_cast<const float4*>(q + (row0 + 4 * i) * G3Group::kTile + (tid & 63) * 4);
+                const float4 w = *reinterpret_cast<const float4*>(q + (row0 + R * i) * G3Group::kCols + tid % L * 4);
                 v[i].x += w.x; v[i].y += w.y; v[i].z += w.z; v[i].w += w.w;
             }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int m = m0 + row0 + 4 * i;
+            const int m = m0 + row0 + R * i;
             if (m < j.M) *reinterpret_cast<float4*>(j.out + (int64_t)m * j.N + n) = v[i];
         }
     }
     if (n0 == 0 && blockIdx.y == 0 && m0 + tid < j.M) {
         float v = 0.0f;
-        for (int z = 0; z < work.slices; ++z) v += p[(int64_t)z * G3Group::kPart + G3Group::kTile * G3Group::kTile + tid];
+        for (int z = 0; z < work.slices; ++z) v += p[(int64_t)z * G3Group::kPart + G3Group::kRows * G3Group::kCols + tid];
         j.out[(int64_t)j.M * j.N + m0 + tid] = v;
     }
 }
 
 // Estimates in us: 1.78 for a k-tile of a 256 x 256 tile (8192^3), 8 for a unit's prologue and epilogue, partial sums at 6 TB/s and a launch.
 constexpr double kG3KtileUs = 1.78, kG3UnitUs = 8.0;
+// The same of a 256 x 128 tile of a group, and for adding its accumulators to the totals (12 layers of 768 features over 1024 to 8192 rows).
+constexpr double kGroupKtileUs = 1.10, kGroupUnitUs = 9.0, kGroupTotalUs = 0.5;
 static double partial_sums_us(double slices, double elems) { return slices > 1 ? 3.0 + (slices + 1.0) * elems * 4.0 / 6e6 : 0.0; }
 
 struct G3GroupPlan {
-    int whole, slices, k_per_slice;
+    int whole, slices, k_per_slice, chain;
     double us;
 };
+// k-tiles that are summed in one go, of kt: about the square root of as many multiplies, with as many roundings in a chain as in the totals
+static int g3_group_chain(int64_t kt) { return kt < 16 ? 2 : kt < 64 ? 4 : 8; }
+static int64_t g3_group_tiles(int64_t M, int64_t N) { return (int64_t)cdiv(M, G3Group::kRows) * cdiv(N, G3Group::kCols); }
 // `whole` tiles (whole rounds of the device) unsliced, the others in the number of slices that is quickest.
 static G3GroupPlan g3_group_plan(int64_t tiles, int64_t K, int64_t ws_elems) {
     const int cus = compute_units();
     const int64_t kt = K / 64, full = tiles / cus;
-    G3GroupPlan best{0, 0, 0, 0.0};
+    const int chain = g3_group_chain(kt);
+    const double ktile_us = kGroupKtileUs + kGroupTotalUs / chain;
+    G3GroupPlan best{0, 0, 0, chain, 0.0};
     for (int64_t f = full > 0 ? full - 1 : 0; f <= full; ++f) {
         const int64_t whole = f * cus, cut = tiles - whole;
         for (int64_t want = 1; want <= 16; ++want) {
             if (want > 1 && (kt < want * 8 || cut == 0)) break;
             const int64_t per = cdiv(kt, want), slices = cdiv(kt, per), rounds = cdiv(cut * slices, cus);
             if (slices > 1 && cut * slices * G3Group::kPart > ws_elems) break;
-            const double us = (double)(f * kt + rounds * per) * kG3KtileUs + (double)(f + rounds) * kG3UnitUs +
-                              partial_sums_us((double)slices, (double)cut * 65536.0);
-            if (best.slices == 0 || us < best.us) best = {(int)whole, (int)slices, (int)per * 64, us};
+            const double us = (double)(f * kt + rounds * per) * ktile_us + (double)(f + rounds) * kGroupUnitUs +
+                              partial_sums_us((double)slices, (double)cut * G3Group::kRows * G3Group::kCols);
+            if (best.slices == 0 || us < best.us) best = {(int)whole, (int)slices, (int)per * 64, chain, us};
         }
     }
     return best;
@@ -455,14 +466,14 @@ bool dense_wgrad_groups(int dtype, int64_t rows, int Din, int Dout) {
            (int64_t)cdiv(Din, 256) * 256 * 3 <= (int64_t)Din * 4 && (int64_t)cdiv(Dout, 256) * 256 * 3 <= (int64_t)Dout * 4;
 }
 
-constexpr int64_t kGroupMaxElems = (int64_t)512 * G3Group::kPart;   // partial tiles of two rounds of the device
+constexpr int64_t kGroupMaxElems = (int64_t)1024 * G3Group::kPart;   // partial tiles of four rounds of the device
 
 int64_t dense_wgrad_group_elems(int64_t rows, const int (*dims)[2], int n) {
     if (n < 1 || n > kG3GroupMax) return -1;
     int64_t tiles = 0;
     double alone = 0.0;
     for (int i = 0; i < n; ++i) {
-        tiles += g3_tiles(dims[i][1], dims[i][0]);
+        tiles += g3_group_tiles(dims[i][1], dims[i][0]);
         alone += wgrad_alone_us(dims[i][1], dims[i][0], rows);
     }
     const G3GroupPlan p = g3_group_plan(tiles, rows, kGroupMaxElems);
@@ -478,24 +489,24 @@ hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_
     for (int i = 0; i < n; ++i) {
         const DenseWgradJob& j = jobs[i];
         if (!dense_wgrad_groups(dtype, rows, j.Din, j.Dout) || !aligned16(j.dy) || !aligned16(j.x) || !aligned16(j.gw)) return hipErrorInvalidValue;
-        const int tm = cdiv(j.Dout, 256), tn = cdiv(j.Din, 256), col_major = j.Din > j.Dout ? 1 : 0;
+        const int tm = cdiv(j.Dout, G3Group::kRows), tn = cdiv(j.Din, G3Group::kCols), col_major = j.Din > j.Dout ? 1 : 0;
         g.job[i] = G3Job{(const bf16_t*)j.dy, (const bf16_t*)j.x, j.gw, j.Dout, j.Din, tiles, col_major, FastDiv(col_major ? tm : tn)};
         tiles += tm * tn;
     }
     const G3GroupPlan p = g3_group_plan(tiles, rows, ws && aligned16(ws) ? ws_elems : 0);
     const int cut = tiles - p.whole;
     g.jobs = n; g.k_total = (int)rows; g.tiles = tiles; g.whole = p.whole; g.k_per_slice = p.k_per_slice; g.part = ws;
-    g.slices = p.slices;
+    g.slices = p.slices; g.chain = p.chain;
     if (p.slices == 1) g.whole = tiles;   // (one slice is the whole of k)
     g.d_cut = FastDiv(cut > 0 ? cut : 1);
-    constexpr int lds = gemm3_lds_bytes<256, 256, 64, 2>();
+    constexpr int lds = gemm3_lds_bytes<G3Group::kRows, G3Group::kCols, 64, kG3GroupStages>();
     void (*const kern)(G3Group) = gemm3_kernel;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     const int units = g.whole + (tiles - g.whole) * g.slices, slots = compute_units();
-    hipError_t e = launch_timed(kcDenseWgrad, kern, dim3(units < slots ? units : slots), dim3(512), lds, s, g);
+    hipError_t e = launch_timed(kcDenseWgrad, kern, dim3(units < slots ? units : slots), dim3(256), lds, s, g);
     if (e != hipSuccess || p.slices == 1) return e;
-    return launch_timed(kcSliceSum, g3_group_sum_kernel, dim3(cut, 16), dim3(256), 0, s, g);
+    return launch_timed(kcSliceSum, g3_group_sum_kernel, dim3(cut, G3Group::kRows / 32), dim3(256), 0, s, g);
 }
 
 // ---------------------------------------------------------------------------------------- dense

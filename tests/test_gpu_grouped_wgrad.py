@@ -9,7 +9,7 @@ from paper_2410_14312_amd import load_library
 from tests.test_gpu_stage import run_stage_case
 from workloads.configs import layernorm, linear, softmax_ce, transformer_block
 
-PART = 256 * 256 + 256   # floats of a partial tile
+PART = 256 * 128 + 256   # floats of a partial tile
 
 
 def group_elems(widths, rows):
@@ -19,8 +19,10 @@ def group_elems(widths, rows):
     return f(C.c_int64(rows), (C.c_int * len(dims))(*dims), len(dims) // 2)
 
 
-# widths, rows, partial tiles: none; 40 of 42 tiles' slices; a ragged last tile in both directions; a whole round and 64 tiles in two slices
-CASES = [([768, 2304, 768, 3072, 768], 512, 0), ([1024] * 5, 4096, 256), ([1032, 2048, 776, 1288], 2048, None), ([1024] * 21, 1024, 128)]
+# widths, rows, partial tiles: none; 128 tiles in two slices; a ragged last tile in both directions; more than two rounds; a whole round and 64 tiles in
+# two slices; the same with ragged ones among them; 25 k-tiles, which chains of 4 do not divide, in slices of 13 and 12
+CASES = [([768, 2304, 768, 3072, 768], 512, 0), ([1024] * 5, 4096, 256), ([1032, 2048, 776, 1288], 2048, None), ([1024] * 21, 1024, None),
+         ([1024] * 11, 1024, 128), ([1032, 1040, 776] * 3 + [1032], 1024, 184), ([1024] * 5, 1600, 256)]
 
 
 @pytest.mark.parametrize("widths,rows,parts", CASES)
@@ -37,6 +39,45 @@ def test_the_rule_leaves_few_or_short_ones_alone():
 @pytest.mark.parametrize("widths,rows,parts", CASES)
 def test_grouped_weight_gradients(widths, rows, parts):
     run_stage_case([linear(a, b, False, rows=rows // 4) for a, b in zip(widths, widths[1:])], "bf16", 2, 2, seed=rows, deep=len(widths) > 10)
+
+
+# rows, k-tiles of 64 that are summed in one go
+CHAINS = [(512, 2), (960, 2), (1024, 4), (1600, 4), (4032, 4), (4096, 8), (8192, 8)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,chain", CHAINS)
+def test_long_sums_are_as_exact_as_short_ones(rows, chain):
+    """The last layer's gradient of a group against the sum of the same bf16 products in 64 bits.  A sum of random terms that takes n roundings on its
+    way is 2^-24 sqrt(n / 6) from it (each rounding 2^-24 / sqrt(3) of the sum so far, whose square grows evenly): a chain of `chain` k-tiles takes four
+    roundings a k-tile, the sum of the chains one each; a quarter more is allowed."""
+    import torch
+    from paper_2410_14312_amd import Stage
+
+    widths = [768, 2304, 768, 3072, 768]
+    assert group_elems(widths, rows) >= 0
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(rows)
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    specs = [linear(a, b, False) for a, b in zip(widths, widths[1:])]
+    p = [{"w": (randn(b, a) / a ** 0.5).cpu().numpy(), "b": np.zeros(b, np.float32)} for a, b in zip(widths, widths[1:])]
+    x = randn(rows, widths[0]).bfloat16()
+    dy = (randn(rows, widths[-1]) / rows).bfloat16()
+    below = Stage(specs[:-1], "bf16", rows, 1, 1, 0.1, 0.9, borrow_input=True)   # (the last layer's input)
+    below.set_params(p[:-1])
+    mid = torch.empty(rows, widths[-2], dtype=torch.bfloat16, device="cuda:0")
+    below.forward_micro(0, x, y=mid)
+    st = Stage(specs, "bf16", rows, 1, 1, 0.1, 0.9, borrow_input=True)
+    st.set_params(p)
+    st.forward_micro(0, x)
+    st.backward([0], dy=dy)
+    torch.cuda.synchronize()
+    got = st.get_grads()[-1]
+    want = (dy.double().t().contiguous() @ mid.double()).cpu().numpy()
+    bound = 1.25 * 2.0 ** -24 * ((4 * chain + rows / 64 / chain) / 6) ** 0.5
+    assert np.linalg.norm(got["w"] - want) < bound * np.linalg.norm(want)
+    want = dy.double().sum(0).cpu().numpy()
+    assert np.linalg.norm(got["b"] - want) < bound * np.linalg.norm(want)
 
 
 @pytest.mark.gpu
