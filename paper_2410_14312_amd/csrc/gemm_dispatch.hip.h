@@ -283,7 +283,7 @@ hipError_t conv_rows(int variant, int kc, const bf16_t* x, const bf16_t* w, cons
 struct WgradRowsPlan {
     int slices, per_slice;
 };
-WgradRowsPlan conv_wgrad_rows_plan(const ConvShape& c, double other_us);
+WgradRowsPlan conv_wgrad_rows_plan(const ConvShape& c, const Plan2& other);
 hipError_t conv_wgrad_rows(const WgradRowsPlan& p, const bf16_t* dy, const bf16_t* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s);
 
 template <class T, class Epi>
@@ -341,7 +341,7 @@ template <class T> static hipError_t conv_wgrad_t(const T* dy, const T* x, float
     constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
     if (c.Cin % V != 0 || c.Cout % V != 0 || !aligned16(dy) || !aligned16(x) || !small_enough(c)) return gather_conv_wgrad<T>(dy, x, gw, c, ws, s);
     if constexpr (sizeof(T) == 2) {
-        const WgradRowsPlan p = conv_wgrad_rows_plan(c, plan_for(rows, cols, K, true, 2, kByKConv).cost / 2400.0);
+        const WgradRowsPlan p = conv_wgrad_rows_plan(c, plan_for(rows, cols, K, true, 2, kByKConv));
         if (p.slices && (p.slices == 1 ? aligned16(gw) : ws.ws && aligned16(ws.ws))) return conv_wgrad_rows(p, dy, x, gw, c, ws, s);
     }
     const int rows_bk = BK / c.Wo;

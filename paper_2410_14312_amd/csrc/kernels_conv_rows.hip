@@ -104,27 +104,36 @@ template hipError_t conv_rows<true, EpiMask<bf16_t, bf16_t>>(int, int, const bf1
 // Weight gradients: the number of k-slices with the least estimated time, which is rounds of the device times a fixed part and 128 positions at a time, and
 // what slices write and are added up for (5 TB/s).  Estimated, on this kernel and on the others (us): 128 images of 2 x 2 x 512 10.0, 10.6, 13.8, of
 // 4 x 4 x 512 21, 22, 29, of 8 x 8 x 256 27, 26, 30, of 16 x 16 x 128 27, 28, 31, of 32 x 32 x 64 27, 28, 40; 64 images of 56 x 56 x 64 32, 34,
-// 53, of 14 x 14 x 512 97, 94, 105, of 28 x 28 x 512 311, 300, 337; 8 of 7 x 7 x 512 10.0, 9.9, 12.6.  The other kernels' plan estimates up to 1.4 times
+// 53, of 28 x 28 x 512 311, 300, 337; 8 of 7 x 7 x 512 10.0, 9.9, 12.6.  The other kernels' plan estimates up to 1.4 times
 // too little (see conv_rows_variant); with 1.5 the one taken is within 3 % of the better one in 29 of 30 shapes, in the other one 9 % off (7.5 us against 6.9).
+// A wave rounds a sum twice a chunk.  A slice has no more chunks than 64, which leaves its sums 2.75e-7 (2-norm) from those in 64 bits, or than make as many
+// roundings as the other kernels' plan would.  Unlimited, the slice of 98 chunks that 64 images of 14 x 14 x 512 made and the one of 128 of 256
+// images of 8 x 8 x 512 were 3.3 and 3.8e-7 off, the other kernels 2.7 and 3.0e-7; in four slices they are
+// 1.6 and 1.8e-7 off and take no longer (103 and 118 us; in one 105 and 122).
+static int64_t roundings(const Plan2& p, int64_t K) {
+    const int chains = p.kind == kByK ? 4 : p.kind == kAsync || p.bm * p.bn == 4096 ? 2 : 1;   // waves or wave groups by k, alternating accumulators
+    return cdiv(K, (int64_t)16 * p.slices * chains);
+}
 static int wgrad_run_groups(const ConvShape& c) { return (128 + 2 * c.W + 2 + 7) / 8; }
 
-WgradRowsPlan conv_wgrad_rows_plan(const ConvShape& c, double other_us) {
+WgradRowsPlan conv_wgrad_rows_plan(const ConvShape& c, const Plan2& other) {
     WgradRowsPlan best{0, 0};
     if (c.R != 3 || c.S != 3 || c.stride != 1 || c.pad != 1 || c.Cin % 64 != 0 || c.Cout % 64 != 0 || !small_enough(c)) return best;
     if (conv_wgrad_rows_lds(wgrad_run_groups(c)) > kMaxLds) return best;
     const int64_t M = (int64_t)c.B * c.H * c.W, count = (int64_t)c.Cout * (9 * c.Cin + 1);
+    const int64_t other_chunks = roundings(other, M) / 2, most = other_chunks > 64 ? other_chunks : 64;
     const int chunks = cdiv(M, 128), tiles = c.Cout / 64 * (c.Cin / 64) * 3;
     double best_us = 1e9;
     for (int s = 1; s <= 128 && s <= chunks; ++s) {
         const int per = cdiv(chunks, s);
-        if (cdiv(chunks, per) != s) continue;
+        if (cdiv(chunks, per) != s || per > most) continue;
         const double us = cdiv((int64_t)tiles * s, kCUs) * (6.3 + 0.93 * per) + (s > 1 ? 3.5 + s * count * 8.0 / 5e6 : 0.0);
         if (us < best_us) {
             best_us = us;
             best = WgradRowsPlan{s, per * 128};
         }
     }
-    return best_us < 1.5 * other_us ? best : WgradRowsPlan{0, 0};
+    return best_us < 1.5 * other.cost / 2400.0 ? best : WgradRowsPlan{0, 0};
 }
 
 hipError_t conv_wgrad_rows(const WgradRowsPlan& p, const bf16_t* dy, const bf16_t* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) {

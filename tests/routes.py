@@ -73,3 +73,22 @@ def conv_routes(sp, dtype, micro, N):
         v = rows(C.byref(shape), m, n, c, plan(m, n, taps * c, False, 2, CONV).cost / 2400.0) if dtype == "bf16" else 0
         out.append("rows %d" % v if v else _route(m, n, taps * c, FORWARD, e, CONV))
     return out[0], out[1], _route(cout, taps * cin, micro * N * ho * wo, WEIGHT, e, CONV)
+
+
+class _RowsPlan(C.Structure):
+    _fields_ = [("slices", C.c_int), ("per_slice", C.c_int)]
+
+
+def conv_wgrad_plan(sp, samples):
+    """What the weight gradient of a convolution runs on where it is not the kernel on runs of rows."""
+    ho, wo = ((sp[k] + 2 * sp["pad"] - sp[f]) // sp["stride"] + 1 for k, f in (("h", "r"), ("w", "s")))
+    return _functions()[0](sp["cout"], sp["r"] * sp["s"] * sp["cin"], samples * ho * wo, True, 2, CONV)
+
+
+def conv_wgrad_rows(sp, samples):
+    """k-slices and positions of each of a weight gradient on runs of rows (bf16); no slices: it runs on another kernel."""
+    f = getattr(load_library(), "_ZN4tmps20conv_wgrad_rows_planERKNS_9ConvShapeERKNS_5Plan2E")
+    f.restype, f.argtypes = _RowsPlan, [C.POINTER(_Conv), C.POINTER(_Plan)]
+    ho, wo = ((sp[k] + 2 * sp["pad"] - sp[r]) // sp["stride"] + 1 for k, r in (("h", "r"), ("w", "s")))
+    shape = _Conv(samples, sp["h"], sp["w"], sp["cin"], ho, wo, sp["cout"], sp["r"], sp["s"], sp["stride"], sp["pad"])
+    return f(C.byref(shape), C.byref(conv_wgrad_plan(sp, samples)))
