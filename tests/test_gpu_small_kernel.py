@@ -1,6 +1,7 @@
 """The small contraction kernel's tiles of 16 x 16, 16 x 32 and 32 x 32 outputs, with eight and with four waves, at their remainders: rows, columns
 and k that are no whole tile or step, single ones, a k shorter than a step, and the tile sizes' own limits.  Against the oracle (a stage of one
-layer: forward pass, and the weight gradient where it is a launch of its own); which tiles a size takes is asked of the library."""
+layer: forward pass, and the weight gradient where it is a launch of its own); which tiles a size takes is asked of the library.
+And the forward pass in fp32 against the sums in 64 bits."""
 import ctypes as C
 
 import pytest
@@ -37,3 +38,25 @@ def test_tiles(dtype, rows, din, dout, want):
 @pytest.mark.parametrize("rows,din,dout,want", SIZES)
 def test_small_kernel(dtype, rows, din, dout, want):
     run_stage_case([linear(din, dout, True)], dtype, rows, 1, seed=rows + din + dout)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,din,dout", [(47, 1000, 1000), (235, 1000, 1000), (256, 1024, 1000), (33, 1370, 100), (16, 1600, 16)])
+def test_sums_of_long_contractions(rows, din, dout):
+    """Chains of at most 16 roundings (six steps of one multiply, two roundings each, for each of four accumulators, and their sum), one for every six
+    steps of a wave and one for every wave: as far from the sum in 64 bits as a chain of 28, 2^-24 sqrt(28 / 6) (2-norm; each rounding is 2^-24 / sqrt(3)
+    of the sum so far, whose square grows evenly).  One chain to a wave: twice as many and more, from 1000 features on."""
+    import numpy as np
+    import torch
+    from paper_2410_14312_amd import Stage
+
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(din)
+    w = torch.randn(dout, din, generator=gen, device="cuda:0") / din ** 0.5
+    x = torch.randn(rows, din, generator=gen, device="cuda:0")
+    st = Stage([linear(din, dout, False)], "f32", rows, 1, 1, 0.1, 0.9, borrow_input=True)
+    st.set_params([{"w": w.cpu().numpy(), "b": np.zeros(dout, np.float32)}])
+    y = torch.empty(rows, dout, device="cuda:0")
+    st.forward_micro(0, x, y=y)
+    want = x.double() @ w.double().t().contiguous()
+    assert (y.double() - want).norm() < 2.0 ** -24 * (28 / 6) ** 0.5 * want.norm()
