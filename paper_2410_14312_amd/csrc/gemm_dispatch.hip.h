@@ -249,10 +249,10 @@ int backward_kind(int64_t B, int64_t Din, int64_t Dout, int esize);
 int small_backward_tile(int64_t M, int64_t N, int esize);   // 1 or 2: tiles of 16 x 16 or 32 x 32 outputs
 template <int TX, int TW, class T>
 static hipError_t small_backward_inst(int kc, const T* dy, const T* x, const T* w, float* gw, const EpiMask<T, T>& epi, int B, int Din, int Dout, hipStream_t s) {
-    const int split = cdiv(Din, 16 * TX) * cdiv(B, 16 * TX), grid = split + cdiv(Din, 16 * TW) * cdiv(Dout, 16 * TW);
+    const int of_x = cdiv(Din, 16 * TX) * cdiv(B, 16 * TX), of_w = cdiv(Din, 16 * TW) * cdiv(Dout, 16 * TW), grid = of_x + of_w;
     constexpr int lx = small_lds_floats(4, TX, TX), lw = small_lds_floats(4, TW, TW);
     return launch_timed(kc, gemm_small_backward_kernel<4, TX, TW, T>, dim3(grid), dim3(256), (lx > lw ? lx : lw) * 4, s, dy, x, w, epi,
-                        EpiWgrad{gw, Din, (int64_t)Dout * Din, 0}, B, Din, Dout, split);
+                        EpiWgrad{gw, Din, (int64_t)Dout * Din, 0}, B, Din, Dout, Dout >= B ? of_x : of_w);
 }
 template <class T>
 static hipError_t small_backward_t(int kc, const T* dy, const T* x, const T* w, float* gw, const EpiMask<T, T>& epi, int B, int Din, int Dout, hipStream_t s) {

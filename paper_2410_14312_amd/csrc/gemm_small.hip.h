@@ -212,15 +212,17 @@ __global__ __launch_bounds__(64 * NW, sizeof(typename AOp::T) == 4 ? 3 : 1) void
     gemm_small_tile<NW, TM, TN, ROWSUM>(A, B, epi, M, N, K, blockIdx.x, blockIdx.y);
 }
 
-// Input and weight gradient of a dense layer in one launch: dx[B, Din] = dy w (the first `split` workgroups, the longer contractions
-// where a batch is small) and gw[Dout, Din] = dy^T x.  Neither depends on the other, and a launch of its own costs each more than its work:
-// 32 x 64 -> 128 in fp32 2.5 us against 4.4 in two launches (the rule, backward_kind, has the others).
+// Input and weight gradient of a dense layer in one launch: dx[B, Din] = dy w and gw[Dout, Din] = dy^T x, the longer contraction by the first
+// `split` workgroups, since the launch lasts as long as the last of them (weight gradients last and first, us: fp32 916 x 1336 -> 136 28.8 and 15.9,
+// 2299 x 456 -> 32 13.0 and 11.1; bf16 2192 x 752 -> 24 13.5 and 8.2, 2752 x 288 -> 560 23.0 and 15.8).  Neither depends on the other, and
+// a launch of its own costs each more than its work: 32 x 64 -> 128 in fp32 2.5 us against 4.4 in two launches (the rule, backward_kind, has the others).
 // (TX, TW: tiles of 16 TX square outputs of dx and 16 TW square ones of gw)
 template <int NW, int TX, int TW, class T>
-__global__ __launch_bounds__(64 * NW) void gemm_small_backward_kernel(const T* dy, const T* x, const T* w, EpiMask<T, T> ex, EpiWgrad ew,
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 3 : 1) void gemm_small_backward_kernel(const T* dy, const T* x, const T* w, EpiMask<T, T> ex, EpiWgrad ew,
                                                                       int rows, int Din, int Dout, int split) {
-    const int b = blockIdx.x;
-    if (b < split) {
+    const bool early = (int)blockIdx.x < split;
+    const int b = early ? blockIdx.x : blockIdx.x - split;
+    if (early == (Dout >= rows)) {
         const int tiles_n = (Din + 16 * TX - 1) / (16 * TX), by = b / tiles_n, bx = b - by * tiles_n;
         gemm_small_tile<NW, TX, TX, false>(SmallOperand<T, true>{dy, rows, Dout}, SmallOperand<T, false>{w, Din, Din}, ex, rows, Din, Dout, bx, by);
     } else {

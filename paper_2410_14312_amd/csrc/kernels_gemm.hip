@@ -643,10 +643,13 @@ double two_backward_us(int64_t B, int64_t Din, int64_t Dout, int esize) {
     return alone(B, Din, Dout, false) + 2.0 + alone(Dout, Din, B, true) + (double)Din * Dout * 4.0 / 6e6;
 }
 
-// What the gradients of a dense layer run on: kTwo launches, or one of the small or of the tiled kernel.
+// What the gradients of a dense layer run on: kTwo launches, or one of the small or of the tiled kernel.  The tiled kernel's takes up to 1024 rows and the
+// small one's up to 5120 in bf16, for which the estimates hold.  Beyond, its weight gradients are sums over all rows in one workgroup, where the launches they
+// replace have slices: in one launch and in two (kernels alone, us) 4096 x 1024 -> 512 34.4 and 25.3, 1920 x 1920 -> 384 23.2 and 20.8, 2326 x 560 -> 856 22.8 and 26.9, with
+// errors of 2.7e-7, 1.9e-7 and 2.0e-7 (2-norm, against 64 bits) instead of 1.3e-7, 0.9e-7 and 1.0e-7; 8115 x 24 -> 1960, small, 40.3 and 23.6, 6328 x 64 -> 800 24.2 and 20.1.
 int backward_kind(int64_t B, int64_t Din, int64_t Dout, int esize) {
-    const double two = two_backward_us(B, Din, Dout, esize), small = small_backward_us(B, Din, Dout, esize);
-    const double tiled = esize == 2 && Din % 8 == 0 && Dout % 8 == 0 ? tiled_backward_us(B, Din, Dout) / 0.95 : 1e9;
+    const double two = two_backward_us(B, Din, Dout, esize), small = esize == 4 || B <= 5120 ? small_backward_us(B, Din, Dout, esize) : 1e9;
+    const double tiled = esize == 2 && Din % 8 == 0 && Dout % 8 == 0 && B <= 1024 ? tiled_backward_us(B, Din, Dout) / 0.95 : 1e9;
     if (small >= two && tiled >= two) return kTwo;
     return small <= tiled ? kOneSmall : kOneTiled;
 }
