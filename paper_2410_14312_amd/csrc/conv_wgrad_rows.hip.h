@@ -158,9 +158,12 @@ __global__ __launch_bounds__(512, 2) void conv_wgrad_rows_kernel(ConvWgradRows c
         }
         if (sum_rows && wc == 0) {
 #pragma unroll
-            for (int f = 0; f < NF; ++f)
+            for (int n = 0; n < 2; ++n) {   // (a sum of the chunk's own first: a slice's takes one rounding for each chunk)
+                float chunk_sum = 0.0f;
 #pragma unroll
-                for (int n = 0; n < 2; ++n) rs[n] = add_frag(rs[n], cur.a[f][n]);
+                for (int f = 0; f < NF; ++f) chunk_sum = add_frag(chunk_sum, cur.a[f][n]);
+                rs[n] += chunk_sum;
+            }
         }
         read_places(s2);
         put(chunk + NS, stage);

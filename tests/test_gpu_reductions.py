@@ -1,6 +1,6 @@
 """Sums of partial results in one launch, any number and mix of them: outputs in 16-byte pieces and ragged ones, few slices and many rows,
 more sums than a launch takes.  Each is a sum of fp32 values in a fixed order: against fp64, the error of n additions, n 2^-24 relative to the sum of
-the absolute values; and a sum among others equals the same sum alone bit for bit."""
+the absolute values, and the error of as long a chain as each form really has; and a sum among others equals the same sum alone bit for bit."""
 import ctypes as C
 
 import numpy as np
@@ -60,3 +60,20 @@ def test_sums(n):
         keep[k][1].fill_(7.0)
         reduce_all([jobs[k]])
         assert torch.equal(before, keep[k][1])
+
+
+@pytest.mark.parametrize("count,slices,rows,odd", [(4096, 128, False, 0), (4096, 128, False, 1), (4096, 1024, True, 0), (4096, 1025, True, 1)])
+def test_partial_results_are_added_in_pairs(count, slices, rows, odd):
+    """The totals of eight are added up in a chain, by sixteen lanes of rows where rows are added up, whose sums are added in pairs again.  A chain of n
+    additions of random terms is 2^-24 sqrt(n / 6) (2-norm) from the sum in 64 bits, a level of pairs as far as a chain of two; a tenth more is allowed."""
+    import torch
+
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(slices)
+    flat = torch.randn(slices * count + 1, generator=gen, device="cuda:0")
+    part, out = flat[odd:odd + slices * count], torch.zeros(count + 1, device="cuda:0")
+    reduce_all([_Reduction(part.data_ptr(), out.data_ptr() + 4 * odd, count, slices, rows)])
+    want = part.view(slices, count).double().sum(0)
+    chain = slices / (8 * 16) + 4 * 2 if rows else slices / 8
+    bound = 1.1 * 2.0 ** -24 * ((chain + 3 * 2) / 6) ** 0.5
+    assert (out[odd:odd + count].double() - want).norm() < bound * want.norm()
