@@ -51,12 +51,39 @@ def _route(M, N, K, which, esize, operands):
     return KINDS[p.kind] + (" split" if p.slices > 1 else "")
 
 
+def dense_backward_kind(rows, din, dout, dtype):
+    """What both gradients of a dense layer run on: 0 two launches, 1 / 2 one of the small / the tiled kernel."""
+    f = getattr(load_library(), "_ZN4tmps13backward_kindEllli")
+    f.restype, f.argtypes = C.c_int, [C.c_long, C.c_long, C.c_long, C.c_int]
+    return f(rows, din, dout, 2 if dtype == "bf16" else 4)
+
+
+def dense_waits(rows, din, dout, dtype):
+    """Whether the weight gradient of a stage's only dense layer waits for the launch at the end of a backward pass."""
+    lib = load_library()
+    asked, elems = getattr(lib, "_ZN4tmps18dense_wgrad_groupsEilii"), getattr(lib, "_ZN4tmps23dense_wgrad_group_elemsElPA2_Kii")
+    asked.restype, elems.restype = C.c_bool, C.c_int64
+    return asked(C.c_int(1 if dtype == "bf16" else 0), C.c_long(rows), din, dout) and elems(C.c_long(rows), (C.c_int * 2)(din, dout), 1) >= 0
+
+
 def dense_routes(sp, dtype, micro, N):
-    """(forward, input gradient, weight gradient) of a linear layer whose widths are whole 16-byte chunks."""
+    """(forward, input gradient, weight gradient) of a linear layer whose widths are whole 16-byte chunks, alone in a stage that hands a gradient down."""
     e, rows = 2 if dtype == "bf16" else 4, sp.get("rows", 1)
     din, dout, mb, M = sp["din"], sp["dout"], micro * rows, micro * N * rows
     assert din % (16 // e) == 0 and dout % (16 // e) == 0
-    return _route(mb, dout, din, FORWARD, e, DENSE), _route(M, din, dout, INPUT, e, DENSE), _route(dout, din, M, WEIGHT, e, DENSE)
+    forward, dx, gw = _route(mb, dout, din, FORWARD, e, DENSE), _route(M, din, dout, INPUT, e, DENSE), _route(dout, din, M, WEIGHT, e, DENSE)
+    if dense_waits(M, din, dout, dtype):
+        return forward, dx, "grouped"
+    kind = dense_backward_kind(M, din, dout, dtype)
+    return (forward,) + ((dx, gw), ("joint small",) * 2, ("joint tiled",) * 2)[kind]
+
+
+def pointwise_routes(sp, dtype, micro, N):
+    """The same of a 1 x 1 convolution with unit stride (the same contractions over its positions, always one to a launch)."""
+    e, rows = 2 if dtype == "bf16" else 4, sp["h"] * sp["w"]
+    assert sp["r"] == sp["s"] == sp["stride"] == 1 and sp["pad"] == 0 and sp["cin"] % (16 // e) == 0 and sp["cout"] % (16 // e) == 0
+    mb, M, cin, cout = micro * rows, micro * N * rows, sp["cin"], sp["cout"]
+    return _route(mb, cout, cin, FORWARD, e, DENSE), _route(M, cin, cout, INPUT, e, DENSE), _route(cout, cin, M, WEIGHT, e, DENSE)
 
 
 def conv_routes(sp, dtype, micro, N):
@@ -72,6 +99,8 @@ def conv_routes(sp, dtype, micro, N):
         shape = _Conv(B, sp["h"], sp["w"], cin, ho, wo, cout, sp["r"], sp["s"], sp["stride"], sp["pad"])
         v = rows(C.byref(shape), m, n, c, plan(m, n, taps * c, False, 2, CONV).cost / 2400.0) if dtype == "bf16" else 0
         out.append("rows %d" % v if v else _route(m, n, taps * c, FORWARD, e, CONV))
+    if dtype == "bf16" and conv_wgrad_rows(sp, micro * N).slices:
+        return out[0], out[1], "rows"
     return out[0], out[1], _route(cout, taps * cin, micro * N * ho * wo, WEIGHT, e, CONV)
 
 

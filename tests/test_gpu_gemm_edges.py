@@ -20,6 +20,7 @@ DENSE = [
     (1000, 10, 235, 1),    # a narrow output layer
     (72, 2601, 40, 2),     # odd output: ragged rows of dY in both gradients
     (1001, 1003, 300, 1),  # ragged everywhere, tiled
+    (1001, 1003, 375, 4),  # the same with gradients in launches of their own
     (264, 520, 700, 1),    # fp32 tiles of several sizes, ragged last tiles
     (2048, 96, 512, 1),    # few tiles, long k: k-slices
 ]
