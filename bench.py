@@ -25,13 +25,15 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 
 
-def algorithmic_work(cfg, only_stage=None, passes=None):
+def algorithmic_work(cfg, only_stage=None, passes=None, joint=None):
     """Per kernel class and per mini-batch: (launches, FLOPs, algorithmic bytes) from the shapes alone
     (of every stage, or of stage `only_stage` alone).
 
     passes: forward passes that a mini-batch is made in, on average over the layers.  A pass over one micro-batch each
     (the default, N passes) and a pass over several make the same FLOPs and move the same rows; each pass launches a layer's
     kernel once and reads its weights once.
+
+    joint(dtype, rows, din, dout): whether both gradients of a dense layer are one launch, which then counts as "dense_backward".
 
     Dense GEMMs count 2*rows*Din*Dout FLOPs and their operand/result bytes once; the update counts
     22 bytes per parameter in bf16 stages (read w, buf, g fp32; write w, buf fp32 and the bf16 copy)
@@ -58,9 +60,11 @@ def algorithmic_work(cfg, only_stage=None, passes=None):
                 osz = 4 if (li + 1 < len(st) and st[li + 1]["kind"] == "softmax_ce") else asz
                 extra = (1 if sp.get("skip") else 0) + (1 if sp.get("act") == "gelu" else 0)   # residual read, z write
                 add("dense_fwd", F, 2.0 * rb * din * dout, F * din * dout * asz + rb * (din * asz + dout * (osz + extra * asz)))
-                add("dense_wgrad", 1, 2.0 * rb * din * dout, rb * (din + dout) * asz + (din * dout + dout) * 4)
-                if not (si == 0 and li == 0):
-                    add("dense_dgrad", 1, 2.0 * rb * din * dout, rb * (din + dout) * asz + din * dout * asz)
+                first = si == 0 and li == 0
+                both = joint is not None and not first and joint(cfg.dtype, rb, din, dout)
+                add("dense_backward" if both else "dense_wgrad", 1, 2.0 * rb * din * dout, rb * (din + dout) * asz + (din * dout + dout) * 4)
+                if not first:
+                    add("dense_backward" if both else "dense_dgrad", 0 if both else 1, 2.0 * rb * din * dout, rb * (din + dout) * asz + din * dout * asz)
             elif sp["kind"] == "layernorm":
                 d, rows = sp["d"], sp["rows"]
                 P += 2 * d
@@ -114,18 +118,19 @@ def algorithmic_work(cfg, only_stage=None, passes=None):
 
 
 # classes whose kernels carry their own start/stop timestamps (no bracket overhead)
-KERNEL_STAMPED = ("dense_fwd", "dense_dgrad", "dense_wgrad", "conv_fwd", "conv_dgrad", "conv_wgrad", "splitk_finish",
+KERNEL_STAMPED = ("dense_fwd", "dense_dgrad", "dense_wgrad", "dense_backward", "conv_fwd", "conv_dgrad", "conv_wgrad", "splitk_finish",
                   "slice_sum", "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd")
 
 
-def class_entry(cfg, klass, ms, launches):
+def class_entry(cfg, klass, ms, launches, joint=None):
     """What a kernel class takes and does per mini-batch, from its measured time (ms) and number of launches.  The work of a
-    class comes from the shapes and not from the launches: consecutive micro-batches may be forwarded in one pass."""
+    class comes from the shapes and not from the launches: consecutive micro-batches may be forwarded in one pass.  (joint: see
+    algorithmic_work.)"""
     ent = {"class": klass, "launches_per_step": launches, "avg_us": 1e3 * ms / launches, "ms_per_step": ms}
-    per = algorithmic_work(cfg).get(klass)
+    per = algorithmic_work(cfg, joint=joint).get(klass)
     if per and per[0]:
         if klass in ("dense_fwd", "conv_fwd"):   # launches of a layer = passes; each reads the layer's weights
-            per = algorithmic_work(cfg, passes=cfg.N * launches / per[0])[klass]
+            per = algorithmic_work(cfg, passes=cfg.N * launches / per[0], joint=joint)[klass]
         ent["gflop_per_launch"] = per[1] / launches / 1e9
         ent["mbytes_per_launch"] = per[2] / launches / 1e6
         ent["tflops"] = per[1] / (ms / 1e3) / 1e12
@@ -353,7 +358,7 @@ def main():
                 continue
             if k not in KERNEL_STAMPED:      # bracketed classes also contain the cost of the event pair
                 ms = max(ms - cnt * pair_us / 1e3, 0.05 * ms)
-            ent = class_entry(cfg, k, ms / args.steps, cnt / args.steps)
+            ent = class_entry(cfg, k, ms / args.steps, cnt / args.steps, T.dense_gradients_joint)
             out.append(ent)
         out.sort(key=lambda e: -e["ms_per_step"])
         return out, pair_us

@@ -311,7 +311,8 @@ int tmps_streams_destroy(void** streams, int n);
 /* ---- measurement aid (not part of the method) ----
  *
  * While enabled, every kernel launch made by the calls above is timed with HIP events on the stream
- * it is launched on.  The contraction kernels (the six *_FWD / *_DGRAD / *_WGRAD classes) and the
+ * it is launched on.  The contraction kernels (the six *_FWD / *_DGRAD / *_WGRAD classes, and
+ * TMPS_KC_DENSE_BACKWARD: launches that hold both gradients of a dense layer) and the
  * reductions of their k-split (TMPS_KC_SPLIT_FINISH, TMPS_KC_SLICE_SUM) are launched with a start and
  * a stop event of their own, which the runtime stamps with the start and end of that kernel's
  * execution.  The other classes are bracketed by two events recorded around the launch, which also
@@ -325,10 +326,14 @@ enum {
     TMPS_KC_CONV_DGRAD, TMPS_KC_CONV_WGRAD, TMPS_KC_SOFTMAX_CE, TMPS_KC_UPDATE, TMPS_KC_POOL_FWD,
     TMPS_KC_POOL_BWD, TMPS_KC_RELU_MASK, TMPS_KC_REDUCE, TMPS_KC_COPY, TMPS_KC_EVENT_PAIR,
     TMPS_KC_SPLIT_FINISH, TMPS_KC_SLICE_SUM, TMPS_KC_LAYERNORM,
-    TMPS_KC_ATTN_FWD, TMPS_KC_ATTN_BWD, TMPS_KC_EMBEDDING, TMPS_KC_AFFINE, TMPS_KC_RESADD, TMPS_KERNEL_CLASSES
+    TMPS_KC_ATTN_FWD, TMPS_KC_ATTN_BWD, TMPS_KC_EMBEDDING, TMPS_KC_AFFINE, TMPS_KC_RESADD,
+    TMPS_KC_DENSE_BACKWARD, TMPS_KERNEL_CLASSES
 };
 int tmps_profile_enable(int on);
 int tmps_profile_read(double* total_ms, int64_t* launches, int n_classes);
+/* 1: the input and the weight gradient of a linear layer over `rows` rows are one launch (TMPS_KC_DENSE_BACKWARD) where a
+ * backward pass forms both one after the other; 0: they are launches of their own classes.  (TMPS_F32 or TMPS_BF16_F32MASTER.) */
+int tmps_dense_gradients_joint(int dtype, int64_t rows, int din, int dout);
 
 const char* tmps_last_error(void);
 

@@ -69,6 +69,7 @@ EXPORTS = {
     "tmps_streams_destroy": (C.c_int, [C.POINTER(C.c_void_p), C.c_int]),
     "tmps_profile_enable": (C.c_int, [C.c_int]),
     "tmps_profile_read": (C.c_int, [C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int]),
+    "tmps_dense_gradients_joint": (C.c_int, [C.c_int, C.c_int64, C.c_int, C.c_int]),
     "tmps_last_error": (C.c_char_p, []),
 }
 
@@ -132,7 +133,7 @@ def version_diff_simulated(W, N):
 
 KERNEL_CLASSES = ["dense_fwd", "dense_dgrad", "dense_wgrad", "conv_fwd", "conv_dgrad", "conv_wgrad", "softmax_ce",
                   "update", "pool_fwd", "pool_bwd", "relu_mask", "reduce", "copy", "event_pair", "splitk_finish", "slice_sum",
-                  "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd"]
+                  "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd", "dense_backward"]
 
 
 def profile_enable(on):
@@ -146,6 +147,11 @@ def profile_read():
     cnt = (C.c_int64 * n)()
     _check(lib().tmps_profile_read(ms, cnt, n))
     return {k: (ms[i], cnt[i]) for i, k in enumerate(KERNEL_CLASSES)}
+
+
+def dense_gradients_joint(dtype, rows, din, dout):
+    """Whether both gradients of a linear layer are one launch, timed under "dense_backward"."""
+    return bool(lib().tmps_dense_gradients_joint(TMPS_BF16_F32MASTER if dtype == "bf16" else TMPS_F32, rows, din, dout))
 
 
 def layer_descs(specs):

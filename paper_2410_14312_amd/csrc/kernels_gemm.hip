@@ -672,16 +672,16 @@ hipError_t dense_backward(int dtype, const void* dy, const void* x, const void* 
     const EpiMask<bf16_t, bf16_t> ex{(bf16_t*)dx, (const bf16_t*)mask, Din, mask_mode, (const bf16_t*)add};
     if (kind == kOneSmall) {
         if (dtype != kBF16)
-            return small_backward_f32(kcDenseWgrad, (const float*)dy, (const float*)x, (const float*)w, gw,
+            return small_backward_f32(kcDenseBackward, (const float*)dy, (const float*)x, (const float*)w, gw,
                                       EpiMask<float, float>{(float*)dx, (const float*)mask, Din, mask_mode, (const float*)add}, B, Din, Dout, s);
-        return small_backward_t<bf16_t>(kcDenseWgrad, (const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)w, gw, ex, B, Din, Dout, s);
+        return small_backward_t<bf16_t>(kcDenseBackward, (const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)w, gw, ex, B, Din, Dout, s);
     }
     if (kind == kOneTiled && aligned16(dy) && aligned16(x) && aligned16(w)) {
         typedef bf16_t T;
         const EpiWgrad ew{gw, Din, (int64_t)Dout * Din, 0};
         constexpr int lds_x = gemm2_lds_bytes<64, 64, DenseKC<T>, DenseRC<T>>(), lds_w = gemm2_lds_bytes<64, 64, DenseRC<T>, DenseRC<T>>();
         const int n = cdiv(Din, 64), split = n * cdiv(B, 64), tw = n * cdiv(Dout, 64);
-        return launch_timed(kcDenseWgrad, gemm2_backward_kernel<4, T>, dim3(split + tw), dim3(256), lds_x > lds_w ? lds_x : lds_w, s, (const T*)dy, (const T*)x,
+        return launch_timed(kcDenseBackward, gemm2_backward_kernel<4, T>, dim3(split + tw), dim3(256), lds_x > lds_w ? lds_x : lds_w, s, (const T*)dy, (const T*)x,
                             (const T*)w, ex, ew, B, Din, Dout, split, FastDiv(n), FastDiv(split), FastDiv(tw), ex.wide_ok() && ew.wide_ok() ? 1 : 0);
     }
     const hipError_t e = dense_wgrad(dtype, dy, x, gw, B, Din, Dout, ws_w, s);
@@ -743,3 +743,8 @@ hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const
 }
 
 }  // namespace tmps
+
+extern "C" int tmps_dense_gradients_joint(int dtype, int64_t rows, int din, int dout) {
+    using namespace tmps;
+    return rows > 0 && din > 0 && dout > 0 && !dense_wgrad_groups(dtype, rows, din, dout) && backward_kind(rows, din, dout, dtype == kBF16 ? 2 : 4) != kTwo;
+}

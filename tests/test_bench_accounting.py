@@ -119,3 +119,24 @@ def test_weights_are_read_once_by_every_pass():
     weights = (64 * 128 + 128 * 128 + 128 * 10) * 4
     by_pass = [bench.algorithmic_work(cfg, passes=p)["dense_fwd"][2] for p in (1, 2, 4)]
     assert by_pass[1] - by_pass[0] == weights and by_pass[2] - by_pass[0] == 3 * weights
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_both_gradients_of_a_layer_in_one_launch_count_together(name):
+    """What the library launches together is moved to a class of its own, with all of its work: at the batch sizes of the two smaller networks' layers
+    and of two of VGG-16's classifier, and nowhere for the transformer, whose weight gradients wait for the end of a pass."""
+    from paper_2410_14312_amd import dense_gradients_joint
+
+    cfg = get_config(name)
+    apart, got = bench.algorithmic_work(cfg), bench.algorithmic_work(cfg, joint=dense_gradients_joint)
+    classes = ("dense_dgrad", "dense_wgrad", "dense_backward")
+    for i in (1, 2):
+        assert sum(got.get(k, [0] * 3)[i] for k in classes) == pytest.approx(sum(apart.get(k, [0] * 3)[i] for k in classes), rel=1e-12)
+    layers = {"tiny_mlp_f32": 2, "mlp4x1024_bf16": 4, "vgg16_bf16": 2, "resnet50_bf16": 0, "gpt2_small_bf16": 0}[name]
+    both = got.get("dense_backward", [0, 0.0, 0.0])
+    assert both[0] == layers
+    assert both[0] + got.get("dense_wgrad", [0])[0] == apart["dense_wgrad"][0] and both[0] + got.get("dense_dgrad", [0])[0] == apart["dense_dgrad"][0]
+    if layers:
+        e = bench.class_entry(cfg, "dense_backward", 2.0, layers, dense_gradients_joint)
+        assert e["tflops"] == pytest.approx(both[1] / 2e-3 / 1e12, rel=1e-12)
+    assert "dense_dgrad" not in got if name == "mlp4x1024_bf16" else True
