@@ -142,7 +142,8 @@ size_t layernorm_workspace_elems(int64_t rows, int D);
 // h*D/H.. of each part).  o[B*S, D]; lse[B, H, S] = log-sum-exp of the scaled scores of each query.
 hipError_t attention_forward(int dtype, const void* qkv, void* o, float* lse, int B, int S, int D, int H,
                              hipStream_t s);
-// dqkv[B*S, 3*D] from the gradient dout[B*S, D] of the output; delta: workspace of B*H*S floats.
+// dqkv[B*S, 3*D] from the gradient dout[B*S, D] of the output; delta: workspace of B*H*S floats, for heads and
+// addresses that the matrix kernels do not take (those form it as they go).
 hipError_t attention_backward(int dtype, const void* qkv, const void* o, const void* dout, const float* lse,
                               float* delta, void* dqkv, int B, int S, int D, int H, hipStream_t s);
 size_t attention_workspace_elems(int B, int S, int H);

@@ -874,6 +874,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 1 : 2) void attn_bwd_mfma
     else attn_bwd_kv<T, DH, NW>(sm, base, ob, dob, lse, dbase, slot >> 1, S, D, scale);
 }
 
+// (of the kernels that take a row at a time: heads of other sizes than 32 and 64 features, and these where an operand is not aligned, which a caller decides
+// only with the pointers of a pass)
 size_t attention_workspace_elems(int B, int S, int H) { return (size_t)B * S * H; }
 
 // The kernel with the key range split over a workgroup's waves, where the tiled one has too few workgroups: its time is that of the longest way (3.5 us

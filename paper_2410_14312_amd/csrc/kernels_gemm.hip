@@ -480,6 +480,7 @@ bool dense_wgrad_groups(int dtype, int64_t rows, int Din, int Dout) {
 
 constexpr int64_t kGroupMaxElems = (int64_t)1024 * G3Group::kPart;   // partial tiles of four rounds of the device
 
+static_assert(kG3GroupMax == kWgradGroupMax, "a stage fills groups that one launch takes");
 int64_t dense_wgrad_group_elems(int64_t rows, const int (*dims)[2], int n) {
     if (n < 1 || n > kG3GroupMax) return -1;
     int64_t tiles = 0;

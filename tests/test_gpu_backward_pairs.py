@@ -56,7 +56,7 @@ def test_weight_gradients_over_many_rows(dtype, rows, din, dout):
 
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(rows)
-    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    randn = lambda *shape: torch.randn(*shape, generator=gen, dtype=torch.float32, device="cuda:0")
     st = Stage([linear(din, dout, False)], dtype, rows, 1, 1, 0.1, 0.9, borrow_input=True)
     st.set_params([{"w": (randn(dout, din) / din ** 0.5).cpu().numpy(), "b": np.zeros(dout, np.float32)}])
     x, dy = randn(rows, din).to(st.act_dtype), (randn(rows, dout) / rows).to(st.act_dtype)

@@ -70,8 +70,9 @@ def test_partial_results_are_added_in_pairs(count, slices, rows, odd):
 
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(slices)
-    flat = torch.randn(slices * count + 1, generator=gen, device="cuda:0")
-    part, out = flat[odd:odd + slices * count], torch.zeros(count + 1, device="cuda:0")
+    f32 = dict(dtype=torch.float32, device="cuda:0")
+    flat = torch.randn(slices * count + 1, generator=gen, **f32)
+    part, out = flat[odd:odd + slices * count], torch.zeros(count + 1, **f32)
     reduce_all([_Reduction(part.data_ptr(), out.data_ptr() + 4 * odd, count, slices, rows)])
     want = part.view(slices, count).double().sum(0)
     chain = slices / (8 * 16) + 4 * 2 if rows else slices / 8

@@ -52,11 +52,12 @@ def test_sums_of_long_contractions(rows, din, dout):
 
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(din)
-    w = torch.randn(dout, din, generator=gen, device="cuda:0") / din ** 0.5
-    x = torch.randn(rows, din, generator=gen, device="cuda:0")
+    f32 = dict(dtype=torch.float32, device="cuda:0")
+    w = torch.randn(dout, din, generator=gen, **f32) / din ** 0.5
+    x = torch.randn(rows, din, generator=gen, **f32)
     st = Stage([linear(din, dout, False)], "f32", rows, 1, 1, 0.1, 0.9, borrow_input=True)
     st.set_params([{"w": w.cpu().numpy(), "b": np.zeros(dout, np.float32)}])
-    y = torch.empty(rows, dout, device="cuda:0")
+    y = torch.empty(rows, dout, **f32)
     st.forward_micro(0, x, y=y)
     want = x.double() @ w.double().t().contiguous()
     assert (y.double() - want).norm() < 2.0 ** -24 * (28 / 6) ** 0.5 * want.norm()
