@@ -12,8 +12,8 @@
 // partial sums cost what they write; fragments read in the step they are multiplied in, 1.05 us.  On the other kernels and here, with the slices'
 // sum (us): 128 images of 2 x 2 x 512 13.8 and 10.6, of 4 x 4 x 512 29 and 22, of 8 x 8 x 256 30 and 26, of 16 x 16 x 128 31 and 28, of
 // 32 x 32 x 64 40 and 28; 64 images of 56 x 56 x 64 53 and 34, 32 of 28 x 28 x 128 30 and 25, of 14 x 14 x 256 27 and 23, of 7 x 7 x 512 23 and 18.
-// Errors (2-norm, against 64 bits), there and here: 128 images of 4 x 4 x 512 1.7e-7 and 1.2e-7, of 32 x 32 x 64 2.6e-7 and 2.0e-7, 64 of 28 x 28 x 256
-// 3.7e-7 and 3.0e-7, of 14 x 14 x 512 2.7e-7 and 1.6e-7 (the number of slices sees to it: conv_wgrad_rows_plan).
+// Errors (2-norm, against 64 bits), there and here: 128 images of 4 x 4 x 512 1.7e-7 and 1.2e-7, of 32 x 32 x 64 2.6e-7 and 1.5e-7, 64 of 56 x 56 x 64
+// 2.2e-7 and 1.7e-7, of 14 x 14 x 512 2.7e-7 and 1.6e-7 (the number of slices sees to it: conv_wgrad_rows_plan).
 #pragma once
 #include "gemm4.hip.h"
 

@@ -9,7 +9,7 @@
 // consecutive bytes of a row with four lanes (those of 32 x 32 only 32 bytes), and an output of few rows is cut into the smallest tiles
 // that the device has units for, which each load the least.  Launch to launch, with 32 x 32 multiplies and with these (us): fp32
 // 32 x 64 -> 128 3.1 and 2.2, 47 x 1000 -> 1000 8.9 and 4.8, 128 x 1024 -> 1024 9.8 and 7.7, 256 x 1024 -> 1024 10.1 and 10.3; bf16 64 x 1024 -> 1024 5.7 and
-// 3.8, 64 x 3072 -> 1024 11.7 (in k-slices) and 7.4, 256 x 1024 -> 1024 5.9 and 5.8.
+// 3.8, 64 x 3072 -> 1024 11.7 (in k-slices) and 7.4, 256 x 1024 -> 1024 5.9 and 5.8 (what its sums' second set takes of that stands below).
 #pragma once
 #include "gemm2.hip.h"
 

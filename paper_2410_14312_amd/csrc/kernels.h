@@ -14,8 +14,8 @@ constexpr int kBF16 = 1;
 
 inline size_t act_bytes(int dtype) { return dtype == kBF16 ? 2 : 4; }
 
-// Sum of partial results: out[i] = sum over z < slices of part[z * count + i], i < count: in order (k-slices of a contraction) or, where
-// many short rows are added up (slabs of a normalisation or affine layer), sixteen rows at a time.  What a backward pass adds up of its
+// Sum of partial results: out[i] = sum over z < slices of part[z * count + i], i < count: eight at a time, in pairs, and the totals in
+// order (k-slices of a contraction) or, where many short rows are added up (slabs of a normalisation or affine layer), in sixteen such sums side by side.  What a backward pass adds up of its
 // parameter gradients can wait for its end and be one launch: a launcher that is given a list to put its sum on leaves it to
 // reduce_all, and its partial results stay in memory of their own until then.
 struct Reduction {

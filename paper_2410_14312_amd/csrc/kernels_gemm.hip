@@ -171,7 +171,7 @@ struct ReduceJob {
     const float* part;
     float* out;
     int64_t count;
-    int slices, form;   // form: 0 four in order, 1 one in order, 2 rows
+    int slices, form;   // form: 0 four outputs to a thread, 1 one, 2 rows
 };
 struct ReduceJobs {
     int first[kReduceMax];   // first workgroup of a job; where there is none, the number of workgroups
