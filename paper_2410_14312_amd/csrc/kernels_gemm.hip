@@ -129,10 +129,12 @@ Plan2 plan_for(int64_t M, int64_t N, int64_t K, bool rowsum, int esize, int by_k
 }
 
 // Small kernel: the smallest tiles that are no more than the compute units.  What a unit's fragment loads touch sets the pace: cycles per k
-// of 16 x 16, 16 x 32 and 32 x 32 outputs 9, 14 and 20 in fp32, 4.2, 6.2 and 9.2 in bf16 (64 to 256 rows x 768 to 1024, K = 64 to 3072), and a fixed part.
+// of 16 x 16, 16 x 32 and 32 x 32 outputs 9, 14 and 18.5 in fp32, 4.2, 6.2 and 9.2 in bf16 (64 to 256 rows x 768 to 1024, K = 64 to 3072), and a fixed part.
+// (20 for the third, as alone it measures, sends fp32 layers of some 300 such outputs to the tiled kernel in slices: forward 235 x 748 -> 1581 and 69 x 1518 -> 1730, both gradients
+// with them, 38.5 and 38.9 us instead of 37.4 and 37.1; sums 1.7e-7 (2-norm) from those in 64 bits instead of 1.0e-7.)
 SmallPlan small_plan(int64_t M, int64_t N, int64_t K, int esize) {
     static const int shape[3][2] = {{1, 1}, {1, 2}, {2, 2}};
-    static const double per_k[2][3] = {{9.0, 14.0, 20.0}, {4.2, 6.2, 9.2}};
+    static const double per_k[2][3] = {{9.0, 14.0, 18.5}, {4.2, 6.2, 9.2}};
     for (int i = 0;; ++i) {
         const int64_t tiles = (int64_t)cdiv(M, 16 * shape[i][0]) * cdiv(N, 16 * shape[i][1]);
         if (i == 2 || tiles <= kCUs) return SmallPlan{shape[i][0], shape[i][1], 2500.0 + (double)cdiv(tiles, kCUs) * K * per_k[esize == 4 ? 0 : 1][i]};

@@ -21,6 +21,8 @@ DENSE = [
     ("f32", 201, 768, 2760, ("by_k", None, None)),
     ("f32", 141, 3856, 748, (None, "by_k", None)),
     ("f32", 753, 2704, 200, (None, None, "by_k")),
+    ("f32", 236, 748, 1584, ("small", None, None)),
+    ("f32", 262, 1552, 940, (None, "small", None)),
     ("bf16", 1000, 776, 2952, ("async", "by_k", "async")),     # 13 k-tiles, the last one short
     ("bf16", 1003, 2952, 776, ("by_k", "async", "async")),
     ("bf16", 3745, 3464, 72, (None, None, "async split")),
