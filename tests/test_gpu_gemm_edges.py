@@ -1,5 +1,5 @@
-"""Contractions at the edges of their kernels' ranges: the small kernel (32 x 32 tiles, the k range shared by the waves)
-at its tile, fragment and wave-count borders, matrices whose rows are not whole 16-byte chunks (ragged loaders) or less
+"""Contractions at the edges of their kernels' ranges: the small kernel (16 x 16 to 32 x 32 outputs, the k range
+shared by the waves; most of these layers' gradients are one launch of it) at its tile, step and wave-count borders, matrices whose rows are not whole 16-byte chunks (ragged loaders) or less
 than one (gathering loaders), convolutions over channel counts that are not whole chunks, and the tiled fp32 kernel
 with and without k-slices.  Against the oracle, all three passes, in both types."""
 import pytest
@@ -13,10 +13,10 @@ DENSE = [
     # (din, dout, micro, N)
     (3, 5, 2, 2),          # rows of less than a chunk: gathered
     (8, 4, 1, 1),          # one row
-    (16, 33, 33, 1),       # one fragment pair of k (bf16) / two (fp32), a tile and a column over
+    (16, 33, 33, 1),       # half a step of k (bf16) / one (fp32), a tile and a column over
     (17, 31, 16, 2),       # a tail of one k
-    (127, 129, 31, 2),     # 4 and 8 waves, tails in every pass
-    (513, 65, 47, 1),      # 16 waves and a tail
+    (127, 129, 31, 2),     # 4 waves, tails in every pass
+    (513, 65, 47, 1),      # 8 waves and a tail
     (1000, 10, 235, 1),    # a narrow output layer
     (72, 2601, 40, 2),     # odd output: ragged rows of dY in both gradients
     (1001, 1003, 300, 1),  # ragged everywhere, tiled
