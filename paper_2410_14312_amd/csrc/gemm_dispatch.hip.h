@@ -286,10 +286,19 @@ struct WgradRowsPlan {
 WgradRowsPlan conv_wgrad_rows_plan(const ConvShape& c, const Plan2& other);
 hipError_t conv_wgrad_rows(const WgradRowsPlan& p, const bf16_t* dy, const bf16_t* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s);
 
+// Convolutions over eight channels (kernels_conv_first.hip, bf16): which of them it is, 0 for any other and where the other kernels are quicker; slices
+// of its weight gradient.
+int conv_first_kind(const ConvShape& c, bool wgrad);
+template <class Epi> hipError_t conv_first(int kind, const bf16_t* x, const bf16_t* w, const Epi& epi, const ConvShape& c, hipStream_t s);
+int conv_first_wgrad_slices(const ConvShape& c);
+hipError_t conv_first_wgrad(int kind, const bf16_t* dy, const bf16_t* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s);
+
 template <class T, class Epi>
 static hipError_t conv_forward_t(const T* x, const T* w, const Epi& epi, const ConvShape& c, float* ws, hipStream_t s) {
     const int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
     if constexpr (sizeof(T) == 2) {
+        const int first = conv_first_kind(c, false);
+        if (first && epi.wide_ok() && aligned16(x) && aligned16(w)) return conv_first(first, x, w, epi, c, s);
         const int v = conv_rows_variant(c, M, c.Cout, c.Cin, plan_for(M, c.Cout, K, false, 2, kByKConv).cost / 2400.0);
         if (v && epi.wide_ok() && aligned16(x) && aligned16(w)) return conv_rows<false>(v, kcConvFwd, x, w, epi, c, s);
     }
@@ -341,6 +350,8 @@ template <class T> static hipError_t conv_wgrad_t(const T* dy, const T* x, float
     constexpr int V = ElemTile<T>::V, BK = ElemTile<T>::BK;
     if (c.Cin % V != 0 || c.Cout % V != 0 || !aligned16(dy) || !aligned16(x) || !small_enough(c)) return gather_conv_wgrad<T>(dy, x, gw, c, ws, s);
     if constexpr (sizeof(T) == 2) {
+        const int first = conv_first_kind(c, true);
+        if (first && (conv_first_wgrad_slices(c) == 1 ? aligned16(gw) : ws.ws && aligned16(ws.ws))) return conv_first_wgrad(first, dy, x, gw, c, ws, s);
         const WgradRowsPlan p = conv_wgrad_rows_plan(c, plan_for(rows, cols, K, true, 2, kByKConv));
         if (p.slices && (p.slices == 1 ? aligned16(gw) : ws.ws && aligned16(ws.ws))) return conv_wgrad_rows(p, dy, x, gw, c, ws, s);
     }

@@ -735,7 +735,7 @@ size_t conv_wgrad_workspace_elems(int dtype, const ConvShape& c) {
     const int64_t cols = (int64_t)c.R * c.S * c.Cin, K = (int64_t)c.B * c.Ho * c.Wo;
     const size_t n = gemm_workspace_elems(c.Cout, cols, K, kWsRowSums | (dtype == kBF16 ? 0 : kWsF32));
     if (dtype != kBF16) return n;
-    const int slices = conv_wgrad_rows_plan(c, plan_for(c.Cout, (int)cols, K, true, 2, kByKConv)).slices;
+    const int slices = conv_first_kind(c, true) ? conv_first_wgrad_slices(c) : conv_wgrad_rows_plan(c, plan_for(c.Cout, (int)cols, K, true, 2, kByKConv)).slices;
     return slices > 1 ? std::max(n, (size_t)slices * (size_t)(c.Cout * cols + c.Cout)) : n;
 }
 

@@ -114,6 +114,14 @@ def conv_wgrad_plan(sp, samples):
     return _functions()[0](sp["cout"], sp["r"] * sp["s"] * sp["cin"], samples * ho * wo, True, 2, CONV)
 
 
+def conv_first(spec, samples, wgrad):
+    """Whether a convolution (a pass of it) runs on the kernels for eight channels: 1 (3 x 3), 2 (7 x 7, stride 2) or 0."""
+    f = getattr(load_library(), "_ZN4tmps15conv_first_kindERKNS_9ConvShapeEb")
+    f.restype, f.argtypes = C.c_int, [C.POINTER(_Conv), C.c_bool]
+    ho, wo = ((spec[k] + 2 * spec["pad"] - spec[r]) // spec["stride"] + 1 for k, r in (("h", "r"), ("w", "s")))
+    return f(C.byref(_Conv(samples, spec["h"], spec["w"], spec["cin"], ho, wo, spec["cout"], spec["r"], spec["s"], spec["stride"], spec["pad"])), wgrad)
+
+
 def conv_wgrad_rows(sp, samples):
     """k-slices and positions of each of a weight gradient on runs of rows (bf16); no slices: it runs on another kernel."""
     f = getattr(load_library(), "_ZN4tmps20conv_wgrad_rows_planERKNS_9ConvShapeERKNS_5Plan2E")
