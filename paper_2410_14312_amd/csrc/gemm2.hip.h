@@ -123,6 +123,19 @@ template <class T_> struct DenseKC {
     __device__ __forceinline__ void next(KS& ks) const { ks.k += BK; }
 };
 
+// A matrix whose rows are the positions of a map's every stride-th row and column: what a 1 x 1 filter with that stride reaches.
+template <class T_> struct StridedKC : DenseKC<T_> {
+    int H, W, stride;
+    FastDiv d_howo, d_wo;
+    StridedKC(const DenseKC<T_>& m, int h, int w, int st, int ho, int wo) : DenseKC<T_>(m), H(h), W(w), stride(st), d_howo(ho * wo), d_wo(wo) {}
+    __device__ __forceinline__ int out_row(int m) const {
+        uint32_t img, rest, h, w;
+        d_howo.divmod((uint32_t)m, img, rest);
+        d_wo.divmod(rest, h, w);
+        return ((int)img * H + (int)h * stride) * W + (int)w * stride;
+    }
+};
+
 template <class T_> struct DenseRC {
     typedef T_ T;
     static constexpr bool kContig = false, kSettle = false;

@@ -86,6 +86,7 @@ static hipError_t launch4(int kc, const AOp& A, const BOp& B, const Epi& epi, in
 template <class Op> struct IsMatrix { static constexpr bool value = false; };
 template <class T> struct IsMatrix<DenseKC<T>> { static constexpr bool value = true; };
 template <class T> struct IsMatrix<DenseRC<T>> { static constexpr bool value = true; };
+template <class T> struct IsMatrix<StridedKC<T>> { static constexpr bool value = true; };
 template <class Op> constexpr bool has_addr() { return !IsGather<Op>::value && !Op::kSettle; }
 template <class AOp, class BOp> constexpr int by_k_mode() {
     return !has_addr<AOp>() || !has_addr<BOp>() ? kByKNo : IsMatrix<AOp>::value && IsMatrix<BOp>::value ? kByKDense : kByKConv;
@@ -315,6 +316,14 @@ static hipError_t conv_dgrad_t(const T* dy, const T* w, const EpiMask<T, T>& epi
     if constexpr (sizeof(T) == 2) {
         const int v = conv_rows_variant(c, M, c.Cin, c.Cout, plan_for(M, c.Cin, K, false, 2, kByKConv).cost / 2400.0);
         if (v && epi.wide_ok()) return conv_rows<true>(v, kcConvDgrad, dy, w, epi, c, s);
+    }
+    if (c.rest_done && c.R == 1 && c.S == 1 && c.pad == 0 && epi.add == epi.out && epi.wide_ok()) {
+        // A 1 x 1 filter with a stride reaches one position of stride^2: a dense product over those, added where they lie.  (No k-slices: their partial
+        // sums would be as large as the map.)  Over the whole map three positions in four were read and written for nothing, for a
+        // dx that the layer beside it then read once more: 64 images of 56 x 56 x 256 from 512 channels 138 us, of 14 x 14 x 1024 from 2048 119.
+        const int Mo = c.B * c.Ho * c.Wo;
+        const StridedKC<T> A(DenseKC<T>{dy, Mo, c.Cout, c.Cout}, c.H, c.W, c.stride, c.Ho, c.Wo);
+        return run2(kcConvDgrad, A, DenseRC<T>{w, c.Cin, c.Cout, c.Cin}, epi, Mo, c.Cin, c.Cout, nullptr, s);
     }
     if (c.stride == 2 && c.H % 2 == 0 && c.W % 2 == 0 && c.Cin % 8 == 0) {
         // Rows ordered by the parity of their position, each class walking only the filter taps that reach it:

@@ -42,6 +42,8 @@ struct Partials {
 
 struct ConvShape {
     int B, H, W, Cin, Ho, Wo, Cout, R, S, stride, pad;
+    // conv_dgrad, of a pass that adds to dx in place: positions that no filter tap reaches have their final value (the mask applied) already
+    int rest_done = 0;
 };
 
 // Tile edge (64 or 128) and number of k-slices chosen for a bf16 [M x N x K] contraction.

@@ -722,6 +722,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         const void* ptr = nullptr;
         int buf = -1;      // pool buffer that holds it; -1: memory that is not ours to write or free (dy, the stash, dx)
         bool set = false;
+        bool masked = false;   // it has passed through the activation of the layer whose result it belongs to
     };
     const int nl = (int)st->layers.size();
     std::vector<Grad> grads(nl + 1);
@@ -794,6 +795,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         G.ptr = T.dst;
         G.buf = T.buf;
         G.set = true;
+        G.masked = true;   // (by the kernel that wrote it)
         --remaining[t + 1];
     };
     // hand an existing gradient (g) to result t as its contribution, without a kernel when it is the first
@@ -816,6 +818,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             if (G.buf != T.buf) release(G.buf);
             G.ptr = T.dst; G.buf = T.buf;
         }
+        G.masked = false;
         --remaining[t + 1];
         return TMPS_OK;
     };
@@ -840,6 +843,33 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         waiting.clear();
         return TMPS_OK;
     };
+
+    // The input gradient of a 1 x 1 convolution with a stride touches few positions of its input's gradient.  Where other layers read the same input
+    // it comes last, added in place, instead of first over the whole map (one at a time: its own gradient is kept until then).
+    struct {
+        int li = -1;
+        Grad g;
+    } strided;
+    auto conv_input_gradient = [&](int li, const Grad& g) -> int {
+        const LayerRT& L = st->layers[li];
+        ConvShape c = conv_shape(L.d, M);
+        int mode;
+        const void* mask = mask_of(L.in_t, mode);
+        Target T;
+        int rc = target(L.in_t, T);
+        if (rc != TMPS_OK || !T.wanted) return rc;
+        if (mode == 2) return fail(TMPS_EUNSUPPORTED, "a convolution directly after a GELU layer");
+        c.rest_done = T.add && T.add == T.dst && (!mask || grads[L.in_t + 1].masked);
+        TMPS_GEMM(conv_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, T.add, c, ws, s));
+        commit(L.in_t, T);
+        return TMPS_OK;
+    };
+    auto can_wait = [&](const LayerRT& L) {
+        const int32_t* d = L.d.dims;
+        return strided.li < 0 && !in_order && d[4] == 1 && d[5] == 1 && d[6] > 1 && d[7] == 0 && remaining[L.in_t + 1] > 1 && !grads[L.in_t + 1].set &&
+               (L.in_t >= 0 || dx) && std::count(refs, refs + st->n_gbuf, 0) >= 3;
+    };
+    auto strided_is_last = [&]() { return strided.li >= 0 && remaining[st->layers[strided.li].in_t + 1] == 1; };
 
     int top = nl - 1;
     if (st->cfg.is_last) {
@@ -899,14 +929,12 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                 break;
             }
             case TMPS_CONV2D: {
-                ConvShape c = conv_shape(L.d, M);
-                TMPS_GEMM(conv_wgrad(dt, g.ptr, in, gw, c, partials(L), s));
-                if ((rc = target(t_in, T)) != TMPS_OK) return rc;
-                if (T.wanted) {
-                    if (mask_mode == 2) return fail(TMPS_EUNSUPPORTED, "a convolution directly after a GELU layer");
-                    TMPS_GEMM(conv_dgrad(dt, g.ptr, st->wptr(L), T.dst, mask, T.add, c, ws, s));
-                    commit(t_in, T);
-                }
+                TMPS_GEMM(conv_wgrad(dt, g.ptr, in, gw, conv_shape(L.d, M), partials(L), s));
+                if (can_wait(L)) {
+                    strided.li = li;
+                    strided.g = g;
+                    if (g.buf >= 0) ++refs[g.buf];
+                } else if ((rc = conv_input_gradient(li, g)) != TMPS_OK) return rc;
                 break;
             }
             case TMPS_MAXPOOL:
@@ -965,6 +993,11 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         }
         release(g.buf);
         grads[li + 1].set = false;
+        if (strided_is_last()) {
+            if ((rc = conv_input_gradient(strided.li, strided.g)) != TMPS_OK) return rc;
+            release(strided.g.buf);
+            strided.li = -1;
+        }
         // A result whose gradient is complete but was only handed over (never written through a kernel that applies
         // the activation of its producer) still has to pass through that activation.
         if (t_in >= 0 && remaining[t_in + 1] == 0 && grads[t_in + 1].set && L.d.kind == TMPS_RESADD) {
