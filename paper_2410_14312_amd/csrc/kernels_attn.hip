@@ -17,21 +17,11 @@
 #include "gemm2.hip.h"
 #include "kernels.h"
 #include "launch.h"
+#include "wave.hip.h"
 
 namespace tmps {
 
 static inline int cdiv_at(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-
-__device__ __forceinline__ float wsum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float wmax(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 
 // ------------------------------------------------------------------------- generic path
 // qkv rows are [q | k | v] of D features each; head h owns features h*dh .. h*dh+dh-1 of each part.

@@ -2,21 +2,11 @@
 // ReLU gradient mask, casts and small reductions.
 #include "gemm.hip.h"
 #include "kernels.h"
+#include "wave.hip.h"
 
 namespace tmps {
 
 static inline int cdiv64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // ------------------------------------------------------------------------- softmax cross-entropy
 // One wave per row; 4 rows per block.  dlogits = (softmax - onehot) * inv_M, loss = lse - z[label].
@@ -32,10 +22,10 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* __restrict
     const float* z = logits + (int64_t)row * C;
     float mx = -INFINITY;
     for (int c = lane; c < C; c += 64) mx = fmaxf(mx, z[c]);
-    mx = wave_max(mx);
+    mx = wmax(mx);
     float sum = 0.0f;
     for (int c = lane; c < C; c += 64) sum += expf(z[c] - mx);
-    sum = wave_sum(sum);
+    sum = wsum(sum);
     const float inv = 1.0f / sum;
     const int label = labels[row];
     const bool label_ok = label >= 0 && label < C;  // an out-of-range label gives a NaN loss, never a wild read
@@ -68,8 +58,8 @@ __global__ __launch_bounds__(256) void softmax_ce_wide_kernel(const float* __res
             sum += expf(v - mx);
         }
     }
-    const float wm = wave_max(mx);
-    sum = wave_sum(sum * expf(mx - wm));   // a thread that saw nothing has sum 0 and mx -inf: 0 * exp(-inf) = 0
+    const float wm = wmax(mx);
+    sum = wsum(sum * expf(mx - wm));   // a thread that saw nothing has sum 0 and mx -inf: 0 * exp(-inf) = 0
     if (lane == 0) {
         sm[wave] = wm;
         ss[wave] = sum;
@@ -113,7 +103,7 @@ __global__ __launch_bounds__(kCeThreads) void softmax_ce_lds_kernel(const float*
         s4[c] = v;
         mx = fmaxf(fmaxf(mx, fmaxf(v.x, v.y)), fmaxf(v.z, v.w));
     }
-    mx = wave_max(mx);
+    mx = wmax(mx);
     if (lane == 0) sm[wave] = mx;
     __syncthreads();
     float bm = sm[0];
@@ -126,7 +116,7 @@ __global__ __launch_bounds__(kCeThreads) void softmax_ce_lds_kernel(const float*
         s4[c] = v;   // keep the exponentials: the gradient needs them again
         sum += (v.x + v.y) + (v.z + v.w);
     }
-    sum = wave_sum(sum);
+    sum = wsum(sum);
     if (lane == 0) ss[wave] = sum;
     __syncthreads();
     float bs = 0.0f;
@@ -177,7 +167,7 @@ __global__ __launch_bounds__(kCeThreads, 8) void softmax_ce_reg_kernel(const flo
 #pragma unroll
     for (int k = 0; k < NV; ++k)
         if (tid + k * kCeThreads < C4) mx = fmaxf(fmaxf(mx, fmaxf(v[k].x, v[k].y)), fmaxf(v[k].z, v[k].w));
-    mx = wave_max(mx);
+    mx = wmax(mx);
     if (lane == 0) sm[wave] = mx;
     __syncthreads();
     float bm = sm[0];
@@ -190,7 +180,7 @@ __global__ __launch_bounds__(kCeThreads, 8) void softmax_ce_reg_kernel(const flo
             v[k].x = __expf(v[k].x - bm); v[k].y = __expf(v[k].y - bm); v[k].z = __expf(v[k].z - bm); v[k].w = __expf(v[k].w - bm);
             sum += (v[k].x + v[k].y) + (v[k].z + v[k].w);
         }
-    sum = wave_sum(sum);
+    sum = wsum(sum);
     if (lane == 0) ss[wave] = sum;
     __syncthreads();
     float bs = 0.0f;
@@ -278,7 +268,7 @@ __global__ __launch_bounds__(256) void reduce_scaled_sum_kernel(const float* __r
     __shared__ float part[4];
     float a = 0.0f;
     for (int i = threadIdx.x; i < n; i += 256) a += in[i];
-    a = wave_sum(a);
+    a = wsum(a);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
     __syncthreads();
     if (threadIdx.x == 0) out[0] = (part[0] + part[1] + part[2] + part[3]) * scale;
@@ -351,7 +341,7 @@ __global__ __launch_bounds__(1024) void softmax_ce_small_kernel(const float* __r
     if (tid < 256) {
         float a = 0.0f;
         for (int i = tid; i < before + rows; i += 256) a += row_loss[i];
-        a = wave_sum(a);
+        a = wsum(a);
         if ((tid & 63) == 0) part[tid >> 6] = a;
     }
     __syncthreads();
