@@ -118,7 +118,7 @@ static inline bool epi_al16(const void* p) { return (reinterpret_cast<uintptr_t>
 // out[m, n] = act(v + bias[n]) + res[m, n].  With GELU the DERIVATIVE gelu'(v + bias[n]) is stored as well (zout): the
 // backward pass then multiplies by a stored factor, as it does for ReLU, instead of evaluating an erf and an
 // exponential per element in the epilogue of the input-gradient GEMM (where that cost more than the GEMM's k-loop).
-// res: a residual connection's source, same shape as out.
+// res: a residual connection's source, same shape as out.  Without GELU zout is a second place for the result (what a stage hands to the next worker).
 template <typename TOut> struct EpiBiasAct {
     TOut* out;
     const float* bias;  // may be null
@@ -135,6 +135,7 @@ template <typename TOut> struct EpiBiasAct {
         }
         if (res) v += to_f32(res[idx]);
         out[idx] = from_f32<TOut>(v);
+        if (relu != kActGelu && zout) zout[idx] = from_f32<TOut>(v);
     }
     bool wide_ok() const { return ld % 8 == 0 && epi_al16(out) && epi_al16(bias) && epi_al16(res) && epi_al16(zout); }
     // the same in two steps: column(n) fetches the bias once, at() finishes element idx = m*ld + n
@@ -174,15 +175,15 @@ template <typename TOut> struct EpiBiasAct {
             for (int e = 0; e < 8; ++e) v[e] += r[e];
         }
         store8(out + idx, v);
+        if (relu != kActGelu && zout) store8(zout + idx, v);
     }
     __device__ __forceinline__ void rowsum(int, float, int) const {}
 };
 
 // Convolution followed by a per-channel affine layer and, optionally, a residual join, in one epilogue:
 //   z = v + bias[n]                        -> out   (the convolution's result, kept for the affine layer's gradient)
-//   a = gain[n] * z + shift[n]             -> aout  (null when nothing reads it: the backward pass of the affine layer
-//                                                    needs z, that of the join only y)
-//   y = act(a + res[m, n])                 -> yout  (res may be null)
+//   a = gain[n] * z + shift[n]             (not stored: the backward pass of the affine layer needs z, that of the join only y)
+//   y = act(a + res[m, n])                 -> yout and, if it is given, again (res may be null)
 // Every stored tensor is rounded to its storage type before the next step reads it, exactly as if the three layers
 // had run one after the other.
 template <typename TOut> struct EpiConvAffine {
@@ -191,13 +192,13 @@ template <typename TOut> struct EpiConvAffine {
     int64_t ld;
     const float* gain;
     const float* shift;
-    TOut* aout;          // affine result; null when the affine layer itself writes yout, or when only the join reads it
+    TOut* again;         // a second place for y (what a stage hands to the next worker); may be null
     const TOut* res;     // second source of the residual join; may be null
     TOut* yout;
     int relu;
     struct Col { float b, g, s; };
     bool wide_ok() const {
-        return ld % 8 == 0 && epi_al16(out) && epi_al16(bias) && epi_al16(gain) && epi_al16(shift) && epi_al16(aout) &&
+        return ld % 8 == 0 && epi_al16(out) && epi_al16(bias) && epi_al16(gain) && epi_al16(shift) && epi_al16(again) &&
                epi_al16(res) && epi_al16(yout);
     }
     __device__ __forceinline__ Col column(int n) const { return Col{bias ? bias[n] : 0.0f, gain[n], shift[n]}; }
@@ -205,11 +206,11 @@ template <typename TOut> struct EpiConvAffine {
         const TOut z = from_f32<TOut>(v + c.b);
         out[idx] = z;
         const TOut ar = from_f32<TOut>(c.g * to_f32(z) + c.s);   // rounded as the stored tensor would be, stored or not
-        if (aout) aout[idx] = ar;
         float a = to_f32(ar);
         if (res) a += to_f32(res[idx]);
         if (relu) a = a > 0.0f ? a : 0.0f;
         yout[idx] = from_f32<TOut>(a);
+        if (again) again[idx] = from_f32<TOut>(a);
     }
     struct Col8 { float b[8], g[8], s[8]; };
     struct Row8 { Raw8<TOut> r; };
@@ -235,7 +236,6 @@ template <typename TOut> struct EpiConvAffine {
         store8(out + idx, v);
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = to_f32(from_f32<TOut>(c.g[e] * v[e] + c.s[e]));   // rounded as the stored tensor would be
-        if (aout) store8(aout + idx, v);
         if (res) {
             float r[8];
             p.r.get(r);
@@ -247,6 +247,7 @@ template <typename TOut> struct EpiConvAffine {
             for (int e = 0; e < 8; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
         }
         store8(yout + idx, v);
+        if (again) store8(again + idx, v);
     }
     __device__ __forceinline__ void rowsum(int, float, int) const {}
 };

@@ -59,7 +59,8 @@ size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t K, int flags);
 
 // y[B, Dout] = act(x[B, Din] w^T + b).  w is the working copy (bf16 or fp32 per dtype), bias fp32.
 // out_f32: write fp32 regardless of dtype (logits).
-// act: 0 none, 1 ReLU, 2 exact GELU (then zout, if not null, receives the derivative gelu'(pre-activation) for the backward pass).  res (may be
+// act: 0 none, 1 ReLU, 2 exact GELU (then zout, if not null, receives the derivative gelu'(pre-activation) for the backward
+// pass; without GELU it receives y once more).  res (may be
 // null): tensor of y's shape and dtype added after the activation (residual connection).
 hipError_t dense_forward(int dtype, const void* x, const void* w, const float* bias, void* y, int B,
                          int Din, int Dout, int act, int out_f32, const void* res, void* zout, float* ws,
@@ -94,11 +95,10 @@ hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_
 
 hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y,
                         const ConvShape& c, int relu, float* ws, hipStream_t s);
-// Convolution (no activation of its own) fused with the per-channel affine layer that follows it and, when res or
-// aout is given, with the residual join after that: y -> z (the convolution's result), aout (may be null) the affine
-// layer's result, yout = act(affine + res) (res may be null).
+// Convolution (no activation of its own) fused with the per-channel affine layer that follows it and, when res is given,
+// with the residual join after that: y -> z (the convolution's result), yout and again (may be null) = act(affine + res).
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain,
-                               const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c,
+                               const float* shift, void* again, const void* res, void* yout, int relu, const ConvShape& c,
                                float* ws, hipStream_t s);
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add,
                       const ConvShape& c, float* ws, hipStream_t s);

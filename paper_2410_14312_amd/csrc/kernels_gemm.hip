@@ -551,7 +551,7 @@ static hipError_t dense_forward_as(int kc, int dtype, const void* x, const void*
                                  B, Din, Dout, ws, s);
     const bool aligned = aligned16(y) && aligned16(bias) && aligned16(res) && aligned16(zout);
     if (out_f32)
-        return dense_forward_bf16(kc, (const bf16_t*)x, (const bf16_t*)w, EpiBiasAct<float>{(float*)y, bias, Dout, relu}, aligned, B, Din, Dout, ws, s);
+        return dense_forward_bf16(kc, (const bf16_t*)x, (const bf16_t*)w, EpiBiasAct<float>{(float*)y, bias, Dout, relu, nullptr, (float*)zout}, aligned, B, Din, Dout, ws, s);
     return dense_forward_bf16(kc, (const bf16_t*)x, (const bf16_t*)w, EpiBiasAct<bf16_t>{(bf16_t*)y, bias, Dout, relu, (const bf16_t*)res, (bf16_t*)zout},
                               aligned, B, Din, Dout, ws, s);
 }
@@ -703,17 +703,17 @@ hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bi
 }
 
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain,
-                               const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c,
+                               const float* shift, void* again, const void* res, void* yout, int relu, const ConvShape& c,
                                float* ws, hipStream_t s) {
     if (dtype != kBF16)
         return conv_affine_f32((const float*)x, (const float*)w,
-                               EpiConvAffine<float>{(float*)z, bias, c.Cout, gain, shift, (float*)aout, (const float*)res, (float*)yout, relu}, c, ws, s);
+                               EpiConvAffine<float>{(float*)z, bias, c.Cout, gain, shift, (float*)again, (const float*)res, (float*)yout, relu}, c, ws, s);
     const int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
     const bf16_t *xb = (const bf16_t*)x, *wb = (const bf16_t*)w;
-    const EpiConvAffine<bf16_t> epi{(bf16_t*)z, bias, c.Cout, gain, shift, (bf16_t*)aout, (const bf16_t*)res, (bf16_t*)yout, relu};
+    const EpiConvAffine<bf16_t> epi{(bf16_t*)z, bias, c.Cout, gain, shift, (bf16_t*)again, (const bf16_t*)res, (bf16_t*)yout, relu};
     if (pointwise(c) && c.Cin % 8 == 0 && aligned16(x) && aligned16(w)) {
         if (g3_forward_ok(M, c.Cout, K) && aligned16(z) && aligned16(bias) && aligned16(gain) && aligned16(shift) &&
-            aligned16(aout) && aligned16(res) && aligned16(yout))
+            aligned16(again) && aligned16(res) && aligned16(yout))
             return launch3<true, true, false>(kcConvFwd, G3Operand<true>{xb, M, K}, G3Operand<true>{wb, c.Cout, K}, epi, M, c.Cout, K,
                                               g3_plan(M, c.Cout, K, 1), s);
         return run2(kcConvFwd, DenseKC<bf16_t>{xb, M, K, K}, DenseKC<bf16_t>{wb, c.Cout, K, K}, epi, M, c.Cout, K, ws, s);

@@ -513,6 +513,11 @@ extern "C" int tmps_stage_use_graphs(tmps_stage* st, int on) {
     return TMPS_OK;
 }
 
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p && q && p < q + nb && q < p + na;
+}
+
 static const void* layer_input(const tmps_stage* st, int li, const void* x0, int64_t row0) {
     return li == 0 ? x0 : (const void*)st->out_ptr(st->layers[li - 1], row0);
 }
@@ -554,6 +559,19 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
     // (asked of a whole mini-batch's rows: all of its passes then run the same kernel, however they are cut)
     const bool small_loss = st->cfg.is_last && softmax_ce_small_takes((int64_t)st->M() * st->label_rps, st->layers.back().d.dims[0]);
     float* const y_by_loss = small_loss && !st->use_graphs ? static_cast<float*>(y) : nullptr;
+    // The result for the next worker leaves the kernel that forms it in two places, where that is a contraction (a copy afterwards reads it once more: 1.5 MB
+    // 3.4 us, 20 MB of logits 8.4, 13 MB 5.1).  Not into what the pass still reads, and not from a captured graph, whose addresses are fixed.
+    const size_t out_layer = st->layers.size() - (st->cfg.is_last ? 2 : 1);
+    const LayerRT& O = st->layers[out_layer];
+    const size_t y_bytes = (size_t)mb * O.out_elems * O.out_esize;
+    const bool twice = y && !y_by_loss && !st->use_graphs && (reinterpret_cast<uintptr_t>(y) & 15) == 0 &&
+                       !overlap(y, y_bytes, x0, (size_t)mb * st->in_elems * st->in_esize);
+    bool y_done = false;
+    auto again = [&](size_t li) -> void* {   // for the result of layer li
+        if (!twice || li != out_layer) return nullptr;
+        y_done = true;
+        return y;
+    };
     const int rc = run_or_replay(st, key, s, [&]() -> int {
     for (size_t li = 0; li < st->layers.size(); ++li) {
         const LayerRT& L = st->layers[li];
@@ -567,7 +585,7 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
                     const int src = (int)li - L.skip;
                     res = src == 0 ? x0 : (const void*)st->out_ptr(st->layers[src - 1], row0);
                 }
-                void* zout = L.act == 2 ? (void*)(st->stash + L.z_off + (size_t)row0 * L.out_elems * st->asz) : nullptr;
+                void* zout = L.act == 2 ? (void*)(st->stash + L.z_off + (size_t)row0 * L.out_elems * st->asz) : again(li);
                 TMPS_GEMM(dense_forward(dt, in, st->wptr(L), st->bptr(L), out, mb * L.rps, d[0], d[1], L.act, L.out_f32, res,
                                         zout, ws, s));
                 break;
@@ -580,17 +598,15 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
                     const LayerRT& A = st->layers[li + 1];
                     const bool join = !A.relu && li + 2 < nl && st->layers[li + 2].d.kind == TMPS_RESADD &&
                                       st->readers[li + 2] == 1;
-                    void* aout = st->out_ptr(A, row0);
                     if (join) {
-                        // the affine result itself is not stored: only the join reads it, and no gradient needs it
                         const LayerRT& J = st->layers[li + 2];
                         const void* b = J.in_b < 0 ? x0 : (const void*)st->out_ptr(st->layers[J.in_b], row0);
                         TMPS_GEMM(conv_affine_forward(dt, in, st->wptr(L), st->bptr(L), out, st->master + A.w_off, st->master + A.b_off,
-                                                      nullptr, b, st->out_ptr(J, row0), J.relu, conv_shape(L.d, mb), ws, s));
+                                                      again(li + 2), b, st->out_ptr(J, row0), J.relu, conv_shape(L.d, mb), ws, s));
                         li += 2;
                     } else {
                         TMPS_GEMM(conv_affine_forward(dt, in, st->wptr(L), st->bptr(L), out, st->master + A.w_off, st->master + A.b_off,
-                                                      nullptr, nullptr, aout, A.relu, conv_shape(L.d, mb), ws, s));
+                                                      again(li + 1), nullptr, st->out_ptr(A, row0), A.relu, conv_shape(L.d, mb), ws, s));
                         li += 1;
                     }
                     break;
@@ -645,11 +661,7 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
     return TMPS_OK;
     });
     if (rc != TMPS_OK) return rc;
-    if (y && !y_by_loss) {
-        const LayerRT& L = st->cfg.is_last ? st->layers[st->layers.size() - 2] : st->layers.back();
-        TMPS_RUN(kcCopy, s, hipMemcpyAsync(y, st->out_ptr(L, row0), (size_t)mb * L.out_elems * L.out_esize,
-                                hipMemcpyDeviceToDevice, s));
-    }
+    if (y && !y_by_loss && !y_done) TMPS_RUN(kcCopy, s, hipMemcpyAsync(y, st->out_ptr(O, row0), y_bytes, hipMemcpyDeviceToDevice, s));
     for (int j = 0; j < count; ++j) st->slot_used[slot + j] = 1;
     return TMPS_OK;
 }
@@ -825,10 +837,6 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
 
     // A caller may have the gradient w.r.t. the input written over the upstream gradient or the input: then every kernel that reads
     // those comes, as they are called, before the one that writes.
-    auto overlap = [](const void* a, size_t na, const void* b, size_t nb) {
-        const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
-        return p && q && p < q + nb && q < p + na;
-    };
     const size_t dx_bytes = (size_t)M * st->in_elems * st->asz;
     const bool in_order = overlap(dx, dx_bytes, dy, (size_t)M * st->out_elems * st->asz) || overlap(dx, dx_bytes, x0, (size_t)M * st->in_elems * st->in_esize);
     Reductions sums;   // left to the end of the pass
