@@ -780,7 +780,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             if (!dx) return TMPS_OK;   // nobody wants the gradient w.r.t. the stage input
             T.wanted = true;
             T.dst = dx;
-            T.add = G.set ? dx : nullptr;
+            T.add = G.set ? G.ptr : nullptr;
             return TMPS_OK;
         }
         T.wanted = true;
@@ -796,6 +796,13 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             return TMPS_OK;
         }
         T.buf = take();
+        if (T.buf < 0 && dx && grads[0].set && grads[0].buf >= 0) {   // (what dx is still to be added to holds one)
+            TMPS_RUN(kcCopy, s, copy_bytes(dx, grads[0].ptr, (size_t)M * st->in_elems * st->asz, s));
+            release(grads[0].buf);
+            grads[0].ptr = dx;
+            grads[0].buf = -1;
+            T.buf = take();
+        }
         if (T.buf < 0) return fail(TMPS_EUNSUPPORTED, "out of gradient buffers (too many open residual connections)");
         T.dst = gbuf[T.buf];
         T.add = G.set ? G.ptr : nullptr;
@@ -810,16 +817,22 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         G.masked = true;   // (by the kernel that wrote it)
         --remaining[t + 1];
     };
+    // A caller may have the gradient w.r.t. the input written over the upstream gradient or the input: then every kernel that reads
+    // those comes, as they are called, before the one that writes.
+    const size_t dx_bytes = (size_t)M * st->in_elems * st->asz;
+    const bool in_order = overlap(dx, dx_bytes, dy, (size_t)M * st->out_elems * st->asz) || overlap(dx, dx_bytes, x0, (size_t)M * st->in_elems * st->in_esize);
     // hand an existing gradient (g) to result t as its contribution, without a kernel when it is the first
     auto share = [&](int t, const Grad& g) -> int {
         if (t < 0 && !dx) return TMPS_OK;
         Grad& G = grads[t + 1];
         const int64_t n = (int64_t)M * st->tensor_elems(t);
-        if (t < 0) {
-            if (G.set) TMPS_GEMM(resadd_forward(dt, dx, g.ptr, dx, n, 0, s));
+        if (t < 0 && (G.set || in_order || remaining[0] == 1)) {
+            if (G.set) TMPS_GEMM(resadd_forward(dt, G.ptr, g.ptr, dx, n, 0, s));
             else TMPS_RUN(kcCopy, s, copy_bytes(dx, g.ptr, (size_t)n * st->asz, s));
+            release(G.buf);
             G.ptr = dx; G.buf = -1; G.set = true;
         } else if (!G.set) {
+            // (also of the stage input: the layer that reads it beside this one adds this to its own contribution and writes dx)
             G = g;
             if (g.buf >= 0) ++refs[g.buf];
         } else {
@@ -835,10 +848,6 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         return TMPS_OK;
     };
 
-    // A caller may have the gradient w.r.t. the input written over the upstream gradient or the input: then every kernel that reads
-    // those comes, as they are called, before the one that writes.
-    const size_t dx_bytes = (size_t)M * st->in_elems * st->asz;
-    const bool in_order = overlap(dx, dx_bytes, dy, (size_t)M * st->out_elems * st->asz) || overlap(dx, dx_bytes, x0, (size_t)M * st->in_elems * st->in_esize);
     Reductions sums;   // left to the end of the pass
     auto partials = [&](const LayerRT& L) {
         return L.part_elems ? Partials(reinterpret_cast<float*>(st->scratch + L.part_off), &sums) : Partials(ws);
