@@ -457,6 +457,60 @@ __global__ __launch_bounds__(256) void embedding_bwd_tok_kernel(const int32_t* _
     }
 }
 
+// Both table gradients of small tables in one launch: a wave to a token, which collects the rows that have it in row order (none: its row is zero), and
+// behind those workgroups a thread to an element of the position table.  The sums are those of the two kernels above, bit for bit.  256 rows of
+// 64 features, 96 tokens: one launch of 3.4 us for three of 1.9, 4.3 and 2.6.
+template <typename T>
+__global__ __launch_bounds__(256) void embedding_bwd_small_kernel(const int32_t* __restrict__ tok, const T* __restrict__ dy, float* __restrict__ dwte,
+                                                                  float* __restrict__ dwpe, int rows, int D, int vocab, int tok_blocks, int B, int64_t SD) {
+    if ((int)blockIdx.x >= tok_blocks) {
+        const int64_t i = (int64_t)(blockIdx.x - tok_blocks) * 256 + threadIdx.x;
+        if (i >= SD) return;
+        float a = 0.0f;
+#pragma unroll 4
+        for (int b = 0; b < B; ++b) a += to_f32(dy[b * SD + i]);
+        dwpe[i] = a;
+        return;
+    }
+    constexpr int CAP = 64;   // rows collected before they are added up
+    __shared__ int list[4][CAP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = blockIdx.x * 4 + wave;
+    if (t >= vocab) return;
+    float* const dst = dwte + (int64_t)t * D;
+    int n = 0;
+    bool begun = false;
+    auto add_up = [&]() {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the list is one wave's: its LDS operations complete in order)
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < D; i += 64) {
+            float a = begun ? dst[i] : n > 0 ? to_f32(dy[(int64_t)list[wave][0] * D + i]) : 0.0f;
+#pragma unroll 4
+            for (int k = begun ? 0 : 1; k < n; ++k) a += to_f32(dy[(int64_t)list[wave][k] * D + i]);
+            dst[i] = a;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        begun = true;
+        n = 0;
+    };
+    for (int base = 0; base < rows; base += 256) {
+        int v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = base + u * 64 + lane;
+            v[u] = j < rows ? tok[j] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const unsigned long long m = __ballot(v[u] == t);
+            if (!m) continue;
+            if (n + __popcll(m) > CAP) add_up();
+            if (v[u] == t) list[wave][n + __popcll(m & ((1ull << lane) - 1))] = base + u * 64 + lane;
+            n += __popcll(m);
+        }
+    }
+    if (n > 0 || !begun) add_up();
+}
+
 hipError_t embedding_forward(int dtype, const int32_t* tok, const void* wte, const void* wpe, void* y, int64_t rows, int S,
                              int D, int vocab, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
@@ -472,6 +526,17 @@ hipError_t embedding_backward(int dtype, const int32_t* tok, const void* dy, flo
                               int D, int vocab, hipStream_t s) {
     if (B <= 0) return hipSuccess;
     const int64_t nw = (int64_t)vocab * D, SD = (int64_t)S * D, rows = B * S;
+    // (a wave to a token reads all rows' tokens, 16 thousand steps of 64 at most, some 16 to a SIMD; with larger tables the launches below, a wave to a
+    // row, are the ones with less to read, and their three launches are no longer what counts)
+    if (rows * vocab <= (int64_t(1) << 20) && SD <= (int64_t(1) << 20)) {
+        const int tok_blocks = cdiv_tf(vocab, 4);
+        const dim3 grid(tok_blocks + cdiv_tf(SD, 256));
+        if (dtype == kBF16)
+            return launch_timed(kcEmbedding, embedding_bwd_small_kernel<bf16_t>, grid, dim3(256), 0, s, tok, (const bf16_t*)dy, dwte, dwpe, (int)rows, D, vocab,
+                                tok_blocks, (int)B, SD);
+        return launch_timed(kcEmbedding, embedding_bwd_small_kernel<float>, grid, dim3(256), 0, s, tok, (const float*)dy, dwte, dwpe, (int)rows, D, vocab,
+                            tok_blocks, (int)B, SD);
+    }
     int zb = cdiv_tf(nw, 256);
     if (zb > 4096) zb = 4096;
     hipError_t e = launch_timed(kcEmbedding, zero_f32_kernel, dim3(zb), dim3(256), 0, s, dwte, nw);
