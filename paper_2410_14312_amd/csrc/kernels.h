@@ -176,6 +176,17 @@ hipError_t relu_mask(int dtype, const void* dy, const void* y, void* dz, int64_t
 // buf <- mu*buf + g;  w <- w - lr*buf;  wcopy <- bf16(w) when wcopy != null
 hipError_t sgd_momentum(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr,
                         float mu, hipStream_t s);
+// Up to kUpdateMax of them in one launch.
+constexpr int kUpdateMax = 16;
+struct Update {
+    float* w;
+    float* buf;
+    const float* g;
+    void* wcopy;
+    int64_t n;
+    float lr, mu;
+};
+hipError_t sgd_momentum_all(const Update* list, int n, hipStream_t s);
 // The same; w and wcopy as they were before go to kept_w and kept_wcopy (arrays that overlap none of the others).
 hipError_t sgd_momentum_keeping(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu,
                                 float* kept_w, void* kept_wcopy, hipStream_t s);

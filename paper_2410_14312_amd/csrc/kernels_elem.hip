@@ -426,13 +426,12 @@ hipError_t relu_mask(int dtype, const void* dy, const void* y, void* dz, int64_t
 // over the parameters.  (Two mini-batches of VGG-16 with vertical weight stashing 2325 -> 2258 us, one of GPT-2 in 1F1B order
 // 23.29 -> 22.83 ms, whose copies of 0.13 to 0.26 GB took 52 us each.)
 template <bool KEEP>
-__global__ __launch_bounds__(256) void sgd_momentum_kernel(float* __restrict__ w, float* __restrict__ buf,
-                                                           const float* __restrict__ g,
-                                                           bf16_t* __restrict__ wc, int64_t n, float lr,
-                                                           float mu, float* __restrict__ kept_w, bf16_t* __restrict__ kept_wc) {
+__device__ __forceinline__ void sgd_momentum_block(int block, int blocks, float* __restrict__ w, float* __restrict__ buf,
+                                                   const float* __restrict__ g, bf16_t* __restrict__ wc, int64_t n, float lr,
+                                                   float mu, float* __restrict__ kept_w, bf16_t* __restrict__ kept_wc) {
     const int64_t n4 = n >> 2;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    int64_t i = (int64_t)block * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)blocks * blockDim.x;
     for (; i < n4; i += stride) {
         float4 wv = reinterpret_cast<const float4*>(w)[i];
         float4 bv = reinterpret_cast<const float4*>(buf)[i];
@@ -451,7 +450,7 @@ __global__ __launch_bounds__(256) void sgd_momentum_kernel(float* __restrict__ w
             reinterpret_cast<uint2*>(wc)[i] = pk.u;
         }
     }
-    int64_t t = (n4 << 2) + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int64_t t = (n4 << 2) + (int64_t)block * blockDim.x + threadIdx.x;
     if (t < n) {
         float b = mu * buf[t] + g[t];
         if (KEEP) {
@@ -465,6 +464,47 @@ __global__ __launch_bounds__(256) void sgd_momentum_kernel(float* __restrict__ w
     }
 }
 
+template <bool KEEP>
+__global__ __launch_bounds__(256) void sgd_momentum_kernel(float* __restrict__ w, float* __restrict__ buf,
+                                                           const float* __restrict__ g,
+                                                           bf16_t* __restrict__ wc, int64_t n, float lr,
+                                                           float mu, float* __restrict__ kept_w, bf16_t* __restrict__ kept_wc) {
+    sgd_momentum_block<KEEP>(blockIdx.x, gridDim.x, w, buf, g, wc, n, lr, mu, kept_w, kept_wc);
+}
+
+// The updates of several stages in one launch.  A run on one stream is bound by its launches where the stages are small, 2.5 to 3 us each on the device and 3.1 on the host.
+struct SgdJobs {
+    int first[kUpdateMax + 1];   // first workgroup of a stage; behind the last one the number of workgroups
+    Update job[kUpdateMax];
+};
+__global__ __launch_bounds__(256) void sgd_momentum_all_kernel(SgdJobs all) {
+    int j = 0;
+#pragma unroll
+    for (int k = 1; k < kUpdateMax; ++k) j += (int)blockIdx.x >= all.first[k] ? 1 : 0;
+    const Update u = all.job[j];
+    sgd_momentum_block<false>(blockIdx.x - all.first[j], all.first[j + 1] - all.first[j], u.w, u.buf, u.g, (bf16_t*)u.wcopy, u.n, u.lr, u.mu, nullptr, nullptr);
+}
+
+static int sgd_blocks(int64_t n) {
+    const int blocks = cdiv64((n >> 2) + 4, 256);
+    return blocks > 2048 ? 2048 : blocks;
+}
+
+hipError_t sgd_momentum_all(const Update* list, int n, hipStream_t s) {
+    if (n < 1 || n > kUpdateMax) return n < 1 ? hipSuccess : hipErrorInvalidValue;
+    SgdJobs all;
+    int blocks = 0;
+    for (int k = 0; k <= kUpdateMax; ++k) {
+        all.first[k] = blocks;
+        if (k == kUpdateMax) break;
+        all.job[k] = k < n ? list[k] : Update{};
+        if (k < n && list[k].n > 0) blocks += sgd_blocks(list[k].n);
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(sgd_momentum_all_kernel, dim3(blocks), dim3(256), 0, s, all);
+    return hipGetLastError();
+}
+
 hipError_t sgd_momentum(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu,
                         hipStream_t s) {
     return sgd_momentum_keeping(w, buf, g, wcopy_bf16, n, lr, mu, nullptr, nullptr, s);
@@ -473,8 +513,7 @@ hipError_t sgd_momentum(float* w, float* buf, const float* g, void* wcopy_bf16, 
 hipError_t sgd_momentum_keeping(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu,
                                 float* kept_w, void* kept_wcopy, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    int blocks = cdiv64((n >> 2) + 4, 256);
-    if (blocks > 2048) blocks = 2048;
+    const int blocks = sgd_blocks(n);
     if (kept_w)
         hipLaunchKernelGGL(sgd_momentum_kernel<true>, dim3(blocks), dim3(256), 0, s, w, buf, g, (bf16_t*)wcopy_bf16, n,
                            lr, mu, kept_w, (bf16_t*)kept_wcopy);

@@ -55,6 +55,7 @@ struct RunCtx {
     bool vsync = false;              // forward passes read the weight version they are tagged with
     bool one_f1b = false;            // the comparison system: a backward pass per batch, on the weights of its forward pass
     bool one_queue = false;          // all stages issue on one stream: its order stands for the events
+    std::vector<tmps_stage*> updates;   // then: stages whose update is still to be issued, with those of other stages or before their next pass
     std::vector<long> base_version;  // every stage's version when the run started
     tmps_stage** stages;
     int K, N, M, mb, n_minibatches;
@@ -125,10 +126,21 @@ struct RunCtx {
     }
 };
 
+int issue_updates(RunCtx& c) {
+    if (c.updates.empty()) return TMPS_OK;
+    const int rc = update_all(c.updates.data(), (int)c.updates.size(), c.streams[0]);
+    c.updates.clear();
+    return rc;
+}
+
 // Issue one node on its stage's stream.
 int issue(RunCtx& c, const Node& n) {
     tmps_stage* st = c.stages[n.stage];
     hipStream_t s = (hipStream_t)(c.one_queue ? c.streams[0] : c.streams[n.stage]);
+    if (std::find(c.updates.begin(), c.updates.end(), st) != c.updates.end()) {
+        const int rc = issue_updates(c);
+        if (rc != TMPS_OK) return rc;
+    }
     const int b0 = n.b0, N = c.N, K = c.K;
     if (c.log) {
         const int32_t live = (int32_t)(st->version - c.base_version[n.stage]);
@@ -185,7 +197,8 @@ int issue(RunCtx& c, const Node& n) {
             rc = backward_between(st, slots, N, dy, dx, s, flags);
         if (rc != TMPS_OK) return rc;
         if ((rc = c.record(c.bwd_ev(n.stage, b0), s)) != TMPS_OK) return rc;
-        if ((rc = tmps_update(st, s)) != TMPS_OK) return rc;
+        if (c.one_queue) c.updates.push_back(st);
+        else if ((rc = tmps_update(st, s)) != TMPS_OK) return rc;
     }
     return TMPS_OK;
 }
@@ -272,14 +285,18 @@ int issue_all(RunCtx& c) {
         }
         if (!best) {
             // nothing is ready: everything has been issued, or the order asks for a pass that never comes
+            const int rc = issue_updates(c);
             for (int s = 0; s < c.K; ++s)
                 if (head[s] < c.nodes[s].size())
                     return fail(TMPS_EINVAL, "the schedule's order cannot be satisfied: stage %d is left with %zu of %zu passes", s,
                                 c.nodes[s].size() - head[s], c.nodes[s].size());
-            return TMPS_OK;
+            return rc;
         }
         const int rc = issue(c, *best);
-        if (rc != TMPS_OK) return rc;
+        if (rc != TMPS_OK) {
+            (void)issue_updates(c);   // (of the passes before)
+            return rc;
+        }
         ++head[best->stage];
     }
 }

@@ -1053,6 +1053,29 @@ extern "C" int tmps_update(tmps_stage* st, void* hip_stream) {
     return TMPS_OK;
 }
 
+int tmps::update_all(tmps_stage* const* stages, int n, void* hip_stream) {
+    hipStream_t s = (hipStream_t)hip_stream;
+    Update list[kUpdateMax];
+    int k = 0;
+    auto flush = [&]() -> int {
+        if (k > 0) TMPS_RUN(kcUpdate, s, sgd_momentum_all(list, k, s));
+        k = 0;
+        return TMPS_OK;
+    };
+    int rc;
+    for (int i = 0; i < n; ++i) {
+        tmps_stage* st = stages[i];
+        if (n == 1 || st->shadow_n > 0) {
+            if ((rc = tmps_update(st, hip_stream)) != TMPS_OK) return rc;
+            continue;
+        }
+        if (k == kUpdateMax && (rc = flush()) != TMPS_OK) return rc;
+        list[k++] = Update{st->master, st->mom, st->grad, st->wcopy, st->P, st->cfg.lr, st->cfg.momentum};
+        ++st->version;
+    }
+    return flush();
+}
+
 extern "C" int tmps_backward_at(tmps_stage* st, long version, const int* slots, int n_slots, const void* dy, void* dx,
                                 void* hip_stream) {
     return backward_between_at(st, version, slots, n_slots, dy, dx, hip_stream, 0);

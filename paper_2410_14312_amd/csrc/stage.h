@@ -122,6 +122,8 @@ int forward_run_at(tmps_stage* st, long version, int slot, int count, const void
 // pass is told so (kDyMasked) and makes no pass over the gradient for it.
 enum { kMaskDx = 1, kDyMasked = 2 };
 bool can_mask_dx(const tmps_stage& st);
+// tmps_update of several stages, in one launch where they keep no older versions.
+int update_all(tmps_stage* const* stages, int n, void* hip_stream);
 int backward_between(tmps_stage* st, const int* slots, int n_slots, const void* dy, void* dx, void* hip_stream, int flags);
 int backward_between_at(tmps_stage* st, long version, const int* slots, int n_slots, const void* dy, void* dx, void* hip_stream, int flags);
 }  // namespace tmps

@@ -48,6 +48,7 @@ hipError_t softmax_ce_small(int, const float*, const int32_t*, void*, float*, fl
 hipError_t reduce_scaled_sum(const float* in, int n, float scale, float* out, hipStream_t s) { return hipSuccess; }
 hipError_t relu_mask(int dtype, const void* dy, const void* y, void* dz, int64_t n, hipStream_t s) { return hipSuccess; }
 hipError_t sgd_momentum(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu, hipStream_t s) { return hipSuccess; }
+hipError_t sgd_momentum_all(const Update*, int, hipStream_t) { return hipSuccess; }
 hipError_t sgd_momentum_keeping(float* w, float* buf, const float* g, void* wcopy_bf16, int64_t n, float lr, float mu, float* kept_w, void* kept_wcopy, hipStream_t s) {
     memcpy(kept_w, w, (size_t)n * 4);
     if (wcopy_bf16) memcpy(kept_wcopy, wcopy_bf16, (size_t)n * 2);
