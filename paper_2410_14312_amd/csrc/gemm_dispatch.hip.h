@@ -184,6 +184,21 @@ static hipError_t run_small(int kc, const AOp& A, const BOp& B, const Epi& epi, 
     return small_inst<8, 1, 1, ROWSUM>(kc, A, B, epi, M, N, K, s);
 }
 
+// A layer normalisation and the dense layer behind it on the small kernel: rows of one piece to a lane, a contraction that four waves share in one step
+// each, and a dense layer that this kernel takes in 16 x 16 tiles by itself.
+template <class T> static bool norm_dense_takes(int64_t rows, int D, int N) {
+    constexpr int esize = sizeof(T);
+    if (D % 8 != 0 || D > 4 * (64 / esize) || !small_is_better(rows, N, D, esize, plan_for(rows, N, D, false, esize, kByKDense))) return false;
+    const SmallPlan p = small_plan(rows, N, D, esize);
+    return p.tm == 1 && p.tn == 1;
+}
+template <class T, class Epi>
+static hipError_t norm_dense_small(int kc, const T* x, const float* gamma, const float* beta, T* y, float* stats, const T* w, const Epi& epi, int M, int N, int D,
+                                   float eps, hipStream_t s) {
+    const int lds = small_lds_floats(kNormWaves, 1, 1) * 4 + 16 * small_norm_ld<T>(D) * (int)sizeof(T);
+    return launch_timed(kc, norm_dense_small_kernel<T, Epi>, dim3(cdiv(N, 16), cdiv(M, 16)), dim3(64 * kNormWaves), lds, s, x, gamma, beta, y, stats, w, epi, M, N, D, eps);
+}
+
 // ---- element-wise gathering instances (kernels_gemm_gather.hip, both types) ------------------------------
 template <class T, class Epi> hipError_t gather_dense_kc_kc(int kc, const T* a, const T* b, const Epi& epi, int M, int N, int K, float* ws, hipStream_t s);
 template <class T> hipError_t gather_dense_dgrad(int kc, const T* dy, const T* w, const EpiMask<T, T>& epi, int M, int N, int K, float* ws, hipStream_t s);
@@ -377,6 +392,9 @@ static inline bool pointwise(const ConvShape& c) {
 
 // fp32 passes (kernels_gemm_f32.hip)
 hipError_t dense_forward_f32(int kc, const float* x, const float* w, const EpiBiasAct<float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
+bool norm_dense_takes_f32(int64_t rows, int D, int N);
+hipError_t norm_dense_f32(const float* x, const float* gamma, const float* beta, float* y, float* stats, const float* w, const EpiBiasAct<float>& epi, int M, int N,
+                          int D, float eps, hipStream_t s);
 hipError_t dense_dgrad_f32(int kc, const float* dy, const float* w, const EpiMask<float, float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s);
 hipError_t dense_wgrad_f32(int kc, const float* dy, const float* x, float* gw, int B, int Din, int Dout, const Partials& ws, hipStream_t s);
 hipError_t small_backward_f32(int kc, const float* dy, const float* x, const float* w, float* gw, const EpiMask<float, float>& epi, int B, int Din, int Dout, hipStream_t s);

@@ -12,16 +12,18 @@
 // 3.8, 64 x 3072 -> 1024 11.7 (in k-slices) and 7.4, 256 x 1024 -> 1024 5.9 and 5.8 (what its sums' second set takes of that stands below).
 #pragma once
 #include "gemm2.hip.h"
+#include "wave.hip.h"
 
 namespace tmps {
 
 // Operand of the small kernel.  KC: element (row, k) at p[row * ld + k], otherwise at p[k * ld + row].
 template <class T_, bool KC> struct SmallOperand {
     typedef T_ T;
-    static constexpr bool kContig = KC;
+    static constexpr bool kContig = KC, kLocal = false;
     const T* p;
     int rows;
     int64_t ld;
+    __device__ __forceinline__ void prepare() const {}
 };
 
 // Fragment of a lane (row lane % 16, quarter lane / 16): V elements from k on, at p (k-contiguous) or p, p + ld, ...
@@ -63,7 +65,7 @@ __device__ __forceinline__ void gemm_small_tile(const AOp& A, const BOp& B, cons
     const T *pa[TM], *pb[TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        const int r = min(m0 + 16 * i + row, M - 1);
+        const int r = AOp::kLocal ? 16 * i + row : min(m0 + 16 * i + row, M - 1);
         pa[i] = AKC ? A.p + (int64_t)r * A.ld + quarter * V : A.p + (int64_t)(quarter * V) * A.ld + r;
     }
 #pragma unroll
@@ -131,17 +133,35 @@ __device__ __forceinline__ void gemm_small_tile(const AOp& A, const BOp& B, cons
         }
     };
     frag_t fa[D][TM], fb[D][TN];   // ring: step i of this wave in place i % D
-    auto fetch = [&](int d, int i) {
+    auto fetch_a = [&](int d, int i) {
         const int64_t k = (int64_t)(wave + i * NW) * GK;
 #pragma unroll
         for (int t = 0; t < TM; ++t) fa[d][t] = small_frag<T, AKC>(pa[t] + (AKC ? k : k * A.ld), A.ld);
+    };
+    auto fetch_b = [&](int d, int i) {
+        const int64_t k = (int64_t)(wave + i * NW) * GK;
 #pragma unroll
         for (int t = 0; t < TN; ++t) fb[d][t] = small_frag<T, BKC>(pb[t] + (BKC ? k : k * B.ld), B.ld);
     };
+    auto fetch = [&](int d, int i) {
+        fetch_a(d, i);
+        fetch_b(d, i);
+    };
     const int mine_n = wave < groups ? (groups - wave + NW - 1) / NW : 0;
+    if constexpr (AOp::kLocal) {   // (formed by the workgroup itself, while its first fragments of B are on their way)
 #pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (d < mine_n) fetch(d, d);
+        for (int d = 0; d < D; ++d)
+            if (d < mine_n) fetch_b(d, d);
+        A.prepare();
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d < mine_n) fetch_a(d, d);
+    } else {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d < mine_n) fetch(d, d);
+    }
     int i = 0;
     // (no branch around a load here: the compiler then waits for a step with the younger ones still in flight)
     for (; i + 2 * D <= mine_n; i += D) {
@@ -210,6 +230,95 @@ __device__ __forceinline__ void gemm_small_tile(const AOp& A, const BOp& B, cons
 template <int NW, int TM, int TN, bool ROWSUM, class AOp, class BOp, class Epi>
 __global__ __launch_bounds__(64 * NW, sizeof(typename AOp::T) == 4 ? 3 : 1) void gemm_small_kernel(AOp A, BOp B, Epi epi, int M, int N, int K) {
     gemm_small_tile<NW, TM, TN, ROWSUM>(A, B, epi, M, N, K, blockIdx.x, blockIdx.y);
+}
+
+// A layer normalisation and the dense layer that reads it: y = normalise(x) gamma + beta (with the rows' statistics, as the normalisation's own kernel
+// leaves them), C = y w^T.  Every workgroup normalises its 16 rows itself, four to a wave, rounds them to LDS and multiplies from there; those of the
+// first column of tiles store them.  For rows that one piece of V features to a lane holds, where the layer's launch costs as much as all of
+// its work: 256 x 64 -> 192 in fp32 4.9 us for 2.6 and 3.2 in two launches, and 3 us less of a host thread that issues nothing but short launches
+// (two mini-batches of two transformer blocks of width 64, two stages: 332 and 314 us).
+template <class T> struct SmallNormalised : SmallOperand<T, true> {
+    static constexpr bool kLocal = true;
+    static constexpr int V = sizeof(T) == 2 ? 8 : 1;
+    const T* x;        // [M][D] in global memory
+    const float* gamma;
+    const float* beta;
+    T* y;              // null: not to be stored by this workgroup
+    float* stats;
+    int m0, M, D;
+    float eps;
+    __device__ __forceinline__ void prepare() const {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane * V;
+        T* const tile = const_cast<T*>(this->p);
+        float v[4][V], g[V], b[V];
+        const bool mine = c < D;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = min(m0 + wave * 4 + r, M - 1);
+            if (mine) {
+                if constexpr (V == 8) load8(x + (int64_t)row * D + c, v[r]);
+                else v[r][0] = to_f32(x[(int64_t)row * D + c]);
+            }
+        }
+        if (mine) {
+            if constexpr (V == 8) {
+                load8(gamma + c, g);
+                load8(beta + c, b);
+            } else {
+                g[0] = gamma[c];
+                b[0] = beta[c];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float s = 0.0f, q = 0.0f;
+            if (mine) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) s += v[r][e];
+            }
+            const float mean = wsum(s) / (float)D;
+            if (mine) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const float d = v[r][e] - mean;
+                    q += d * d;
+                }
+            }
+            const float rstd = 1.0f / sqrtf(wsum(q) / (float)D + eps);
+            const int local = wave * 4 + r, row = m0 + local;
+            if (mine) {
+                float o[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) o[e] = (v[r][e] - mean) * rstd * g[e] + b[e];
+                if constexpr (V == 8) {
+                    store8(tile + local * this->ld + c, o);
+                    if (y && row < M) store8(y + (int64_t)row * D + c, o);
+                } else {
+                    tile[local * this->ld + c] = from_f32<T>(o[0]);
+                    if (y && row < M) y[(int64_t)row * D + c] = from_f32<T>(o[0]);
+                }
+            }
+            if (y && lane == 0 && row < M) {
+                stats[2 * row] = mean;
+                stats[2 * row + 1] = rstd;
+            }
+        }
+    }
+};
+constexpr int kNormWaves = 4;
+template <class T> constexpr int small_norm_ld(int D) { return D + 16 / (int)sizeof(T); }   // elements of a row in LDS
+template <class T, class Epi>
+__global__ __launch_bounds__(64 * kNormWaves) void norm_dense_small_kernel(const T* x, const float* gamma, const float* beta, T* y, float* stats, const T* w, Epi epi,
+                                                                          int M, int N, int D, float eps) {
+    extern __shared__ __attribute__((aligned(16))) float part[];
+    SmallNormalised<T> A;
+    A.p = reinterpret_cast<const T*>(part + small_lds_floats(kNormWaves, 1, 1));
+    A.rows = 16;
+    A.ld = small_norm_ld<T>(D);
+    A.x = x; A.gamma = gamma; A.beta = beta; A.stats = stats;
+    A.y = blockIdx.x == 0 ? y : nullptr;
+    A.m0 = blockIdx.y * 16; A.M = M; A.D = D; A.eps = eps;
+    gemm_small_tile<kNormWaves, 1, 1, false>(A, SmallOperand<T, true>{w, N, D}, epi, M, N, D, blockIdx.x, blockIdx.y);
 }
 
 // Input and weight gradient of a dense layer in one launch: dx[B, Din] = dy w and gw[Dout, Din] = dy^T x, the longer contraction by the first

@@ -65,6 +65,11 @@ size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t K, int flags);
 hipError_t dense_forward(int dtype, const void* x, const void* w, const float* bias, void* y, int B,
                          int Din, int Dout, int act, int out_f32, const void* res, void* zout, float* ws,
                          hipStream_t s);
+// A layer normalisation (y and stats as layernorm_forward leaves them) and the dense layer that reads it (as dense_forward) in one launch;
+// norm_dense_takes: where that is quicker.
+bool norm_dense_takes(int dtype, int64_t rows, int D, int Dout);
+hipError_t norm_dense_forward(int dtype, const void* x, const float* gamma, const float* beta, void* y, float* stats, float eps, const void* w, const float* bias,
+                              void* out, int rows, int D, int Dout, int act, int out_f32, const void* res, void* zout, hipStream_t s);
 // dx[B, Din] = dy[B, Dout] w, passed through the activation of the layer below: mask_mode 1: zeroed
 // where mask[B, Din] <= 0 (mask = that layer's output); mask_mode 2: times gelu'(mask) (mask = that
 // layer's pre-activation).  mask may be null; activation dtype.

@@ -561,6 +561,26 @@ hipError_t dense_forward(int dtype, const void* x, const void* w, const float* b
     return dense_forward_as(tmps::kcDenseFwd, dtype, x, w, bias, y, B, Din, Dout, relu, out_f32, res, zout, ws, s);
 }
 
+bool norm_dense_takes(int dtype, int64_t rows, int D, int Dout) {
+    return dtype == kBF16 ? norm_dense_takes<bf16_t>(rows, D, Dout) : norm_dense_takes_f32(rows, D, Dout);
+}
+hipError_t norm_dense_forward(int dtype, const void* x, const float* gamma, const float* beta, void* y, float* stats, float eps, const void* w, const float* bias,
+                              void* out, int rows, int D, int Dout, int act, int out_f32, const void* res, void* zout, hipStream_t s) {
+    const bool vec = dtype != kBF16 || (aligned16(x) && aligned16(y) && aligned16(gamma) && aligned16(beta));
+    if (!vec) {
+        const hipError_t e = layernorm_forward(dtype, x, gamma, beta, y, stats, rows, D, eps, s);
+        return e != hipSuccess ? e : dense_forward(dtype, y, w, bias, out, rows, D, Dout, act, out_f32, res, zout, nullptr, s);
+    }
+    if (dtype != kBF16)
+        return norm_dense_f32((const float*)x, gamma, beta, (float*)y, stats, (const float*)w,
+                              EpiBiasAct<float>{(float*)out, bias, Dout, act, (const float*)res, (float*)zout}, rows, Dout, D, eps, s);
+    if (out_f32)
+        return norm_dense_small<bf16_t>(kcDenseFwd, (const bf16_t*)x, gamma, beta, (bf16_t*)y, stats, (const bf16_t*)w,
+                                        EpiBiasAct<float>{(float*)out, bias, Dout, act, nullptr, (float*)zout}, rows, Dout, D, eps, s);
+    return norm_dense_small<bf16_t>(kcDenseFwd, (const bf16_t*)x, gamma, beta, (bf16_t*)y, stats, (const bf16_t*)w,
+                                    EpiBiasAct<bf16_t>{(bf16_t*)out, bias, Dout, act, (const bf16_t*)res, (bf16_t*)zout}, rows, Dout, D, eps, s);
+}
+
 static hipError_t dense_dgrad_as(int kc, int dtype, const void* dy, const void* w, void* dx, const void* mask, int mask_mode,
                                  const void* add, int B, int Din, int Dout, float* ws, hipStream_t s) {
     // dx[m, n] = sum_k dy[m, k] * w[k, n]:  A = dy (k-contiguous), B(n, k) = w[k*Din + n] (row-contiguous)

@@ -6,6 +6,11 @@ namespace tmps {
 hipError_t dense_forward_f32(int kc, const float* x, const float* w, const EpiBiasAct<float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s) {
     return dense_forward_t<float>(kc, x, w, epi, B, Din, Dout, ws, s);
 }
+bool norm_dense_takes_f32(int64_t rows, int D, int N) { return norm_dense_takes<float>(rows, D, N); }
+hipError_t norm_dense_f32(const float* x, const float* gamma, const float* beta, float* y, float* stats, const float* w, const EpiBiasAct<float>& epi, int M, int N,
+                          int D, float eps, hipStream_t s) {
+    return norm_dense_small<float>(kcDenseFwd, x, gamma, beta, y, stats, w, epi, M, N, D, eps, s);
+}
 hipError_t dense_dgrad_f32(int kc, const float* dy, const float* w, const EpiMask<float, float>& epi, int B, int Din, int Dout, float* ws, hipStream_t s) {
     return dense_dgrad_t<float>(kc, dy, w, epi, B, Din, Dout, ws, s);
 }

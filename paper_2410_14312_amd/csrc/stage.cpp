@@ -572,6 +572,11 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
         y_done = true;
         return y;
     };
+    auto skipped = [&](size_t li) -> const void* {   // what a residual connection adds to the result of layer li
+        const int src = (int)li - st->layers[li].skip;
+        if (!st->layers[li].skip) return nullptr;
+        return src == 0 ? x0 : (const void*)st->out_ptr(st->layers[src - 1], row0);
+    };
     const int rc = run_or_replay(st, key, s, [&]() -> int {
     for (size_t li = 0; li < st->layers.size(); ++li) {
         const LayerRT& L = st->layers[li];
@@ -580,11 +585,7 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
         const void* in = L.in_t < 0 ? x0 : (const void*)st->out_ptr(st->layers[L.in_t], row0);
         switch (L.d.kind) {
             case TMPS_LINEAR: {
-                const void* res = nullptr;
-                if (L.skip) {
-                    const int src = (int)li - L.skip;
-                    res = src == 0 ? x0 : (const void*)st->out_ptr(st->layers[src - 1], row0);
-                }
+                const void* res = skipped(li);
                 void* zout = L.act == 2 ? (void*)(st->stash + L.z_off + (size_t)row0 * L.out_elems * st->asz) : again(li);
                 TMPS_GEMM(dense_forward(dt, in, st->wptr(L), st->bptr(L), out, mb * L.rps, d[0], d[1], L.act, L.out_f32, res,
                                         zout, ws, s));
@@ -629,11 +630,19 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
             case TMPS_AVGPOOL:
                 TMPS_GEMM(avgpool_forward(dt, in, out, mb, d[0] * d[1], d[2], s));
                 break;
-            case TMPS_LAYERNORM:
-                TMPS_GEMM(layernorm_forward(dt, in, st->master + L.w_off, st->master + L.b_off, out,
-                                            reinterpret_cast<float*>(st->stash + L.aux_off) + (size_t)row0 * L.rps * 2,
-                                            (int64_t)mb * L.rps, d[0], 1e-5f, s));
+            case TMPS_LAYERNORM: {
+                float* stats = reinterpret_cast<float*>(st->stash + L.aux_off) + (size_t)row0 * L.rps * 2;
+                if (li + 1 < st->layers.size() && st->layers[li + 1].d.kind == TMPS_LINEAR && st->layers[li + 1].rps == L.rps &&
+                    norm_dense_takes(dt, (int64_t)mb * L.rps, d[0], st->layers[li + 1].d.dims[1])) {
+                    const LayerRT& F = st->layers[++li];
+                    void* zout = F.act == 2 ? (void*)(st->stash + F.z_off + (size_t)row0 * F.out_elems * st->asz) : again(li);
+                    TMPS_GEMM(norm_dense_forward(dt, in, st->master + L.w_off, st->master + L.b_off, out, stats, 1e-5f, st->wptr(F), st->bptr(F),
+                                                 st->out_ptr(F, row0), mb * L.rps, d[0], F.d.dims[1], F.act, F.out_f32, skipped(li), zout, s));
+                    break;
+                }
+                TMPS_GEMM(layernorm_forward(dt, in, st->master + L.w_off, st->master + L.b_off, out, stats, (int64_t)mb * L.rps, d[0], 1e-5f, s));
                 break;
+            }
             case TMPS_ATTENTION:
                 TMPS_GEMM(attention_forward(dt, in, out,
                                             reinterpret_cast<float*>(st->stash + L.aux_off) + (size_t)row0 * d[2] * d[0], mb,

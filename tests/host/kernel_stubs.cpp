@@ -19,6 +19,8 @@ hipError_t dense_backward(int, const void*, const void*, const void*, float*, vo
 bool dense_wgrad_groups(int, int64_t, int, int) { return true; }
 int64_t dense_wgrad_group_elems(int64_t, const int (*)[2], int n) { return n > 1 ? 1000 : -1; }
 hipError_t dense_wgrad_group(int, const DenseWgradJob*, int, int64_t, float*, int64_t, hipStream_t) { return hipSuccess; }
+bool norm_dense_takes(int, int64_t, int, int) { return false; }
+hipError_t norm_dense_forward(int, const void*, const float*, const float*, void*, float*, float, const void*, const float*, void*, int, int, int, int, int, const void*, void*, hipStream_t) { return hipSuccess; }
 hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y, const ConvShape& c, int relu, float* ws, hipStream_t s) {
     std::lock_guard<std::mutex> lock(kernel_stubs.m);
     kernel_stubs.conv_samples.push_back(c.B);
