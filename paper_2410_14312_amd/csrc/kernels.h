@@ -111,12 +111,17 @@ hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const
                       const Partials& ws, hipStream_t s);
 size_t conv_wgrad_workspace_elems(int dtype, const ConvShape& c);   // fp32, for its partial results
 
-// 2-D max pooling, channels-last, no padding.  Backward recomputes the winner (first maximum in
-// row-major window order) from the stored input; relu_mask: also zero where the input is <= 0.
-hipError_t maxpool_forward(int dtype, const void* x, void* y, int B, int H, int W, int C, int k,
-                           int stride, int pad, hipStream_t s);
-hipError_t maxpool_backward(int dtype, const void* x, const void* dy, void* dx, int B, int H, int W,
-                            int C, int k, int stride, int pad, int relu_mask, hipStream_t s);
+// 2-D max pooling, channels-last.  won (a byte per result, as the forward pass leaves it; null: the windows are larger than maxpool_keeps_winners takes, and the
+// backward pass finds the winners again in x): the first maximum of every window in row-major order; relu_mask: also zero where the input is <= 0.
+bool maxpool_keeps_winners(int k);
+hipError_t maxpool_forward(int dtype, const void* x, void* y, uint8_t* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s);
+hipError_t maxpool_backward(int dtype, const void* x, const void* dy, const uint8_t* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad,
+                            int relu_mask, hipStream_t s);
+// The same behind an affine layer (affine_backward) that only the pooling reads, in one pass: z is that layer's input, dz its gradient (rows positions);
+// dy, z, gain and dz on 16 bytes.
+bool maxpool_affine_takes(int dtype, int64_t rows, int C, int k, int stride);
+hipError_t maxpool_affine_backward(int dtype, const void* dy, const uint8_t* won, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& ws,
+                                   int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s);
 
 // Per-channel affine layer on channels-last rows: y[r, c] = gain[c] x[r, c] + shift[c], then ReLU if asked.
 hipError_t affine_forward(int dtype, const void* x, const float* gain, const float* shift, void* y, int64_t rows, int C,

@@ -1,4 +1,4 @@
-// Bandwidth-bound kernels of the stage step: softmax cross-entropy, momentum update, max pooling,
+// Bandwidth-bound kernels of the stage step: softmax cross-entropy, momentum update,
 // ReLU gradient mask, casts and small reductions.
 #include "gemm.hip.h"
 #include "kernels.h"
@@ -554,402 +554,6 @@ hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t s) {
     if (blocks > 8192) blocks = 8192;
     hipLaunchKernelGGL(copy_bytes_kernel, dim3(blocks), dim3(256), 0, s, (const unsigned char*)src, (unsigned char*)dst, n16,
                        (int64_t)bytes);
-    return hipGetLastError();
-}
-
-// --------------------------------------------------------------------------------- max pooling
-// One thread per output element (channels fastest, so a wave reads/writes consecutive channels).
-template <typename T>
-__global__ void maxpool_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, int B, int H, int W, int C,
-                                   int Ho, int Wo, int k, int stride, int pad) {
-    int64_t total = (int64_t)B * Ho * Wo * C;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    int c = (int)(i % C);
-    int64_t t = i / C;
-    int wo = (int)(t % Wo); t /= Wo;
-    int ho = (int)(t % Ho);
-    int n = (int)(t / Ho);
-    float best = -INFINITY;
-    for (int r = 0; r < k; ++r)
-        for (int s = 0; s < k; ++s) {
-            const int hh = ho * stride - pad + r, ww = wo * stride - pad + s;
-            if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;   // padding never wins
-            float v = to_f32(x[(((int64_t)n * H + hh) * W + ww) * C + c]);
-            if (v > best) best = v;
-        }
-    y[i] = from_f32<T>(best);
-}
-
-// The same with 8 channels (16 bytes) per thread and access, bf16, C % 8 == 0.
-__global__ __launch_bounds__(256) void maxpool_fwd_bf16x8_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, int B, int H,
-                                                                 int W, int C, int Ho, int Wo, int k, int stride, int pad) {
-    const int C8 = C >> 3;
-    const int64_t total = (int64_t)B * Ho * Wo * C8;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int c8 = (int)(i % C8);
-    int64_t t = i / C8;
-    const int wo = (int)(t % Wo); t /= Wo;
-    const int ho = (int)(t % Ho);
-    const int n = (int)(t / Ho);
-    float best[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) best[e] = -INFINITY;
-    for (int r = 0; r < k; ++r)
-        for (int q = 0; q < k; ++q) {
-            const int hh = ho * stride - pad + r, ww = wo * stride - pad + q;
-            if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;   // padding never wins
-            Pack8 o;
-            o.u = *reinterpret_cast<const uint4*>(x + ((((int64_t)n * H + hh) * W + ww) * C8 + c8) * 8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) best[e] = fmaxf(best[e], (float)o.h[e]);
-        }
-    Pack8 out;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) out.h[e] = (bf16_t)best[e];
-    *reinterpret_cast<uint4*>(y + i * 8) = out.u;
-}
-
-// Gather form, one thread per INPUT element: sum dy over the windows whose winner (first maximum in
-// row-major window order) it is.  Handles overlapping windows and inputs no window covers.
-template <typename T>
-__global__ void maxpool_bwd_kernel(const T* __restrict__ x, const T* __restrict__ dy, T* __restrict__ dx,
-                                   int B, int H, int W, int C, int Ho, int Wo, int k, int stride, int pad,
-                                   int relu_mask) {
-    int64_t total = (int64_t)B * H * W * C;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    int c = (int)(i % C);
-    int64_t t = i / C;
-    int w = (int)(t % W); t /= W;
-    int h = (int)(t % H);
-    int n = (int)(t / H);
-    float xv = to_f32(x[i]);
-    float acc = 0.0f;
-    if (!(relu_mask && !(xv > 0.0f))) {
-        // windows that contain (h, w): ho * stride - pad <= h <= ho * stride - pad + k - 1
-        const int hp = h + pad, wp = w + pad;
-        int ho_lo = hp - k + 1 > 0 ? (hp - k + 1 + stride - 1) / stride : 0;
-        int wo_lo = wp - k + 1 > 0 ? (wp - k + 1 + stride - 1) / stride : 0;
-        for (int ho = ho_lo; ho < Ho && ho * stride <= hp; ++ho)
-            for (int wo = wo_lo; wo < Wo && wo * stride <= wp; ++wo) {
-                bool win = true;
-                for (int r = 0; r < k && win; ++r)
-                    for (int s = 0; s < k; ++s) {
-                        int hh = ho * stride - pad + r, ww = wo * stride - pad + s;
-                        if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;
-                        float v = to_f32(x[(((int64_t)n * H + hh) * W + ww) * C + c]);
-                        bool before = (hh < h) || (hh == h && ww < w);
-                        if (v > xv || (before && v == xv)) { win = false; break; }
-                    }
-                if (win) acc += to_f32(dy[(((int64_t)n * Ho + ho) * Wo + wo) * C + c]);
-            }
-    }
-    dx[i] = from_f32<T>(acc);
-}
-
-// The same gather with 8 channels (16 bytes) per thread and access, bf16, C % 8 == 0: any window, stride, padding.
-__global__ __launch_bounds__(256) void maxpool_bwd_bf16x8_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
-                                                                 bf16_t* __restrict__ dx, int B, int H, int W, int C, int Ho,
-                                                                 int Wo, int k, int stride, int pad, int relu_mask) {
-    const int C8 = C >> 3;
-    const int64_t total = (int64_t)B * H * W * C8;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int c8 = (int)(i % C8);
-    int64_t t = i / C8;
-    const int w = (int)(t % W); t /= W;
-    const int h = (int)(t % H);
-    const int n = (int)(t / H);
-    Pack8 me, out;
-    me.u = *reinterpret_cast<const uint4*>(x + i * 8);
-    float xv[8], acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        xv[e] = (float)me.h[e];
-        acc[e] = 0.0f;
-    }
-    const int hp = h + pad, wp = w + pad;
-    const int ho_lo = hp - k + 1 > 0 ? (hp - k + 1 + stride - 1) / stride : 0;
-    const int wo_lo = wp - k + 1 > 0 ? (wp - k + 1 + stride - 1) / stride : 0;
-    for (int ho = ho_lo; ho < Ho && ho * stride <= hp; ++ho)
-        for (int wo = wo_lo; wo < Wo && wo * stride <= wp; ++wo) {
-            bool win[8] = {true, true, true, true, true, true, true, true};
-            for (int r = 0; r < k; ++r)
-                for (int s = 0; s < k; ++s) {
-                    const int hh = ho * stride - pad + r, ww = wo * stride - pad + s;
-                    if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;
-                    if (hh == h && ww == w) continue;
-                    Pack8 o;
-                    o.u = *reinterpret_cast<const uint4*>(x + ((((int64_t)n * H + hh) * W + ww) * C8 + c8) * 8);
-                    const bool before = (hh < h) || (hh == h && ww < w);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float v = (float)o.h[e];
-                        if (v > xv[e] || (before && v == xv[e])) win[e] = false;
-                    }
-                }
-            Pack8 g;
-            g.u = *reinterpret_cast<const uint4*>(dy + ((((int64_t)n * Ho + ho) * Wo + wo) * C8 + c8) * 8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (win[e]) acc[e] += (float)g.h[e];
-        }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) out.h[e] = (bf16_t)((relu_mask && !(xv[e] > 0.0f)) ? 0.0f : acc[e]);
-    *reinterpret_cast<uint4*>(dx + i * 8) = out.u;
-}
-
-// Large feature maps: a workgroup owns an 8 x 16 tile of input positions of one image and up to 64 channels.
-//   1. Every input position that shares a window with the tile (at most k-1 more rows and columns on each side) is
-//      copied into LDS, 128 bytes per position: x is read from memory once (plus the halo).
-//   2. Every window that touches the tile is scanned ONCE (per 8 channels) in row-major order for its first maximum;
-//      the winner's place in the window (r * k + q) is kept in LDS, one byte per channel.
-//   3. Every position of the tile looks up the (at most ceil(k / stride)^2) windows that contain it and adds dy where the
-//      stored place is its own.
-// Scanning a window once instead of once per element it contains is what makes the difference: the per-element gather
-// above spends 4 k^2 comparisons per element and channel and is bound by the vector ALUs on large maps.
-// K, S: window and stride where they are known at compile time (0: the arguments).  The kernel is bound by its integer and
-// comparison instructions: 3 x 3 windows of stride 2 (the stem of a residual network) have an instance of their own,
-// without divisions, its loops unrolled and with five workgroups to a compute unit instead of three (64
-// images of 112 x 112 x 64: 146 -> 76 us)
-constexpr int kPoolTH = 8, kPoolTW = 16;
-template <int K, int S>
-__global__ __launch_bounds__(256) void maxpool_bwd_tiled_bf16_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
-                                                                     bf16_t* __restrict__ dx, int H, int W, int C, int Ho,
-                                                                     int Wo, int k_arg, int stride_arg, int pad, int relu_mask,
-                                                                     int groups, int patch_bytes) {
-    const int k = K ? K : k_arg, stride = S ? S : stride_arg;
-    extern __shared__ __attribute__((aligned(16))) unsigned char pool_smem[];
-    uint4* const patch = reinterpret_cast<uint4*>(pool_smem);                 // [rows][cols][8 chunks of 8 channels]
-    uint2* const place = reinterpret_cast<uint2*>(pool_smem + patch_bytes);   // [windows][8 chunks]: 8 bytes = 8 channels
-    const int C8 = C >> 3;
-    const int n = blockIdx.z / groups, c8base = (blockIdx.z % groups) * 8;
-    const int h0 = blockIdx.y * kPoolTH, w0 = blockIdx.x * kPoolTW;
-    const int h1 = min(h0 + kPoolTH, H) - 1, w1 = min(w0 + kPoolTW, W) - 1;   // last position of the tile
-    // windows that contain a position of the tile, and the input positions they cover
-    const int ho_lo = h0 + pad - k + 1 > 0 ? (h0 + pad - k + 1 + stride - 1) / stride : 0;
-    const int wo_lo = w0 + pad - k + 1 > 0 ? (w0 + pad - k + 1 + stride - 1) / stride : 0;
-    const int ho_hi = min(Ho - 1, (h1 + pad) / stride), wo_hi = min(Wo - 1, (w1 + pad) / stride);
-    const int nwh = max(0, ho_hi - ho_lo + 1), nww = max(0, wo_hi - wo_lo + 1);
-    const int ph0 = max(0, ho_lo * stride - pad), pw0 = max(0, wo_lo * stride - pad);
-    const int ph1 = min(H - 1, ho_hi * stride - pad + k - 1), pw1 = min(W - 1, wo_hi * stride - pad + k - 1);
-    const int nph = max(0, ph1 - ph0 + 1), npw = max(0, pw1 - pw0 + 1);
-    const bf16_t* xn = x + (int64_t)n * H * W * C;
-    const int ch = threadIdx.x & 7;
-    // (positions and windows of the patch are walked 32 at a time, row by row, without dividing by the patch's width)
-    auto walk = [&](int rows, int cols, auto&& f) {
-        int r = 0, c = threadIdx.x >> 3;
-        for (int idx = threadIdx.x; idx < rows * cols * 8; idx += 256) {
-            while (c >= cols) {
-                c -= cols;
-                ++r;
-            }
-            f(idx, r, c);
-            c += 32;
-        }
-    };
-    walk(nph, npw, [&](int idx, int pr, int pc) {
-        if (c8base + ch < C8)
-            patch[idx] = *reinterpret_cast<const uint4*>(xn + (((int64_t)(ph0 + pr) * W + pw0 + pc) * C8 + c8base + ch) * 8);
-    });
-    __syncthreads();
-    walk(nwh, nww, [&](int idx, int wr, int wc) {
-        if (c8base + ch >= C8) return;
-        const int hb = (ho_lo + wr) * stride - pad, wb = (wo_lo + wc) * stride - pad;
-        float best[8];
-        unsigned where[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            best[e] = -INFINITY;
-            where[e] = 255u;
-        }
-        constexpr int U = K ? K : 1;
-#pragma unroll U
-        for (int r = 0; r < k; ++r)
-#pragma unroll U
-            for (int q = 0; q < k; ++q) {
-                const int hh = hb + r, ww = wb + q;
-                if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;
-                Pack8 o;
-                o.u = patch[((hh - ph0) * npw + (ww - pw0)) * 8 + ch];
-                const unsigned me = (unsigned)(r * k + q);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float v = (float)o.h[e];
-                    if (v > best[e]) {   // strict: the first maximum in row-major order stays
-                        best[e] = v;
-                        where[e] = me;
-                    }
-                }
-            }
-        uint2 pk;
-        pk.x = where[0] | (where[1] << 8) | (where[2] << 16) | (where[3] << 24);
-        pk.y = where[4] | (where[5] << 8) | (where[6] << 16) | (where[7] << 24);
-        place[idx] = pk;
-    });
-    __syncthreads();
-    for (int it = threadIdx.x; it < kPoolTH * kPoolTW * 8; it += 256) {
-        const int pos = it >> 3;
-        const int h = h0 + pos / kPoolTW, w = w0 + pos % kPoolTW, c8 = c8base + ch;
-        if (h >= H || w >= W || c8 >= C8) continue;
-        const int64_t i = (((int64_t)n * H + h) * W + w) * C8 + c8;
-        float acc[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-        const int hp = h + pad, wp = w + pad;
-        const int a_lo = hp - k + 1 > 0 ? (hp - k + 1 + stride - 1) / stride : 0;
-        const int b_lo = wp - k + 1 > 0 ? (wp - k + 1 + stride - 1) / stride : 0;
-        auto add = [&](unsigned me, uint2 pk, const Pack8& g) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const unsigned wv = ((e < 4 ? pk.x : pk.y) >> (8 * (e & 3))) & 255u;
-                acc[e] += wv == me ? (float)g.h[e] : 0.0f;
-            }
-        };
-        if constexpr (K > 0) {
-            // (every window's gradient is requested before the first is looked at; what is no window matches nothing)
-            constexpr int NA = (K + S - 1) / S;
-            uint2 pk[NA * NA];
-            Pack8 g[NA * NA];
-            unsigned me[NA * NA];
-#pragma unroll
-            for (int a = 0; a < NA * NA; ++a) {
-                const int ho = a_lo + a / NA, wo = b_lo + a % NA;
-                const bool ok = ho <= ho_hi && ho * S <= hp && wo <= wo_hi && wo * S <= wp;
-                me[a] = ok ? (unsigned)((hp - ho * S) * K + (wp - wo * S)) : 256u;
-                const int hs = ok ? ho : 0, ws = ok ? wo : 0;
-                pk[a] = place[ok ? ((ho - ho_lo) * nww + (wo - wo_lo)) * 8 + ch : ch];
-                g[a].u = *reinterpret_cast<const uint4*>(dy + ((((int64_t)n * Ho + hs) * Wo + ws) * C8 + c8) * 8);
-            }
-#pragma unroll
-            for (int a = 0; a < NA * NA; ++a) add(me[a], pk[a], g[a]);
-        } else {
-            for (int ho = a_lo; ho < Ho && ho * stride <= hp; ++ho)
-                for (int wo = b_lo; wo < Wo && wo * stride <= wp; ++wo) {
-                    Pack8 g;
-                    g.u = *reinterpret_cast<const uint4*>(dy + ((((int64_t)n * Ho + ho) * Wo + wo) * C8 + c8) * 8);
-                    add((unsigned)((hp - ho * stride) * k + (wp - wo * stride)), place[((ho - ho_lo) * nww + (wo - wo_lo)) * 8 + ch], g);
-                }
-        }
-        Pack8 out;
-        if (relu_mask) {
-            Pack8 mine;   // (a position outside the patch lies in no window: its gradient is zero with or without the mask)
-            const bool here = h >= ph0 && h <= ph1 && w >= pw0 && w <= pw1;
-            mine.u = patch[here ? ((h - ph0) * npw + (w - pw0)) * 8 + ch : 0];
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (!((float)mine.h[e] > 0.0f)) acc[e] = 0.0f;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out.h[e] = (bf16_t)acc[e];
-        *reinterpret_cast<uint4*>(dx + i * 8) = out.u;
-    }
-}
-
-// 2x2 windows with stride 2 on even H, W and C % 8 == 0 (bf16): one thread per window and 8 channels,
-// 16-byte loads of the 4 inputs and of dy, 16-byte stores of the 4 gradients.
-__global__ __launch_bounds__(256) void maxpool2x2_bwd_bf16_kernel(const bf16_t* __restrict__ x,
-                                                                  const bf16_t* __restrict__ dy,
-                                                                  bf16_t* __restrict__ dx, int B, int H, int W,
-                                                                  int C, int relu_mask) {
-    const int Ho = H >> 1, Wo = W >> 1, C8 = C >> 3;
-    int64_t total = (int64_t)B * Ho * Wo * C8;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    int c8 = (int)(i % C8);
-    int64_t t = i / C8;
-    int wo = (int)(t % Wo); t /= Wo;
-    int ho = (int)(t % Ho);
-    int n = (int)(t / Ho);
-    Pack8 in[4], out[4], g;
-    g.u = *reinterpret_cast<const uint4*>(dy + i * 8);
-    int64_t base = (((int64_t)n * H + 2 * ho) * W + 2 * wo) * C + c8 * 8;
-    const int64_t off[4] = {0, C, (int64_t)W * C, (int64_t)W * C + C};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) in[q].u = *reinterpret_cast<const uint4*>(x + base + off[q]);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = (float)in[q].h[e];
-        int best = 0;
-#pragma unroll
-        for (int q = 1; q < 4; ++q)
-            if (v[q] > v[best]) best = q;
-        const bool pass = !(relu_mask && !(v[best] > 0.0f));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q].h[e] = (q == best && pass) ? g.h[e] : (bf16_t)0.0f;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) *reinterpret_cast<uint4*>(dx + base + off[q]) = out[q].u;
-}
-
-hipError_t maxpool_forward(int dtype, const void* x, void* y, int B, int H, int W, int C, int k, int stride, int pad,
-                           hipStream_t s) {
-    int Ho = (H + 2 * pad - k) / stride + 1, Wo = (W + 2 * pad - k) / stride + 1;
-    int64_t total = (int64_t)B * Ho * Wo * C;
-    if (total <= 0) return hipSuccess;
-    if (dtype == kBF16 && C % 8 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15) == 0) {
-        hipLaunchKernelGGL(maxpool_fwd_bf16x8_kernel, dim3(cdiv64(total / 8, 256)), dim3(256), 0, s, (const bf16_t*)x, (bf16_t*)y,
-                           B, H, W, C, Ho, Wo, k, stride, pad);
-        return hipGetLastError();
-    }
-    dim3 grid(cdiv64(total, 256));
-    if (dtype == kBF16)
-        hipLaunchKernelGGL(maxpool_fwd_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)x, (bf16_t*)y, B, H,
-                           W, C, Ho, Wo, k, stride, pad);
-    else
-        hipLaunchKernelGGL(maxpool_fwd_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (float*)y, B, H, W,
-                           C, Ho, Wo, k, stride, pad);
-    return hipGetLastError();
-}
-
-hipError_t maxpool_backward(int dtype, const void* x, const void* dy, void* dx, int B, int H, int W, int C,
-                            int k, int stride, int pad, int relu_mask, hipStream_t s) {
-    int Ho = (H + 2 * pad - k) / stride + 1, Wo = (W + 2 * pad - k) / stride + 1;
-    int64_t total = (int64_t)B * H * W * C;
-    if (total <= 0) return hipSuccess;
-    if (dtype == kBF16 && k == 2 && stride == 2 && pad == 0 && H % 2 == 0 && W % 2 == 0 && C % 8 == 0 &&
-        (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(dy) & 15) == 0 &&
-        (reinterpret_cast<uintptr_t>(dx) & 15) == 0) {
-        int64_t windows = (int64_t)B * Ho * Wo * (C / 8);
-        hipLaunchKernelGGL(maxpool2x2_bwd_bf16_kernel, dim3(cdiv64(windows, 256)), dim3(256), 0, s, (const bf16_t*)x,
-                           (const bf16_t*)dy, (bf16_t*)dx, B, H, W, C, relu_mask);
-        return hipGetLastError();
-    }
-    if (dtype == kBF16 && C % 8 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(dy) & 15) == 0 &&
-        (reinterpret_cast<uintptr_t>(dx) & 15) == 0) {
-        // large maps: the LDS-tiled form (its patch of (8 + 2(k-1)) x (16 + 2(k-1)) positions x 128 bytes and the
-        // winners of at most (8 + k-1) x (16 + k-1) windows x 64 bytes must fit; a window has at most 255 places)
-        const int groups = (C / 8 + 7) / 8;
-        const int64_t patch_bytes = (int64_t)(kPoolTH + 2 * (k - 1)) * (kPoolTW + 2 * (k - 1)) * 128;
-        const int64_t lds = patch_bytes + (int64_t)(kPoolTH + k - 1) * (kPoolTW + k - 1) * 64;
-        const int64_t blocks_z = (int64_t)B * groups;
-        if (H >= 2 * kPoolTH && W >= 2 * kPoolTW && lds <= 64 * 1024 && blocks_z <= 65535 && k * k <= 255) {
-            dim3 grid((W + kPoolTW - 1) / kPoolTW, (H + kPoolTH - 1) / kPoolTH, (unsigned)blocks_z);
-            if (k == 3 && stride == 2) {   // at most 5 x 9 windows touch a tile, over 11 x 19 positions
-                constexpr int kWinH = (kPoolTH + 1) / 2 + 1, kWinW = (kPoolTW + 1) / 2 + 1, kPatch = (2 * kWinH + 1) * (2 * kWinW + 1) * 128;
-                hipLaunchKernelGGL((maxpool_bwd_tiled_bf16_kernel<3, 2>), grid, dim3(256), kPatch + kWinH * kWinW * 64, s, (const bf16_t*)x,
-                                   (const bf16_t*)dy, (bf16_t*)dx, H, W, C, Ho, Wo, k, stride, pad, relu_mask, groups, kPatch);
-                return hipGetLastError();
-            }
-            hipLaunchKernelGGL((maxpool_bwd_tiled_bf16_kernel<0, 0>), grid, dim3(256), (unsigned)lds, s, (const bf16_t*)x, (const bf16_t*)dy,
-                               (bf16_t*)dx, H, W, C, Ho, Wo, k, stride, pad, relu_mask, groups, (int)patch_bytes);
-            return hipGetLastError();
-        }
-        hipLaunchKernelGGL(maxpool_bwd_bf16x8_kernel, dim3(cdiv64(total / 8, 256)), dim3(256), 0, s, (const bf16_t*)x,
-                           (const bf16_t*)dy, (bf16_t*)dx, B, H, W, C, Ho, Wo, k, stride, pad, relu_mask);
-        return hipGetLastError();
-    }
-    dim3 grid(cdiv64(total, 256));
-    if (dtype == kBF16)
-        hipLaunchKernelGGL(maxpool_bwd_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)x,
-                           (const bf16_t*)dy, (bf16_t*)dx, B, H, W, C, Ho, Wo, k, stride, pad, relu_mask);
-    else
-        hipLaunchKernelGGL(maxpool_bwd_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (const float*)dy,
-                           (float*)dx, B, H, W, C, Ho, Wo, k, stride, pad, relu_mask);
     return hipGetLastError();
 }
 

@@ -48,6 +48,11 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Partial results of one layer's parameter gradient that may wait for the end of the backward pass.
 static constexpr size_t kLatePartBytes = size_t(16) << 20;
 
+// A pooling layer's winners from row row0 of the stash on (null: it keeps none).
+static uint8_t* winners(const tmps_stage* st, const LayerRT& L, int64_t row0) {
+    return maxpool_keeps_winners(L.d.dims[3]) ? reinterpret_cast<uint8_t*>(st->stash + L.aux_off) + (size_t)row0 * L.out_elems : nullptr;
+}
+
 static ConvShape conv_shape(const tmps_layer_desc& d, int B) {
     ConvShape c;
     c.B = B; c.H = d.dims[0]; c.W = d.dims[1]; c.Cin = d.dims[2]; c.Cout = d.dims[3];
@@ -268,6 +273,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
         if (L.d.kind == TMPS_SOFTMAX_CE) aux = (size_t)rows_all * L.rps * 4;                  // per-row losses
         if (L.d.kind == TMPS_LAYERNORM) aux = (size_t)rows_all * L.rps * 8;                   // (mean, 1/std) per row
         if (L.d.kind == TMPS_ATTENTION) aux = (size_t)rows_all * L.d.dims[2] * L.d.dims[0] * 4;  // log-sum-exp per head and query
+        if (L.d.kind == TMPS_MAXPOOL && maxpool_keeps_winners(L.d.dims[3])) aux = (size_t)rows_all * L.out_elems;   // every window's winner
         if (aux) {
             L.aux_off = soff;
             soff = align_up(soff + aux, 256);
@@ -616,7 +622,7 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
                 break;
             }
             case TMPS_MAXPOOL:
-                TMPS_RUN(kcPoolFwd, s, maxpool_forward(dt, in, out, mb, d[0], d[1], d[2], d[3], d[4], d[5], s));
+                TMPS_GEMM(maxpool_forward(dt, in, out, winners(st, L, row0), mb, d[0], d[1], d[2], d[3], d[4], d[5], s));
                 break;
             case TMPS_AFFINE:
                 TMPS_GEMM(affine_forward(dt, in, st->master + L.w_off, st->master + L.b_off, out, (int64_t)mb * d[0] * d[1], d[2],
@@ -930,7 +936,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         const void* mask = mask_of(t_in, mask_mode);
         float* gw = st->grad + L.w_off;
         Target T;
-        int rc;
+        int rc, with_below = 0;   // layers below whose backward pass this one's includes
         switch (L.d.kind) {
             case TMPS_LINEAR: {
                 const int rows = M * L.rps;
@@ -963,14 +969,32 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                 } else if ((rc = conv_input_gradient(li, g)) != TMPS_OK) return rc;
                 break;
             }
-            case TMPS_MAXPOOL:
+            case TMPS_MAXPOOL: {
+                const uint8_t* won = winners(st, L, row0);
+                const LayerRT* A = t_in >= 0 && st->layers[t_in].d.kind == TMPS_AFFINE ? &st->layers[t_in] : nullptr;
+                const int64_t rows = (int64_t)M * d[0] * d[1];
+                if (A && won && st->readers[t_in + 1] == 1 && !in_order && maxpool_affine_takes(dt, rows, d[2], d[3], d[4])) {
+                    if ((rc = target(A->in_t, T)) != TMPS_OK) return rc;
+                    if (T.add) return fail(TMPS_EUNSUPPORTED, "an affine layer on a shared input");
+                    const void* const z = A->in_t < 0 ? (const void*)x0 : (const void*)st->out_ptr(st->layers[A->in_t], row0);
+                    if (T.wanted && ((reinterpret_cast<uintptr_t>(g.ptr) | reinterpret_cast<uintptr_t>(z) | reinterpret_cast<uintptr_t>(T.dst)) & 15) == 0) {
+                        TMPS_GEMM(maxpool_affine_backward(dt, g.ptr, won, z, st->master + A->w_off, T.dst, st->grad + A->w_off, partials(*A), M, d[0], d[1], d[2], d[3],
+                                                          d[4], d[5], mask ? 1 : 0, s));
+                        commit(A->in_t, T);
+                        --remaining[t_in + 1];
+                        with_below = 1;
+                        break;
+                    }
+                    release(T.buf);
+                }
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 if (T.wanted) {
                     if (T.add || mask_mode == 2) return fail(TMPS_EUNSUPPORTED, "max pooling on a shared or GELU input");
-                    TMPS_RUN(kcPoolBwd, s, maxpool_backward(dt, in, g.ptr, T.dst, M, d[0], d[1], d[2], d[3], d[4], d[5], mask ? 1 : 0, s));
+                    TMPS_GEMM(maxpool_backward(dt, in, g.ptr, won, T.dst, M, d[0], d[1], d[2], d[3], d[4], d[5], mask ? 1 : 0, s));
                     commit(t_in, T);
                 }
                 break;
+            }
             case TMPS_AVGPOOL:
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 if (T.wanted) {
@@ -1033,6 +1057,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
         }
         if (L.d.kind == TMPS_RESADD && L.in_b >= 0 && remaining[L.in_b + 1] == 0 && st->layers[L.in_b].act != 0)
             return fail(TMPS_EUNSUPPORTED, "a residual connection must start at a result that another, earlier layer reads too");
+        li -= with_below;
     }
     int rc = flush_group();
     if (rc != TMPS_OK) return rc;

@@ -29,8 +29,11 @@ hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bi
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain, const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) { return hipSuccess; }
-hipError_t maxpool_forward(int dtype, const void* x, void* y, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) { return hipSuccess; }
-hipError_t maxpool_backward(int dtype, const void* x, const void* dy, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) { return hipSuccess; }
+bool maxpool_keeps_winners(int k) { return k <= 11; }
+bool maxpool_affine_takes(int, int64_t, int, int, int) { return false; }
+hipError_t maxpool_affine_backward(int, const void*, const uint8_t*, const void*, const float*, void*, float*, const Partials&, int, int, int, int, int, int, int, int, hipStream_t) { return hipSuccess; }
+hipError_t maxpool_forward(int dtype, const void* x, void* y, uint8_t* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) { return hipSuccess; }
+hipError_t maxpool_backward(int dtype, const void* x, const void* dy, const uint8_t* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) { return hipSuccess; }
 hipError_t affine_forward(int dtype, const void* x, const float* gain, const float* shift, void* y, int64_t rows, int C, int relu, hipStream_t s) { return hipSuccess; }
 hipError_t affine_backward(int dtype, const void* dy, const void* x, const float* gain, void* dx, float* dgain_dshift, const Partials& ws, int64_t rows, int C, hipStream_t s) { return hipSuccess; }
 hipError_t resadd_forward(int dtype, const void* a, const void* b, void* y, int64_t n, int relu, hipStream_t s) { return hipSuccess; }
