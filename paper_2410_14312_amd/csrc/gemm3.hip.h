@@ -1,5 +1,5 @@
 // Persistent MFMA GEMM for gfx950 with asynchronous global -> LDS copies (bf16 in, fp32 accumulate), used
-// by the dense contractions whose shapes allow it (K a multiple of 64, row counts of row-contiguous
+// by the dense contractions whose shapes allow it (K a multiple of 64 but in groups of weight gradients, row counts of row-contiguous
 // operands a multiple of 8, 16-byte aligned operands).
 //
 //   C[m, n] = sum_k A(m, k) * B(n, k)
@@ -87,6 +87,9 @@ template <class T> __device__ __forceinline__ void settle(const T& t) {
 // LDS bytes of one launch
 template <int BM, int BN, int BK, int NS> constexpr int gemm3_lds_bytes() { return NS * (BM + BN) * BK * 2; }
 
+// what a copy reads in place of elements that are not there
+__device__ __attribute__((aligned(16))) static const uint32_t g3_zeros[4] = {0, 0, 0, 0};
+
 // Per-wave copy state of one operand tile of ROWS rows x BK k (BK = 32 or 64): GROUPS 1-KB groups per k-tile.
 template <int ROWS, int BK, int NW, bool KC> struct G3Loader {
     static constexpr int GROUPS = ROWS * BK * 2 / 1024 / NW;
@@ -127,6 +130,14 @@ template <int ROWS, int BK, int NW, bool KC> struct G3Loader {
     __device__ __forceinline__ void issue_group(lds_t tile, int64_t ld, int wave, int g) {
         copy16_to_lds(ptr[g], tile + (wave + g * NW) * 1024);
         ptr[g] += KC ? BK : BK * ld;
+    }
+    // row-contiguous, of a k-tile with `left` k (BK or fewer): zeros take the place of those behind its end, which are not read
+    __device__ __forceinline__ void issue_group(lds_t tile, int64_t ld, int wave, int g, int lane, int left) {
+        static_assert(!KC, "k-rows are whole lanes of a row-contiguous tile only");
+        constexpr int CPR = ROWS / 8;
+        const int k = (wave + g * NW) * (64 / CPR) + lane / CPR;
+        copy16_to_lds(k < left ? (const void*)ptr[g] : (const void*)g3_zeros, tile + (wave + g * NW) * 1024);
+        ptr[g] += BK * ld;
     }
 };
 
@@ -185,6 +196,7 @@ struct G3Plan {
 // One work unit as the kernel walks it: the first row and column of its tile, its k range and what its epilogue needs to know.
 struct G3Unit {
     int m0, n0, k0, nk;   // nk: k-tiles of BK
+    int last;             // k of the last one (kRagged: BK or fewer)
     int z, job, part_tile;   // k-slice; which contraction of a group and which of its cut tiles
     bool first_col;       // a tile of the first column of tiles
 };
@@ -192,7 +204,7 @@ struct G3Unit {
 // The units of one contraction.
 template <int BM, int BN, int BK, bool AKC, bool BKC, class Epi_> struct G3One {
     typedef Epi_ Epi;
-    static constexpr bool kTotals = false;
+    static constexpr bool kTotals = false, kRagged = false;
     G3Operand<AKC> A;
     G3Operand<BKC> B;
     Epi_ e;
@@ -212,7 +224,7 @@ template <int BM, int BN, int BK, bool AKC, bool BKC, class Epi_> struct G3One {
         } else if (plan.col_major) plan.d_tn.divmod(rem, n_, m_);
         else plan.d_tn.divmod(rem, m_, n_);
         const int z = (int)zz, k0 = z * plan.k_per_slice, k1 = min(k_total, k0 + plan.k_per_slice);
-        return G3Unit{(int)m_ * BM, (int)n_ * BN, k0, (k1 - k0) / BK, z, 0, 0, n_ == 0};
+        return G3Unit{(int)m_ * BM, (int)n_ * BN, k0, (k1 - k0) / BK, BK, z, 0, 0, n_ == 0};
     }
     __device__ __forceinline__ const G3Operand<AKC>& a(const G3Unit&) const { return A; }
     __device__ __forceinline__ const G3Operand<BKC>& b(const G3Unit&) const { return B; }
@@ -258,7 +270,7 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     LoaderA la;
     LoaderB lb;
     const int units = work.units();
-    int iu = vb, ikt = 0, ink = 0, istage = 0;
+    int iu = vb, ikt = 0, ink = 0, istage = 0, ilast = BK;
     int64_t ild_a = 0, ild_b = 0;   // leading dimensions of the cursor's operands
     auto seek_unit = [&]() {
         if (iu < units) {
@@ -266,6 +278,7 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
             const auto& A = work.a(t);
             const auto& B = work.b(t);
             ink = t.nk;
+            ilast = t.last;
             ild_a = A.ld;
             ild_b = B.ld;
             la.seek(A, t.m0, t.k0, wave, lane);
@@ -277,8 +290,14 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     // copy group g (of G) of the cursor's k-tile into stage `istage`
     auto issue_group = [&](int g) {
         const lds_t st = smem + istage * STAGE;
-        if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g);
-        else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS);
+        if constexpr (Work::kRagged) {
+            const int left = ikt + 1 == ink ? ilast : BK;
+            if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g, lane, left);
+            else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS, lane, left);
+        } else {
+            if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g);
+            else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS);
+        }
     };
     // all G groups of the cursor's k-tile are issued: step the cursor
     auto advance = [&]() {
@@ -626,7 +645,7 @@ struct G3Job {
 };
 struct G3Group {
     typedef EpiWgrad Epi;
-    static constexpr bool kTotals = true;
+    static constexpr bool kTotals = true, kRagged = false;
     static constexpr int kRows = 256, kCols = 128, kPart = kRows * kCols + kRows;   // a tile; floats of a partial one: results, then row sums
     G3Job job[kG3GroupMax];
     int jobs, k_total, tiles, whole;   // tiles of all jobs; the first `whole` of them are not sliced
@@ -660,7 +679,8 @@ struct G3Group {
             g.k0 = g.z * k_per_slice;
             k1 = min(k_total, g.k0 + k_per_slice);
         }
-        g.nk = (k1 - g.k0) >> 6;
+        g.nk = (k1 - g.k0 + 63) >> 6;
+        g.last = k1 - g.k0 - (g.nk - 1) * 64;
         g.job = place(t, g.m0, g.n0);
         g.first_col = g.n0 == 0;
         g.part_tile = t - whole;
@@ -677,6 +697,13 @@ struct G3Group {
         const int64_t first = (int64_t)g.m0 * kCols + g.n0;
         return EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kCols, first + kRows * kCols - g.m0, 0};
     }
+};
+// Over rows that are no multiple of 64: the last k-tile of the last slice is short.  An instance of its own, so that the comparison and the two selects of
+// every copy are paid only where rows need them.  In launches of their own such gradients ran on 64 x 64 tiles: eight of a stage with two blocks of 512
+// features over 3996 rows 156 us, the stage 1127 us and 1087 with one launch; four blocks of 768 over two stages with 1266 rows, two mini-batches, 2570 and
+// 2399; four blocks of 640 in 1F1B order, 1564 rows a pass, 9 % of a run; one mini-batch of three blocks of 768 over 524 rows 1.5 %.
+struct G3GroupRagged : G3Group {
+    static constexpr bool kRagged = true;
 };
 
 }  // namespace tmps

@@ -399,6 +399,9 @@ constexpr int kG3GroupStages = 3;
 __global__ __launch_bounds__(256) void gemm3_kernel(G3Group work) {
     gemm3_walk<G3Group::kRows, G3Group::kCols, 64, 2, 2, kG3GroupStages, false, false, true>(work);
 }
+__global__ __launch_bounds__(256) void gemm3_kernel(G3GroupRagged work) {
+    gemm3_walk<G3Group::kRows, G3Group::kCols, 64, 2, 2, kG3GroupStages, false, false, true>(work);
+}
 
 // Adds up the slices of the cut tiles, in slice order: workgroup (r, y) takes 32 rows of cut tile r, a thread 4 columns of 4 rows.
 __global__ __launch_bounds__(256) void g3_group_sum_kernel(G3Group work) {
@@ -449,7 +452,7 @@ static int64_t g3_group_tiles(int64_t M, int64_t N) { return (int64_t)cdiv(M, G3
 // `whole` tiles (whole rounds of the device) unsliced, the others in the number of slices that is quickest.
 static G3GroupPlan g3_group_plan(int64_t tiles, int64_t K, int64_t ws_elems) {
     const int cus = compute_units();
-    const int64_t kt = K / 64, full = tiles / cus;
+    const int64_t kt = cdiv(K, 64), full = tiles / cus;
     const int chain = g3_group_chain(kt);
     const double ktile_us = kGroupKtileUs + kGroupTotalUs / chain;
     G3GroupPlan best{0, 0, 0, chain, 0.0};
@@ -476,7 +479,7 @@ static double wgrad_alone_us(int64_t M, int64_t N, int64_t K) {
 
 // (not where more than a quarter of the 256-wide tiles would be padding)
 bool dense_wgrad_groups(int dtype, int64_t rows, int Din, int Dout) {
-    return dtype == kBF16 && rows % 64 == 0 && rows >= 512 && rows < (int64_t(1) << 31) && Din % 8 == 0 && Dout % 8 == 0 &&
+    return dtype == kBF16 && rows >= 512 && rows < (int64_t(1) << 31) && Din % 8 == 0 && Dout % 8 == 0 &&
            (int64_t)cdiv(Din, 256) * 256 * 3 <= (int64_t)Din * 4 && (int64_t)cdiv(Dout, 256) * 256 * 3 <= (int64_t)Dout * 4;
 }
 
@@ -499,7 +502,7 @@ int64_t dense_wgrad_group_elems(int64_t rows, const int (*dims)[2], int n) {
 hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_t rows, float* ws, int64_t ws_elems, hipStream_t s) {
     if (n < 1) return hipSuccess;
     if (dtype != kBF16 || n > kG3GroupMax) return hipErrorInvalidValue;
-    G3Group g;
+    G3GroupRagged g;
     int tiles = 0;
     for (int i = 0; i < n; ++i) {
         const DenseWgradJob& j = jobs[i];
@@ -516,12 +519,16 @@ hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_
     g.d_cut = FastDiv(cut > 0 ? cut : 1);
     constexpr int lds = gemm3_lds_bytes<G3Group::kRows, G3Group::kCols, 64, kG3GroupStages>();
     void (*const kern)(G3Group) = gemm3_kernel;
+    void (*const ragged)(G3GroupRagged) = gemm3_kernel;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (attr != hipSuccess) return attr;
+    static hipError_t attr_r = hipFuncSetAttribute(reinterpret_cast<const void*>(ragged), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess || attr_r != hipSuccess) return attr != hipSuccess ? attr : attr_r;
     const int units = g.whole + (tiles - g.whole) * g.slices, slots = compute_units();
-    hipError_t e = launch_timed(kcDenseWgrad, kern, dim3(units < slots ? units : slots), dim3(256), lds, s, g);
+    const dim3 grid(units < slots ? units : slots);
+    hipError_t e = rows % 64 == 0 ? launch_timed(kcDenseWgrad, kern, grid, dim3(256), lds, s, (const G3Group&)g)
+                                  : launch_timed(kcDenseWgrad, ragged, grid, dim3(256), lds, s, g);
     if (e != hipSuccess || p.slices == 1) return e;
-    return launch_timed(kcSliceSum, g3_group_sum_kernel, dim3(cut, G3Group::kRows / 32), dim3(256), 0, s, g);
+    return launch_timed(kcSliceSum, g3_group_sum_kernel, dim3(cut, G3Group::kRows / 32), dim3(256), 0, s, (const G3Group&)g);
 }
 
 // ---------------------------------------------------------------------------------------- dense
