@@ -696,10 +696,24 @@ int backward_kind(int64_t B, int64_t Din, int64_t Dout, int esize) {
     return small <= tiled ? kOneSmall : kOneTiled;
 }
 
+// fp32: whether the two launches of both gradients run as one on two kernels' tiles (gemm_mixed_backward_kernel): the small kernel's 32 x 32 and the tiled
+// kernel's 64 x 64, unsliced, so the results are the same bits.  Forward and backward pass and update of one layer, two launches and one (us): 235 x 1000 -> 1000
+// 39.1 and 32.2, 256 x 1024 -> 1024 39.7 and 32.6.  Where the small kernel takes both this is sometimes quicker too (235 x 784 -> 1000 33.7 and 30.5, but 512 x 768 -> 768
+// 44.1 and 46.7), with longer chains in the sums of the weight gradient: 2.0e-7 (2-norm) from those in 64 bits instead of 1.0e-7.
+bool mixed_backward_takes(int64_t B, int64_t Din, int64_t Dout) {
+    if (Din % 4 != 0 || Dout % 4 != 0 || backward_kind(B, Din, Dout, 4) != kTwo) return false;
+    const Plan2 pw = plan_for(Dout, Din, B, true, 4, kByKDense);
+    return small_is_better(B, Din, Dout, 4, plan_for(B, Din, Dout, false, 4, kByKDense)) && small_plan(B, Din, Dout, 4).tm == 2 &&
+           !small_is_better(Dout, Din, B, 4, pw) && pw.kind == kTiled && pw.bm == 64 && pw.bn == 64 && pw.slices == 1;
+}
+
 hipError_t dense_backward(int dtype, const void* dy, const void* x, const void* w, float* gw, void* dx, const void* mask, int mask_mode,
                           const void* add, int B, int Din, int Dout, float* ws, const Partials& ws_w, hipStream_t s) {
     const int kind = backward_kind(B, Din, Dout, dtype == kBF16 ? 2 : 4);
     const EpiMask<bf16_t, bf16_t> ex{(bf16_t*)dx, (const bf16_t*)mask, Din, mask_mode, (const bf16_t*)add};
+    if (dtype != kBF16 && mixed_backward_takes(B, Din, Dout) && aligned16(dy) && aligned16(x))
+        return mixed_backward_f32(kcDenseBackward, (const float*)dy, (const float*)x, (const float*)w, gw,
+                                  EpiMask<float, float>{(float*)dx, (const float*)mask, Din, mask_mode, (const float*)add}, B, Din, Dout, s);
     if (kind == kOneSmall) {
         if (dtype != kBF16)
             return small_backward_f32(kcDenseBackward, (const float*)dy, (const float*)x, (const float*)w, gw,
@@ -776,5 +790,6 @@ hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const
 
 extern "C" int tmps_dense_gradients_joint(int dtype, int64_t rows, int din, int dout) {
     using namespace tmps;
-    return rows > 0 && din > 0 && dout > 0 && !dense_wgrad_groups(dtype, rows, din, dout) && backward_kind(rows, din, dout, dtype == kBF16 ? 2 : 4) != kTwo;
+    return rows > 0 && din > 0 && dout > 0 && !dense_wgrad_groups(dtype, rows, din, dout) &&
+           (backward_kind(rows, din, dout, dtype == kBF16 ? 2 : 4) != kTwo || (dtype != kBF16 && mixed_backward_takes(rows, din, dout)));
 }
