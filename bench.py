@@ -25,7 +25,7 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 
 
-def algorithmic_work(cfg, only_stage=None, passes=None, joint=None):
+def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointwise=None):
     """Per kernel class and per mini-batch: (launches, FLOPs, algorithmic bytes) from the shapes alone
     (of every stage, or of stage `only_stage` alone).
 
@@ -34,6 +34,7 @@ def algorithmic_work(cfg, only_stage=None, passes=None, joint=None):
     kernel once and reads its weights once.
 
     joint(dtype, rows, din, dout): whether both gradients of a dense layer are one launch, which then counts as "dense_backward".
+    joint_pointwise(dtype, positions, cin, cout): whether those of a 1 x 1 convolution are one with the affine layer's behind it, which then counts as "affine".
 
     Dense GEMMs count 2*rows*Din*Dout FLOPs and their operand/result bytes once; the update counts
     22 bytes per parameter in bf16 stages (read w, buf, g fp32; write w, buf fp32 and the bf16 copy)
@@ -88,9 +89,11 @@ def algorithmic_work(cfg, only_stage=None, passes=None, joint=None):
                 P += kk * sp["cout"] + sp["cout"]
                 x_e, y_e = sp["h"] * sp["w"] * sp["cin"], ho * wo * sp["cout"]
                 add("conv_fwd", F, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + F * kk * sp["cout"] * asz)
-                add("conv_wgrad", 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * 4)
+                one = (joint_pointwise is not None and not (si == 0 and li == 0) and sp["r"] == sp["s"] == sp["stride"] == 1 and sp["pad"] == 0 and
+                       li + 1 < len(st) and st[li + 1]["kind"] == "affine" and joint_pointwise(cfg.dtype, M * ho * wo, sp["cin"], sp["cout"]))
+                add("affine" if one else "conv_wgrad", 0 if one else 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * 4)
                 if not (si == 0 and li == 0):
-                    add("conv_dgrad", 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * asz)
+                    add("affine" if one else "conv_dgrad", 0 if one else 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * asz)
             elif sp["kind"] == "affine":
                 e = sp["h"] * sp["w"] * sp["c"]
                 P += 2 * sp["c"]
@@ -122,15 +125,15 @@ KERNEL_STAMPED = ("dense_fwd", "dense_dgrad", "dense_wgrad", "dense_backward", "
                   "slice_sum", "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd")
 
 
-def class_entry(cfg, klass, ms, launches, joint=None):
+def class_entry(cfg, klass, ms, launches, joint=None, joint_pointwise=None):
     """What a kernel class takes and does per mini-batch, from its measured time (ms) and number of launches.  The work of a
-    class comes from the shapes and not from the launches: consecutive micro-batches may be forwarded in one pass.  (joint: see
+    class comes from the shapes and not from the launches: consecutive micro-batches may be forwarded in one pass.  (joint, joint_pointwise: see
     algorithmic_work.)"""
     ent = {"class": klass, "launches_per_step": launches, "avg_us": 1e3 * ms / launches, "ms_per_step": ms}
-    per = algorithmic_work(cfg, joint=joint).get(klass)
+    per = algorithmic_work(cfg, joint=joint, joint_pointwise=joint_pointwise).get(klass)
     if per and per[0]:
         if klass in ("dense_fwd", "conv_fwd"):   # launches of a layer = passes; each reads the layer's weights
-            per = algorithmic_work(cfg, passes=cfg.N * launches / per[0], joint=joint)[klass]
+            per = algorithmic_work(cfg, passes=cfg.N * launches / per[0], joint=joint, joint_pointwise=joint_pointwise)[klass]
         ent["gflop_per_launch"] = per[1] / launches / 1e9
         ent["mbytes_per_launch"] = per[2] / launches / 1e6
         ent["tflops"] = per[1] / (ms / 1e3) / 1e12
@@ -358,7 +361,7 @@ def main():
                 continue
             if k not in KERNEL_STAMPED:      # bracketed classes also contain the cost of the event pair
                 ms = max(ms - cnt * pair_us / 1e3, 0.05 * ms)
-            ent = class_entry(cfg, k, ms / args.steps, cnt / args.steps, T.dense_gradients_joint)
+            ent = class_entry(cfg, k, ms / args.steps, cnt / args.steps, T.dense_gradients_joint, T.pointwise_gradients_joint)
             out.append(ent)
         out.sort(key=lambda e: -e["ms_per_step"])
         return out, pair_us

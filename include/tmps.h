@@ -334,6 +334,9 @@ int tmps_profile_read(double* total_ms, int64_t* launches, int n_classes);
 /* 1: the input and the weight gradient of a linear layer over `rows` rows are one launch (TMPS_KC_DENSE_BACKWARD) where a
  * backward pass forms both one after the other; 0: they are launches of their own classes.  (TMPS_F32 or TMPS_BF16_F32MASTER.) */
 int tmps_dense_gradients_joint(int dtype, int64_t rows, int din, int dout);
+/* 1: the gradients of a 1 x 1 convolution of unit stride over `positions` positions and those of the affine layer that alone reads its result are
+ * one launch (TMPS_KC_AFFINE), where the gradient of the convolution's input is wanted. */
+int tmps_pointwise_gradients_joint(int dtype, int64_t positions, int cin, int cout);
 
 const char* tmps_last_error(void);
 

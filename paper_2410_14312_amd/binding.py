@@ -70,6 +70,7 @@ EXPORTS = {
     "tmps_profile_enable": (C.c_int, [C.c_int]),
     "tmps_profile_read": (C.c_int, [C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int]),
     "tmps_dense_gradients_joint": (C.c_int, [C.c_int, C.c_int64, C.c_int, C.c_int]),
+    "tmps_pointwise_gradients_joint": (C.c_int, [C.c_int, C.c_int64, C.c_int, C.c_int]),
     "tmps_last_error": (C.c_char_p, []),
 }
 
@@ -152,6 +153,11 @@ def profile_read():
 def dense_gradients_joint(dtype, rows, din, dout):
     """Whether both gradients of a linear layer are one launch, timed under "dense_backward"."""
     return bool(lib().tmps_dense_gradients_joint(TMPS_BF16_F32MASTER if dtype == "bf16" else TMPS_F32, rows, din, dout))
+
+
+def pointwise_gradients_joint(dtype, positions, cin, cout):
+    """Whether the gradients of a 1 x 1 convolution and the affine layer behind it are one launch, timed under "affine"."""
+    return bool(lib().tmps_pointwise_gradients_joint(TMPS_BF16_F32MASTER if dtype == "bf16" else TMPS_F32, positions, cin, cout))
 
 
 def layer_descs(specs):

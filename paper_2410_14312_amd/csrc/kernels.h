@@ -111,6 +111,14 @@ hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const
                       const Partials& ws, hipStream_t s);
 size_t conv_wgrad_workspace_elems(int dtype, const ConvShape& c);   // fp32, for its partial results
 
+// Backward pass of a 1 x 1 convolution of unit stride (x [P][I] -> z [P][O]) and the affine layer that alone reads its result, in one pass: dy is the affine layer's
+// incoming gradient, dx the convolution's input gradient (add: joined first, may be dx; masked: then zero where x <= 0), gw_affine and gw_conv as affine_backward and
+// conv_wgrad leave them.  affine_pointwise_takes: where that is quicker; affine_pointwise_slabs: partial results of 2 O and O I + O values that pa and pw hold.
+bool affine_pointwise_takes(int dtype, int64_t P, int O, int I);
+int affine_pointwise_slabs(int64_t P, int O, int I);
+hipError_t affine_pointwise_backward(const void* dy, const void* z, const void* x, const void* w, const float* gain, const void* add, int masked, void* dx,
+                                     float* gw_affine, float* gw_conv, const Partials& pa, const Partials& pw, int64_t P, int O, int I, hipStream_t s);
+
 // 2-D max pooling, channels-last.  won (a byte per result, as the forward pass leaves it; null: the windows are larger than maxpool_keeps_winners takes, and the
 // backward pass finds the winners again in x): the first maximum of every window in row-major order; relu_mask: also zero where the input is <= 0.
 bool maxpool_keeps_winners(int k);

@@ -173,7 +173,7 @@ struct ReduceJob {
     const float* part;
     float* out;
     int64_t count;
-    int slices, form;   // form: 0 four outputs to a thread, 1 one, 2 rows
+    int slices, form;   // form: 0 four outputs to a thread, 1 one, 2 rows, 3 rows of four outputs
 };
 struct ReduceJobs {
     int first[kReduceMax];   // first workgroup of a job; where there is none, the number of workgroups
@@ -211,6 +211,46 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceJobs all) {
             p += r.count;
         }
         *reinterpret_cast<float4*>(r.out + i) = a;
+        return;
+    }
+    if (r.form == 3) {
+        // sixteen lanes of rows, four outputs to a thread, eight rows in flight
+        __shared__ float4 sp4[16][16];
+        const int64_t i = (int64_t)blk * 64 + (tid & 15) * 4;
+        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        auto plus = [](float4& x, const float4& y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
+        if (i < r.count) {
+            const float* p = r.part + (int64_t)(tid >> 4) * r.count + i;
+            const int64_t step = 16 * r.count;
+            int z = tid >> 4;
+            for (; z + 7 * 16 < r.slices; z += 8 * 16) {
+                float4 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(p + u * step);
+#pragma unroll
+                for (int h = 4; h > 0; h >>= 1)
+#pragma unroll
+                    for (int u = 0; u < h; ++u) plus(v[u], v[u + h]);
+                plus(a, v[0]);
+                p += 8 * step;
+            }
+            for (; z < r.slices; z += 16) {
+                plus(a, *reinterpret_cast<const float4*>(p));
+                p += step;
+            }
+        }
+        sp4[tid >> 4][tid & 15] = a;
+        __syncthreads();
+        if (tid < 16 && i < r.count) {
+            float4 t[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) t[k] = sp4[k][tid];
+#pragma unroll
+            for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+                for (int k = 0; k < h; ++k) plus(t[k], t[k + h]);
+            *reinterpret_cast<float4*>(r.out + i) = t[0];
+        }
         return;
     }
     const bool rows = r.form == 2;
@@ -265,9 +305,10 @@ hipError_t reduce_all(const Reductions& list, hipStream_t s) {
             all.job[k] = ReduceJob{nullptr, nullptr, 0, 0, 1};
             if (k >= n) continue;
             const Reduction& r = list[at + k];
-            const int form = r.rows ? 2 : r.count % 4 == 0 && aligned16(r.part) && aligned16(r.out) ? 0 : 1;
+            const bool wide = r.count % 4 == 0 && aligned16(r.part) && aligned16(r.out);
+            const int form = r.rows ? 2 : !wide ? 1 : r.slices >= 32 && r.count <= (1 << 18) ? 3 : 0;
             all.job[k] = ReduceJob{r.part, r.out, r.count, r.slices, form};
-            blocks += cdiv(r.count, form == 0 ? 1024 : form == 1 ? 256 : 16);
+            blocks += cdiv(r.count, form == 0 ? 1024 : form == 1 ? 256 : form == 2 ? 16 : 64);
             if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
         }
         if (blocks == 0) continue;

@@ -1,0 +1,275 @@
+// Backward pass of a 1 x 1 convolution with a per-channel affine layer behind it, in one pass over memory (bf16, unit stride).
+//
+// On the way back the affine layer forms g = gain dY and its own sums, the convolution dW = g^T x and dx = mask(g W + add).  As launches of their own these
+// read dY, z and x, write g, read it twice more and read x again for the mask; the bottleneck blocks' maps of 64 and 256 channels are bound by exactly that.
+// Here a workgroup takes a run of positions, 64 at a time, and reads dY, z, x and add once: g and x go to LDS, dx comes from there and from W, which the waves keep
+// in registers, and dW stays in the accumulators until the workgroup's last position.  One workgroup of eight waves to a compute unit; the next positions' loads are on
+// their way during all of a step's multiplies.  What remains beside the maps is each workgroup's partial sums, 66 KB for 256 x 64.
+//
+// g is rounded to bf16 as where it was stored, dx once after add and mask: the same values but for the order of sums.
+//
+// Maps of 56 x 56 x 256 from 64, 64 images (200704 positions, 258 MB): 52 us, 5 TB/s, for 118 in three launches; 64 from 256 with a gradient to join 73 for 143; the
+// first group of ResNet-50's blocks as a stage 2248 -> 1880 us.  Forward and backward pass and update of both layers, before and now (us): 256 from 64 at 65536
+// positions 76 and 58, 16384 39 and 31, 64 from 64 at 65536 43 and 27, at 4096 and below 27 and 22 (the launches).  Errors of dW against 64 bits (2-norm) over 200704,
+// 16384 and 1024 positions 1.8, 1.0 and 0.7e-7 before, 1.2, 1.0 and 0.7e-7 now.
+#include <algorithm>
+
+#include "gemm3.hip.h"
+#include "kernels.h"
+#include "launch.h"
+
+namespace tmps {
+
+typedef float f32x4v_t __attribute__((ext_vector_type(4)));
+
+static constexpr int kPwThreads = 512, kPwRows = 64;   // positions of a step
+// Row strides in LDS, bytes: whole 16-byte pieces, an odd number of them modulo 16, so that 16 rows read at one column and 4 rows of 64 bytes read transposed
+// fall on different banks (64 values: the latter two by two).
+__host__ __device__ constexpr int pw_stride(int n) { return n == 64 ? 144 : n == 128 ? 336 : 592; }
+template <int O, int I> constexpr int pw_lds_bytes() { return kPwRows * (pw_stride(O) + pw_stride(I) + (I + 4) * 4) + I * pw_stride(O); }
+
+__device__ __forceinline__ void pw_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// dy, z: [P][O]; x, add (may be null), dx: [P][I]; w: [O][I].  Workgroup b takes positions b per .. b per + per - 1 (per: a multiple of 16).
+// part_a: [workgroups][2][O] sums of dy z and of dy; part_w: [workgroups][O I + O] dW, then the sums of g.
+template <int O, int I>
+__global__ __launch_bounds__(kPwThreads) void affine_pointwise_bwd_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ z, const bf16_t* __restrict__ x,
+                                                                          const bf16_t* __restrict__ w, const float* __restrict__ gain, const bf16_t* add, int masked,
+                                                                          bf16_t* dx, float* __restrict__ part_a, float* __restrict__ part_w, int P, int per) {
+    constexpr int CO = O / 8, CI = I / 8;                               // 16-byte pieces of a row
+    constexpr int RO = kPwThreads / CO, RI = kPwThreads / CI;           // rows that the workgroup's threads cover at a time
+    constexpr int NO = kPwRows / RO, NI = kPwRows / RI;                 // pieces of a thread
+    constexpr int SG = pw_stride(O), SX = pw_stride(I), SD = I + 4;     // row strides in LDS: bytes, bytes, floats
+    constexpr int CB = I / 64, KS = O / 32;                             // dx: 16-column blocks and 32-k steps of a wave
+    constexpr int TO = O / 32, TI = I / 32, PW = TO * TI >= 8 ? TO * TI / 8 : 1;   // dW: 32 x 32 blocks of a wave
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const lds_t G = (lds_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
+    const lds_t X = G + kPwRows * SG, D = X + kPwRows * SX, W = D + kPwRows * SD * 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, quarter = lane >> 4;
+    const int co = tid % CO, ro = tid / CO, ci = tid % CI, ri = tid / CI;
+    const int p0 = blockIdx.x * per, p1 = min(P, p0 + per);
+
+    float gn[8], s_g[8], s_dy[8], s_dyz[8];   // (a step's values are summed by themselves first, here and in dW: no chain of roundings over all positions)
+    load8(gain + co * 8, gn);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s_g[e] = s_dy[e] = s_dyz[e] = 0.0f;
+
+    // W transposed, [I][O]
+#pragma unroll
+    for (int n = 0; n < O * I / kPwThreads; ++n) {
+        const int at = n * kPwThreads + tid;
+        *lds_ptr<bf16_t>(W + at % I * SG + at / I * 2) = w[at];
+    }
+    // dx: wave (column group, half of the positions)
+    const int cg = wave & 3, ph = wave >> 2;
+
+    // dW: a wave's blocks share the block of the wider side
+    const int wide = O >= I ? TO : TI;
+    const int b_wide = wave % wide, b_other = wave / wide * PW;
+    const bool multiplies = TO * TI >= 8 || wave < TO * TI;
+    f32x16_t dw[PW];
+#pragma unroll
+    for (int b = 0; b < PW; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dw[b][r] = 0.0f;
+    // transposed fragment: rows (channels) 32 block + .., k (positions) 16 kk + 8 (lane / 32) + 0 .. 7
+    const int tk = (lane >> 5) * 8 + ((lane & 15) >> 2), tc = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+    auto fragment = [&](lds_t tile, int stride, int block, int kk) {
+        const lds_t a = tile + (kk * 16 + tk) * stride + (block * 32 + tc) * 2;
+        union { s16x4_t h[2]; bf16x8_t v; } u;
+        u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(a));
+        u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(a + 4 * stride));
+        return u.v;
+    };
+
+    bf16x8_t vdy[NO], vz[NO], vx[NI], va[NI];
+    const bf16x8_t none = {};
+    // (positions from here on are the workgroup's own: 32-bit offsets)
+    const int mine = p1 - p0;
+    dy += (int64_t)p0 * O;
+    z += (int64_t)p0 * O;
+    x += (int64_t)p0 * I;
+    dx += (int64_t)p0 * I;
+    if (add) add += (int64_t)p0 * I;
+    auto request = [&](int base) {
+#pragma unroll
+        for (int n = 0; n < NO; ++n) {
+            const int p = base + ro + n * RO;
+            const uint32_t at = (uint32_t)(p * O + co * 8);
+            vdy[n] = p < mine ? *reinterpret_cast<const bf16x8_t*>(dy + at) : none;
+            vz[n] = p < mine ? *reinterpret_cast<const bf16x8_t*>(z + at) : none;
+        }
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int p = base + ri + n * RI;
+            const uint32_t at = (uint32_t)(p * I + ci * 8);
+            vx[n] = p < mine ? *reinterpret_cast<const bf16x8_t*>(x + at) : none;
+            va[n] = add && p < mine ? *reinterpret_cast<const bf16x8_t*>(add + at) : none;
+        }
+    };
+    if (mine > 0) request(0);
+    for (int base = 0; base < mine; base += kPwRows) {
+        float t_g[8] = {}, t_dy[8] = {}, t_dyz[8] = {};
+#pragma unroll
+        for (int n = 0; n < NO; ++n) {
+            bf16x8_t g;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float d = (float)vdy[n][e];
+                t_dy[e] += d;
+                t_dyz[e] += d * (float)vz[n][e];
+                g[e] = (bf16_t)(d * gn[e]);
+                t_g[e] += (float)g[e];
+            }
+            *lds_ptr<bf16x8_t>(G + (ro + n * RO) * SG + co * 16) = g;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            s_g[e] += t_g[e];
+            s_dy[e] += t_dy[e];
+            s_dyz[e] += t_dyz[e];
+        }
+        bf16x8_t keep[NI];
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            *lds_ptr<bf16x8_t>(X + (ri + n * RI) * SX + ci * 16) = vx[n];
+            keep[n] = va[n];
+        }
+        if (base + kPwRows < mine) request(base + kPwRows);
+        pw_barrier();
+
+        f32x4v_t d[2][CB];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) d[h][c] = f32x4v_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            bf16x8_t af[2], wf[CB];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) wf[c] = *lds_ptr<const bf16x8_t>(W + (cg * (I / 4) + c * 16 + l16) * SG + k * 64 + quarter * 16);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) af[h] = *lds_ptr<const bf16x8_t>(G + (ph * 32 + h * 16 + l16) * SG + k * 64 + quarter * 16);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int c = 0; c < CB; ++c) d[h][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h], wf[c], d[h][c], 0, 0, 0);
+        }
+        // register r of a lane: position 4 (lane / 16) + r, column lane % 16
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    *lds_ptr<float>(D + ((ph * 32 + h * 16 + quarter * 4 + r) * SD + cg * (I / 4) + c * 16 + l16) * 4) = d[h][c][r];
+        if (multiplies) {
+#pragma unroll
+            for (int b = 0; b < PW; ++b) {
+                f32x16_t t = {};
+#pragma unroll
+                for (int kk = 0; kk < kPwRows / 16; ++kk)
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment(G, SG, O >= I ? b_wide : b_other + b, kk), fragment(X, SX, O >= I ? b_other + b : b_wide, kk), t, 0, 0, 0);
+                dw[b] += t;
+            }
+        }
+        pw_barrier();
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int row = ri + n * RI, p = base + row;
+            if (p < mine) {
+                const f32x4v_t lo = *lds_ptr<const f32x4v_t>(D + (row * SD + ci * 8) * 4), hi = *lds_ptr<const f32x4v_t>(D + (row * SD + ci * 8 + 4) * 4);
+                float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                const bf16x8_t t = *lds_ptr<const bf16x8_t>(X + row * SX + ci * 16);   // (this thread's own piece)
+                bf16x8_t out;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (add) v[e] += (float)keep[n][e];
+                    if (masked && !((float)t[e] > 0.0f)) v[e] = 0.0f;
+                    out[e] = (bf16_t)v[e];
+                }
+                *reinterpret_cast<bf16x8_t*>(dx + (uint32_t)(p * I + ci * 8)) = out;
+            }
+        }
+    }
+
+    float* const pw = part_w + (int64_t)blockIdx.x * (O * I + O);
+    if (multiplies) {
+        // register r of a lane: row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32
+#pragma unroll
+        for (int b = 0; b < PW; ++b) {
+            const int o = (O >= I ? b_wide : b_other + b) * 32, i = (O >= I ? b_other + b : b_wide) * 32;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) pw[(o + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * I + i + (lane & 31)] = dw[b][r];
+        }
+    }
+    // sums over the rows of the threads that hold the same channels
+    float* const sums = reinterpret_cast<float*>(smem_raw);   // [RO][O]
+#pragma unroll
+    for (int which = 0; which < 3; ++which) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sums[ro * O + co * 8 + e] = which == 0 ? s_dyz[e] : which == 1 ? s_dy[e] : s_g[e];
+        __syncthreads();
+        if (tid < O) {
+            float v = 0.0f;
+            for (int r = 0; r < RO; r += 8) {
+                float t[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t[u] = sums[(r + u) * O + tid];
+                v += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+            }
+            if (which < 2) part_a[((int64_t)blockIdx.x * 2 + which) * O + tid] = v;
+            else pw[O * I + tid] = v;
+        }
+    }
+}
+
+// Partial results stay within the 16 MB that a backward pass keeps until its end, a workgroup to a compute unit.
+int affine_pointwise_slabs(int64_t P, int O, int I) {
+    const int64_t most = std::min<int64_t>(256, (int64_t(1) << 22) / (O * I + O)), per = ((P + most - 1) / most + 15) / 16 * 16;
+    return (int)((P + per - 1) / per);
+}
+
+// From 1024 positions on: below, a step of 64 is mostly the workgroup's start and end.  dW has to fit the accumulators of a workgroup beside what is on its way.
+bool affine_pointwise_takes(int dtype, int64_t P, int O, int I) {
+    auto width = [](int n) { return n == 64 || n == 128 || n == 256; };
+    return dtype == kBF16 && width(O) && width(I) && O * I <= 16384 && P >= 1024 && P < (int64_t(1) << 31) - 4096;
+}
+
+template <int O, int I>
+static hipError_t launch_pointwise(const void* dy, const void* z, const void* x, const void* w, const float* gain, const void* add, int masked, void* dx,
+                                   float* gw_affine, float* gw_conv, const Partials& pa, const Partials& pw, int P, hipStream_t s) {
+    constexpr int lds = pw_lds_bytes<O, I>();
+    auto kern = affine_pointwise_bwd_kernel<O, I>;
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return attr;
+    const int slabs = affine_pointwise_slabs(P, O, I), per = ((P + slabs - 1) / slabs + 15) / 16 * 16;
+    hipError_t e = launch_timed(kcAffine, kern, dim3(slabs), dim3(kPwThreads), lds, s, (const bf16_t*)dy, (const bf16_t*)z, (const bf16_t*)x, (const bf16_t*)w, gain,
+                                (const bf16_t*)add, masked, (bf16_t*)dx, pa.ws, pw.ws, P, per);
+    if (e != hipSuccess) return e;
+    if ((e = pa.finish(Reduction{pa.ws, gw_affine, 2 * O, slabs, true}, s)) != hipSuccess) return e;
+    return pw.finish(Reduction{pw.ws, gw_conv, (int64_t)O * I + O, slabs, false}, s);
+}
+
+hipError_t affine_pointwise_backward(const void* dy, const void* z, const void* x, const void* w, const float* gain, const void* add, int masked, void* dx,
+                                     float* gw_affine, float* gw_conv, const Partials& pa, const Partials& pw, int64_t P, int O, int I, hipStream_t s) {
+#define TMPS_POINTWISE(o, i) \
+    if (O == o && I == i) return launch_pointwise<o, i>(dy, z, x, w, gain, add, masked, dx, gw_affine, gw_conv, pa, pw, (int)P, s)
+    TMPS_POINTWISE(64, 64);
+    TMPS_POINTWISE(64, 128);
+    TMPS_POINTWISE(128, 64);
+    TMPS_POINTWISE(128, 128);
+    TMPS_POINTWISE(64, 256);
+    TMPS_POINTWISE(256, 64);
+#undef TMPS_POINTWISE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace tmps
+
+extern "C" int tmps_pointwise_gradients_joint(int dtype, int64_t positions, int cin, int cout) {
+    return tmps::affine_pointwise_takes(dtype, positions, cout, cin) ? 1 : 0;
+}

@@ -62,6 +62,13 @@ static ConvShape conv_shape(const tmps_layer_desc& d, int B) {
     return c;
 }
 
+// whether layer i is an affine layer behind a 1 x 1 convolution of unit stride
+static bool pointwise_below(const tmps_stage& st, int i) {
+    if (i < 1 || st.layers[i].d.kind != TMPS_AFFINE || st.layers[i].in_t != i - 1 || st.layers[i - 1].d.kind != TMPS_CONV2D) return false;
+    const int32_t* c = st.layers[i - 1].d.dims;
+    return c[4] == 1 && c[5] == 1 && c[6] == 1 && c[7] == 0;
+}
+
 // The MFMA convolutions index positions with 24 bits and tensors with 31 (larger ones take an element-wise path): a
 // forward pass over several micro-batches stays within that.
 static bool conv_index_range_ok(const ConvShape& c) {
@@ -288,6 +295,17 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
         soff = align_up(soff + (size_t)rows_all * st.label_rps * 4, 256);
     }
     st.stash_bytes = soff;
+
+    // (a convolution whose gradients come from one pass with those of the affine layer behind it: partial results of both for every workgroup of that pass)
+    for (int i = 1; i < n_layers; ++i) {
+        LayerRT& C = st.layers[i - 1];
+        if (!pointwise_below(st, i)) continue;
+        const int64_t P = (int64_t)M * C.d.dims[0] * C.d.dims[1], O = C.d.dims[3], I = C.d.dims[2];
+        if (!affine_pointwise_takes(cfg->dtype, P, (int)O, (int)I)) continue;
+        const size_t slabs = (size_t)affine_pointwise_slabs(P, (int)O, (int)I);
+        C.part_elems = std::max<size_t>(C.part_elems, slabs * (size_t)(O * I + O));
+        st.layers[i].part_elems = std::max<size_t>(st.layers[i].part_elems, slabs * 2 * (size_t)O);
+    }
 
     // Weight gradients that the backward pass leaves to its end, in groups of one launch each.  The gradient of such a layer's
     // result then has to last that long: it gets memory of its own, unless it is the upstream gradient or the loss's.
@@ -1005,6 +1023,26 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                 break;
             case TMPS_AFFINE:
                 // the layer before has no activation (checked at creation): nothing to pass through
+                if (pointwise_below(*st, li) && st->readers[t_in + 1] == 1 && !in_order) {
+                    const LayerRT& C = st->layers[li - 1];
+                    const int64_t P = (int64_t)M * d[0] * d[1];
+                    const int I = C.d.dims[2];
+                    const void* const x = C.in_t < 0 ? (const void*)x0 : (const void*)st->out_ptr(st->layers[C.in_t], row0);
+                    const Grad& G = grads[C.in_t + 1];
+                    auto bits = [](const void* p) { return reinterpret_cast<uintptr_t>(p); };
+                    int mode;
+                    const void* const relu = mask_of(C.in_t, mode);
+                    if (affine_pointwise_takes(dt, P, d[2], I) && L.part_elems && C.part_elems && mode == 1 && (C.in_t >= 0 || dx) &&
+                        ((bits(g.ptr) | bits(in) | bits(x) | bits(st->master + L.w_off) | (G.set ? bits(G.ptr) : 0) | (C.in_t < 0 ? bits(dx) : 0)) & 15) == 0) {
+                        if ((rc = target(C.in_t, T)) != TMPS_OK) return rc;
+                        TMPS_GEMM(affine_pointwise_backward(g.ptr, in, x, st->wptr(C), st->master + L.w_off, T.add, relu ? 1 : 0, T.dst, gw, st->grad + C.w_off,
+                                                            partials(L), partials(C), P, d[2], I, s));
+                        commit(C.in_t, T);
+                        --remaining[t_in + 1];
+                        with_below = 1;
+                        break;
+                    }
+                }
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 if (T.add) return fail(TMPS_EUNSUPPORTED, "an affine layer on a shared input");
                 TMPS_GEMM(affine_backward(dt, g.ptr, in, st->master + L.w_off, T.wanted ? T.dst : nullptr, gw, partials(L),

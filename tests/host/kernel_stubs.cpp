@@ -29,6 +29,9 @@ hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bi
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain, const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) { return hipSuccess; }
+bool affine_pointwise_takes(int, int64_t, int, int) { return false; }
+int affine_pointwise_slabs(int64_t, int, int) { return 1; }
+hipError_t affine_pointwise_backward(const void*, const void*, const void*, const void*, const float*, const void*, int, void*, float*, float*, const Partials&, const Partials&, int64_t, int, int, hipStream_t) { return hipSuccess; }
 bool maxpool_keeps_winners(int k) { return k <= 11; }
 bool maxpool_affine_takes(int, int64_t, int, int, int) { return false; }
 hipError_t maxpool_affine_backward(int, const void*, const uint8_t*, const void*, const float*, void*, float*, const Partials&, int, int, int, int, int, int, int, int, hipStream_t) { return hipSuccess; }

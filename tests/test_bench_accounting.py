@@ -140,3 +140,15 @@ def test_both_gradients_of_a_layer_in_one_launch_count_together(name):
         e = bench.class_entry(cfg, "dense_backward", 2.0, layers, dense_gradients_joint)
         assert e["tflops"] == pytest.approx(both[1] / 2e-3 / 1e12, rel=1e-12)
     assert "dense_dgrad" not in got if name == "mlp4x1024_bf16" else True
+
+
+def test_gradients_of_a_convolution_in_one_launch_with_the_affine_layer_behind_count_there():
+    """Seven of the first group's 1 x 1 convolutions (the second group's have more outputs than a workgroup's accumulators), with all of their work."""
+    from paper_2410_14312_amd import pointwise_gradients_joint
+
+    cfg = get_config("resnet50_bf16")
+    apart, got = bench.algorithmic_work(cfg), bench.algorithmic_work(cfg, joint_pointwise=pointwise_gradients_joint)
+    classes = ("conv_dgrad", "conv_wgrad", "affine")
+    for i in (1, 2):
+        assert sum(got[k][i] for k in classes) == pytest.approx(sum(apart[k][i] for k in classes), rel=1e-12)
+    assert apart["conv_dgrad"][0] - got["conv_dgrad"][0] == 7 and apart["conv_wgrad"][0] - got["conv_wgrad"][0] == 7

@@ -1,0 +1,85 @@
+"""Gradients of a 1 x 1 convolution and the affine layer behind it in one pass: every pair of widths, positions that end inside a step of 64, a piece of 16 and a
+workgroup's run, with and without ReLU below, a gradient to join; against sums of the same bf16 values in 64 bits."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2410_14312_amd import load_library
+from workloads.configs import affine, conv, resadd
+
+WIDTHS = [(64, 64), (64, 128), (128, 64), (128, 128), (64, 256), (256, 64)]   # out of the convolution, into it
+# samples, height, width of the map: 1024 positions, 16 to a workgroup, and one more; 16384, 80 to a workgroup; a last one with fewer, off 16
+MAPS = [(1, 32, 32), (1, 25, 41), (4, 64, 64), (7, 49, 51), (16, 35, 36)]
+
+
+def takes(P, O, I, dtype=1):
+    f = getattr(load_library(), "_ZN4tmps22affine_pointwise_takesEilii")
+    f.restype, f.argtypes = C.c_bool, [C.c_int, C.c_long, C.c_int, C.c_int]
+    return f(dtype, P, O, I)
+
+
+def test_the_rule():
+    assert all(takes(1024, o, i) for o, i in WIDTHS)
+    assert not takes(1023, 64, 64) and not takes(20000, 128, 256) and not takes(20000, 96, 64) and not takes(20000, 512, 64) and not takes(20000, 64, 64, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("B,h,w", MAPS)
+@pytest.mark.parametrize("cout,cin", WIDTHS)
+def test_against_64_bits(cout, cin, B, h, w, relu):
+    import torch
+    from paper_2410_14312_amd import Stage
+
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(cout + cin + h)
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    P = B * h * w
+    # (with ReLU the convolution reads another's result, through which its input gradient passes: a 1 x 1 layer of 8 channels)
+    specs = ([conv(h, w, 8, cin, 1, 1, 0, True)] if relu else []) + [conv(h, w, cin, cout, 1, 1, 0, False), affine(h, w, cout, False)]
+    p = ([{"w": randn(cin, 1, 1, 8) / 8 ** 0.5, "b": 0.1 * randn(cin)}] if relu else []) + [
+        {"w": randn(cout, 1, 1, cin) / cin ** 0.5, "b": 0.1 * randn(cout)}, {"w": 1 + 0.2 * randn(cout), "b": 0.1 * randn(cout)}]
+    st = Stage(specs, "bf16", B, 1, 1, 0.1, 0.9, borrow_input=True)
+    st.set_params([{k: v.cpu().numpy() for k, v in q.items()} for q in p])
+    x = randn(B, h * w * (8 if relu else cin)).bfloat16()
+    dy = (randn(B, h * w * cout) / P).bfloat16()
+    dx = torch.full_like(x, float("nan"))
+    st.forward_micro(0, x)
+    st.backward([0], dy=dy, dx=dx)
+    torch.cuda.synchronize()
+    got = st.get_grads()
+    d64 = lambda t: t.double()
+    xin = x.view(P, -1)
+    if relu:   # the stored activation: fp32 sums of eight products, rounded
+        xin = torch.relu(d64(xin) @ d64(p[0]["w"].view(cin, 8).bfloat16()).t() + d64(p[0]["b"])).bfloat16()
+    wb = p[-2]["w"].view(cout, cin).bfloat16()
+    z = (d64(xin) @ d64(wb).t() + d64(p[-2]["b"])).bfloat16()
+    g = (dy.view(P, cout).float() * p[-1]["w"]).bfloat16()
+    rel = lambda a, b: float(torch.linalg.norm(d64(torch.as_tensor(a).to(b.device)) - b) / torch.linalg.norm(b))
+    # z and x may differ from the stored ones by a rounding here and there: 2^-9 of a value in one of some thousand
+    assert rel(got[-1]["w"], (d64(dy.view(P, cout)) * d64(z)).sum(0)) < 1e-4
+    assert rel(got[-1]["b"], d64(dy.view(P, cout)).sum(0)) < 5e-7
+    assert rel(got[-2]["b"], d64(g).sum(0)) < 5e-7
+    want = d64(g).t().contiguous() @ d64(xin)
+    assert rel(got[-2]["w"].reshape(cout, cin), want) < (1e-4 if relu else 2.5e-7)
+    if not relu:
+        want = d64(g) @ d64(wb)
+        assert rel(dx.view(P, cin), want) < 2.0 ** -8.5
+        assert float((d64(dx.view(P, cin)) - want).abs().max() / want.abs().max()) < 2.0 ** -8
+    else:
+        # stored in bf16: one value in some thousand is rounded to the other side, by 2^-8 of it, 2^-8 / sqrt(1000) of the whole in the 2-norm
+        below = d64(((d64(g) @ d64(wb)) * (xin > 0)).bfloat16())
+        assert rel(got[0]["w"].reshape(cin, 8), below.t().contiguous() @ d64(x.view(P, 8))) < 2.5e-4
+        assert rel(got[0]["b"], below.sum(0)) < 2.5e-4
+
+
+@pytest.mark.gpu
+def test_bottleneck_blocks_against_the_oracle():
+    """Both 1 x 1 convolutions of a block with a projection and of one without, whose shortcut's gradient the first one joins."""
+    from tests.test_gpu_stage import run_stage_case
+    from workloads.configs import bottleneck
+
+    first, h, c = bottleneck(32, 64, 64, 1, True)
+    second, h, c = bottleneck(h, c, 64, 1, False)
+    run_stage_case(first + second, "bf16", 8, 2, seed=11, deep=True)
