@@ -227,6 +227,159 @@ __global__ __launch_bounds__(kPwThreads) void affine_pointwise_bwd_kernel(const 
     }
 }
 
+// ---- forward: 64 channels to 256, and from those to 64 again ------------------------------------------------------------------------------------------------
+// z = x w^T + bias, y = act(gain z + shift + res) as EpiConvAffine forms and rounds them; PAIR: and the next block's first convolution, which reads y, with its
+// affine layer, from LDS instead of memory.  A workgroup of eight waves takes a run of positions, 64 at a time; a wave owns 32 of the wide result's channels (and 16 of the
+// narrow one's for half of the positions) and keeps their weights in registers; x and res of the next step are on their way during a step.  A wave's two blocks of 16
+// channels are interleaved in fours, so that a lane holds 8 consecutive channels of a position.
+struct PwWide {
+    const bf16_t *x, *w, *res;   // [P][64], [256][64], [P][256] or null
+    const float *bias, *gain, *shift;
+    bf16_t *z, *y, *again;   // [P][256] each; again: y once more, or null
+    int relu;
+};
+struct PwNarrow {
+    const bf16_t* w;   // [64][256]
+    const float *bias, *gain, *shift;
+    bf16_t *z, *y;     // [P][64] each
+    int relu;
+};
+
+template <bool PAIR>
+__global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwNarrow b, int P, int per) {
+    constexpr int C = 64, W = 256, SX = pw_stride(C), SY = pw_stride(W);
+    __shared__ __attribute__((aligned(16))) unsigned char xs[kPwRows * SX];
+    __shared__ __attribute__((aligned(16))) unsigned char ys[PAIR ? kPwRows * SY : 16];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quarter = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p0 = blockIdx.x * per, mine = min(P - p0, per);
+    if (mine <= 0) return;
+    const bf16_t* const x = a.x + (int64_t)p0 * C;
+    const bf16_t* const res = a.res ? a.res + (int64_t)p0 * W : nullptr;
+    bf16_t *const z = a.z + (int64_t)p0 * W, *const y = a.y + (int64_t)p0 * W, *const again = a.again ? a.again + (int64_t)p0 * W : nullptr;
+
+    const bf16x8_t none = {};
+    const int xr = tid >> 3, xc = (tid & 7) * 8;
+    const int ch = wave * 32 + quarter * 8;   // this lane's channels of the wide result: ch .. ch + 7
+    bf16x8_t vx, vr[4];
+    auto request_x = [&](int base) { vx = base + xr < mine ? *reinterpret_cast<const bf16x8_t*>(x + (uint32_t)((base + xr) * C + xc)) : none; };
+    auto request_res = [&](int base) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int p = base + c * 16 + l16;
+            vr[c] = res && p < mine ? *reinterpret_cast<const bf16x8_t*>(res + (uint32_t)(p * W + ch)) : none;
+        }
+    };
+    request_x(0);
+    request_res(0);
+
+    bf16x8_t wf[2][2];   // [block][step of 32 k]: row l16 of block j is channel 32 wave + 8 (l16 / 4) + 4 j + l16 % 4
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) wf[j][k] = *reinterpret_cast<const bf16x8_t*>(a.w + (wave * 32 + (l16 >> 2) * 8 + j * 4 + (l16 & 3)) * C + k * 32 + quarter * 8);
+    float g[8], sh[8], bi[8];
+    load8(a.gain + ch, g);
+    load8(a.shift + ch, sh);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bi[e] = a.bias ? a.bias[ch + e] : 0.0f;
+    // the narrow result: channels 16 (wave % 4) + 4 quarter + 0 .. 3, positions 32 (wave / 4) + 16 h + l16
+    const int cn = (wave & 3) * 16, ph = wave >> 2;
+    bf16x8_t wn[PAIR ? 8 : 1];
+    float gn[4], sn[4], bn[4];
+    if constexpr (PAIR) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) wn[k] = *reinterpret_cast<const bf16x8_t*>(b.w + (cn + l16) * W + k * 32 + quarter * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            gn[e] = b.gain[cn + quarter * 4 + e];
+            sn[e] = b.shift[cn + quarter * 4 + e];
+            bn[e] = b.bias ? b.bias[cn + quarter * 4 + e] : 0.0f;
+        }
+    }
+
+    *reinterpret_cast<bf16x8_t*>(xs + xr * SX + xc * 2) = vx;
+    for (int base = 0; base < mine; base += kPwRows) {
+        const bool more = base + kPwRows < mine;
+        if (more) request_x(base + kPwRows);
+        pw_barrier();
+        f32x4v_t d[2][4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) d[j][c] = f32x4v_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const bf16x8_t f = *reinterpret_cast<const bf16x8_t*>(xs + (c * 16 + l16) * SX + k * 64 + quarter * 16);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) d[j][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][k], f, d[j][c], 0, 0, 0);
+            }
+        }
+        // register r of block j: channel ch + 4 j + r of position 16 c + l16
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int p = base + c * 16 + l16;
+            bf16x8_t zo, yo;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                zo[e] = (bf16_t)(d[e >> 2][c][e & 3] + bi[e]);
+                float v = (float)(bf16_t)(g[e] * (float)zo[e] + sh[e]);   // rounded as the stored tensor would be
+                if (res) v += (float)vr[c][e];
+                if (a.relu) v = v > 0.0f ? v : 0.0f;
+                yo[e] = (bf16_t)v;
+            }
+            if (p < mine) {
+                const uint32_t at = (uint32_t)(p * W + ch);
+                *reinterpret_cast<bf16x8_t*>(z + at) = zo;
+                *reinterpret_cast<bf16x8_t*>(y + at) = yo;
+                if (again) *reinterpret_cast<bf16x8_t*>(again + at) = yo;
+            }
+            if constexpr (PAIR) *reinterpret_cast<bf16x8_t*>(ys + (c * 16 + l16) * SY + ch * 2) = yo;
+        }
+        if (more) request_res(base + kPwRows);
+        pw_barrier();
+        if (more) *reinterpret_cast<bf16x8_t*>(xs + xr * SX + xc * 2) = vx;
+        if constexpr (PAIR) {
+            f32x4v_t n[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    n[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wn[k], *reinterpret_cast<const bf16x8_t*>(ys + (ph * 32 + h * 16 + l16) * SY + k * 64 + quarter * 16), n[h],
+                                                                   0, 0, 0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int p = base + ph * 32 + h * 16 + l16;
+                typedef bf16_t bf16x4_t __attribute__((ext_vector_type(4)));
+                bf16x4_t zo, yo;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    zo[e] = (bf16_t)(n[h][e] + bn[e]);
+                    float v = (float)(bf16_t)(gn[e] * (float)zo[e] + sn[e]);
+                    if (b.relu) v = v > 0.0f ? v : 0.0f;
+                    yo[e] = (bf16_t)v;
+                }
+                if (p < mine) {
+                    const int64_t at = (int64_t)(p0 + p) * C + cn + quarter * 4;
+                    *reinterpret_cast<bf16x4_t*>(b.z + at) = zo;
+                    *reinterpret_cast<bf16x4_t*>(b.y + at) = yo;
+                }
+            }
+        }
+    }
+}
+
+bool pointwise_forward_takes(int64_t P, int Cin, int Cout) { return Cin == 64 && Cout == 256 && P >= 4096 && P < (int64_t(1) << 31) - 4096; }
+
+hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, hipStream_t s) {
+    const PwWide a{(const bf16_t*)f.x, (const bf16_t*)f.w, (const bf16_t*)f.res, f.bias, f.gain, f.shift, (bf16_t*)f.z, (bf16_t*)f.y, (bf16_t*)f.again, f.relu};
+    PwNarrow b{};
+    if (next) b = PwNarrow{(const bf16_t*)next->w, next->bias, next->gain, next->shift, (bf16_t*)next->z, (bf16_t*)next->y, next->relu};
+    const int grid = (int)std::min<int64_t>(256, (P + 31) / 32), per = (int)((P + grid - 1) / grid);
+    if (next) return launch_timed(kcConvFwd, pointwise_fwd_kernel<true>, dim3(grid), dim3(kPwThreads), 0, s, a, b, (int)P, per);
+    return launch_timed(kcConvFwd, pointwise_fwd_kernel<false>, dim3(grid), dim3(kPwThreads), 0, s, a, b, (int)P, per);
+}
+
 // Partial results stay within the 16 MB that a backward pass keeps until its end, a workgroup to a compute unit.
 int affine_pointwise_slabs(int64_t P, int O, int I) {
     const int64_t most = std::min<int64_t>(256, (int64_t(1) << 22) / (O * I + O)), per = ((P + most - 1) / most + 15) / 16 * 16;

@@ -62,6 +62,12 @@ static ConvShape conv_shape(const tmps_layer_desc& d, int B) {
     return c;
 }
 
+static bool on16(std::initializer_list<const void*> all) {
+    uintptr_t bits = 0;
+    for (const void* p : all) bits |= reinterpret_cast<uintptr_t>(p);
+    return (bits & 15) == 0;
+}
+
 // whether layer i is an affine layer behind a 1 x 1 convolution of unit stride
 static bool pointwise_below(const tmps_stage& st, int i) {
     if (i < 1 || st.layers[i].d.kind != TMPS_AFFINE || st.layers[i].in_t != i - 1 || st.layers[i - 1].d.kind != TMPS_CONV2D) return false;
@@ -626,6 +632,20 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
                     if (join) {
                         const LayerRT& J = st->layers[li + 2];
                         const void* b = J.in_b < 0 ? x0 : (const void*)st->out_ptr(st->layers[J.in_b], row0);
+                        // the next block's first convolution, which reads the join, in the same launch
+                        if (dt == kBF16 && li + 4 < nl && pointwise_below(*st, (int)li + 1) && pointwise_below(*st, (int)li + 4) && st->layers[li + 3].in_t == (int)li + 2 &&
+                            st->layers[li + 3].act == 0 && st->readers[li + 4] == 1 && st->layers[li + 3].d.dims[3] == d[2] && li + 4 != out_layer &&
+                            pointwise_forward_takes((int64_t)mb * d[0] * d[1], d[2], d[3])) {
+                            const LayerRT &C = st->layers[li + 3], &B = st->layers[li + 4];
+                            const PointwiseForward f{in, st->wptr(L), b, st->bptr(L), st->master + A.w_off, st->master + A.b_off, out, st->out_ptr(J, row0), nullptr, J.relu};
+                            const PointwiseForward n{nullptr, st->wptr(C), nullptr, st->bptr(C), st->master + B.w_off, st->master + B.b_off, st->out_ptr(C, row0),
+                                                     st->out_ptr(B, row0), nullptr, B.relu};
+                            if (on16({f.x, f.w, f.res, f.gain, f.shift, f.z, f.y, n.w, n.z, n.y})) {
+                                TMPS_GEMM(pointwise_forward(f, &n, (int64_t)mb * d[0] * d[1], s));
+                                li += 4;
+                                break;
+                            }
+                        }
                         TMPS_GEMM(conv_affine_forward(dt, in, st->wptr(L), st->bptr(L), out, st->master + A.w_off, st->master + A.b_off,
                                                       again(li + 2), b, st->out_ptr(J, row0), J.relu, conv_shape(L.d, mb), ws, s));
                         li += 2;
@@ -1029,11 +1049,10 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                     const int I = C.d.dims[2];
                     const void* const x = C.in_t < 0 ? (const void*)x0 : (const void*)st->out_ptr(st->layers[C.in_t], row0);
                     const Grad& G = grads[C.in_t + 1];
-                    auto bits = [](const void* p) { return reinterpret_cast<uintptr_t>(p); };
                     int mode;
                     const void* const relu = mask_of(C.in_t, mode);
                     if (affine_pointwise_takes(dt, P, d[2], I) && L.part_elems && C.part_elems && mode == 1 && (C.in_t >= 0 || dx) &&
-                        ((bits(g.ptr) | bits(in) | bits(x) | bits(st->master + L.w_off) | (G.set ? bits(G.ptr) : 0) | (C.in_t < 0 ? bits(dx) : 0)) & 15) == 0) {
+                        on16({g.ptr, in, x, st->master + L.w_off, G.set ? G.ptr : nullptr, C.in_t < 0 ? dx : nullptr})) {
                         if ((rc = target(C.in_t, T)) != TMPS_OK) return rc;
                         TMPS_GEMM(affine_pointwise_backward(g.ptr, in, x, st->wptr(C), st->master + L.w_off, T.add, relu ? 1 : 0, T.dst, gw, st->grad + C.w_off,
                                                             partials(L), partials(C), P, d[2], I, s));

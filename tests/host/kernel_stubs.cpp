@@ -29,6 +29,8 @@ hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bi
 hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain, const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) { return hipSuccess; }
+bool pointwise_forward_takes(int64_t, int, int) { return false; }
+hipError_t pointwise_forward(const PointwiseForward&, const PointwiseForward*, int64_t, hipStream_t) { return hipSuccess; }
 bool affine_pointwise_takes(int, int64_t, int, int) { return false; }
 int affine_pointwise_slabs(int64_t, int, int) { return 1; }
 hipError_t affine_pointwise_backward(const void*, const void*, const void*, const void*, const float*, const void*, int, void*, float*, float*, const Partials&, const Partials&, int64_t, int, int, hipStream_t) { return hipSuccess; }

@@ -1,4 +1,4 @@
-"""Gradients of a 1 x 1 convolution and the affine layer behind it in one pass: every pair of widths, positions that end inside a step of 64, a piece of 16 and a
+"""A 1 x 1 convolution and the affine layer behind it, forward from 64 channels to 256 and their gradients in one pass: every pair of widths, positions that end inside a step of 64, a piece of 16 and a
 workgroup's run, with and without ReLU below, a gradient to join; against sums of the same bf16 values in 64 bits."""
 import ctypes as C
 
@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2410_14312_amd import load_library
-from workloads.configs import affine, conv, resadd
+from workloads.configs import affine, conv
 
 WIDTHS = [(64, 64), (64, 128), (128, 64), (128, 128), (64, 256), (256, 64)]   # out of the convolution, into it
 # samples, height, width of the map: 1024 positions, 16 to a workgroup, and one more; 16384, 80 to a workgroup; a last one with fewer, off 16
@@ -75,11 +75,43 @@ def test_against_64_bits(cout, cin, B, h, w, relu):
 
 
 @pytest.mark.gpu
-def test_bottleneck_blocks_against_the_oracle():
-    """Both 1 x 1 convolutions of a block with a projection and of one without, whose shortcut's gradient the first one joins."""
+@pytest.mark.parametrize("h,micro", [(32, 8), (37, 3), (64, 1), (31, 4)])
+def test_bottleneck_blocks_against_the_oracle(h, micro):
+    """Both 1 x 1 convolutions of a block with a projection and of two without, whose shortcut's gradient the first one joins; forward the join and the next
+    block's first convolution leave one launch (from 4096 positions of a micro-batch on), with positions off 16 and 64, and the projection and the last join theirs."""
     from tests.test_gpu_stage import run_stage_case
     from workloads.configs import bottleneck
 
-    first, h, c = bottleneck(32, 64, 64, 1, True)
-    second, h, c = bottleneck(h, c, 64, 1, False)
-    run_stage_case(first + second, "bf16", 8, 2, seed=11, deep=True)
+    specs, c = [], 64
+    for k in range(3):
+        block, h, c = bottleneck(h, c, 64, 1, k == 0)
+        specs += block
+    run_stage_case(specs, "bf16", micro, 2, seed=11, deep=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("B,h,w", [(1, 64, 64), (3, 37, 37), (1, 71, 103), (5, 60, 60)])
+def test_forward_is_as_its_layers_round(B, h, w, relu):
+    """64 channels to 256 with the affine layer: sums in 64 bits, rounded where the layers store; beside them only neighbours of a rounding may differ."""
+    import torch
+    from paper_2410_14312_amd import Stage
+
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(h + w)
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    P = B * h * w
+    wt, bias, gain, shift = randn(256, 1, 1, 64) / 8, 0.1 * randn(256), 1 + 0.2 * randn(256), 0.1 * randn(256)
+    st = Stage([conv(h, w, 64, 256, 1, 1, 0, False), affine(h, w, 256, relu)], "bf16", B, 1, 1, 0.1, 0.9, borrow_input=True)
+    st.set_params([{"w": wt.cpu().numpy(), "b": bias.cpu().numpy()}, {"w": gain.cpu().numpy(), "b": shift.cpu().numpy()}])
+    x = randn(B, h * w * 64).bfloat16()
+    y = torch.full((B, h * w * 256), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    st.forward_micro(0, x, y=y)
+    torch.cuda.synchronize()
+    z = (x.view(P, 64).double() @ wt.view(256, 64).bfloat16().double().t() + bias.double()).bfloat16()
+    want = gain.double() * z.double() + shift.double()
+    want = (torch.relu(want) if relu else want).bfloat16()
+    got = y.view(P, 256)
+    assert float((got != want).double().mean()) < 1e-3
+    # (a z on the other side of its rounding, 2^-8 of it, times a gain below 2, and y's own rounding)
+    assert float(((got.double() - want.double()).abs() - 2.0 ** -7 * (z.double().abs() * 2 + want.double().abs())).max()) <= 0
