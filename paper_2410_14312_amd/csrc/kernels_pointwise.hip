@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwN
             }
             if (p < mine) {
                 const uint32_t at = (uint32_t)(p * W + ch);
-                *reinterpret_cast<bf16x8_t*>(z + at) = zo;
+                __builtin_nontemporal_store(zo, reinterpret_cast<bf16x8_t*>(z + at));
                 *reinterpret_cast<bf16x8_t*>(y + at) = yo;
                 if (again) *reinterpret_cast<bf16x8_t*>(again + at) = yo;
             }
@@ -375,7 +375,7 @@ hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* 
     const PwWide a{(const bf16_t*)f.x, (const bf16_t*)f.w, (const bf16_t*)f.res, f.bias, f.gain, f.shift, (bf16_t*)f.z, (bf16_t*)f.y, (bf16_t*)f.again, f.relu};
     PwNarrow b{};
     if (next) b = PwNarrow{(const bf16_t*)next->w, next->bias, next->gain, next->shift, (bf16_t*)next->z, (bf16_t*)next->y, next->relu};
-    const int grid = (int)std::min<int64_t>(256, (P + 31) / 32), per = (int)((P + grid - 1) / grid);
+    const int grid = (int)std::min<int64_t>(next ? 256 : 512, (P + 31) / 32), per = (int)((P + grid - 1) / grid);
     if (next) return launch_timed(kcConvFwd, pointwise_fwd_kernel<true>, dim3(grid), dim3(kPwThreads), 0, s, a, b, (int)P, per);
     return launch_timed(kcConvFwd, pointwise_fwd_kernel<false>, dim3(grid), dim3(kPwThreads), 0, s, a, b, (int)P, per);
 }
