@@ -131,13 +131,13 @@ template <int ROWS, int BK, int NW, bool KC> struct G3Loader {
         copy16_to_lds(ptr[g], tile + (wave + g * NW) * 1024);
         ptr[g] += KC ? BK : BK * ld;
     }
-    // row-contiguous, of a k-tile with `left` k (BK or fewer): zeros take the place of those behind its end, which are not read
-    __device__ __forceinline__ void issue_group(lds_t tile, int64_t ld, int wave, int g, int lane, int left) {
+    // row-contiguous: the current k-tile is a unit's last and has `left` k (fewer than BK): zeros take the place of those behind its end, which are not read
+    __device__ __forceinline__ void cut(int wave, int lane, int left) {
         static_assert(!KC, "k-rows are whole lanes of a row-contiguous tile only");
         constexpr int CPR = ROWS / 8;
-        const int k = (wave + g * NW) * (64 / CPR) + lane / CPR;
-        copy16_to_lds(k < left ? (const void*)ptr[g] : (const void*)g3_zeros, tile + (wave + g * NW) * 1024);
-        ptr[g] += BK * ld;
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g)
+            if ((wave + g * NW) * (64 / CPR) + lane / CPR >= left) ptr[g] = reinterpret_cast<const bf16_t*>(g3_zeros);
     }
 };
 
@@ -286,18 +286,20 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         }
         ikt = 0;
     };
+    auto cut_last = [&]() {
+        if constexpr (Work::kRagged) {
+            if (ikt + 1 == ink && ilast < BK) {
+                la.cut(wave, lane, ilast);
+                lb.cut(wave, lane, ilast);
+            }
+        }
+    };
     auto copies_left = [&]() { return iu < units; };
     // copy group g (of G) of the cursor's k-tile into stage `istage`
     auto issue_group = [&](int g) {
         const lds_t st = smem + istage * STAGE;
-        if constexpr (Work::kRagged) {
-            const int left = ikt + 1 == ink ? ilast : BK;
-            if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g, lane, left);
-            else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS, lane, left);
-        } else {
-            if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g);
-            else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS);
-        }
+        if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g);
+        else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS);
     };
     // all G groups of the cursor's k-tile are issued: step the cursor
     auto advance = [&]() {
@@ -306,6 +308,7 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
             iu += grid;
             seek_unit();
         }
+        cut_last();
     };
     // copy the cursor's whole k-tile (if any is left); returns false when all is issued
     auto issue_next = [&]() -> bool {
@@ -322,6 +325,7 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     fb.init(wn * (BN / WN), lane);
 
     seek_unit();
+    cut_last();
     int ahead = 0;   // k-tiles issued beyond the one being multiplied
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -698,8 +702,8 @@ struct G3Group {
         return EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kCols, first + kRows * kCols - g.m0, 0};
     }
 };
-// Over rows that are no multiple of 64: the last k-tile of the last slice is short.  An instance of its own, so that the comparison and the two selects of
-// every copy are paid only where rows need them.  In launches of their own such gradients ran on 64 x 64 tiles: eight of a stage with two blocks of 512
+// Over rows that are no multiple of 64: the last k-tile of the last slice is short.  An instance of its own, so that its tests are paid only where rows
+// need them.  In launches of their own such gradients ran on 64 x 64 tiles: eight of a stage with two blocks of 512
 // features over 3996 rows 156 us, the stage 1127 us and 1087 with one launch; four blocks of 768 over two stages with 1266 rows, two mini-batches, 2570 and
 // 2399; four blocks of 640 in 1F1B order, 1564 rows a pass, 9 % of a run; one mini-batch of three blocks of 768 over 524 rows 1.5 %.
 struct G3GroupRagged : G3Group {

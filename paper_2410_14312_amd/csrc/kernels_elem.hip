@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kCeThreads, 8) void softmax_ce_reg_kernel(const flo
 
 // Rows of any length and alignment, up to T NE values: a block of T threads reads a row once, a value at a time, and keeps it in registers.  Values of neighbouring
 // threads are neighbours in memory, so this costs wider rows' bandwidth little: 999 x 5003 values in bf16 19.8 us as two passes of softmax_ce_wide_kernel
-// and 9.6 so.  (Exponentials as there: expf.)
+// and 10.8 so.  (Exponentials as there: expf.)
 template <typename TG, int T, int NE>
 __global__ __launch_bounds__(T) void softmax_ce_any_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels, TG* __restrict__ dlogits,
                                                           float* __restrict__ row_loss, int C, float inv_M) {
