@@ -34,7 +34,7 @@ def test_against_64_bits(cout, cin, B, h, w, relu):
 
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(cout + cin + h)
-    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0", dtype=torch.float32)
     P = B * h * w
     # (with ReLU the convolution reads another's result, through which its input gradient passes: a 1 x 1 layer of 8 channels)
     specs = ([conv(h, w, 8, cin, 1, 1, 0, True)] if relu else []) + [conv(h, w, cin, cout, 1, 1, 0, False), affine(h, w, cout, False)]
@@ -99,7 +99,7 @@ def test_forward_is_as_its_layers_round(B, h, w, relu):
 
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(h + w)
-    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0", dtype=torch.float32)
     P = B * h * w
     wt, bias, gain, shift = randn(256, 1, 1, 64) / 8, 0.1 * randn(256), 1 + 0.2 * randn(256), 0.1 * randn(256)
     st = Stage([conv(h, w, 64, 256, 1, 1, 0, False), affine(h, w, 256, relu)], "bf16", B, 1, 1, 0.1, 0.9, borrow_input=True)

@@ -38,8 +38,8 @@ def test_both_gradients(rows, din, dout, odd):
 
     def randn(*shape):
         n = int(np.prod(shape))
-        flat = torch.zeros(n + 4, device="cuda:0")
-        flat[odd:odd + n] = torch.randn(n, generator=gen, device="cuda:0")
+        flat = torch.zeros(n + 4, device="cuda:0", dtype=torch.float32)
+        flat[odd:odd + n] = torch.randn(n, generator=gen, device="cuda:0", dtype=torch.float32)
         return flat[odd:odd + n].view(shape)
 
     w, x, dy = randn(dout, din) / din ** 0.5, randn(rows, din), randn(rows, dout)
@@ -48,7 +48,7 @@ def test_both_gradients(rows, din, dout, odd):
         st = Stage([linear(din, dout, False)], "f32", rows, 1, 1, 0.1, 0.9, borrow_input=True)
         st.set_params([{"w": w.cpu().numpy(), "b": np.zeros(dout, np.float32)}])
         st.forward_micro(0, x)
-        dx = torch.zeros(rows * din + 4, device="cuda:0")[odd:odd + rows * din].view(rows, din)
+        dx = torch.zeros(rows * din + 4, device="cuda:0", dtype=torch.float32)[odd:odd + rows * din].view(rows, din)
         st.backward([0], dy=dy, dx=dx if down else None)
         torch.cuda.synchronize()
         got.append((dx.cpu().numpy(), st.get_grads()[0]))

@@ -27,7 +27,7 @@ def test_against_64_bits(widths, rows, parts):
 
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(rows)
-    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0", dtype=torch.float32)
     specs = [linear(a, b, False) for a, b in zip(widths, widths[1:])]
     p = [{"w": (randn(b, a) / a ** 0.5).cpu().numpy(), "b": np.zeros(b, np.float32)} for a, b in zip(widths, widths[1:])]
 

@@ -27,7 +27,7 @@ def test_against_its_definition(dtype, C):
     x = torch.from_numpy(4.0 * rng.standard_normal((M, rows * 32)).astype(np.float32)).to(st.device).to(st.act_dtype)
     labels = torch.from_numpy(rng.integers(0, C, size=(M, rows)).astype(np.int32)).to(st.device)
     labels[0, 0], labels[0, 1], labels[1, 0] = 0, C - 1, 2048
-    loss, y = torch.zeros(1, device=st.device), torch.empty(M, rows * C, device=st.device)
+    loss, y = torch.zeros(1, device=st.device, dtype=torch.float32), torch.empty(M, rows * C, device=st.device, dtype=torch.float32)
     st.forward_micro(0, x, y=y, labels=labels, loss_out=loss)
     dx = torch.empty_like(x)
     st.backward([0], dx=dx)
@@ -53,7 +53,7 @@ def test_infinities_and_labels_out_of_range(C):
     def loss_of(bias, label):
         st = Stage([linear(32, C, False), softmax_ce(C)], "bf16", 1, 1, 1, 0.5, 0.0)
         st.set_params([{"w": np.zeros((C, 32), np.float32), "b": bias}, {}])
-        loss = torch.zeros(1, device=st.device)
+        loss = torch.zeros(1, device=st.device, dtype=torch.float32)
         st.forward_micro(0, torch.zeros(1, 32, dtype=torch.bfloat16, device=st.device), labels=torch.tensor([[label]], dtype=torch.int32, device=st.device), loss_out=loss)
         torch.cuda.synchronize()
         return float(loss)

@@ -55,7 +55,7 @@ def test_over_the_input():
     gen = np.random.default_rng(8)
     st = Stage(specs, "f32", micro, 1, 1, 0.1, 0.9, borrow_input=True, device="cuda:0")
     st.set_params(make_params(specs, gen))
-    x = torch.randn(micro, 64, device=st.device)
+    x = torch.randn(micro, 64, device=st.device, dtype=torch.float32)
     ref, both = torch.empty_like(x), x.clone()
     st.forward_micro(0, x, y=ref)
     torch.cuda.synchronize()
