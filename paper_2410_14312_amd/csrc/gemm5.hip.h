@@ -1,49 +1,41 @@
 // MFMA GEMM for gfx950 of 128 x 128 tiles with asynchronous copies: C[m, n] = sum_k A(m, k) * B(n, k), bf16 in, fp32 accumulate,
 // operands described by the loaders of gemm2.hip.h.
 //
-// Eight waves in two groups of four (2 x 2, 64 x 64 each); the groups take the k-tiles in turn and their partial tiles are added
-// through LDS at the end.  k-tiles go from memory to LDS without passing through registers (global_load_lds), the next
-// step's while the current one is multiplied; a step's fragments are read while the step before is multiplied, one LDS read
-// and every other time a copy after each MFMA, so that reading, copying and multiplying overlap.
-// A step of two k-tiles takes 1.03 us (0.56 of them multiplies): it is bound by the copies, 64 KB of which are under way per
-// compute unit.  One workgroup to a unit (128 KB of LDS): for outputs of some 100 to 256 tiles, where the tiled kernel's
-// smaller tiles read each operand more often: 1024 x 3072 x 768 forward 13.9 -> 11.9 us, input gradient 13.7 -> 11.0 us,
-// weight gradient 17.6 -> 14.0 us; 4096 x 768 -> 3072 weight gradient 52 -> 39 us; a stride-2 3 x 3 convolution of 64
+// Eight waves in two groups of four (2 x 2, 64 x 64 each); a k-tile is every wave's, each group multiplies half of it, and the groups'
+// partial tiles are added through LDS at the end.  k-tiles go from memory to LDS without passing through registers
+// (global_load_lds) into five stages: the fragments of the next k-tile are read while one is multiplied, one LDS read after each
+// MFMA, and the copies of the k-tile five ahead go into the stage that this freed, so that a copy has four k-tiles' time to arrive.
+// One workgroup to a unit (160 KB of LDS), for outputs of some 100 to 256 tiles, where the tiled kernel's smaller tiles read each operand more often.
+// What bounds it: 32 KB copied for 0.28 us of multiplies; and of 15 us some 6 are the launch, the first copies and the epilogue.  With two stages of
+// two k-tiles, which left a copy issued last no time at all, 1024 x 3072 x 768 forward took 16.8 us in a transformer's stage (15.6 now), 1024 x 2304 x 768
+// 13.4 (11.9), the input gradient of 12544 x 256 x 256 17.6 (15.3).  Against the tiled kernel, before that: 1024 x 3072 x 768 forward 13.9 -> 11.9 us, input
+// gradient 13.7 -> 11.0 us, weight gradient 17.6 -> 14.0 us; 4096 x 768 -> 3072 weight gradient 52 -> 39 us; a stride-2 3 x 3 convolution of 64
 // images of 28 x 28 x 256 35 -> 26 us.
 #pragma once
 #include "gemm4.hip.h"
 
 namespace tmps {
 
-template <class Op> __device__ __forceinline__ auto op_skip(const Op& op, typename Op::Ctx& c, int) -> decltype(op.skip(c), void()) { op.skip(c); }
-template <class Op> __device__ __forceinline__ void op_skip(const Op&, typename Op::Ctx&, long) {}
-
 // A wave's share of the copies of a 128-row operand tile, and its reads.  LDS: two subtiles of 64 rows, 8 KB in eight 1-KB groups each:
 //   k-contiguous   [64 rows][8 chunks]: position p of row r holds chunk p ^ ((r / 2) % 8): sixteen consecutive rows read at one
 //                  chunk lie in different banks
 //   row-contiguous as in gemm4.hip.h
-template <class Op, int KG> struct Tile128 {
+template <class Op> struct Tile128 {
     static constexpr bool KC = Op::kContig;
     typename Op::KS ks;
-    typename Op::Ctx c[4];
-    // (w: the wave in its group; it copies groups w, w + 4, w + 8 and w + 12 of 16, all even or all odd)
+    typename Op::Ctx c[2];
+    // (wave w of eight copies groups w and w + 8 of 16, both even or both odd)
     __device__ __forceinline__ void init(const Op& op, int row0, int k_begin, int w, int lane) {
         op.init_thread(ks, k_begin, (lane & 7) ^ (lane >> 4) ^ ((w & 1) << 2));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int g = w + 4 * i;
+        for (int i = 0; i < 2; ++i) {
+            const int g = w + 8 * i;
             if constexpr (KC) op.init(c[i], row0 + g * 8 + (lane >> 3), 0, k_begin);
             else op.init(c[i], row0 + (g >> 3) * 64 + ((lane & 7) ^ (((lane >> 4) & 1) << 2)) * 8, (g & 7) * 8 + (lane >> 3), k_begin);
         }
     }
     __device__ __forceinline__ void copy(const Op& op, int i, lds_t tile, int w, int k_end) {
-        copy16_to_lds(op.addr(c[i], ks, k_end), tile + (w + 4 * i) * 1024);
-#pragma unroll
-        for (int k = 1; k < KG; ++k) op_skip(op, c[i], 0);
-    }
-    __device__ __forceinline__ void next(const Op& op) {
-#pragma unroll
-        for (int k = 0; k < KG; ++k) op.next(ks);
+        copy16_to_lds(op.addr(c[i], ks, k_end), tile + (w + 8 * i) * 1024);
     }
     // fragment f (of 4) of rows 32 i .. 32 i + 31 of a subtile
     static __device__ __forceinline__ bf16x8_t read(lds_t tile, int i, int f, int lane) {
@@ -53,12 +45,13 @@ template <class Op, int KG> struct Tile128 {
     }
 };
 
-constexpr int kGemm5Waves = 8, kGemm5Stages = 2, kGemm5Lds = kGemm5Stages * (kGemm5Waves / 4) * 32768;
+constexpr int kGemm5Waves = 8, kGemm5Stages = 5, kGemm5Lds = kGemm5Stages * 32768;
+static_assert(kGemm5Lds >= kGemm5Waves * 64 * 64 * 4, "the partial tiles are added in the stages' place");
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
 __global__ __launch_bounds__(64 * kGemm5Waves, 2) void gemm5_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice, int col_major,
                                                            FastDiv d_plane, FastDiv d_minor) {
-    constexpr int NW = kGemm5Waves, NS = kGemm5Stages, KG = NW / 4, STAGE = KG * 32768;
+    constexpr int NW = kGemm5Waves, NS = kGemm5Stages, KG = NW / 4, STAGE = 32768, NF = 4 / KG;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     const lds_t smem = (lds_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -85,24 +78,26 @@ __global__ __launch_bounds__(64 * kGemm5Waves, 2) void gemm5_kernel(AOp A, BOp B
     op_begin_tile(A, m0, 0);
     op_begin_tile(B, m0, 0);
     const int k_begin = z * k_per_slice, k_end = min(op_k_total(A, K, 0), k_begin + k_per_slice);
-    const int steps = (max(0, (k_end - k_begin + 63) >> 6) + KG - 1) / KG;
+    const int steps = max(0, (k_end - k_begin + 63) >> 6);
 
-    Tile128<AOp, KG> ta;
-    Tile128<BOp, KG> tb;
-    ta.init(A, m0, k_begin + kg * 64, w, lane);
-    tb.init(B, n0, k_begin + kg * 64, w, lane);
-    const lds_t mine = smem + kg * 32768;
-    auto copy = [&](int stage, int i) {   // copy i of 8 of the group's next k-tile (beyond the range: zeros)
-        const lds_t st = mine + stage * STAGE;
-        if (i < 4) ta.copy(A, i, st, w, k_end);
-        else tb.copy(B, i - 4, st + 16384, w, k_end);
+    Tile128<AOp> ta;
+    Tile128<BOp> tb;
+    ta.init(A, m0, k_begin, wave, lane);
+    tb.init(B, n0, k_begin, wave, lane);
+    auto copy = [&](int stage, int i) {   // the wave's copy i of 4 of the next k-tile (beyond the range: zeros)
+        const lds_t st = smem + stage * STAGE;
+        if (i < 2) ta.copy(A, i, st, wave, k_end);
+        else tb.copy(B, i - 2, st + 16384, wave, k_end);
+    };
+    auto next_tile = [&]() {
+        A.next(ta.ks);
+        B.next(tb.ks);
     };
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) copy(s, i);
-        ta.next(A);
-        tb.next(B);
+        for (int i = 0; i < 4; ++i) copy(s, i);
+        next_tile();
     }
     f32x16_t acc[2][2];
 #pragma unroll
@@ -114,20 +109,21 @@ __global__ __launch_bounds__(64 * kGemm5Waves, 2) void gemm5_kernel(AOp A, BOp B
     float rs[2] = {0.0f, 0.0f};
     const bool sum_rows = ROWSUM && tile_x == 0;
 
-    struct Frags { bf16x8_t a[4][2], b[4][2]; };
-    auto read_a = [&](Frags& q, int stage, int f, int i) { q.a[f][i] = Tile128<AOp, KG>::read(mine + stage * STAGE + wm * 8192, i, f, lane); };
-    auto read_b = [&](Frags& q, int stage, int f, int i) { q.b[f][i] = Tile128<BOp, KG>::read(mine + stage * STAGE + 16384 + wn * 8192, i, f, lane); };
-    // One barrier per step, before the reads of the next step's fragments: behind it that step's k-tiles are there (everyone has
-    // waited for its copies) and the stage of the step being multiplied is free (everyone has its fragments in registers).
+    struct Frags { bf16x8_t a[NF][2], b[NF][2]; };   // the group's half of a k-tile: 16 k, 16 of the other's
+    auto read_a = [&](Frags& q, int stage, int f, int i) { q.a[f][i] = Tile128<AOp>::read(smem + stage * STAGE + wm * 8192, i, f * KG + kg, lane); };
+    auto read_b = [&](Frags& q, int stage, int f, int i) { q.b[f][i] = Tile128<BOp>::read(smem + stage * STAGE + 16384 + wn * 8192, i, f * KG + kg, lane); };
+    // One barrier per step, before the reads of the next step's fragments: behind it that step's k-tile is there (everyone has
+    // waited for its copies; those of the NS - 2 k-tiles after it stay under way) and the stage of the step being multiplied is
+    // free (everyone has its fragments in registers).
     int stage = 0;   // of the step being multiplied: refilled meanwhile
     auto one_step = [&](const Frags& cur, Frags& next) {
         const int ahead = stage + 1 == NS ? 0 : stage + 1;
-        wait_vmcnt<(NS - 2) * 8>();
+        wait_vmcnt<(NS - 2) * 4>();
         __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
+        for (int f = 0; f < NF; ++f) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -143,16 +139,15 @@ __global__ __launch_bounds__(64 * kGemm5Waves, 2) void gemm5_kernel(AOp A, BOp B
                 for (int i = 0; i < 2; ++i) rs[i] = add_frag(rs[i], cur.a[f][i]);
             }
         }
-        ta.next(A);
-        tb.next(B);
+        next_tile();
         stage = ahead;
     };
     Frags f0, f1;
-    wait_vmcnt<(NS - 1) * 8>();
+    wait_vmcnt<(NS - 1) * 4>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
+    for (int f = 0; f < NF; ++f)
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             read_a(f0, 0, f, i);
