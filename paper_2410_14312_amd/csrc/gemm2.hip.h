@@ -759,6 +759,39 @@ __device__ __forceinline__ float add_frag(float sum, const bf16x8_t& v) {
 }
 __device__ __forceinline__ float add_frag(float sum, const f32x4v_t& v) { return sum + ((v[0] + v[1]) + (v[2] + v[3])); }
 
+// Workgroups are handed to the 8 XCDs (each with its own L2) round-robin in launch order (x fastest, then y, then
+// z).  Renumber them so that the workgroups of one XCD own a contiguous run of (k-slice, tile) pairs, the tiles of
+// a k-slice next to each other: the tiles of one k-slice read the same k-range of both operands (a split
+// weight gradient: the same positions of dY and of X, nine times over for a 3x3 filter), which then comes in
+// from memory once instead of once per XCD.  Within a k-slice, in row-major order the tiles of a row share their
+// A panel and find it in their own L2, but every XCD fetches all of B; in column-major order (order 1, chosen
+// by the host when B is the larger operand) it is the other way round.
+// Orders 3 and 4: one k-slice whose tiles the XCDs share as a grid of 4 x 2 or 2 x 4 rectangles, so that an XCD fetches a part of either
+// operand: 1024 x 768 x 3072 in tiles of 64 x 64 31 MB for 44, 14.2 -> 13.9 us alone and 26.2 -> 24.0 beside three other stages' kernels.  (The host knows that both sides can be divided so: xcd_order.)
+// d_plane divides by the tiles of a k-slice, d_minor by the tiles along the direction walked first: the host prepares the
+// multipliers, so that the workgroup reaches its first loads without integer divisions.
+__device__ __forceinline__ void xcd_tile(int order, const FastDiv& d_plane, const FastDiv& d_minor, int gx, int gy, int gz, int& tile_x, int& tile_y, int& z) {
+    const int nb = gx * gy, total = nb * gz;
+    const int lin = (z * gy + tile_y) * gx + tile_x;
+    const int xcd = lin & 7, idx = lin >> 3, q = total >> 3, r = total & 7;
+    if (order >= 2) {
+        const int lb = order - 2, w = gx >> lb, y = (int)d_minor.div((uint32_t)idx);
+        tile_y = (xcd >> lb) * (gy >> (3 - lb)) + y;
+        tile_x = (xcd & ((1 << lb) - 1)) * w + idx - y * w;
+        return;
+    }
+    int moved = xcd * q + min(xcd, r) + idx;
+    z = (int)d_plane.div((uint32_t)moved);
+    moved -= z * nb;
+    if (order == 1) {
+        tile_x = (int)d_minor.div((uint32_t)moved);
+        tile_y = moved - tile_x * gy;
+    } else {
+        tile_y = (int)d_minor.div((uint32_t)moved);
+        tile_x = moved - tile_y * gx;
+    }
+}
+
 // LDS bytes of one launch: two buffers of an A tile and a B tile.
 template <int BM, int BN, class AOp, class BOp> constexpr int gemm2_lds_bytes() {
     typedef typename AOp::T T;
@@ -771,7 +804,7 @@ template <int BM, int BN, class AOp, class BOp> constexpr int gemm2_lds_bytes() 
 // a second, nearly empty round.
 // Workgroup (tile_x, tile_y, z) of a gx x gy x gz grid.
 template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
-__device__ __forceinline__ void gemm2_tile(AOp A, BOp B, const Epi& epi, int M, int N, int K, int k_per_slice, int col_major, int wide,
+__device__ __forceinline__ void gemm2_tile(AOp A, BOp B, const Epi& epi, int M, int N, int K, int k_per_slice, int order, int wide,
                                            const FastDiv& d_plane, const FastDiv& d_minor, int tile_x, int tile_y, int z, int gx, int gy, int gz) {
     constexpr bool AKC = AOp::kContig, BKC = BOp::kContig;
     typedef typename AOp::T T;
@@ -785,33 +818,7 @@ __device__ __forceinline__ void gemm2_tile(AOp A, BOp B, const Epi& epi, int M, 
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin in launch order (x fastest, then y, then
-    // z).  Renumber them so that the workgroups of one XCD own a contiguous run of (k-slice, tile) pairs, the tiles of
-    // a k-slice next to each other: the tiles of one k-slice read the same k-range of both operands (a split
-    // weight gradient: the same positions of dY and of X, nine times over for a 3x3 filter), which then comes in
-    // from memory once instead of once per XCD.  Within a k-slice, in row-major order the tiles of a row share their
-    // A panel and find it in their own L2, but every XCD fetches all of B; in column-major order (col_major, chosen
-    // by the host when B is the larger operand) it is the other way round.
-    {
-        const int nb = gx * gy, total = nb * gz;
-        if (total >= 16) {
-            const int lin = (z * gy + tile_y) * gx + tile_x;
-            const int xcd = lin & 7, idx = lin >> 3;
-            const int q = total >> 3, r = total & 7;
-            // (d_plane divides by the tiles of a k-slice, d_minor by the tiles along the direction walked first: the host
-            // prepares the multipliers, so that the workgroup reaches its first loads without integer divisions)
-            int moved = xcd * q + min(xcd, r) + idx;
-            z = (int)d_plane.div((uint32_t)moved);
-            moved -= z * nb;
-            if (col_major) {
-                tile_x = (int)d_minor.div((uint32_t)moved);
-                tile_y = moved - tile_x * gy;
-            } else {
-                tile_y = (int)d_minor.div((uint32_t)moved);
-                tile_x = moved - tile_y * gx;
-            }
-        }
-    }
+    if (gx * gy * gz >= 16) xcd_tile(order, d_plane, d_minor, gx, gy, gz, tile_x, tile_y, z);
     const int m0 = tile_y * BM, n0 = tile_x * BN;
     // (a loader may walk a k range of its own for this tile, and may keep its rows in another order than memory does:
     // the wide epilogue below asks it for the memory row; the host sends such a loader only there)
@@ -1054,8 +1061,8 @@ __device__ __forceinline__ void gemm2_tile(AOp A, BOp B, const Epi& epi, int M, 
 
 template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
 __global__ __launch_bounds__(256, (BM == 64 && BN == 64) ? 3 : 2) void gemm2_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice,
-                                                    int col_major, int wide, FastDiv d_plane, FastDiv d_minor) {
-    gemm2_tile<BM, BN, D, ROWSUM>(A, B, epi, M, N, K, k_per_slice, col_major, wide, d_plane, d_minor, blockIdx.x, blockIdx.y, blockIdx.z,
+                                                    int order, int wide, FastDiv d_plane, FastDiv d_minor) {
+    gemm2_tile<BM, BN, D, ROWSUM>(A, B, epi, M, N, K, k_per_slice, order, wide, d_plane, d_minor, blockIdx.x, blockIdx.y, blockIdx.z,
                                   gridDim.x, gridDim.y, gridDim.z);
 }
 

@@ -67,7 +67,7 @@ template <class Op> struct WaveTile {
 constexpr int kGemm4Stages = 2, kGemm4Lds = 4 * kGemm4Stages * 16384;
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
-__global__ __launch_bounds__(256, 1) void gemm4_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice, int col_major, int wide,
+__global__ __launch_bounds__(256, 1) void gemm4_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice, int order, int wide,
                                                         FastDiv d_plane, FastDiv d_minor) {
     typedef typename AOp::T T;
     typedef typename Frag<T>::type frag_t;
@@ -77,23 +77,8 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(AOp A, BOp B, Epi epi, in
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // (renumbering of the workgroups by XCD: see gemm2_kernel)
     int tile_x = blockIdx.x, tile_y = blockIdx.y, z = blockIdx.z;
-    {
-        const int gx = gridDim.x, gy = gridDim.y, nb = gx * gy, total = nb * gridDim.z;
-        const int lin = (z * gy + tile_y) * gx + tile_x;
-        const int xcd = lin & 7, idx = lin >> 3, q = total >> 3, r = total & 7;
-        int moved = xcd * q + min(xcd, r) + idx;
-        z = (int)d_plane.div((uint32_t)moved);
-        moved -= z * nb;
-        if (col_major) {
-            tile_x = (int)d_minor.div((uint32_t)moved);
-            tile_y = moved - tile_x * gy;
-        } else {
-            tile_y = (int)d_minor.div((uint32_t)moved);
-            tile_x = moved - tile_y * gx;
-        }
-    }
+    xcd_tile(order, d_plane, d_minor, gridDim.x, gridDim.y, gridDim.z, tile_x, tile_y, z);
     const int m0 = tile_y * 64, n0 = tile_x * 64;
     op_begin_tile(A, m0, 0);
     op_begin_tile(B, m0, 0);

@@ -49,7 +49,7 @@ constexpr int kGemm5Waves = 8, kGemm5Stages = 5, kGemm5Lds = kGemm5Stages * 3276
 static_assert(kGemm5Lds >= kGemm5Waves * 64 * 64 * 4, "the partial tiles are added in the stages' place");
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
-__global__ __launch_bounds__(64 * kGemm5Waves, 2) void gemm5_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice, int col_major,
+__global__ __launch_bounds__(64 * kGemm5Waves, 2) void gemm5_kernel(AOp A, BOp B, Epi epi, int M, int N, int K, int k_per_slice, int order,
                                                            FastDiv d_plane, FastDiv d_minor) {
     constexpr int NW = kGemm5Waves, NS = kGemm5Stages, KG = NW / 4, STAGE = 32768, NF = 4 / KG;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -57,23 +57,8 @@ __global__ __launch_bounds__(64 * kGemm5Waves, 2) void gemm5_kernel(AOp A, BOp B
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave >> 2, w = wave & 3, wm = w >> 1, wn = w & 1;
 
-    // (renumbering of the workgroups by XCD: see gemm2_kernel)
     int tile_x = blockIdx.x, tile_y = blockIdx.y, z = blockIdx.z;
-    {
-        const int gx = gridDim.x, gy = gridDim.y, nb = gx * gy, total = nb * gridDim.z;
-        const int lin = (z * gy + tile_y) * gx + tile_x;
-        const int xcd = lin & 7, idx = lin >> 3, q = total >> 3, r = total & 7;
-        int moved = xcd * q + min(xcd, r) + idx;
-        z = (int)d_plane.div((uint32_t)moved);
-        moved -= z * nb;
-        if (col_major) {
-            tile_x = (int)d_minor.div((uint32_t)moved);
-            tile_y = moved - tile_x * gy;
-        } else {
-            tile_y = (int)d_minor.div((uint32_t)moved);
-            tile_x = moved - tile_y * gx;
-        }
-    }
+    xcd_tile(order, d_plane, d_minor, gridDim.x, gridDim.y, gridDim.z, tile_x, tile_y, z);
     const int m0 = tile_y * 128, n0 = tile_x * 128;
     op_begin_tile(A, m0, 0);
     op_begin_tile(B, m0, 0);

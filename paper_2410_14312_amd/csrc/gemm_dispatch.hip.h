@@ -48,7 +48,41 @@ static void slice_geometry(int64_t K, int want, int ktile, int& per, int& nz) {
 }
 
 
+// (gathering loaders put a chunk together from eight or four loads: one small tile, a short ring)
+template <class Op> struct IsGather { static constexpr bool value = false; };
+template <class T, bool KC, class View> struct IsGather<Gather<T, KC, View>> { static constexpr bool value = true; };
+
+// how the k-sharing kernel can take a pair of loaders (it needs a chunk's address)
+template <class Op> struct IsMatrix { static constexpr bool value = false; };
+template <class T> struct IsMatrix<DenseKC<T>> { static constexpr bool value = true; };
+template <class T> struct IsMatrix<DenseRC<T>> { static constexpr bool value = true; };
+template <class T> struct IsMatrix<StridedKC<T>> { static constexpr bool value = true; };
+template <class Op> constexpr bool has_addr() { return !IsGather<Op>::value && !Op::kSettle; }
+template <class AOp, class BOp> constexpr int by_k_mode() {
+    return !has_addr<AOp>() || !has_addr<BOp>() ? kByKNo : IsMatrix<AOp>::value && IsMatrix<BOp>::value ? kByKDense : kByKConv;
+}
+
 // ---- launches -------------------------------------------------------------------------------------
+// How the XCDs share the tiles of a launch (xcd_tile) and what its d_minor divides by.  Strips: the XCDs split the operand with more rows between
+// them and each reads the other one whole.  Rectangles where tiles divide evenly and an XCD's share of both operands has fewer rows than that (matrices only:
+// rows of a convolution's operand overlap in memory).
+struct XcdOrder {
+    int order, minor;
+};
+static XcdOrder xcd_order(int gx, int gy, int nz, int64_t M, int64_t N, bool matrices) {
+    XcdOrder o = N > M ? XcdOrder{1, gy} : XcdOrder{0, gx};
+    if (!matrices || nz != 1) return o;
+    int64_t best = N > M ? M + N / 8 : N + M / 8;
+    for (int lb = 1; lb <= 2; ++lb) {
+        const int64_t rows = M / (8 >> lb) + N / (1 << lb);
+        if (gx % (1 << lb) == 0 && gy % (8 >> lb) == 0 && rows < best) {
+            best = rows;
+            o = XcdOrder{2 + lb, gx >> lb};
+        }
+    }
+    return o;
+}
+
 template <int BM, int BN, int D, bool ROWSUM, class AOp, class BOp, class Epi>
 static hipError_t launch2_inst(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per,
                                int nz, hipStream_t s) {
@@ -61,15 +95,11 @@ static hipError_t launch2_inst(int kc, const AOp& A, const BOp& B, const Epi& ep
         if (attr != hipSuccess) return attr;
     }
     dim3 grid(cdiv(N, BN), cdiv(M, BM), nz);
-    // the XCDs split the operand with more rows between them and each reads the other one whole
-    const int col_major = N > M ? 1 : 0;
-    return launch_timed(kc, kern, grid, dim3(256), lds, s, A, B, epi, M, N, K, per, col_major,
-                        (N % 8 == 0 && epi.wide_ok()) ? 1 : 0, FastDiv(grid.x * grid.y), FastDiv(col_major ? grid.y : grid.x));
+    const XcdOrder o = xcd_order(grid.x, grid.y, nz, M, N, by_k_mode<AOp, BOp>() == kByKDense);
+    return launch_timed(kc, kern, grid, dim3(256), lds, s, A, B, epi, M, N, K, per, o.order,
+                        (N % 8 == 0 && epi.wide_ok()) ? 1 : 0, FastDiv(grid.x * grid.y), FastDiv(o.minor));
 }
 
-// (gathering loaders put a chunk together from eight or four loads: one small tile, a short ring)
-template <class Op> struct IsGather { static constexpr bool value = false; };
-template <class T, bool KC, class View> struct IsGather<Gather<T, KC, View>> { static constexpr bool value = true; };
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
 static hipError_t launch4(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
@@ -77,20 +107,11 @@ static hipError_t launch4(int kc, const AOp& A, const BOp& B, const Epi& epi, in
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kGemm4Lds);
     if (attr != hipSuccess) return attr;
     dim3 grid(cdiv(N, 64), cdiv(M, 64), nz);
-    const int col_major = N > M ? 1 : 0;
-    return launch_timed(kc, kern, grid, dim3(256), kGemm4Lds, s, A, B, epi, M, N, K, per, col_major, (N % 8 == 0 && epi.wide_ok()) ? 1 : 0,
-                        FastDiv(grid.x * grid.y), FastDiv(col_major ? grid.y : grid.x));
+    const XcdOrder o = xcd_order(grid.x, grid.y, nz, M, N, by_k_mode<AOp, BOp>() == kByKDense);
+    return launch_timed(kc, kern, grid, dim3(256), kGemm4Lds, s, A, B, epi, M, N, K, per, o.order, (N % 8 == 0 && epi.wide_ok()) ? 1 : 0,
+                        FastDiv(grid.x * grid.y), FastDiv(o.minor));
 }
 
-// how the k-sharing kernel can take a pair of loaders (it needs a chunk's address)
-template <class Op> struct IsMatrix { static constexpr bool value = false; };
-template <class T> struct IsMatrix<DenseKC<T>> { static constexpr bool value = true; };
-template <class T> struct IsMatrix<DenseRC<T>> { static constexpr bool value = true; };
-template <class T> struct IsMatrix<StridedKC<T>> { static constexpr bool value = true; };
-template <class Op> constexpr bool has_addr() { return !IsGather<Op>::value && !Op::kSettle; }
-template <class AOp, class BOp> constexpr int by_k_mode() {
-    return !has_addr<AOp>() || !has_addr<BOp>() ? kByKNo : IsMatrix<AOp>::value && IsMatrix<BOp>::value ? kByKDense : kByKConv;
-}
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
 static hipError_t launch5(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
@@ -99,8 +120,8 @@ static hipError_t launch5(int kc, const AOp& A, const BOp& B, const Epi& epi, in
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     dim3 grid(cdiv(N, 128), cdiv(M, 128), nz);
-    const int col_major = N > M ? 1 : 0;
-    return launch_timed(kc, kern, grid, dim3(64 * kGemm5Waves), lds, s, A, B, epi, M, N, K, per, col_major, FastDiv(grid.x * grid.y), FastDiv(col_major ? grid.y : grid.x));
+    const XcdOrder o = xcd_order(grid.x, grid.y, nz, M, N, by_k_mode<AOp, BOp>() == kByKDense);
+    return launch_timed(kc, kern, grid, dim3(64 * kGemm5Waves), lds, s, A, B, epi, M, N, K, per, o.order, FastDiv(grid.x * grid.y), FastDiv(o.minor));
 }
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
