@@ -10,7 +10,7 @@ CASES = [   # rows, din, dout, kernel of the forward pass
     (1000, 3080, 512, "by_k"), (500, 3080, 760, "by_k"), (512, 3080, 776, "by_k"),
     (1000, 776, 512, "tiled"), (500, 776, 760, "tiled"), (1000, 72, 2000, "tiled"), (1030, 776, 256, "tiled"),
     (1000, 776, 3072, "async"), (1030, 776, 2000, "async"),
-    (896, 512, 4096, "async"), (1152, 576, 2560, "async"), (1024, 640, 3072, "async"), (896, 696, 2560, "async"),   # 8, 9, 10 and 11 k-tiles
+    (896, 512, 4096, "async"), (1024, 640, 3072, "async"), (896, 696, 2560, "async"), (1024, 768, 2560, "async"), (1024, 840, 3072, "async"),   # 8, 10, 11, 12, 14 k-tiles: every remainder
 ]
 
 
