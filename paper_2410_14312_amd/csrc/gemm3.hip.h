@@ -683,8 +683,8 @@ struct G3Group {
             g.k0 = g.z * k_per_slice;
             k1 = min(k_total, g.k0 + k_per_slice);
         }
-        g.nk = (k1 - g.k0 + 63) >> 6;
-        g.last = k1 - g.k0 - (g.nk - 1) * 64;
+        g.nk = (k1 - g.k0) >> 6;
+        g.last = 64;
         g.job = place(t, g.m0, g.n0);
         g.first_col = g.n0 == 0;
         g.part_tile = t - whole;
@@ -702,12 +702,19 @@ struct G3Group {
         return EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kCols, first + kRows * kCols - g.m0, 0};
     }
 };
-// Over rows that are no multiple of 64: the last k-tile of the last slice is short.  An instance of its own, so that its tests are paid only where rows
-// need them.  In launches of their own such gradients ran on 64 x 64 tiles: eight of a stage with two blocks of 512
+// Over rows that are no multiple of 64: the last k-tile of the last slice is short.  An instance and a way to a unit of its own, so that its tests are paid only where rows
+// need them (with a short last k-tile in the common unit() the whole rows' instance took 447 us for three GPT-2 blocks, 437 without).  In launches of their own such gradients ran on 64 x 64 tiles: eight of a stage with two blocks of 512
 // features over 3996 rows 156 us, the stage 1127 us and 1087 with one launch; four blocks of 768 over two stages with 1266 rows, two mini-batches, 2570 and
 // 2399; four blocks of 640 in 1F1B order, 1564 rows a pass, 9 % of a run; one mini-batch of three blocks of 768 over 524 rows 1.5 %.
 struct G3GroupRagged : G3Group {
     static constexpr bool kRagged = true;
+    __device__ __forceinline__ G3Unit unit(int u) const {
+        G3Unit g = G3Group::unit(u);
+        const int k = (g.z < 0 ? k_total : min(k_total, g.k0 + k_per_slice)) - g.k0;
+        g.nk = (k + 63) >> 6;
+        g.last = k - (g.nk - 1) * 64;
+        return g;
+    }
 };
 
 }  // namespace tmps
