@@ -68,9 +68,16 @@ static bool on16(std::initializer_list<const void*> all) {
     return (bits & 15) == 0;
 }
 
-// whether layer i is an affine layer behind a 1 x 1 convolution of unit stride
+// Whether layer i is an affine layer over the channels of the convolution that it reads.  (Layers that follow each other agree in the number of their values
+// only: one may read a result as a map of other channels, and is then a launch of its own.)
+static bool affine_of_conv(const tmps_stage& st, int i) {
+    return i >= 1 && st.layers[i].d.kind == TMPS_AFFINE && st.layers[i].in_t == i - 1 && st.layers[i - 1].d.kind == TMPS_CONV2D &&
+           st.layers[i].d.dims[2] == st.layers[i - 1].d.dims[3];
+}
+
+// ... and that convolution is 1 x 1 with unit stride
 static bool pointwise_below(const tmps_stage& st, int i) {
-    if (i < 1 || st.layers[i].d.kind != TMPS_AFFINE || st.layers[i].in_t != i - 1 || st.layers[i - 1].d.kind != TMPS_CONV2D) return false;
+    if (!affine_of_conv(st, i)) return false;
     const int32_t* c = st.layers[i - 1].d.dims;
     return c[4] == 1 && c[5] == 1 && c[6] == 1 && c[7] == 0;
 }
@@ -622,10 +629,10 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
                 break;
             }
             case TMPS_CONV2D: {
-                // A convolution without activation whose only reader is a per-channel affine layer runs fused with
+                // A convolution without activation whose only reader is an affine layer over its channels runs fused with
                 // it, and with the residual join after the affine layer when that follows directly.
                 const size_t nl = st->layers.size();
-                if (L.act == 0 && li + 1 < nl && st->layers[li + 1].d.kind == TMPS_AFFINE && st->readers[li + 1] == 1) {
+                if (L.act == 0 && li + 1 < nl && affine_of_conv(*st, (int)li + 1) && st->readers[li + 1] == 1) {
                     const LayerRT& A = st->layers[li + 1];
                     const bool join = !A.relu && li + 2 < nl && st->layers[li + 2].d.kind == TMPS_RESADD &&
                                       st->readers[li + 2] == 1;

@@ -10,37 +10,126 @@
 
 KernelStubs kernel_stubs;
 
+// A launch under `joint`: its arrays, read or written whole (null: not given).
+static volatile unsigned char sink;
+struct Launch {
+    const char* name;
+    const bool on;
+    explicit Launch(const char* n) : name(n), on(kernel_stubs.joint) {
+        if (!on) return;
+        std::lock_guard<std::mutex> lock(kernel_stubs.m);
+        ++kernel_stubs.launches[n];
+    }
+    void keep(const void* p, size_t bytes, bool write) const {
+        std::lock_guard<std::mutex> lock(kernel_stubs.m);
+        kernel_stubs.touched.push_back({name, p, bytes, write});
+    }
+    const Launch& reads(const void* p, size_t bytes) const {
+        if (!on || !p) return *this;
+        unsigned char sum = 0;
+        for (size_t i = 0; i < bytes; ++i) sum += static_cast<const unsigned char*>(p)[i];
+        sink = sum;
+        keep(p, bytes, false);
+        return *this;
+    }
+    const Launch& writes(void* p, size_t bytes) const {
+        if (!on || !p) return *this;
+        memset(p, 1, bytes);
+        keep(p, bytes, true);
+        return *this;
+    }
+};
+
 namespace tmps {
+static size_t esize(int dtype) { return dtype == kBF16 ? 2 : 4; }
+size_t affine_workspace_elems(int64_t, int C) { return (size_t)(2 * C * 8); }
+
 hipError_t dense_forward(int dtype, const void* x, const void* w, const float* bias, void* y, int B, int Din, int Dout, int act, int out_f32, const void* res, void* zout, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t dense_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, int mask_mode, const void* add, int B, int Din, int Dout, float* ws, hipStream_t s) { return hipSuccess; }
 hipError_t dense_wgrad(int dtype, const void* dy, const void* x, float* gw, int B, int Din, int Dout, const Partials& ws, hipStream_t s) { return hipSuccess; }
-hipError_t reduce_all(const Reductions&, hipStream_t) { return hipSuccess; }
+hipError_t reduce_all(const Reductions& list, hipStream_t) {
+    for (const Reduction& r : list) Launch("reduce").reads(r.part, (size_t)r.slices * r.count * 4).writes(r.out, (size_t)r.count * 4);
+    return hipSuccess;
+}
 hipError_t dense_backward(int, const void*, const void*, const void*, float*, void*, const void*, int, const void*, int, int, int, float*, const Partials&, hipStream_t) { return hipSuccess; }
 bool dense_wgrad_groups(int, int64_t, int, int) { return true; }
 int64_t dense_wgrad_group_elems(int64_t, const int (*)[2], int n) { return n > 1 ? 1000 : -1; }
 hipError_t dense_wgrad_group(int, const DenseWgradJob*, int, int64_t, float*, int64_t, hipStream_t) { return hipSuccess; }
-bool norm_dense_takes(int, int64_t, int, int) { return false; }
-hipError_t norm_dense_forward(int, const void*, const float*, const float*, void*, float*, float, const void*, const float*, void*, int, int, int, int, int, const void*, void*, hipStream_t) { return hipSuccess; }
+bool norm_dense_takes(int, int64_t, int, int) { return kernel_stubs.joint; }
+hipError_t norm_dense_forward(int dtype, const void* x, const float* gamma, const float* beta, void* y, float* stats, float, const void* w, const float* bias, void* out, int rows, int D, int Dout, int, int out_f32, const void* res, void* zout, hipStream_t) {
+    const size_t e = esize(dtype), in = (size_t)rows * D * e, eo = out_f32 ? 4 : e, to = (size_t)rows * Dout * eo;
+    Launch("norm_dense_forward").reads(x, in).reads(gamma, D * 4).reads(beta, D * 4).writes(y, in).writes(stats, (size_t)rows * 8).reads(w, (size_t)D * Dout * e)
+        .reads(bias, (size_t)Dout * 4).reads(res, to).writes(out, to).writes(zout, to);
+    return hipSuccess;
+}
 hipError_t conv_forward(int dtype, const void* x, const void* w, const float* bias, void* y, const ConvShape& c, int relu, float* ws, hipStream_t s) {
     std::lock_guard<std::mutex> lock(kernel_stubs.m);
     kernel_stubs.conv_samples.push_back(c.B);
     return hipSuccess;
 }
-hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain, const float* shift, void* aout, const void* res, void* yout, int relu, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
-hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add, const ConvShape& c, float* ws, hipStream_t s) { return hipSuccess; }
-hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) { return hipSuccess; }
-bool pointwise_forward_takes(int64_t, int, int) { return false; }
-hipError_t pointwise_forward(const PointwiseForward&, const PointwiseForward*, int64_t, hipStream_t) { return hipSuccess; }
-bool affine_pointwise_takes(int, int64_t, int, int) { return false; }
-int affine_pointwise_slabs(int64_t, int, int) { return 1; }
-hipError_t affine_pointwise_backward(const void*, const void*, const void*, const void*, const float*, const void*, int, void*, float*, float*, const Partials&, const Partials&, int64_t, int, int, hipStream_t) { return hipSuccess; }
+hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const float* bias, void* z, const float* gain, const float* shift, void* again, const void* res, void* yout, int relu, const ConvShape& c, float* ws, hipStream_t s) {
+    const size_t e = esize(dtype), in = (size_t)c.B * c.H * c.W * c.Cin * e, out = (size_t)c.B * c.Ho * c.Wo * c.Cout * e, ch = (size_t)c.Cout * 4;
+    Launch("conv_affine_forward").reads(x, in).reads(w, (size_t)c.Cout * c.R * c.S * c.Cin * e).reads(bias, ch).reads(gain, ch).reads(shift, ch).reads(res, out)
+        .writes(z, out).writes(yout, out).writes(again, out);
+    return hipSuccess;
+}
+hipError_t conv_dgrad(int dtype, const void* dy, const void* w, void* dx, const void* mask, const void* add, const ConvShape& c, float* ws, hipStream_t s) {
+    const size_t e = esize(dtype), in = (size_t)c.B * c.H * c.W * c.Cin * e;
+    Launch("conv_dgrad").reads(dy, (size_t)c.B * c.Ho * c.Wo * c.Cout * e).reads(w, (size_t)c.Cout * c.R * c.S * c.Cin * e).reads(mask, in).reads(add, in).writes(dx, in);
+    return hipSuccess;
+}
+hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const ConvShape& c, const Partials& ws, hipStream_t s) {
+    const size_t e = esize(dtype), count = (size_t)c.Cout * (c.R * c.S * c.Cin + 1);
+    Launch("conv_wgrad").reads(dy, (size_t)c.B * c.Ho * c.Wo * c.Cout * e).reads(x, (size_t)c.B * c.H * c.W * c.Cin * e).writes(ws.ws, 2 * count * 4);
+    return ws.finish(Reduction{ws.ws, gw, (int64_t)count, 2, false}, s);
+}
+bool pointwise_forward_takes(int64_t, int Cin, int Cout) { return kernel_stubs.joint && Cout == 4 * Cin; }
+hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, hipStream_t) {
+    const size_t c = 64, w = 256, narrow = (size_t)P * c * 2, wide = (size_t)P * w * 2;   // (the kernel's widths)
+    const Launch l(next ? "pointwise_forward of two" : "pointwise_forward");
+    l.reads(f.x, narrow).reads(f.w, w * c * 2).reads(f.bias, w * 4).reads(f.gain, w * 4).reads(f.shift, w * 4).reads(f.res, wide).writes(f.z, wide).writes(f.y, wide)
+        .writes(f.again, wide);
+    if (next) l.reads(next->w, w * c * 2).reads(next->bias, c * 4).reads(next->gain, c * 4).reads(next->shift, c * 4).writes(next->z, narrow).writes(next->y, narrow);
+    return hipSuccess;
+}
+bool affine_pointwise_takes(int dtype, int64_t, int, int) { return kernel_stubs.joint && dtype == kBF16; }
+int affine_pointwise_slabs(int64_t, int, int) { return 3; }
+hipError_t affine_pointwise_backward(const void* dy, const void* z, const void* x, const void* w, const float* gain, const void* add, int, void* dx, float* gw_affine, float* gw_conv, const Partials& pa, const Partials& pw, int64_t P, int O, int I, hipStream_t s) {
+    const size_t out = (size_t)P * O * 2, in = (size_t)P * I * 2, slabs = affine_pointwise_slabs(P, O, I);
+    Launch("affine_pointwise_backward").reads(dy, out).reads(z, out).reads(x, in).reads(w, (size_t)O * I * 2).reads(gain, (size_t)O * 4).reads(add, in).writes(dx, in)
+        .writes(pa.ws, slabs * 2 * O * 4).writes(pw.ws, slabs * ((size_t)O * I + O) * 4);
+    const hipError_t e = pa.finish(Reduction{pa.ws, gw_affine, 2 * O, (int)slabs, true}, s);
+    return e != hipSuccess ? e : pw.finish(Reduction{pw.ws, gw_conv, (int64_t)O * I + O, (int)slabs, false}, s);
+}
 bool maxpool_keeps_winners(int k) { return k <= 11; }
-bool maxpool_affine_takes(int, int64_t, int, int, int) { return false; }
-hipError_t maxpool_affine_backward(int, const void*, const uint8_t*, const void*, const float*, void*, float*, const Partials&, int, int, int, int, int, int, int, int, hipStream_t) { return hipSuccess; }
-hipError_t maxpool_forward(int dtype, const void* x, void* y, uint8_t* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) { return hipSuccess; }
-hipError_t maxpool_backward(int dtype, const void* x, const void* dy, const uint8_t* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) { return hipSuccess; }
-hipError_t affine_forward(int dtype, const void* x, const float* gain, const float* shift, void* y, int64_t rows, int C, int relu, hipStream_t s) { return hipSuccess; }
-hipError_t affine_backward(int dtype, const void* dy, const void* x, const float* gain, void* dx, float* dgain_dshift, const Partials& ws, int64_t rows, int C, hipStream_t s) { return hipSuccess; }
+bool maxpool_affine_takes(int, int64_t, int, int, int) { return kernel_stubs.joint; }
+static size_t pooled(int B, int H, int W, int C, int k, int stride, int pad) { return (size_t)B * ((H + 2 * pad - k) / stride + 1) * ((W + 2 * pad - k) / stride + 1) * C; }
+hipError_t maxpool_affine_backward(int dtype, const void* dy, const uint8_t* won, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& ws, int B, int H, int W, int C, int k, int stride, int pad, int, hipStream_t s) {
+    const size_t e = esize(dtype), in = (size_t)B * H * W * C * e, out = pooled(B, H, W, C, k, stride, pad);
+    const int slabs = (int)(affine_workspace_elems((int64_t)B * H * W, C) / (2 * C));
+    Launch("maxpool_affine_backward").reads(dy, out * e).reads(won, out).reads(z, in).reads(gain, (size_t)C * 4).writes(dz, in).writes(ws.ws, (size_t)slabs * 2 * C * 4);
+    return ws.finish(Reduction{ws.ws, dgain_dshift, 2 * C, slabs, true}, s);
+}
+hipError_t maxpool_forward(int dtype, const void* x, void* y, uint8_t* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) {
+    const size_t e = esize(dtype), out = pooled(B, H, W, C, k, stride, pad);
+    Launch("maxpool_forward").reads(x, (size_t)B * H * W * C * e).writes(y, out * e).writes(won, out);
+    return hipSuccess;
+}
+hipError_t maxpool_backward(int dtype, const void* x, const void* dy, const uint8_t* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) {
+    const size_t e = esize(dtype), out = pooled(B, H, W, C, k, stride, pad);
+    Launch("maxpool_backward").reads(dy, out * e).reads(won, out).writes(dx, (size_t)B * H * W * C * e);
+    return hipSuccess;
+}
+hipError_t affine_forward(int dtype, const void* x, const float* gain, const float* shift, void* y, int64_t rows, int C, int relu, hipStream_t s) {
+    const size_t n = (size_t)rows * C * esize(dtype), ch = (size_t)C * 4;
+    Launch("affine_forward").reads(x, n).reads(gain, ch).reads(shift, ch).writes(y, n);
+    return hipSuccess;
+}
+hipError_t affine_backward(int dtype, const void* dy, const void* x, const float* gain, void* dx, float* dgain_dshift, const Partials& ws, int64_t rows, int C, hipStream_t s) {
+    const size_t n = (size_t)rows * C * esize(dtype), slabs = affine_workspace_elems(rows, C) / (2 * C);
+    Launch("affine_backward").reads(dy, n).reads(x, n).reads(gain, (size_t)C * 4).writes(dx, n).writes(ws.ws, slabs * 2 * C * 4);
+    return ws.finish(Reduction{ws.ws, dgain_dshift, 2 * C, (int)slabs, true}, s);
+}
 hipError_t resadd_forward(int dtype, const void* a, const void* b, void* y, int64_t n, int relu, hipStream_t s) { return hipSuccess; }
 hipError_t avgpool_forward(int dtype, const void* x, void* y, int B, int HW, int C, hipStream_t s) { return hipSuccess; }
 hipError_t avgpool_backward(int dtype, const void* dy, const void* x, void* dx, int B, int HW, int C, int relu_mask, hipStream_t s) { return hipSuccess; }
@@ -69,7 +158,6 @@ hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t) { m
 GemmPlan plan_gemm(int64_t, int64_t, int64_t) { return GemmPlan{64, 1}; }
 size_t conv_wgrad_workspace_elems(int, const ConvShape& c) { return (size_t)(2 * ((int64_t)c.Cout * c.R * c.S * c.Cin + c.Cout)); }
 size_t gemm_workspace_elems(int64_t M, int64_t N, int64_t, int with_rowsum) { return (size_t)(2 * (M * N + (with_rowsum ? M : 0))); }
-size_t affine_workspace_elems(int64_t, int C) { return (size_t)(2 * C * 8); }
 size_t layernorm_workspace_elems(int64_t, int D) { return (size_t)(2 * D * 8); }
 size_t attention_workspace_elems(int B, int S, int H) { return (size_t)B * S * H; }
 }  // namespace tmps
