@@ -106,6 +106,18 @@ int main() {
     run("gradients of conv and affine of fewer channels", pointwise(L(TMPS_AFFINE, {8, 8, 8}, R)), bf16, "affine_pointwise_backward", 0);
     run("gradients of conv and affine of more channels", pointwise(L(TMPS_AFFINE, {2, 2, 128}, R)), bf16, "affine_pointwise_backward", 0);
 
+    // a join and the next block's first convolution
+    auto blocks = [&](tmps_layer_desc conv, tmps_layer_desc aff, tmps_layer_desc last) {
+        return std::vector<tmps_layer_desc>{L(TMPS_CONV2D, {4, 4, 8, 256, 1, 1, 1, 0}, R), L(TMPS_CONV2D, {4, 4, 256, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {4, 4, 64}, R),
+                                            L(TMPS_CONV2D, {4, 4, 64, 256, 1, 1, 1, 0}), L(TMPS_AFFINE, {4, 4, 256}), L(TMPS_RESADD, {4, 4, 256, 5}, R), conv, aff, last};
+    };
+    const auto pair = "pointwise_forward of two";
+    run("join and convolution", blocks(L(TMPS_CONV2D, {4, 4, 256, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {4, 4, 64}, R), L(TMPS_CONV2D, {4, 4, 64, 8, 1, 1, 1, 0})), bf16, pair, 4);
+    run("join and convolution that reads other channels", blocks(L(TMPS_CONV2D, {8, 8, 64, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {8, 8, 64}, R), L(TMPS_CONV2D, {8, 8, 64, 8, 1, 1, 1, 0})),
+        bf16, pair, 0);
+    run("join, convolution and affine of other channels", blocks(L(TMPS_CONV2D, {4, 4, 256, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {8, 8, 16}, R), L(TMPS_CONV2D, {8, 8, 16, 8, 1, 1, 1, 0})),
+        bf16, pair, 0);
+
     // a layer normalisation and the dense layer behind it
     for (int dtype : {(int)TMPS_F32, bf16})
         run("norm and dense", {L(TMPS_LAYERNORM, {16, 3}), L(TMPS_LINEAR, {16, 24, 0, 3}, TMPS_FLAG_GELU), L(TMPS_LINEAR, {24, 16, 2, 3}), L(TMPS_LAYERNORM, {16, 3}),

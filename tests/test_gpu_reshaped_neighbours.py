@@ -3,7 +3,7 @@ with the one that forms it: against the oracle, which runs them one by one."""
 import pytest
 
 from tests.test_gpu_stage import run_stage_case
-from workloads.configs import affine, conv, linear
+from workloads.configs import affine, bottleneck, conv, linear
 
 pytestmark = pytest.mark.gpu
 
@@ -18,3 +18,16 @@ def test_affine_behind_a_convolution(dtype, r, h, cout, c):
     if side * side * c != h * h * cout:   # (a map that is no square)
         specs[2] = affine(h * h * cout // c // h, h, c, True)
     run_stage_case(specs, dtype, 2, 2, seed=h + c + r)
+
+
+@pytest.mark.parametrize("h,cin,first,second", [(64, 256, 64, 64), (32, 64, 64, 64), (64, 64, 64, 16), (64, 128, 64, 64)])
+def test_convolution_behind_a_join(h, cin, first, second):
+    """The next block's first convolution leaves the join's launch (64 x 64 positions from 64 channels to 256) where it reads the join's 256 channels; the others
+    here read it as maps of 64 and 128, one of them 64 x 64 again."""
+    side = {(64, 256): (64, 64), (32, 64): (64, 64), (64, 64): (128, 128), (64, 128): (64, 128)}[h, cin]
+    block, _, _ = bottleneck(h, 64, 64, 1, True)
+    conv_ = conv(h, h, cin, first, 1, 1, 0, False)
+    conv_.update(h=side[0], w=side[1])
+    n = side[0] * side[1] * first // second
+    run_stage_case([conv(h, h, 8, 64, 3, 1, 1, True)] + block + [conv_, affine(side[0], n // side[0], second, True), conv(side[0], n // side[0], second, 8, 1, 1, 0, False)],
+                   "bf16", 4 if h == 32 else 1, 2, seed=h + cin + second, deep=True)
