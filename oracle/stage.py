@@ -73,7 +73,7 @@ class Stage:
                 a, c = L.conv_forward(a, q(p["w"]), p["b"], spec["stride"], spec["pad"], spec["relu"])
                 a = c["y"] = q(a)
             elif k == "maxpool":
-                a, c = L.maxpool_forward(a, spec["k"], spec["stride"], spec.get("pad", 0))
+                a, c = L.maxpool_forward(a.reshape(a.shape[0], spec["h"], spec["w"], spec["c"]), spec["k"], spec["stride"], spec.get("pad", 0))
             elif k == "affine":
                 a, c = L.affine_forward(a.reshape(a.shape[0], spec["h"], spec["w"], spec["c"]), p["w"], p["b"], spec["relu"])
                 a = c["y"] = q(a)

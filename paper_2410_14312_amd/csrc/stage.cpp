@@ -1016,7 +1016,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
             }
             case TMPS_MAXPOOL: {
                 const uint8_t* won = winners(st, L, row0);
-                const LayerRT* A = t_in >= 0 && st->layers[t_in].d.kind == TMPS_AFFINE ? &st->layers[t_in] : nullptr;
+                const LayerRT* A = t_in >= 0 && st->layers[t_in].d.kind == TMPS_AFFINE && st->layers[t_in].d.dims[2] == d[2] ? &st->layers[t_in] : nullptr;
                 const int64_t rows = (int64_t)M * d[0] * d[1];
                 if (A && won && st->readers[t_in + 1] == 1 && !in_order && maxpool_affine_takes(dt, rows, d[2], d[3], d[4])) {
                     if ((rc = target(A->in_t, T)) != TMPS_OK) return rc;

@@ -118,6 +118,16 @@ int main() {
     run("join, convolution and affine of other channels", blocks(L(TMPS_CONV2D, {4, 4, 256, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {8, 8, 16}, R), L(TMPS_CONV2D, {8, 8, 16, 8, 1, 1, 1, 0})),
         bf16, pair, 0);
 
+    // max pooling behind an affine layer
+    auto pooled = [&](tmps_layer_desc pool, int n) {
+        return std::vector<tmps_layer_desc>{L(TMPS_CONV2D, {8, 8, 8, 16, 3, 3, 1, 1}), L(TMPS_AFFINE, {8, 8, 16}, R), pool, L(TMPS_LINEAR, {n, 8, 0, 1})};
+    };
+    for (int dtype : {(int)TMPS_F32, bf16}) {
+        run("pooling and affine", pooled(L(TMPS_MAXPOOL, {8, 8, 16, 3, 2, 1}), 4 * 4 * 16), dtype, "maxpool_affine_backward", 2);
+        run("pooling and affine on another map", pooled(L(TMPS_MAXPOOL, {16, 4, 16, 3, 2, 1}), 8 * 2 * 16), dtype, "maxpool_affine_backward", 2);
+        run("pooling and affine of fewer channels", pooled(L(TMPS_MAXPOOL, {4, 4, 64, 3, 2, 1}), 2 * 2 * 64), dtype, "maxpool_affine_backward", 0);
+        run("pooling and affine of more channels", pooled(L(TMPS_MAXPOOL, {16, 16, 4, 3, 2, 1}), 8 * 8 * 4), dtype, "maxpool_affine_backward", 0);
+    }
     // a layer normalisation and the dense layer behind it
     for (int dtype : {(int)TMPS_F32, bf16})
         run("norm and dense", {L(TMPS_LAYERNORM, {16, 3}), L(TMPS_LINEAR, {16, 24, 0, 3}, TMPS_FLAG_GELU), L(TMPS_LINEAR, {24, 16, 2, 3}), L(TMPS_LAYERNORM, {16, 3}),

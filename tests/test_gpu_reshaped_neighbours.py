@@ -3,7 +3,7 @@ with the one that forms it: against the oracle, which runs them one by one."""
 import pytest
 
 from tests.test_gpu_stage import run_stage_case
-from workloads.configs import affine, bottleneck, conv, linear
+from workloads.configs import affine, bottleneck, conv, linear, maxpool
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +31,12 @@ def test_convolution_behind_a_join(h, cin, first, second):
     n = side[0] * side[1] * first // second
     run_stage_case([conv(h, h, 8, 64, 3, 1, 1, True)] + block + [conv_, affine(side[0], n // side[0], second, True), conv(side[0], n // side[0], second, 8, 1, 1, 0, False)],
                    "bf16", 4 if h == 32 else 1, 2, seed=h + cin + second, deep=True)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("h,w,c", [(8, 8, 16), (16, 4, 16), (4, 4, 64), (16, 16, 4), (8, 4, 32)])
+def test_pooling_behind_an_affine_layer(dtype, h, w, c):
+    """The pooling's input gradient and the affine layer's are one pass over the channels of both."""
+    ho, wo = (h - 1) // 2 + 1, (w - 1) // 2 + 1
+    run_stage_case([conv(8, 8, 8, 16, 3, 1, 1, False), affine(8, 8, 16, True), maxpool(h, w, c, k=3, stride=2, pad=1), linear(ho * wo * c, 8, False)], dtype, 3, 2,
+                   seed=h + c, has_pool=True)
