@@ -122,7 +122,7 @@ def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointw
 
 # classes whose kernels carry their own start/stop timestamps (no bracket overhead)
 KERNEL_STAMPED = ("dense_fwd", "dense_dgrad", "dense_wgrad", "dense_backward", "conv_fwd", "conv_dgrad", "conv_wgrad", "splitk_finish",
-                  "slice_sum", "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd")
+                  "slice_sum", "pool_fwd", "pool_bwd", "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd")
 
 
 def class_entry(cfg, klass, ms, launches, joint=None, joint_pointwise=None):

@@ -311,12 +311,11 @@ int tmps_streams_destroy(void** streams, int n);
 /* ---- measurement aid (not part of the method) ----
  *
  * While enabled, every kernel launch made by the calls above is timed with HIP events on the stream
- * it is launched on.  The contraction kernels (the six *_FWD / *_DGRAD / *_WGRAD classes, and
- * TMPS_KC_DENSE_BACKWARD: launches that hold both gradients of a dense layer) and the
- * reductions of their k-split (TMPS_KC_SPLIT_FINISH, TMPS_KC_SLICE_SUM) are launched with a start and
- * a stop event of their own, which the runtime stamps with the start and end of that kernel's
- * execution.  The other classes are bracketed by two events recorded around the launch, which also
- * measures dispatch latency; TMPS_KC_EVENT_PAIR is an empty bracket recorded before every update, the
+ * it is launched on.  The launches of the loss (TMPS_KC_SOFTMAX_CE, TMPS_KC_REDUCE), the update, the
+ * mask of an upstream gradient (TMPS_KC_RELU_MASK) and copies are bracketed by two events recorded
+ * around the launch, which also measures dispatch latency; every other class's kernels are launched
+ * with a start and a stop event of their own, which the runtime stamps with the start and end of that
+ * kernel's execution.  TMPS_KC_EVENT_PAIR is an empty bracket recorded before every update launch, the
  * cost of such a pair by itself.  tmps_profile_read() waits for the recorded events, adds the elapsed
  * milliseconds and launch counts per class into total_ms[] / launches[] (host arrays of n_classes >=
  * TMPS_KERNEL_CLASSES entries), clears the record and returns TMPS_KERNEL_CLASSES.  Timing adds host

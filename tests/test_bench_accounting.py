@@ -152,3 +152,21 @@ def test_gradients_of_a_convolution_in_one_launch_with_the_affine_layer_behind_c
     for i in (1, 2):
         assert sum(got[k][i] for k in classes) == pytest.approx(sum(apart[k][i] for k in classes), rel=1e-12)
     assert apart["conv_dgrad"][0] - got["conv_dgrad"][0] == 7 and apart["conv_wgrad"][0] - got["conv_wgrad"][0] == 7
+
+
+def test_classes_that_hold_no_event_pair_are_those_that_are_launched_with_stamps():
+    """An empty pair of events is subtracted from every class but these: a class is either launched with its kernels' own stamps (launch_timed) or bracketed."""
+    import re
+
+    from paper_2410_14312_amd import KERNEL_CLASSES
+
+    root = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_14312_amd", "csrc")
+    text = "\n".join(open(os.path.join(root, f)).read() for f in sorted(os.listdir(root)))
+    enum = re.findall(r"\bkc\w+", re.search(r"enum KernelClass \{(.*?)\};", open(os.path.join(root, "profile.h")).read(), re.S).group(1))
+    names = dict(zip(enum, KERNEL_CLASSES))
+    assert len(enum) == len(KERNEL_CLASSES) + 1 and enum[-1] == "kcCount"
+    bracketed = {names[k] for k in re.findall(r"(?:TMPS_RUN\(|ProfileScope \w+\()(kc\w+)", text)}
+    assert bracketed == {"softmax_ce", "update", "relu_mask", "reduce", "copy", "event_pair"}
+    assert set(bench.KERNEL_STAMPED) == set(KERNEL_CLASSES) - bracketed
+    stamped = {names[k] for k in re.findall(r"launch_timed\((kc\w+)", text)}
+    assert stamped and not stamped & bracketed
