@@ -1130,13 +1130,13 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
     });   // (free_slots releases the group)
 }
 
+// What a pair of timing events costs by itself on this stream: the brackets of its launches hold one each.
+static void empty_bracket(hipStream_t s) { ProfileScope empty(kcEventPair, s); }
+
 extern "C" int tmps_update(tmps_stage* st, void* hip_stream) {
     if (!st) return fail(TMPS_EINVAL, "stage is null");
     hipStream_t s = (hipStream_t)hip_stream;
-    {
-        // an empty bracket: what a pair of timing events costs by itself on this stream
-        ProfileScope empty(kcEventPair, s);
-    }
+    empty_bracket(s);
     if (st->shadow_n > 0) {
         // the version about to be superseded is kept for the passes tagged with it: the update stores what it replaces
         const int slot = (int)(st->version % st->shadow_n);
@@ -1156,7 +1156,9 @@ int tmps::update_all(tmps_stage* const* stages, int n, void* hip_stream) {
     Update list[kUpdateMax];
     int k = 0;
     auto flush = [&]() -> int {
-        if (k > 0) TMPS_RUN(kcUpdate, s, sgd_momentum_all(list, k, s));
+        if (k == 0) return TMPS_OK;
+        empty_bracket(s);
+        TMPS_RUN(kcUpdate, s, sgd_momentum_all(list, k, s));
         k = 0;
         return TMPS_OK;
     };

@@ -32,3 +32,20 @@ def test_updates_together(monkeypatch, K, N, batches, vertical_sync, dtype):
         for la, lb in zip(a, b):
             for k in la:
                 assert np.array_equal(la[k], lb[k]), k
+
+
+@pytest.mark.parametrize("one,K", [(True, 1), (True, 4), (True, 19), (False, 4)])
+def test_every_launch_of_updates_has_an_empty_bracket(one, K):
+    """What a pair of timing events costs is measured beside every launch that is bracketed so, on one stream as on K."""
+    import paper_2410_14312_amd as T
+    cfg = _mlp(K, 2, "f32")
+    pipe = T.Pipeline(cfg, init_params(cfg), one_stream=one)
+    data = [make_batch(cfg, i) for i in range(2)]
+    pipe.run(data)
+    T.profile_enable(True)
+    try:
+        pipe.run(data)
+        prof = T.profile_read()
+    finally:
+        T.profile_enable(False)
+    assert prof["event_pair"][1] == prof["update"][1] > 0
