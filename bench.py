@@ -25,7 +25,7 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 
 
-def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointwise=None):
+def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointwise=None, joint_pool=None, joint_forward=None):
     """Per kernel class and per mini-batch: (launches, FLOPs, algorithmic bytes) from the shapes alone
     (of every stage, or of stage `only_stage` alone).
 
@@ -35,12 +35,45 @@ def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointw
 
     joint(dtype, rows, din, dout): whether both gradients of a dense layer are one launch, which then counts as "dense_backward".
     joint_pointwise(dtype, positions, cin, cout): whether those of a 1 x 1 convolution are one with the affine layer's behind it, which then counts as "affine".
+    joint_pool(dtype, positions, channels, window, stride): whether the gradient of max pooling is one with those of the affine layer below, which then counts as "pool_bwd".
+    joint_forward(dtype, positions, cin, cout): whether a 1 x 1 convolution with its affine layer and a residual join is one launch with the next
+    block's first convolution, of which the join's result is then not read again.
+    What layers do in one launch counts with the bytes that this one cannot do without: their maps once, not once for each layer.
 
     Dense GEMMs count 2*rows*Din*Dout FLOPs and their operand/result bytes once; the update counts
     22 bytes per parameter in bf16 stages (read w, buf, g fp32; write w, buf fp32 and the bf16 copy)
     or 20 in fp32 stages."""
     asz = 2 if cfg.dtype == "bf16" else 4
     M, F = cfg.M, cfg.N if passes is None else passes
+
+    def source(st, li):   # the result that layer li reads (-1: the stage input)
+        return li - (st[li].get("src", 1) if st[li]["kind"] == "conv" else 1)
+
+    def readers(st, t):
+        return [i for i, sp in enumerate(st) if source(st, i) == t] + [i for i, sp in enumerate(st) if sp["kind"] == "resadd" and max(i - sp["src_b"], -1) == t]
+
+    def pointwise_affine(st, li):   # a 1 x 1 convolution of unit stride that only an affine layer over its channels reads
+        sp = st[li]
+        return (sp["kind"] == "conv" and sp["r"] == sp["s"] == sp["stride"] == 1 and sp["pad"] == 0 and li + 1 < len(st) and st[li + 1]["kind"] == "affine" and
+                st[li + 1]["c"] == sp["cout"] and len(readers(st, li)) == 1)
+
+    def gradients_joint(si, st, li):
+        sp = st[li]
+        return (joint_pointwise is not None and not (si == 0 and li == 0) and pointwise_affine(st, li) and
+                joint_pointwise(cfg.dtype, M * sp["h"] * sp["w"], sp["cin"], sp["cout"]))
+
+    def pooled_joint(st, li):   # max pooling behind an affine layer that only it reads
+        sp = st[li]
+        return (joint_pool is not None and sp["kind"] == "maxpool" and li > 0 and st[li - 1]["kind"] == "affine" and st[li - 1]["c"] == sp["c"] and
+                len(readers(st, li - 1)) == 1 and joint_pool(cfg.dtype, M * sp["h"] * sp["w"], sp["c"], sp["k"], sp["stride"]))
+
+    def behind_join(st, li):   # the first convolution of a block whose input is joined in the same launch
+        if joint_forward is None or li < 3 or li + 2 >= len(st) or source(st, li) != li - 1:
+            return False
+        a = st[li - 3]
+        return (pointwise_affine(st, li) and not st[li]["relu"] and pointwise_affine(st, li - 3) and not st[li - 2]["relu"] and len(readers(st, li - 2)) == 1 and
+                st[li - 1]["kind"] == "resadd" and (st[li]["cin"], st[li]["cout"]) == (a["cout"], a["cin"]) and
+                joint_forward(cfg.dtype, M * a["h"] * a["w"] / F, a["cin"], a["cout"]))
     work = {}
 
     def add(k, launches, flops, nbytes):
@@ -88,18 +121,24 @@ def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointw
                 kk = sp["r"] * sp["s"] * sp["cin"]
                 P += kk * sp["cout"] + sp["cout"]
                 x_e, y_e = sp["h"] * sp["w"] * sp["cin"], ho * wo * sp["cout"]
-                add("conv_fwd", F, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + F * kk * sp["cout"] * asz)
-                one = (joint_pointwise is not None and not (si == 0 and li == 0) and sp["r"] == sp["s"] == sp["stride"] == 1 and sp["pad"] == 0 and
-                       li + 1 < len(st) and st[li + 1]["kind"] == "affine" and joint_pointwise(cfg.dtype, M * ho * wo, sp["cin"], sp["cout"]))
-                add("affine" if one else "conv_wgrad", 0 if one else 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * 4)
+                flops = 2.0 * M * ho * wo * kk * sp["cout"]
+                joined = behind_join(st, li)
+                add("conv_fwd", 0 if joined else F, flops, M * ((0 if joined else x_e) + y_e) * asz + F * kk * sp["cout"] * asz)
+                if gradients_joint(si, st, li):
+                    # one launch reads dY, z, x and what other, later readers of x contributed, and writes dx
+                    more = 1 if len([i for i in readers(st, source(st, li)) if i > li]) else 0
+                    add("affine", 1, 2 * flops, M * (2 * y_e + (2 + more) * x_e) * asz + kk * sp["cout"] * (asz + 4))
+                    continue
+                add("conv_wgrad", 1, flops, M * (x_e + y_e) * asz + kk * sp["cout"] * 4)
                 if not (si == 0 and li == 0):
-                    add("affine" if one else "conv_dgrad", 0 if one else 1, 2.0 * M * ho * wo * kk * sp["cout"], M * (x_e + y_e) * asz + kk * sp["cout"] * asz)
+                    add("conv_dgrad", 1, flops, M * (x_e + y_e) * asz + kk * sp["cout"] * asz)
             elif sp["kind"] == "affine":
                 e = sp["h"] * sp["w"] * sp["c"]
                 P += 2 * sp["c"]
                 # the forward pass runs inside the convolution's epilogue; what is launched is the backward pass
-                # (read dy and x, write dx) and the reduction of its per-slab partial sums
-                add("affine", 2, 0.0, M * 3 * e * asz)
+                # (read dy and x, write dx; the sum of its slabs' partial results is of class slice_sum), where it is a launch of its own
+                if not (li > 0 and gradients_joint(si, st, li - 1)) and not (li + 1 < len(st) and pooled_joint(st, li + 1)):
+                    add("affine", 1, 0.0, M * 3 * e * asz)
             elif sp["kind"] == "resadd":
                 e = sp["h"] * sp["w"] * sp["c"]
                 add("resadd", F, 0.0, M * 3 * e * asz)
@@ -111,8 +150,9 @@ def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointw
                 pad = sp.get("pad", 0)
                 ho, wo = (sp["h"] + 2 * pad - sp["k"]) // sp["stride"] + 1, (sp["w"] + 2 * pad - sp["k"]) // sp["stride"] + 1
                 x_e, y_e = sp["h"] * sp["w"] * sp["c"], ho * wo * sp["c"]
-                add("pool_fwd", F, 0.0, M * (x_e + y_e) * asz)
-                add("pool_bwd", 1, 0.0, M * (2 * x_e + y_e) * asz)
+                won = sp["k"] ** 2 < 128   # (a byte for every window's winner, instead of the input searched again)
+                add("pool_fwd", F, 0.0, M * ((x_e + y_e) * asz + (y_e if won else 0)))
+                add("pool_bwd", 1, 0.0, M * ((x_e + y_e) * asz + (y_e if won else x_e * asz) + (x_e * asz if pooled_joint(st, li) else 0)))
             elif sp["kind"] == "softmax_ce":
                 c, rows = sp["classes"], sp.get("rows", 1)
                 add("softmax_ce", F, 0.0, M * rows * (c * 4 + c * asz + 8))
@@ -125,15 +165,15 @@ KERNEL_STAMPED = ("dense_fwd", "dense_dgrad", "dense_wgrad", "dense_backward", "
                   "slice_sum", "pool_fwd", "pool_bwd", "layernorm", "attn_fwd", "attn_bwd", "embedding", "affine", "resadd")
 
 
-def class_entry(cfg, klass, ms, launches, joint=None, joint_pointwise=None):
+def class_entry(cfg, klass, ms, launches, joint=None, joint_pointwise=None, joint_pool=None, joint_forward=None):
     """What a kernel class takes and does per mini-batch, from its measured time (ms) and number of launches.  The work of a
-    class comes from the shapes and not from the launches: consecutive micro-batches may be forwarded in one pass.  (joint, joint_pointwise: see
-    algorithmic_work.)"""
+    class comes from the shapes and not from the launches: consecutive micro-batches may be forwarded in one pass.  (joint, ..: see algorithmic_work.)"""
+    together = dict(joint=joint, joint_pointwise=joint_pointwise, joint_pool=joint_pool, joint_forward=joint_forward)
     ent = {"class": klass, "launches_per_step": launches, "avg_us": 1e3 * ms / launches, "ms_per_step": ms}
-    per = algorithmic_work(cfg, joint=joint, joint_pointwise=joint_pointwise).get(klass)
+    per = algorithmic_work(cfg, **together).get(klass)
     if per and per[0]:
         if klass in ("dense_fwd", "conv_fwd"):   # launches of a layer = passes; each reads the layer's weights
-            per = algorithmic_work(cfg, passes=cfg.N * launches / per[0], joint=joint, joint_pointwise=joint_pointwise)[klass]
+            per = algorithmic_work(cfg, passes=cfg.N * launches / per[0], **together)[klass]
         ent["gflop_per_launch"] = per[1] / launches / 1e9
         ent["mbytes_per_launch"] = per[2] / launches / 1e6
         ent["tflops"] = per[1] / (ms / 1e3) / 1e12
@@ -361,7 +401,8 @@ def main():
                 continue
             if k not in KERNEL_STAMPED:      # bracketed classes also contain the cost of the event pair
                 ms = max(ms - cnt * pair_us / 1e3, 0.05 * ms)
-            ent = class_entry(cfg, k, ms / args.steps, cnt / args.steps, T.dense_gradients_joint, T.pointwise_gradients_joint)
+            ent = class_entry(cfg, k, ms / args.steps, cnt / args.steps, T.dense_gradients_joint, T.pointwise_gradients_joint, T.pool_affine_gradients_joint,
+                              T.pointwise_forward_joint)
             out.append(ent)
         out.sort(key=lambda e: -e["ms_per_step"])
         return out, pair_us

@@ -336,6 +336,11 @@ int tmps_dense_gradients_joint(int dtype, int64_t rows, int din, int dout);
 /* 1: the gradients of a 1 x 1 convolution of unit stride over `positions` positions and those of the affine layer that alone reads its result are
  * one launch (TMPS_KC_AFFINE), where the gradient of the convolution's input is wanted. */
 int tmps_pointwise_gradients_joint(int dtype, int64_t positions, int cin, int cout);
+/* 1: the gradient of max pooling over maps of `positions` positions and those of the affine layer that it alone reads are one launch (TMPS_KC_POOL_BWD). */
+int tmps_pool_affine_gradients_joint(int dtype, int64_t positions, int channels, int window, int stride);
+/* 1: a forward pass over `positions` positions of a 1 x 1 convolution of unit stride with its affine layer and the residual join behind them is one launch with the 1 x 1
+ * convolution back to `cin` channels that reads the join first, and that one's affine layer (TMPS_KC_CONV_FWD). */
+int tmps_pointwise_forward_joint(int dtype, int64_t positions, int cin, int cout);
 
 const char* tmps_last_error(void);
 

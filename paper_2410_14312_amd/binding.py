@@ -71,6 +71,8 @@ EXPORTS = {
     "tmps_profile_read": (C.c_int, [C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int]),
     "tmps_dense_gradients_joint": (C.c_int, [C.c_int, C.c_int64, C.c_int, C.c_int]),
     "tmps_pointwise_gradients_joint": (C.c_int, [C.c_int, C.c_int64, C.c_int, C.c_int]),
+    "tmps_pool_affine_gradients_joint": (C.c_int, [C.c_int, C.c_int64, C.c_int, C.c_int, C.c_int]),
+    "tmps_pointwise_forward_joint": (C.c_int, [C.c_int, C.c_int64, C.c_int, C.c_int]),
     "tmps_last_error": (C.c_char_p, []),
 }
 
@@ -158,6 +160,16 @@ def dense_gradients_joint(dtype, rows, din, dout):
 def pointwise_gradients_joint(dtype, positions, cin, cout):
     """Whether the gradients of a 1 x 1 convolution and the affine layer behind it are one launch, timed under "affine"."""
     return bool(lib().tmps_pointwise_gradients_joint(TMPS_BF16_F32MASTER if dtype == "bf16" else TMPS_F32, positions, cin, cout))
+
+
+def pool_affine_gradients_joint(dtype, positions, channels, window, stride):
+    """Whether the gradient of max pooling and those of the affine layer below are one launch, timed under "pool_bwd"."""
+    return bool(lib().tmps_pool_affine_gradients_joint(TMPS_BF16_F32MASTER if dtype == "bf16" else TMPS_F32, positions, channels, window, stride))
+
+
+def pointwise_forward_joint(dtype, positions, cin, cout):
+    """Whether a 1 x 1 convolution with its affine layer and a residual join is one launch with the convolution that reads the join first."""
+    return bool(lib().tmps_pointwise_forward_joint(TMPS_BF16_F32MASTER if dtype == "bf16" else TMPS_F32, int(positions), cin, cout))
 
 
 def layer_descs(specs):

@@ -426,3 +426,6 @@ hipError_t affine_pointwise_backward(const void* dy, const void* z, const void* 
 extern "C" int tmps_pointwise_gradients_joint(int dtype, int64_t positions, int cin, int cout) {
     return tmps::affine_pointwise_takes(dtype, positions, cout, cin) ? 1 : 0;
 }
+extern "C" int tmps_pointwise_forward_joint(int dtype, int64_t positions, int cin, int cout) {
+    return dtype == tmps::kBF16 && tmps::pointwise_forward_takes(positions, cin, cout) ? 1 : 0;
+}

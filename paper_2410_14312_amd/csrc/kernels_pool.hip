@@ -412,3 +412,7 @@ hipError_t maxpool_affine_backward(int dtype, const void* dy, const uint8_t* won
 }
 
 }  // namespace tmps
+
+extern "C" int tmps_pool_affine_gradients_joint(int dtype, int64_t positions, int channels, int window, int stride) {
+    return tmps::maxpool_keeps_winners(window) && tmps::maxpool_affine_takes(dtype, positions, channels, window, stride) ? 1 : 0;
+}

@@ -143,15 +143,51 @@ def test_both_gradients_of_a_layer_in_one_launch_count_together(name):
 
 
 def test_gradients_of_a_convolution_in_one_launch_with_the_affine_layer_behind_count_there():
-    """Seven of the first group's 1 x 1 convolutions (the second group's have more outputs than a workgroup's accumulators), with all of their work."""
+    """Seven of the first group's 1 x 1 convolutions (the second group's have more outputs than a workgroup's accumulators), with all of their products and
+    with the bytes of one launch: the result's gradient, the result and the input read once, what a later reader of the input contributed, the input's gradient written."""
     from paper_2410_14312_amd import pointwise_gradients_joint
 
     cfg = get_config("resnet50_bf16")
     apart, got = bench.algorithmic_work(cfg), bench.algorithmic_work(cfg, joint_pointwise=pointwise_gradients_joint)
     classes = ("conv_dgrad", "conv_wgrad", "affine")
-    for i in (1, 2):
-        assert sum(got[k][i] for k in classes) == pytest.approx(sum(apart[k][i] for k in classes), rel=1e-12)
-    assert apart["conv_dgrad"][0] - got["conv_dgrad"][0] == 7 and apart["conv_wgrad"][0] - got["conv_wgrad"][0] == 7
+    assert sum(got[k][1] for k in classes) == pytest.approx(sum(apart[k][1] for k in classes), rel=1e-12)
+    assert apart["conv_dgrad"][0] - got["conv_dgrad"][0] == 7 and apart["conv_wgrad"][0] - got["conv_wgrad"][0] == 7 and apart["affine"][0] == got["affine"][0]
+    # (inputs, outputs, a joined gradient): the first block's reduction, expansion and projection, two more blocks' reductions and expansions
+    P, layers = cfg.M * 56 * 56, [(64, 64, 1), (64, 256, 0), (64, 256, 0), (256, 64, 1), (64, 256, 0), (256, 64, 1), (64, 256, 0)]
+    one = sum(P * (2 * o + (2 + j) * i) * 2 + i * o * 6 for i, o, j in layers)
+    assert got["affine"][2] - (apart["affine"][2] - sum(P * 3 * o * 2 for _, o, _ in layers)) == pytest.approx(one, rel=1e-12)
+    moved = sum(2 * P * (i + o) * 2 + i * o * 6 for i, o, _ in layers)
+    assert sum(apart[k][2] - got[k][2] for k in classes[:2]) == pytest.approx(moved, rel=1e-12)
+
+
+def test_the_stem_s_pooling_counts_with_the_affine_layer_below_where_both_are_one_launch():
+    from paper_2410_14312_amd import pool_affine_gradients_joint
+
+    cfg = get_config("resnet50_bf16")
+    apart, got = bench.algorithmic_work(cfg), bench.algorithmic_work(cfg, joint_pool=pool_affine_gradients_joint)
+    z, y = cfg.M * 112 * 112 * 64, cfg.M * 56 * 56 * 64
+    assert apart["affine"][0] - got["affine"][0] == 1 and apart["affine"][2] - got["affine"][2] == 3 * z * 2
+    assert got["pool_bwd"][0] == apart["pool_bwd"][0] and got["pool_bwd"][2] - apart["pool_bwd"][2] == z * 2
+    rest = cfg.M * (2 * 7 * 7 * 2048 + 2048) * 2   # (the global average pooling)
+    assert got["pool_bwd"][2] - rest == 2 * z * 2 + y * 3   # read z, dy and a byte for each winner, write dz
+    # 2 x 2 windows without an affine layer: winners and dy read, dx written
+    vgg = get_config("vgg16_bf16")
+    maps = vgg.M * sum(hw * hw * c for hw, c in ((32, 64), (16, 128), (8, 256), (4, 512), (2, 512)))
+    assert bench.algorithmic_work(vgg, joint_pool=pool_affine_gradients_joint)["pool_bwd"][2] == maps * 2 + maps // 4 * 3
+
+
+def test_a_join_and_the_next_block_s_first_convolution_count_as_one_launch():
+    """Two of the first group's, where the join's result is not read again."""
+    from paper_2410_14312_amd import pointwise_forward_joint
+
+    cfg = get_config("resnet50_bf16")
+    apart, got = bench.algorithmic_work(cfg), bench.algorithmic_work(cfg, joint_forward=pointwise_forward_joint)
+    pairs = 2
+    assert apart["conv_fwd"][0] - got["conv_fwd"][0] == pairs * cfg.N and apart["conv_fwd"][1] == pytest.approx(got["conv_fwd"][1], rel=1e-12)
+    assert apart["conv_fwd"][2] - got["conv_fwd"][2] == pytest.approx(pairs * cfg.M * 56 * 56 * 256 * 2, rel=1e-12)
+    # as many launches as passes over one micro-batch each make
+    e = bench.class_entry(cfg, "conv_fwd", 2.0, got["conv_fwd"][0], joint_forward=pointwise_forward_joint)
+    assert e["gbs"] == pytest.approx(got["conv_fwd"][2] / 2e-3 / 1e9, rel=1e-12)
 
 
 def test_classes_that_hold_no_event_pair_are_those_that_are_launched_with_stamps():
