@@ -150,9 +150,9 @@ def algorithmic_work(cfg, only_stage=None, passes=None, joint=None, joint_pointw
                 pad = sp.get("pad", 0)
                 ho, wo = (sp["h"] + 2 * pad - sp["k"]) // sp["stride"] + 1, (sp["w"] + 2 * pad - sp["k"]) // sp["stride"] + 1
                 x_e, y_e = sp["h"] * sp["w"] * sp["c"], ho * wo * sp["c"]
-                won = sp["k"] ** 2 < 128   # (a byte for every window's winner, instead of the input searched again)
-                add("pool_fwd", F, 0.0, M * ((x_e + y_e) * asz + (y_e if won else 0)))
-                add("pool_bwd", 1, 0.0, M * ((x_e + y_e) * asz + (y_e if won else x_e * asz) + (x_e * asz if pooled_joint(st, li) else 0)))
+                won = y_e * (1 if sp["k"] ** 2 < 128 else 4)   # (every window's winner, of which a byte holds 128)
+                add("pool_fwd", F, 0.0, M * ((x_e + y_e) * asz + won))
+                add("pool_bwd", 1, 0.0, M * ((x_e + y_e) * asz + won + (x_e * asz if pooled_joint(st, li) else 0)))
             elif sp["kind"] == "softmax_ce":
                 c, rows = sp["classes"], sp.get("rows", 1)
                 add("softmax_ce", F, 0.0, M * rows * (c * 4 + c * asz + 8))

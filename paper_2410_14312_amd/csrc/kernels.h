@@ -130,16 +130,16 @@ int affine_pointwise_slabs(int64_t P, int O, int I);
 hipError_t affine_pointwise_backward(const void* dy, const void* z, const void* x, const void* w, const float* gain, const void* add, int masked, void* dx,
                                      float* gw_affine, float* gw_conv, const Partials& pa, const Partials& pw, int64_t P, int O, int I, hipStream_t s);
 
-// 2-D max pooling, channels-last.  won (a byte per result, as the forward pass leaves it; null: the windows are larger than maxpool_keeps_winners takes, and the
-// backward pass finds the winners again in x): the first maximum of every window in row-major order; relu_mask: also zero where the input is <= 0.
-bool maxpool_keeps_winners(int k);
-hipError_t maxpool_forward(int dtype, const void* x, void* y, uint8_t* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s);
-hipError_t maxpool_backward(int dtype, const void* x, const void* dy, const uint8_t* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad,
-                            int relu_mask, hipStream_t s);
+// 2-D max pooling, channels-last.  won: every window's winner as the forward pass leaves it, maxpool_winner_bytes each (on as many bytes): the first maximum in
+// row-major order, of which NaN is none (nor of the result); in a window of negative infinities and NaN alone the first place inside the map.  relu_mask: also zero
+// where the input is <= 0.
+int maxpool_winner_bytes(int k);
+hipError_t maxpool_forward(int dtype, const void* x, void* y, void* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s);
+hipError_t maxpool_backward(int dtype, const void* dy, const void* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s);
 // The same behind an affine layer (affine_backward) that only the pooling reads, in one pass: z is that layer's input, dz its gradient (rows positions);
 // dy, z, gain and dz on 16 bytes.
 bool maxpool_affine_takes(int dtype, int64_t rows, int C, int k, int stride);
-hipError_t maxpool_affine_backward(int dtype, const void* dy, const uint8_t* won, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& ws,
+hipError_t maxpool_affine_backward(int dtype, const void* dy, const void* won, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& ws,
                                    int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s);
 
 // Per-channel affine layer on channels-last rows: y[r, c] = gain[c] x[r, c] + shift[c], then ReLU if asked.

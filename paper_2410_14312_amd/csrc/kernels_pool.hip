@@ -1,6 +1,8 @@
-// Max pooling over channels-last maps.  The forward pass keeps every window's winner (the first maximum in row-major order) as a byte beside the
-// result, so that the backward pass reads these instead of finding them again in the input: a quarter (2 x 2) or less of its bytes, and none
-// of the comparisons that bound it before.
+// Max pooling over channels-last maps.  The forward pass keeps every window's winner (the first maximum in row-major order) beside the
+// result, as a byte (for windows of 12 x 12 and more as four), so that the backward pass reads these instead of finding them again in the input: a quarter (2 x 2) or
+// less of its bytes, and none of the comparisons that bound it before.  Backward pass with the input searched and by winners (us, bf16): 64 maps of 56 x 56 x 64, 3 x 3
+// windows of stride 1 91 and 30, 5 x 5 of stride 2 99 and 23, 12 x 12 of stride 12 672 and 13; 64 of 13 x 13 x 512, 9 x 9 of stride 1 12197 and 68; 16 of 19 x 19 x 512, 13 x 13
+// of stride 1 29656 and 147.
 #include "gemm.hip.h"
 #include "gemm2.hip.h"
 #include "kernels.h"
@@ -11,9 +13,11 @@ namespace tmps {
 static inline int cdiv_pool(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 static inline bool al16p(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// A winner: r * k + q of its place in the window, with kNotPositive where it is not above zero (what the ReLU of the layer below then stops); the first
-// place inside the map in a window of negative infinities and NaN.  kNoWinner: no such window.
+// A winner of a window whose places a byte tells apart: r * k + q of its place, with kNotPositive where it is not above zero (what the ReLU of the layer below then
+// stops).  Of a larger one: its position in the map, h W + w, in 32 bits, the highest of them for that.  In a window of negative infinities and NaN alone: the first
+// place inside the map.  kNoWinner: no such window.
 constexpr unsigned kNotPositive = 128, kNoWinner = 255;
+template <class W> constexpr uint32_t not_positive() { return sizeof(W) == 1 ? kNotPositive : 0x80000000u; }
 
 struct PoolDims {
     int B, H, W, C, Ho, Wo, k, stride, pad;
@@ -37,11 +41,12 @@ template <class T, int V> struct PoolVec {
         else *reinterpret_cast<uint4*>(p) = u.raw;
     }
 };
-template <int V> struct Winners {
-    unsigned w[V > 4 ? V / 4 : 1];
+template <class W, int V> struct Winners;
+template <int V> struct Winners<uint8_t, V> {
+    uint32_t w[V > 4 ? V / 4 : 1];
     __device__ __forceinline__ void load(const uint8_t* p) {
         if constexpr (V == 1) w[0] = *p;
-        else if constexpr (V == 4) w[0] = *reinterpret_cast<const unsigned*>(p);
+        else if constexpr (V == 4) w[0] = *reinterpret_cast<const uint32_t*>(p);
         else {
             const uint2 t = *reinterpret_cast<const uint2*>(p);
             w[0] = t.x;
@@ -50,25 +55,56 @@ template <int V> struct Winners {
     }
     __device__ __forceinline__ void store(uint8_t* p) const {
         if constexpr (V == 1) *p = (uint8_t)w[0];
-        else if constexpr (V == 4) *reinterpret_cast<unsigned*>(p) = w[0];
+        else if constexpr (V == 4) *reinterpret_cast<uint32_t*>(p) = w[0];
         else *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
     }
-    __device__ __forceinline__ unsigned at(int e) const { return (w[e >> 2] >> (8 * (e & 3))) & 255u; }
-    __device__ __forceinline__ void fill(unsigned byte) {
+    __device__ __forceinline__ uint32_t at(int e) const { return (w[e >> 2] >> (8 * (e & 3))) & 255u; }
+    __device__ __forceinline__ void set(int e, uint32_t v) {   // (in order, from the first one on)
+        if ((e & 3) == 0) w[e >> 2] = v;
+        else w[e >> 2] |= v << (8 * (e & 3));
+    }
+    __device__ __forceinline__ void fill(uint32_t byte) {
 #pragma unroll
         for (int i = 0; i < (V > 4 ? V / 4 : 1); ++i) w[i] = byte * 0x01010101u;
     }
-    __device__ __forceinline__ void mask(unsigned byte) {
+    __device__ __forceinline__ void mask(uint32_t byte) {
 #pragma unroll
         for (int i = 0; i < (V > 4 ? V / 4 : 1); ++i) w[i] &= byte * 0x01010101u;
+    }
+};
+template <int V> struct Winners<uint32_t, V> {
+    uint32_t w[V];
+    __device__ __forceinline__ void load(const uint32_t* p) {
+        if constexpr (V == 1) w[0] = *p;
+        else {
+#pragma unroll
+            for (int i = 0; i < V; i += 4) {
+                const uint4 t = *reinterpret_cast<const uint4*>(p + i);
+                w[i] = t.x; w[i + 1] = t.y; w[i + 2] = t.z; w[i + 3] = t.w;
+            }
+        }
+    }
+    __device__ __forceinline__ void store(uint32_t* p) const {
+        if constexpr (V == 1) *p = w[0];
+        else {
+#pragma unroll
+            for (int i = 0; i < V; i += 4) *reinterpret_cast<uint4*>(p + i) = make_uint4(w[i], w[i + 1], w[i + 2], w[i + 3]);
+        }
+    }
+    __device__ __forceinline__ uint32_t at(int e) const { return w[e]; }
+    __device__ __forceinline__ void set(int e, uint32_t v) { w[e] = v; }
+    __device__ __forceinline__ void mask(uint32_t bits) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) w[e] &= bits;
     }
 };
 
 // One thread per window and V channels.  K: the window where it is known at compile time (0: the argument); all of its elements are then requested at
 // once (8 images of 112 x 112 x 64, 3 x 3 windows of stride 2: 6.7 us; a loop that waits for one at a time 8.5).
-template <class T, int V, int K>
-__global__ __launch_bounds__(256) void maxpool_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, uint8_t* __restrict__ won, PoolDims p) {
-    const int CV = p.C / V, k = K ? K : p.k;
+template <class T, int V, int K, class W>
+__global__ __launch_bounds__(256) void maxpool_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, W* __restrict__ won, PoolDims p) {
+    constexpr bool kByte = sizeof(W) == 1;
+    const int CV = p.C / V;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)p.B * p.Ho * p.Wo * CV) return;
     const int c = (int)(i % CV) * V;
@@ -76,16 +112,17 @@ __global__ __launch_bounds__(256) void maxpool_fwd_kernel(const T* __restrict__ 
     const int wo = (int)(t % p.Wo); t /= p.Wo;
     const int ho = (int)(t % p.Ho);
     const int n = (int)(t / p.Ho);
-    const int h0 = ho * p.stride - p.pad, w0 = wo * p.stride - p.pad;
+    const int h0 = ho * p.stride - p.pad, w0 = wo * p.stride - p.pad, hl = max(h0, 0), wl = max(w0, 0);   // (the first place inside the map)
     const T* const xn = x + (int64_t)n * p.H * p.W * p.C + c;
+    auto place = [&](int h, int w) { return kByte ? (uint32_t)((h - h0) * (K ? K : p.k) + w - w0) : (uint32_t)(h * p.W + w); };
     float best[V];
-    unsigned where[V];
+    uint32_t where[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) {
         best[e] = -INFINITY;
-        where[e] = (unsigned)(max(-h0, 0) * k + max(-w0, 0));
+        where[e] = place(hl, wl);
     }
-    auto look = [&](const PoolVec<T, V>& o, unsigned me) {
+    auto look = [&](const PoolVec<T, V>& o, uint32_t me) {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             const float v = to_f32(o.u.e[e]);
@@ -105,26 +142,38 @@ __global__ __launch_bounds__(256) void maxpool_fwd_kernel(const T* __restrict__ 
 #pragma unroll
         for (int a = 0; a < K * K; ++a)   // (padding never wins)
             if ((unsigned)(h0 + a / K) < (unsigned)p.H && (unsigned)(w0 + a % K) < (unsigned)p.W) look(o[a], a);
-    } else {
-        for (int r = 0; r < k; ++r)
-            for (int q = 0; q < k; ++q) {
-                const int hh = h0 + r, ww = w0 + q;
-                if ((unsigned)hh >= (unsigned)p.H || (unsigned)ww >= (unsigned)p.W) continue;
+    } else if constexpr (kByte) {
+        for (int r = 0; r < p.k; ++r)
+            for (int q = 0; q < p.k; ++q) {
+                const int h = h0 + r, w = w0 + q;
+                if ((unsigned)h >= (unsigned)p.H || (unsigned)w >= (unsigned)p.W) continue;
                 PoolVec<T, V> o;
-                o.load(xn + ((int64_t)hh * p.W + ww) * p.C);
-                look(o, (unsigned)(r * k + q));
+                o.load(xn + ((int64_t)h * p.W + w) * p.C);
+                look(o, place(h, w));
             }
+    } else {
+        // (long rows, four of whose elements are requested at a time: 14 x 14 windows of 64 maps of 56 x 56 x 64 in bf16 85 and 36 us; rows of four and five lose by it,
+        // 4 x 4 of stride 2 over 30 x 30 8.7 and 12.0)
+        const int h1 = min(h0 + p.k, p.H), w1 = min(w0 + p.k, p.W);
+        for (int h = hl; h < h1; ++h) {
+            const T* const row = xn + (int64_t)h * p.W * p.C;
+#pragma unroll 4
+            for (int w = wl; w < w1; ++w) {
+                PoolVec<T, V> o;
+                o.load(row + (int64_t)w * p.C);
+                look(o, place(h, w));
+            }
+        }
     }
     PoolVec<T, V> out;
-    Winners<V> win;
-    win.fill(0);
+    Winners<W, V> win;
 #pragma unroll
     for (int e = 0; e < V; ++e) {
         out.u.e[e] = from_f32<T>(best[e]);
-        win.w[e >> 2] |= (best[e] > 0.0f ? where[e] : where[e] | kNotPositive) << (8 * (e & 3));
+        win.set(e, best[e] > 0.0f ? where[e] : where[e] | not_positive<W>());
     }
     out.store(y + i * V);
-    if (won) win.store(won + i * V);
+    win.store(won + i * V);
 }
 
 // The input gradients of an S x S block of positions, (i S + a - pad, j S + b - pad) for a, b < S, each the sum of the upstream gradients of the windows
@@ -133,7 +182,7 @@ template <class T, int V, int K, int S>
 __device__ __forceinline__ void pool_block(const PoolDims& p, const T* dy, const uint8_t* won, int n, int i, int j, int c, bool relu, float (&acc)[S * S][V]) {
     constexpr int NA = (K - 1) / S + 1;
     PoolVec<T, V> g[NA * NA];
-    Winners<V> win[NA * NA];
+    Winners<uint8_t, V> win[NA * NA];
 #pragma unroll
     for (int a = 0; a < NA * NA; ++a) {
         const int ho = i - a / NA, wo = j - a % NA;
@@ -190,8 +239,8 @@ __global__ __launch_bounds__(256) void maxpool_bwd_kernel(const T* __restrict__ 
 }
 
 // Any window, stride and channel count: one thread per position and V channels.
-template <class T, int V>
-__global__ __launch_bounds__(256) void maxpool_bwd_any_kernel(const T* __restrict__ dy, const uint8_t* __restrict__ won, T* __restrict__ dx, PoolDims p, int relu) {
+template <class T, int V, class W>
+__global__ __launch_bounds__(256) void maxpool_bwd_any_kernel(const T* __restrict__ dy, const W* __restrict__ won, T* __restrict__ dx, PoolDims p, int relu) {
     const int CV = p.C / V;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)p.B * p.H * p.W * CV) return;
@@ -210,11 +259,11 @@ __global__ __launch_bounds__(256) void maxpool_bwd_any_kernel(const T* __restric
         for (int wo = wo_lo; wo < p.Wo && wo * p.stride <= wp; ++wo) {
             const int64_t at = (((int64_t)n * p.Ho + ho) * p.Wo + wo) * p.C + c;
             PoolVec<T, V> g;
-            Winners<V> win;
+            Winners<W, V> win;
             g.load(dy + at);
             win.load(won + at);
-            if (!relu) win.mask(kNotPositive - 1);
-            const unsigned me = (unsigned)((hp - ho * p.stride) * p.k + wp - wo * p.stride);
+            if (!relu) win.mask(not_positive<W>() - 1);
+            const uint32_t me = sizeof(W) == 1 ? (uint32_t)((hp - ho * p.stride) * p.k + wp - wo * p.stride) : (uint32_t)(h * p.W + w);
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[e] += win.at(e) == me ? to_f32(g.u.e[e]) : 0.0f;
         }
@@ -222,40 +271,6 @@ __global__ __launch_bounds__(256) void maxpool_bwd_any_kernel(const T* __restric
 #pragma unroll
     for (int e = 0; e < V; ++e) out.u.e[e] = from_f32<T>(acc[e]);
     out.store(dx + i * V);
-}
-
-// Windows of more places than a byte tells apart: the winner is found again in the input, one thread per element of it.
-template <typename T>
-__global__ void maxpool_bwd_search_kernel(const T* __restrict__ x, const T* __restrict__ dy, T* __restrict__ dx, PoolDims p, int relu_mask) {
-    int64_t total = (int64_t)p.B * p.H * p.W * p.C;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    int c = (int)(i % p.C);
-    int64_t t = i / p.C;
-    int w = (int)(t % p.W); t /= p.W;
-    int h = (int)(t % p.H);
-    int n = (int)(t / p.H);
-    const float xv = to_f32(x[i]);
-    float acc = 0.0f;
-    if (!(relu_mask && !(xv > 0.0f))) {
-        const int hp = h + p.pad, wp = w + p.pad;
-        int ho_lo = hp - p.k + 1 > 0 ? (hp - p.k + p.stride) / p.stride : 0;
-        int wo_lo = wp - p.k + 1 > 0 ? (wp - p.k + p.stride) / p.stride : 0;
-        for (int ho = ho_lo; ho < p.Ho && ho * p.stride <= hp; ++ho)
-            for (int wo = wo_lo; wo < p.Wo && wo * p.stride <= wp; ++wo) {
-                bool win = true;
-                for (int r = 0; r < p.k && win; ++r)
-                    for (int s = 0; s < p.k; ++s) {
-                        int hh = ho * p.stride - p.pad + r, ww = wo * p.stride - p.pad + s;
-                        if ((unsigned)hh >= (unsigned)p.H || (unsigned)ww >= (unsigned)p.W) continue;
-                        float v = to_f32(x[(((int64_t)n * p.H + hh) * p.W + ww) * p.C + c]);
-                        bool before = (hh < h) || (hh == h && ww < w);
-                        if (v > xv || (before && v == xv)) { win = false; break; }
-                    }
-                if (win) acc += to_f32(dy[(((int64_t)n * p.Ho + ho) * p.Wo + wo) * p.C + c]);
-            }
-    }
-    dx[i] = from_f32<T>(acc);
 }
 
 // Max pooling behind a per-channel affine layer that nothing else reads: the affine layer's backward pass (dz = gain * da and the sums of da * z and of
@@ -326,26 +341,30 @@ __global__ __launch_bounds__(256) void maxpool_affine_bwd_kernel(const T* __rest
     }
 }
 
-bool maxpool_keeps_winners(int k) { return k * k < (int)kNotPositive; }
+int maxpool_winner_bytes(int k) { return (int64_t)k * k < (int64_t)kNotPositive ? 1 : 4; }
 
-template <class T>
-static hipError_t forward_t(const T* x, T* y, uint8_t* won, const PoolDims& p, hipStream_t s) {
+template <class T, class W>
+static hipError_t forward_t(const T* x, T* y, W* won, const PoolDims& p, hipStream_t s) {
     constexpr int V = 16 / sizeof(T);
     const int64_t n = (int64_t)p.B * p.Ho * p.Wo * p.C;
     if (p.C % V == 0 && al16p(x) && al16p(y)) {
         const dim3 grid(cdiv_pool(n / V, 256));
-        if (p.k == 2) return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, V, 2>, grid, dim3(256), 0, s, x, y, won, p);
-        if (p.k == 3) return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, V, 3>, grid, dim3(256), 0, s, x, y, won, p);
-        return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, V, 0>, grid, dim3(256), 0, s, x, y, won, p);
+        if constexpr (sizeof(W) == 1) {
+            if (p.k == 2) return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, V, 2, W>, grid, dim3(256), 0, s, x, y, won, p);
+            if (p.k == 3) return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, V, 3, W>, grid, dim3(256), 0, s, x, y, won, p);
+        }
+        return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, V, 0, W>, grid, dim3(256), 0, s, x, y, won, p);
     }
-    return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, 1, 0>, dim3(cdiv_pool(n, 256)), dim3(256), 0, s, x, y, won, p);
+    return launch_timed(kcPoolFwd, maxpool_fwd_kernel<T, 1, 0, W>, dim3(cdiv_pool(n, 256)), dim3(256), 0, s, x, y, won, p);
 }
 
-hipError_t maxpool_forward(int dtype, const void* x, void* y, uint8_t* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) {
+hipError_t maxpool_forward(int dtype, const void* x, void* y, void* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) {
     const PoolDims p = pool_dims(B, H, W, C, k, stride, pad);
     if ((int64_t)B * p.Ho * p.Wo * C <= 0) return hipSuccess;
-    if (dtype == kBF16) return forward_t((const bf16_t*)x, (bf16_t*)y, won, p, s);
-    return forward_t((const float*)x, (float*)y, won, p, s);
+    if (maxpool_winner_bytes(k) == 1)
+        return dtype == kBF16 ? forward_t((const bf16_t*)x, (bf16_t*)y, (uint8_t*)won, p, s) : forward_t((const float*)x, (float*)y, (uint8_t*)won, p, s);
+    if ((int64_t)H * W >= (int64_t(1) << 31)) return hipErrorInvalidValue;   // (a winner's position is kept in 31 bits)
+    return dtype == kBF16 ? forward_t((const bf16_t*)x, (bf16_t*)y, (uint32_t*)won, p, s) : forward_t((const float*)x, (float*)y, (uint32_t*)won, p, s);
 }
 
 static PoolBlocks pool_blocks(const PoolDims& p, int V) {
@@ -358,30 +377,32 @@ static PoolBlocks pool_blocks(const PoolDims& p, int V) {
     return b;
 }
 
-template <class T>
-static hipError_t backward_t(const T* x, const T* dy, const uint8_t* won, T* dx, const PoolDims& p, int relu, hipStream_t s) {
+template <class T, class W>
+static hipError_t backward_t(const T* dy, const W* won, T* dx, const PoolDims& p, int relu, hipStream_t s) {
     constexpr int V = 16 / sizeof(T);
     const int64_t n = (int64_t)p.B * p.H * p.W * p.C;
-    if (!won)
-        return launch_timed(kcPoolBwd, maxpool_bwd_search_kernel<T>, dim3(cdiv_pool(n, 256)), dim3(256), 0, s, x, dy, dx, p, relu);
     if (p.C % V != 0 || !al16p(dy) || !al16p(dx))
-        return launch_timed(kcPoolBwd, maxpool_bwd_any_kernel<T, 1>, dim3(cdiv_pool(n, 256)), dim3(256), 0, s, dy, won, dx, p, relu);
-    const PoolBlocks b = pool_blocks(p, V);
-    const int64_t total = (int64_t)p.B * b.nh * b.nw * (p.C / V);
-    if (p.stride == 2 && (p.k == 2 || p.k == 3) && total < (int64_t(1) << 30)) {
-        const dim3 grid(cdiv_pool(total, 256));
-        if (p.k == 2) return launch_timed(kcPoolBwd, maxpool_bwd_kernel<T, V, 2, 2>, grid, dim3(256), 0, s, dy, won, dx, p, b, (int)total, relu);
-        return launch_timed(kcPoolBwd, maxpool_bwd_kernel<T, V, 3, 2>, grid, dim3(256), 0, s, dy, won, dx, p, b, (int)total, relu);
+        return launch_timed(kcPoolBwd, maxpool_bwd_any_kernel<T, 1, W>, dim3(cdiv_pool(n, 256)), dim3(256), 0, s, dy, won, dx, p, relu);
+    if constexpr (sizeof(W) == 1) {
+        const PoolBlocks b = pool_blocks(p, V);
+        const int64_t total = (int64_t)p.B * b.nh * b.nw * (p.C / V);
+        if (p.stride == 2 && (p.k == 2 || p.k == 3) && total < (int64_t(1) << 30)) {
+            const dim3 grid(cdiv_pool(total, 256));
+            if (p.k == 2) return launch_timed(kcPoolBwd, maxpool_bwd_kernel<T, V, 2, 2>, grid, dim3(256), 0, s, dy, won, dx, p, b, (int)total, relu);
+            return launch_timed(kcPoolBwd, maxpool_bwd_kernel<T, V, 3, 2>, grid, dim3(256), 0, s, dy, won, dx, p, b, (int)total, relu);
+        }
     }
-    return launch_timed(kcPoolBwd, maxpool_bwd_any_kernel<T, V>, dim3(cdiv_pool(n / V, 256)), dim3(256), 0, s, dy, won, dx, p, relu);
+    return launch_timed(kcPoolBwd, maxpool_bwd_any_kernel<T, V, W>, dim3(cdiv_pool(n / V, 256)), dim3(256), 0, s, dy, won, dx, p, relu);
 }
 
-hipError_t maxpool_backward(int dtype, const void* x, const void* dy, const uint8_t* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad,
-                            int relu_mask, hipStream_t s) {
+hipError_t maxpool_backward(int dtype, const void* dy, const void* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) {
     const PoolDims p = pool_dims(B, H, W, C, k, stride, pad);
     if ((int64_t)B * H * W * C <= 0) return hipSuccess;
-    if (dtype == kBF16) return backward_t((const bf16_t*)x, (const bf16_t*)dy, won, (bf16_t*)dx, p, relu_mask, s);
-    return backward_t((const float*)x, (const float*)dy, won, (float*)dx, p, relu_mask, s);
+    if (maxpool_winner_bytes(k) == 1)
+        return dtype == kBF16 ? backward_t((const bf16_t*)dy, (const uint8_t*)won, (bf16_t*)dx, p, relu_mask, s)
+                              : backward_t((const float*)dy, (const uint8_t*)won, (float*)dx, p, relu_mask, s);
+    return dtype == kBF16 ? backward_t((const bf16_t*)dy, (const uint32_t*)won, (bf16_t*)dx, p, relu_mask, s)
+                          : backward_t((const float*)dy, (const uint32_t*)won, (float*)dx, p, relu_mask, s);
 }
 
 bool maxpool_affine_takes(int dtype, int64_t rows, int C, int k, int stride) {
@@ -399,11 +420,12 @@ static hipError_t affine_t(const T* dy, const uint8_t* won, const T* z, const fl
                         relu);
 }
 
-hipError_t maxpool_affine_backward(int dtype, const void* dy, const uint8_t* won, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& partials,
+hipError_t maxpool_affine_backward(int dtype, const void* dy, const void* winners, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& partials,
                                    int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) {
     const PoolDims p = pool_dims(B, H, W, C, k, stride, pad);
     if ((int64_t)B * H * W * C <= 0) return hipSuccess;
     const int room = (int)(affine_workspace_elems((int64_t)B * H * W, C) / (2 * (size_t)C));   // as many slabs as the affine layer alone has
+    const uint8_t* const won = (const uint8_t*)winners;
     int slabs = 0;
     const hipError_t e = dtype == kBF16 ? affine_t((const bf16_t*)dy, won, (const bf16_t*)z, gain, (bf16_t*)dz, partials.ws, room, p, relu_mask, slabs, s)
                                         : affine_t((const float*)dy, won, (const float*)z, gain, (float*)dz, partials.ws, room, p, relu_mask, slabs, s);
@@ -414,5 +436,5 @@ hipError_t maxpool_affine_backward(int dtype, const void* dy, const uint8_t* won
 }  // namespace tmps
 
 extern "C" int tmps_pool_affine_gradients_joint(int dtype, int64_t positions, int channels, int window, int stride) {
-    return tmps::maxpool_keeps_winners(window) && tmps::maxpool_affine_takes(dtype, positions, channels, window, stride) ? 1 : 0;
+    return tmps::maxpool_affine_takes(dtype, positions, channels, window, stride) ? 1 : 0;
 }

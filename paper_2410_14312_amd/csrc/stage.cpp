@@ -48,9 +48,9 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Partial results of one layer's parameter gradient that may wait for the end of the backward pass.
 static constexpr size_t kLatePartBytes = size_t(16) << 20;
 
-// A pooling layer's winners from row row0 of the stash on (null: it keeps none).
-static uint8_t* winners(const tmps_stage* st, const LayerRT& L, int64_t row0) {
-    return maxpool_keeps_winners(L.d.dims[3]) ? reinterpret_cast<uint8_t*>(st->stash + L.aux_off) + (size_t)row0 * L.out_elems : nullptr;
+// A pooling layer's winners from row row0 of the stash on.
+static void* winners(const tmps_stage* st, const LayerRT& L, int64_t row0) {
+    return st->stash + L.aux_off + (size_t)row0 * L.out_elems * maxpool_winner_bytes(L.d.dims[3]);
 }
 
 static ConvShape conv_shape(const tmps_layer_desc& d, int B) {
@@ -293,7 +293,7 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
         if (L.d.kind == TMPS_SOFTMAX_CE) aux = (size_t)rows_all * L.rps * 4;                  // per-row losses
         if (L.d.kind == TMPS_LAYERNORM) aux = (size_t)rows_all * L.rps * 8;                   // (mean, 1/std) per row
         if (L.d.kind == TMPS_ATTENTION) aux = (size_t)rows_all * L.d.dims[2] * L.d.dims[0] * 4;  // log-sum-exp per head and query
-        if (L.d.kind == TMPS_MAXPOOL && maxpool_keeps_winners(L.d.dims[3])) aux = (size_t)rows_all * L.out_elems;   // every window's winner
+        if (L.d.kind == TMPS_MAXPOOL) aux = (size_t)rows_all * L.out_elems * maxpool_winner_bytes(L.d.dims[3]);   // every window's winner
         if (aux) {
             L.aux_off = soff;
             soff = align_up(soff + aux, 256);
@@ -1015,10 +1015,10 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                 break;
             }
             case TMPS_MAXPOOL: {
-                const uint8_t* won = winners(st, L, row0);
+                const void* won = winners(st, L, row0);
                 const LayerRT* A = t_in >= 0 && st->layers[t_in].d.kind == TMPS_AFFINE && st->layers[t_in].d.dims[2] == d[2] ? &st->layers[t_in] : nullptr;
                 const int64_t rows = (int64_t)M * d[0] * d[1];
-                if (A && won && st->readers[t_in + 1] == 1 && !in_order && maxpool_affine_takes(dt, rows, d[2], d[3], d[4])) {
+                if (A && st->readers[t_in + 1] == 1 && !in_order && maxpool_affine_takes(dt, rows, d[2], d[3], d[4])) {
                     if ((rc = target(A->in_t, T)) != TMPS_OK) return rc;
                     if (T.add) return fail(TMPS_EUNSUPPORTED, "an affine layer on a shared input");
                     const void* const z = A->in_t < 0 ? (const void*)x0 : (const void*)st->out_ptr(st->layers[A->in_t], row0);
@@ -1035,7 +1035,7 @@ int tmps::backward_between(tmps_stage* st, const int* slots, int n_slots, const 
                 if ((rc = target(t_in, T)) != TMPS_OK) return rc;
                 if (T.wanted) {
                     if (T.add || mask_mode == 2) return fail(TMPS_EUNSUPPORTED, "max pooling on a shared or GELU input");
-                    TMPS_GEMM(maxpool_backward(dt, in, g.ptr, won, T.dst, M, d[0], d[1], d[2], d[3], d[4], d[5], mask ? 1 : 0, s));
+                    TMPS_GEMM(maxpool_backward(dt, g.ptr, won, T.dst, M, d[0], d[1], d[2], d[3], d[4], d[5], mask ? 1 : 0, s));
                     commit(t_in, T);
                 }
                 break;

@@ -125,6 +125,7 @@ int main() {
     for (int dtype : {(int)TMPS_F32, bf16}) {
         run("pooling and affine", pooled(L(TMPS_MAXPOOL, {8, 8, 16, 3, 2, 1}), 4 * 4 * 16), dtype, "maxpool_affine_backward", 2);
         run("pooling and affine on another map", pooled(L(TMPS_MAXPOOL, {16, 4, 16, 3, 2, 1}), 8 * 2 * 16), dtype, "maxpool_affine_backward", 2);
+        run("pooling in larger windows", pooled(L(TMPS_MAXPOOL, {4, 4, 64, 12, 4, 5}), 64), dtype, "maxpool_backward", 2);
         run("pooling and affine of fewer channels", pooled(L(TMPS_MAXPOOL, {4, 4, 64, 3, 2, 1}), 2 * 2 * 64), dtype, "maxpool_affine_backward", 0);
         run("pooling and affine of more channels", pooled(L(TMPS_MAXPOOL, {16, 16, 4, 3, 2, 1}), 8 * 8 * 4), dtype, "maxpool_affine_backward", 0);
     }

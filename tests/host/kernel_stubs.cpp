@@ -101,23 +101,23 @@ hipError_t affine_pointwise_backward(const void* dy, const void* z, const void* 
     const hipError_t e = pa.finish(Reduction{pa.ws, gw_affine, 2 * O, (int)slabs, true}, s);
     return e != hipSuccess ? e : pw.finish(Reduction{pw.ws, gw_conv, (int64_t)O * I + O, (int)slabs, false}, s);
 }
-bool maxpool_keeps_winners(int k) { return k <= 11; }
+int maxpool_winner_bytes(int k) { return k <= 11 ? 1 : 4; }
 bool maxpool_affine_takes(int, int64_t, int, int, int) { return kernel_stubs.joint; }
 static size_t pooled(int B, int H, int W, int C, int k, int stride, int pad) { return (size_t)B * ((H + 2 * pad - k) / stride + 1) * ((W + 2 * pad - k) / stride + 1) * C; }
-hipError_t maxpool_affine_backward(int dtype, const void* dy, const uint8_t* won, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& ws, int B, int H, int W, int C, int k, int stride, int pad, int, hipStream_t s) {
+hipError_t maxpool_affine_backward(int dtype, const void* dy, const void* won, const void* z, const float* gain, void* dz, float* dgain_dshift, const Partials& ws, int B, int H, int W, int C, int k, int stride, int pad, int, hipStream_t s) {
     const size_t e = esize(dtype), in = (size_t)B * H * W * C * e, out = pooled(B, H, W, C, k, stride, pad);
     const int slabs = (int)(affine_workspace_elems((int64_t)B * H * W, C) / (2 * C));
     Launch("maxpool_affine_backward").reads(dy, out * e).reads(won, out).reads(z, in).reads(gain, (size_t)C * 4).writes(dz, in).writes(ws.ws, (size_t)slabs * 2 * C * 4);
     return ws.finish(Reduction{ws.ws, dgain_dshift, 2 * C, slabs, true}, s);
 }
-hipError_t maxpool_forward(int dtype, const void* x, void* y, uint8_t* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) {
+hipError_t maxpool_forward(int dtype, const void* x, void* y, void* won, int B, int H, int W, int C, int k, int stride, int pad, hipStream_t s) {
     const size_t e = esize(dtype), out = pooled(B, H, W, C, k, stride, pad);
-    Launch("maxpool_forward").reads(x, (size_t)B * H * W * C * e).writes(y, out * e).writes(won, out);
+    Launch("maxpool_forward").reads(x, (size_t)B * H * W * C * e).writes(y, out * e).writes(won, out * maxpool_winner_bytes(k));
     return hipSuccess;
 }
-hipError_t maxpool_backward(int dtype, const void* x, const void* dy, const uint8_t* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) {
+hipError_t maxpool_backward(int dtype, const void* dy, const void* won, void* dx, int B, int H, int W, int C, int k, int stride, int pad, int relu_mask, hipStream_t s) {
     const size_t e = esize(dtype), out = pooled(B, H, W, C, k, stride, pad);
-    Launch("maxpool_backward").reads(dy, out * e).reads(won, out).writes(dx, (size_t)B * H * W * C * e);
+    Launch("maxpool_backward").reads(dy, out * e).reads(won, out * maxpool_winner_bytes(k)).writes(dx, (size_t)B * H * W * C * e);
     return hipSuccess;
 }
 hipError_t affine_forward(int dtype, const void* x, const float* gain, const float* shift, void* y, int64_t rows, int C, int relu, hipStream_t s) {
