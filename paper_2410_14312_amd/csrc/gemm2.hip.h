@@ -1136,14 +1136,15 @@ __global__ void splitk_finish_kernel(const float* __restrict__ part, Epi epi, in
 
 // The same for 8 consecutive columns per thread (N a multiple of 8, every tensor of the epilogue 16-byte aligned):
 // 16-byte loads of the partial sums and of what the epilogue reads, 16-byte stores; sums in the order of the kernel
-// above (slice z goes to accumulator z % 4).
-template <class Epi>
-__global__ __launch_bounds__(256) void splitk_finish8_kernel(const float* __restrict__ part, Epi epi, int M, int N, int slices) {
+// above (slice z goes to accumulator z % 4).  rows: a loader that knows where a row of the partial sums lies in the result, or anything else.
+struct SameRows {};
+template <class Epi, class Rows>
+__global__ __launch_bounds__(256) void splitk_finish8_kernel(const float* __restrict__ part, Epi epi, int M, int N, int slices, Rows rows) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int n8 = N >> 3;
     if (c >= (int64_t)M * n8) return;
     const int m = (int)(c / n8), n = (int)(c - (int64_t)m * n8) * 8;
-    const int64_t total = (int64_t)M * N, idx = (int64_t)m * epi.ld + n;
+    const int64_t total = (int64_t)M * N, idx = (int64_t)op_out_row(rows, m, 0) * epi.ld + n;
     const typename Epi::Col8 pcol = epi.col8(n);
     const typename Epi::Row8 prow = epi.row8(idx, true);
     const float* p = part + (int64_t)m * N + n;

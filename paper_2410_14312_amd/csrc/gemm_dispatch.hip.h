@@ -165,10 +165,22 @@ static hipError_t run2(int kc, const AOp& A, const BOp& B, const Epi& epi, int M
     if (e != hipSuccess) return e;
     int64_t total = (int64_t)M * N;
     if (N % 8 == 0 && epi.wide_ok() && aligned16(ws))
-        return launch_timed(kcSplitFinish, splitk_finish8_kernel<Epi>, dim3(cdiv(total / 8, 256)), dim3(256), 0, s,
-                            (const float*)ws, epi, M, N, nz);
+        return launch_timed(kcSplitFinish, splitk_finish8_kernel<Epi, SameRows>, dim3(cdiv(total / 8, 256)), dim3(256), 0, s,
+                            (const float*)ws, epi, M, N, nz, SameRows{});
     return launch_timed(kcSplitFinish, splitk_finish_kernel<Epi>, dim3(cdiv(total, 256)), dim3(256), 0, s,
                         (const float*)ws, epi, M, N, nz);
+}
+
+// The same of rows that lie apart in the result (every tensor of the epilogue 16-byte aligned, N a multiple of 8).
+template <class T, class BOp, class Epi>
+static hipError_t run2_strided(int kc, const StridedKC<T>& A, const BOp& B, const Epi& epi, int M, int N, int K, float* ws, hipStream_t s) {
+    const Plan2 p = plan_for(M, N, K, false, sizeof(T), by_k_mode<StridedKC<T>, BOp>());
+    int per, nz;
+    slice_geometry(K, aligned16(ws) && ws ? p.slices : 1, ElemTile<T>::BK, per, nz);
+    if (nz <= 1) return launch2_tile<false>(kc, p, A, B, epi, M, N, K, per, nz, s);
+    const hipError_t e = launch2_tile<false>(kc, p, static_cast<const DenseKC<T>&>(A), B, EpiPartial{ws, N, (int64_t)M * N}, M, N, K, per, nz, s);
+    if (e != hipSuccess) return e;
+    return launch_timed(kcSplitFinish, splitk_finish8_kernel<Epi, StridedKC<T>>, dim3(cdiv((int64_t)M * N / 8, 256)), dim3(256), 0, s, (const float*)ws, epi, M, N, nz, A);
 }
 
 // Weight-gradient style GEMM: fp32 result [rows x cols] followed by the row sums of A (bias gradient).
@@ -354,12 +366,13 @@ static hipError_t conv_dgrad_t(const T* dy, const T* w, const EpiMask<T, T>& epi
         if (v && epi.wide_ok()) return conv_rows<true>(v, kcConvDgrad, dy, w, epi, c, s);
     }
     if (c.rest_done && c.R == 1 && c.S == 1 && c.pad == 0 && epi.add == epi.out && epi.wide_ok()) {
-        // A 1 x 1 filter with a stride reaches one position of stride^2: a dense product over those, added where they lie.  (No k-slices: their partial
-        // sums would be as large as the map.)  Over the whole map three positions in four were read and written for nothing, for a
+        // A 1 x 1 filter with a stride reaches one position of stride^2: a dense product over those, added where they lie.  (In k-slices, which small
+        // maps need, the partial sums are of those positions too: a block's forward and backward pass in fp32, in one slice and in as many as the plan has, 4 images of
+        // 8 x 8 x 64 into 4096 channels 283 and 202 us, one of 14 x 14 x 1024 into 2048 211 and 173.)  Over the whole map three positions in four were read and written for nothing, for a
         // dx that the layer beside it then read once more: 64 images of 56 x 56 x 256 from 512 channels 138 us, of 14 x 14 x 1024 from 2048 119.
         const int Mo = c.B * c.Ho * c.Wo;
         const StridedKC<T> A(DenseKC<T>{dy, Mo, c.Cout, c.Cout}, c.H, c.W, c.stride, c.Ho, c.Wo);
-        return run2(kcConvDgrad, A, DenseRC<T>{w, c.Cin, c.Cout, c.Cin}, epi, Mo, c.Cin, c.Cout, nullptr, s);
+        return run2_strided(kcConvDgrad, A, DenseRC<T>{w, c.Cin, c.Cout, c.Cin}, epi, Mo, c.Cin, c.Cout, ws, s);
     }
     if (c.stride == 2 && c.H % 2 == 0 && c.W % 2 == 0 && c.Cin % 8 == 0) {
         // Rows ordered by the parity of their position, each class walking only the filter taps that reach it:

@@ -649,8 +649,8 @@ static hipError_t dense_dgrad_as(int kc, int dtype, const void* dy, const void* 
             EpiPartial part{ws, Din, (int64_t)B * Din};
             hipError_t e = launch3<true, false, false>(kc, A, Bv, part, B, Din, Dout, plan, s);
             if (e != hipSuccess) return e;
-            return launch_timed(kcSplitFinish, splitk_finish8_kernel<EpiMask<bf16_t, bf16_t>>, dim3(cdiv((int64_t)B * Din / 8, 256)),
-                                dim3(256), 0, s, (const float*)ws, epi, B, Din, plan.slices);
+            return launch_timed(kcSplitFinish, splitk_finish8_kernel<EpiMask<bf16_t, bf16_t>, SameRows>, dim3(cdiv((int64_t)B * Din / 8, 256)),
+                                dim3(256), 0, s, (const float*)ws, epi, B, Din, plan.slices, SameRows{});
         }
         if (fast && g3_narrow_ok(B, Din, Dout) && aligned16(dx) && aligned16(mask) && aligned16(add)) {
             G3Operand<true> A{(const bf16_t*)dy, B, Dout};

@@ -174,6 +174,8 @@ int stage_layout(tmps_stage& st, const tmps_layer_desc* layers, int n_layers, co
                 if (c.stride == 2)   // (the input gradient may walk each position's own taps only)
                     L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)M * c.H * c.W, c.Cin,
                                                                            (int64_t)((c.R + 1) / 2) * ((c.S + 1) / 2) * c.Cout, f32));
+                if (c.stride > 1 && c.R == 1 && c.S == 1)   // (or be formed for the positions that the filter reaches alone)
+                    L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)M * c.Ho * c.Wo, c.Cin, c.Cout, f32));
                 for (int r = 2; r <= cfg->n_micro; ++r)
                     L.ws_elems = std::max(L.ws_elems, gemm_workspace_elems((int64_t)r * mb * c.Ho * c.Wo, c.Cout, kf, f32));
                 break;

@@ -48,3 +48,13 @@ def test_beside_a_join(dtype):
     two = conv(h, h, c, 24, 3, 2, 1, False, src=3)
     run_stage_case([conv(h, h, 8, c, 1, 1, 0, True)] + block + [one, affine(ho, ho, 24, False), two, affine(ho, ho, 24, False), resadd(ho, ho, 24, src_b=3, relu=True)],
                    dtype, 2, 2, seed=4)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("h,cin,width,stride", [(4, 64, 256, 2), (7, 40, 200, 2), (1, 8, 192, 2), (5, 24, 300, 3)])
+def test_in_slices(h, cin, width, stride, dtype):
+    """Few positions and a long contraction: its slices' sums are of the positions that the filter reaches."""
+    from tests.routes import DENSE, _functions
+    block, ho, cout = bottleneck(h, cin, width, stride, True)
+    assert _functions()[0](6 * ho * ho, cin, cout, False, 2 if dtype == "bf16" else 4, DENSE).slices > 1
+    run_stage_case([conv(h, h, 8, cin, 1, 1, 0, True)] + block + [avgpool(ho, ho, cout), linear(cout, 10, False), softmax_ce(10)], dtype, 3, 2, seed=h + cin)
