@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("vocab,s,d,micro,N", [(1, 1, 8, 1, 1), (2, 65, 64, 1, 1), (3, 64, 72, 2, 2), (4, 257, 64, 1, 1), (5, 85, 200, 3, 1), (7, 63, 64, 1, 4), (96, 32, 64, 2, 4),
                                                (500, 40, 8, 3, 2), (2000, 64, 64, 4, 2),
-                                               (65, 512, 32, 8, 4)])   # (16384 rows: beyond the line, 250 to a token)
+                                               (65, 512, 32, 8, 4),   # (16384 rows: beyond the line, 250 to a token)
+                                               (100000, 3, 8, 1, 2), (100001, 3, 8, 1, 2)])   # (few rows, on both sides of the line for tables)
 def test_embedding(vocab, s, d, micro, N, dtype):
     run_stage_case([embedding(vocab, s, d), linear(d, 16, False, rows=s)], dtype, micro, N, seed=vocab + s)
