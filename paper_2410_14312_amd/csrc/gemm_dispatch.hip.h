@@ -219,6 +219,10 @@ static hipError_t run_small(int kc, const AOp& A, const BOp& B, const Epi& epi, 
 
 // A layer normalisation and the dense layer behind it on the small kernel: rows of one piece to a lane, a contraction that four waves share in one step
 // each, and a dense layer that this kernel takes in 16 x 16 tiles by itself.
+// Forward and backward pass of both layers, bound by their launches, in two launches and in one (us): bf16, 64 -> 192 over 16, 64 and 256 rows 20.9 / 22.0 / 20.3 and
+// 18.7 / 19.6 / 18.3, 32 -> 32 over 2048 rows 21.0 and 18.8, 128 -> 512 over 64 rows 20.3 and 18.0; fp32 64 -> 192 20.3 / 20.5 / 20.0 and 18.9 / 18.2 / 17.5, 64 -> 4096 over 16
+// rows 26.2 and 23.7.  The line, where the dense layer alone moves to larger tiles, is on the safe side: in 16 x 16 tiles all the same one launch would take 19.5 for 21.3 (fp32
+// 64 -> 192 over 512 rows), 19.3 for 21.1 (bf16 64 -> 256 over 1024), 20.9 for 21.4 (bf16 64 -> 64 over 2048).
 template <class T> static bool norm_dense_takes(int64_t rows, int D, int N) {
     constexpr int esize = sizeof(T);
     if (D % 8 != 0 || D > 4 * (64 / esize) || !small_is_better(rows, N, D, esize, plan_for(rows, N, D, false, esize, kByKDense))) return false;

@@ -752,7 +752,7 @@ hipError_t dense_backward(int dtype, const void* dy, const void* x, const void* 
                           const void* add, int B, int Din, int Dout, float* ws, const Partials& ws_w, hipStream_t s) {
     const int kind = backward_kind(B, Din, Dout, dtype == kBF16 ? 2 : 4);
     const EpiMask<bf16_t, bf16_t> ex{(bf16_t*)dx, (const bf16_t*)mask, Din, mask_mode, (const bf16_t*)add};
-    if (dtype != kBF16 && mixed_backward_takes(B, Din, Dout) && aligned16(dy) && aligned16(x))
+    if (dtype != kBF16 && kind == kTwo && mixed_backward_takes(B, Din, Dout) && aligned16(dy) && aligned16(x))
         return mixed_backward_f32(kcDenseBackward, (const float*)dy, (const float*)x, (const float*)w, gw,
                                   EpiMask<float, float>{(float*)dx, (const float*)mask, Din, mask_mode, (const float*)add}, B, Din, Dout, s);
     if (kind == kOneSmall) {

@@ -232,8 +232,7 @@ void build_nodes(RunCtx& c, const std::vector<Task>& tasks) {
 // Device time of a pass over `rows` samples, roughly: 5 us for every launch it is expected to make (a contraction one
 // forward and a split now and then, two to three backward; other layers one and two), its operations at the rates that
 // mid-sized contractions reach, and the update at 4 TB/s.  Whole runs take less than their estimate: two mini-batches on one
-// stream 114 us of 166 (tiny fp32 MLP), 266 of 408 (bf16 MLP), 1.96 ms of 3.3 (VGG-16), 13.9 of 17.9 (ResNet-50), 21.6 of 47.8 (GPT-2;
-// 54.9 of 77.9 in 1F1B order).
+// stream 96 us of 166 (tiny fp32 MLP), 235 of 408 (bf16 MLP), 1.90 ms of 3.3 (VGG-16), 11.8 of 17.9 (ResNet-50), 21.7 of 47.8 (GPT-2).
 double pass_us(const tmps_stage& st, int rows, bool backward) {
     double us = 0.0;
     for (const LayerRT& L : st.layers) {
@@ -252,11 +251,11 @@ double pass_us(const tmps_stage& st, int rows, bool backward) {
 // (about 100 us a run) and for every hand-over from stream to stream (about 25 us in a chain of short passes) and gains
 // what the workers' passes overlap: nothing within a single mini-batch, some 5 % of the work where a mini-batch's
 // micro-batches are forwarded together, some 20 % where mini-batches are short against the pipeline (N <= 2) and in 1F1B
-// order.  Measured on K streams and on one: two mini-batches of the tiny fp32 MLP 285 and 114 us, the bf16 MLP 441 and 266,
-// the tiny fp32 transformer 530 and 355, VGG-16 1.95 and 1.96 ms, ResNet-50 13.9 and 13.9, GPT-2 21.0 and 21.6; twenty of VGG-16 19.7 and
-// 20.1 ms, ResNet-50 137 and 141, GPT-2 207 and 221; 1F1B order, VGG-16 5.0 and 5.9 ms, ResNet-50 24.9 and 37.7, GPT-2 44.9 and 54.9.
-// Not in the estimate: a hand-over costs a short pass some 8 us of every run, however long; twenty mini-batches of the bf16 MLP (3.5 and 2.5 ms)
-// or the tiny transformer (4.3 and 3.3) are left on K streams.  One stream wherever less than 0.35 of the estimate is operations mends these and
+// order.  Measured on K streams and on one: two mini-batches of the tiny fp32 MLP 222 and 96 us, the bf16 MLP 464 and 235,
+// the tiny fp32 transformer 455 and 303, VGG-16 1.91 and 1.90 ms, ResNet-50 11.8 and 11.8, GPT-2 21.1 and 21.7; twenty of VGG-16 19.5 and
+// 19.6 ms, ResNet-50 116 and 120, GPT-2 208 and 221; eight batches in 1F1B order, VGG-16 5.1 and 6.0 ms, ResNet-50 11.9 and 17.3, GPT-2 21.7 and 26.5.
+// Not in the estimate: a hand-over costs a short pass some 8 us of every run, however long; twenty mini-batches of the bf16 MLP (3.5 and 2.6 ms)
+// or the tiny transformer (4.1 and 3.4) are left on K streams.  One stream wherever less than 0.35 of the estimate is operations mends these and
 // loses 3 % or more on others (three mini-batches of an fp32 residual network of 9 blocks on 30 images of 99 x 99).
 bool serial_is_quicker(const RunCtx& c) {
     double total = 0.0;
