@@ -111,16 +111,17 @@ hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const
                       const Partials& ws, hipStream_t s);
 size_t conv_wgrad_workspace_elems(int dtype, const ConvShape& c);   // fp32, for its partial results
 
-// Forward pass of a 1 x 1 convolution of unit stride from 64 channels to 256 over P positions with its affine layer and, if res is given, the join (as conv_affine_forward, bf16);
-// next: also the following convolution from those 256 channels to 64 with its affine layer (its x, res and again are not used).  All of it on 16 bytes.
+// Forward pass of a 1 x 1 convolution of unit stride over P positions with its affine layer and, if res is given, the join (as conv_affine_forward, bf16);
+// next: also the following convolution from those channels back to Cin with its affine layer (its x, res and again are not used).  All of it on 16 bytes.
+// pointwise_forward_takes: where that is quicker, without and with a next one.
 struct PointwiseForward {
     const void *x, *w, *res;
     const float *bias, *gain, *shift;
     void *z, *y, *again;
     int relu;
 };
-bool pointwise_forward_takes(int64_t P, int Cin, int Cout);
-hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, hipStream_t s);
+bool pointwise_forward_takes(int64_t P, int Cin, int Cout, bool next);
+hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, int Cin, int Cout, hipStream_t s);
 
 // Backward pass of a 1 x 1 convolution of unit stride (x [P][I] -> z [P][O]) and the affine layer that alone reads its result, in one pass: dy is the affine layer's
 // incoming gradient, dx the convolution's input gradient (add: joined first, may be dx; masked: then zero where x <= 0), gw_affine and gw_conv as affine_backward and

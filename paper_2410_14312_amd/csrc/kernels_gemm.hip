@@ -793,8 +793,8 @@ hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const fl
     const int M = c.B * c.Ho * c.Wo, K = c.R * c.S * c.Cin;
     const bf16_t *xb = (const bf16_t*)x, *wb = (const bf16_t*)w;
     const EpiConvAffine<bf16_t> epi{(bf16_t*)z, bias, c.Cout, gain, shift, (bf16_t*)again, (const bf16_t*)res, (bf16_t*)yout, relu};
-    if (pointwise(c) && pointwise_forward_takes(M, c.Cin, c.Cout) && aligned16(x) && aligned16(w) && epi.wide_ok())
-        return pointwise_forward(PointwiseForward{x, w, res, bias, gain, shift, z, yout, again, relu}, nullptr, M, s);
+    if (pointwise(c) && pointwise_forward_takes(M, c.Cin, c.Cout, false) && aligned16(x) && aligned16(w) && epi.wide_ok())
+        return pointwise_forward(PointwiseForward{x, w, res, bias, gain, shift, z, yout, again, relu}, nullptr, M, c.Cin, c.Cout, s);
     if (pointwise(c) && c.Cin % 8 == 0 && aligned16(x) && aligned16(w)) {
         if (g3_forward_ok(M, c.Cout, K) && aligned16(z) && aligned16(bias) && aligned16(gain) && aligned16(shift) &&
             aligned16(again) && aligned16(res) && aligned16(yout))

@@ -2,8 +2,8 @@
 //
 // On the way back the affine layer forms g = gain dY and its own sums, the convolution dW = g^T x and dx = mask(g W + add).  As launches of their own these
 // read dY, z and x, write g, read it twice more and read x again for the mask; the bottleneck blocks' maps of 64 and 256 channels are bound by exactly that.
-// Here a workgroup takes a run of positions, 64 at a time, and reads dY, z, x and add once: g and x go to LDS, dx comes from there and from W, which the waves keep
-// in registers, and dW stays in the accumulators until the workgroup's last position.  One workgroup of eight waves to a compute unit; the next positions' loads are on
+// Here a workgroup takes a run of positions, 64 at a time, and reads dY, z, x and add once: g and x go to LDS, dx comes from there and from W, which lies in LDS too,
+// transposed, for the workgroup's whole run and is read there in every step, and dW stays in the accumulators until the workgroup's last position.  One workgroup of eight waves to a compute unit; the next positions' loads are on
 // their way during all of a step's multiplies.  What remains beside the maps is each workgroup's partial sums, 66 KB for 256 x 64.
 //
 // g is rounded to bf16 as where it was stored, dx once after add and mask: the same values but for the order of sums.
@@ -25,7 +25,7 @@ typedef float f32x4v_t __attribute__((ext_vector_type(4)));
 static constexpr int kPwThreads = 512, kPwRows = 64;   // positions of a step
 // Row strides in LDS, bytes: whole 16-byte pieces, an odd number of them modulo 16, so that 16 rows read at one column and 4 rows of 64 bytes read transposed
 // fall on different banks (64 values: the latter two by two).
-__host__ __device__ constexpr int pw_stride(int n) { return n == 64 ? 144 : n == 128 ? 336 : 592; }
+__host__ __device__ constexpr int pw_stride(int n) { return n == 32 ? 80 : n == 64 ? 144 : n == 128 ? 336 : 592; }
 template <int O, int I> constexpr int pw_lds_bytes() { return kPwRows * (pw_stride(O) + pw_stride(I) + (I + 4) * 4) + I * pw_stride(O); }
 
 __device__ __forceinline__ void pw_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -227,27 +227,30 @@ __global__ __launch_bounds__(kPwThreads) void affine_pointwise_bwd_kernel(const 
     }
 }
 
-// ---- forward: 64 channels to 256, and from those to 64 again ------------------------------------------------------------------------------------------------
+// ---- forward: C channels to W, and from those to C again -----------------------------------------------------------------------------------------------------
 // z = x w^T + bias, y = act(gain z + shift + res) as EpiConvAffine forms and rounds them; PAIR: and the next block's first convolution, which reads y, with its
-// affine layer, from LDS instead of memory.  A workgroup of eight waves takes a run of positions, 64 at a time; a wave owns 32 of the wide result's channels (and 16 of the
-// narrow one's for half of the positions) and keeps their weights in registers; x and res of the next step are on their way during a step.  A wave's two blocks of 16
+// affine layer, from LDS instead of memory.  A workgroup takes a run of positions, 64 at a time; it has a wave for every 32 of the wide result's channels (which also has 16 of
+// the narrow one's for its share of the positions) and keeps their weights in registers; x and res of the next step are on their way during a step.  A wave's two blocks of 16
 // channels are interleaved in fours, so that a lane holds 8 consecutive channels of a position.
 struct PwWide {
-    const bf16_t *x, *w, *res;   // [P][64], [256][64], [P][256] or null
+    const bf16_t *x, *w, *res;   // [P][C], [W][C], [P][W] or null
     const float *bias, *gain, *shift;
-    bf16_t *z, *y, *again;   // [P][256] each; again: y once more, or null
+    bf16_t *z, *y, *again;   // [P][W] each; again: y once more, or null
     int relu;
 };
 struct PwNarrow {
-    const bf16_t* w;   // [64][256]
+    const bf16_t* w;   // [C][W]
     const float *bias, *gain, *shift;
-    bf16_t *z, *y;     // [P][64] each
+    bf16_t *z, *y;     // [P][C] each
     int relu;
 };
 
-template <bool PAIR>
-__global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwNarrow b, int P, int per) {
-    constexpr int C = 64, W = 256, SX = pw_stride(C), SY = pw_stride(W);
+template <int C, int W, bool PAIR>
+__global__ __launch_bounds__(2 * W) void pointwise_fwd_kernel(PwWide a, PwNarrow b, int P, int per) {
+    constexpr int T = 2 * W, SX = pw_stride(C), SY = pw_stride(W), CP = C / 8;
+    constexpr int NX = kPwRows * CP / T, KX = C / 32;                    // pieces of x of a thread; steps of 32 k of the wide result
+    constexpr int CB = C / 16, NH = PAIR ? 4 * CB * 32 / W : 1, KN = PAIR ? W / 32 : 1;   // narrow result: blocks of channels, of a wave's positions; steps
+    static_assert(NX >= 1 && W >= 2 * C, "a piece of x to every thread, a block of the narrow result's channels to every wave");
     __shared__ __attribute__((aligned(16))) unsigned char xs[kPwRows * SX];
     __shared__ __attribute__((aligned(16))) unsigned char ys[PAIR ? kPwRows * SY : 16];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quarter = lane >> 4;
@@ -259,10 +262,20 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwN
     bf16_t *const z = a.z + (int64_t)p0 * W, *const y = a.y + (int64_t)p0 * W, *const again = a.again ? a.again + (int64_t)p0 * W : nullptr;
 
     const bf16x8_t none = {};
-    const int xr = tid >> 3, xc = (tid & 7) * 8;
+    const int xr = tid / CP, xc = tid % CP * 8;
     const int ch = wave * 32 + quarter * 8;   // this lane's channels of the wide result: ch .. ch + 7
-    bf16x8_t vx, vr[4];
-    auto request_x = [&](int base) { vx = base + xr < mine ? *reinterpret_cast<const bf16x8_t*>(x + (uint32_t)((base + xr) * C + xc)) : none; };
+    bf16x8_t vx[NX], vr[4];
+    auto request_x = [&](int base) {
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+            const int p = base + xr + n * (T / CP);
+            vx[n] = p < mine ? *reinterpret_cast<const bf16x8_t*>(x + (uint32_t)(p * C + xc)) : none;
+        }
+    };
+    auto keep_x = [&]() {
+#pragma unroll
+        for (int n = 0; n < NX; ++n) *reinterpret_cast<bf16x8_t*>(xs + (xr + n * (T / CP)) * SX + xc * 2) = vx[n];
+    };
     auto request_res = [&](int base) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -273,23 +286,23 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwN
     request_x(0);
     request_res(0);
 
-    bf16x8_t wf[2][2];   // [block][step of 32 k]: row l16 of block j is channel 32 wave + 8 (l16 / 4) + 4 j + l16 % 4
+    bf16x8_t wf[2][KX];   // [block][step of 32 k]: row l16 of block j is channel 32 wave + 8 (l16 / 4) + 4 j + l16 % 4
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) wf[j][k] = *reinterpret_cast<const bf16x8_t*>(a.w + (wave * 32 + (l16 >> 2) * 8 + j * 4 + (l16 & 3)) * C + k * 32 + quarter * 8);
+        for (int k = 0; k < KX; ++k) wf[j][k] = *reinterpret_cast<const bf16x8_t*>(a.w + (wave * 32 + (l16 >> 2) * 8 + j * 4 + (l16 & 3)) * C + k * 32 + quarter * 8);
     float g[8], sh[8], bi[8];
     load8(a.gain + ch, g);
     load8(a.shift + ch, sh);
 #pragma unroll
     for (int e = 0; e < 8; ++e) bi[e] = a.bias ? a.bias[ch + e] : 0.0f;
-    // the narrow result: channels 16 (wave % 4) + 4 quarter + 0 .. 3, positions 32 (wave / 4) + 16 h + l16
-    const int cn = (wave & 3) * 16, ph = wave >> 2;
-    bf16x8_t wn[PAIR ? 8 : 1];
+    // the narrow result: channels 16 (wave % CB) + 4 quarter + 0 .. 3, positions 16 NH (wave / CB) + 16 h + l16
+    const int cn = wave % CB * 16, pn = wave / CB * (16 * NH);
+    bf16x8_t wn[KN];
     float gn[4], sn[4], bn[4];
     if constexpr (PAIR) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) wn[k] = *reinterpret_cast<const bf16x8_t*>(b.w + (cn + l16) * W + k * 32 + quarter * 8);
+        for (int k = 0; k < KN; ++k) wn[k] = *reinterpret_cast<const bf16x8_t*>(b.w + (cn + l16) * W + k * 32 + quarter * 8);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             gn[e] = b.gain[cn + quarter * 4 + e];
@@ -298,7 +311,7 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwN
         }
     }
 
-    *reinterpret_cast<bf16x8_t*>(xs + xr * SX + xc * 2) = vx;
+    keep_x();
     for (int base = 0; base < mine; base += kPwRows) {
         const bool more = base + kPwRows < mine;
         if (more) request_x(base + kPwRows);
@@ -309,7 +322,7 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwN
 #pragma unroll
             for (int j = 0; j < 2; ++j) d[j][c] = f32x4v_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < KX; ++k) {
                 const bf16x8_t f = *reinterpret_cast<const bf16x8_t*>(xs + (c * 16 + l16) * SX + k * 64 + quarter * 16);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) d[j][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][k], f, d[j][c], 0, 0, 0);
@@ -338,18 +351,19 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwN
         }
         if (more) request_res(base + kPwRows);
         pw_barrier();
-        if (more) *reinterpret_cast<bf16x8_t*>(xs + xr * SX + xc * 2) = vx;
+        if (more) keep_x();
         if constexpr (PAIR) {
-            f32x4v_t n[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+            f32x4v_t n[NH];
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
+            for (int h = 0; h < NH; ++h) n[h] = f32x4v_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    n[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wn[k], *reinterpret_cast<const bf16x8_t*>(ys + (ph * 32 + h * 16 + l16) * SY + k * 64 + quarter * 16), n[h],
-                                                                   0, 0, 0);
+            for (int k = 0; k < KN; ++k)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int p = base + ph * 32 + h * 16 + l16;
+                for (int h = 0; h < NH; ++h)
+                    n[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wn[k], *reinterpret_cast<const bf16x8_t*>(ys + (pn + h * 16 + l16) * SY + k * 64 + quarter * 16), n[h], 0, 0, 0);
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                const int p = base + pn + h * 16 + l16;
                 typedef bf16_t bf16x4_t __attribute__((ext_vector_type(4)));
                 bf16x4_t zo, yo;
 #pragma unroll
@@ -369,15 +383,38 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_fwd_kernel(PwWide a, PwN
     }
 }
 
-bool pointwise_forward_takes(int64_t P, int Cin, int Cout) { return Cin == 64 && Cout == 256 && P >= 4096 && P < (int64_t(1) << 31) - 4096; }
+// Layers that widen 32 or 64 channels to twice or four times as many (a bottleneck block's last one).  The contractions' kernels and this one over 1024, 4096, 16384, 65536
+// and 200704 positions (us): 32 -> 64 5.0 / 5.5 / 6.4 / 10.4 / 20.0 and 4.5 / 4.9 / 5.0 / 8.0 / 13.0, 32 -> 128 5.3 / 5.3 / 8.5 / 11.7 / 31.0 and 5.0 / 5.0 / 6.9 / 10.2 /
+// 20.4, 64 -> 128 5.0 / 6.0 / 8.4 / 11.7 / 32.1 and 5.4 / 5.6 / 7.5 / 10.6 / 23.0, 64 -> 256 5.2 / 7.2 / 11.6 / 21.3 / 62 and 6.1 / 6.6 / 8.6 / 15.6 / 39.  As wide as
+// their input they gain at some sizes and lose at others (64 -> 64 over 32768 8.5 and 6.8, over 65536 9.4 and 9.7), and from 128 channels, whose weights take the registers of
+// what should be on its way, they lose (128 -> 256 over 65536 15.5 and 21, 128 -> 512 over 4096 6.3 and 9.1).  With the next convolution a launch is saved as well: all
+// convolutions of a block and the next one's first over 256, 1024, 4096, 16384 and 200704 positions, 32 and 64 channels 18.0 / 18.5 / 18.9 / 19.0 / 75 and 13.2 / 13.0 / 13.9 / 16.7 / 57,
+// 32 and 128 17.5 / 18.3 / 19.0 / 20.8 / 98 and 13.7 / 13.4 / 14.9 / 17.0 / 71, 64 and 128 17.8 / 18.4 / 19.0 / 21.5 / 103 and 14.5 / 15.2 / 15.6 / 19.6 / 88; 64 and 256
+// as a stage, forward and backward, 256 to 3840 positions 51.4 / 54.7 / 53.8 / 60.4 / 66.1 / 70.1 / 65.2 and 50.4 / 53.6 / 52.8 / 59.2 / 64.9 / 68.6 / 63.8.
+bool pointwise_forward_takes(int64_t P, int Cin, int Cout, bool next) {
+    return (Cin == 32 || Cin == 64) && (Cout == 2 * Cin || Cout == 4 * Cin) && P >= (next ? 256 : 4096) && P < (int64_t(1) << 31) - 4096;
+}
 
-hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, hipStream_t s) {
+// Sixteen waves to a compute unit, eight with a second layer.
+template <int C, int W, bool PAIR>
+static hipError_t launch_pointwise_forward(const PwWide& a, const PwNarrow& b, int64_t P, hipStream_t s) {
+    constexpr int most = (PAIR ? 8 : 16) * 256 * 32 / W;
+    const int grid = (int)std::min<int64_t>(most, (P + 31) / 32), per = (int)((P + grid - 1) / grid);
+    return launch_timed(kcConvFwd, pointwise_fwd_kernel<C, W, PAIR>, dim3(grid), dim3(2 * W), 0, s, a, b, (int)P, per);
+}
+
+hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, int Cin, int Cout, hipStream_t s) {
     const PwWide a{(const bf16_t*)f.x, (const bf16_t*)f.w, (const bf16_t*)f.res, f.bias, f.gain, f.shift, (bf16_t*)f.z, (bf16_t*)f.y, (bf16_t*)f.again, f.relu};
     PwNarrow b{};
     if (next) b = PwNarrow{(const bf16_t*)next->w, next->bias, next->gain, next->shift, (bf16_t*)next->z, (bf16_t*)next->y, next->relu};
-    const int grid = (int)std::min<int64_t>(next ? 256 : 512, (P + 31) / 32), per = (int)((P + grid - 1) / grid);
-    if (next) return launch_timed(kcConvFwd, pointwise_fwd_kernel<true>, dim3(grid), dim3(kPwThreads), 0, s, a, b, (int)P, per);
-    return launch_timed(kcConvFwd, pointwise_fwd_kernel<false>, dim3(grid), dim3(kPwThreads), 0, s, a, b, (int)P, per);
+#define TMPS_POINTWISE(c, w) \
+    if (Cin == c && Cout == w) return next ? launch_pointwise_forward<c, w, true>(a, b, P, s) : launch_pointwise_forward<c, w, false>(a, b, P, s)
+    TMPS_POINTWISE(32, 64);
+    TMPS_POINTWISE(32, 128);
+    TMPS_POINTWISE(64, 128);
+    TMPS_POINTWISE(64, 256);
+#undef TMPS_POINTWISE
+    return hipErrorInvalidValue;
 }
 
 // Partial results stay within the 16 MB that a backward pass keeps until its end, a workgroup to a compute unit.
@@ -427,5 +464,5 @@ extern "C" int tmps_pointwise_gradients_joint(int dtype, int64_t positions, int 
     return tmps::affine_pointwise_takes(dtype, positions, cout, cin) ? 1 : 0;
 }
 extern "C" int tmps_pointwise_forward_joint(int dtype, int64_t positions, int cin, int cout) {
-    return dtype == tmps::kBF16 && tmps::pointwise_forward_takes(positions, cin, cout) ? 1 : 0;
+    return dtype == tmps::kBF16 && tmps::pointwise_forward_takes(positions, cin, cout, true) ? 1 : 0;
 }

@@ -644,13 +644,13 @@ int tmps::forward_with_workspace(tmps_stage* st, int slot, int count, const void
                         // the next block's first convolution, which reads the join as a map of its channels, in the same launch
                         if (dt == kBF16 && li + 4 < nl && pointwise_below(*st, (int)li + 1) && pointwise_below(*st, (int)li + 4) && st->layers[li + 3].in_t == (int)li + 2 &&
                             st->layers[li + 3].act == 0 && st->readers[li + 4] == 1 && st->layers[li + 3].d.dims[2] == d[3] && st->layers[li + 3].d.dims[3] == d[2] && li + 4 != out_layer &&
-                            pointwise_forward_takes((int64_t)mb * d[0] * d[1], d[2], d[3])) {
+                            pointwise_forward_takes((int64_t)mb * d[0] * d[1], d[2], d[3], true)) {
                             const LayerRT &C = st->layers[li + 3], &B = st->layers[li + 4];
                             const PointwiseForward f{in, st->wptr(L), b, st->bptr(L), st->master + A.w_off, st->master + A.b_off, out, st->out_ptr(J, row0), nullptr, J.relu};
                             const PointwiseForward n{nullptr, st->wptr(C), nullptr, st->bptr(C), st->master + B.w_off, st->master + B.b_off, st->out_ptr(C, row0),
                                                      st->out_ptr(B, row0), nullptr, B.relu};
                             if (on16({f.x, f.w, f.res, f.gain, f.shift, f.z, f.y, n.w, n.z, n.y})) {
-                                TMPS_GEMM(pointwise_forward(f, &n, (int64_t)mb * d[0] * d[1], s));
+                                TMPS_GEMM(pointwise_forward(f, &n, (int64_t)mb * d[0] * d[1], d[2], d[3], s));
                                 li += 4;
                                 break;
                             }

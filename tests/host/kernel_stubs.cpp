@@ -83,9 +83,9 @@ hipError_t conv_wgrad(int dtype, const void* dy, const void* x, float* gw, const
     Launch("conv_wgrad").reads(dy, (size_t)c.B * c.Ho * c.Wo * c.Cout * e).reads(x, (size_t)c.B * c.H * c.W * c.Cin * e).writes(ws.ws, 2 * count * 4);
     return ws.finish(Reduction{ws.ws, gw, (int64_t)count, 2, false}, s);
 }
-bool pointwise_forward_takes(int64_t, int Cin, int Cout) { return kernel_stubs.joint && Cout == 4 * Cin; }
-hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, hipStream_t) {
-    const size_t c = 64, w = 256, narrow = (size_t)P * c * 2, wide = (size_t)P * w * 2;   // (the kernel's widths)
+bool pointwise_forward_takes(int64_t, int Cin, int Cout, bool) { return kernel_stubs.joint && Cout >= Cin; }
+hipError_t pointwise_forward(const PointwiseForward& f, const PointwiseForward* next, int64_t P, int Cin, int Cout, hipStream_t) {
+    const size_t c = Cin, w = Cout, narrow = (size_t)P * c * 2, wide = (size_t)P * w * 2;
     const Launch l(next ? "pointwise_forward of two" : "pointwise_forward");
     l.reads(f.x, narrow).reads(f.w, w * c * 2).reads(f.bias, w * 4).reads(f.gain, w * 4).reads(f.shift, w * 4).reads(f.res, wide).writes(f.z, wide).writes(f.y, wide)
         .writes(f.again, wide);

@@ -1,4 +1,4 @@
-"""A 1 x 1 convolution and the affine layer behind it, forward from 64 channels to 256 and their gradients in one pass: every pair of widths, positions that end inside a step of 64, a piece of 16 and a
+"""A 1 x 1 convolution and the affine layer behind it, forward to twice and four times as many channels and their gradients in one pass: every pair of widths, positions that end inside a step of 64, a piece of 16 and a
 workgroup's run, with and without ReLU below, a gradient to join; against sums of the same bf16 values in 64 bits."""
 import ctypes as C
 
@@ -115,3 +115,59 @@ def test_forward_is_as_its_layers_round(B, h, w, relu):
     assert float((got != want).double().mean()) < 1e-3
     # (a z on the other side of its rounding, 2^-8 of it, times a gain below 2, and y's own rounding)
     assert float(((got.double() - want.double()).abs() - 2.0 ** -7 * (z.double().abs() * 2 + want.double().abs())).max()) <= 0
+
+
+FORWARD = [(32, 64), (32, 128), (64, 128), (64, 256)]   # into the convolution, out of it
+
+
+def forward_takes(P, I, O, following):
+    f = getattr(load_library(), "_ZN4tmps23pointwise_forward_takesEliib")
+    f.restype, f.argtypes = C.c_bool, [C.c_long, C.c_int, C.c_int, C.c_bool]
+    return f(P, I, O, following)
+
+
+def test_the_rule_of_the_forward_pass():
+    for i, o in FORWARD:
+        assert forward_takes(4096, i, o, False) and forward_takes(256, i, o, True) and not forward_takes(4095, i, o, False) and not forward_takes(255, i, o, True)
+        assert not forward_takes(20000, o, i, False) and not forward_takes(20000, i, i, True)
+    assert not forward_takes(20000, 128, 256, False) and not forward_takes(20000, 128, 512, True) and not forward_takes(20000, 16, 64, False)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,h,w", [(1, 64, 64), (5, 37, 37), (2, 120, 73)])
+@pytest.mark.parametrize("cin,cout", FORWARD)
+def test_forward_of_every_pair_of_widths(cin, cout, B, h, w):
+    """Sums in 64 bits, rounded where the layers store, with a second place for the result: beside them only neighbours of a rounding may differ."""
+    import torch
+    from paper_2410_14312_amd import Stage
+
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(h + w + cin + cout)
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0", dtype=torch.float32)
+    P = B * h * w
+    wt, bias, gain, shift = randn(cout, 1, 1, cin) / cin ** 0.5, 0.1 * randn(cout), 1 + 0.2 * randn(cout), 0.1 * randn(cout)
+    st = Stage([conv(h, w, cin, cout, 1, 1, 0, False), affine(h, w, cout, True)], "bf16", B, 1, 1, 0.1, 0.9, borrow_input=True)
+    st.set_params([{"w": wt.cpu().numpy(), "b": bias.cpu().numpy()}, {"w": gain.cpu().numpy(), "b": shift.cpu().numpy()}])
+    x = randn(B, h * w * cin).bfloat16()
+    y = torch.full((B, h * w * cout), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    st.forward_micro(0, x, y=y)
+    torch.cuda.synchronize()
+    z = (x.view(P, cin).double() @ wt.view(cout, cin).bfloat16().double().t() + bias.double()).bfloat16()
+    want = torch.relu(gain.double() * z.double() + shift.double()).bfloat16()
+    got = y.view(P, cout)
+    assert float((got != want).double().mean()) < 1e-3
+    # (a z on the other side of its rounding, 2^-8 of it, times a gain below 2, and y's own rounding)
+    assert float(((got.double() - want.double()).abs() - 2.0 ** -7 * (z.double().abs() * 2 + want.double().abs())).max()) <= 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("h,w,micro", [(16, 16, 1), (17, 19, 1), (8, 9, 4), (64, 65, 1), (15, 17, 1)])
+@pytest.mark.parametrize("cin,cout", FORWARD)
+def test_join_and_the_next_convolution_of_every_pair_of_widths(cin, cout, h, w, micro):
+    """From 256 positions of a micro-batch on in one launch (the last case: 255), with positions off 16, 32 and 64."""
+    from tests.test_gpu_stage import run_stage_case
+    from workloads.configs import resadd
+
+    block = [conv(h, w, cout, cin, 1, 1, 0, False), affine(h, w, cin, True), conv(h, w, cin, cout, 1, 1, 0, False), affine(h, w, cout, False, init_gain=0.2),
+             resadd(h, w, cout, src_b=5, relu=True)]
+    run_stage_case([conv(h, w, 8, cout, 1, 1, 0, True)] + block + block[:2] + [conv(h, w, cin, 8, 1, 1, 0, False)], "bf16", micro, 2, seed=h + cin + cout, deep=True)
