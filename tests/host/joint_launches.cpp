@@ -30,21 +30,23 @@ struct OneStage {
         tmps_stage_destroy(st);
         for (void* p : r) free(p);
     }
-    // A mini-batch and the update, with and without the gradient of the input, with a second place for the result.
+    // A mini-batch and the update, without and with the gradient of the input, in memory of its own or over the upstream one, with a second place for the result.
     void step() {
         const size_t M = (size_t)c.micro_batch * c.n_micro, in = tmps_stage_input_elems(st) * 4, out = tmps_stage_output_elems(st) * 4;
         std::vector<float> x(M * in), y(c.micro_batch * out), dy(M * out), dx(M * in);   // (on 16 bytes)
         std::vector<int32_t> labels(M);
         std::vector<int> slots;
         const size_t esz = c.dtype == TMPS_F32 ? 4 : 2;
-        for (int want = 0; want < 2; ++want) {
+        std::vector<float> same(M * (in > out ? in : out));
+        for (int want = 0; want < 3; ++want) {
             slots.clear();
             for (int j = 0; j < c.n_micro; ++j) {
                 const char* xj = reinterpret_cast<const char*>(x.data()) + (size_t)j * c.micro_batch * (in / 4) * esz;
                 expect(tmps_forward_micro(st, j, xj, y.data(), c.is_last ? labels.data() : nullptr, nullptr, nullptr) == TMPS_OK, "forward");
                 slots.push_back(j);
             }
-            expect(tmps_backward(st, slots.data(), c.n_micro, c.is_last ? nullptr : dy.data(), want ? dx.data() : nullptr, nullptr) == TMPS_OK, "backward");
+            expect(tmps_backward(st, slots.data(), c.n_micro, c.is_last ? nullptr : want == 2 ? same.data() : dy.data(),
+                                 want == 2 ? same.data() : want ? dx.data() : nullptr, nullptr) == TMPS_OK, "backward");
             expect(tmps_update(st, nullptr) == TMPS_OK, "update");
         }
     }
@@ -75,7 +77,7 @@ struct OneStage {
     }
 };
 
-// `launch` is made this many times in two mini-batches (-1: at all)
+// `launch` is made this many times in three mini-batches (-1: at all)
 static void run(const char* what, std::vector<tmps_layer_desc> layers, int dtype, const char* launch, int times, int micro = 2, int N = 2) {
     kernel_stubs.clear();
     OneStage s(layers, dtype, micro, N);
@@ -93,8 +95,8 @@ int main() {
 
     // a convolution and the affine layer that reads it
     for (int dtype : {(int)TMPS_F32, bf16}) {
-        run("conv and affine", {L(TMPS_CONV2D, {4, 4, 8, 16, 3, 3, 1, 1}), L(TMPS_AFFINE, {4, 4, 16}, R)}, dtype, "conv_affine_forward", 4);
-        run("conv and affine of the same channels on another map", {L(TMPS_CONV2D, {4, 4, 8, 16, 3, 3, 1, 1}), L(TMPS_AFFINE, {8, 2, 16}, R)}, dtype, "conv_affine_forward", 4);
+        run("conv and affine", {L(TMPS_CONV2D, {4, 4, 8, 16, 3, 3, 1, 1}), L(TMPS_AFFINE, {4, 4, 16}, R)}, dtype, "conv_affine_forward", 6);
+        run("conv and affine of the same channels on another map", {L(TMPS_CONV2D, {4, 4, 8, 16, 3, 3, 1, 1}), L(TMPS_AFFINE, {8, 2, 16}, R)}, dtype, "conv_affine_forward", 6);
         run("conv and affine of other channels", {L(TMPS_CONV2D, {4, 4, 8, 16, 3, 3, 1, 1}), L(TMPS_AFFINE, {8, 8, 4}, R)}, dtype, "conv_affine_forward", 0);
         run("conv and affine of more channels", {L(TMPS_CONV2D, {4, 4, 8, 16, 3, 3, 1, 1}), L(TMPS_AFFINE, {2, 2, 64}, R)}, dtype, "conv_affine_forward", 0);
     }
@@ -112,7 +114,7 @@ int main() {
                                             L(TMPS_CONV2D, {4, 4, 64, 256, 1, 1, 1, 0}), L(TMPS_AFFINE, {4, 4, 256}), L(TMPS_RESADD, {4, 4, 256, 5}, R), conv, aff, last};
     };
     const auto pair = "pointwise_forward of two";
-    run("join and convolution", blocks(L(TMPS_CONV2D, {4, 4, 256, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {4, 4, 64}, R), L(TMPS_CONV2D, {4, 4, 64, 8, 1, 1, 1, 0})), bf16, pair, 4);
+    run("join and convolution", blocks(L(TMPS_CONV2D, {4, 4, 256, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {4, 4, 64}, R), L(TMPS_CONV2D, {4, 4, 64, 8, 1, 1, 1, 0})), bf16, pair, 6);
     run("join and convolution that reads other channels", blocks(L(TMPS_CONV2D, {8, 8, 64, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {8, 8, 64}, R), L(TMPS_CONV2D, {8, 8, 64, 8, 1, 1, 1, 0})),
         bf16, pair, 0);
     run("join, convolution and affine of other channels", blocks(L(TMPS_CONV2D, {4, 4, 256, 64, 1, 1, 1, 0}), L(TMPS_AFFINE, {8, 8, 16}, R), L(TMPS_CONV2D, {8, 8, 16, 8, 1, 1, 1, 0})),
@@ -125,13 +127,51 @@ int main() {
     for (int dtype : {(int)TMPS_F32, bf16}) {
         run("pooling and affine", pooled(L(TMPS_MAXPOOL, {8, 8, 16, 3, 2, 1}), 4 * 4 * 16), dtype, "maxpool_affine_backward", 2);
         run("pooling and affine on another map", pooled(L(TMPS_MAXPOOL, {16, 4, 16, 3, 2, 1}), 8 * 2 * 16), dtype, "maxpool_affine_backward", 2);
-        run("pooling in larger windows", pooled(L(TMPS_MAXPOOL, {4, 4, 64, 12, 4, 5}), 64), dtype, "maxpool_backward", 2);
+        run("pooling in larger windows", pooled(L(TMPS_MAXPOOL, {4, 4, 64, 12, 4, 5}), 64), dtype, "maxpool_backward", 3);
         run("pooling and affine of fewer channels", pooled(L(TMPS_MAXPOOL, {4, 4, 64, 3, 2, 1}), 2 * 2 * 64), dtype, "maxpool_affine_backward", 0);
         run("pooling and affine of more channels", pooled(L(TMPS_MAXPOOL, {16, 16, 4, 3, 2, 1}), 8 * 8 * 4), dtype, "maxpool_affine_backward", 0);
     }
     // a layer normalisation and the dense layer behind it
     for (int dtype : {(int)TMPS_F32, bf16})
         run("norm and dense", {L(TMPS_LAYERNORM, {16, 3}), L(TMPS_LINEAR, {16, 24, 0, 3}, TMPS_FLAG_GELU), L(TMPS_LINEAR, {24, 16, 2, 3}), L(TMPS_LAYERNORM, {16, 3}),
-                               L(TMPS_LINEAR, {16, 16, 1, 3}, R)}, dtype, "norm_dense_forward", 8);
+                               L(TMPS_LINEAR, {16, 16, 1, 3}, R)}, dtype, "norm_dense_forward", 12);
+    // bottleneck blocks: one with a strided projection, whose input gradient waits for the other readers of the block's input, and one without, at the stage input, behind
+    // a layer with an activation and one without, and in front of another of either kind
+    auto bottleneck = [&](int h, int cin, int width, int stride, bool project) {
+        const int ho = (h - 1) / stride + 1, cout = 4 * width;
+        std::vector<tmps_layer_desc> b = {L(TMPS_CONV2D, {h, h, cin, width, 1, 1, 1, 0}), L(TMPS_AFFINE, {h, h, width}, R), L(TMPS_CONV2D, {h, h, width, width, 3, 3, stride, 1}),
+                                          L(TMPS_AFFINE, {ho, ho, width}, R), L(TMPS_CONV2D, {ho, ho, width, cout, 1, 1, 1, 0}), L(TMPS_AFFINE, {ho, ho, cout})};
+        if (project) {
+            b.push_back(L(TMPS_CONV2D, {h, h, cin, cout, 1, 1, stride, 0}, TMPS_FLAG_SRC(7)));
+            b.push_back(L(TMPS_AFFINE, {ho, ho, cout}));
+            b.push_back(L(TMPS_RESADD, {ho, ho, cout, 3}, R));
+        } else
+            b.push_back(L(TMPS_RESADD, {ho, ho, cout, 7}, R));
+        return b;
+    };
+    for (int below = 0; below < 3; ++below)
+        for (int stride = 1; stride < 4; ++stride)
+            for (int second = 0; second < 3; ++second)
+                for (int last = 0; last < 2; ++last) {
+                    std::vector<tmps_layer_desc> ls;
+                    if (below) ls.push_back(L(TMPS_CONV2D, {7, 7, 8, 16, 3, 3, 1, 1}, below == 1 ? R : 0));
+                    int h = 7, c = 16;
+                    auto add = [&](int width, int st, bool project) {
+                        const auto b = bottleneck(h, c, width, st, project);
+                        ls.insert(ls.end(), b.begin(), b.end());
+                        h = (h - 1) / st + 1;
+                        c = 4 * width;
+                    };
+                    add(8, stride, true);
+                    if (second) add(8, 1, second == 2);
+                    add(8, 2, true);
+                    if (last) {
+                        ls.push_back(L(TMPS_AVGPOOL, {h, h, c}));
+                        ls.push_back(L(TMPS_LINEAR, {c, 10, 0, 1}));
+                        ls.push_back(L(TMPS_SOFTMAX_CE, {10, 1}));
+                    }
+                    run("bottleneck blocks", ls, bf16, "conv_dgrad", -1);
+                    run("bottleneck blocks", ls, TMPS_F32, "conv_affine_forward", -1);
+                }
     return bad ? 1 : 0;
 }
