@@ -8,8 +8,8 @@
 //
 // g is rounded to bf16 as where it was stored, dx once after add and mask: the same values but for the order of sums.
 //
-// Maps of 56 x 56 x 256 from 64, 64 images (200704 positions, 258 MB): 52 us, 5 TB/s, for 118 in three launches; 64 from 256 with a gradient to join 73 for 143; the
-// first group of ResNet-50's blocks as a stage 2248 -> 1880 us.  Forward and backward pass and update of both layers, before and now (us): 256 from 64 at 65536
+// Maps of 56 x 56 x 256 from 64, 64 images (200704 positions, 258 MB): 52 us, 5 TB/s, for 118 in three launches (55 among a run's other kernels); 64 from 256 with a gradient
+// to join 70 for 143 (69); the first group of ResNet-50's blocks as a stage 2248 -> 1871 us.  Forward and backward pass and update of both layers, before and now (us): 256 from 64 at 65536
 // positions 76 and 58, 16384 39 and 31, 64 from 64 at 65536 43 and 27, at 4096 and below 27 and 22 (the launches).  Errors of dW against 64 bits (2-norm) over 200704,
 // 16384 and 1024 positions 1.8, 1.0 and 0.7e-7 before, 1.2, 1.0 and 0.7e-7 now.
 #include <algorithm>
