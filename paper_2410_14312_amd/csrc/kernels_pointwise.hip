@@ -385,12 +385,12 @@ __global__ __launch_bounds__(2 * W) void pointwise_fwd_kernel(PwWide a, PwNarrow
 
 // Layers that widen 32 or 64 channels to twice or four times as many (a bottleneck block's last one).  The contractions' kernels and this one over 1024, 4096, 16384, 65536
 // and 200704 positions (us): 32 -> 64 5.0 / 5.5 / 6.4 / 10.4 / 20.0 and 4.5 / 4.9 / 5.0 / 8.0 / 13.0, 32 -> 128 5.3 / 5.3 / 8.5 / 11.7 / 31.0 and 5.0 / 5.0 / 6.9 / 10.2 /
-// 20.4, 64 -> 128 5.0 / 6.0 / 8.4 / 11.7 / 32.1 and 5.4 / 5.6 / 7.5 / 10.6 / 23.0, 64 -> 256 5.2 / 7.2 / 11.6 / 21.3 / 62 and 6.1 / 6.6 / 8.6 / 15.6 / 39.  As wide as
+// 20.4, 64 -> 128 5.0 / 6.0 / 8.4 / 11.7 / 32.1 and 5.4 / 5.6 / 7.5 / 10.6 / 23.0, 64 -> 256 5.0 / 6.2 / 9.9 / 20.3 / 64 and 6.1 / 6.3 / 8.5 / 15.1 / 40.  As wide as
 // their input they gain at some sizes and lose at others (64 -> 64 over 32768 8.5 and 6.8, over 65536 9.4 and 9.7), and from 128 channels, whose weights take the registers of
 // what should be on its way, they lose (128 -> 256 over 65536 15.5 and 21, 128 -> 512 over 4096 6.3 and 9.1).  With the next convolution a launch is saved as well: all
-// convolutions of a block and the next one's first over 256, 1024, 4096, 16384 and 200704 positions, 32 and 64 channels 18.0 / 18.5 / 18.9 / 19.0 / 75 and 13.2 / 13.0 / 13.9 / 16.7 / 57,
-// 32 and 128 17.5 / 18.3 / 19.0 / 20.8 / 98 and 13.7 / 13.4 / 14.9 / 17.0 / 71, 64 and 128 17.8 / 18.4 / 19.0 / 21.5 / 103 and 14.5 / 15.2 / 15.6 / 19.6 / 88; 64 and 256
-// as a stage, forward and backward, 256 to 3840 positions 51.4 / 54.7 / 53.8 / 60.4 / 66.1 / 70.1 / 65.2 and 50.4 / 53.6 / 52.8 / 59.2 / 64.9 / 68.6 / 63.8.
+// convolutions of a block and the next one's first over 256, 1024, 4096, 16384 and 200704 positions, 32 and 64 channels 18.0 / 18.5 / 18.9 / 19.0 / 75 and 13.2 / 13.0 / 13.9 /
+// 16.7 / 57, 32 and 128 17.5 / 18.3 / 19.0 / 20.8 / 98 and 13.7 / 13.4 / 14.9 / 17.0 / 71, 64 and 128 17.8 / 18.4 / 19.0 / 21.5 / 103 and 14.5 / 15.2 / 15.6 / 19.6 / 88, 64
+// and 256 18.1 / 19.5 / 19.2 / 23.2 / 173 and 17.0 / 17.8 / 17.6 / 20.2 / 155.
 bool pointwise_forward_takes(int64_t P, int Cin, int Cout, bool next) {
     return (Cin == 32 || Cin == 64) && (Cout == 2 * Cin || Cout == 4 * Cin) && P >= (next ? 256 : 4096) && P < (int64_t(1) << 31) - 4096;
 }
