@@ -14,10 +14,11 @@ static inline int cdiv_pool(int64_t a, int64_t b) { return (int)((a + b - 1) / b
 static inline bool al16p(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // A winner of a window whose places a byte tells apart: r * k + q of its place, with kNotPositive where it is not above zero (what the ReLU of the layer below then
-// stops).  Of a larger one: its position in the map, h W + w, in 32 bits, the highest of them for that.  In a window of negative infinities and NaN alone: the first
+// stops).  Of a larger one: its position in the map, h W + w, in 31 bits (which tell apart the positions of any window that spans fewer), and the highest bit for that.  In a window of negative infinities and NaN alone: the first
 // place inside the map.  kNoWinner: no such window.
 constexpr unsigned kNotPositive = 128, kNoWinner = 255;
 template <class W> constexpr uint32_t not_positive() { return sizeof(W) == 1 ? kNotPositive : 0x80000000u; }
+__device__ __forceinline__ uint32_t map_position(int h, int w, int width) { return ((uint32_t)h * (uint32_t)width + (uint32_t)w) & 0x7FFFFFFFu; }
 
 struct PoolDims {
     int B, H, W, C, Ho, Wo, k, stride, pad;
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(256) void maxpool_fwd_kernel(const T* __restrict__ 
     const int n = (int)(t / p.Ho);
     const int h0 = ho * p.stride - p.pad, w0 = wo * p.stride - p.pad, hl = max(h0, 0), wl = max(w0, 0);   // (the first place inside the map)
     const T* const xn = x + (int64_t)n * p.H * p.W * p.C + c;
-    auto place = [&](int h, int w) { return kByte ? (uint32_t)((h - h0) * (K ? K : p.k) + w - w0) : (uint32_t)(h * p.W + w); };
+    auto place = [&](int h, int w) { return kByte ? (uint32_t)((h - h0) * (K ? K : p.k) + w - w0) : map_position(h, w, p.W); };
     float best[V];
     uint32_t where[V];
 #pragma unroll
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(256) void maxpool_bwd_any_kernel(const T* __restric
             g.load(dy + at);
             win.load(won + at);
             if (!relu) win.mask(not_positive<W>() - 1);
-            const uint32_t me = sizeof(W) == 1 ? (uint32_t)((hp - ho * p.stride) * p.k + wp - wo * p.stride) : (uint32_t)(h * p.W + w);
+            const uint32_t me = sizeof(W) == 1 ? (uint32_t)((hp - ho * p.stride) * p.k + wp - wo * p.stride) : map_position(h, w, p.W);
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[e] += win.at(e) == me ? to_f32(g.u.e[e]) : 0.0f;
         }
@@ -363,7 +364,7 @@ hipError_t maxpool_forward(int dtype, const void* x, void* y, void* won, int B, 
     if ((int64_t)B * p.Ho * p.Wo * C <= 0) return hipSuccess;
     if (maxpool_winner_bytes(k) == 1)
         return dtype == kBF16 ? forward_t((const bf16_t*)x, (bf16_t*)y, (uint8_t*)won, p, s) : forward_t((const float*)x, (float*)y, (uint8_t*)won, p, s);
-    if ((int64_t)H * W >= (int64_t(1) << 31)) return hipErrorInvalidValue;   // (a winner's position is kept in 31 bits)
+    if ((int64_t)(k < H ? k : H) * W >= (int64_t(1) << 31)) return hipErrorInvalidValue;   // (a window's positions would not all differ in 31 bits)
     return dtype == kBF16 ? forward_t((const bf16_t*)x, (bf16_t*)y, (uint32_t*)won, p, s) : forward_t((const float*)x, (float*)y, (uint32_t*)won, p, s);
 }
 
