@@ -64,10 +64,13 @@ enum { kActNone = 0, kActRelu = 1, kActGelu = 2 };
 
 // 8 consecutive elements with 16-byte accesses (the address is 16-byte aligned)
 __device__ __forceinline__ void store8(bf16_t* p, const float (&v)[8]) {
-    Pack8 pk;
+    // (in pairs: one conversion makes two values in the halves of a register, one by one they are put together with a permutation more each)
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    uint32_t w[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) pk.h[e] = (bf16_t)v[e];
-    *reinterpret_cast<uint4*>(p) = pk.u;
+    for (int e = 0; e < 4; ++e) w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{v[2 * e], v[2 * e + 1]}), bf16x2_t));
+    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 __device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
@@ -91,11 +94,14 @@ template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {
     uint4 u;
     __device__ __forceinline__ void load(const bf16_t* p) { u = *reinterpret_cast<const uint4*>(p); }
+    // (from whole words: as an array of 16-bit values the compiler takes them apart where they arrive and holds twice the registers)
     __device__ __forceinline__ void get(float (&v)[8]) const {
-        Pack8 pk;
-        pk.u = u;
+        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (float)pk.h[e];
+        for (int e = 0; e < 4; ++e) {
+            v[2 * e] = __builtin_bit_cast(float, w[e] << 16);
+            v[2 * e + 1] = __builtin_bit_cast(float, w[e] & 0xffff0000u);
+        }
     }
 };
 template <> struct Raw8<float> {

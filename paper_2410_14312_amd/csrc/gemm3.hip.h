@@ -24,6 +24,7 @@
 // k-loop of the next unit.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "gemm2.hip.h"
 
@@ -44,6 +45,12 @@ template <bool KC> struct G3Operand {
     int64_t ld;  // elements between consecutive rows (KC) or consecutive k (RC)
 };
 
+// f(0), f(1), .. f(N - 1) with the index as a constant
+template <class F, int... I> __device__ __forceinline__ void static_for_each(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(F&& f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
+
 // wait until at most N vector-memory operations of this wave are outstanding
 // (the trailing comment tells this wait from the ones the compiler inserts, for tests/test_gemm3_isa.py)
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
@@ -63,10 +70,10 @@ __device__ __forceinline__ void copy16_to_lds(const void* src, lds_t dst) {
     const uint32_t lds = __builtin_amdgcn_readfirstlane(dst);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
 }
-// the same from `off` bytes (of each lane) behind a base that all lanes share
-__device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t off, lds_t dst) {
+// the same from `off` bytes (of each lane) behind a base that all lanes share to LDS `DIST` bytes behind `dst`
+template <int DIST = 0> __device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t off, lds_t dst) {
     const uint32_t lds = __builtin_amdgcn_readfirstlane(dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base), "n"(DIST) : "memory", "m0", "scc");
 }
 #pragma clang diagnostic pop
 
@@ -90,50 +97,57 @@ template <int BM, int BN, int BK, int NS> constexpr int gemm3_lds_bytes() { retu
 // what a copy reads in place of elements that are not there
 __device__ __attribute__((aligned(16))) static const uint32_t g3_zeros[4] = {0, 0, 0, 0};
 
-// Per-wave copy state of one operand tile of ROWS rows x BK k (BK = 32 or 64): GROUPS 1-KB groups per k-tile.
-template <int ROWS, int BK, int NW, bool KC> struct G3Loader {
+// Per-wave copy state of one operand tile of ROWS rows x BK k (BK = 32 or 64): GROUPS 1-KB groups per k-tile.  A lane's address is a base that
+// the wave shares, stepped by the scalar unit, and a 32-bit offset that stays as it is for a unit: a copy is then three instructions.  With an
+// address of 64 bits in each lane, stepped after each copy, the vector unit's additions and moves took issue slots between the multiplies
+// (see the k-loop).  RAGGED units, whose last k-tile may end early, keep such addresses: zeros replace single lanes' sources there.
+template <int ROWS, int BK, int NW, bool KC, bool RAGGED> struct G3Loader {
     static constexpr int GROUPS = ROWS * BK * 2 / 1024 / NW;
     static_assert(GROUPS >= 1 && GROUPS * NW * 1024 == ROWS * BK * 2, "the waves must share a tile evenly");
     static_assert(KC || (ROWS / 8 <= 64 && 64 % (ROWS / 8) == 0), "a 1 KB group of a row-contiguous tile covers whole k-rows");
-    const bf16_t* ptr[GROUPS];
+    static_assert(!RAGGED || !KC, "k-rows are whole lanes of a row-contiguous tile only");
+    const bf16_t* base;
+    uint32_t off[RAGGED ? 1 : GROUPS];
+    const bf16_t* ptr[RAGGED ? GROUPS : 1];
     // (re)compute the lane addresses for the tile starting at row0, k range starting at k0
     __device__ __forceinline__ void seek(const G3Operand<KC>& op, int row0, int k0, int wave, int lane) {
+        base = op.p + (KC ? (int64_t)row0 * op.ld + k0 : (int64_t)k0 * op.ld + row0);
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
             const int grp = wave + g * NW;
+            uint32_t o;
             if constexpr (KC) {
                 // LDS tile [ROWS][BK]; a group is 1 KB of consecutive rows; the 16-byte chunk at (r, p) holds global
                 // chunk p ^ s(r) of row r, s(r) = (r >> 1) & 7 for BK = 64 (8 chunks per row), (r >> 2) & 3 for BK = 32
                 constexpr int CPR = BK / 8;   // chunks per row
                 const int r = grp * (64 / CPR) + lane / CPR;
                 const int c = (lane % CPR) ^ (BK == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3));
-                int gr = row0 + r;
-                gr = gr < op.rows ? gr : op.rows - 1;
-                ptr[g] = op.p + (int64_t)gr * op.ld + k0 + c * 8;
+                o = (uint32_t)min(r, op.rows - 1 - row0) * (uint32_t)op.ld + c * 8;
             } else {
                 // LDS tile [BK][ROWS]; the chunk at (k, p) holds rows 8 * (p ^ ((k & 3) << 2)) .. + 7 of k
                 constexpr int CPR = ROWS / 8;  // chunks per k-row
                 const int k = grp * (64 / CPR) + lane / CPR;
                 const int c = (lane % CPR) ^ ((k & 3) << 2);
-                int r = row0 + c * 8;
-                r = r + 8 <= op.rows ? r : op.rows - 8;
-                ptr[g] = op.p + (int64_t)(k0 + k) * op.ld + r;
+                o = (uint32_t)k * (uint32_t)op.ld + min(c * 8, op.rows - 8 - row0);
             }
+            if constexpr (RAGGED) ptr[g] = base + o;
+            else off[g] = o * 2;
         }
     }
-    // copy this wave's groups of the current k-tile into `tile` (LDS) and step to the next k-tile
-    __device__ __forceinline__ void issue(lds_t tile, int64_t ld, int wave) {
+    // copy one of this wave's groups of the current k-tile (every one exactly once, in any order) into the tile whose LDS starts `wave` KB before `dst`
+    template <int G> __device__ __forceinline__ void issue_group(lds_t dst) const {
+        if constexpr (RAGGED) copy16_to_lds(ptr[G], dst + G * NW * 1024);
+        else copy16_to_lds<G * NW * 1024>(base, off[G], dst);
+    }
+    // step to the next k-tile
+    __device__ __forceinline__ void next(int64_t ld) {
+        if constexpr (RAGGED) {
 #pragma unroll
-        for (int g = 0; g < GROUPS; ++g) issue_group(tile, ld, wave, g);
+            for (int g = 0; g < GROUPS; ++g) ptr[g] += BK * ld;
+        } else base += KC ? BK : BK * ld;
     }
-    // the same, one group at a time (every group of a k-tile exactly once, in any order)
-    __device__ __forceinline__ void issue_group(lds_t tile, int64_t ld, int wave, int g) {
-        copy16_to_lds(ptr[g], tile + (wave + g * NW) * 1024);
-        ptr[g] += KC ? BK : BK * ld;
-    }
-    // row-contiguous: the current k-tile is a unit's last and has `left` k (fewer than BK): zeros take the place of those behind its end, which are not read
+    // the current k-tile is a unit's last and has `left` k (fewer than BK): zeros take the place of those behind its end, which are not read
     __device__ __forceinline__ void cut(int wave, int lane, int left) {
-        static_assert(!KC, "k-rows are whole lanes of a row-contiguous tile only");
         constexpr int CPR = ROWS / 8;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g)
@@ -144,37 +158,33 @@ template <int ROWS, int BK, int NW, bool KC> struct G3Loader {
 // Fragment reader of one operand for a wave whose first row in the tile is wrow0: T fragments of 32 rows.
 template <int ROWS, int BK, int T, bool KC> struct G3Frags {
     static constexpr int KK = BK / 16;
-    int base[KC ? 1 : T];   // byte offsets that depend on the lane (and, for RC, on the fragment)
-    int koff[KC ? KK : 1];
+    int at[KC ? KK : T];   // byte offsets in a tile that depend on the lane, of a multiply step (KC) or of a fragment
     __device__ __forceinline__ void init(int wrow0, int lane) {
         if constexpr (KC) {
             // s(row) of row = wrow0 + 32 i + lane % 32 depends on the lane only
             const int half = lane >> 5, swz = BK == 64 ? ((lane >> 1) & 7) : ((lane >> 2) & 3);
-            base[0] = (wrow0 + (lane & 31)) * (BK * 2);
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) koff[kk] = ((kk * 2 + half) ^ swz) << 4;
+            for (int kk = 0; kk < KK; ++kk) at[kk] = (wrow0 + (lane & 31)) * (BK * 2) + (((kk * 2 + half) ^ swz) << 4);
         } else {
             // transpose read: lane supplies 4 consecutive rows (8 bytes) at k = 16 kk + 8 half + (lane % 16) / 4,
             // rows rb + 16 ((lane / 16) % 2) + 4 (lane % 4); a second read 4 k further completes the 8 k of a lane
             const int kl = (lane >> 5) * 8 + ((lane & 15) >> 2);
             const int sw = ((lane >> 2) & 3) << 2;   // (k & 3) << 2
-            koff[0] = kl * (ROWS * 2);
 #pragma unroll
             for (int i = 0; i < T; ++i) {
                 const int col = wrow0 + 32 * i + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
-                base[i] = (((col >> 3) ^ sw) << 4) + (col & 7) * 2;
+                at[i] = kl * (ROWS * 2) + (((col >> 3) ^ sw) << 4) + (col & 7) * 2;
             }
         }
     }
     __device__ __forceinline__ bf16x8_t read(lds_t tile, int i, int kk) const {
         if constexpr (KC) {
-            return *lds_ptr<const bf16x8_t>(tile + base[0] + i * (32 * BK * 2) + koff[kk]);
+            return *lds_ptr<const bf16x8_t>(tile + at[kk] + i * (32 * BK * 2));
         } else {
-            const lds_t p0 = tile + koff[0] + kk * 16 * (ROWS * 2) + base[i];
-            const lds_t p1 = p0 + 4 * (ROWS * 2);
+            const lds_t p = tile + at[i] + kk * 16 * (ROWS * 2);
             union { s16x4_t h[2]; bf16x8_t v; } u;
-            u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p0));
-            u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p1));
+            u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p));
+            u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr<s16x4_t>(p + 4 * (ROWS * 2)));
             return u.v;
         }
     }
@@ -241,8 +251,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int KK = BK / 16;
     constexpr int A_BYTES = BM * BK * 2, STAGE = (BM + BN) * BK * 2;
-    typedef G3Loader<BM, BK, NW, AKC> LoaderA;
-    typedef G3Loader<BN, BK, NW, BKC> LoaderB;
+    typedef G3Loader<BM, BK, NW, AKC, Work::kRagged> LoaderA;
+    typedef G3Loader<BN, BK, NW, BKC, Work::kRagged> LoaderB;
     constexpr int G = LoaderA::GROUPS + LoaderB::GROUPS;   // copy instructions per wave and k-tile
     static_assert((NS - 1) * G <= 63, "too many copies in flight for the vmcnt counter");
     static_assert(!ROWSUM || !AKC, "row sums are built for a row-contiguous A");
@@ -272,6 +282,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     const int units = work.units();
     int iu = vb, ikt = 0, ink = 0, istage = 0, ilast = BK;
     int64_t ild_a = 0, ild_b = 0;   // leading dimensions of the cursor's operands
+    int left = 0;                   // k-tiles that are still to be copied
+    for (int u = vb; u < units; u += grid) left += work.unit(u).nk;
     auto seek_unit = [&]() {
         if (iu < units) {
             const G3Unit t = work.unit(iu);
@@ -294,16 +306,19 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
             }
         }
     };
-    auto copies_left = [&]() { return iu < units; };
     // copy group g (of G) of the cursor's k-tile into stage `istage`
-    auto issue_group = [&](int g) {
-        const lds_t st = smem + istage * STAGE;
-        if (g < LoaderA::GROUPS) la.issue_group(st, ild_a, wave, g);
-        else lb.issue_group(st + A_BYTES, ild_b, wave, g - LoaderA::GROUPS);
+    auto issue_group = [&](auto group) {
+        constexpr int g = decltype(group)::value;
+        const lds_t st = smem + istage * STAGE + wave * 1024;
+        if constexpr (g < LoaderA::GROUPS) la.template issue_group<g>(st);
+        else lb.template issue_group<g - LoaderA::GROUPS>(st + A_BYTES);
     };
     // all G groups of the cursor's k-tile are issued: step the cursor
     auto advance = [&]() {
         istage = istage + 1 == NS ? 0 : istage + 1;
+        --left;
+        la.next(ild_a);
+        lb.next(ild_b);
         if (++ikt == ink) {
             iu += grid;
             seek_unit();
@@ -312,9 +327,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     };
     // copy the cursor's whole k-tile (if any is left); returns false when all is issued
     auto issue_next = [&]() -> bool {
-        if (!copies_left()) return false;
-#pragma unroll
-        for (int g = 0; g < G; ++g) issue_group(g);
+        if (left <= 0) return false;
+        static_for<G>([&](auto g) { issue_group(g); });
         advance();
         return true;
     };
@@ -332,11 +346,6 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         if (issue_next()) ++ahead;
     if (ahead == 0) return;   // no unit for this workgroup (uniform)
     --ahead;
-    // first k-tile: wait for it, make it visible to all waves, fetch its first fragments
-    if (ahead == NS - 1) wait_vmcnt<(NS - 1) * G>();
-    else wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
     // Fragments are fetched PD multiply steps (of 16 k) ahead of their use.  With two waves per SIMD one step is
     // enough: the other wave's multiplies cover a wave's LDS latency.  With one wave per SIMD (the 4-wave instances)
     // a fragment requested during a step of TM * TN multiplies has not arrived when the next step starts, so these
@@ -345,17 +354,6 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     static_assert(PD < KK && KK % NBUF == 0, "the fragment sets rotate once per k-tile");
     bf16x8_t af[NBUF][TM], bfr[NBUF][TN];
     int cstage = 0;
-    {
-        const lds_t sa = smem;
-#pragma unroll
-        for (int p = 0; p < PD; ++p) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[p][i] = fa.read(sa, i, p);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bfr[p][j] = fb.read(sa + A_BYTES, j, p);
-        }
-    }
-
     for (int cu = vb; cu < units; cu += grid) {
         const G3Unit cur = work.unit(cu);
         const int nk = cur.nk, m0 = cur.m0, n0 = cur.n0, z = cur.z;
@@ -418,7 +416,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         };
 
         // What the epilogue reads from memory (a bias per column, a residual source or a mask per element), block by
-        // block of 32 rows x 64 columns of this wave's results (block b: rows 32 (b / (TN / 2)), columns 64 (b % (TN / 2))).
+        // block of 32 rows x 64 columns of this wave's results (block b: rows 32 (b / (TN / 2)), columns 64 (b % (TN / 2))).  Places outside the
+        // matrix read the last ones inside it: a load under a lane's condition is a branch each.
         constexpr int NB = TM * (TN / 2);
         const int64_t epi_ld = epi.ld;
         typename Work::Epi::Col8 pcol[TN / 2];
@@ -426,81 +425,104 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         // (ln: the lane's index as the caller has it; see the epilogue)
         auto epi_n = [&](int jp, int ln) { return n0 + wn * (BN / WN) + jp * 64 + (ln & 7) * 8; };
         auto epi_request = [&](int b, int ln) {
-            const int i = b / (TN / 2), jp = b % (TN / 2), n = epi_n(jp, ln);
-            if (i == 0) pcol[jp] = epi.col8(n < N ? n : 0);
+            const int i = b / (TN / 2), jp = b % (TN / 2), n = min(epi_n(jp, ln), N - 8);
+            if (i == 0) pcol[jp] = epi.col8(n);
 #pragma unroll
             for (int sp = 0; sp < 4; ++sp) {
                 const int pm = m0 + wm * (BM / WM) + i * 32 + sp * 8 + (ln >> 3);
-                prow[b][sp] = epi.row8((int64_t)pm * epi_ld + n, pm < M && n < N);
+                prow[b][sp] = epi.row8((int64_t)min(pm, M - 1) * epi_ld + n, true);
             }
         };
         // With registers to spare (the 4-wave instances: 512 per lane) all of it is requested before the k-loop; the
-        // 8-wave instances, which would spill, request a block's data when they come to the block.  A wave waits for
+        // 8-wave instances, which would spill, request a block's data while they work on the block before.  A wave waits for
         // its requests in issue order, stores included: waiting for data requested after a store means waiting for the
         // store to be acknowledged.
         constexpr bool EARLY = NW <= 4;
+        // (a block at a time where the columns' data is more than a bias: 24 registers of gains, shifts and biases leave none for two blocks' rows)
+        constexpr bool AHEAD = !EARLY && sizeof(typename Work::Epi::Col8) <= 32;
+        if (cu == vb) {
+            // The workgroup's first k-tile: wait for it and make it visible to all waves.  (Here, so that what stands above, which needs none of it, is
+            // done while it is on its way.)
+            if (ahead == NS - 1) wait_vmcnt<(NS - 1) * G>();
+            else wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        // The unit's first fragments.  (Its first k-tile is there since the barrier of the last unit's last one; requested then already, they would
+        // take registers that the results need on their way out.)
+        {
+            const lds_t sa = smem + cstage * STAGE;
+#pragma unroll
+            for (int p = 0; p < PD; ++p) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) af[p][i] = fa.read(sa, i, p);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) bfr[p][j] = fb.read(sa + A_BYTES, j, p);
+            }
+        }
         if constexpr (EARLY) {
 #pragma unroll
             for (int b = 0; b < NB; ++b) epi_request(b, lane);
         }
 
-        for (int kt = 0; kt < nk; ++kt) {
-            // Invariant: the fragments of this k-tile's first PD multiply steps are in registers or on their way
-            // (requested during the previous k-tile's last PD steps); `ahead` younger k-tiles are in flight or have landed.
-            asm volatile("; tmps k-tile begin");
+        // One k-tile.  Invariant: the fragments of its first PD multiply steps are in registers or on their way (requested during the previous
+        // k-tile's last PD steps); `ahead` younger k-tiles are in flight or have landed.  last: the unit's last one, which requests no fragments for a next.
+        //
+        // fill: after the barrier its stage is free and refilled at once, the copies spread over the multiplies that follow the barrier; not in a
+        // unit's last k-tile, whose stage the results go through first, nor when all is copied.  The two forms are loops of their own, and the
+        // one that is walked nearly always has no branch in it: with a wave or two to a SIMD every branch, every address that is put together and every
+        // pointer that is stepped between two multiplies delays the next one.  256 x 128 tiles, four waves: 1830 cycles a k-tile with a test before
+        // each copy and its address in 64-bit registers, 1500 as it is (multiplies 1024); 8192 x 768 over 3072 51 -> 43 us, 8192^3 in 256 x 256 tiles 874 -> 814 us.
+        auto k_tile = [&](int kt, auto fill, auto last) {
+            constexpr bool FILL = decltype(fill)::value, LAST = decltype(last)::value;
+            if constexpr (FILL) asm volatile("; tmps k-tile begin");
             const lds_t sa = smem + cstage * STAGE;
             const int nstage = cstage + 1 == NS ? 0 : cstage + 1;
-            // After the barrier of this k-tile its stage is free; unless the unit's results go through it first (the
-            // unit's last k-tile) it is refilled at once, the copies spread over the multiplies that follow the barrier.
-            bool fill = false;
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                const int nx = kk + PD;   // the step whose fragments are requested during this one
-                if (nx == KK) {
+            const lds_t sn = smem + nstage * STAGE;
+            static_for<KK>([&](auto step) {
+                constexpr int kk = decltype(step)::value;
+                constexpr int nx = kk + PD;   // the step whose fragments are requested during this one
+                if constexpr (nx == KK) {
                     // Every fragment of this k-tile has been requested.  The next k-tile is the oldest copy in
                     // flight: copies complete in issue order, so it has landed once at most (ahead - 1) * G younger
                     // copies are outstanding.  Result stores of an earlier unit are younger than it too and only
                     // make the wait stricter.  While the pipeline drains (ahead < NS - 1) wait for everything.
-                    if (ahead > 0) {
-                        if (ahead == NS - 1) wait_vmcnt<(NS - 2) * G>();
-                        else wait_vmcnt<0>();
-                    }
+                    if (FILL || ahead == NS - 1) wait_vmcnt<(NS - 2) * G>();
+                    else wait_vmcnt<0>();
                     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's reads of the current stage are done
                     __builtin_amdgcn_s_barrier();
                     // All waves are past their last read of the current stage, and the next k-tile is visible to all:
-                    // its first fragments are fetched under the cover of the remaining multiply steps.  (While the
-                    // pipeline drains there is no next k-tile: the reads then fetch stale bytes that nothing uses.)
-                    fill = kt + 1 < nk && copies_left();
+                    // its first fragments are fetched under the cover of the remaining multiply steps.
                 }
                 // This step in program order, kept by the scheduling barriers: before multiply g, the g-th share of
                 // the fragment requests of step nx and, after the barrier, of the copies: a wave has one instruction
                 // stream, and what it issues between two multiplies costs nothing while the matrix unit is busy.
-                const lds_t ra = nx < KK ? sa : smem + nstage * STAGE;
-                const int rk = nx < KK ? nx : nx - KK;
+                const lds_t ra = nx < KK ? sa : sn;
+                constexpr int rk = nx < KK ? nx : nx - KK;
                 constexpr int NM = TM * TN, NR = TM + TN, CPS = G / PD;
                 static_assert(G % PD == 0, "the copies of a k-tile are spread evenly over the steps after the barrier");
-#pragma unroll
-                for (int g = 0; g < NM; ++g) {
+                static_for<NM>([&](auto multiply) {
+                    constexpr int g = decltype(multiply)::value;
 #pragma unroll
                     for (int r = g * NR / NM; r < (g + 1) * NR / NM; ++r) {
+                        if (LAST && nx >= KK) continue;
                         if (r < TM) af[nx % NBUF][r] = fa.read(ra, r, rk);
                         else bfr[nx % NBUF][r - TM] = fb.read(ra + A_BYTES, r - TM, rk);
                     }
-                    if (nx >= KK) {
-                        if (fill) {
-#pragma unroll
-                            for (int c = g * CPS / NM; c < (g + 1) * CPS / NM; ++c) issue_group((nx - KK) * CPS + c);
-                        }
+                    if constexpr (FILL && nx >= KK) {
+                        constexpr int c0 = g * CPS / NM, c1 = (g + 1) * CPS / NM;
+                        static_for<c1 - c0>([&](auto c) { issue_group(std::integral_constant<int, (nx - KK) * CPS + c0 + decltype(c)::value>{}); });
                     }
-                    if constexpr (TOT) {
-                        if (kk == 0 && g % TN == 0 && ((kt - (g / TN) * chain / TM) & (chain - 1)) == 0) add_to_totals(g / TN);
+                    if constexpr (TOT && kk == 0 && g % TN == 0) {
+                        if (((kt - (g / TN) * chain / TM) & (chain - 1)) == 0) add_to_totals(g / TN);
                     }
-                    acc[g / TN][g % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk % NBUF][g / TN], bfr[kk % NBUF][g % TN], acc[g / TN][g % TN], 0, 0, 0);
-                    if constexpr (ROWSUM) {
+                    // (B's fragment first: the block comes out transposed, four consecutive columns of a row in a lane's registers; see the results)
+                    acc[g / TN][g % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk % NBUF][g % TN], af[kk % NBUF][g / TN], acc[g / TN][g % TN], 0, 0, 0);
+                    if constexpr (ROWSUM && g % TN == 0) {
                         // Behind the fragment's first multiply, so that it is issued while that one runs; written as
                         // instructions because the compiler otherwise turns the branch into selects and moves the
                         // additions, which nothing in the loop depends on, below the multiplies of the k-tile.
-                        if (g % TN == 0 && sum_rows && (g / TN) % WN == wn) {
+                        if (sum_rows && (g / TN) % WN == wn) {
                             typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
                             const u32x4_t f = __builtin_bit_cast(u32x4_t, af[kk % NBUF][g / TN]);
 #pragma unroll
@@ -509,18 +531,18 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (fill) {
-                advance();
-                ++ahead;
-            }
-            if (kt + 1 < nk) {
-                --ahead;   // kt + 1 < nk: a next k-tile exists
-                cstage = nstage;
-            }
-            asm volatile("; tmps k-tile end");
-        }
+                });
+            });
+            if constexpr (FILL) advance();
+            else if constexpr (!LAST) --ahead;
+            if constexpr (!LAST) cstage = nstage;
+            if constexpr (FILL) asm volatile("; tmps k-tile end");
+        };
+        const int filled = min(nk - 1, left);
+        int kt = 0;
+        for (; kt < filled; ++kt) k_tile(kt, std::true_type{}, std::false_type{});
+        for (; kt + 1 < nk; ++kt) k_tile(kt, std::false_type{}, std::false_type{});
+        k_tile(kt, std::false_type{}, std::true_type{});
         if constexpr (TOT) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
@@ -533,24 +555,23 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         }
 
         // ---- results ----
-        // The stage of the unit's last k-tile is free and not yet refilled: each wave transposes its accumulators
+        // The stage of the unit's last k-tile is free and not yet refilled: each wave passes its accumulators
         // through the 8 KB of that stage that its own copies write (so no other wave touches them), one block of
         // 32 rows x 64 columns of fp32 at a time, and leaves with 8 consecutive columns of one row per lane: a store
-        // instruction then writes 8 rows of 128 (bf16) or 256 (fp32) consecutive bytes.
+        // instruction then writes 8 rows of 128 (bf16) or 256 (fp32) consecutive bytes.  A block's 16-byte chunks lie at an XOR of their row, so that
+        // neither side's accesses meet in a bank.
         {
-            const lds_t stg = smem + cstage * STAGE;
-            // piece p (1 KB = 4 staged rows) of this wave: its p-th copy group
-            // (computed where it is used: an array of them indexed by the lane's half would live in scratch memory)
-            auto piece = [&](int p) {
-                return p < LoaderA::GROUPS ? (wave + p * NW) * 1024 : A_BYTES + (wave + (p - LoaderA::GROUPS) * NW) * 1024;
-            };
             // Everything the epilogue derives from the lane's index is derived here, from a copy of the index that the
             // compiler cannot trace back: otherwise it computes these offsets before the k-loop and, in the 8-wave
             // instances, whose loop leaves no register free, spills them around it — and every reload from scratch
             // memory is a wait for all of the wave's requests, result stores included.
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            const int half = ln >> 5, col_in = ln & 31;
+            // staged row r: piece r / 4 (1 KB: the wave's copy group of that number), row r % 4 of it; chunk c (4 columns) at c ^ (r % 16)
+            const lds_t stg = smem + cstage * STAGE + wave * 1024;
+            static_assert(A_BYTES == LoaderA::GROUPS * NW * 1024, "a wave's copy groups lie NW KB apart, from A's tile on to B's");
+            lds_t put = stg + ((ln & 31) >> 2) * (NW * 1024) + (ln & 3) * 256 + (((ln >> 5) ^ (ln & 15)) << 4);
+            lds_t get = stg + (ln >> 5) * (NW * 1024) + ((ln >> 3) & 3) * 256 + (((2 * (ln & 7)) ^ (ln >> 3)) << 4);
             if constexpr (EARLY) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
@@ -558,35 +579,35 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
 #pragma unroll
                     for (int sp = 0; sp < 4; ++sp) settle(prow[b][sp]);
                 }
-            }
+            } else if constexpr (AHEAD) epi_request(0, ln);
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const int i = b / (TN / 2), jp = b % (TN / 2);
-                // (requested before the block is transposed: one memory latency per block, not one per group of rows)
-                if constexpr (!EARLY) epi_request(b, ln);
                 const int n = epi_n(jp, ln);
-                // accumulator register r of a lane: row 8 (r / 4) + 4 half + r % 4, column lane % 32
+                asm volatile("" : "+v"(put), "+v"(get));   // (a block's addresses are formed anew: kept for the next one they would be spilled)
+                if constexpr (!EARLY && !AHEAD) epi_request(b, ln);
+                typedef float f32x4_t __attribute__((ext_vector_type(4)));
+                // accumulator register r of a lane: row lane % 32, column 8 (r / 4) + 4 (lane / 32) + r % 4
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int base = half ? piece(2 * (r >> 2) + 1) : piece(2 * (r >> 2));
-                        *lds_ptr<float>(stg + base + (r & 3) * 256 + (jj * 32 + col_in) * 4) = acc[i][2 * jp + jj][r];
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x16_t& v = acc[i][2 * jp + jj];
+                        *lds_ptr<f32x4_t>(put ^ ((jj * 8 + q * 2) << 4)) = f32x4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
                     }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 if constexpr (!EARLY) {
-                    // before the block's first store, where the block's data is the wave's youngest request
+                    // the block's data before the next block's requests and its own first store
                     if (i == 0) settle(pcol[jp]);
 #pragma unroll
                     for (int sp = 0; sp < 4; ++sp) settle(prow[b][sp]);
+                    if (AHEAD && b + 1 < NB) epi_request(b + 1, ln);
                 }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
                 for (int sp = 0; sp < 4; ++sp) {
-                    // staged row 8 sp + lane / 8 lies in piece 2 sp + half, at row (lane / 8) % 4 of the piece
-                    const int base = half ? piece(2 * sp + 1) : piece(2 * sp);
-                    const lds_t src = stg + base + ((ln >> 3) & 3) * 256 + (ln & 7) * 32;
-                    typedef float f32x4_t __attribute__((ext_vector_type(4)));
-                    const f32x4_t lo = *lds_ptr<const f32x4_t>(src), hi = *lds_ptr<const f32x4_t>(src + 16);
+                    // staged row 8 sp + lane / 8, chunks 2 (lane % 8) and the next
+                    const lds_t src = (get ^ ((sp & 1) << 7)) + 2 * sp * (NW * 1024);
+                    const f32x4_t lo = *lds_ptr<const f32x4_t>(src), hi = *lds_ptr<const f32x4_t>(src ^ 16);
                     float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                     const int m = m0 + wm * (BM / WM) + i * 32 + sp * 8 + (ln >> 3);
                     if (m < M && n < N) epi.at8(pcol[jp], prow[b][sp], (int64_t)m * epi_ld + n, v, z);   // N is a multiple of 8

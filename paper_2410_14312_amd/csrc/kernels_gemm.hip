@@ -587,7 +587,7 @@ static hipError_t dense_forward_bf16(int kc, const bf16_t* x, const bf16_t* w, c
     // 35 / 59 and 15.7 / 19.7 / 22.9 / 39 / 70, 6144 x 768 15.3 / 18.6 / 21.1 / 34 / 58 and 15.0 / 19.2 / 22.6 / 37 / 69, 4096 x 1280
     // 17.0 / - / 22.5 / 36 / 62 and 14.8 / - / 22.2 / 37 / 77)
     if (aligned && Din >= 1024 && g3_narrow_ok(B, Dout, Din) && aligned16(x) && aligned16(w))
-        return launch3_inst<256, 128, 2, 2, 2, 1, true, true, false>(kc, G3Operand<true>{x, B, Din}, G3Operand<true>{w, Dout, Din}, epi, B, Dout, Din,
+        return launch3_inst<256, 128, 2, 2, 3, 1, true, true, false>(kc, G3Operand<true>{x, B, Din}, G3Operand<true>{w, Dout, Din}, epi, B, Dout, Din,
                                                                      g3_plan(B, Dout, Din, 1, 256, 128), s);
     return dense_forward_t<bf16_t>(kc, x, w, epi, B, Din, Dout, ws, s);
 }
@@ -655,7 +655,7 @@ static hipError_t dense_dgrad_as(int kc, int dtype, const void* dy, const void* 
         if (fast && g3_narrow_ok(B, Din, Dout) && aligned16(dx) && aligned16(mask) && aligned16(add)) {
             G3Operand<true> A{(const bf16_t*)dy, B, Dout};
             G3Operand<false> Bv{(const bf16_t*)w, Din, Din};
-            return launch3_inst<256, 128, 2, 2, 2, 1, true, false, false>(kc, A, Bv, epi, B, Din, Dout, g3_plan(B, Din, Dout, 1, 256, 128), s);
+            return launch3_inst<256, 128, 2, 2, 3, 1, true, false, false>(kc, A, Bv, epi, B, Din, Dout, g3_plan(B, Din, Dout, 1, 256, 128), s);
         }
         return dense_dgrad_t<bf16_t>(kc, (const bf16_t*)dy, (const bf16_t*)w, epi, B, Din, Dout, ws, s);
     }
