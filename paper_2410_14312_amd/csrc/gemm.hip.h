@@ -117,6 +117,23 @@ template <> struct Raw8<float> {
 struct NoCol8 {};
 struct NoRow8 {};
 
+// Forms of an epilogue.  What an epilogue does hangs on arguments that are the same for a whole launch (an activation, a mask, a second result); asked for
+// at every 8 elements, those questions are branches and moves that a kernel with a wave or two to a SIMD waits for.  E::form() names the combination (below 0:
+// none of those that have an instance of their own); EpiForm is E for one of them, with the elements at `base` (the same for the wave) + `off` (of
+// the lane): a store then takes a scalar base and a 32-bit offset.
+template <class T> __device__ __forceinline__ T* at_lane(T* p, int64_t base, uint32_t off) {
+    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p + base) + (uint32_t)(off * (uint32_t)sizeof(T)));
+}
+constexpr int64_t kFormMaxLd = 1 << 22;   // 128 rows of fp32 are then less than 2^32 bytes
+template <class E, int F> struct EpiForm : E {
+    static constexpr bool kFormed = true;
+    typedef decltype(E::template raw8f<F>()) Row8;
+    __device__ __forceinline__ Row8 row8f(int64_t base, uint32_t off) const { return E::template request8f<F>(base, off); }
+    __device__ __forceinline__ void at8f(const typename E::Col8& c, const Row8& p, int64_t base, uint32_t off, float (&v)[8], int z) const {
+        E::template finish8f<F>(c, p, base, off, v, z);
+    }
+};
+
 // Host-side test for the 8-wide (16-byte) form of an epilogue: every tensor it touches is 16-byte aligned and a row
 // start keeps that alignment.
 static inline bool epi_al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -182,6 +199,42 @@ template <typename TOut> struct EpiBiasAct {
         }
         store8(out + idx, v);
         if (relu != kActGelu && zout) store8(zout + idx, v);
+    }
+    // 0: bias only, 1: ReLU, 2: GELU and its derivative, 3: a residual source
+    static constexpr bool kFormed = false;
+    static constexpr int kForms = sizeof(TOut) == 2 ? 4 : 1;
+    int form() const {
+        if (!bias || ld > kFormMaxLd) return -1;
+        if (relu == kActGelu) return zout && !res ? 2 : -1;
+        return zout ? -1 : relu == kActRelu ? (res ? -1 : 1) : (res ? 3 : 0);
+    }
+    template <int F> static __device__ __host__ auto raw8f() {
+        if constexpr (F == 3) return Row8{};
+        else return NoRow8{};
+    }
+    template <int F> __device__ __forceinline__ auto request8f(int64_t base, uint32_t off) const {
+        decltype(raw8f<F>()) p;
+        if constexpr (F == 3) p.r.load(at_lane(res, base, off));
+        return p;
+    }
+    template <int F, class R> __device__ __forceinline__ void finish8f(const Col8& c, const R& p, int64_t base, uint32_t off, float (&v)[8], int) const {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += c.b[e];
+        if constexpr (F == 1) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+        } else if constexpr (F == 2) {
+            float d[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) gelu_both(v[e], v[e], d[e]);
+            store8(at_lane(zout, base, off), d);
+        } else if constexpr (F == 3) {
+            float r[8];
+            p.r.get(r);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += r[e];
+        }
+        store8(at_lane(out, base, off), v);
     }
     __device__ __forceinline__ void rowsum(int, float, int) const {}
 };
@@ -255,6 +308,37 @@ template <typename TOut> struct EpiConvAffine {
         store8(yout + idx, v);
         if (again) store8(again + idx, v);
     }
+    // without a bias and a second copy: 0 the layers alone, 1 with ReLU, 2 with a residual source and ReLU
+    static constexpr bool kFormed = false;
+    static constexpr int kForms = sizeof(TOut) == 2 ? 3 : 0;
+    int form() const { return bias || again || ld > kFormMaxLd ? -1 : res ? (relu ? 2 : -1) : relu ? 1 : 0; }
+    template <int F> static __device__ __host__ auto raw8f() {
+        if constexpr (F == 2) return Row8{};
+        else return NoRow8{};
+    }
+    template <int F> __device__ __forceinline__ auto request8f(int64_t base, uint32_t off) const {
+        decltype(raw8f<F>()) p;
+        if constexpr (F == 2) p.r.load(at_lane(res, base, off));
+        return p;
+    }
+    template <int F, class R> __device__ __forceinline__ void finish8f(const Col8& c, const R& p, int64_t base, uint32_t off, float (&v)[8], int) const {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = to_f32(from_f32<TOut>(v[e]));
+        store8(at_lane(out, base, off), v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = to_f32(from_f32<TOut>(c.g[e] * v[e] + c.s[e]));   // rounded as the stored tensor would be
+        if constexpr (F == 2) {
+            float r[8];
+            p.r.get(r);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += r[e];
+        }
+        if constexpr (F >= 1) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+        }
+        store8(at_lane(yout, base, off), v);
+    }
     __device__ __forceinline__ void rowsum(int, float, int) const {}
 };
 
@@ -307,6 +391,44 @@ template <typename TOut, typename TMask> struct EpiMask {
         }
         store8(out + i, v);
     }
+    // 0: no mask, 1: ReLU's, 2: GELU's, 3: what others have contributed and ReLU's
+    static constexpr bool kFormed = false;
+    static constexpr int kForms = sizeof(TOut) == 2 && sizeof(TMask) == 2 ? 4 : 0;
+    int form() const {
+        if (ld > kFormMaxLd) return -1;
+        if (add) return mask && mode == kActRelu ? 3 : -1;
+        return !mask ? 0 : mode == kActGelu ? 2 : 1;
+    }
+    struct Mask8 { Raw8<TMask> t; };
+    template <int F> static __device__ __host__ auto raw8f() {
+        if constexpr (F == 3) return Row8{};
+        else if constexpr (F > 0) return Mask8{};
+        else return NoRow8{};
+    }
+    template <int F> __device__ __forceinline__ auto request8f(int64_t base, uint32_t off) const {
+        decltype(raw8f<F>()) p;
+        if constexpr (F == 3) p.a.load(at_lane(add, base, off));
+        if constexpr (F > 0) p.t.load(at_lane(mask, base, off));
+        return p;
+    }
+    template <int F, class R> __device__ __forceinline__ void finish8f(const Col8&, const R& p, int64_t base, uint32_t off, float (&v)[8], int) const {
+        if constexpr (F == 3) {
+            float a[8];
+            p.a.get(a);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += a[e];
+        }
+        if constexpr (F > 0) {
+            float t[8];
+            p.t.get(t);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if constexpr (F == 2) v[e] *= t[e];
+                else if (!(t[e] > 0.0f)) v[e] = 0.0f;
+            }
+        }
+        store8(at_lane(out, base, off), v);
+    }
     __device__ __forceinline__ void rowsum(int, float, int) const {}
 };
 
@@ -328,6 +450,14 @@ struct EpiWgrad {
     __device__ __forceinline__ Row8 row8(int64_t, bool) const { return Row8{}; }
     __device__ __forceinline__ void at8(const Col8&, const Row8&, int64_t idx, float (&v)[8], int z) const {
         store8(out + z * slice_stride + idx, v);
+    }
+    static constexpr bool kFormed = false;
+    static constexpr int kForms = 1;
+    int form() const { return ld > kFormMaxLd ? -1 : 0; }
+    template <int> static __device__ __host__ NoRow8 raw8f() { return NoRow8{}; }
+    template <int> __device__ __forceinline__ NoRow8 request8f(int64_t, uint32_t) const { return NoRow8{}; }
+    template <int> __device__ __forceinline__ void finish8f(const Col8&, const NoRow8&, int64_t base, uint32_t off, float (&v)[8], int z) const {
+        store8(at_lane(out + z * slice_stride, base, off), v);
     }
     __device__ __forceinline__ void rowsum(int m, float v, int z) const {
         out[z * slice_stride + bias_off + m] = v;

@@ -18,10 +18,13 @@
 // are avoided by permuting 16-byte chunks with an XOR of the row (k-contiguous tiles, [rows][64]) or of k
 // (row-contiguous tiles, [64][rows]), which only changes WHICH global chunk a lane fetches.
 // Fragments: k-contiguous tiles are read with 16-byte LDS reads, row-contiguous ones with the transpose
-// read of gfx950.  Results are transposed through LDS on their way out, so that every lane stores 16 bytes and
-// a store instruction covers whole 128-byte lines: the wave must wait for its stores before it can tell that
-// a later copy has landed (both are counted by the same counter), so slow scattered stores would stall the
-// k-loop of the next unit.
+// read of gfx950.  Results are transposed through 4 KB of LDS that each wave has to itself, so that every lane stores 16 bytes and
+// a store instruction covers whole 128-byte lines.  Copies and stores are counted by the same counter, in order: before a unit's first store the
+// wave waits for its copies in flight, which have had the last multiplies to arrive in, and then need not wait again for NS - 1 k-tiles, in which
+// the stores drain.
+// What bounds it, by the device clock of each workgroup: 8192 x 768 over 3072 38 us, of which 2 are the first copies, 35 the k-loop, 3 the results; over 768 9 of 14.
+// The results took 4.5 us (6.6 the first time, when their code is fetched) as long as they asked at each 8 elements what to do with them (see EpiForm): 8192 x 768
+// over 2304 37.7 -> 35.0 us, 8192 x 3072 over 768 with GELU's mask in GPT-2's stage 65 -> 58.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -91,8 +94,9 @@ template <class T> __device__ __forceinline__ void settle(const T& t) {
     }
 }
 
-// LDS bytes of one launch
-template <int BM, int BN, int BK, int NS> constexpr int gemm3_lds_bytes() { return NS * (BM + BN) * BK * 2; }
+// LDS bytes of one launch: the stages, and 4 KB for each wave's results on their way out
+constexpr int kG3StageOut = 4096;
+template <int BM, int BN, int BK, int NS> constexpr int gemm3_lds_bytes(int waves) { return NS * (BM + BN) * BK * 2 + waves * kG3StageOut; }
 
 // what a copy reads in place of elements that are not there
 __device__ __attribute__((aligned(16))) static const uint32_t g3_zeros[4] = {0, 0, 0, 0};
@@ -256,7 +260,7 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     constexpr int G = LoaderA::GROUPS + LoaderB::GROUPS;   // copy instructions per wave and k-tile
     static_assert((NS - 1) * G <= 63, "too many copies in flight for the vmcnt counter");
     static_assert(!ROWSUM || !AKC, "row sums are built for a row-contiguous A");
-    static_assert(TN % 2 == 0 && G >= 8, "results are staged 32 x 64 at a time through 8 KB of a wave's own copy targets");
+    static_assert(TN % 2 == 0, "results are staged 16 x 64 at a time");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     const lds_t smem = (lds_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
 
@@ -353,6 +357,9 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     constexpr int PD = NW <= 4 ? 2 : 1, NBUF = PD == 2 ? 4 : 2;
     static_assert(PD < KK && KK % NBUF == 0, "the fragment sets rotate once per k-tile");
     bf16x8_t af[NBUF][TM], bfr[NBUF][TN];
+    // Weight gradients keep a unit's last k-tile apart and refill its stage behind the results: with two sets of sums the registers that it would take to walk on
+    // are moved back and forth in every k-tile (ragged rows: 418 moves instead of 256; a stage of two blocks of 512 features over 3996 rows 1065 us instead of 1005).
+    constexpr bool PEEL = ROWSUM;
     int cstage = 0;
     for (int cu = vb; cu < units; cu += grid) {
         const G3Unit cur = work.unit(cu);
@@ -424,13 +431,18 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         typename Work::Epi::Row8 prow[NB][4];
         // (ln: the lane's index as the caller has it; see the epilogue)
         auto epi_n = [&](int jp, int ln) { return n0 + wn * (BN / WN) + jp * 64 + (ln & 7) * 8; };
+        constexpr bool FORMED = Work::Epi::kFormed, ROWS = !std::is_empty<typename Work::Epi::Row8>::value;
+        const int mw = m0 + wm * (BM / WM), mr = min(mw, M - 1);   // the wave's first row, and where its requests start
         auto epi_request = [&](int b, int ln) {
             const int i = b / (TN / 2), jp = b % (TN / 2), n = min(epi_n(jp, ln), N - 8);
             if (i == 0) pcol[jp] = epi.col8(n);
+            if constexpr (ROWS) {
 #pragma unroll
-            for (int sp = 0; sp < 4; ++sp) {
-                const int pm = m0 + wm * (BM / WM) + i * 32 + sp * 8 + (ln >> 3);
-                prow[b][sp] = epi.row8((int64_t)min(pm, M - 1) * epi_ld + n, true);
+                for (int sp = 0; sp < 4; ++sp) {
+                    const int r = min(i * 32 + sp * 8 + (ln >> 3), M - 1 - mr);
+                    if constexpr (FORMED) prow[b][sp] = epi.row8f((int64_t)mr * epi_ld, __umul24((uint32_t)r, (uint32_t)epi_ld) + n);
+                    else prow[b][sp] = epi.row8((int64_t)(mr + r) * epi_ld + n, true);
+                }
             }
         };
         // With registers to spare (the 4-wave instances: 512 per lane) all of it is requested before the k-loop; the
@@ -438,8 +450,11 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         // its requests in issue order, stores included: waiting for data requested after a store means waiting for the
         // store to be acknowledged.
         constexpr bool EARLY = NW <= 4;
-        // (a block at a time where the columns' data is more than a bias: 24 registers of gains, shifts and biases leave none for two blocks' rows)
-        constexpr bool AHEAD = !EARLY && sizeof(typename Work::Epi::Col8) <= 32;
+        // (a block at a time where the columns' data is more than a bias: 24 registers of gains, shifts and biases leave none for two blocks' rows; and where the
+        // general epilogue has 8 registers of a row)
+        constexpr bool AHEAD = !EARLY && sizeof(typename Work::Epi::Col8) <= 32 && (Work::Epi::kFormed || sizeof(typename Work::Epi::Row8) < 32);
+        // k-tiles whose next one has landed: the copies that were waited for before the last unit's first store are those of NS k-tiles (one fewer with PEEL)
+        const int quiet = cu == vb ? 0 : PEEL ? NS - 2 : NS - 1;
         if (cu == vb) {
             // The workgroup's first k-tile: wait for it and make it visible to all waves.  (Here, so that what stands above, which needs none of it, is
             // done while it is on its way.)
@@ -466,10 +481,11 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         }
 
         // One k-tile.  Invariant: the fragments of its first PD multiply steps are in registers or on their way (requested during the previous
-        // k-tile's last PD steps); `ahead` younger k-tiles are in flight or have landed.  last: the unit's last one, which requests no fragments for a next.
+        // k-tile's last PD steps); `ahead` younger k-tiles are in flight or have landed.  last: the unit's last one, if that is a form of its own (PEEL),
+        // which requests no fragments for a next.
         //
-        // fill: after the barrier its stage is free and refilled at once, the copies spread over the multiplies that follow the barrier; not in a
-        // unit's last k-tile, whose stage the results go through first, nor when all is copied.  The two forms are loops of their own, and the
+        // fill: after the barrier its stage is free and refilled at once, the copies spread over the multiplies that follow the barrier, unless all is
+        // copied.  The two forms are loops of their own, and the
         // one that is walked nearly always has no branch in it: with a wave or two to a SIMD every branch, every address that is put together and every
         // pointer that is stepped between two multiplies delays the next one.  256 x 128 tiles, four waves: 1830 cycles a k-tile with a test before
         // each copy and its address in 64-bit registers, 1500 as it is (multiplies 1024); 8192 x 768 over 3072 51 -> 43 us, 8192^3 in 256 x 256 tiles 874 -> 814 us.
@@ -487,8 +503,10 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
                     // flight: copies complete in issue order, so it has landed once at most (ahead - 1) * G younger
                     // copies are outstanding.  Result stores of an earlier unit are younger than it too and only
                     // make the wait stricter.  While the pipeline drains (ahead < NS - 1) wait for everything.
-                    if (FILL || ahead == NS - 1) wait_vmcnt<(NS - 2) * G>();
-                    else wait_vmcnt<0>();
+                    if (kt >= quiet) {
+                        if (FILL || ahead == NS - 1) wait_vmcnt<(NS - 2) * G>();
+                        else wait_vmcnt<0>();
+                    }
                     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's reads of the current stage are done
                     __builtin_amdgcn_s_barrier();
                     // All waves are past their last read of the current stage, and the next k-tile is visible to all:
@@ -534,15 +552,15 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
                 });
             });
             if constexpr (FILL) advance();
-            else if constexpr (!LAST) --ahead;
-            if constexpr (!LAST) cstage = nstage;
+            else if (ahead > 0) --ahead;
+            cstage = nstage;
             if constexpr (FILL) asm volatile("; tmps k-tile end");
         };
-        const int filled = min(nk - 1, left);
+        const int filled = min(PEEL ? nk - 1 : nk, left);
         int kt = 0;
         for (; kt < filled; ++kt) k_tile(kt, std::true_type{}, std::false_type{});
-        for (; kt + 1 < nk; ++kt) k_tile(kt, std::false_type{}, std::false_type{});
-        k_tile(kt, std::false_type{}, std::true_type{});
+        for (; kt < (PEEL ? nk - 1 : nk); ++kt) k_tile(kt, std::false_type{}, std::false_type{});
+        if constexpr (PEEL) k_tile(kt, std::false_type{}, std::true_type{});
         if constexpr (TOT) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
@@ -555,11 +573,9 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         }
 
         // ---- results ----
-        // The stage of the unit's last k-tile is free and not yet refilled: each wave passes its accumulators
-        // through the 8 KB of that stage that its own copies write (so no other wave touches them), one block of
-        // 32 rows x 64 columns of fp32 at a time, and leaves with 8 consecutive columns of one row per lane: a store
-        // instruction then writes 8 rows of 128 (bf16) or 256 (fp32) consecutive bytes.  A block's 16-byte chunks lie at an XOR of their row, so that
-        // neither side's accesses meet in a bank.
+        // Each wave passes its accumulators through 4 KB of LDS of its own, one half of a block at a time (16 rows x 64 columns of fp32), and leaves with 8
+        // consecutive columns of one row per lane: a store instruction then writes 8 rows of 128 (bf16) or 256 (fp32) consecutive bytes.  A half's
+        // 16-byte chunks lie at an XOR of their row, so that neither side's accesses meet in a bank.
         {
             // Everything the epilogue derives from the lane's index is derived here, from a copy of the index that the
             // compiler cannot trace back: otherwise it computes these offsets before the k-loop and, in the 8-wave
@@ -567,52 +583,94 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
             // memory is a wait for all of the wave's requests, result stores included.
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            // staged row r: piece r / 4 (1 KB: the wave's copy group of that number), row r % 4 of it; chunk c (4 columns) at c ^ (r % 16)
-            const lds_t stg = smem + cstage * STAGE + wave * 1024;
-            static_assert(A_BYTES == LoaderA::GROUPS * NW * 1024, "a wave's copy groups lie NW KB apart, from A's tile on to B's");
-            lds_t put = stg + ((ln & 31) >> 2) * (NW * 1024) + (ln & 3) * 256 + (((ln >> 5) ^ (ln & 15)) << 4);
-            lds_t get = stg + (ln >> 5) * (NW * 1024) + ((ln >> 3) & 3) * 256 + (((2 * (ln & 7)) ^ (ln >> 3)) << 4);
+            // staged row r (of 16) takes 256 bytes; chunk c (4 columns) lies at c ^ r
+            const lds_t stg = smem + NS * STAGE + wave * kG3StageOut;
+            lds_t put = stg + (ln & 15) * 256 + (((ln >> 5) ^ (ln & 15)) << 4);
+            lds_t get = stg + (ln >> 3) * 256 + (((2 * (ln & 7)) ^ (ln >> 3)) << 4);
+            typedef float f32x4_t __attribute__((ext_vector_type(4)));
+            // half h (16 rows) of block b through LDS.  (A wave's LDS instructions take effect in order.)
+            auto stage = [&](int b, int h) {
+                const int i = b / (TN / 2), jp = b % (TN / 2);
+                // accumulator register r of a lane: row lane % 32, column 8 (r / 4) + 4 (lane / 32) + r % 4
+                if (((ln >> 4) & 1) == h) {
+#pragma unroll
+                    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x16_t& v = acc[i][2 * jp + jj];
+                            *lds_ptr<f32x4_t>(put ^ ((jj * 8 + q * 2) << 4)) = f32x4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+                        }
+                }
+                asm volatile("" ::: "memory");
+            };
+            auto fetch = [&](float (&v)[2][8]) {
+#pragma unroll
+                for (int sp = 0; sp < 2; ++sp) {
+                    // staged row 8 sp + lane / 8, chunks 2 (lane % 8) and the next
+                    const lds_t src = (get ^ (sp << 7)) + sp * 2048;
+                    const f32x4_t lo = *lds_ptr<const f32x4_t>(src), hi = *lds_ptr<const f32x4_t>(src ^ 16);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[sp][e] = lo[e];
+                        v[sp][4 + e] = hi[e];
+                    }
+                }
+                asm volatile("" ::: "memory");
+            };
             if constexpr (EARLY) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     if (b < TN / 2) settle(pcol[b]);
+                    if constexpr (ROWS) {
 #pragma unroll
-                    for (int sp = 0; sp < 4; ++sp) settle(prow[b][sp]);
+                        for (int sp = 0; sp < 4; ++sp) settle(prow[b][sp]);
+                    }
                 }
             } else if constexpr (AHEAD) epi_request(0, ln);
+            // The half in work and, where registers allow, the next one, on its way through LDS meanwhile (8-wave instances that ask for everything have none left).
+            constexpr bool NEXT = EARLY || FORMED;
+            float v[2][2][8];
+            if constexpr (NEXT) {
+                stage(0, 0);
+                fetch(v[0]);
+            }
+            const uint32_t off = (uint32_t)(ln >> 3) * (uint32_t)epi_ld + (ln & 7) * 8;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const int i = b / (TN / 2), jp = b % (TN / 2);
                 const int n = epi_n(jp, ln);
-                asm volatile("" : "+v"(put), "+v"(get));   // (a block's addresses are formed anew: kept for the next one they would be spilled)
-                if constexpr (!EARLY && !AHEAD) epi_request(b, ln);
-                typedef float f32x4_t __attribute__((ext_vector_type(4)));
-                // accumulator register r of a lane: row lane % 32, column 8 (r / 4) + 4 (lane / 32) + r % 4
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const f32x16_t& v = acc[i][2 * jp + jj];
-                        *lds_ptr<f32x4_t>(put ^ ((jj * 8 + q * 2) << 4)) = f32x4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-                    }
                 if constexpr (!EARLY) {
                     // the block's data before the next block's requests and its own first store
+                    if constexpr (!AHEAD) epi_request(b, ln);
                     if (i == 0) settle(pcol[jp]);
+                    if constexpr (ROWS) {
 #pragma unroll
-                    for (int sp = 0; sp < 4; ++sp) settle(prow[b][sp]);
-                    if (AHEAD && b + 1 < NB) epi_request(b + 1, ln);
+                        for (int sp = 0; sp < 4; ++sp) settle(prow[b][sp]);
+                    }
                 }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (b == 0) wait_vmcnt<0>();
+                if constexpr (AHEAD) {
+                    if (b + 1 < NB) epi_request(b + 1, ln);
+                }
 #pragma unroll
-                for (int sp = 0; sp < 4; ++sp) {
-                    // staged row 8 sp + lane / 8, chunks 2 (lane % 8) and the next
-                    const lds_t src = (get ^ ((sp & 1) << 7)) + 2 * sp * (NW * 1024);
-                    const f32x4_t lo = *lds_ptr<const f32x4_t>(src), hi = *lds_ptr<const f32x4_t>(src ^ 16);
-                    float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-                    const int m = m0 + wm * (BM / WM) + i * 32 + sp * 8 + (ln >> 3);
-                    if (m < M && n < N) epi.at8(pcol[jp], prow[b][sp], (int64_t)m * epi_ld + n, v, z);   // N is a multiple of 8
+                for (int h = 0; h < 2; ++h) {
+                    if constexpr (!NEXT) {
+                        stage(b, h);
+                        fetch(v[h]);
+                    } else if (2 * b + h + 1 < 2 * NB) {
+                        stage(b + (h == 1), 1 - h);
+                        fetch(v[1 - h]);
+                    }
+#pragma unroll
+                    for (int sp = 0; sp < 2; ++sp) {
+                        const int row = i * 32 + h * 16 + sp * 8;   // of the wave's
+                        const int m = mw + row + (ln >> 3);
+                        if (m < M && n < N) {   // N is a multiple of 8
+                            if constexpr (FORMED) epi.at8f(pcol[jp], prow[b][2 * h + sp], (int64_t)(mw + row) * epi_ld + (n0 + wn * (BN / WN) + jp * 64), off, v[h][sp], z);
+                            else epi.at8(pcol[jp], prow[b][2 * h + sp], (int64_t)m * epi_ld + n, v[h][sp], z);
+                        }
+                    }
                 }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // staged values are in registers before they are overwritten
             }
         }
         if constexpr (ROWSUM) {
@@ -627,11 +685,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
                 }
             }
         }
-        // refill the stage the results went through, and move on to the next unit's first k-tile
-        if (issue_next()) ++ahead;
-        if (ahead > 0) {
-            --ahead;
-            cstage = cstage + 1 == NS ? 0 : cstage + 1;
+        if constexpr (PEEL) {
+            if (issue_next()) ++ahead;
         }
     }
 }
@@ -669,7 +724,7 @@ struct G3Job {
     FastDiv d_minor;   // by the tiles along the direction walked first
 };
 struct G3Group {
-    typedef EpiWgrad Epi;
+    typedef EpiForm<EpiWgrad, 0> Epi;
     static constexpr bool kTotals = true, kRagged = false;
     static constexpr int kRows = 256, kCols = 128, kPart = kRows * kCols + kRows;   // a tile; floats of a partial one: results, then row sums
     G3Job job[kG3GroupMax];
@@ -716,11 +771,11 @@ struct G3Group {
     __device__ __forceinline__ int M(const G3Unit& g) const { return job[g.job].M; }
     __device__ __forceinline__ int N(const G3Unit& g) const { return job[g.job].N; }
     // (addressed as the whole matrix is: a partial tile's base lies as far in front of it as the tile's first element lies inside the matrix)
-    __device__ __forceinline__ EpiWgrad epi(const G3Unit& g) const {
+    __device__ __forceinline__ Epi epi(const G3Unit& g) const {
         const G3Job& j = job[g.job];
-        if (g.z < 0) return EpiWgrad{j.out, j.N, (int64_t)j.M * j.N, 0};
+        if (g.z < 0) return Epi{EpiWgrad{j.out, j.N, (int64_t)j.M * j.N, 0}};
         const int64_t first = (int64_t)g.m0 * kCols + g.n0;
-        return EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kCols, first + kRows * kCols - g.m0, 0};
+        return Epi{EpiWgrad{part + ((int64_t)g.part_tile * slices + g.z) * kPart - first, kCols, first + kRows * kCols - g.m0, 0}};
     }
 };
 // Over rows that are no multiple of 64: the last k-tile of the last slice is short.  An instance and a way to a unit of its own, so that its tests are paid only where rows

@@ -417,16 +417,30 @@ static G3Plan g3_plan(int M, int N, int K, int slices, int bm = kG3Tile, int bn 
 }
 
 // 256 x 256 x 64 tiles, 8 waves (2 x 4), two LDS stages: the configuration that did best on every large shape tried.
+// f(epi) with the epilogue as its form's type where it has one
+template <int F = 0, class Epi, class Fn> static hipError_t with_form(int form, const Epi& epi, Fn&& f) {
+    if constexpr (F < Epi::kForms) return form == F ? f(EpiForm<Epi, F>{epi}) : with_form<F + 1>(form, epi, f);
+    else return f(epi);
+}
+
 template <int BM, int BN, int WM, int WN, int NS, int PER_CU, bool AKC, bool BKC, bool ROWSUM, class Epi>
-static hipError_t launch3_inst(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>& B, const Epi& epi, int M, int N, int K,
+static hipError_t launch3_form(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>& B, const Epi& epi, int M, int N, int K,
                                const G3Plan& plan, hipStream_t s) {
-    constexpr int lds = gemm3_lds_bytes<BM, BN, 64, NS>();
+    constexpr int lds = gemm3_lds_bytes<BM, BN, 64, NS>(WM * WN);
     auto kern = gemm3_kernel<BM, BN, 64, WM, WN, NS, AKC, BKC, ROWSUM, Epi>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     const int slots = compute_units() * PER_CU;
     const int grid = plan.units < slots ? plan.units : slots;
     return launch_timed(kc, kern, dim3(grid), dim3(64 * WM * WN), lds, s, A, B, epi, M, N, K, plan);
+}
+
+template <int BM, int BN, int WM, int WN, int NS, int PER_CU, bool AKC, bool BKC, bool ROWSUM, class Epi>
+static hipError_t launch3_inst(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>& B, const Epi& epi, int M, int N, int K,
+                               const G3Plan& plan, hipStream_t s) {
+    return with_form(epi.form(), epi, [&](const auto& e) {
+        return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM>(kc, A, B, e, M, N, K, plan, s);
+    });
 }
 
 template <bool AKC, bool BKC, bool ROWSUM, class Epi>
@@ -520,7 +534,7 @@ static double wgrad_alone_us(int64_t M, int64_t N, int64_t K) {
 
 // (not where more than a quarter of the 256-wide tiles would be padding)
 bool dense_wgrad_groups(int dtype, int64_t rows, int Din, int Dout) {
-    return dtype == kBF16 && rows >= 512 && rows < (int64_t(1) << 31) && Din % 8 == 0 && Dout % 8 == 0 &&
+    return dtype == kBF16 && rows >= 512 && rows < (int64_t(1) << 31) && Din % 8 == 0 && Dout % 8 == 0 && Din <= kFormMaxLd &&
            (int64_t)cdiv(Din, 256) * 256 * 3 <= (int64_t)Din * 4 && (int64_t)cdiv(Dout, 256) * 256 * 3 <= (int64_t)Dout * 4;
 }
 
@@ -558,7 +572,7 @@ hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_
     g.slices = p.slices; g.chain = p.chain;
     if (p.slices == 1) g.whole = tiles;   // (one slice is the whole of k)
     g.d_cut = FastDiv(cut > 0 ? cut : 1);
-    constexpr int lds = gemm3_lds_bytes<G3Group::kRows, G3Group::kCols, 64, kG3GroupStages>();
+    constexpr int lds = gemm3_lds_bytes<G3Group::kRows, G3Group::kCols, 64, kG3GroupStages>(4);
     void (*const kern)(G3Group) = gemm3_kernel;
     void (*const ragged)(G3GroupRagged) = gemm3_kernel;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -1,0 +1,35 @@
+"""Epilogues of the persistent kernel whose arguments make them an instance of their own (bias alone, ReLU, GELU and its derivative, a residual source; masks
+of both activations, with and without what others have contributed), on tiles that the output's last rows and columns leave partly empty, in both tile sizes, over
+as few k-tiles as the kernel takes; beside them combinations that keep the general epilogue.  Against the oracle."""
+import pytest
+
+from tests import routes
+from tests.test_gpu_stage import run_stage_case
+from workloads.configs import layernorm, linear, softmax_ce
+
+WIDE = 12400   # rows of 49 tiles of 256, the last one with 112; 1000 columns are 4 tiles, the last one with 232
+CASES = [
+    # (layers, rows)
+    ([linear(128, 1000, False), linear(1000, 128, False)], WIDE),
+    ([linear(128, 1000, True), linear(1000, 128, False)], WIDE),
+    ([linear(192, 1000, False, act="gelu"), linear(1000, 192, False)], WIDE),
+    ([layernorm(1000, 1), linear(1000, 128, False), linear(128, 1000, False, skip=2), linear(1000, 128, False)], WIDE),   # a residual source; its gradient is added to
+    ([linear(128, 1000, True)], WIDE),                                                               # the result twice: general
+    ([linear(128, 1000, False), softmax_ce(1000)], WIDE),                                            # fp32 results
+    ([linear(1024, 1024, True), linear(1024, 1024, False)], 4200),                                   # 256 x 128 tiles
+    ([layernorm(1024, 1), linear(1024, 1024, False, act="gelu"), linear(1024, 1024, False, skip=2), linear(1024, 1024, False)], 4200),
+]
+
+
+def test_cases_reach_the_persistent_kernel():
+    for layers, rows in CASES:
+        wide = max((l for l in layers if l["kind"] == "linear"), key=lambda l: l["dout"])
+        want = "persistent narrow" if rows == 4200 else "persistent"
+        assert routes.dense_routes(wide, "bf16", rows, 1)[0] == want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_forms(case):
+    layers, rows = CASES[case]
+    run_stage_case(layers, "bf16", rows, 1, seed=case)
