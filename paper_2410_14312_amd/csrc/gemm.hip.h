@@ -132,6 +132,15 @@ template <class E, int F> struct EpiForm : E {
     __device__ __forceinline__ void at8f(const typename E::Col8& c, const Row8& p, int64_t base, uint32_t off, float (&v)[8], int z) const {
         E::template finish8f<F>(c, p, base, off, v, z);
     }
+    // (for kernels whose rows lie where their loader says)
+    __device__ __forceinline__ Row8 row8(int64_t idx, bool ok) const {
+        Row8 p;
+        if (ok) p = E::template request8f<F>(idx, 0);
+        return p;
+    }
+    __device__ __forceinline__ void at8(const typename E::Col8& c, const Row8& p, int64_t idx, float (&v)[8], int z) const {
+        E::template finish8f<F>(c, p, idx, 0, v, z);
+    }
 };
 
 // Host-side test for the 8-wide (16-byte) form of an epilogue: every tensor it touches is 16-byte aligned and a row

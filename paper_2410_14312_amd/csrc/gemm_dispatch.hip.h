@@ -101,8 +101,14 @@ static hipError_t launch2_inst(int kc, const AOp& A, const BOp& B, const Epi& ep
 }
 
 
+// f(epi) with the epilogue as its form's type where it has one
+template <int F = 0, class Epi, class Fn> static hipError_t with_form(int form, const Epi& epi, Fn&& f) {
+    if constexpr (F < Epi::kForms) return form == F ? f(EpiForm<Epi, F>{epi}) : with_form<F + 1>(form, epi, f);
+    else return f(epi);
+}
+
 template <bool ROWSUM, class AOp, class BOp, class Epi>
-static hipError_t launch4(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
+static hipError_t launch4_form(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
     auto kern = gemm4_kernel<ROWSUM, AOp, BOp, Epi>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kGemm4Lds);
     if (attr != hipSuccess) return attr;
@@ -114,7 +120,16 @@ static hipError_t launch4(int kc, const AOp& A, const BOp& B, const Epi& epi, in
 
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>
-static hipError_t launch5(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
+static hipError_t launch4(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
+    if constexpr (sizeof(typename AOp::T) == 2 && by_k_mode<AOp, BOp>() == kByKDense && Epi::kForms > 1) {
+        if (N % 8 == 0 && epi.wide_ok())
+            return with_form(epi.form(), epi, [&](const auto& e) { return launch4_form<ROWSUM>(kc, A, B, e, M, N, K, per, nz, s); });
+    }
+    return launch4_form<ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
+}
+
+template <bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t launch5_form(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
     constexpr int lds = kGemm5Lds;
     auto kern = gemm5_kernel<ROWSUM, AOp, BOp, Epi>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -122,6 +137,14 @@ static hipError_t launch5(int kc, const AOp& A, const BOp& B, const Epi& epi, in
     dim3 grid(cdiv(N, 128), cdiv(M, 128), nz);
     const XcdOrder o = xcd_order(grid.x, grid.y, nz, M, N, by_k_mode<AOp, BOp>() == kByKDense);
     return launch_timed(kc, kern, grid, dim3(64 * kGemm5Waves), lds, s, A, B, epi, M, N, K, per, o.order, FastDiv(grid.x * grid.y), FastDiv(o.minor));
+}
+
+// (dense layers' epilogues in their forms, as the persistent kernel has them)
+template <bool ROWSUM, class AOp, class BOp, class Epi>
+static hipError_t launch5(int kc, const AOp& A, const BOp& B, const Epi& epi, int M, int N, int K, int per, int nz, hipStream_t s) {
+    if constexpr (by_k_mode<AOp, BOp>() == kByKDense && Epi::kForms > 1)
+        return with_form(epi.form(), epi, [&](const auto& e) { return launch5_form<ROWSUM>(kc, A, B, e, M, N, K, per, nz, s); });
+    else return launch5_form<ROWSUM>(kc, A, B, epi, M, N, K, per, nz, s);
 }
 
 template <bool ROWSUM, class AOp, class BOp, class Epi>

@@ -417,12 +417,6 @@ static G3Plan g3_plan(int M, int N, int K, int slices, int bm = kG3Tile, int bn 
 }
 
 // 256 x 256 x 64 tiles, 8 waves (2 x 4), two LDS stages: the configuration that did best on every large shape tried.
-// f(epi) with the epilogue as its form's type where it has one
-template <int F = 0, class Epi, class Fn> static hipError_t with_form(int form, const Epi& epi, Fn&& f) {
-    if constexpr (F < Epi::kForms) return form == F ? f(EpiForm<Epi, F>{epi}) : with_form<F + 1>(form, epi, f);
-    else return f(epi);
-}
-
 template <int BM, int BN, int WM, int WN, int NS, int PER_CU, bool AKC, bool BKC, bool ROWSUM, class Epi>
 static hipError_t launch3_form(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>& B, const Epi& epi, int M, int N, int K,
                                const G3Plan& plan, hipStream_t s) {

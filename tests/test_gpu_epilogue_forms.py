@@ -1,4 +1,4 @@
-"""Epilogues of the persistent kernel whose arguments make them an instance of their own (bias alone, ReLU, GELU and its derivative, a residual source; masks
+"""Epilogues of the persistent kernel and of those with asynchronous copies whose arguments make them an instance of their own (bias alone, ReLU, GELU and its derivative, a residual source; masks
 of both activations, with and without what others have contributed), on tiles that the output's last rows and columns leave partly empty, in both tile sizes, over
 as few k-tiles as the kernel takes; beside them combinations that keep the general epilogue.  Against the oracle."""
 import pytest
@@ -18,14 +18,19 @@ CASES = [
     ([linear(128, 1000, False), softmax_ce(1000)], WIDE),                                            # fp32 results
     ([linear(1024, 1024, True), linear(1024, 1024, False)], 4200),                                   # 256 x 128 tiles
     ([layernorm(1024, 1), linear(1024, 1024, False, act="gelu"), linear(1024, 1024, False, skip=2), linear(1024, 1024, False)], 4200),
+    ([linear(776, 2952, True), linear(2952, 776, False)], 1000),                                     # 128 x 128 tiles; 64 x 64 shared by k
+    ([layernorm(776, 1), linear(776, 2952, False, act="gelu"), linear(2952, 776, False, skip=2), linear(776, 64, False)], 1000),
+    ([linear(2056, 712, True), linear(712, 64, False)], 760),
 ]
 
 
-def test_cases_reach_the_persistent_kernel():
+KERNELS = {WIDE: "persistent", 4200: "persistent narrow", 1000: "async", 760: "by_k"}
+
+
+def test_cases_reach_their_kernels():
     for layers, rows in CASES:
         wide = max((l for l in layers if l["kind"] == "linear"), key=lambda l: l["dout"])
-        want = "persistent narrow" if rows == 4200 else "persistent"
-        assert routes.dense_routes(wide, "bf16", rows, 1)[0] == want
+        assert routes.dense_routes(wide, "bf16", rows, 1)[0] == KERNELS[rows]
 
 
 @pytest.mark.gpu
