@@ -24,7 +24,7 @@
 // the stores drain.
 // What bounds it, by the device clock of each workgroup: 8192 x 768 over 3072 38 us, of which 2 are the first copies, 35 the k-loop, 3 the results; over 768 9 of 14.
 // The results took 4.5 us (6.6 the first time, when their code is fetched) as long as they asked at each 8 elements what to do with them (see EpiForm): 8192 x 768
-// over 2304 37.7 -> 35.0 us, 8192 x 3072 over 768 with GELU's mask in GPT-2's stage 65 -> 58.
+// over 2304 37.7 -> 35.0 us, 8192 x 3072 over 768 with GELU's mask in GPT-2's stage 66 -> 61.
 #pragma once
 #include <type_traits>
 #include <utility>

@@ -354,7 +354,7 @@ bool g3_forward_ok(int64_t M, int64_t N, int64_t K) {
 // one round: 256 tiles of 4096 x 1024, contraction 1024, 14 us against 21, 215 tiles of 640 x 5504 13 against 24), and a k-loop of at least 8
 // k-tiles carries the unit's prologue and epilogue.  Input gradients, persistent and other kernels (us), contractions over 512 /
 // 1024 / 2048 / 4096: 8448 x 512 (264 tiles of 128 x 128) 15.6 / 20.6 / 33 / 61 and 14.8 / 22 / 44 / 78, 16384 x 512 (512 tiles)
-// 17.9 / 24 / 40 / 69 and 16.3 / 25 / 47 / 81; the 8192 x 768 of a transformer block, over 2304 / 768 / 3072, 45 / 21 / 57 and 52 / 23 / 67.
+// 17.9 / 24 / 40 / 69 and 16.3 / 25 / 47 / 81; the 8192 x 768 of a transformer block, over 2304 / 768 / 3072, 45 / 21 / 57 (now 35 / 17 / 44) and 52 / 23 / 67.
 bool g3_narrow_ok(int64_t M, int64_t N, int64_t K) {
     if (K % 64 != 0 || K < 512 || N % 128 != 0) return false;
     return (int64_t)cdiv(M, 256) * (N / 128) <= compute_units() && (int64_t)cdiv(M, 128) * (N / 128) > compute_units();
