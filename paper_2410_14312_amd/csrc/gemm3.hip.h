@@ -98,60 +98,66 @@ template <class T> __device__ __forceinline__ void settle(const T& t) {
 constexpr int kG3StageOut = 4096;
 template <int BM, int BN, int BK, int NS> constexpr int gemm3_lds_bytes(int waves) { return NS * (BM + BN) * BK * 2 + waves * kG3StageOut; }
 
+// Whether the bytes from a tile's first element to any of its chunks fit 32 bits: `lines` rows of the tile (k-contiguous) or k of a k-tile (row-contiguous), `ld`
+// elements apart, `across` elements each: up to 8.4 million elements apart for 256 rows, 34 million for 64 k.
+constexpr bool g3_offsets_fit(int lines, int across, int64_t ld) { return ((int64_t)(lines - 1) * ld + across) * 2 <= (int64_t(1) << 32); }
+
 // what a copy reads in place of elements that are not there
 __device__ __attribute__((aligned(16))) static const uint32_t g3_zeros[4] = {0, 0, 0, 0};
 
 // Per-wave copy state of one operand tile of ROWS rows x BK k (BK = 32 or 64): GROUPS 1-KB groups per k-tile.  A lane's address is a base that
 // the wave shares, stepped by the scalar unit, and a 32-bit offset that stays as it is for a unit: a copy is then three instructions.  With an
 // address of 64 bits in each lane, stepped after each copy, the vector unit's additions and moves took issue slots between the multiplies
-// (see the k-loop).  RAGGED units, whose last k-tile may end early, keep such addresses: zeros replace single lanes' sources there.
-template <int ROWS, int BK, int NW, bool KC, bool RAGGED> struct G3Loader {
+// (see the k-loop).  WIDE instances keep such addresses: units whose last k-tile may end early, where zeros replace single lanes' sources, and operands whose rows
+// (k-contiguous) or k (row-contiguous) lie so far apart that offsets inside a tile do not fit 32 bits (see offsets_fit).
+template <int ROWS, int BK, int NW, bool KC, bool WIDE> struct G3Loader {
     static constexpr int GROUPS = ROWS * BK * 2 / 1024 / NW;
     static_assert(GROUPS >= 1 && GROUPS * NW * 1024 == ROWS * BK * 2, "the waves must share a tile evenly");
     static_assert(KC || (ROWS / 8 <= 64 && 64 % (ROWS / 8) == 0), "a 1 KB group of a row-contiguous tile covers whole k-rows");
-    static_assert(!RAGGED || !KC, "k-rows are whole lanes of a row-contiguous tile only");
     const bf16_t* base;
-    uint32_t off[RAGGED ? 1 : GROUPS];
-    const bf16_t* ptr[RAGGED ? GROUPS : 1];
+    uint32_t off[WIDE ? 1 : GROUPS];
+    const bf16_t* ptr[WIDE ? GROUPS : 1];
+    __device__ __forceinline__ void place(int g, int line, int64_t ld, int at) {
+        if constexpr (WIDE) ptr[g] = base + (line * ld + at);
+        else off[g] = ((uint32_t)line * (uint32_t)ld + at) * 2;
+    }
     // (re)compute the lane addresses for the tile starting at row0, k range starting at k0
     __device__ __forceinline__ void seek(const G3Operand<KC>& op, int row0, int k0, int wave, int lane) {
         base = op.p + (KC ? (int64_t)row0 * op.ld + k0 : (int64_t)k0 * op.ld + row0);
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
             const int grp = wave + g * NW;
-            uint32_t o;
             if constexpr (KC) {
                 // LDS tile [ROWS][BK]; a group is 1 KB of consecutive rows; the 16-byte chunk at (r, p) holds global
                 // chunk p ^ s(r) of row r, s(r) = (r >> 1) & 7 for BK = 64 (8 chunks per row), (r >> 2) & 3 for BK = 32
                 constexpr int CPR = BK / 8;   // chunks per row
                 const int r = grp * (64 / CPR) + lane / CPR;
                 const int c = (lane % CPR) ^ (BK == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3));
-                o = (uint32_t)min(r, op.rows - 1 - row0) * (uint32_t)op.ld + c * 8;
+                place(g, min(r, op.rows - 1 - row0), op.ld, c * 8);
             } else {
                 // LDS tile [BK][ROWS]; the chunk at (k, p) holds rows 8 * (p ^ ((k & 3) << 2)) .. + 7 of k
                 constexpr int CPR = ROWS / 8;  // chunks per k-row
                 const int k = grp * (64 / CPR) + lane / CPR;
                 const int c = (lane % CPR) ^ ((k & 3) << 2);
-                o = (uint32_t)k * (uint32_t)op.ld + min(c * 8, op.rows - 8 - row0);
+                place(g, k, op.ld, min(c * 8, op.rows - 8 - row0));
             }
-            if constexpr (RAGGED) ptr[g] = base + o;
-            else off[g] = o * 2;
         }
     }
     // copy one of this wave's groups of the current k-tile (every one exactly once, in any order) into the tile whose LDS starts `wave` KB before `dst`
     template <int G> __device__ __forceinline__ void issue_group(lds_t dst) const {
-        if constexpr (RAGGED) copy16_to_lds(ptr[G], dst + G * NW * 1024);
+        if constexpr (WIDE) copy16_to_lds(ptr[G], dst + G * NW * 1024);
         else copy16_to_lds<G * NW * 1024>(base, off[G], dst);
     }
     // step to the next k-tile
     __device__ __forceinline__ void next(int64_t ld) {
-        if constexpr (RAGGED) {
+        if constexpr (WIDE) {
 #pragma unroll
-            for (int g = 0; g < GROUPS; ++g) ptr[g] += BK * ld;
+            for (int g = 0; g < GROUPS; ++g) ptr[g] += KC ? BK : BK * ld;
         } else base += KC ? BK : BK * ld;
     }
     // the current k-tile is a unit's last and has `left` k (fewer than BK): zeros take the place of those behind its end, which are not read
     __device__ __forceinline__ void cut(int wave, int lane, int left) {
+        static_assert(!KC && WIDE, "k-rows are whole lanes of a row-contiguous tile only");
         constexpr int CPR = ROWS / 8;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g)
@@ -216,9 +222,9 @@ struct G3Unit {
 };
 
 // The units of one contraction.
-template <int BM, int BN, int BK, bool AKC, bool BKC, class Epi_> struct G3One {
+template <int BM, int BN, int BK, bool AKC, bool BKC, class Epi_, bool WIDE> struct G3One {
     typedef Epi_ Epi;
-    static constexpr bool kTotals = false, kRagged = false;
+    static constexpr bool kTotals = false, kRagged = false, kWide = WIDE;
     G3Operand<AKC> A;
     G3Operand<BKC> B;
     Epi_ e;
@@ -255,8 +261,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int KK = BK / 16;
     constexpr int A_BYTES = BM * BK * 2, STAGE = (BM + BN) * BK * 2;
-    typedef G3Loader<BM, BK, NW, AKC, Work::kRagged> LoaderA;
-    typedef G3Loader<BN, BK, NW, BKC, Work::kRagged> LoaderB;
+    typedef G3Loader<BM, BK, NW, AKC, Work::kWide> LoaderA;
+    typedef G3Loader<BN, BK, NW, BKC, Work::kWide> LoaderB;
     constexpr int G = LoaderA::GROUPS + LoaderB::GROUPS;   // copy instructions per wave and k-tile
     static_assert((NS - 1) * G <= 63, "too many copies in flight for the vmcnt counter");
     static_assert(!ROWSUM || !AKC, "row sums are built for a row-contiguous A");
@@ -691,10 +697,10 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
     }
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool AKC, bool BKC, bool ROWSUM, class Epi>
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool AKC, bool BKC, bool ROWSUM, bool WIDE, class Epi>
 __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G3Operand<BKC> B, Epi epi, int M, int N,
                                                               int K, G3Plan plan) {
-    const G3One<BM, BN, BK, AKC, BKC, Epi> work{A, B, epi, M, N, K, plan};
+    const G3One<BM, BN, BK, AKC, BKC, Epi, WIDE> work{A, B, epi, M, N, K, plan};
     gemm3_walk<BM, BN, BK, WM, WN, NS, AKC, BKC, ROWSUM>(work);
 }
 
@@ -725,7 +731,7 @@ struct G3Job {
 };
 struct G3Group {
     typedef EpiForm<EpiWgrad, 0> Epi;
-    static constexpr bool kTotals = true, kRagged = false;
+    static constexpr bool kTotals = true, kRagged = false, kWide = false;
     static constexpr int kRows = 256, kCols = 128, kPart = kRows * kCols + kRows;   // a tile; floats of a partial one: results, then row sums
     G3Job job[kG3GroupMax];
     int jobs, k_total, tiles, whole;   // tiles of all jobs; the first `whole` of them are not sliced
@@ -784,8 +790,9 @@ struct G3Group {
 // 2399; four blocks of 640 in 1F1B order, 1564 rows a pass, 9 % of a run; one mini-batch of three blocks of 768 over 524 rows 1.5 %.
 // Errors of the gradients (2-norm, against 64 bits) of a block's layers in launches of their own and in one: 999 rows, 512 features 1.3 and 0.9e-7, 524 rows, 768 0.9 and
 // 0.7e-7, 1564 rows, 640 1.6 and 1.0e-7, 3996 rows, 512 1.9 and 1.1e-7 (the layer of 512 into 512, which had more slices, 1.0 and 1.1e-7), 8100 rows, 768 3.2 and 1.5e-7.
+// It also takes rows of any length (kWide).
 struct G3GroupRagged : G3Group {
-    static constexpr bool kRagged = true;
+    static constexpr bool kRagged = true, kWide = true;
     __device__ __forceinline__ G3Unit unit(int u) const {
         G3Unit g = G3Group::unit(u);
         const int k = (g.z < 0 ? k_total : min(k_total, g.k0 + k_per_slice)) - g.k0;

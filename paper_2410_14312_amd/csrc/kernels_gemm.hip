@@ -416,12 +416,21 @@ static G3Plan g3_plan(int M, int N, int K, int slices, int bm = kG3Tile, int bn 
     return p;
 }
 
+// Whether a tile of `rows` rows of an operand is copied at 32-bit offsets from a base that a wave shares.  Launches with longer rows are instances with
+// addresses in each lane, which every length fits: the tiled kernels, whose grids hold fewer than 65536 rows of tiles, would refuse a weight gradient of so many.  Forward
+// passes in 256 x 256 tiles have none (eight waves have no registers for such addresses beside that epilogue, 42 spills) and leave those rows to the tiled
+// kernels: 192 tiles of 8.4 million k are 315 GB of operands, masters and momentum at the least.
+bool g3_lane_offsets(bool k_contiguous, int rows, int64_t ld) {
+    return k_contiguous ? g3_offsets_fit(rows, 64, ld) : g3_offsets_fit(64, rows, ld);
+}
+static bool g3_forward_takes(int64_t M, int64_t N, int64_t K) { return g3_forward_ok(M, N, K) && g3_lane_offsets(true, kG3Tile, K); }
+
 // 256 x 256 x 64 tiles, 8 waves (2 x 4), two LDS stages: the configuration that did best on every large shape tried.
-template <int BM, int BN, int WM, int WN, int NS, int PER_CU, bool AKC, bool BKC, bool ROWSUM, class Epi>
+template <int BM, int BN, int WM, int WN, int NS, int PER_CU, bool AKC, bool BKC, bool ROWSUM, bool WIDE, class Epi>
 static hipError_t launch3_form(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>& B, const Epi& epi, int M, int N, int K,
                                const G3Plan& plan, hipStream_t s) {
     constexpr int lds = gemm3_lds_bytes<BM, BN, 64, NS>(WM * WN);
-    auto kern = gemm3_kernel<BM, BN, 64, WM, WN, NS, AKC, BKC, ROWSUM, Epi>;
+    auto kern = gemm3_kernel<BM, BN, 64, WM, WN, NS, AKC, BKC, ROWSUM, WIDE, Epi>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     const int slots = compute_units() * PER_CU;
@@ -432,8 +441,12 @@ static hipError_t launch3_form(int kc, const G3Operand<AKC>& A, const G3Operand<
 template <int BM, int BN, int WM, int WN, int NS, int PER_CU, bool AKC, bool BKC, bool ROWSUM, class Epi>
 static hipError_t launch3_inst(int kc, const G3Operand<AKC>& A, const G3Operand<BKC>& B, const Epi& epi, int M, int N, int K,
                                const G3Plan& plan, hipStream_t s) {
+    if (!g3_lane_offsets(AKC, BM, A.ld) || !g3_lane_offsets(BKC, BN, B.ld)) {
+        if constexpr (WM * WN > 4 && AKC && BKC) return hipErrorInvalidValue;   // (g3_forward_takes)
+        else return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM, true>(kc, A, B, epi, M, N, K, plan, s);
+    }
     return with_form(epi.form(), epi, [&](const auto& e) {
-        return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM>(kc, A, B, e, M, N, K, plan, s);
+        return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM, false>(kc, A, B, e, M, N, K, plan, s);
     });
 }
 
@@ -553,8 +566,10 @@ hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_
     if (dtype != kBF16 || n > kG3GroupMax) return hipErrorInvalidValue;
     G3GroupRagged g;
     int tiles = 0;
+    bool whole_rows = rows % 64 == 0;
     for (int i = 0; i < n; ++i) {
         const DenseWgradJob& j = jobs[i];
+        whole_rows = whole_rows && g3_lane_offsets(false, G3Group::kRows, j.Dout) && g3_lane_offsets(false, G3Group::kCols, j.Din);
         if (!dense_wgrad_groups(dtype, rows, j.Din, j.Dout) || !aligned16(j.dy) || !aligned16(j.x) || !aligned16(j.gw)) return hipErrorInvalidValue;
         const int tm = cdiv(j.Dout, G3Group::kRows), tn = cdiv(j.Din, G3Group::kCols), col_major = j.Din > j.Dout ? 1 : 0;
         g.job[i] = G3Job{(const bf16_t*)j.dy, (const bf16_t*)j.x, j.gw, j.Dout, j.Din, tiles, col_major, FastDiv(col_major ? tm : tn)};
@@ -574,7 +589,7 @@ hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_
     if (attr != hipSuccess || attr_r != hipSuccess) return attr != hipSuccess ? attr : attr_r;
     const int units = g.whole + (tiles - g.whole) * g.slices, slots = compute_units();
     const dim3 grid(units < slots ? units : slots);
-    hipError_t e = rows % 64 == 0 ? launch_timed(kcDenseWgrad, kern, grid, dim3(256), lds, s, (const G3Group&)g)
+    hipError_t e = whole_rows ? launch_timed(kcDenseWgrad, kern, grid, dim3(256), lds, s, (const G3Group&)g)
                                   : launch_timed(kcDenseWgrad, ragged, grid, dim3(256), lds, s, g);
     if (e != hipSuccess || p.slices == 1) return e;
     return launch_timed(kcSliceSum, g3_group_sum_kernel, dim3(cut, G3Group::kRows / 32), dim3(256), 0, s, (const G3Group&)g);
@@ -586,7 +601,7 @@ hipError_t dense_wgrad_group(int dtype, const DenseWgradJob* jobs, int n, int64_
 template <class Epi>
 static hipError_t dense_forward_bf16(int kc, const bf16_t* x, const bf16_t* w, const Epi& epi, bool aligned, int B, int Din, int Dout, float* ws,
                                      hipStream_t s) {
-    if (aligned && g3_forward_ok(B, Dout, Din) && aligned16(x) && aligned16(w)) {
+    if (aligned && g3_forward_takes(B, Dout, Din) && aligned16(x) && aligned16(w)) {
         G3Operand<true> A{x, B, Din};
         G3Operand<true> Bv{w, Dout, Din};
         return launch3<true, true, false>(kc, A, Bv, epi, B, Dout, Din, g3_plan(B, Dout, Din, 1), s);
@@ -804,7 +819,7 @@ hipError_t conv_affine_forward(int dtype, const void* x, const void* w, const fl
     if (pointwise(c) && pointwise_forward_takes(M, c.Cin, c.Cout, false) && aligned16(x) && aligned16(w) && epi.wide_ok())
         return pointwise_forward(PointwiseForward{x, w, res, bias, gain, shift, z, yout, again, relu}, nullptr, M, c.Cin, c.Cout, s);
     if (pointwise(c) && c.Cin % 8 == 0 && aligned16(x) && aligned16(w)) {
-        if (g3_forward_ok(M, c.Cout, K) && aligned16(z) && aligned16(bias) && aligned16(gain) && aligned16(shift) &&
+        if (g3_forward_takes(M, c.Cout, K) && aligned16(z) && aligned16(bias) && aligned16(gain) && aligned16(shift) &&
             aligned16(again) && aligned16(res) && aligned16(yout))
             return launch3<true, true, false>(kcConvFwd, G3Operand<true>{xb, M, K}, G3Operand<true>{wb, c.Cout, K}, epi, M, c.Cout, K,
                                               g3_plan(M, c.Cout, K, 1), s);
