@@ -539,9 +539,12 @@ static double wgrad_alone_us(int64_t M, int64_t N, int64_t K) {
     return (double)(rounds * per) * kG3KtileUs + (double)rounds * kG3UnitUs + partial_sums_us(s3, (double)M * N);
 }
 
-// (not where more than a quarter of the 256-wide tiles would be padding)
+// (not where more than a quarter of the 256-wide tiles would be padding; the eight rows that a wave stores at once lie within 2^32 bytes up to 2^27 columns of fp32, with
+// at least 192 rows 360 GB of masters, momentum, gradient and working copy)
+constexpr int64_t kGroupMaxCols = int64_t(1) << 27;
+static_assert((7 * kGroupMaxCols + 64) * 4 <= (int64_t(1) << 32), "offsets of a wave's stores");
 bool dense_wgrad_groups(int dtype, int64_t rows, int Din, int Dout) {
-    return dtype == kBF16 && rows >= 512 && rows < (int64_t(1) << 31) && Din % 8 == 0 && Dout % 8 == 0 && Din <= kFormMaxLd &&
+    return dtype == kBF16 && rows >= 512 && rows < (int64_t(1) << 31) && Din % 8 == 0 && Dout % 8 == 0 && Din <= kGroupMaxCols &&
            (int64_t)cdiv(Din, 256) * 256 * 3 <= (int64_t)Din * 4 && (int64_t)cdiv(Dout, 256) * 256 * 3 <= (int64_t)Dout * 4;
 }
 

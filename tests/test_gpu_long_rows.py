@@ -84,14 +84,21 @@ def test_weight_gradient(dout, din):
     _check_wgrad(gw, dy, x)
 
 
+GROUPED = [(LONG, 192), (192, LONG), (192, 2 ** 22 + 8)]   # the last one: rows that offsets reach, more columns than the forms of other epilogues take
+
+
+@pytest.mark.parametrize("dout,din", GROUPED)
+def test_the_rule_groups_long_rows(dout, din):
+    asked = getattr(load_library(), "_ZN4tmps18dense_wgrad_groupsEilii")
+    asked.restype = C.c_bool
+    assert asked(BF16, C.c_long(512), din, dout)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("dout,din", [(LONG, 192)])
+@pytest.mark.parametrize("dout,din", GROUPED)
 def test_grouped_weight_gradient(dout, din):
     import torch
     rows = 512
-    asked = getattr(load_library(), "_ZN4tmps18dense_wgrad_groupsEilii")
-    asked.restype = C.c_bool
-    assert asked(BF16, C.c_long(rows), din, dout)
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(dout)
     dy, x = _normal(gen, rows, dout), _normal(gen, rows, din)
