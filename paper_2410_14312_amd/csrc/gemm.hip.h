@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace tmps {
 
 typedef __bf16 bf16_t;
@@ -120,9 +122,11 @@ struct NoRow8 {};
 // Forms of an epilogue.  What an epilogue does hangs on arguments that are the same for a whole launch (an activation, a mask, a second result); asked for
 // at every 8 elements, those questions are branches and moves that a kernel with a wave or two to a SIMD waits for.  E::form() names the combination (below 0:
 // none of those that have an instance of their own); EpiForm is E for one of them, with the elements at `base` (the same for the wave) + `off` (of
-// the lane): a store then takes a scalar base and a 32-bit offset.
+// the lane): a load takes a scalar base and a 32-bit offset, a store one addition in the vector unit.  (Bytes are counted on the pointer: behind a cast to an integer and back the compiler
+// no longer knows that it points to global memory and takes generic accesses, which count as LDS accesses too, so that it waits for all of both.)
 template <class T> __device__ __forceinline__ T* at_lane(T* p, int64_t base, uint32_t off) {
-    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p + base) + (uint32_t)(off * (uint32_t)sizeof(T)));
+    typedef std::conditional_t<std::is_const<T>::value, const char, char> byte_t;
+    return reinterpret_cast<T*>(reinterpret_cast<byte_t*>(p + base) + (uint32_t)(off * (uint32_t)sizeof(T)));
 }
 constexpr int64_t kFormMaxLd = 1 << 22;   // 128 rows of fp32 are then less than 2^32 bytes
 template <class E, int F> struct EpiForm : E {

@@ -159,3 +159,16 @@ def test_tiled_gemm_loops_never_wait_for_all_their_loads(isa):
                 checked += 1
             name = None
     assert checked >= 12, checked
+
+
+def test_no_access_is_generic(isa):
+    # A generic load or store (flat_*) counts on the vector-memory and on the LDS counter and may complete out of order with either: around one the compiler can only wait
+    # for everything, fragment reads and result stores among it.  Every pointer of these kernels is known to be global or LDS.
+    name, found = None, {}
+    for l in isa:
+        m = re.match(r"^(_Z\w+):", l)
+        if m:
+            name = m.group(1)
+        elif re.match(r"\s+flat_", l):
+            found[name] = found.get(name, 0) + 1
+    assert not found, found
