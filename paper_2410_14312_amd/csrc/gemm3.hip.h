@@ -497,7 +497,10 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         // each copy and its address in 64-bit registers, 1500 as it is (multiplies 1024); 8192 x 768 over 3072 51 -> 43 us, 8192^3 in 256 x 256 tiles 874 -> 814 us.
         auto k_tile = [&](int kt, auto fill, auto last) {
             constexpr bool FILL = decltype(fill)::value, LAST = decltype(last)::value;
+            // (comments in the instruction stream, by which tests/test_gemm3_isa.py finds the three forms)
             if constexpr (FILL) asm volatile("; tmps k-tile begin");
+            else if constexpr (LAST) asm volatile("; tmps last k-tile begin");
+            else asm volatile("; tmps draining k-tile begin");
             const lds_t sa = smem + cstage * STAGE;
             const int nstage = cstage + 1 == NS ? 0 : cstage + 1;
             const lds_t sn = smem + nstage * STAGE;
@@ -561,6 +564,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
             else if (ahead > 0) --ahead;
             cstage = nstage;
             if constexpr (FILL) asm volatile("; tmps k-tile end");
+            else if constexpr (LAST) asm volatile("; tmps last k-tile end");
+            else asm volatile("; tmps draining k-tile end");
         };
         const int filled = min(PEEL ? nk - 1 : nk, left);
         int kt = 0;

@@ -3,7 +3,8 @@ works while the ONLY waits on the vector-memory counter inside a k-tile are the 
 The compiler inserts such waits of its own when it believes a register or an LDS location may still be the target of an
 operation in flight, and one of them at the head of the loop serialises copies and multiplies without changing any
 result, so no numerical test sees it.  This test compiles the kernels for gfx950 and reads the instruction stream of
-every instance between the kernel's k-tile markers: every `vmcnt` wait there must carry the kernel's own tag, nothing
+every instance between the kernel's markers of a k-tile in its three forms (in the loop that copies, in the loop that drains what is under way,
+and a unit's last one where that stands apart): every `vmcnt` wait there must carry the kernel's own tag, nothing
 may be spilled there, and every instance must show the copies, the transposing or 16-byte fragment reads and the MFMAs.
 """
 import os
@@ -40,8 +41,8 @@ def kernels(lines):
             name = None
 
 
-def k_tile_loop(body):
-    """The instructions of the loop over k-tiles: every basic block the compiler lists as part of the innermost loop
+def k_tile_loop(body, marker="; tmps k-tile begin"):
+    """The instructions of the loop over k-tiles (that copies, or the one with another marker): every basic block the compiler lists as part of the innermost loop
     that holds the kernel's k-tile marker (the blocks of a loop need not be contiguous, nor in program order)."""
     blocks, cur, child_of = [], None, {}   # (label, header of the depth-2 loop it belongs to or None, lines)
     for i, l in enumerate(body):
@@ -69,7 +70,7 @@ def k_tile_loop(body):
             blocks.append(cur)
         elif cur is not None:
             cur[2].append(l)
-    mine = [b for b in blocks if any("; tmps k-tile begin" in l for l in b[2])]
+    mine = [b for b in blocks if any(marker in l for l in b[2])]
     assert len(mine) == 1 and mine[0][1], "the k-tile marker sits in exactly one block of a depth-2 loop"
     head = mine[0][1]
     loop = [b for b in blocks if b[1] == head]
@@ -105,6 +106,29 @@ def test_k_loops_wait_only_where_the_kernel_says(isa):
         assert "ds_read_b128" in text or "ds_read_b64_tr_b16" in text, name
         seen += 1
     assert seen >= 6, "expected the forward, input-gradient, partial-sum, weight-gradient, convolution and narrow instances"
+
+
+def test_k_tiles_that_copy_nothing_wait_only_where_the_kernel_says(isa):
+    # The other two forms of a k-tile: of the loop that drains the pipeline at a workgroup's end, and of a unit's last one where that stands apart (weight gradients).
+    draining = last = 0
+    for name, body in kernels(isa):
+        forms = [k_tile_loop(body, "; tmps draining k-tile begin")[0]]
+        draining += 1
+        begin, end = ([i for i, l in enumerate(body) if "; tmps last k-tile %s" % w in l] for w in ("begin", "end"))
+        if begin:
+            assert len(begin) == len(end) == 1 and begin < end, name
+            forms.append(body[begin[0]:end[0]])
+            last += 1
+        for tile in forms:
+            text = "\n".join(tile)
+            waits = [l.strip() for l in tile if "vmcnt" in l]
+            foreign = [w for w in waits if "; tmps" not in w]
+            assert not foreign, "%s: compiler-inserted waits on the copy counter: %s" % (name, foreign)
+            assert 1 <= len(waits) <= 2, (name, waits)
+            assert "scratch_" not in text and "global_load" not in text and text.count("s_barrier") == 1, name
+            n_mfma = text.count("v_mfma_f32_32x32x16_bf16")
+            assert n_mfma == 32 or (begin and n_mfma == 31), (name, n_mfma)   # (the last k-tile's first multiply may stand in front of the marker)
+    assert draining >= 6 and last >= 3, (draining, last)
 
 
 def innermost_mfma_loop(body):
@@ -172,3 +196,6 @@ def test_no_access_is_generic(isa):
         elif re.match(r"\s+flat_", l):
             found[name] = found.get(name, 0) + 1
     assert not found, found
+    for name, body in kernels(isa):   # at most one wait for all fragments requested in each of a k-tile's four steps (8 beside generic stores)
+        waits = sum("lgkmcnt(0)" in l for l in k_tile_loop(body)[0])
+        assert 1 <= waits <= 4, (name, waits)
