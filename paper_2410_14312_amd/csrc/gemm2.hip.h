@@ -1107,7 +1107,6 @@ struct EpiPartial {
     }
     static constexpr bool kFormed = false;
     static constexpr int kForms = 1;
-    int form() const { return ld > kFormMaxLd ? -1 : 0; }
     template <int> static __device__ __host__ NoRow8 raw8f() { return NoRow8{}; }
     template <int> __device__ __forceinline__ NoRow8 request8f(int64_t, uint32_t) const { return NoRow8{}; }
     template <int> __device__ __forceinline__ void finish8f(const Col8&, const NoRow8&, int64_t base, uint32_t off, float (&v)[8], int z) const {

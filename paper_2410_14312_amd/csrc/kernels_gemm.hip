@@ -445,9 +445,11 @@ static hipError_t launch3_inst(int kc, const G3Operand<AKC>& A, const G3Operand<
         if constexpr (WM * WN > 4 && AKC && BKC) return hipErrorInvalidValue;   // (g3_forward_takes)
         else return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM, true>(kc, A, B, epi, M, N, K, plan, s);
     }
-    return with_form(epi.form(), epi, [&](const auto& e) {
-        return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM, false>(kc, A, B, e, M, N, K, plan, s);
-    });
+    if constexpr (Epi::kFormed) return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM, false>(kc, A, B, epi, M, N, K, plan, s);
+    else
+        return with_form(epi.form(), epi, [&](const auto& e) {
+            return launch3_form<BM, BN, WM, WN, NS, PER_CU, AKC, BKC, ROWSUM, false>(kc, A, B, e, M, N, K, plan, s);
+        });
 }
 
 template <bool AKC, bool BKC, bool ROWSUM, class Epi>
@@ -672,7 +674,7 @@ static hipError_t dense_dgrad_as(int kc, int dtype, const void* dy, const void* 
             G3Operand<true> A{(const bf16_t*)dy, B, Dout};
             G3Operand<false> Bv{(const bf16_t*)w, Din, Din};
             const G3Plan plan = g3_plan(B, Din, Dout, s3);
-            EpiPartial part{ws, Din, (int64_t)B * Din};
+            const EpiForm<EpiPartial, 0> part{EpiPartial{ws, Din, (int64_t)B * Din}};   // (fewer than 192 tiles: rows are far shorter than kFormMaxLd)
             hipError_t e = launch3<true, false, false>(kc, A, Bv, part, B, Din, Dout, plan, s);
             if (e != hipSuccess) return e;
             return launch_timed(kcSplitFinish, splitk_finish8_kernel<EpiMask<bf16_t, bf16_t>, SameRows>, dim3(cdiv((int64_t)B * Din / 8, 256)),
