@@ -129,6 +129,10 @@ template <class T> __device__ __forceinline__ T* at_lane(T* p, int64_t base, uin
     return reinterpret_cast<T*>(reinterpret_cast<byte_t*>(p + base) + (uint32_t)(off * (uint32_t)sizeof(T)));
 }
 constexpr int64_t kFormMaxLd = 1 << 22;   // 128 rows of fp32 are then less than 2^32 bytes
+// The forms of the epilogues below by what they are given.
+int bias_act_form(int act, bool bias, bool res, bool second, int64_t ld);
+int conv_affine_form(bool bias, bool again, bool res, bool relu, int64_t ld);
+int mask_form(int mode, bool mask, bool add, int64_t ld);
 template <class E, int F> struct EpiForm : E {
     static constexpr bool kFormed = true;
     typedef decltype(E::template raw8f<F>()) Row8;
@@ -216,11 +220,7 @@ template <typename TOut> struct EpiBiasAct {
     // 0: bias only, 1: ReLU, 2: GELU and its derivative, 3: a residual source
     static constexpr bool kFormed = false;
     static constexpr int kForms = sizeof(TOut) == 2 ? 4 : 1;
-    int form() const {
-        if (!bias || ld > kFormMaxLd) return -1;
-        if (relu == kActGelu) return zout && !res ? 2 : -1;
-        return zout ? -1 : relu == kActRelu ? (res ? -1 : 1) : (res ? 3 : 0);
-    }
+    int form() const { return bias_act_form(relu, bias, res, zout, ld); }
     template <int F> static __device__ __host__ auto raw8f() {
         if constexpr (F == 3) return Row8{};
         else return NoRow8{};
@@ -324,7 +324,7 @@ template <typename TOut> struct EpiConvAffine {
     // without a bias and a second copy: 0 the layers alone, 1 with ReLU, 2 with a residual source and ReLU
     static constexpr bool kFormed = false;
     static constexpr int kForms = sizeof(TOut) == 2 ? 3 : 0;
-    int form() const { return bias || again || ld > kFormMaxLd ? -1 : res ? (relu ? 2 : -1) : relu ? 1 : 0; }
+    int form() const { return conv_affine_form(bias, again, res, relu, ld); }
     template <int F> static __device__ __host__ auto raw8f() {
         if constexpr (F == 2) return Row8{};
         else return NoRow8{};
@@ -407,11 +407,7 @@ template <typename TOut, typename TMask> struct EpiMask {
     // 0: no mask, 1: ReLU's, 2: GELU's, 3: what others have contributed and ReLU's
     static constexpr bool kFormed = false;
     static constexpr int kForms = sizeof(TOut) == 2 && sizeof(TMask) == 2 ? 4 : 0;
-    int form() const {
-        if (ld > kFormMaxLd) return -1;
-        if (add) return mask && mode == kActRelu ? 3 : -1;
-        return !mask ? 0 : mode == kActGelu ? 2 : 1;
-    }
+    int form() const { return mask_form(mode, mask, add, ld); }
     struct Mask8 { Raw8<TMask> t; };
     template <int F> static __device__ __host__ auto raw8f() {
         if constexpr (F == 3) return Row8{};

@@ -318,6 +318,21 @@ hipError_t reduce_all(const Reductions& list, hipStream_t s) {
     return hipSuccess;
 }
 
+// ---- forms of the dense epilogues ------------------------------------------------------------------------
+int bias_act_form(int act, bool bias, bool res, bool second, int64_t ld) {
+    if (!bias || ld > kFormMaxLd) return -1;
+    if (act == kActGelu) return second && !res ? 2 : -1;
+    return second ? -1 : act == kActRelu ? (res ? -1 : 1) : (res ? 3 : 0);
+}
+int conv_affine_form(bool bias, bool again, bool res, bool relu, int64_t ld) {
+    return bias || again || ld > kFormMaxLd ? -1 : res ? (relu ? 2 : -1) : relu ? 1 : 0;
+}
+int mask_form(int mode, bool mask, bool add, int64_t ld) {
+    if (ld > kFormMaxLd) return -1;
+    if (add) return mask && mode == kActRelu ? 3 : -1;
+    return !mask ? 0 : mode == kActGelu ? 2 : 1;
+}
+
 // ---- persistent MFMA path (gemm3.hip.h): large dense contractions --------------------------------------
 static int compute_units() {
     static int n = [] {

@@ -1,6 +1,7 @@
-"""Epilogues of the persistent kernel and of those with asynchronous copies whose arguments make them an instance of their own (bias alone, ReLU, GELU and its derivative, a residual source; masks
-of both activations, with and without what others have contributed), on tiles that the output's last rows and columns leave partly empty, in both tile sizes, over
-as few k-tiles as the kernel takes; beside them combinations that keep the general epilogue.  Against the oracle."""
+"""Epilogues of the persistent kernel and of those with asynchronous copies whose arguments make them an instance of their own, as stages pass them (bias alone, ReLU, GELU and its derivative, a
+residual source; masks of both activations), on tiles that the output's last rows and columns leave partly empty, in both tile sizes, over
+as few k-tiles as the kernel takes; beside them combinations that keep the general epilogue.  Against the oracle.  (Every combination of arguments, over
+several units of a workgroup: tests/test_gpu_epilogue_arguments.py.)"""
 import pytest
 
 from tests import routes
@@ -27,10 +28,16 @@ CASES = [
 KERNELS = {WIDE: "persistent", 4200: "persistent narrow", 1000: "async", 760: "by_k"}
 
 
+MASKS = [   # the kernel of the input gradient of each dense layer that reads another's result
+    ["persistent"], ["persistent"], ["persistent"], ["persistent", "tiled", "persistent"], [], [], ["persistent narrow"], ["persistent narrow"] * 3,
+    ["async"], ["by_k", "async", "joint small"], ["joint small"]]
+
+
 def test_cases_reach_their_kernels():
-    for layers, rows in CASES:
-        wide = max((l for l in layers if l["kind"] == "linear"), key=lambda l: l["dout"])
-        assert routes.dense_routes(wide, "bf16", rows, 1)[0] == KERNELS[rows]
+    for (layers, rows), masks in zip(CASES, MASKS):
+        dense = [l for l in layers if l["kind"] == "linear"]
+        assert routes.dense_routes(max(dense, key=lambda l: l["dout"]), "bf16", rows, 1)[0] == KERNELS[rows]
+        assert [routes.dense_routes(l, "bf16", rows, 1)[1] for l in dense if l is not layers[0]] == masks
 
 
 @pytest.mark.gpu

@@ -7,6 +7,7 @@ import pytest
 
 from paper_2410_14312_amd import load_library
 from tests import routes
+from tests.util import call_internal
 
 BF16 = 1
 
@@ -20,14 +21,6 @@ def test_launches_with_long_rows_keep_whole_addresses(k_contiguous, rows):
     for ld in (64, 768, limit - 8, limit, limit + 8, limit + 16, 2 ** 26, 2 ** 30):
         # (the last chunk's last byte; offsets in a lane are formed modulo 2^32)
         assert f(k_contiguous, rows, ld) == (((lines - 1) * ld + across) * 2 - 1 < 2 ** 32), ld
-
-
-def _call(name, *args):
-    import torch
-    f = getattr(load_library(), name)
-    f.restype = C.c_int
-    conv = [C.c_void_p(a.data_ptr()) if torch.is_tensor(a) else C.c_void_p() if a is None else a for a in args]
-    assert f(*conv, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
 
 
 def _normal(gen, *shape):
@@ -80,7 +73,7 @@ def test_weight_gradient(dout, din):
     dy, x = _normal(gen, rows, dout), _normal(gen, rows, din)
     gw = torch.zeros(dout * din + dout, device="cuda:0")
     none = _Partials()
-    _call("_ZN4tmps11dense_wgradEiPKvS1_PfiiiRKNS_8PartialsEP12ihipStream_t", BF16, dy, x, gw, rows, din, dout, C.byref(none))
+    call_internal("_ZN4tmps11dense_wgradEiPKvS1_PfiiiRKNS_8PartialsEP12ihipStream_t", BF16, dy, x, gw, rows, din, dout, C.byref(none))
     _check_wgrad(gw, dy, x)
 
 
@@ -104,7 +97,7 @@ def test_grouped_weight_gradient(dout, din):
     dy, x = _normal(gen, rows, dout), _normal(gen, rows, din)
     gw = torch.zeros(dout * din + dout, device="cuda:0")
     job = _Job(dy.data_ptr(), x.data_ptr(), gw.data_ptr(), din, dout)
-    _call("_ZN4tmps17dense_wgrad_groupEiPKNS_13DenseWgradJobEilPflP12ihipStream_t", BF16, C.byref(job), 1, C.c_long(rows), None, C.c_long(0))
+    call_internal("_ZN4tmps17dense_wgrad_groupEiPKNS_13DenseWgradJobEilPflP12ihipStream_t", BF16, C.byref(job), 1, C.c_long(rows), None, C.c_long(0))
     _check_wgrad(gw, dy, x)
 
 
@@ -134,10 +127,10 @@ def test_long_contractions():
 
     w = b.view(N, K)
     bias = torch.zeros(N, device="cuda:0")
-    _call("_ZN4tmps13dense_forwardEiPKvS1_PKfPviiiiiS1_S4_PfP12ihipStream_t", BF16, a, w, bias, out, M, K, N, 0, 0, None, None, None)
+    call_internal("_ZN4tmps13dense_forwardEiPKvS1_PKfPviiiiiS1_S4_PfP12ihipStream_t", BF16, a, w, bias, out, M, K, N, 0, 0, None, None, None)
     check(lambda k, n: w[:, k:k + n].t())
     w = b.view(K, N)
     for ws in (None, torch.empty((slices + 1) * M * N, device="cuda:0")):
         out.zero_()
-        _call("_ZN4tmps11dense_dgradEiPKvS1_PvS1_iS1_iiiPfP12ihipStream_t", BF16, a, w, out, None, 0, None, M, N, K, ws)
+        call_internal("_ZN4tmps11dense_dgradEiPKvS1_PvS1_iS1_iiiPfP12ihipStream_t", BF16, a, w, out, None, 0, None, M, N, K, ws)
         check(lambda k, n: w[k:k + n])

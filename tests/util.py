@@ -1,4 +1,6 @@
 """Helpers shared by the tests: error norms and a stage-level oracle/HIP comparison harness."""
+import ctypes as C
+
 import numpy as np
 
 
@@ -26,3 +28,14 @@ def frac_outside(got, ref, tol):
 
 
 TOL = {"f32": 1e-4, "bf16": 2e-2}
+
+
+def call_internal(name, *args):
+    """Calls a launcher of the library that its own stages call (the symbol's name) on torch's stream: tensors and None are passed as pointers, the rest as it is."""
+    import torch
+    from paper_2410_14312_amd import load_library
+
+    f = getattr(load_library(), name)
+    f.restype = C.c_int
+    passed = [C.c_void_p(a.data_ptr()) if torch.is_tensor(a) else C.c_void_p() if a is None else a for a in args]
+    assert f(*passed, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0, name
