@@ -48,7 +48,7 @@ class _Tensors:
         self.gen.manual_seed(seed)
 
     def normal(self, *shape, scale=1.0, dtype=None):
-        t = self.torch.empty(*shape, device="cuda:0").normal_(generator=self.gen) * scale
+        t = self.torch.empty(*shape, dtype=self.torch.float32, device="cuda:0").normal_(generator=self.gen) * scale
         return t.to(dtype or self.torch.bfloat16)
 
     def result(self, M, N, dtype=None):

@@ -71,7 +71,7 @@ def test_weight_gradient(dout, din):
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(dout)
     dy, x = _normal(gen, rows, dout), _normal(gen, rows, din)
-    gw = torch.zeros(dout * din + dout, device="cuda:0")
+    gw = torch.zeros(dout * din + dout, dtype=torch.float32, device="cuda:0")
     none = _Partials()
     call_internal("_ZN4tmps11dense_wgradEiPKvS1_PfiiiRKNS_8PartialsEP12ihipStream_t", BF16, dy, x, gw, rows, din, dout, C.byref(none))
     _check_wgrad(gw, dy, x)
@@ -95,7 +95,7 @@ def test_grouped_weight_gradient(dout, din):
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(dout)
     dy, x = _normal(gen, rows, dout), _normal(gen, rows, din)
-    gw = torch.zeros(dout * din + dout, device="cuda:0")
+    gw = torch.zeros(dout * din + dout, dtype=torch.float32, device="cuda:0")
     job = _Job(dy.data_ptr(), x.data_ptr(), gw.data_ptr(), din, dout)
     call_internal("_ZN4tmps17dense_wgrad_groupEiPKNS_13DenseWgradJobEilPflP12ihipStream_t", BF16, C.byref(job), 1, C.c_long(rows), None, C.c_long(0))
     _check_wgrad(gw, dy, x)
@@ -117,7 +117,7 @@ def test_long_contractions():
     out = torch.empty(M, N, dtype=torch.bfloat16, device="cuda:0")
 
     def check(right):   # right(k, n): the other operand's rows k .. k + n, [n, N]
-        ref = torch.zeros(M, N, device="cuda:0")
+        ref = torch.zeros(M, N, dtype=torch.float32, device="cuda:0")
         for k in range(0, K, 1 << 18):
             n = min(1 << 18, K - k)
             ref += a[:, k:k + n].float() @ right(k, n).float()
@@ -126,11 +126,11 @@ def test_long_contractions():
         assert err.max().item() < 1.0, err.max().item()
 
     w = b.view(N, K)
-    bias = torch.zeros(N, device="cuda:0")
+    bias = torch.zeros(N, dtype=torch.float32, device="cuda:0")
     call_internal("_ZN4tmps13dense_forwardEiPKvS1_PKfPviiiiiS1_S4_PfP12ihipStream_t", BF16, a, w, bias, out, M, K, N, 0, 0, None, None, None)
     check(lambda k, n: w[:, k:k + n].t())
     w = b.view(K, N)
-    for ws in (None, torch.empty((slices + 1) * M * N, device="cuda:0")):
+    for ws in (None, torch.empty((slices + 1) * M * N, dtype=torch.float32, device="cuda:0")):
         out.zero_()
         call_internal("_ZN4tmps11dense_dgradEiPKvS1_PvS1_iS1_iiiPfP12ihipStream_t", BF16, a, w, out, None, 0, None, M, N, K, ws)
         check(lambda k, n: w[k:k + n])

@@ -37,5 +37,6 @@ def call_internal(name, *args):
 
     f = getattr(load_library(), name)
     f.restype = C.c_int
+    assert not any(torch.is_tensor(a) and a.dtype == torch.float64 for a in args), "no launcher takes doubles (the default type of some processes)"
     passed = [C.c_void_p(a.data_ptr()) if torch.is_tensor(a) else C.c_void_p() if a is None else a for a in args]
     assert f(*passed, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0, name
