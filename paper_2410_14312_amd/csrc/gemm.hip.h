@@ -217,7 +217,8 @@ template <typename TOut> struct EpiBiasAct {
         store8(out + idx, v);
         if (relu != kActGelu && zout) store8(zout + idx, v);
     }
-    // 0: bias only, 1: ReLU, 2: GELU and its derivative, 3: a residual source
+    // 0: bias only, 1: ReLU, 2: GELU and its derivative, 3: a residual source.  (The last layer of a stage, whose result leaves twice, keeps the general
+    // epilogue, with a residual source or without; an instance of its own for it has not been measured.)
     static constexpr bool kFormed = false;
     static constexpr int kForms = sizeof(TOut) == 2 ? 4 : 1;
     int form() const { return bias_act_form(relu, bias, res, zout, ld); }
@@ -321,7 +322,7 @@ template <typename TOut> struct EpiConvAffine {
         store8(yout + idx, v);
         if (again) store8(again + idx, v);
     }
-    // without a bias and a second copy: 0 the layers alone, 1 with ReLU, 2 with a residual source and ReLU
+    // without a bias and a second copy (not measured as instances of their own): 0 the layers alone, 1 with ReLU, 2 with a residual source and ReLU
     static constexpr bool kFormed = false;
     static constexpr int kForms = sizeof(TOut) == 2 ? 3 : 0;
     int form() const { return conv_affine_form(bias, again, res, relu, ld); }

@@ -22,8 +22,10 @@
 // a store instruction covers whole 128-byte lines.  Copies and stores are counted by the same counter, in order: before a unit's first store the
 // wave waits for its copies in flight, which have had the last multiplies to arrive in, and then need not wait again for NS - 1 k-tiles, in which
 // the stores drain.
-// What bounds it, by the device clock of each workgroup: 8192 x 768 over 3072 38 us, of which 2 are the first copies, 35 the k-loop, 3 the results; over 768 9 of 14.
-// The results took 4.5 us (6.6 the first time, when their code is fetched) as long as they asked at each 8 elements what to do with them (see EpiForm): 8192 x 768
+// What bounds it, by the device clock of each workgroup (us): a unit of 256 x 128 over 3072 (8192 x 768, 41 a launch) waits 1.9 for its first copies, 34.3 are the
+// k-loop, 0.4 the wait for the last ones under way, 2.3 the results; over 768 (16 a launch) 1.7, 8.6, 0.4 and 2.3.  A unit of 256 x 256 over 768 (8192 x 3072, 50 a
+// launch): 1.7, 18.5, 0.6 and 3.0, with GELU and its derivative 7.9, with GELU's mask 5.8 and 4.3 (the first unit's code is fetched), and between units 0.2.
+// The results took 4.5 us (6.6 the first time) as long as they asked at each 8 elements what to do with them (see EpiForm): 8192 x 768
 // over 2304 37.7 -> 35.0 us, 8192 x 3072 over 768 with GELU's mask in GPT-2's stage 66 -> 61.
 #pragma once
 #include <type_traits>
@@ -469,8 +471,9 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }
-        // The unit's first fragments.  (Its first k-tile is there since the barrier of the last unit's last one; requested then already, they would
-        // take registers that the results need on their way out.)
+        // The unit's first fragments.  (Its first k-tile is there since the barrier of the last unit's last one; requested then already and kept, they would
+        // take registers that the results need on their way out.  Without PEEL that k-tile requests them all the same, as every k-tile does the next one's, and they
+        // are dropped: of a unit of 12 k-tiles 2 % of the LDS reads with eight waves and 4 % with four.)
         {
             const lds_t sa = smem + cstage * STAGE;
 #pragma unroll
@@ -494,7 +497,8 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
         // copied.  The two forms are loops of their own, and the
         // one that is walked nearly always has no branch in it: with a wave or two to a SIMD every branch, every address that is put together and every
         // pointer that is stepped between two multiplies delays the next one.  256 x 128 tiles, four waves: 1830 cycles a k-tile with a test before
-        // each copy and its address in 64-bit registers, 1500 as it is (multiplies 1024); 8192 x 768 over 3072 51 -> 43 us, 8192^3 in 256 x 256 tiles 874 -> 814 us.
+        // each copy and its address in 64-bit registers, 1500 as it is (multiplies 1024); 8192 x 768 over 3072 forward 51 -> 41 us, input gradient 52 -> 43, 8192^3 in 256 x 256
+        // tiles 874 -> 807 us (with the exchanged operands and the third stage; on another machine 41, 40 and 850 now).
         auto k_tile = [&](int kt, auto fill, auto last) {
             constexpr bool FILL = decltype(fill)::value, LAST = decltype(last)::value;
             // (comments in the instruction stream, by which tests/test_gemm3_isa.py finds the three forms)
@@ -510,8 +514,9 @@ __device__ __forceinline__ void gemm3_walk(const Work& work) {
                 if constexpr (nx == KK) {
                     // Every fragment of this k-tile has been requested.  The next k-tile is the oldest copy in
                     // flight: copies complete in issue order, so it has landed once at most (ahead - 1) * G younger
-                    // copies are outstanding.  Result stores of an earlier unit are younger than it too and only
-                    // make the wait stricter.  While the pipeline drains (ahead < NS - 1) wait for everything.
+                    // copies are outstanding.  While the pipeline drains (ahead < NS - 1) wait for everything.
+                    // A unit's first `quiet` k-tiles wait for nothing: what comes next was waited for in front of the last unit's first store.  The k-tile that is
+                    // waited for first was copied behind those stores, so this wait is for them as well; they have had `quiet` k-tiles to drain in.
                     if (kt >= quiet) {
                         if (FILL || ahead == NS - 1) wait_vmcnt<(NS - 2) * G>();
                         else wait_vmcnt<0>();
@@ -725,7 +730,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm3_kernel(G3Operand<AKC> A, G
 // many multiplies: 12 layers of 768 features over 8192 rows 450 us instead of 356.  Totals in memory instead were estimated at the same.
 //
 // The four layers of a transformer block of 768 features over 8192 / 1024 rows, one block, two, three, four (us, launches of their own and one):
-// 199 and 159, 413 and 316, 623 and 450, 828 and 580 / 52 and 32, 105 and 59, 157 and 84, 214 and 114; 20 of 1024 x 1024 over 1024 rows 195 and 89.
+// 192 and 142, 394 and 309, 595 and 448, 792 and 590 / 55 and 31, 109 and 54, 161 and 78, 215 and 107; 20 of 1024 x 1024 over 1024 rows 218 and 82.
 constexpr int kG3GroupMax = 32;   // contractions of a launch (kernel arguments hold 4 KB)
 struct G3Job {
     const bf16_t* a;   // dY [K][M]

@@ -346,8 +346,11 @@ static int compute_units() {
 
 constexpr int kG3Tile = 256;
 static int64_t g3_tiles(int64_t M, int64_t N) { return (int64_t)cdiv(M, kG3Tile) * cdiv(N, kG3Tile); }
-// k-slices of a weight-gradient contraction on the persistent path (0: leave it to the other path).  Measured:
-// the path pays once a launch has about as many (tile, slice) units as the device has compute units.
+// k-slices of a weight-gradient contraction on the persistent path (0: leave it to the other path).  Measured in whole runs:
+// the path pays once a launch has about as many (tile, slice) units as the device has compute units.  Alone on the device (us, persistent and other kernels, with the
+// sums of their slices): 4096 x 4096 over 1024 / 4096 rows 42 and 57 / 122 and 174, 4096 x 2048 over 4096 85 and 90, 3072 x 768 over 8192 58 and 67; but also 3072 x 3072, 144 units, which
+// the line leaves to the others, over 1024 / 4096 32 and 38 / 89 and 123, and 2048 x 2048 over 4096, 4096 x 2048 over 2048 and 2048 x 1024 over 8192, 256 units each, which
+// it does not, 56 and 43, 58 and 49, 56 and 49.
 int g3_wgrad_slices(int64_t M, int64_t N, int64_t K) {
     if (K % 64 != 0 || M % 8 != 0 || N % 8 != 0) return 0;
     const int64_t tiles = g3_tiles(M, N);
@@ -358,7 +361,9 @@ int g3_wgrad_slices(int64_t M, int64_t N, int64_t K) {
 }
 // Not for a contraction of a single k-tile, which is all epilogue (many small workgroups keep more memory requests in
 // flight than one persistent workgroup per compute unit), nor when more than a quarter of the 256-wide tiles would be
-// padding (measured on the 1x1 convolutions of the residual networks).
+// padding (measured on the 1x1 convolutions of the residual networks).  192 tiles: swept in whole runs from 128 to 450, which changed nothing, when a k-tile took a fifth longer.  Alone on
+// the device now (us, persistent and other kernels), 1024 columns over 256 / 768 / 3072: 256 tiles 16 and 22 / 28 and 40 / 87 and 124, 192 tiles 14 and 18 / 24 and 30 / 71 and 94; also
+// 176, 160 and 144 tiles, which the line leaves to the others, 14 and 18 / 23 and 29 / 62 to 67 and 89, and only 128 no longer, 14 and 13 / 22 and 22 / 64 and 64.
 bool g3_forward_ok(int64_t M, int64_t N, int64_t K) {
     return K % 64 == 0 && K >= 128 && N % 8 == 0 && g3_tiles(M, N) >= 192 && (int64_t)cdiv(N, 256) * 256 * 3 <= N * 4;
 }
@@ -366,10 +371,11 @@ bool g3_forward_ok(int64_t M, int64_t N, int64_t K) {
 // A tall, narrow output (the 8192 x 768 input gradients of a transformer block: 96 tiles of 256 x 256, which leave most
 // of the device idle) goes to the persistent kernel in 256 x 128 tiles with four waves of 128 x 64 each, where every unit has a
 // compute unit to itself, the same output in 128 x 128 tiles would not (then the kernel with asynchronous copies walks it in
-// one round: 256 tiles of 4096 x 1024, contraction 1024, 14 us against 21, 215 tiles of 640 x 5504 13 against 24), and a k-loop of at least 8
-// k-tiles carries the unit's prologue and epilogue.  Input gradients, persistent and other kernels (us), contractions over 512 /
-// 1024 / 2048 / 4096: 8448 x 512 (264 tiles of 128 x 128) 15.6 / 20.6 / 33 / 61 and 14.8 / 22 / 44 / 78, 16384 x 512 (512 tiles)
-// 17.9 / 24 / 40 / 69 and 16.3 / 25 / 47 / 81; the 8192 x 768 of a transformer block, over 2304 / 768 / 3072, 45 / 21 / 57 (now 35 / 17 / 44) and 52 / 23 / 67.
+// one round: 256 tiles of 4096 x 1024, contraction 1024, 14.5 us against 17.7, 215 tiles of 640 x 5504 13.5 against 17.6), and a k-loop of at least 8
+// k-tiles carries the unit's prologue and epilogue.  Input gradients alone on the device, persistent and other kernels (us), contractions over 512 /
+// 1024 / 2048 / 4096: 8448 x 512 (264 tiles of 128 x 128) 11.5 / 16.6 / 25 / 44 and 15.5 / 23 / 42 / 72, 16384 x 512 (512 tiles)
+// 14.3 / 21 / 35 / 62 and 18.1 / 28 / 47 / 87; the 8192 x 768 of a transformer block, over 2304 / 768 / 3072, 32 / 16 / 40 and 46 / 20 / 59.  (The 8 k-tiles are where both took
+// 15 to 18 us when the line was drawn; over 256, 8192 x 1024 takes 10.8 and 12.7 now.)
 bool g3_narrow_ok(int64_t M, int64_t N, int64_t K) {
     if (K % 64 != 0 || K < 512 || N % 128 != 0) return false;
     return (int64_t)cdiv(M, 256) * (N / 128) <= compute_units() && (int64_t)cdiv(M, 128) * (N / 128) > compute_units();
@@ -378,7 +384,9 @@ bool g3_narrow_ok(int64_t M, int64_t N, int64_t K) {
 // An output of few 256-wide tiles with a very long contraction (the input gradient of a vocabulary-wide output layer:
 // 96 tiles, k = 32000) goes to the persistent kernel in k-slices: the slice count is the one whose (tile, slice) units
 // fill whole rounds of the device best, weighed against the fp32 partial sums it writes and the finishing pass reads
-// (rates measured: 1 PFLOP/s in the k-loop, 5 TB/s for the partial sums).  0: leave it to the tiled kernel.
+// (rates: 1 PFLOP/s in the k-loop, 5 TB/s for the partial sums; the k-loop is at 1.2 to 1.3 now, which leaves the choice as it is).  Of 2 to 16 slices the choice is the quickest of those measured, alone on the device
+// (us, in brackets the slices; then the tiled kernel): 8192 x 768 over 32000 380 (5) and 459, 4096 x 768 187 (5) and 243, 8192 x 512 240 (4) and 305, 8192 x 1024 over 16384 238 (2) and 284,
+// 4096 x 2048 over 8192 130 (2) and 142, 4096 x 1024 76 (4) and 72.  0: leave it to the tiled kernel.
 int g3_long_k_slices(int64_t M, int64_t N, int64_t K) {
     if (K % 64 != 0 || N % 8 != 0 || K < 8192) return 0;
     const int64_t tiles = g3_tiles(M, N);
@@ -515,9 +523,12 @@ __global__ __launch_bounds__(256) void g3_group_sum_kernel(G3Group work) {
     }
 }
 
-// Estimates in us: 1.78 for a k-tile of a 256 x 256 tile (8192^3), 8 for a unit's prologue and epilogue, partial sums at 6 TB/s and a launch.
+// Estimates of weight gradients in us: 1.78 for a k-tile of a 256 x 256 tile (8192^3: 911 us for 512 of them in a row), 8 for a unit's prologue and epilogue, partial sums at 6 TB/s and a
+// launch.  Estimated and measured: 4096 x 4096 over 1024 / 2048 / 4096 / 8192 rows 36 and 42 / 65 and 69 / 122 and 122 / 236 and 233, 3072 x 768 over 8192 57 and 58, 2304 x 768 50 and 48.
 constexpr double kG3KtileUs = 1.78, kG3UnitUs = 8.0;
-// The same of a 256 x 128 tile of a group, and for adding its accumulators to the totals (12 layers of 768 features over 1024 to 8192 rows).
+// The same of a 256 x 128 tile of a group, and for adding its accumulators to the totals: 12 layers of 768 features over 1024 / 8192 rows 86 and 82 / 448 and 455.  What the estimates choose was
+// the quicker of one launch and several for 52 of 60 groups measured (one to four transformer blocks of 512 to 1280 features, one to twenty square layers of 768 to 4096, 1024 to 8192 rows); the other
+// eight keep launches of their own where one would be 6 to 25 % quicker: one block of 1024 features 61 and 53 us over 1024 rows, 95 and 79 over 2048.
 constexpr double kGroupKtileUs = 1.10, kGroupUnitUs = 9.0, kGroupTotalUs = 0.5;
 static double partial_sums_us(double slices, double elems) { return slices > 1 ? 3.0 + (slices + 1.0) * elems * 4.0 / 6e6 : 0.0; }
 
@@ -626,9 +637,10 @@ static hipError_t dense_forward_bf16(int kc, const bf16_t* x, const bf16_t* w, c
         G3Operand<true> Bv{w, Dout, Din};
         return launch3<true, true, false>(kc, A, Bv, epi, B, Dout, Din, g3_plan(B, Dout, Din, 1), s);
     }
-    // (from 1024 on.  Forward passes, persistent and other kernels (us), over 512 / 768 / 1024 / 2048 / 4096: 8192 x 768 16.4 / 19.0 / 22.0 /
-    // 35 / 59 and 15.7 / 19.7 / 22.9 / 39 / 70, 6144 x 768 15.3 / 18.6 / 21.1 / 34 / 58 and 15.0 / 19.2 / 22.6 / 37 / 69, 4096 x 1280
-    // 17.0 / - / 22.5 / 36 / 62 and 14.8 / - / 22.2 / 37 / 77)
+    // (from 1024 on, where the persistent kernel was the quicker one when the line was drawn: 8192 x 768 over 512 / 768 / 1024 16.4 / 19.0 / 22.0 us and 15.7 / 19.7 / 22.9.
+    // Forward passes alone on the device now, persistent and other kernels (us), over 512 / 768 / 1024 / 2048 / 4096: 8192 x 768 14.2 / 16.1 / 18.2 /
+    // 29 / 51 and 17.3 / 20.5 / 23.2 / 40 / 73, 6144 x 768 11.9 / 14.1 / 17.1 / 26 / 45 and 15.0 / 18.4 / 22.2 / 38 / 70, 4096 x 1280
+    // 12.9 / 15.8 / 17.5 / 27 / 47 and 15.0 / 19.0 / 22.3 / 39 / 70: 512 and 768 would be quicker there as well)
     if (aligned && Din >= 1024 && g3_narrow_ok(B, Dout, Din) && aligned16(x) && aligned16(w))
         return launch3_inst<256, 128, 2, 2, 3, 1, true, true, false>(kc, G3Operand<true>{x, B, Din}, G3Operand<true>{w, Dout, Din}, epi, B, Dout, Din,
                                                                      g3_plan(B, Dout, Din, 1, 256, 128), s);
